@@ -1040,3 +1040,20 @@ def test_binding_rejects_mistyped_and_short_buffers():
         gk.graphkv_select(p, s.double())
     with pytest.raises(gk.GraphKVError):
         gk.graphkv_score(p, Kd.cpu(), Qd)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("d,P", [(8, 1), (24, 63), (64, 257), (80, 64), (128, 1000), (200, 65), (512, 300)])
+def test_knorm_row_widths(oracle, d, P, dtype):
+    """Key norms for rows of 1 to 128 16-byte pieces (8 to 64 lanes share a row, pieces that do not
+    fill the lanes, rows of two turns) and row counts off the 64 rows of a wave.  The oracle sums in
+    64 bits; fp32 sums of d squares are within d * 2^-24 of it."""
+    say(f"knorm d={d} P={P} {dtype}")
+    H, w = 2, 3
+    rng = np.random.default_rng(d * 7 + P)
+    K = synth.to_storage(rng.standard_normal((H, P + w, d)).astype(np.float32), dtype)
+    dt = gk.FP32 if dtype == "fp32" else gk.BF16
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, dtype=dt)
+    got = gk.graphkv_score_knorm(p, gk.to_device(K, dt)).cpu().numpy().astype(np.float64)
+    ref = oracle.score_knorm(K, dtype, w)
+    assert np.all(np.abs(got - ref) <= (d + 4) * 2.0 ** -24 * np.abs(ref))
