@@ -121,7 +121,9 @@ bool budget_ok(const graphkv_params *p)
     return p->budget > p->window && p->budget <= p->n_tokens;
 }
 
-Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true)
+// `like`: the dimensions of the call's full launch group, whose routes a smaller last group takes
+// too (so that the workspace sized for the full group is enough).
+Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, const Dims *like = nullptr)
 {
     Dims D;
     D.L = n_layers;
@@ -138,7 +140,8 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true)
     D.T = p->rounds;
     D.mfma_score = mfma_score_ok(p);
     D.mfma_cosine = mfma_cosine_ok(p);
-    D.filter = D.mfma_cosine && D.T > 0 && mfma_filter_applies(D.P, D.m);
+    D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && mfma_filter_applies(D.P, D.m, (long)D.H * D.S);
+    if (like) speculate = like->speculate;
     // The neighbourhood of a source depends on the keys alone (Eq. 1, Eq. 3), not on the
     // scores: with re-picked sources the lists of returning sources are kept.
     D.speculate = speculate;
@@ -197,9 +200,9 @@ Workspace carve(const graphkv_params *p, const Dims &D)
 inline bool aligned16(const void *ptr) { return ptr && ((uintptr_t)ptr & 15u) == 0; }
 inline bool aligned4(const void *ptr) { return ptr && ((uintptr_t)ptr & 3u) == 0; }
 
-int32_t check_ws(const Workspace &W, const void *ws, size_t ws_bytes)
+int32_t check_ws(size_t need, const void *ws, size_t ws_bytes)
 {
-    if (!ws || ((uintptr_t)ws & (kAlign - 1)) || ws_bytes < W.total) return GRAPHKV_EWORKSPACE;
+    if (!ws || ((uintptr_t)ws & (kAlign - 1)) || ws_bytes < need) return GRAPHKV_EWORKSPACE;
     return GRAPHKV_OK;
 }
 
@@ -434,11 +437,11 @@ int32_t run_select(const Dims &D, const LayerPlan &plan, const float *scores, in
 }
 
 // The whole pass for a batch of n_layers contiguous layers (n_layers <= kMaxLayers).
-int32_t run_compress(const graphkv_params *p, int n_layers, bool speculate, const int32_t *budgets, const void *Kc,
+int32_t run_compress(const graphkv_params *p, int n_layers, const Dims &group, const int32_t *budgets, const void *Kc,
                      const void *Vc, const void *Qw, void *Kout, void *Vout, int32_t *idx,
                      float *scores_out, void *ws, hipStream_t st)
 {
-    const Dims D = dims_of(p, n_layers, speculate);
+    const Dims D = n_layers == group.L ? group : dims_of(p, n_layers, true, &group);
     const Workspace W = carve(p, D);
     int max_budget = 0;
     const LayerPlan plan = make_plan(p, n_layers, budgets, &max_budget);
@@ -482,6 +485,16 @@ Dims group_dims(const graphkv_params *p, int n_layers)
     return dims_of(p, 1, false);
 }
 
+// Scratch of a call: its full group's, or its smaller last group's should that need more.
+size_t scratch_bytes(const graphkv_params *p, int n_layers, const Dims &group)
+{
+    const size_t full = carve(p, group).total;
+    const int rest = n_layers % group.L;
+    if (rest == 0) return full;
+    const size_t last = carve(p, dims_of(p, rest, true, &group)).total;
+    return last > full ? last : full;
+}
+
 bool budgets_ok(const graphkv_params *p, int n_layers, const int32_t *budgets)
 {
     for (int l = 0; l < n_layers; ++l) {
@@ -517,7 +530,7 @@ int32_t graphkv_score(const graphkv_params *p, const void *Kc, const void *Qw, f
     q.scorer = GRAPHKV_SCORER_ATTENTION;
     const Dims D = group_dims(&q, 1);
     const Workspace W = carve(&q, D);
-    if (int32_t rc = check_ws(W, ws, ws_bytes)) return rc;
+    if (int32_t rc = check_ws(W.total, ws, ws_bytes)) return rc;
     return run_score(&q, D, W, Kc, Qw, scores, ws, (hipStream_t)stream);
 }
 
@@ -544,7 +557,7 @@ int32_t graphkv_propagate_edges(const graphkv_params *p, const void *Ac, const v
         return GRAPHKV_EINVAL;
     const Dims D = group_dims(p, 1);
     const Workspace W = carve(p, D);
-    if (int32_t rc = check_ws(W, ws, ws_bytes)) return rc;
+    if (int32_t rc = check_ws(W.total, ws, ws_bytes)) return rc;
     return run_propagate(p, D, W, Ac, Bc, scores, dbg_src, dbg_nbr, dbg_e, ws,
                          (hipStream_t)stream);
 }
@@ -591,7 +604,7 @@ int32_t graphkv_compress_static(const graphkv_params *p, const void *Kc, const v
 size_t graphkv_workspace_bytes_batched(const graphkv_params *p, int32_t n_layers)
 {
     if (!base_ok(p) || n_layers < 1) return 0;
-    return carve(p, group_dims(p, n_layers)).total;
+    return scratch_bytes(p, n_layers, group_dims(p, n_layers));
 }
 
 int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, const int32_t *budgets,
@@ -609,8 +622,7 @@ int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, cons
     if (scores_out && !aligned4(scores_out)) return GRAPHKV_EINVAL;
     const Dims DG = group_dims(p, n_layers);   // layers per group, and whether its filter passes speculate
     const int group = DG.L;
-    const Workspace W = carve(p, DG);
-    if (int32_t rc = check_ws(W, ws, ws_bytes)) return rc;
+    if (int32_t rc = check_ws(scratch_bytes(p, n_layers, DG), ws, ws_bytes)) return rc;
     hipStream_t st = (hipStream_t)stream;
     const size_t esize = p->dtype == GRAPHKV_FP32 ? 4 : 2;
     const size_t kv_layer = (size_t)p->n_kv_heads * p->n_tokens * p->head_dim * esize;
@@ -621,7 +633,7 @@ int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, cons
         const int nl = n_layers - l0 < group ? n_layers - l0 : group;
         const int32_t *bl = budgets ? budgets + l0 : nullptr;
         const int32_t rc = run_compress(
-            p, nl, DG.speculate, bl, (const char *)Kc + l0 * kv_layer, (const char *)Vc + l0 * kv_layer,
+            p, nl, DG, bl, (const char *)Kc + l0 * kv_layer, (const char *)Vc + l0 * kv_layer,
             Qw ? (const char *)Qw + l0 * q_layer : nullptr, (char *)Kout + out_rows * p->head_dim * esize,
             (char *)Vout + out_rows * p->head_dim * esize, idx + out_rows,
             scores_out ? scores_out + l0 * s_layer : nullptr, ws, st);

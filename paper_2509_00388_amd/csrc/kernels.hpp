@@ -100,7 +100,7 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
 hipError_t launch_mfma_cosine(const void *Ac, const void *Kc, int Hkv, int N, int P, int S, const int32_t *src,
                               float *E, const int32_t *gate, hipStream_t st);
 // Neighbourhoods without the dense block (see mfma_cosine.hip):
-bool mfma_filter_applies(int P, int m);
+bool mfma_filter_applies(int P, int m, long rows);   // rows: heads x sources of the launch
 int mfma_sample_cols(int P);          // keys in the strided sample
 int mfma_bound_rank(int m, int stride);   // rank in the sample at which a row's bound is taken (<= m)
 int mfma_cand_cap(int P, int m);      // candidates per source the exact select can take

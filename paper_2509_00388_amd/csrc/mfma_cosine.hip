@@ -1150,12 +1150,19 @@ int mfma_cand_cap(int P, int m)
     return (int)cap;
 }
 
-bool mfma_filter_applies(int P, int m)
+// `rows`: source rows of the whole launch (heads x sources).  Short prompts (2048 <= P < 8192) take
+// the filter route when their edge block would be large, from 2^23 edges (32 MiB) on: the dense
+// route writes and re-reads the block, the filter route costs two more launches.  Measured (one round,
+// us, dense / filter): 8 heads x 128 sources x 4064 keys (4 M edges) 117 / 119, 16 x 128 x 2968
+// (6 M) 120 / 123, 32 x 64 x 4064 (8 M) 105 / 100, 64 x 64 x 2068 (8 M) 100 / 97, 64 x 64 x 7968
+// (33 M) 299 / 150, 256 x 64 x 7968 (131 M) 1055 / 382.
+bool mfma_filter_applies(int P, int m, long rows)
 {
     // The sample must hold far more than m keys for its m-th largest edge to be a
     // useful bound, the key index must fit the 24 bits of a staged candidate, and
     // the select kernel's LDS must hold a full list.
-    if (P < 8192 || P >= (1 << 24)) return false;
+    if (P < 2048 || P >= (1 << 24)) return false;
+    if (P < 8192 && rows * P < (8L << 20)) return false;
     if (m > mfma_sample_cols(P) / 8) return false;
     return (size_t)mfma_cand_cap(P, m) * 8 + (size_t)m * 8 + 8 <= 140 * 1024;
 }

@@ -986,7 +986,7 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
                                int32_t *ext, hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;
-    if (n <= 4096 || S + X > kSmallK) return hipErrorInvalidValue;
+    if (S + X > n || S + X > kSmallK) return hipErrorInvalidValue;
     if (n <= 32768)
         hipLaunchKernelGGL(pick_sources_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, S + X, S, src,
                            (long)S, ext, (long)(S + X));

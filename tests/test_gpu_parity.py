@@ -1057,3 +1057,26 @@ def test_knorm_row_widths(oracle, d, P, dtype):
     got = gk.graphkv_score_knorm(p, gk.to_device(K, dt)).cpu().numpy().astype(np.float64)
     ref = oracle.score_knorm(K, dtype, w)
     assert np.all(np.abs(got - ref) <= (d + 4) * 2.0 ** -24 * np.abs(ref))
+
+
+@pytest.mark.parametrize("L,n_tokens,S,m,rounds", [(66, 2080, 128, 9, 2), (16, 4097 + 32, 64, 32, 2), (17, 8191 + 32, 64, 5, 3)])
+def test_batched_short_prompts_take_the_filter_route(L, n_tokens, S, m, rounds):
+    """Batches of 2048 <= P < 8192 keys with 2^23 edges or more skip the dense edge block, a layer
+    on its own does not: the bytes must be the same (also in the smaller last launch group of 66
+    layers, which follows the full group's route).  Key norms as scores: they do not depend on how
+    a batch cuts the keys into chunks."""
+    say(f"short-prompt filter route L={L} N={n_tokens} S={S} m={m} T={rounds}")
+    H = 8 if L < 60 else 1
+    cfg = small_bf16_cfg(n_tokens=n_tokens, n_kv_heads=H, n_q_heads=4 * H, n_sources=S, n_neighbors=m, rounds=rounds,
+                         budget=400)
+    p = util.params_from_cfg(cfg, scorer=gk.SCORER_KNORM)
+    assert min(L, 64) * p.n_kv_heads * S * p.n_prefix >= 1 << 23 > p.n_kv_heads * S * p.n_prefix
+    some = [util.device_layer(cfg, l)[1] for l in range(3)]
+    K, V, Q = (torch.stack([some[l % 3][i] for l in range(L)]).contiguous() for i in range(3))
+    sc = torch.empty((L, p.n_kv_heads, p.n_prefix), dtype=torch.float32, device="cuda")
+    _, _, idx = gk.graphkv_compress_batched(p, L, None, K, V, Q, scores_out=sc)
+    idx, sc = idx.cpu().numpy().reshape(L, p.n_kv_heads, p.budget), sc.cpu().numpy()
+    for l in range(3):
+        one, s_l = run_compress(p, some[l])
+        for at in range(l, L, 3):
+            assert np.array_equal(idx[at], one[2]) and np.array_equal(sc[at], s_l), f"layer {at}"
