@@ -83,6 +83,90 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
     return r;
 }
 
+// ---- wave-wide scans and reductions on the vector ALU --------------------------------
+// gfx9 data-parallel primitives move a value along the lanes inside a vector instruction
+// (a shift within a row of 16 lanes, then the last lane of a row to the next row, then lane 31 to
+// the upper half).  A step costs a few clocks; __shfl goes through the LDS crossbar and costs
+// over a hundred, which is what the one-workgroup-per-head kernels spent much of their time on.
+// Lanes without a source read `identity`.
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan_op(uint32_t v, uint32_t identity, Op op)
+{
+#define GKV_DPP(ctrl, rows) (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, ctrl, rows, 0xf, false)
+    v = op(v, GKV_DPP(0x111, 0xf));   // row_shr:1
+    v = op(v, GKV_DPP(0x112, 0xf));   // row_shr:2
+    v = op(v, GKV_DPP(0x114, 0xf));   // row_shr:4
+    v = op(v, GKV_DPP(0x118, 0xf));   // row_shr:8
+    v = op(v, GKV_DPP(0x142, 0xa));   // row_bcast:15 into rows 1 and 3
+    v = op(v, GKV_DPP(0x143, 0xc));   // row_bcast:31 into rows 2 and 3
+#undef GKV_DPP
+    return v;
+}
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v)
+{
+    return wave_scan_op(v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+// The same value in every lane (a scalar).
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
+{
+    v = wave_scan_op(v, 0xffffffffu, [](uint32_t a, uint32_t b) { return min(a, b); });
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    v = wave_scan_op(v, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(v), 63);
+}
+// Number of lanes below this one whose bit is set in a wave vote.
+__device__ __forceinline__ uint32_t votes_below(uint64_t votes)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(votes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)votes, 0u));
+}
+
+// Exclusive sum over the threads of a workgroup of NW <= 16 waves; `total` gets the sum of all.
+// `part` holds NW words of LDS that nobody else touches; contains one barrier, and the caller puts
+// another between two uses of the same `part`.
+template <int NW>
+__device__ __forceinline__ uint32_t block_scan_add(uint32_t v, uint32_t *part, int lane, int wv, uint32_t &total)
+{
+    static_assert(NW <= 16, "one DPP row holds the wave sums");
+    const uint32_t incl = wave_scan_add(v);
+    if (lane == kWave - 1) part[wv] = incl;
+    __syncthreads();
+    const uint32_t sums = wave_scan_add(lane < NW ? part[lane] : 0u);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)sums, 63);
+    // (wv is the same in all lanes of a wave: moved to a scalar so that the read below is one)
+    const int w = __builtin_amdgcn_readfirstlane(wv);
+    const uint32_t before = w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)sums, w - 1) : 0u;
+    return before + incl - v;
+}
+
+// The bin of a 2 * BLOCK-bin LDS histogram in which the count from the top reaches `need` (the
+// bins hold at least `need` entries).  Thread t owns two bins, the highest pair first, so every
+// thread reads eight consecutive bytes.  out[0] = the bin, out[1] = need minus the entries in
+// higher bins, out[2] = entries in the bin.  Two barriers; the histogram is read before the second.
+template <int BLOCK>
+__device__ __forceinline__ void find_bin_block(const uint32_t *hist, uint32_t need, uint32_t *part, uint32_t *out,
+                                               int tid, int lane, int wv)
+{
+    const int hi = 2 * (BLOCK - 1 - tid);
+    const uint2 c = *reinterpret_cast<const uint2 *>(hist + hi);   // bins hi, hi + 1
+    uint32_t total;
+    const uint32_t above = block_scan_add<BLOCK / kWave>(c.x + c.y, part, lane, wv, total);
+    if (above < need && need <= above + c.x + c.y) {
+        const bool top = above + c.y >= need;
+        out[0] = (uint32_t)(top ? hi + 1 : hi);
+        out[1] = need - (top ? above : above + c.y);
+        out[2] = top ? c.y : c.x;
+    }
+    __syncthreads();
+}
+
 // The m-th largest of the keys in the first NIT registers of every lane (unused registers
 // hold 0, below every key), all between kmin and kmax: built bit by bit from the top; the
 // count of the keys that reach a trial value is one wave vote per register.  Straight-line

@@ -85,12 +85,11 @@ __device__ __forceinline__ void find_bin(const uint32_t *hist, uint32_t need, in
 // ballots and scans the cells once.
 // DIG = bits per radix sweep (11 for long rows, 8 for short ones: fewer bins to clear
 // and scan).
-template <int BLOCK, bool PLAN, int DIG>
+template <int BLOCK, int DIG>
 __device__ __forceinline__ void topk_row_lds(
     int row, const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out,
     long idx_ld, float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out,
-    int append_from, int append_count,
-    const typename std::conditional<PLAN, LayerPlan, int>::type &plan)
+    int append_from, int append_count)
 {
     constexpr int NW = BLOCK / kWave;
     constexpr int NBINS = 1 << DIG;
@@ -107,11 +106,6 @@ __device__ __forceinline__ void topk_row_lds(
     const float *xr = x + (long)row * ld;
     int32_t *out = idx_out ? idx_out + (long)row * idx_ld : nullptr;
     float *vout = val_out ? val_out + (long)row * val_ld : nullptr;
-    if constexpr (PLAN) {   // per-layer budget: k and the output row come from the plan
-        const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
-        k = plan.budget[g] - append_count;
-        out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
-    }
 
     if (out)
         for (int r = tid; r < append_count; r += BLOCK) out[k + r] = append_from + r;
@@ -216,12 +210,11 @@ __device__ __forceinline__ void topk_row_lds(
 // One workgroup per row (WALK = false); with a gate, a smaller grid whose workgroups walk
 // the rows and skip those whose gate is 0 (WALK = true: a launch that mostly skips then
 // costs next to nothing).
-template <int BLOCK, bool PLAN, int DIG, bool WALK>
+template <int BLOCK, int DIG, bool WALK>
 __global__ __launch_bounds__(BLOCK) void topk_rows_lds_kernel(
     const float *__restrict__ x, long ld, int n, int rows, int k, int32_t *__restrict__ idx_out,
     long idx_ld, float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out,
-    int append_from, int append_count, const int32_t *__restrict__ gate, int rows_per_gate,
-    typename std::conditional<PLAN, LayerPlan, int>::type plan)
+    int append_from, int append_count, const int32_t *__restrict__ gate, int rows_per_gate)
 {
     if constexpr (WALK) {
         // one round trip settles the usual case of no gate being set at all
@@ -232,12 +225,12 @@ __global__ __launch_bounds__(BLOCK) void topk_rows_lds_kernel(
         for (int row = blockIdx.x; row < rows; row += gridDim.x) {
             if (gate[row / rows_per_gate] == 0) continue;
             __syncthreads();   // LDS is reused from row to row
-            topk_row_lds<BLOCK, PLAN, DIG>(row, x, ld, n, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                           append_from, append_count, plan);
+            topk_row_lds<BLOCK, DIG>(row, x, ld, n, k, idx_out, idx_ld, val_out, val_ld, tau_out,
+                                           append_from, append_count);
         }
     } else {
-        topk_row_lds<BLOCK, PLAN, DIG>(blockIdx.x, x, ld, n, k, idx_out, idx_ld, val_out, val_ld,
-                                       tau_out, append_from, append_count, plan);
+        topk_row_lds<BLOCK, DIG>(blockIdx.x, x, ld, n, k, idx_out, idx_ld, val_out, val_ld,
+                                       tau_out, append_from, append_count);
     }
 }
 
@@ -826,6 +819,327 @@ __global__ __launch_bounds__(BLOCK) void topk_rows_long_smallk_kernel(
     emit_sources(win, k, S, out, ext_row, cls, tid);   // ascending index order
 }
 
+// ---- budgeted selection ---------------------------------------------------------------
+// The B_l - w best entries of each row in ascending index order, then the window (Problem
+// Formulation).  One workgroup of 16 waves per row; what bounds it is the chain of steps, each a
+// round trip to memory or LDS, so the steps are few: the row's keys sit in registers, one histogram
+// sweep over 11 bits of key - kmin finds the bin of the cut, the bin's entries (usually below a
+// hundred) go to a list on which every thread ranks one entry against all others, and the
+// winners' places come from wave votes and one scan of the vote counts.  All scans run on the
+// vector ALU (common.hpp).  (Three histogram sweeps through LDS copies of the keys, with a
+// one-wave bin search whose lanes all hit the same LDS bank: 27.6 us for 8 rows of 32736 entries;
+// this way 15.2 us; 256 threads and two
+// histogram sweeps more: 13.9 us for rows of 4064 entries, this way 5.6 us.)
+constexpr int kBudgetBlock = 1024;
+constexpr int kBudgetList = 8192;    // entries in the cut's bin that the long-row kernel can list
+constexpr int kPairs = 1024;         // ... that are ranked pair by pair
+
+// Which of the `cnt` (<= kPairs) listed keys is the need-th largest: out[0] = that key, out[1] =
+// how many entries equal to it are among the need largest, out[2] = how many there are.  `list` is
+// padded with zeros (below every key) to a multiple of four.  Ends with a barrier.
+__device__ __forceinline__ void rank_in_pairs(const uint32_t *list, int cnt, uint32_t need, uint32_t *out, int tid)
+{
+    if (tid < cnt) {
+        const uint32_t mine = list[tid];
+        uint32_t above = 0, same = 0;
+        for (int u = 0; u < cnt; u += 4) {
+            const uint4 o = *reinterpret_cast<const uint4 *>(list + u);
+            above += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
+            same += (o.x == mine) + (o.y == mine) + (o.z == mine) + (o.w == mine);
+        }
+        if (above < need && need <= above + same) {   // (every entry equal to the cut writes the same)
+            out[0] = mine;
+            out[1] = need - above;
+            out[2] = same;
+        }
+    }
+    __syncthreads();
+}
+
+// Indices of the set bits of a bitmap in LDS -> out, ascending.  A thread owns a run of words: it
+// counts their bits, one scan over the workgroup places the run, and it writes the run's indices.
+template <int NW>
+__device__ __forceinline__ void emit_bitmap(const uint64_t *map, int words, uint32_t *part, int32_t *out, int tid,
+                                            int lane, int wv)
+{
+    const int per = (words + NW * kWave - 1) / (NW * kWave), w0 = min(tid * per, words), w1 = min(w0 + per, words);
+    uint32_t mine = 0, total;
+    for (int w = w0; w < w1; ++w) mine += (uint32_t)__popcll(map[w]);
+    int32_t *o = out + block_scan_add<NW>(mine, part, lane, wv, total);
+    for (int w = w0; w < w1; ++w) {
+        uint64_t bits = map[w];
+        while (bits) {
+            *o++ = w * kWave + __ffsll((long long)bits) - 1;
+            bits &= bits - 1;
+        }
+    }
+}
+
+template <int ITEMS>
+__global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
+    const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, LayerPlan plan)
+{
+    constexpr int NW = kBudgetBlock / kWave, CELLS = ITEMS * NW;
+    __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
+    __shared__ __align__(16) uint32_t list[kPairs];
+    __shared__ uint64_t map[CELLS];
+    __shared__ uint32_t s_part[2][NW], s_min[NW], s_max[NW], s_out[3], s_cnt;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
+    const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
+    const int k = plan.budget[g] - append_count;
+    int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
+    const float *xr = x + (long)row * n;
+
+    // the loads of the row leave together (unconditional, clamped, pinned before the first use)
+    float val[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * kBudgetBlock + tid, n - 1)];
+    hist[tid] = 0;
+    hist[tid + kBudgetBlock] = 0;
+    list[tid] = 0;
+    if (tid == 0) s_cnt = 0;
+    for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));
+    uint32_t key[ITEMS], kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool in = i * kBudgetBlock + tid < n;
+        key[i] = in ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
+        kmin = min(kmin, in ? key[i] : 0xffffffffu);
+        kmax = max(kmax, key[i]);
+    }
+    kmin = wave_min_u32(kmin);
+    kmax = wave_max_u32(kmax);
+    if (lane == 0) { s_min[wv] = kmin; s_max[wv] = kmax; }
+    __syncthreads();
+    kmin = wave_min_u32(s_min[lane & (NW - 1)]);
+    kmax = wave_max_u32(s_max[lane & (NW - 1)]);
+
+    // radix select on key - kmin from the top bit in which the row's keys differ; it ends when the
+    // bin of the cut is one key wide or holds few enough entries to rank them pair by pair
+    int shift = kmax > kmin ? 32 - __clz(kmax - kmin) : 0;
+    uint32_t tau = kmin, need = (uint32_t)k, equal = (uint32_t)n;
+    for (int sweep = 0; shift > 0; ++sweep) {
+        const int below = shift;   // key bits that may still differ inside the current bin
+        shift = below > 11 ? below - 11 : 0;
+        const uint32_t width = below < 32 ? (1u << below) - 1u : 0xffffffffu;   // of the current bin, less one
+        if (sweep > 0) {
+            hist[tid] = 0;
+            hist[tid + kBudgetBlock] = 0;
+            __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (key[i] >= tau && key[i] - tau <= width) atomicAdd(&hist[(key[i] - tau) >> shift], 1u);
+        __syncthreads();
+        find_bin_block<kBudgetBlock>(hist, need, s_part[0], s_out, tid, lane, wv);
+        tau += s_out[0] << shift;
+        need = s_out[1];
+        equal = s_out[2];
+        if (shift > 0 && equal <= (uint32_t)kPairs) {
+            const uint32_t bin = (1u << shift) - 1u;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+                if (key[i] - tau <= bin) list[atomicAdd(&s_cnt, 1u)] = key[i];   // (lower keys wrap around, bin < 2^21)
+            __syncthreads();   // (also: s_out is read by every thread)
+            rank_in_pairs(list, (int)equal, need, s_out, tid);
+            tau = s_out[0];
+            need = s_out[1];
+            equal = s_out[2];
+            break;
+        }
+        __syncthreads();       // s_out and the histogram are read before the next sweep writes them
+    }
+
+    // Winners: every key above tau and the `need` first of those equal to it.  Entry i of thread
+    // tid has index i * 1024 + tid, so the vote on entry i of wave wv is word i * 16 + wv of a
+    // bitmap of the row.  The ties that stay out leave it again, last index first.
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const uint64_t in = __ballot(key[i] >= tau);
+        if (lane == 0) map[i * NW + wv] = in;
+    }
+    __syncthreads();
+    if (equal != need) {
+        // rank of each tied entry in index order: votes per word, one scan over the words
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint64_t eq = __ballot(key[i] == tau);
+            if (lane == 0) hist[i * NW + wv] = (uint32_t)__popcll(eq);
+        }
+        __syncthreads();
+        uint32_t total;
+        const uint32_t before = block_scan_add<NW>(tid < CELLS ? hist[tid] : 0u, s_part[0], lane, wv, total);
+        if (tid < CELLS) hist[tid] = before;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint64_t eq = __ballot(key[i] == tau);
+            const uint64_t drop = __ballot(key[i] == tau && hist[i * NW + wv] + votes_below(eq) >= need);
+            if (lane == 0) map[i * NW + wv] &= ~drop;
+        }
+        __syncthreads();
+    }
+    emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), s_part[1], out, tid, lane, wv);
+}
+
+// Rows beyond 32768 entries: two reads instead of five.  A coarse sample gives the key range, the
+// first read counts every key into 2048 bins over it (keys outside go to the end bins: bins only
+// have to be monotone), the second marks the entries of higher bins in a bitmap in LDS and lists those
+// of the cut's bin, whose winners join the bitmap; the indices are then read off the bitmap in
+// order.  Bound by the vector instructions of one compute unit (a row of 131008 entries is 512
+// wave-wide entries per SIMD, four clocks an instruction): the first read takes nine per entry, the
+// second, which compares the floats with the ends of the bin, about five.  A row with more than
+// kBudgetList entries in the bin of the cut (masses of equal values), or with more ties at the cut
+// than can be ranked pair by pair, goes through the general algorithm.  (Five reads with an LDS
+// histogram of 11, 11 and 10 bits: 110 us for 8 rows of 131008 entries; this way 48 us.)
+__global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
+    const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, LayerPlan plan)
+{
+    constexpr int NW = kBudgetBlock / kWave, U = 16, SAMPLE = 4;
+    extern __shared__ __align__(16) uint32_t dyn[];
+    __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
+    __shared__ uint32_t s_part[2][NW], s_min[NW], s_max[NW], s_out[3], s_cnt;
+    const int words = (n + kWave - 1) / kWave;
+    uint32_t *lkey = dyn, *lidx = dyn + kBudgetList;                                // the cut's bin
+    uint64_t *map = reinterpret_cast<uint64_t *>(dyn + 2 * kBudgetList);            // [words] bit l of word w: entry 64 w + l is in
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
+    const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
+    const int k = plan.budget[g] - append_count;
+    int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
+    const float *xr = x + (long)row * n;
+
+    // range of the sample: SAMPLE stretches of 64 entries per wave, evenly spread
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    {
+        float v[SAMPLE];
+#pragma unroll
+        for (int i = 0; i < SAMPLE; ++i)
+            v[i] = xr[(int)((long)(i * NW + wv) * (words - 1) / (SAMPLE * NW)) * kWave + lane];
+        hist[tid] = 0;
+        hist[tid + kBudgetBlock] = 0;
+        if (tid == 0) s_cnt = 0;
+        for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+#pragma unroll
+        for (int i = 0; i < SAMPLE; ++i) {
+            const uint32_t key = ord_key(v[i]);
+            kmin = min(kmin, key);
+            kmax = max(kmax, key);
+        }
+    }
+    kmin = wave_min_u32(kmin);
+    kmax = wave_max_u32(kmax);
+    if (lane == 0) { s_min[wv] = kmin; s_max[wv] = kmax; }
+    __syncthreads();
+    kmin = wave_min_u32(s_min[lane & (NW - 1)]);
+    kmax = wave_max_u32(s_max[lane & (NW - 1)]);
+    const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > 11 ? bits - 11 : 0;
+    // The whole row in batches of U loads per thread, the next batch on its way while one is used;
+    // use(entry number of the wave / 64, value, in the row) is called by whole waves.  Only the
+    // last batches hold entries past the end.
+    const int turns = (n + kBudgetBlock - 1) / kBudgetBlock, whole = n / kBudgetBlock / U * U;
+    auto sweep = [&](auto &&use) {
+        float a[U], b[U];
+        auto load = [&](float (&v)[U], int i0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v[u] = i0 < whole ? (xr + (i0 + u) * kBudgetBlock)[tid] : xr[min((i0 + u) * kBudgetBlock + tid, n - 1)];
+        };
+        auto work = [&](float (&v)[U], int i0) {
+            if (i0 < whole) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) use((i0 + u) * NW + wv, v[u], true);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (i0 + u < turns) use((i0 + u) * NW + wv, v[u], (i0 + u) * kBudgetBlock + tid < n);
+            }
+        };
+        load(a, 0);
+        for (int i0 = 0; i0 < turns; i0 += 2 * U) {
+            load(b, i0 + U);
+            work(a, i0);
+            load(a, i0 + 2 * U);
+            work(b, i0 + U);
+        }
+    };
+    sweep([&](int, float v, bool in) {
+        if (in) atomicAdd(&hist[(min(max(ord_key(v), kmin), kmax) - kmin) >> shift], 1u);
+    });
+    __syncthreads();
+    find_bin_block<kBudgetBlock>(hist, (uint32_t)k, s_part[0], s_out, tid, lane, wv);
+    const uint32_t bin = s_out[0], cnt = s_out[2];
+    uint32_t need = s_out[1];
+    if (cnt > (uint32_t)kBudgetList) {   // (the same for every thread)
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
+                                            nullptr, 1, plan);
+        return;
+    }
+    if (tid < 4) lkey[min(cnt + (uint32_t)tid, (uint32_t)kBudgetList - 1u)] = 0u;   // padding for reads of four
+    __syncthreads();
+    // The floats at the ends of the bin (the end bins are open).  Floats compare as their keys do.
+    const uint32_t last_bin = (kmax - kmin) >> shift;
+    const float flo = bin == 0 ? -INFINITY : key_to_float(kmin + (bin << shift));
+    const float fhi = bin == last_bin ? INFINITY : key_to_float(kmin + (bin << shift) + ((1u << shift) - 1u));
+    sweep([&](int word, float v, bool in) {
+        const bool reach = in && v >= flo, over = reach && v > fhi;
+        const uint64_t above = __ballot(over);
+        if (lane == 0 && word < words) map[word] = above;
+        if (reach && !over) {
+            const uint32_t at = atomicAdd(&s_cnt, 1u);
+            lkey[at] = ord_key(v);
+            lidx[at] = (uint32_t)(word * kWave + lane);
+        }
+    });
+    __syncthreads();
+    // the need-th largest of the list
+    uint32_t tau, equal;
+    if (cnt <= (uint32_t)kPairs) {
+        rank_in_pairs(lkey, (int)cnt, need, s_out, tid);
+        tau = s_out[0];
+        need = s_out[1];
+        equal = s_out[2];
+    } else {                             // radix select over the listed keys, 11 bits a sweep
+        tau = 0u;
+        equal = cnt;
+        for (int left = 32; left > 0;) {
+            const int low = left > 11 ? left - 11 : 0;
+            hist[tid] = 0;
+            hist[tid + kBudgetBlock] = 0;
+            __syncthreads();
+            for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
+                const uint32_t key = lkey[r];
+                if (left == 32 || (key >> left) == (tau >> left)) atomicAdd(&hist[(key >> low) & 2047u], 1u);
+            }
+            __syncthreads();
+            find_bin_block<kBudgetBlock>(hist, need, s_part[1], s_out, tid, lane, wv);
+            tau |= s_out[0] << low;
+            need = s_out[1];
+            equal = s_out[2];
+            left = low;
+            __syncthreads();
+        }
+    }
+    if (equal != need && cnt > (uint32_t)kPairs) {   // many ties straddle the cut
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
+                                            nullptr, 1, plan);
+        return;
+    }
+    for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
+        const uint32_t key = lkey[r], j = lidx[r];
+        bool in = key > tau || (key == tau && equal == need);
+        if (key == tau && equal != need) {           // the lowest indices of those equal to the cut
+            uint32_t rank = 0;
+            for (int u = 0; u < (int)cnt; ++u) rank += lkey[u] == tau && lidx[u] < j;
+            in = rank < need;
+        }
+        if (in) atomicOr(reinterpret_cast<uint32_t *>(map) + (j >> 5), 1u << (j & 31u));
+    }
+    __syncthreads();
+    emit_bitmap<NW>(map, words, s_part[0], out, tid, lane, wv);
+}
+
 // ---- neighbourhoods of heads whose candidate lists overflowed ------------------------
 // The filter route (mfma_cosine.hip) gives up on a head when a candidate list cannot hold what
 // reaches the bound (masses of equal edges, an adversarial key order) and raises the head's
@@ -882,66 +1196,32 @@ __global__ __launch_bounds__(kRedoBlock) void redo_rows_kernel(
         int32_t *out = nbr + item * m;
         float *vout = nbr_e + item * m;
         if (P <= 32768)
-            topk_row_lds<kRedoBlock, false, 11>(0, erow, P, P, m, out, 0, vout, 0, nullptr, 0, 0, 0);
+            topk_row_lds<kRedoBlock, 11>(0, erow, P, P, m, out, 0, vout, 0, nullptr, 0, 0);
         else
             topk_stream_row<kRedoBlock, false>(0, erow, P, P, m, out, 0, vout, 0, nullptr, 0, 0, nullptr, 1, 0);
     }
 }
 
-template <int BLOCK, bool PLAN, int DIG, typename PlanArg>
+template <int BLOCK, int DIG>
 static hipError_t launch_lds(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
                              long idx_ld, float *val_out, long val_ld, float *tau_out,
                              int append_from, int append_count, const int32_t *gate,
-                             int rows_per_gate, PlanArg plan, hipStream_t st)
+                             int rows_per_gate, hipStream_t st)
 {
     const int items = (n + BLOCK - 1) / BLOCK;
     const size_t lds = ((size_t)items * BLOCK + 2 * (size_t)items * (BLOCK / kWave)) * 4;
     if (lds > 65536 &&    // more than 64 KiB of dynamic LDS needs a one-time opt-in
-        (!allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, PLAN, DIG, false>, 140 * 1024) ||
-         !allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, PLAN, DIG, true>, 140 * 1024)))
+        (!allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, DIG, false>, 140 * 1024) ||
+         !allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, DIG, true>, 140 * 1024)))
         return hipGetLastError();
     if (gate)
-        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, PLAN, DIG, true>), dim3(rows > 1024 ? 1024 : rows),
+        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, DIG, true>), dim3(rows > 1024 ? 1024 : rows),
                            dim3(BLOCK), lds, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld,
-                           tau_out, append_from, append_count, gate, rows_per_gate, plan);
+                           tau_out, append_from, append_count, gate, rows_per_gate);
     else
-        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, PLAN, DIG, false>), dim3(rows), dim3(BLOCK), lds,
+        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, DIG, false>), dim3(rows), dim3(BLOCK), lds,
                            st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
-                           append_count, gate, rows_per_gate, plan);
-    return hipGetLastError();
-}
-
-template <bool PLAN, typename PlanArg>
-static hipError_t launch_any(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
-                             long idx_ld, float *val_out, long val_ld, float *tau_out,
-                             int append_from, int append_count, const int32_t *gate,
-                             int rows_per_gate, PlanArg plan, hipStream_t st)
-{
-    if (rows <= 0) return hipSuccess;
-    if (n <= 4096)
-        return launch_lds<256, PLAN, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                        append_from, append_count, gate, rows_per_gate, plan, st);
-    if constexpr (!PLAN) {
-        if (n > 4096 && n <= 32768 && k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 &&
-            !gate) {
-            hipLaunchKernelGGL(pick_sources_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k, idx_out,
-                               idx_ld, (int32_t *)nullptr, 0L);
-            return hipGetLastError();
-        }
-    }
-    if (n <= 32768)
-        return launch_lds<1024, PLAN, 11>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                          append_from, append_count, gate, rows_per_gate, plan, st);
-    if constexpr (!PLAN) {
-        if (k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate) {
-            hipLaunchKernelGGL(topk_rows_long_smallk_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k,
-                               idx_out, idx_ld, (int32_t *)nullptr, 0L);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((topk_rows_stream_kernel<1024, PLAN>), dim3(gate && rows > 1024 ? 1024 : rows), dim3(1024),
-                       0, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
-                       append_count, gate, rows_per_gate, plan);
+                           append_count, gate, rows_per_gate);
     return hipGetLastError();
 }
 
@@ -950,8 +1230,28 @@ hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int
                             int append_from, int append_count, const int32_t *gate,
                             int rows_per_gate, hipStream_t st)
 {
-    return launch_any<false, int>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                  append_from, append_count, gate, rows_per_gate, 0, st);
+    if (rows <= 0) return hipSuccess;
+    if (n <= 4096)
+        return launch_lds<256, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
+                                  append_from, append_count, gate, rows_per_gate, st);
+    const bool plain = k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate;
+    if (n <= 32768 && plain) {
+        hipLaunchKernelGGL(pick_sources_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k, idx_out,
+                           idx_ld, (int32_t *)nullptr, 0L);
+        return hipGetLastError();
+    }
+    if (n <= 32768)
+        return launch_lds<1024, 11>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
+                                    append_from, append_count, gate, rows_per_gate, st);
+    if (plain) {
+        hipLaunchKernelGGL(topk_rows_long_smallk_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k,
+                           idx_out, idx_ld, (int32_t *)nullptr, 0L);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((topk_rows_stream_kernel<1024, false>), dim3(gate && rows > 1024 ? 1024 : rows), dim3(1024),
+                       0, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
+                       append_count, gate, rows_per_gate, 0);
+    return hipGetLastError();
 }
 
 // Workgroups that walk the rows of flagged heads: one per compute unit, fewer for long rows
@@ -996,11 +1296,33 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
     return hipGetLastError();
 }
 
+// Row length up to which the budgeted selection keeps a bitmap of the row in LDS.
+constexpr int kBitmapRow = 1 << 18;
+
 hipError_t launch_topk_final(const float *scores, int P, int rows, const LayerPlan &plan, int w,
                              int32_t *idx, hipStream_t st)
 {
-    return launch_any<true, LayerPlan>(scores, P, P, rows, 0, idx, 0, nullptr, 0, nullptr, P, w,
-                                       nullptr, 1, plan, st);
+    if (rows <= 0) return hipSuccess;
+#define GKV_BUDGET(ITEMS) \
+    hipLaunchKernelGGL(budget_select_kernel<ITEMS>, dim3(rows), dim3(kBudgetBlock), 0, st, scores, P, idx, P, w, plan)
+    if (P <= 1024) GKV_BUDGET(1);
+    else if (P <= 2048) GKV_BUDGET(2);
+    else if (P <= 4096) GKV_BUDGET(4);
+    else if (P <= 8192) GKV_BUDGET(8);
+    else if (P <= 16384) GKV_BUDGET(16);
+    else if (P <= 32768) GKV_BUDGET(32);
+    else if (P <= kBitmapRow) {
+        if (!allow_big_lds((const void *)budget_select_long_kernel, 140 * 1024)) return hipGetLastError();
+        const size_t words = (size_t)(P + kWave - 1) / kWave;
+        hipLaunchKernelGGL(budget_select_long_kernel, dim3(rows), dim3(kBudgetBlock),
+                           words * 8 + (size_t)kBudgetList * 8, st, scores, P, idx, P, w, plan);
+    } else {
+        hipLaunchKernelGGL((topk_rows_stream_kernel<1024, true>), dim3(rows), dim3(1024), 0, st, scores, (long)P, P,
+                           rows, 0, idx, 0L, (float *)nullptr, 0L, (float *)nullptr, P, w, (const int32_t *)nullptr, 1,
+                           plan);
+    }
+#undef GKV_BUDGET
+    return hipGetLastError();
 }
 
 }  // namespace gkv

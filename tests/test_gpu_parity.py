@@ -1080,3 +1080,26 @@ def test_batched_short_prompts_take_the_filter_route(L, n_tokens, S, m, rounds):
         one, s_l = run_compress(p, some[l])
         for at in range(l, L, 3):
             assert np.array_equal(idx[at], one[2]) and np.array_equal(sc[at], s_l), f"layer {at}"
+
+
+@pytest.mark.parametrize("P,k", [(1024, 1023), (1025, 1), (2049, 700), (8193, 4096), (16385, 9), (32768, 20000),
+                                 (32769, 500), (131007, 130000), (262144, 4000), (262145, 100)])
+def test_budgeted_selection_row_lengths(oracle, P, k):
+    """Every register count of the one-read selection, both ends of the bitmap one and the re-reading
+    one behind it: normal rows, ties that straddle the cut, rows that are nearly all one value (the
+    cut's bin holds the row) and rows with minus infinities (evicted nodes) below and at the cut."""
+    say(f"budgeted selection P={P} k={k}")
+    rng = np.random.default_rng(P + 13 * k)
+    w, H = 5, 6
+    s = rng.standard_normal((H, P)).astype(np.float32)
+    s[1] = rng.integers(0, 3, size=P)                              # ties fill the cut's bin
+    s[2] = 1.0
+    s[2, rng.choice(P, size=min(P, k // 2), replace=False)] = 2.0  # one value straddles the cut
+    s[3] = np.abs(s[3]) * 1e-30
+    s[3, rng.choice(P, size=max(1, k // 3), replace=False)] *= np.float32(1e33)
+    s[4, rng.choice(P, size=max(1, P - k + min(k, 3)), replace=False)] = -np.inf   # k reaches into the infinities
+    s[5] = np.sort(s[5])[::-1]
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=8, n_tokens=P + w, window=w, budget=k + w)
+    idx = gk.graphkv_select(p, torch.from_numpy(s).cuda()).cpu().numpy()
+    ref, _ = oracle.select(s.astype(np.float64), P + w, w, k + w)
+    assert np.array_equal(idx, ref)
