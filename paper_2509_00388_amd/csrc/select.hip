@@ -234,309 +234,6 @@ __global__ __launch_bounds__(BLOCK) void topk_rows_lds_kernel(
     }
 }
 
-// ---- small k out of a long row ------------------------------------------------
-// Winners of a row, (index << 32) | key each, in any order -> the row's outputs.  With
-// ext_out the k winners are the S best and the X = k - S next best: a winner that fewer
-// than S others beat by (key descending, index ascending) is one of the S; src_out gets
-// those in ascending index order, ext_out the same S followed by the others in ascending
-// index order.  Without ext_out (S = k) this is the plain ascending list.  `cls` holds k
-// bytes of LDS; every thread of the workgroup calls this (k <= kSmallK <= blockDim.x).
-constexpr int kSmallK = 256;       // largest k the small-k paths take
-
-__device__ __forceinline__ void emit_sources(const uint64_t *win, int k, int S, int32_t *src_out,
-                                             int32_t *ext_out, uint8_t *cls, int tid)
-{
-    uint64_t mine = 0;
-    bool first_s = true;
-    if (tid < k) {
-        mine = win[tid];
-        const uint32_t key = (uint32_t)mine, idx = (uint32_t)(mine >> 32);
-        int beat = 0;
-        for (int u = 0; u < k; ++u) {
-            const uint64_t w = win[u];
-            const uint32_t ku = (uint32_t)w, iu = (uint32_t)(w >> 32);
-            beat += (ku > key) || (ku == key && iu < idx);
-        }
-        first_s = beat < S;
-        cls[tid] = first_s ? 1 : 0;
-    }
-    __syncthreads();
-    if (tid < k) {
-        int before = 0;   // winners of the same class with a lower index
-        for (int u = 0; u < k; ++u) before += (win[u] >> 32) < (mine >> 32) && (cls[u] != 0) == first_s;
-        const int32_t idx = (int32_t)(mine >> 32);
-        if (first_s) {
-            src_out[before] = idx;
-            if (ext_out) ext_out[before] = idx;
-        } else {
-            ext_out[S + before] = idx;
-        }
-    }
-}
-
-// The same by one wave on its own (no workgroup barrier, no LDS in the loops): lane L keeps
-// winners L, L + 64, ... in R registers (k <= 64 R) and every winner in turn is broadcast to
-// the wave from its lane.
-template <int R>
-__device__ __forceinline__ void emit_sources_wave_r(const uint64_t *win, int k, int S, int32_t *src_out,
-                                                    int32_t *ext_out, int lane)
-{
-    uint32_t key[R], idx[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint64_t w = r * kWave + lane < k ? win[r * kWave + lane] : 0ull;
-        key[r] = (uint32_t)w;
-        idx[r] = (uint32_t)(w >> 32);
-    }
-    // One of the S best: above the S-th largest key of the winners, or equal to it and among the
-    // lowest indices of those (only if the tie straddles the cut are the tied entries ranked).
-    bool first_s[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) first_s[r] = true;
-    if (ext_out && S < k) {
-        uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (r * kWave + lane < k) { kmin = min(kmin, key[r]); kmax = max(kmax, key[r]); }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-            kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-        }
-        const uint32_t tau_s = mth_largest_key<R>(key, kmin, kmax, S);
-        int above = 0, equal = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            above += (int)__popcll(__ballot(r * kWave + lane < k && key[r] > tau_s));
-            equal += (int)__popcll(__ballot(r * kWave + lane < k && key[r] == tau_s));
-        }
-        const int need = S - above;   // tied entries that still belong to the S
-        int tied_before[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) tied_before[r] = 0;
-        if (equal != need) {
-#pragma unroll
-            for (int ru = 0; ru < R; ++ru)
-                for (int l = 0; l < kWave && ru * kWave + l < k; ++l) {
-                    const uint32_t ku = (uint32_t)__builtin_amdgcn_readlane((int)key[ru], l);
-                    const uint32_t iu = (uint32_t)__builtin_amdgcn_readlane((int)idx[ru], l);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) tied_before[r] += ku == tau_s && iu < idx[r];
-                }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) first_s[r] = key[r] > tau_s || (key[r] == tau_s && tied_before[r] < need);
-    }
-    // place = winners of the same class with a lower index
-    int before[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) before[r] = 0;
-#pragma unroll
-    for (int ru = 0; ru < R; ++ru)
-        for (int l = 0; l < kWave && ru * kWave + l < k; ++l) {
-            const uint32_t iu = (uint32_t)__builtin_amdgcn_readlane((int)idx[ru], l);
-            const bool su = __builtin_amdgcn_readlane(first_s[ru] ? 1 : 0, l) != 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) before[r] += iu < idx[r] && su == first_s[r];
-        }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (r * kWave + lane < k) {
-            if (first_s[r]) {
-                src_out[before[r]] = (int32_t)idx[r];
-                if (ext_out) ext_out[before[r]] = (int32_t)idx[r];
-            } else {
-                ext_out[S + before[r]] = (int32_t)idx[r];
-            }
-        }
-}
-
-__device__ __forceinline__ void emit_sources_wave(const uint64_t *win, int k, int S, int32_t *src_out,
-                                                  int32_t *ext_out, int lane)
-{
-    if (k <= kWave) emit_sources_wave_r<1>(win, k, S, src_out, ext_out, lane);
-    else if (k <= 2 * kWave) emit_sources_wave_r<2>(win, k, S, src_out, ext_out, lane);
-    else emit_sources_wave_r<kSmallK / kWave>(win, k, S, src_out, ext_out, lane);
-}
-
-// For k far below the row length (the source nodes: 64 of 32736, with the speculative
-// rows 96) the row is read once into registers (32 keys per thread).  A bound comes almost
-// for free: split the threads into G >= k groups; the smallest of the G group maxima is
-// reached by G different entries, so the k-th largest key is at least that (if too many
-// entries reach it, one radix sweep raises it).  The few hundred
-// keys that reach the bound are compacted into an LDS list (positions from wave votes, one
-// atomic per wave and register), and from there on the registers are free: one wave finds the
-// k-th largest key of the list bit by bit (its keys in registers, a wave vote per register and
-// bit, no barrier), every entry above it and the lowest-index entries equal to it are the
-// winners, and emit_sources() orders them.  A row with more than kPickCap entries at or above
-// the bound (masses of equal values) takes the algorithm that re-reads the row instead.
-constexpr int kPickCap = 2048;     // list entries: 32 registers of a wave
-
-template <int BLOCK, bool PLAN> __device__ __forceinline__ void topk_stream_row(
-    int row, const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out, long idx_ld,
-    float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out, int append_from,
-    int append_count, const int32_t *__restrict__ gate, int rows_per_gate,
-    typename std::conditional<PLAN, LayerPlan, int>::type plan);
-
-template <int NIT>
-__device__ __forceinline__ uint32_t pick_tau(const uint32_t *lk, int cnt, int lane, int k, uint32_t kmin,
-                                             uint32_t kmax)
-{
-    uint32_t E[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) E[it] = it * 64 + lane < cnt ? lk[it * 64 + lane] : 0u;
-    return mth_largest_key<NIT>(E, kmin, kmax, k);
-}
-
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void pick_sources_kernel(
-    const float *__restrict__ x, long ld, int n, int k, int S, int32_t *__restrict__ src_out, long src_ld,
-    int32_t *__restrict__ ext_out, long ext_ld)
-{
-    constexpr int ITEMS = 32768 / BLOCK, NW = BLOCK / kWave, DIG = 11, NBINS = 1 << DIG;
-    __shared__ uint32_t lk[kPickCap], lj[kPickCap];   // keys and indices of the entries that reach the bound
-    __shared__ uint32_t hist[NBINS];
-    __shared__ uint64_t win[kSmallK];
-    __shared__ uint8_t cls[kSmallK];
-    __shared__ uint32_t s_grp[kSmallK], s_bound, s_wmax[NW], s_max, s_cnt, s_need, s_bin;
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const float *xr = x + (long)row * ld;
-    int32_t *src_row = src_out + (long)row * src_ld;
-    int32_t *ext_row = ext_out ? ext_out + (long)row * ext_ld : nullptr;
-
-    // All loads of the row leave together: clamped, unconditional, and their values pinned in
-    // registers before the first use (otherwise the compiler moves every load behind the
-    // test of its index and waits for each in turn).
-    float val[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * BLOCK + tid, n - 1)];
-#pragma unroll
-    for (int i = 0; i < ITEMS; i += 8)
-        asm volatile("" : "+v"(val[i]), "+v"(val[i + 1]), "+v"(val[i + 2]), "+v"(val[i + 3]), "+v"(val[i + 4]),
-                          "+v"(val[i + 5]), "+v"(val[i + 6]), "+v"(val[i + 7]));
-    uint32_t key[ITEMS];
-    uint32_t best = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        key[i] = i * BLOCK + tid < n ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
-        best = max(best, key[i]);
-    }
-    // G groups (G a power of two, k <= G <= 256): thread t belongs to group t mod G, so a group
-    // owns the entries whose index is t mod G -- scores are smooth along the row (pooling), and
-    // this way the few peaks that hold the winners spread over many groups.  Group maxima (an
-    // LDS atomic per thread), their minimum = the bound; the row maximum on the way.
-    int G = 16;
-    while (G < k) G <<= 1;
-    if (tid < G) s_grp[tid] = 0u;
-    if (tid == 0) s_cnt = 0;
-    for (int b = tid; b < NBINS; b += BLOCK) hist[b] = 0;
-    __syncthreads();
-    atomicMax(&s_grp[tid & (G - 1)], best);
-    uint32_t wmax = best;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, o, kWave));
-    if (lane == 0) s_wmax[wv] = wmax;
-    __syncthreads();
-    if (wv == 0) {
-        uint32_t mn = 0xffffffffu, mx = 0u;
-        for (int g = lane; g < G; g += kWave) mn = min(mn, s_grp[g]);
-        if (lane < NW) mx = s_wmax[lane];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            mn = min(mn, (uint32_t)__shfl_xor((int)mn, o, kWave));
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
-        }
-        if (lane == 0) { s_bound = mn; s_max = mx; }
-    }
-    __syncthreads();
-    uint32_t bound = s_bound;
-    const uint32_t kmax = s_max;
-
-    // One radix sweep over the entries that reach the bound -- 11 bits of key - bound from the
-    // top bit in which they can differ -- raises the bound to the lower edge of the bin in which
-    // the count from the top reaches k: a handful of entries beyond the k winners remain.
-    if (kmax > bound) {   // (the same for every thread)
-        const int remaining = 32 - __clz(kmax - bound);
-        const int bits = remaining < DIG ? remaining : DIG, shift = remaining - bits;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            if (key[i] >= bound && key[i] != 0u) atomicAdd(&hist[(key[i] - bound) >> shift], 1u);
-        __syncthreads();
-        if (wv == 0) find_bin<NBINS / 64>(hist, (uint32_t)k, lane, &s_bin, &s_need);
-        __syncthreads();
-        bound += s_bin << shift;
-    }
-
-    // everything that reaches the bound -> the list (any order): a wave counts its entries with
-    // wave votes, takes its stretch of the list with one atomic, and places them
-    const uint64_t below = (1ull << lane) - 1ull;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) mine += (uint32_t)__popcll(__ballot(key[i] >= bound && key[i] != 0u));
-    uint32_t at0 = 0;
-    if (lane == 0 && mine) at0 = atomicAdd(&s_cnt, mine);
-    at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at0);
-    if (mine) {   // (the same for every lane of the wave)
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const bool in = key[i] >= bound && key[i] != 0u;
-            const uint64_t votes = __ballot(in);
-            const uint32_t at = at0 + (uint32_t)__popcll(votes & below);
-            if (in && at < (uint32_t)kPickCap) { lk[at] = key[i]; lj[at] = (uint32_t)(i * BLOCK + tid); }
-            at0 += (uint32_t)__popcll(votes);
-        }
-    }
-    __syncthreads();
-    const int cnt = (int)s_cnt;
-    if (cnt > kPickCap) {   // (the same for every thread) masses of equal values: re-read the row
-        int32_t *tmp = ext_row ? ext_row : src_row;
-        topk_stream_row<BLOCK, false>(row, x, ld, n, k, tmp, 0, nullptr, 0, nullptr, 0, 0, nullptr, 1, 0);
-        if (!ext_row) return;
-        __syncthreads();
-        if (tid < k) {
-            const uint32_t j = (uint32_t)ext_row[tid];
-            win[tid] = ((uint64_t)j << 32) | ord_key(xr[j]);
-        }
-        __syncthreads();
-        emit_sources(win, k, S, src_row, ext_row, cls, tid);
-        return;
-    }
-    if (wv != 0) return;
-
-    // One wave finishes the row on its own: the k-th largest key of the list, ...
-    const int n_it = (cnt + 63) >> 6;
-    uint32_t tau;
-    if (n_it <= 4) tau = pick_tau<4>(lk, cnt, lane, k, bound, kmax);
-    else if (n_it <= 8) tau = pick_tau<8>(lk, cnt, lane, k, bound, kmax);
-    else if (n_it <= 16) tau = pick_tau<16>(lk, cnt, lane, k, bound, kmax);
-    else tau = pick_tau<32>(lk, cnt, lane, k, bound, kmax);
-    int above = 0, equal = 0;
-    for (int r = lane; r < cnt; r += kWave) { above += lk[r] > tau; equal += lk[r] == tau; }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { above += __shfl_xor(above, o, kWave); equal += __shfl_xor(equal, o, kWave); }
-    // ... the winners: every entry above it and, of the entries equal to it, the `need` lowest
-    // indices (usually all of them) ...
-    const int need = k - above;
-    int listed = 0;
-    for (int r0 = 0; r0 < cnt; r0 += kWave) {
-        const int r = r0 + lane;
-        const uint32_t kr = r < cnt ? lk[r] : 0u, jr = r < cnt ? lj[r] : 0u;
-        bool in = r < cnt && kr >= tau;
-        if (in && kr == tau && equal != need) {
-            int rank = 0;
-            for (int u = 0; u < cnt; ++u) rank += (lk[u] == tau) & (lj[u] < jr);
-            in = rank < need;
-        }
-        const uint64_t votes = __ballot(in);
-        if (in) win[listed + (int)__popcll(votes & below)] = ((uint64_t)jr << 32) | kr;
-        listed += (int)__popcll(votes);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // ... and their order.
-    emit_sources_wave(win, k, S, src_row, ext_row, lane);
-}
-
 // ---- rows of any length: every sweep re-reads the row ------------------------
 template <int BLOCK, bool PLAN>
 __device__ __forceinline__ void topk_stream_row(
@@ -673,150 +370,219 @@ __global__ __launch_bounds__(BLOCK) void topk_rows_stream_kernel(
     }
 }
 
-// Long rows, few winners (k <= kSmallK <= BLOCK): two reads of the row instead of five.
-// Every thread takes the maximum of the elements it owns; the k-th largest of those maxima is
-// a lower bound of the row's k-th largest element (k different elements reach it).  The second
-// read collects the few elements that reach the bound into an LDS list, and the exact select
-// (radix select over the list, ties at the cut to the lowest indices, winners ranked by index)
-// runs on that list.  A row with more than kLongCap elements at or above the bound (masses of
-// equal values) goes through the five-read algorithm instead.
-constexpr int kLongCap = 4096;
-
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void topk_rows_long_smallk_kernel(
-    const float *__restrict__ x, long ld, int n, int k, int S, int32_t *__restrict__ idx_out, long idx_ld,
-    int32_t *__restrict__ ext_out, long ext_ld)
+// A row in batches of U loads per thread of a 1024-thread workgroup, the next batch on its way
+// while one is used; use(number of the 64 entries, value, in the row) is called by whole waves.
+// Only the last batches hold entries past the end.
+template <int U, typename Use>
+__device__ __forceinline__ void row_sweep(const float *__restrict__ xr, int n, int tid, int wv, Use &&use)
 {
-    constexpr int NW = BLOCK / kWave, U = 8;
-    __shared__ uint32_t lk[kLongCap], lj[kLongCap];   // keys and indices of the candidates
-    __shared__ uint32_t tmax[BLOCK];
-    __shared__ uint64_t win[kSmallK];                 // (index << 32) | key of the winners
-    __shared__ uint32_t hist8[256];
-    __shared__ uint32_t s_cnt, s_bin, s_need, s_wmax[NW], s_wmin[NW];
-    __shared__ int32_t n_win, n_eq;
-    __shared__ uint8_t cls[kSmallK];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const float *xr = x + (long)blockIdx.x * ld;
-    int32_t *out = idx_out + (long)blockIdx.x * idx_ld;
-    int32_t *ext_row = ext_out ? ext_out + (long)blockIdx.x * ext_ld : nullptr;
-
-    // first read: the largest key each thread owns (0 is below the key of every number)
-    uint32_t mx = 0u;
-    for (int j0 = 0; j0 < n; j0 += BLOCK * U) {
-        float t[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * BLOCK + tid;
-            t[u] = xr[min(j, n - 1)];
-        }
+    constexpr int BLOCK = 1024, NW = BLOCK / kWave;
+    const int turns = (n + BLOCK - 1) / BLOCK, whole = n / BLOCK / U * U;
+    float a[U], b[U];
+    auto load = [&](float (&v)[U], int i0) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (j0 + u * BLOCK + tid < n) mx = max(mx, ord_key(t[u]));
-    }
-    tmax[tid] = mx;
-    uint32_t wmax = mx, wmin = mx;   // the largest and the smallest of the maxima
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, o, kWave));
-        wmin = min(wmin, (uint32_t)__shfl_xor((int)wmin, o, kWave));
-    }
-    if (lane == 0) { s_wmax[wv] = wmax; s_wmin[wv] = wmin; }
-    if (tid == 0) { s_cnt = 0; n_win = 0; n_eq = 0; }
-    __syncthreads();
-    uint32_t kmax = 0u, kmin = 0xffffffffu;
-#pragma unroll
-    for (int u = 0; u < NW; ++u) { kmax = max(kmax, s_wmax[u]); kmin = min(kmin, s_wmin[u]); }
-
-    // The want-th largest of arr[0 .. count), all keys in [lo, kmax]: radix select over key - lo,
-    // 8 bits a sweep from the top bit in which the keys can differ.  Returns the key and leaves
-    // in `left` how many entries equal to it are among the want largest.
-    auto kth_largest = [&](const uint32_t *arr, int count, uint32_t lo, int want, uint32_t &left) {
-        int remaining = kmax > lo ? 32 - __clz(kmax - lo) : 0;
-        uint32_t prefix = 0, mask = 0, need = (uint32_t)want;
-        while (remaining > 0) {
-            const int bits = remaining < 8 ? remaining : 8;
-            const int shift = remaining - bits;
-            const uint32_t dmask = (1u << bits) - 1u;
-            if (tid < 256) hist8[tid] = 0;
-            __syncthreads();
-            for (int r = tid; r < count; r += BLOCK) {
-                const uint32_t rel = arr[r] - lo;
-                if ((rel & mask) == prefix) atomicAdd(&hist8[(rel >> shift) & dmask], 1u);
-            }
-            __syncthreads();
-            if (wv == 0) find_bin<4>(hist8, need, lane, &s_bin, &s_need);
-            __syncthreads();
-            prefix |= s_bin << shift;
-            mask |= dmask << shift;
-            need = s_need;
-            remaining = shift;
-        }
-        left = need;
-        return lo + prefix;
+            v[u] = i0 < whole ? (xr + (i0 + u) * BLOCK)[tid] : xr[min((i0 + u) * BLOCK + tid, n - 1)];
     };
-    uint32_t unused;
-    const uint32_t bound = kth_largest(tmax, BLOCK, kmin, k, unused);
-
-    // second read: everything that reaches the bound goes to the list
-    for (int j0 = 0; j0 < n; j0 += BLOCK * U) {
-        float t[U];
+    auto work = [&](float (&v)[U], int i0) {
+        if (i0 < whole) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * BLOCK + tid;
-            t[u] = xr[min(j, n - 1)];
-        }
+            for (int u = 0; u < U; ++u) use((i0 + u) * NW + wv, v[u], true);
+        } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * BLOCK + tid;
-            const uint32_t key = ord_key(t[u]);
-            if (j < n && key >= bound) {
-                const uint32_t at = atomicAdd(&s_cnt, 1u);
-                if (at < (uint32_t)kLongCap) { lk[at] = key; lj[at] = (uint32_t)j; }
-            }
+            for (int u = 0; u < U; ++u)
+                if (i0 + u < turns) use((i0 + u) * NW + wv, v[u], (i0 + u) * BLOCK + tid < n);
         }
+    };
+    load(a, 0);
+    for (int i0 = 0; i0 < turns; i0 += 2 * U) {
+        load(b, i0 + U);
+        work(a, i0);
+        load(a, i0 + 2 * U);
+        work(b, i0 + U);
     }
-    __syncthreads();
-    const int cnt = (int)s_cnt;
-    if (cnt > kLongCap) {   // (the same for every thread)
-        int32_t *tmp = ext_row ? ext_row : out;
-        topk_stream_row<BLOCK, false>(0, x + (long)blockIdx.x * ld, ld, n, k, tmp, 0, nullptr, 0, nullptr, 0, 0,
-                                      nullptr, 1, 0);
-        if (!ext_row) return;
-        __syncthreads();
-        if (tid < k) {
-            const uint32_t j = (uint32_t)ext_row[tid];
-            win[tid] = ((uint64_t)j << 32) | ord_key(xr[j]);
-        }
-        __syncthreads();
-        emit_sources(win, k, S, out, ext_row, cls, tid);
-        return;
-    }
+}
 
-    uint32_t need;
-    const uint32_t tau = kth_largest(lk, cnt, bound, k, need);
-    // winners above tau; of the entries equal to tau the `need` lowest indices
-    for (int r = tid; r < cnt; r += BLOCK) {
-        const uint32_t key = lk[r];
-        if (key > tau) win[atomicAdd(&n_win, 1)] = ((uint64_t)lj[r] << 32) | key;
-        else if (key == tau) atomicAdd(&n_eq, 1);
-    }
+// ---- few winners (source nodes) -------------------------------------------------------
+// The k <= kSmallK best entries of a row, split into the S best and the X = k - S next best, each
+// group in ascending index order (Eq. 2).  One workgroup of 16 waves per row.  A lower bound of the
+// k-th largest key comes almost for free: every thread takes the largest key it owns, one
+// histogram of those 1024 maxima finds the bin of the k-th largest of them, and at least k entries
+// reach its lower edge.  The entries that do (k and a few dozen more) go to a list of (key, index)
+// pairs; every thread ranks one of them against all others, which gives both the winners and their
+// split, and counts the winners of lower index for its place.  What bounds it is the chain of memory
+// and LDS round trips.  Rows of up to 32768 entries are read once into registers, longer ones
+// twice.  (A group bound through LDS maxima, a radix sweep and one wave that finished the row
+// alone, bit by bit: 21.4 us with k = 96 and 16.4 us with k = 64 for 8 rows of 32736 entries;
+// this way 9.8 and 8.2 us; 256 rows of
+// 131008 entries with k = 192 and k = 128: 72 and 58 us before, 56 and 49 us now.)
+constexpr int kSmallK = 256;       // largest k
+constexpr int kPickBlock = 1024;
+constexpr int kPickList = 1024;    // entries the list takes: one per thread
+
+struct PickLds {
+    __align__(16) uint32_t hist[2 * kPickBlock];
+    __align__(16) uint64_t list[kPickList];   // (key << 32) | ~index: larger = first
+    __align__(16) uint32_t win[kSmallK];      // indices of the winners by rank, then of each group in order
+    uint32_t part[2][kPickBlock / kWave], lo[kPickBlock / kWave], hi[kPickBlock / kWave], out[3], cnt;
+};
+
+// Lower edge of the bin (of 2048 over their range) that holds the k-th largest of the threads'
+// values; a thread without a value passes 0.  `hist` is zero on entry.  Contains barriers.
+__device__ __forceinline__ uint32_t kth_value_bound(uint32_t best, int k, PickLds &L, int tid, int lane, int wv)
+{
+    constexpr int NW = kPickBlock / kWave;
+    const uint32_t mn = wave_min_u32(best ? best : 0xffffffffu), mx = wave_max_u32(best);
+    if (lane == 0) { L.lo[wv] = mn; L.hi[wv] = mx; }
     __syncthreads();
-    const int ne = n_eq, base = n_win;
+    const uint32_t kmin = wave_min_u32(L.lo[lane & (NW - 1)]), kmax = wave_max_u32(L.hi[lane & (NW - 1)]);
+    const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > 11 ? bits - 11 : 0;
+    if (best) atomicAdd(&L.hist[(best - kmin) >> shift], 1u);
     __syncthreads();
-    for (int r = tid; r < cnt; r += BLOCK) {
-        if (lk[r] == tau) {
-            const uint32_t mine = lj[r];
-            if (ne == (int)need) {
-                win[atomicAdd(&n_win, 1)] = ((uint64_t)mine << 32) | tau;
-            } else {
-                uint32_t rank = 0;
-                for (int u = 0; u < cnt; ++u) rank += (lk[u] == tau) & (lj[u] < mine);
-                if (rank < need) win[base + rank] = ((uint64_t)mine << 32) | tau;
-            }
+    find_bin_block<kPickBlock>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+    return kmin + (L.out[0] << shift);
+}
+
+// The list of cnt >= k entries (zeros behind them) -> the row's outputs.  Ends with win[] = the S
+// sources, then the X others, each ascending, and a barrier.
+__device__ __forceinline__ void emit_winners(PickLds &L, int cnt, int k, int S, int32_t *src_out, int32_t *ext_out,
+                                             int tid)
+{
+    if (tid < cnt) {
+        const uint64_t mine = L.list[tid];
+        int rank = 0;
+        for (int u = 0; u < cnt; u += 2) {
+            const ulonglong2 o = *reinterpret_cast<const ulonglong2 *>(L.list + u);
+            rank += (o.x > mine) + (o.y > mine);
         }
+        if (rank < k) L.win[rank] = ~(uint32_t)mine;
     }
     __syncthreads();
-    emit_sources(win, k, S, out, ext_row, cls, tid);   // ascending index order
+    uint32_t mine = 0;
+    int at = 0;
+    if (tid < k) {
+        mine = L.win[tid];
+        at = tid < S ? 0 : S;
+        for (int u = 0; u < k; ++u) at += L.win[u] < mine && (u < S) == (tid < S);
+    }
+    __syncthreads();
+    if (tid < k) {
+        L.win[at] = mine;
+        if (at < S) src_out[at] = (int32_t)mine;
+        if (ext_out) ext_out[at] = (int32_t)mine;
+    }
+    __syncthreads();
+}
+
+// Masses of equal values: the general algorithm picks the k entries, the list holds just them.
+__device__ __forceinline__ void pick_general(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
+                                             PickLds &L, int tid)
+{
+    int32_t *tmp = ext_out ? ext_out : src_out;
+    topk_stream_row<kPickBlock, false>(0, xr, n, n, k, tmp, 0, nullptr, 0, nullptr, 0, 0, nullptr, 1, 0);
+    __syncthreads();
+    const int32_t j = tid < k ? tmp[tid] : 0;
+    L.list[tid] = tid < k ? ((uint64_t)ord_key(xr[j]) << 32) | (uint32_t)~j : 0ull;
+    __syncthreads();
+    emit_winners(L, k, k, S, src_out, ext_out, tid);
+}
+
+// A row of at most ITEMS * 1024 entries.
+template <int ITEMS>
+__device__ __forceinline__ void pick_row(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
+                                         PickLds &L, int tid, int lane, int wv)
+{
+    // the loads of the row leave together: unconditional, clamped, pinned before the first use
+    float val[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * kPickBlock + tid, n - 1)];
+    L.hist[tid] = 0;
+    L.hist[tid + kPickBlock] = 0;
+    L.list[tid] = 0;
+    if (tid == 0) L.cnt = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));
+    uint32_t key[ITEMS], best = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        key[i] = i * kPickBlock + tid < n ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
+        best = max(best, key[i]);
+    }
+    uint32_t bound = kth_value_bound(best, k, L, tid, lane, wv);
+    for (int turn = 0;; ++turn) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (key[i] >= bound) {
+                const uint32_t at = atomicAdd(&L.cnt, 1u);
+                if (at < (uint32_t)kPickList)
+                    L.list[at] = ((uint64_t)key[i] << 32) | (uint32_t)~(i * kPickBlock + tid);
+            }
+        __syncthreads();
+        const int cnt = (int)L.cnt;
+        if (cnt <= kPickList) {   // (the same for every thread, like all branches here)
+            emit_winners(L, cnt, k, S, src_out, ext_out, tid);
+            return;
+        }
+        if (turn) break;
+        // too many entries reach the bound: one histogram over all of them raises it
+        __syncthreads();
+        uint32_t mx = wave_max_u32(best);
+        if (lane == 0) L.hi[wv] = mx;
+        L.hist[tid] = 0;
+        L.hist[tid + kPickBlock] = 0;
+        L.list[tid] = 0;
+        if (tid == 0) L.cnt = 0;
+        __syncthreads();
+        mx = wave_max_u32(L.hi[lane & (kPickBlock / kWave - 1)]);
+        const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > 11 ? bits - 11 : 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (key[i] >= bound) atomicAdd(&L.hist[(key[i] - bound) >> shift], 1u);
+        __syncthreads();
+        find_bin_block<kPickBlock>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+        bound += L.out[0] << shift;
+    }
+    pick_general(xr, n, k, S, src_out, ext_out, L, tid);
+}
+
+// A longer row: read twice, in batches of 16 loads per thread.
+__device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
+                                              PickLds &L, int tid, int lane, int wv)
+{
+    L.hist[tid] = 0;
+    L.hist[tid + kPickBlock] = 0;
+    L.list[tid] = 0;
+    if (tid == 0) L.cnt = 0;
+    float best = -INFINITY;     // (floats order as their keys do)
+    row_sweep<16>(xr, n, tid, wv, [&](int, float v, bool in) { best = fmaxf(best, in ? v : -INFINITY); });
+    const uint32_t bound = kth_value_bound(ord_key(best), k, L, tid, lane, wv);
+    const float fbound = key_to_float(bound);
+    // (bound is the lower edge of a bin and need not be a number's key: below the smallest thread
+    // maximum it cannot lie, and between two numbers the comparison of floats is still that of keys)
+    row_sweep<16>(xr, n, tid, wv, [&](int word, float v, bool in) {
+        if (in && v >= fbound) {
+            const uint32_t at = atomicAdd(&L.cnt, 1u);
+            if (at < (uint32_t)kPickList)
+                L.list[at] = ((uint64_t)ord_key(v) << 32) | (uint32_t)~(word * kWave + lane);
+        }
+    });
+    __syncthreads();
+    const int cnt = (int)L.cnt;
+    if (cnt <= kPickList) emit_winners(L, cnt, k, S, src_out, ext_out, tid);
+    else pick_general(xr, n, k, S, src_out, ext_out, L, tid);
+}
+
+template <int ITEMS>   // 0: rows beyond 32768 entries
+__global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
+    const float *__restrict__ x, long ld, int n, int k, int S, int32_t *__restrict__ src_out, long src_ld,
+    int32_t *__restrict__ ext_out, long ext_ld)
+{
+    __shared__ PickLds L;
+    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const float *xr = x + (long)row * ld;
+    int32_t *src = src_out + (long)row * src_ld, *ext = ext_out ? ext_out + (long)row * ext_ld : nullptr;
+    if constexpr (ITEMS > 0) pick_row<ITEMS>(xr, n, k, S, src, ext, L, tid, lane, wv);
+    else pick_row_long(xr, n, k, S, src, ext, L, tid, lane, wv);
 }
 
 // ---- budgeted selection ---------------------------------------------------------------
@@ -997,7 +763,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, LayerPlan plan)
 {
-    constexpr int NW = kBudgetBlock / kWave, U = 16, SAMPLE = 4;
+    constexpr int NW = kBudgetBlock / kWave, SAMPLE = 4;
     extern __shared__ __align__(16) uint32_t dyn[];
     __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
     __shared__ uint32_t s_part[2][NW], s_min[NW], s_max[NW], s_out[3], s_cnt;
@@ -1035,36 +801,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     kmin = wave_min_u32(s_min[lane & (NW - 1)]);
     kmax = wave_max_u32(s_max[lane & (NW - 1)]);
     const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > 11 ? bits - 11 : 0;
-    // The whole row in batches of U loads per thread, the next batch on its way while one is used;
-    // use(entry number of the wave / 64, value, in the row) is called by whole waves.  Only the
-    // last batches hold entries past the end.
-    const int turns = (n + kBudgetBlock - 1) / kBudgetBlock, whole = n / kBudgetBlock / U * U;
-    auto sweep = [&](auto &&use) {
-        float a[U], b[U];
-        auto load = [&](float (&v)[U], int i0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                v[u] = i0 < whole ? (xr + (i0 + u) * kBudgetBlock)[tid] : xr[min((i0 + u) * kBudgetBlock + tid, n - 1)];
-        };
-        auto work = [&](float (&v)[U], int i0) {
-            if (i0 < whole) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) use((i0 + u) * NW + wv, v[u], true);
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (i0 + u < turns) use((i0 + u) * NW + wv, v[u], (i0 + u) * kBudgetBlock + tid < n);
-            }
-        };
-        load(a, 0);
-        for (int i0 = 0; i0 < turns; i0 += 2 * U) {
-            load(b, i0 + U);
-            work(a, i0);
-            load(a, i0 + 2 * U);
-            work(b, i0 + U);
-        }
-    };
-    sweep([&](int, float v, bool in) {
+    row_sweep<16>(xr, n, tid, wv, [&](int, float v, bool in) {
         if (in) atomicAdd(&hist[(min(max(ord_key(v), kmin), kmax) - kmin) >> shift], 1u);
     });
     __syncthreads();
@@ -1082,7 +819,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     const uint32_t last_bin = (kmax - kmin) >> shift;
     const float flo = bin == 0 ? -INFINITY : key_to_float(kmin + (bin << shift));
     const float fhi = bin == last_bin ? INFINITY : key_to_float(kmin + (bin << shift) + ((1u << shift) - 1u));
-    sweep([&](int word, float v, bool in) {
+    row_sweep<16>(xr, n, tid, wv, [&](int word, float v, bool in) {
         const bool reach = in && v >= flo, over = reach && v > fhi;
         const uint64_t above = __ballot(over);
         if (lane == 0 && word < words) map[word] = above;
@@ -1225,29 +962,36 @@ static hipError_t launch_lds(const float *x, long ld, int n, int rows, int k, in
     return hipGetLastError();
 }
 
+static hipError_t launch_pick(const float *x, long ld, int n, int rows, int k, int S, int32_t *src, long src_ld,
+                              int32_t *ext, long ext_ld, hipStream_t st)
+{
+#define GKV_PICK(ITEMS) \
+    hipLaunchKernelGGL(pick_sources_kernel<ITEMS>, dim3(rows), dim3(kPickBlock), 0, st, x, ld, n, k, S, src, src_ld, ext, ext_ld)
+    if (n <= 1024) GKV_PICK(1);
+    else if (n <= 2048) GKV_PICK(2);
+    else if (n <= 4096) GKV_PICK(4);
+    else if (n <= 8192) GKV_PICK(8);
+    else if (n <= 16384) GKV_PICK(16);
+    else if (n <= 32768) GKV_PICK(32);
+    else GKV_PICK(0);
+#undef GKV_PICK
+    return hipGetLastError();
+}
+
 hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
                             long idx_ld, float *val_out, long val_ld, float *tau_out,
                             int append_from, int append_count, const int32_t *gate,
                             int rows_per_gate, hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;
+    if (k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate)
+        return launch_pick(x, ld, n, rows, k, k, idx_out, idx_ld, nullptr, 0, st);
     if (n <= 4096)
         return launch_lds<256, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
                                   append_from, append_count, gate, rows_per_gate, st);
-    const bool plain = k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate;
-    if (n <= 32768 && plain) {
-        hipLaunchKernelGGL(pick_sources_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k, idx_out,
-                           idx_ld, (int32_t *)nullptr, 0L);
-        return hipGetLastError();
-    }
     if (n <= 32768)
         return launch_lds<1024, 11>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
                                     append_from, append_count, gate, rows_per_gate, st);
-    if (plain) {
-        hipLaunchKernelGGL(topk_rows_long_smallk_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, k, k,
-                           idx_out, idx_ld, (int32_t *)nullptr, 0L);
-        return hipGetLastError();
-    }
     hipLaunchKernelGGL((topk_rows_stream_kernel<1024, false>), dim3(gate && rows > 1024 ? 1024 : rows), dim3(1024),
                        0, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
                        append_count, gate, rows_per_gate, 0);
@@ -1287,13 +1031,7 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
 {
     if (rows <= 0) return hipSuccess;
     if (S + X > n || S + X > kSmallK) return hipErrorInvalidValue;
-    if (n <= 32768)
-        hipLaunchKernelGGL(pick_sources_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, S + X, S, src,
-                           (long)S, ext, (long)(S + X));
-    else
-        hipLaunchKernelGGL(topk_rows_long_smallk_kernel<1024>, dim3(rows), dim3(1024), 0, st, x, ld, n, S + X, S,
-                           src, (long)S, ext, (long)(S + X));
-    return hipGetLastError();
+    return launch_pick(x, ld, n, rows, S + X, S, src, S, ext, S + X, st);
 }
 
 // Row length up to which the budgeted selection keeps a bitmap of the row in LDS.
