@@ -117,125 +117,163 @@ __device__ __forceinline__ void bitonic_sort_lds(uint64_t *keys, int npad, int l
     __syncthreads();
 }
 
-// Eq. 5 for one round, S*m <= 4096.  One workgroup per head, no sort and no float
-// atomics.  Every (source slot, node, edge) triple t finds its node's cell in an
-// LDS hash table (open addressing; integer compare-and-swap claims a cell).  Then
-// the triples of a node are peeled off in ascending t, one per pass: all pending
-// triples post their t with an integer min, the one that reads its own t back
-// multiplies its factor into the cell's product -- it is the cell's only writer in
-// that pass -- and retires.  Sources are stored in ascending index order, so the
-// product is Eq. 5's with a fixed floating-point order whatever the thread timing.
-// Most nodes have a single triple; the number of passes is the largest number of
-// sources that share one neighbour.  Two sets of min cells alternate so that a
-// winner can reset its cell without a third barrier per pass.
-constexpr int kDecayThreads = 512;
-constexpr int kDecayPer = 4096 / kDecayThreads;
-constexpr uint32_t kNoNode = 0xffffffffu;
+// Eq. 5 for one round, S*m <= 16384.  One workgroup per head, no sort and no float atomics.  Every
+// (source slot, node, edge) triple t finds its node's cell in an LDS hash table (open addressing; an
+// integer compare-and-swap claims a cell), and the triples of a node form a chain: the cell holds
+// the last one that came, next[] the one before it.  The thread whose triple ends up at the head of
+// a chain multiplies the chain's factors in ascending t -- sources are stored in ascending index
+// order, so the product is Eq. 5's with a fixed floating-point order whatever the order the chain
+// was built in -- and writes the node's score once.  Most chains have one link; a longer one is
+// walked once per kLinks links.  What bounds it is latency: three dependent loads and one LDS round trip.
+// (A radix sort of the triples: 12.5 us for 8 heads of 2048 triples, 19 us for 256; this way 7.7 and
+// 13 us.)
+// Cell: node and triple in one word, 32 bits (node < 2^18) or 64.
+constexpr int kTripleBits = 14;   // triple ids below 16384
+constexpr uint32_t kChainEnd = 0xffffu;
+constexpr int kLinks = 8;         // triples of a chain that one walk puts in order
 
-__global__ __launch_bounds__(kDecayThreads) void decay_hash_kernel(
-    float *__restrict__ scores, int P, int count, int table_log2, const int32_t *__restrict__ nbr,
+template <typename Cell> struct CellOf;
+template <> struct CellOf<uint32_t> {
+    static constexpr int kShift = kTripleBits;
+    __device__ static __forceinline__ uint32_t swap_if_free(uint32_t *c, uint32_t v) { return atomicCAS(c, ~0u, v); }
+    __device__ static __forceinline__ uint32_t exchange(uint32_t *c, uint32_t v) { return atomicExch(c, v); }
+};
+template <> struct CellOf<uint64_t> {
+    static constexpr int kShift = 32;
+    __device__ static __forceinline__ uint64_t swap_if_free(uint64_t *c, uint64_t v)
+    {
+        return atomicCAS(reinterpret_cast<unsigned long long *>(c), ~0ull, (unsigned long long)v);
+    }
+    __device__ static __forceinline__ uint64_t exchange(uint64_t *c, uint64_t v)
+    {
+        return atomicExch(reinterpret_cast<unsigned long long *>(c), (unsigned long long)v);
+    }
+};
+
+// Bytes of dynamic LDS: cells, edges (unless they stay in global memory), links.
+template <typename Cell> size_t decay_chain_lds(int cells, int slots, bool edges)
+{
+    return (size_t)cells * sizeof(Cell) + (size_t)slots * (edges ? 4 : 0) + (size_t)slots * 2;
+}
+
+template <typename Cell, int BLOCK, int ITEMS, bool EDGES>
+__global__ __launch_bounds__(BLOCK) void decay_chain_kernel(
+    float *__restrict__ scores, int P, int count, int cells, const int32_t *__restrict__ nbr,
     const float *__restrict__ nbr_e, float alpha, int signal)
 {
-    extern __shared__ uint32_t table[];
-    const int Tn = 1 << table_log2;
-    uint32_t *cell_node = table;                               // [Tn] node of a cell
-    uint32_t *low0 = table + Tn, *low1 = table + 2 * Tn;       // [Tn] lowest pending triple, two sets
-    float *prod = reinterpret_cast<float *>(table + 3 * Tn);   // [Tn] product of the retired factors
+    // Few triples: every thread asks for its nodes' scores at once, behind the node numbers.  Many:
+    // only the heads of chains do, at the end, four at a time -- a score read is a 64-byte line for
+    // four bytes, and with 16384 triples about half the nodes occur more than once.
+    constexpr bool kEarly = ITEMS <= 4;
+    constexpr int SLOTS = BLOCK * ITEMS, SH = CellOf<Cell>::kShift, B = kEarly ? ITEMS : 4;
+    constexpr Cell kFree = ~(Cell)0;
+    extern __shared__ __align__(16) unsigned char decay_lds[];
+    Cell *cell = reinterpret_cast<Cell *>(decay_lds);                     // [cells]
+    float *edge = reinterpret_cast<float *>(cell + cells);                // [SLOTS] if EDGES
+    uint16_t *next = reinterpret_cast<uint16_t *>(edge + (EDGES ? SLOTS : 0));
     const int h = blockIdx.x, tid = threadIdx.x;
     const int32_t *nb = nbr + (long)h * count;
     const float *ne = nbr_e + (long)h * count;
     float *s = scores + (long)h * P;
 
-    uint32_t node[kDecayPer], cell[kDecayPer];
-    float fac[kDecayPer];
+    // (unconditional, clamped loads: those of a batch leave together)
+    uint32_t node[ITEMS], at[ITEMS];
+    float early[ITEMS];
 #pragma unroll
-    for (int q = 0; q < kDecayPer; ++q) {
-        const int t = q * kDecayThreads + tid;
-        const int tc = min(t, count - 1);   // (unconditional loads leave together)
-        const uint32_t nd = (uint32_t)nb[tc];
-        const float ed = ne[tc];
-        node[q] = t < count ? nd : kNoNode;
-        fac[q] = t < count ? ed : 0.f;
+    for (int q = 0; q < ITEMS; ++q) node[q] = (uint32_t)nb[min(q * BLOCK + tid, count - 1)];
+    if (EDGES) {
+        float e[ITEMS];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) e[q] = ne[min(q * BLOCK + tid, count - 1)];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) edge[q * BLOCK + tid] = e[q];
     }
-    // the sign of each node's score decides the direction of its factors; these loads are in
-    // flight while the table is set up
-    static_assert(kDecayPer == 8, "the loads below are pinned eight at a time");
-    float sj[kDecayPer];
+    for (int i = tid; i < cells; i += BLOCK) cell[i] = kFree;
 #pragma unroll
-    for (int q = 0; q < kDecayPer; ++q) sj[q] = s[node[q] != kNoNode ? node[q] : 0u];   // (unconditional)
-    asm volatile("" : "+v"(sj[0]), "+v"(sj[1]), "+v"(sj[2]), "+v"(sj[3]), "+v"(sj[4]), "+v"(sj[5]), "+v"(sj[6]),
-                      "+v"(sj[7]));
-#pragma unroll
-    for (int q = 0; q < kDecayPer; ++q)
-        fac[q] = node[q] != kNoNode ? signal_factor(fac[q], alpha, signal, sj[q] < 0.f) : 1.0f;
-    for (int i = tid; i < Tn; i += kDecayThreads) {
-        cell_node[i] = kNoNode;
-        low0[i] = kNoNode;
-        low1[i] = kNoNode;
-        prod[i] = 1.0f;
-    }
+    for (int q = 0; q < ITEMS; ++q) early[q] = kEarly ? s[node[q]] : 0.f;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kDecayPer; ++q) {
-        cell[q] = 0;
-        if (node[q] != kNoNode) {
-            uint32_t c = (node[q] * 2654435761u) >> (32 - table_log2);
-            while (true) {   // the table has at least twice as many cells as triples
-                const uint32_t prev = atomicCAS(&cell_node[c], kNoNode, node[q]);
-                if (prev == kNoNode || prev == node[q]) break;
-                c = (c + 1) & (Tn - 1);
+    for (int q = 0; q < ITEMS; ++q) {
+        const int t = q * BLOCK + tid;
+        at[q] = 0;
+        if (t < count) {
+            const Cell mine = ((Cell)node[q] << SH) | (Cell)t;
+            uint32_t c = (uint32_t)(((uint64_t)(node[q] * 2654435761u) * (uint32_t)cells) >> 32);
+            uint32_t link = kChainEnd;
+            while (true) {   // (there are more cells than triples)
+                const Cell prev = CellOf<Cell>::swap_if_free(&cell[c], mine);
+                if (prev == kFree) break;
+                if ((uint32_t)(prev >> SH) == node[q]) {   // the node's cell: a cell never changes its node
+                    link = (uint32_t)(CellOf<Cell>::exchange(&cell[c], mine) & (((Cell)1 << kTripleBits) - 1));
+                    break;
+                }
+                c = c + 1 < (uint32_t)cells ? c + 1 : 0u;
             }
-            cell[q] = c;
+            next[t] = (uint16_t)link;
+            at[q] = c;
         }
     }
     __syncthreads();
-    for (int pass = 0;; ++pass) {
-        uint32_t *low = (pass & 1) ? low1 : low0;
 #pragma unroll
-        for (int q = 0; q < kDecayPer; ++q)
-            if (node[q] != kNoNode) atomicMin(&low[cell[q]], (uint32_t)(q * kDecayThreads + tid));
-        __syncthreads();
-        int left = 0;
+    for (int q0 = 0; q0 < ITEMS; q0 += B) {
+        bool head[B];
+        float sj[B], e[B];
 #pragma unroll
-        for (int q = 0; q < kDecayPer; ++q) {
-            if (node[q] == kNoNode) continue;
-            if (low[cell[q]] == (uint32_t)(q * kDecayThreads + tid)) {
-                prod[cell[q]] *= fac[q];
-                node[q] = kNoNode;
+        for (int b = 0; b < B; ++b) {
+            const int q = q0 + b, t = q * BLOCK + tid;
+            head[b] = t < count && cell[at[q]] == (((Cell)node[q] << SH) | (Cell)t);
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int q = q0 + b, t = q * BLOCK + tid;
+            sj[b] = kEarly ? early[q] : s[head[b] ? node[q] : 0u];
+            e[b] = EDGES ? edge[t] : ne[head[b] ? t : 0];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int q = q0 + b, t = q * BLOCK + tid;
+            if (!head[b]) continue;
+            if (signal == 2) { s[node[q]] = -INFINITY; continue; }
+            const bool neg = sj[b] < 0.f;
+            float f = 1.0f;
+            if (next[t] == kChainEnd) {
+                f *= signal_factor(e[b], alpha, signal, neg);
             } else {
-                left = 1;
+                // the chain's triples in ascending order, the next kLinks of them by each walk
+                for (uint32_t from = 0, last = 0; last != kChainEnd;) {
+                    uint32_t low[kLinks];
+#pragma unroll
+                    for (int i = 0; i < kLinks; ++i) low[i] = kChainEnd;
+                    for (uint32_t u = (uint32_t)t; u != kChainEnd; u = next[u]) {
+                        uint32_t x = u >= from ? u : kChainEnd;
+#pragma unroll
+                        for (int i = 0; i < kLinks; ++i) {
+                            const uint32_t keep = min(low[i], x);
+                            x = max(low[i], x);
+                            low[i] = keep;
+                        }
+                    }
+                    float el[kLinks];
+#pragma unroll
+                    for (int i = 0; i < kLinks; ++i) {
+                        const uint32_t u = min(low[i], (uint32_t)count - 1u);
+                        el[i] = EDGES ? edge[u] : ne[u];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kLinks; ++i)
+                        if (low[i] != kChainEnd) f *= signal_factor(el[i], alpha, signal, neg);
+                    last = low[kLinks - 1];
+                    from = last + 1;
+                }
             }
+            s[node[q]] = sj[b] * f;
         }
-        // every compare above is done before a winner resets its cell below; the set
-        // is next used two passes on, behind the barriers of the pass in between
-        const int more = __syncthreads_or(left);
-#pragma unroll
-        for (int q = 0; q < kDecayPer; ++q)
-            if (node[q] == kNoNode && low[cell[q]] == (uint32_t)(q * kDecayThreads + tid))
-                low[cell[q]] = kNoNode;
-        if (!more) break;
-    }
-    __syncthreads();
-    for (int base = 0; base < Tn; base += kDecayThreads * 4) {
-        uint32_t nd[4];
-        float sv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = base + q * kDecayThreads + tid;
-            nd[q] = i < Tn ? cell_node[i] : kNoNode;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sv[q] = nd[q] != kNoNode ? s[nd[q]] : 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (nd[q] != kNoNode)
-                s[nd[q]] = signal == 2 ? -INFINITY : sv[q] * prod[base + q * kDecayThreads + tid];
     }
 }
 
-// 4096 < S*m <= 16384: the triples are sorted by (node, slot) in LDS (128 KiB of
-// keys); the first triple of every node multiplies that node's factors in ascending
-// slot order and writes the node's score once.  Edge weights come from global memory.
+// 8192 < S*m <= 16384 and nodes beyond 2^18: the triples are sorted by (node, slot) in LDS (128 KiB of
+// keys); the first triple of every node multiplies that node's factors in ascending slot order and
+// writes the node's score once.  Edge weights come from global memory.
 template <int NT>
 __global__ __launch_bounds__(NT) void decay_sorted_kernel(
     float *__restrict__ scores, int P, int count, int npad, const int32_t *__restrict__ nbr,
@@ -267,7 +305,7 @@ __global__ __launch_bounds__(NT) void decay_sorted_kernel(
 }
 
 // The same update by a radix sort, for up to BLOCK * ITEMS triples whose (node, triple)
-// pair fits 32 bits (node < 2^(32 - kTripleBits)).  Key = node << kTripleBits | triple id.
+// pair fits 32 bits.  Key = node << kTripleBits | triple id.
 // The triple ids ascend in the input, and a least-significant-digit radix sort is stable, so
 // sorting by the node bits alone (6 bits a pass) leaves the triples of a node in ascending
 // id, i.e. ascending source order -- Eq. 5's fixed order.  Per pass every wave ranks the keys of
@@ -276,8 +314,6 @@ __global__ __launch_bounds__(NT) void decay_sorted_kernel(
 // block-wide scan of the (digit, wave) counters gives every key its place; three barriers a
 // pass.  Then the first triple of every node multiplies that node's factors and writes its
 // score once.  Two key buffers in LDS (8 bytes per triple in all).
-constexpr int kTripleBits = 14;   // triple ids below 16384
-
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void decay_radix_kernel(
     float *__restrict__ scores, int P, int count, int node_bits, const int32_t *__restrict__ nbr,
@@ -473,52 +509,65 @@ hipError_t launch_pool_group(const float *votes, int Hkv, int Gv, int P, int poo
     return hipGetLastError();
 }
 
+template <typename Cell, int BLOCK, int ITEMS, bool EDGES>
+static hipError_t launch_decay_chain(float *scores, int Hkv, int P, int count, const int32_t *nbr,
+                                     const float *nbr_e, float alpha, int signal, hipStream_t st)
+{
+    const int slots = BLOCK * ITEMS;
+    const int cells = slots < 8192 ? 2 * slots : slots + slots / 2;   // LDS holds no twice as many beyond
+    const size_t lds = decay_chain_lds<Cell>(cells, slots, EDGES);
+    if (lds > 65536 && !allow_big_lds((const void *)decay_chain_kernel<Cell, BLOCK, ITEMS, EDGES>))
+        return hipGetLastError();
+    hipLaunchKernelGGL((decay_chain_kernel<Cell, BLOCK, ITEMS, EDGES>), dim3(Hkv), dim3(BLOCK), lds, st, scores, P,
+                       count, cells, nbr, nbr_e, alpha, signal);
+    return hipGetLastError();
+}
+
 hipError_t launch_decay(float *scores, int Hkv, int P, int S, int m, const int32_t *nbr,
                         const float *nbr_e, float alpha, int signal, hipStream_t st)
 {
     const long count = (long)S * m;
-    long npad = 512;
-    while (npad < count) npad <<= 1;
-    if (count <= 2048 && P <= (1 << (32 - kTripleBits))) {
-        // few edges: the two-items-per-thread sort beats the hash table by a few microseconds
-        int node_bits = 1;
-        while ((1L << node_bits) < P) ++node_bits;
-        hipLaunchKernelGGL((decay_radix_kernel<1024, 2>), dim3(Hkv), dim3(1024), (size_t)2048 * 8, st, scores, P,
-                           (int)count, node_bits, nbr, nbr_e, alpha, signal);
-    } else if (count <= 4096) {
-        int table_log2 = 10;
-        while ((1L << table_log2) < 2 * count) ++table_log2;
-        const size_t lds = ((size_t)16) << table_log2;
-        if (lds > 65536 && !allow_big_lds((const void *)decay_hash_kernel, 8192 * 16)) return hipGetLastError();
-        hipLaunchKernelGGL(decay_hash_kernel, dim3(Hkv), dim3(kDecayThreads), lds, st, scores, P,
-                           (int)count, table_log2, nbr, nbr_e, alpha, signal);
-    } else if (count <= 16384 && P <= (1 << (32 - kTripleBits))) {
-        int node_bits = 1;
-        while ((1L << node_bits) < P) ++node_bits;
-        if (!allow_big_lds((const void *)decay_radix_kernel<1024, 16>, 16384 * 8) ||
-            !allow_big_lds((const void *)decay_radix_kernel<1024, 8>, 16384 * 8))
+    const bool narrow = P < (1 << (32 - kTripleBits));   // node and triple id share 32 bits (all ones is a free cell)
+#define GKV_DECAY(CELL, BLOCK, ITEMS, EDGES) \
+    return launch_decay_chain<CELL, BLOCK, ITEMS, EDGES>(scores, Hkv, P, (int)count, nbr, nbr_e, alpha, signal, st)
+    if (narrow) {
+        // Many triples in many long rows: the chains' scattered score reads queue up and the sort,
+        // which reads a node's score once, wins (us, sort / chains: 256 heads of 32736 nodes with 8192
+        // triples 45 / 52, with 16384 87 / 106; 64 heads of 131040 nodes 46 / 55 and 75 / 92).  With few
+        // heads or short rows the chains do (8 heads of 32736 nodes 32 / 28 and 60 / 45; 256 heads of 8160
+        // nodes 48 / 22 and 139 / 46), and up to 4096 triples always (256 heads of 32736 nodes 30 / 25).
+        if (count > 4096 && count <= 16384 && P > 16384 && Hkv >= 32) {
+            int node_bits = 1;
+            while ((1L << node_bits) < P) ++node_bits;
+            if (!allow_big_lds((const void *)decay_radix_kernel<1024, 16>, 16384 * 8)) return hipGetLastError();
+            if (count <= 8192)
+                hipLaunchKernelGGL((decay_radix_kernel<1024, 8>), dim3(Hkv), dim3(1024), (size_t)8192 * 8, st, scores, P,
+                                   (int)count, node_bits, nbr, nbr_e, alpha, signal);
+            else
+                hipLaunchKernelGGL((decay_radix_kernel<1024, 16>), dim3(Hkv), dim3(1024), (size_t)16384 * 8, st, scores, P,
+                                   (int)count, node_bits, nbr, nbr_e, alpha, signal);
             return hipGetLastError();
-        if (count <= 8192)
-            hipLaunchKernelGGL((decay_radix_kernel<1024, 8>), dim3(Hkv), dim3(1024), (size_t)8192 * 8, st, scores, P,
-                               (int)count, node_bits, nbr, nbr_e, alpha, signal);
-        else
-            hipLaunchKernelGGL((decay_radix_kernel<1024, 16>), dim3(Hkv), dim3(1024), (size_t)16384 * 8, st, scores, P,
-                               (int)count, node_bits, nbr, nbr_e, alpha, signal);
-    } else if (npad <= 16384) {
-        // 128 KiB of dynamic LDS
-        if (npad * 8 > 65536 && !allow_big_lds((const void *)decay_sorted_kernel<1024>, 16384 * 8))
-            return hipGetLastError();
-        // 16 waves sort 16384 keys four times as fast as 4; 8192 keys are 64 pairs a wave
-        if (npad >= 8192)
-            hipLaunchKernelGGL(decay_sorted_kernel<1024>, dim3(Hkv), dim3(1024), (size_t)npad * 8, st, scores,
-                               P, (int)count, (int)npad, nbr, nbr_e, alpha, signal);
-        else
-            hipLaunchKernelGGL(decay_sorted_kernel<256>, dim3(Hkv), dim3(256), (size_t)npad * 8, st, scores,
-                               P, (int)count, (int)npad, nbr, nbr_e, alpha, signal);
+        }
+        if (count <= 256) GKV_DECAY(uint32_t, 256, 1, true);
+        if (count <= 1024) GKV_DECAY(uint32_t, 1024, 1, true);
+        if (count <= 2048) GKV_DECAY(uint32_t, 1024, 2, true);
+        if (count <= 4096) GKV_DECAY(uint32_t, 1024, 4, true);
+        if (count <= 8192) GKV_DECAY(uint32_t, 1024, 8, true);
+        if (count <= 16384) GKV_DECAY(uint32_t, 1024, 16, false);   // (its edges would not fit beside the cells)
     } else {
-        hipLaunchKernelGGL(decay_sequential_kernel, dim3(Hkv), dim3(1024), 0, st, scores, P, S, m,
-                           nbr, nbr_e, alpha, signal);
+        if (count <= 4096) GKV_DECAY(uint64_t, 1024, 4, true);
+        if (count <= 8192) GKV_DECAY(uint64_t, 1024, 8, true);
+        if (count <= 16384) {
+            // 16 waves sort the 16384 keys of 128 KiB of dynamic LDS
+            if (!allow_big_lds((const void *)decay_sorted_kernel<1024>, 16384 * 8)) return hipGetLastError();
+            hipLaunchKernelGGL(decay_sorted_kernel<1024>, dim3(Hkv), dim3(1024), (size_t)16384 * 8, st, scores, P,
+                               (int)count, 16384, nbr, nbr_e, alpha, signal);
+            return hipGetLastError();
+        }
     }
+#undef GKV_DECAY
+    hipLaunchKernelGGL(decay_sequential_kernel, dim3(Hkv), dim3(1024), 0, st, scores, P, S, m, nbr, nbr_e, alpha,
+                       signal);
     return hipGetLastError();
 }
 

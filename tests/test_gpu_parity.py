@@ -1103,3 +1103,40 @@ def test_budgeted_selection_row_lengths(oracle, P, k):
     idx = gk.graphkv_select(p, torch.from_numpy(s).cuda()).cpu().numpy()
     ref, _ = oracle.select(s.astype(np.float64), P + w, w, k + w)
     assert np.array_equal(idx, ref)
+
+
+@pytest.mark.parametrize("signal", [0, 1, 2])
+@pytest.mark.parametrize("S,m,P", [(1, 1, 9), (16, 16, 400), (20, 60, 1200), (64, 32, 3000), (60, 60, 2000), (80, 90, 2500),
+                                   (128, 128, 2500), (40, 200, (1 << 18) + 50), (90, 90, 1 << 18), (128, 100, (1 << 18) + 9),
+                                   (130, 130, 1500), (100, 60, 16390), (128, 128, 16390)])
+def test_update_products_in_source_order(S, m, P, signal):
+    """Eq. 5's update at the edges of its kernels (256 to 16384 triples, nodes on both sides of 2^18,
+    beyond both) on scores of either sign.  Exact copies of one key make every source that is a copy
+    pick the same neighbours, so that products have up to S factors; the product must be the one of
+    the call's own edges in ascending source order, in 32 bits, bit for bit (alpha 1: a factor is one
+    rounded addition)."""
+    say(f"update S={S} m={m} P={P} signal={signal}")
+    H, d, w = 32 if P == 16390 else 2, 8, 3      # (32 heads of long rows: the sorting kernel)
+    rng = np.random.default_rng(S * m + P)
+    K = rng.standard_normal((H, P + w, d)).astype(np.float32)
+    K[:, rng.choice(P, size=min(P // 2, 2 * m + S), replace=False)] = K[:, :1]
+    s0 = rng.standard_normal((H, P)).astype(np.float32)
+    s0[:, rng.choice(P, size=S, replace=False)] += 20.0
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, budget=w + 1, n_sources=S,
+                  n_neighbors=m, rounds=1, dtype=gk.FP32, signal=signal)
+    sd = torch.from_numpy(s0.copy()).cuda()
+    nbr = torch.empty((1, H, S, m), dtype=torch.int32, device="cuda")
+    ev = torch.empty((1, H, S, m), dtype=torch.float32, device="cuda")
+    gk.graphkv_propagate(p, torch.from_numpy(K).cuda(), sd, None, nbr, ev)
+    got, nbr, ev = sd.cpu().numpy(), nbr.cpu().numpy()[0], ev.cpu().numpy()[0]
+    one = np.float32(1.0)
+    for h in range(H):
+        f = np.ones(P, dtype=np.float32)
+        for a in range(S):
+            plus = (signal == 1) != (s0[h, nbr[h, a]] < 0)
+            f[nbr[h, a]] *= np.where(plus, one + ev[h, a], one - ev[h, a]).astype(np.float32)
+        want = (s0[h] * f).astype(np.float32)
+        if signal == 2:
+            want = s0[h].copy()
+            want[np.unique(nbr[h])] = -np.inf
+        assert np.array_equal(got[h], want)
