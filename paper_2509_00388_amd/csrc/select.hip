@@ -416,111 +416,137 @@ __device__ __forceinline__ void row_sweep(const float *__restrict__ xr, int n, i
 // alone, bit by bit: 21.4 us with k = 96 and 16.4 us with k = 64 for 8 rows of 32736 entries;
 // this way 9.8 and 8.2 us; 256 rows of
 // 131008 entries with k = 192 and k = 128: 72 and 58 us before, 56 and 49 us now.)
+//
+// The same code takes the m best edges of a source from its row of the dense edge block (Eq. 3): 256
+// threads per row of up to 8192 edges, no split, the edges' values beside their indices.  (Three LDS
+// histogram sweeps per row: 14.0 us for 256 rows of 4064 edges with m = 8 and 22.5 us for 512 rows of
+// 8160 with m = 16; this way 5.9 and 7.5 us.)
 constexpr int kSmallK = 256;       // largest k
 constexpr int kPickBlock = 1024;
-constexpr int kPickList = 1024;    // entries the list takes: one per thread
+constexpr int kPickList = 1024;    // entries the list takes
 
-struct PickLds {
-    __align__(16) uint32_t hist[2 * kPickBlock];
+template <int BLOCK> struct PickLds {
+    static constexpr int NW = BLOCK / kWave, kBits = BLOCK == 1024 ? 11 : 9;
+    static_assert((1 << kBits) == 2 * BLOCK, "two bins per thread");
+    __align__(16) uint32_t hist[2 * BLOCK];
     __align__(16) uint64_t list[kPickList];   // (key << 32) | ~index: larger = first
-    __align__(16) uint32_t win[kSmallK];      // indices of the winners by rank, then of each group in order
-    uint32_t part[2][kPickBlock / kWave], lo[kPickBlock / kWave], hi[kPickBlock / kWave], out[3], cnt;
+    __align__(16) uint32_t win[kSmallK];      // indices of the winners by rank
+    uint32_t val[kSmallK];                    // their keys (edges)
+    uint32_t part[2][NW], lo[NW], hi[NW], out[3], cnt;
+
+    __device__ __forceinline__ void clear(int tid)
+    {
+        hist[tid] = 0;
+        hist[tid + BLOCK] = 0;
+#pragma unroll
+        for (int u = 0; u < kPickList; u += BLOCK) list[u + tid] = 0;
+        if (tid == 0) cnt = 0;
+    }
 };
 
-// Lower edge of the bin (of 2048 over their range) that holds the k-th largest of the threads'
+// Where a row's winners go: sources (src, and ext unless null: the S best, then all k), or edges (nbr
+// and their values).
+struct PickOut {
+    int S;
+    int32_t *src, *ext;
+    float *val;
+};
+
+// Lower edge of the bin (of 2 BLOCK over their range) that holds the k-th largest of the threads'
 // values; a thread without a value passes 0.  `hist` is zero on entry.  Contains barriers.
-__device__ __forceinline__ uint32_t kth_value_bound(uint32_t best, int k, PickLds &L, int tid, int lane, int wv)
+template <int BLOCK>
+__device__ __forceinline__ uint32_t kth_value_bound(uint32_t best, int k, PickLds<BLOCK> &L, int tid, int lane, int wv)
 {
-    constexpr int NW = kPickBlock / kWave;
+    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
     const uint32_t mn = wave_min_u32(best ? best : 0xffffffffu), mx = wave_max_u32(best);
     if (lane == 0) { L.lo[wv] = mn; L.hi[wv] = mx; }
     __syncthreads();
     const uint32_t kmin = wave_min_u32(L.lo[lane & (NW - 1)]), kmax = wave_max_u32(L.hi[lane & (NW - 1)]);
-    const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > 11 ? bits - 11 : 0;
+    const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > BITS ? bits - BITS : 0;
     if (best) atomicAdd(&L.hist[(best - kmin) >> shift], 1u);
     __syncthreads();
-    find_bin_block<kPickBlock>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+    find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
     return kmin + (L.out[0] << shift);
 }
 
-// The list of cnt >= k entries (zeros behind them) -> the row's outputs.  Ends with win[] = the S
-// sources, then the X others, each ascending, and a barrier.
-__device__ __forceinline__ void emit_winners(PickLds &L, int cnt, int k, int S, int32_t *src_out, int32_t *ext_out,
-                                             int tid)
+// The list of cnt >= k entries (zeros behind them) -> the row's outputs.
+template <int BLOCK, bool EDGES>
+__device__ __forceinline__ void emit_winners(PickLds<BLOCK> &L, int cnt, int k, const PickOut &o, int tid)
 {
-    if (tid < cnt) {
-        const uint64_t mine = L.list[tid];
+    for (int t = tid; t < cnt; t += BLOCK) {
+        const uint64_t mine = L.list[t];
         int rank = 0;
         for (int u = 0; u < cnt; u += 2) {
-            const ulonglong2 o = *reinterpret_cast<const ulonglong2 *>(L.list + u);
-            rank += (o.x > mine) + (o.y > mine);
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(L.list + u);
+            rank += (v.x > mine) + (v.y > mine);
         }
-        if (rank < k) L.win[rank] = ~(uint32_t)mine;
-    }
-    __syncthreads();
-    uint32_t mine = 0;
-    int at = 0;
-    if (tid < k) {
-        mine = L.win[tid];
-        at = tid < S ? 0 : S;
-        for (int u = 0; u < k; ++u) at += L.win[u] < mine && (u < S) == (tid < S);
+        if (rank < k) {
+            L.win[rank] = ~(uint32_t)mine;
+            if (EDGES) L.val[rank] = (uint32_t)(mine >> 32);
+        }
     }
     __syncthreads();
     if (tid < k) {
-        L.win[at] = mine;
-        if (at < S) src_out[at] = (int32_t)mine;
-        if (ext_out) ext_out[at] = (int32_t)mine;
+        const uint32_t mine = L.win[tid];
+        if (EDGES) {
+            int at = 0;
+            for (int u = 0; u < k; ++u) at += L.win[u] < mine;
+            o.src[at] = (int32_t)mine;
+            o.val[at] = key_to_float(L.val[tid]);
+        } else {
+            int at = tid < o.S ? 0 : o.S;
+            for (int u = 0; u < k; ++u) at += L.win[u] < mine && (u < o.S) == (tid < o.S);
+            if (at < o.S) o.src[at] = (int32_t)mine;
+            if (o.ext) o.ext[at] = (int32_t)mine;
+        }
     }
-    __syncthreads();
 }
 
 // Masses of equal values: the general algorithm picks the k entries, the list holds just them.
-__device__ __forceinline__ void pick_general(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
-                                             PickLds &L, int tid)
+template <int BLOCK, bool EDGES>
+__device__ __forceinline__ void pick_general(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, int tid)
 {
-    int32_t *tmp = ext_out ? ext_out : src_out;
-    topk_stream_row<kPickBlock, false>(0, xr, n, n, k, tmp, 0, nullptr, 0, nullptr, 0, 0, nullptr, 1, 0);
+    int32_t *tmp = !EDGES && o.ext ? o.ext : o.src;
+    topk_stream_row<BLOCK, false>(0, xr, n, n, k, tmp, 0, EDGES ? o.val : nullptr, 0, nullptr, 0, 0, nullptr, 1, 0);
+    if (EDGES) return;
     __syncthreads();
     const int32_t j = tid < k ? tmp[tid] : 0;
-    L.list[tid] = tid < k ? ((uint64_t)ord_key(xr[j]) << 32) | (uint32_t)~j : 0ull;
+    L.list[tid] = tid < k ? ((uint64_t)ord_key(xr[j]) << 32) | (uint32_t)~j : 0ull;   // (k <= 256 <= BLOCK)
     __syncthreads();
-    emit_winners(L, k, k, S, src_out, ext_out, tid);
+    emit_winners<BLOCK, false>(L, k, k, o, tid);
 }
 
-// A row of at most ITEMS * 1024 entries.
-template <int ITEMS>
-__device__ __forceinline__ void pick_row(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
-                                         PickLds &L, int tid, int lane, int wv)
+// A row of at most ITEMS * BLOCK entries.
+template <int BLOCK, int ITEMS, bool EDGES>
+__device__ __forceinline__ void pick_row(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, int tid,
+                                         int lane, int wv)
 {
+    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
     // the loads of the row leave together: unconditional, clamped, pinned before the first use
     float val[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * kPickBlock + tid, n - 1)];
-    L.hist[tid] = 0;
-    L.hist[tid + kPickBlock] = 0;
-    L.list[tid] = 0;
-    if (tid == 0) L.cnt = 0;
+    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * BLOCK + tid, n - 1)];
+    L.clear(tid);
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));
     uint32_t key[ITEMS], best = 0;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        key[i] = i * kPickBlock + tid < n ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
+        key[i] = i * BLOCK + tid < n ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
         best = max(best, key[i]);
     }
-    uint32_t bound = kth_value_bound(best, k, L, tid, lane, wv);
+    uint32_t bound = kth_value_bound<BLOCK>(best, k, L, tid, lane, wv);
     for (int turn = 0;; ++turn) {
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
             if (key[i] >= bound) {
                 const uint32_t at = atomicAdd(&L.cnt, 1u);
-                if (at < (uint32_t)kPickList)
-                    L.list[at] = ((uint64_t)key[i] << 32) | (uint32_t)~(i * kPickBlock + tid);
+                if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key[i] << 32) | (uint32_t)~(i * BLOCK + tid);
             }
         __syncthreads();
         const int cnt = (int)L.cnt;
         if (cnt <= kPickList) {   // (the same for every thread, like all branches here)
-            emit_winners(L, cnt, k, S, src_out, ext_out, tid);
+            emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
             return;
         }
         if (turn) break;
@@ -528,39 +554,31 @@ __device__ __forceinline__ void pick_row(const float *xr, int n, int k, int S, i
         __syncthreads();
         uint32_t mx = wave_max_u32(best);
         if (lane == 0) L.hi[wv] = mx;
-        L.hist[tid] = 0;
-        L.hist[tid + kPickBlock] = 0;
-        L.list[tid] = 0;
-        if (tid == 0) L.cnt = 0;
+        L.clear(tid);
         __syncthreads();
-        mx = wave_max_u32(L.hi[lane & (kPickBlock / kWave - 1)]);
-        const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > 11 ? bits - 11 : 0;
+        mx = wave_max_u32(L.hi[lane & (NW - 1)]);
+        const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > BITS ? bits - BITS : 0;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
             if (key[i] >= bound) atomicAdd(&L.hist[(key[i] - bound) >> shift], 1u);
         __syncthreads();
-        find_bin_block<kPickBlock>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+        find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
         bound += L.out[0] << shift;
     }
-    pick_general(xr, n, k, S, src_out, ext_out, L, tid);
+    pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
 }
 
 // A longer row: read twice, in batches of 16 loads per thread.
-__device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, int S, int32_t *src_out, int32_t *ext_out,
-                                              PickLds &L, int tid, int lane, int wv)
+__device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, const PickOut &o, PickLds<kPickBlock> &L,
+                                              int tid, int lane, int wv)
 {
-    L.hist[tid] = 0;
-    L.hist[tid + kPickBlock] = 0;
-    L.list[tid] = 0;
-    if (tid == 0) L.cnt = 0;
+    L.clear(tid);
     float best = -INFINITY;     // (floats order as their keys do)
     row_sweep<16>(xr, n, tid, wv, [&](int, float v, bool in) { best = fmaxf(best, in ? v : -INFINITY); });
-    const uint32_t bound = kth_value_bound(ord_key(best), k, L, tid, lane, wv);
-    const float fbound = key_to_float(bound);
-    // (bound is the lower edge of a bin and need not be a number's key: below the smallest thread
-    // maximum it cannot lie, and between two numbers the comparison of floats is still that of keys)
+    // (the bound need not be the key of an entry; floats compare with it as their keys do)
+    const float bound = key_to_float(kth_value_bound<kPickBlock>(ord_key(best), k, L, tid, lane, wv));
     row_sweep<16>(xr, n, tid, wv, [&](int word, float v, bool in) {
-        if (in && v >= fbound) {
+        if (in && v >= bound) {
             const uint32_t at = atomicAdd(&L.cnt, 1u);
             if (at < (uint32_t)kPickList)
                 L.list[at] = ((uint64_t)ord_key(v) << 32) | (uint32_t)~(word * kWave + lane);
@@ -568,8 +586,8 @@ __device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, int
     });
     __syncthreads();
     const int cnt = (int)L.cnt;
-    if (cnt <= kPickList) emit_winners(L, cnt, k, S, src_out, ext_out, tid);
-    else pick_general(xr, n, k, S, src_out, ext_out, L, tid);
+    if (cnt <= kPickList) emit_winners<kPickBlock, false>(L, cnt, k, o, tid);
+    else pick_general<kPickBlock, false>(xr, n, k, o, L, tid);
 }
 
 template <int ITEMS>   // 0: rows beyond 32768 entries
@@ -577,12 +595,25 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
     const float *__restrict__ x, long ld, int n, int k, int S, int32_t *__restrict__ src_out, long src_ld,
     int32_t *__restrict__ ext_out, long ext_ld)
 {
-    __shared__ PickLds L;
+    __shared__ PickLds<kPickBlock> L;
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float *xr = x + (long)row * ld;
-    int32_t *src = src_out + (long)row * src_ld, *ext = ext_out ? ext_out + (long)row * ext_ld : nullptr;
-    if constexpr (ITEMS > 0) pick_row<ITEMS>(xr, n, k, S, src, ext, L, tid, lane, wv);
-    else pick_row_long(xr, n, k, S, src, ext, L, tid, lane, wv);
+    const PickOut o{S, src_out + (long)row * src_ld, ext_out ? ext_out + (long)row * ext_ld : nullptr, nullptr};
+    if constexpr (ITEMS > 0) pick_row<kPickBlock, ITEMS, false>(xr, n, k, o, L, tid, lane, wv);
+    else pick_row_long(xr, n, k, o, L, tid, lane, wv);
+}
+
+// The k best edges of each row of a dense edge block, ascending indices, with their values.
+template <int BLOCK, int ITEMS>
+__global__ __launch_bounds__(BLOCK) void pick_edges_kernel(const float *__restrict__ x, long ld, int n, int k,
+                                                           int32_t *__restrict__ idx_out, long idx_ld,
+                                                           float *__restrict__ val_out, long val_ld)
+{
+    __shared__ PickLds<BLOCK> L;
+    const long row = blockIdx.x;
+    const int tid = threadIdx.x;
+    const PickOut o{k, idx_out + row * idx_ld, nullptr, val_out + row * val_ld};
+    pick_row<BLOCK, ITEMS, true>(x + row * ld, n, k, o, L, tid, tid & 63, tid >> 6);
 }
 
 // ---- budgeted selection ---------------------------------------------------------------
@@ -986,6 +1017,20 @@ hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int
     if (rows <= 0) return hipSuccess;
     if (k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate)
         return launch_pick(x, ld, n, rows, k, k, idx_out, idx_ld, nullptr, 0, st);
+    if (k <= kSmallK && n <= 32768 && idx_out && val_out && !tau_out && append_count == 0 && !gate) {
+#define GKV_EDGES(BLOCK, ITEMS)                                                                                  \
+    hipLaunchKernelGGL((pick_edges_kernel<BLOCK, ITEMS>), dim3(rows), dim3(BLOCK), 0, st, x, ld, n, k, idx_out, idx_ld, \
+                       val_out, val_ld)
+        if (n <= 512) GKV_EDGES(256, 2);
+        else if (n <= 1024) GKV_EDGES(256, 4);
+        else if (n <= 2048) GKV_EDGES(256, 8);
+        else if (n <= 4096) GKV_EDGES(256, 16);
+        else if (n <= 8192) GKV_EDGES(256, 32);
+        else if (n <= 16384) GKV_EDGES(1024, 16);
+        else GKV_EDGES(1024, 32);
+#undef GKV_EDGES
+        return hipGetLastError();
+    }
     if (n <= 4096)
         return launch_lds<256, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
                                   append_from, append_count, gate, rows_per_gate, st);
