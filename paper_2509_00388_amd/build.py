@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgraphkv.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["api.hip", "select.hip", "generic.hip", "stages.hip", "mfma_score.hip", "mfma_cosine.hip"]
+SOURCES = ["api.hip", "select.hip", "generic.hip", "gemm.hip", "stages.hip", "mfma_score.hip", "mfma_cosine.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", 

@@ -44,6 +44,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 // H and Hq count the heads of the whole batch (layers x heads per layer).
 struct Dims {
     int L, H, Hq, G, d, N, w, P, B, S, m, T;
+    bool gemm;           // contractions the kernels for bf16 and d = 128 do not cover run in gemm.hip
     bool mfma_score, mfma_cosine, filter;
     bool speculate;      // speculative rows allowed (dropped when their scratch would not fit)
     bool keep;           // neighbour lists are kept from one round to the next
@@ -138,6 +139,7 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, c
     D.S = p->rounds > 0 ? p->n_sources : 0;
     D.m = p->rounds > 0 ? p->n_neighbors : 0;
     D.T = p->rounds;
+    D.gemm = p->impl == GRAPHKV_IMPL_AUTO;
     D.mfma_score = mfma_score_ok(p);
     D.mfma_cosine = mfma_cosine_ok(p);
     D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && mfma_filter_applies(D.P, D.m, (long)D.H * D.S);
@@ -164,8 +166,9 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.row_max = take(rows * 4);
     W.row_sum = take(rows * 4);
     // votes per query head (or row group); not needed when pass B pools and groups them itself
-    const bool votes_stay_in_lds = D.mfma_score && scoring &&
-        mfma_score_fuses_pool(D.G, D.w, p->pool_mode == GRAPHKV_POOL_MAX, p->pool_kernel);
+    const bool votes_stay_in_lds = scoring && (D.mfma_score
+        ? mfma_score_fuses_pool(D.G, D.w, p->pool_mode == GRAPHKV_POOL_MAX, p->pool_kernel)
+        : D.gemm && gemm_votes_pools(p->pool_kernel));
     W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.Hq * D.P * 4 : 0);
     // the dense edge block [heads, S, P] of the routes that materialise it; on the filter route
     // only the scratch rows of the workgroups that redo overflowed heads
@@ -174,7 +177,8 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.nbr = take((size_t)D.H * D.S * D.m * 4);
     W.nbr_e = take((size_t)D.H * D.S * D.m * 4);
     W.scores = take((size_t)D.H * D.P * 4);
-    W.part = take(D.mfma_score ? mfma_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
+    W.part = take(D.mfma_score ? mfma_score_plan(D.H, D.G * D.w, D.N).part_bytes
+                  : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
     const MfmaFilterPlan &g = D.fp;
     const size_t frows = D.filter ? (size_t)D.H * g.pitch : 0;   // rows of the per-row buffers
     W.tau = take(frows * 4);
@@ -280,11 +284,22 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
                                      p->pool_mode, (float)D.G, scores, st));
         return GRAPHKV_OK;
     }
-    GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS, launch_generic_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale,
-                                  at<float>(ws, W.logits), at<float>(ws, W.row_max),
-                                  at<float>(ws, W.row_sum), st));
-    GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_generic_votes(at<float>(ws, W.logits), at<float>(ws, W.row_max),
-                                 at<float>(ws, W.row_sum), D.Hq, D.N, D.w, votes, st));
+    float *logits = at<float>(ws, W.logits), *row_max = at<float>(ws, W.row_max), *row_sum = at<float>(ws, W.row_sum);
+    if (D.gemm) {
+        float *part = at<float>(ws, W.part);
+        GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS,
+                   launch_gemm_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale, logits, part, st));
+        if (gemm_votes_pools(p->pool_kernel)) {
+            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_votes(logits, part, D.H, D.Hq, D.N, D.w, p->pool_kernel,
+                                                                  p->pool_mode, scores, st));
+            return GRAPHKV_OK;
+        }
+        GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_merge_part(part, D.H, D.Hq, D.N, D.w, row_max, row_sum, st));
+    } else {
+        GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS, launch_generic_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale,
+                                                                   logits, row_max, row_sum, st));
+    }
+    GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_generic_votes(logits, row_max, row_sum, D.Hq, D.N, D.w, votes, st));
     GKV_LAUNCH(GRAPHKV_K_POOL, launch_pool_group(votes, D.H, D.G, D.P, p->pool_kernel, p->pool_mode, (float)D.G,
                               scores, st));
     return GRAPHKV_OK;
@@ -389,6 +404,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                 // Eq. 1: edges from every source to every node
                 if (D.mfma_cosine)
                     GKV_LAUNCH(GRAPHKV_K_COSINE, launch_mfma_cosine(Ac, Kc, D.H, D.N, D.P, D.S, src, E, nullptr, st));
+                else if (D.gemm)
+                    GKV_LAUNCH(GRAPHKV_K_GENERIC_COSINE,
+                               launch_gemm_cosine(Ac, Kc, p->dtype, D.H, D.d, D.N, D.P, D.S, src, E, st));
                 else
                     GKV_LAUNCH(GRAPHKV_K_GENERIC_COSINE,
                                launch_generic_cosine(Ac, Kc, p->dtype, D.H, D.d, D.N, D.P, D.S, src, E, st));

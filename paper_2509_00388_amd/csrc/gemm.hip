@@ -1,0 +1,459 @@
+// The two contractions of the pass on the matrix cores for any storage type and head dimension
+// (fp32, and bf16 with d other than 128 or query rows that do not fill the blocks of
+// mfma_score.hip).  fp32 inputs go through v_mfma_f32_32x32x2_f32, bf16 through
+// v_mfma_f32_32x32x16_bf16; both accumulate in fp32.
+//
+// A workgroup of four waves multiplies a tile of keys with up to 128 rows (window queries, or source
+// keys).  Rows and keys pass through LDS in pieces of 256 bytes a row, read from memory with coalesced
+// 16-byte loads and padded to 272 bytes against bank conflicts.  A lane reads 16 bytes of its row per
+// step: for bf16 the eight elements of one instruction, for fp32 four elements that feed four
+// instructions (instruction e takes element e of both half-waves: k = 8 s + e and 8 s + 4 + e, the same
+// pairs for rows and keys).  What bounds the kernels at these sizes is the matrix rate for fp32 and
+// latency for bf16.  (A scalar kernel with a workgroup per query row, each re-reading all keys: 234 us
+// for 1024 rows x 4096 fp32 keys with d = 128, 4.6 TFLOP/s; this way 23 us, 47 TFLOP/s.)
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace gkv {
+
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float acc16 __attribute__((ext_vector_type(16)));
+
+constexpr int kRowBytes = 256;              // bytes of a row staged at a time
+constexpr int kRowPitch = kRowBytes + 16;   // in LDS
+constexpr int kPieces = kRowBytes / 16;
+constexpr int kMaxSteps = kRowBytes / 32;
+
+__device__ __forceinline__ int mfma_row(int i, int hh) { return 8 * (i >> 2) + 4 * hh + (i & 3); }
+
+// acc += (32 rows of a) x (32 rows of b)^T over one step (32 bytes of every row).
+template <typename T> __device__ __forceinline__ void mfma_step(const uint4 &a, const uint4 &b, acc16 &acc);
+template <> __device__ __forceinline__ void mfma_step<float>(const uint4 &a, const uint4 &b, acc16 &acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+}
+template <> __device__ __forceinline__ void mfma_step<uint16_t>(const uint4 &a, const uint4 &b, acc16 &acc)
+{
+    union { uint4 u; bf16x8_t v; } x{a}, y{b};
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, y.v, acc, 0, 0, 0);
+}
+
+template <typename T> __device__ __forceinline__ float sum_squares(const uint4 &v, float s)
+{
+    float t[Elem<T>::kPerVec];
+    Elem<T>::unpack(v, t);
+#pragma unroll
+    for (int e = 0; e < Elem<T>::kPerVec; ++e) s = fmaf(t[e], t[e], s);
+    return s;
+}
+
+// ROWS rows of row_bytes bytes each (row(r) = address of row r) -> LDS, bytes c0 .. c0 + 255 of each,
+// zeros past the end of a row.  Four loads in flight per thread.
+template <int ROWS, typename Row>
+__device__ __forceinline__ void stage_rows(unsigned char *lds, int c0, int row_bytes, int tid, Row &&row)
+{
+    static_assert(ROWS * kPieces % (256 * 2) == 0, "pieces per thread");
+    constexpr int PER = ROWS * kPieces / 256, B = PER < 4 ? PER : 4;
+#pragma unroll
+    for (int u0 = 0; u0 < PER; u0 += B) {
+        uint4 v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int g = tid + (u0 + u) * 256, r = g / kPieces, at = c0 + 16 * (g % kPieces);
+            v[u] = *reinterpret_cast<const uint4 *>(row(r) + (at < row_bytes ? at : 0));
+            if (at >= row_bytes) v[u] = make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int g = tid + (u0 + u) * 256;
+            *reinterpret_cast<uint4 *>(lds + (g / kPieces) * kRowPitch + 16 * (g % kPieces)) = v[u];
+        }
+    }
+}
+
+__device__ __forceinline__ float other_half(float x)   // x of the lane 32 places away
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
+}
+
+// (m, z) <- merge with (m2, z2): running maximum and sum of exp(l - maximum).
+__device__ __forceinline__ void merge_exp(float &m, float &z, float m2, float z2)
+{
+    const float mn = fmaxf(m, m2);
+    z = mn == -INFINITY ? 0.f : z * expf(m - mn) + z2 * expf(m2 - mn);
+    m = mn;
+}
+
+// Waves of a workgroup: RS row groups x (4 / RS) key streams of 32 keys; NBR blocks of 32 rows.
+template <int NBR> struct Shape {
+    static constexpr int RS = NBR >= 2 ? 2 : 1, STREAMS = 4 / RS, NBW = NBR / RS, TR = 32 * NBR, TK = 32 * STREAMS;
+};
+
+// Stage I, logits of the window queries (scaled) and per (chunk of keys, row) the maximum and the sum
+// of exp over the chunk's visible keys.  Keys are the rows of the products, queries the columns: a lane
+// owns one query and keeps its statistics without cross-lane traffic.
+template <typename T, int NBR>
+__global__ __launch_bounds__(256) void gemm_logits_kernel(
+    const T *__restrict__ Kc, const T *__restrict__ Qw, int d, int N, int P, int w, int R, float scale,
+    int chunk_keys, float *__restrict__ logits, float *__restrict__ part)
+{
+    using Sh = Shape<NBR>;
+    __shared__ __align__(16) unsigned char kt[Sh::TK * kRowPitch], qt[Sh::TR * kRowPitch];
+    __shared__ float sm[Sh::STREAMS][Sh::TR], sz[Sh::STREAMS][Sh::TR];
+    const int h = blockIdx.y, chunk = blockIdx.x, row0 = blockIdx.z * Sh::TR;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+    const int stream = wv % Sh::STREAMS, rs = wv / Sh::STREAMS;
+    const int row_bytes = d * (int)sizeof(T);
+    const char *Kh = reinterpret_cast<const char *>(Kc + (long)h * N * d);
+    const char *Qh = reinterpret_cast<const char *>(Qw + (long)h * R * d);
+    const int k0 = chunk * chunk_keys, k1 = min(N, k0 + chunk_keys);
+
+    float m[Sh::NBW], z[Sh::NBW];
+    int last_vis[Sh::NBW];
+#pragma unroll
+    for (int b = 0; b < Sh::NBW; ++b) {
+        m[b] = -INFINITY;
+        z[b] = 0.f;
+        last_vis[b] = min(P + (row0 + 32 * (rs * Sh::NBW + b) + l32) % w, k1 - 1);
+    }
+    for (int t0 = k0; t0 < k1; t0 += Sh::TK) {
+        acc16 acc[Sh::NBW];
+#pragma unroll
+        for (int b = 0; b < Sh::NBW; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+        for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
+            __syncthreads();   // the tiles in LDS are free
+            stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, N - 1) * row_bytes; });
+            if (t0 == k0 || row_bytes > kRowBytes)   // (the queries stay when they fit whole)
+                stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Qh + (long)min(row0 + r, R - 1) * row_bytes; });
+            __syncthreads();
+            const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
+            const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
+            const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
+#pragma unroll
+            for (int s = 0; s < kMaxSteps; ++s) {
+                if (s >= steps) break;
+                const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
+#pragma unroll
+                for (int b = 0; b < Sh::NBW; ++b)
+                    mfma_step<T>(k, *reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), acc[b]);
+            }
+        }
+        const int key0 = t0 + 32 * stream;
+#pragma unroll
+        for (int b = 0; b < Sh::NBW; ++b) {
+            const int row = row0 + 32 * (rs * Sh::NBW + b) + l32;
+            float tm = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                acc[b][i] *= scale;
+                if (key0 + mfma_row(i, hh) <= last_vis[b]) tm = fmaxf(tm, acc[b][i]);
+            }
+            const float mn = fmaxf(m[b], tm);
+            if (mn != -INFINITY) {
+                float zz = z[b] * expf(m[b] - mn);
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (key0 + mfma_row(i, hh) <= last_vis[b]) zz += expf(acc[b][i] - mn);
+                m[b] = mn;
+                z[b] = zz;
+            }
+            if (row < R) {
+                float *o = logits + ((long)h * R + row) * N;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int key = key0 + 8 * v + 4 * hh;
+                    if ((N & 3) == 0 && key + 3 < k1) {
+                        *reinterpret_cast<float4 *>(o + key) =
+                            make_float4(acc[b][4 * v], acc[b][4 * v + 1], acc[b][4 * v + 2], acc[b][4 * v + 3]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (key + e < k1) o[key + e] = acc[b][4 * v + e];
+                    }
+                }
+            }
+        }
+    }
+    // the half-waves (same query, other keys), then the key streams
+#pragma unroll
+    for (int b = 0; b < Sh::NBW; ++b) {
+        merge_exp(m[b], z[b], other_half(m[b]), other_half(z[b]));
+        if (hh == 0) {
+            sm[stream][32 * (rs * Sh::NBW + b) + l32] = m[b];
+            sz[stream][32 * (rs * Sh::NBW + b) + l32] = z[b];
+        }
+    }
+    __syncthreads();
+    if (tid < Sh::TR && row0 + tid < R) {
+        float mm = sm[0][tid], zz = sz[0][tid];
+#pragma unroll
+        for (int u = 1; u < Sh::STREAMS; ++u) merge_exp(mm, zz, sm[u][tid], sz[u][tid]);
+        float *o = part + (((long)h * gridDim.x + chunk) * R + row0 + tid) * 2;
+        o[0] = mm;
+        o[1] = zz;
+    }
+}
+
+// Votes, pooling and the mean over the group in one go: scores[h, j] = 1/G sum_g pool(votes of query
+// head g).  A workgroup takes 256 keys (pool_half of them on either side only for the pooling), its
+// four groups of 256 threads share the window rows; the statistics of 64 rows at a time are merged
+// from the chunks into LDS first.  Average pooling adds the group before it pools.
+constexpr int kVoteKeys = 256;
+constexpr int kVoteHalf = 32;    // widest pooling half-window taken here
+
+__global__ __launch_bounds__(1024) void gemm_votes_kernel(
+    const float *__restrict__ logits, const float *__restrict__ part, int chunks, int N, int P, int w, int G,
+    int pool_half, int pool_mode, float *__restrict__ scores)
+{
+    __shared__ float vs[4][kVoteKeys], s_max[64], s_inv[64];
+    const int h = blockIdx.y, tid = threadIdx.x, t = tid & 255, p = tid >> 8;
+    const int R = G * w, tile = kVoteKeys - 2 * pool_half;
+    const int j = blockIdx.x * tile - pool_half + t;          // this thread's key
+    const bool in = j >= 0 && j < P;
+    const int jc = min(max(j, 0), P - 1);
+    float total = 0.f;
+    for (int g = 0; g < G; ++g) {
+        float v = 0.f;
+        for (int r0 = 0; r0 < w; r0 += 64) {
+            const int rows = min(64, w - r0);
+            __syncthreads();
+            {   // 16 lanes per row merge its chunks
+                const int r = tid >> 4, sub = tid & 15;
+                float mm = -INFINITY, zz = 0.f;
+                if (r < rows)
+                    for (int c = sub; c < chunks; c += 16) {
+                        const float2 o = *reinterpret_cast<const float2 *>(
+                            part + (((long)h * chunks + c) * R + g * w + r0 + r) * 2);
+                        merge_exp(mm, zz, o.x, o.y);
+                    }
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) {
+                    const float m2 = __shfl_xor(mm, o, kWave), z2 = __shfl_xor(zz, o, kWave);
+                    merge_exp(mm, zz, m2, z2);
+                }
+                if (sub == 0 && r < rows) {
+                    s_max[r] = mm;
+                    s_inv[r] = 1.0f / zz;
+                }
+            }
+            __syncthreads();
+            const float *l = logits + ((long)h * R + g * w + r0) * N + jc;
+#pragma unroll 8
+            for (int r = p; r < rows; r += 4) v += expf(l[(long)r * N] - s_max[r]) * s_inv[r];
+        }
+        vs[p][t] = v;
+        __syncthreads();
+        if (p == 0) {
+            v = ((vs[0][t] + vs[1][t]) + vs[2][t]) + vs[3][t];
+            if (pool_mode == 0) total += v;
+            else vs[0][t] = in ? v : -INFINITY;
+        }
+        if (pool_mode != 0) {
+            __syncthreads();
+            if (p == 0 && t >= pool_half && t < kVoteKeys - pool_half) {
+                float best = -INFINITY;
+                for (int u = t - pool_half; u <= t + pool_half; ++u) best = fmaxf(best, vs[0][u]);
+                total += best;
+            }
+        }
+    }
+    if (pool_mode == 0) {
+        __syncthreads();
+        if (p == 0) vs[0][t] = in ? total : 0.f;      // zero padding outside the row
+        __syncthreads();
+        if (p == 0 && t >= pool_half && t < kVoteKeys - pool_half) {
+            total = 0.f;
+            for (int u = t - pool_half; u <= t + pool_half; ++u) total += vs[0][u];
+            total = total / (float)(2 * pool_half + 1);
+        }
+    }
+    if (p == 0 && in && t >= pool_half && t < kVoteKeys - pool_half) scores[(long)h * P + j] = total / (float)G;
+}
+
+// Row statistics on their own (wide pooling windows, which take the separate votes and pooling kernels).
+__global__ __launch_bounds__(256) void merge_part_kernel(const float *__restrict__ part, int chunks, int R, int rows,
+                                                         float *__restrict__ row_max, float *__restrict__ row_sum)
+{
+    const int row = blockIdx.x * 256 + threadIdx.x;
+    if (row >= rows) return;
+    const int h = row / R, r = row % R;
+    float m = -INFINITY, z = 0.f;
+    for (int c = 0; c < chunks; ++c) {
+        const float *o = part + (((long)h * chunks + c) * R + r) * 2;
+        merge_exp(m, z, o[0], o[1]);
+    }
+    row_max[row] = m;
+    row_sum[row] = z;
+}
+
+// Eq. 1: E[h, a, j] = cosine of row src[h, a] of Ac and row j of Kc, -inf where j is the source itself
+// (Eq. 3).  Sources are the rows of the products and keys the columns: a lane owns one key, whose norm
+// it sums from the very registers that feed the products, and stores run along the keys.
+template <typename T, int NBR>
+__global__ __launch_bounds__(256) void gemm_cosine_kernel(
+    const T *__restrict__ Ac, const T *__restrict__ Kc, int d, int N, int P, int S, const int32_t *__restrict__ src,
+    int chunk_keys, float *__restrict__ E)
+{
+    using Sh = Shape<NBR>;
+    __shared__ __align__(16) unsigned char kt[Sh::TK * kRowPitch], qt[Sh::TR * kRowPitch];
+    __shared__ float inv_s[Sh::TR];
+    __shared__ int32_t idx_s[Sh::TR];
+    const int h = blockIdx.y, row0 = blockIdx.z * Sh::TR;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+    const int stream = wv % Sh::STREAMS, rs = wv / Sh::STREAMS;
+    const int row_bytes = d * (int)sizeof(T);
+    const char *Kh = reinterpret_cast<const char *>(Kc + (long)h * N * d);
+    const char *Ah = reinterpret_cast<const char *>(Ac + (long)h * N * d);
+    const int k0 = blockIdx.x * chunk_keys, k1 = min(P, k0 + chunk_keys);
+    for (int r = tid; r < Sh::TR; r += 256) idx_s[r] = src[(long)h * S + min(row0 + r, S - 1)];
+    for (int t0 = k0; t0 < k1; t0 += Sh::TK) {
+        acc16 acc[Sh::NBW];
+#pragma unroll
+        for (int b = 0; b < Sh::NBW; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+        float sq = 0.f, sq_src = 0.f;
+        for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
+            __syncthreads();   // the tiles in LDS are free, the source indices there
+            stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, P - 1) * row_bytes; });
+            if (t0 == k0 || row_bytes > kRowBytes)
+                stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Ah + (long)idx_s[r] * row_bytes; });
+            __syncthreads();
+            const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
+            if (t0 == k0 && tid < Sh::TR)   // a thread per source (zeros behind the row's end)
+                for (int u = 0; u < 2 * steps; ++u)
+                    sq_src = sum_squares<T>(*reinterpret_cast<const uint4 *>(qt + tid * kRowPitch + 16 * u), sq_src);
+            const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
+            const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
+#pragma unroll
+            for (int s = 0; s < kMaxSteps; ++s) {
+                if (s >= steps) break;
+                const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
+                sq = sum_squares<T>(k, sq);
+#pragma unroll
+                for (int b = 0; b < Sh::NBW; ++b)
+                    mfma_step<T>(*reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), k, acc[b]);
+            }
+        }
+        if (t0 == k0) {
+            if (tid < Sh::TR) inv_s[tid] = sq_src == 0.f ? 0.f : 1.0f / sqrtf(sq_src);
+            __syncthreads();
+        }
+        sq += other_half(sq);
+        const float inv_k = sq == 0.f ? 0.f : 1.0f / sqrtf(sq);   // a zero key or source: all edges 0
+        const int key = t0 + 32 * stream + l32;
+        if (key < k1) {
+#pragma unroll
+            for (int b = 0; b < Sh::NBW; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int r = 32 * (rs * Sh::NBW + b) + mfma_row(i, hh);
+                    if (row0 + r < S)
+                        E[((long)h * S + row0 + r) * P + key] =
+                            key == idx_s[r] ? -INFINITY : acc[b][i] * inv_s[r] * inv_k;
+                }
+        }
+    }
+}
+
+// Rows per workgroup: up to 128, no more than the rows need.
+int row_blocks(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
+
+// Keys per workgroup: a multiple of the largest key tile, for about 1024 workgroups.
+int gemm_chunk_keys(int Hkv, int rows, int N)
+{
+    const int nb = row_blocks(rows), groups = (rows + 32 * nb - 1) / (32 * nb);
+    long ck = ((long)Hkv * groups * N + 1023) / 1024;
+    ck = (ck + 127) / 128 * 128;
+    return (int)ck;
+}
+
+}  // namespace
+
+GemmScorePlan gemm_score_plan(int Hkv, int rows, int N)
+{
+    GemmScorePlan pl;
+    pl.chunk_keys = gemm_chunk_keys(Hkv, rows, N);
+    pl.chunks = (N + pl.chunk_keys - 1) / pl.chunk_keys;
+    pl.part_bytes = (size_t)Hkv * rows * pl.chunks * 2 * sizeof(float);
+    return pl;
+}
+
+bool gemm_votes_pools(int pool_kernel) { return (pool_kernel - 1) / 2 <= kVoteHalf; }
+
+template <typename T>
+static void launch_logits_t(const T *K, const T *Q, int Hkv, int R, int d, int N, int P, int w, float scale,
+                            const GemmScorePlan &pl, float *logits, float *part, hipStream_t st)
+{
+    const int nb = row_blocks(R);
+    const dim3 grid(pl.chunks, Hkv, (R + 32 * nb - 1) / (32 * nb));
+#define GKV_LOGITS(NB)                                                                                             \
+    hipLaunchKernelGGL((gemm_logits_kernel<T, NB>), grid, dim3(256), 0, st, K, Q, d, N, P, w, R, scale, pl.chunk_keys, \
+                       logits, part)
+    if (nb == 1) GKV_LOGITS(1);
+    else if (nb == 2) GKV_LOGITS(2);
+    else GKV_LOGITS(4);
+#undef GKV_LOGITS
+}
+
+hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d, int N, int w,
+                              float scale, float *logits, float *part, hipStream_t st)
+{
+    const int R = Hq / Hkv * w, P = N - w;
+    const GemmScorePlan pl = gemm_score_plan(Hkv, R, N);
+    if (dtype == 0) launch_logits_t((const float *)Kc, (const float *)Qw, Hkv, R, d, N, P, w, scale, pl, logits, part, st);
+    else launch_logits_t((const uint16_t *)Kc, (const uint16_t *)Qw, Hkv, R, d, N, P, w, scale, pl, logits, part, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_votes(const float *logits, const float *part, int Hkv, int Hq, int N, int w, int pool_kernel,
+                             int pool_mode, float *scores, hipStream_t st)
+{
+    const int G = Hq / Hkv, P = N - w, half = (pool_kernel - 1) / 2, tile = kVoteKeys - 2 * half;
+    const GemmScorePlan pl = gemm_score_plan(Hkv, G * w, N);
+    hipLaunchKernelGGL(gemm_votes_kernel, dim3((P + tile - 1) / tile, Hkv), dim3(1024), 0, st, logits, part, pl.chunks,
+                       N, P, w, G, half, pool_mode, scores);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge_part(const float *part, int Hkv, int Hq, int N, int w, float *row_max, float *row_sum,
+                             hipStream_t st)
+{
+    const int R = Hq / Hkv * w, rows = Hq * w;
+    const GemmScorePlan pl = gemm_score_plan(Hkv, R, N);
+    hipLaunchKernelGGL(merge_part_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, part, pl.chunks, R, rows, row_max,
+                       row_sum);
+    return hipGetLastError();
+}
+
+template <typename T>
+static void launch_cosine_t(const T *A, const T *K, int Hkv, int d, int N, int P, int S, const int32_t *src, float *E,
+                            hipStream_t st)
+{
+    const int nb = row_blocks(S), ck = gemm_chunk_keys(Hkv, S, P);
+    const dim3 grid((P + ck - 1) / ck, Hkv, (S + 32 * nb - 1) / (32 * nb));
+#define GKV_COSINE(NB) \
+    hipLaunchKernelGGL((gemm_cosine_kernel<T, NB>), grid, dim3(256), 0, st, A, K, d, N, P, S, src, ck, E)
+    if (nb == 1) GKV_COSINE(1);
+    else if (nb == 2) GKV_COSINE(2);
+    else GKV_COSINE(4);
+#undef GKV_COSINE
+}
+
+hipError_t launch_gemm_cosine(const void *Ac, const void *Kc, int dtype, int Hkv, int d, int N, int P, int S,
+                              const int32_t *src, float *E, hipStream_t st)
+{
+    if (dtype == 0) launch_cosine_t((const float *)Ac, (const float *)Kc, Hkv, d, N, P, S, src, E, st);
+    else launch_cosine_t((const uint16_t *)Ac, (const uint16_t *)Kc, Hkv, d, N, P, S, src, E, st);
+    return hipGetLastError();
+}
+
+}  // namespace gkv

@@ -57,6 +57,27 @@ hipError_t launch_generic_cosine(const void *Ac, const void *Kc, int dtype, int 
 hipError_t launch_knorm(const void *Kc, int dtype, int Hkv, int d, int N, int P, float *scores,
                         hipStream_t st);
 
+// ---- the same contractions on the matrix cores, any dtype / shape (gemm.hip) ----------
+struct GemmScorePlan {
+    int chunk_keys, chunks;   // keys per workgroup, workgroups per head and row group
+    size_t part_bytes;        // bytes of per-chunk row statistics
+};
+GemmScorePlan gemm_score_plan(int Hkv, int rows, int N);   // rows: stacked query rows per KV head
+// logits [Hq*w, N] (fp32, scaled) and part [Hkv, chunks, G*w] (max, sum of exp) over visible keys.
+hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d, int N, int w,
+                              float scale, float *logits, float *part, hipStream_t st);
+// scores [Hkv, P] from logits and part, votes, pooling and the mean over the group included
+// (gemm_votes_pools(pool_kernel)); wider pooling windows take launch_merge_part (row statistics
+// as launch_generic_logits leaves them), launch_generic_votes and launch_pool_group.
+bool gemm_votes_pools(int pool_kernel);
+hipError_t launch_gemm_votes(const float *logits, const float *part, int Hkv, int Hq, int N, int w, int pool_kernel,
+                             int pool_mode, float *scores, hipStream_t st);
+hipError_t launch_merge_part(const float *part, int Hkv, int Hq, int N, int w, float *row_max, float *row_sum,
+                             hipStream_t st);
+// Same contract as launch_generic_cosine.
+hipError_t launch_gemm_cosine(const void *Ac, const void *Kc, int dtype, int Hkv, int d, int N, int P, int S,
+                              const int32_t *src, float *E, hipStream_t st);
+
 // ---- pooling, signal propagation, gather (stages.hip) -----------------------
 // votes [Hkv*Gv, P] -> scores [Hkv, P]: pool each of the Gv rows of a head, sum, divide by div.
 hipError_t launch_pool_group(const float *votes, int Hkv, int Gv, int P, int pool_kernel,

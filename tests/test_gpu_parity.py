@@ -1140,3 +1140,48 @@ def test_update_products_in_source_order(S, m, P, signal):
             want = s0[h].copy()
             want[np.unique(nbr[h])] = -np.inf
         assert np.array_equal(got[h], want)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("d,H,G,w,P,pool,mode,S,m", [
+    (8, 2, 1, 3, 70, 1, 0, 5, 4), (24, 1, 3, 7, 129, 5, 1, 33, 9), (64, 2, 2, 16, 900, 7, 0, 32, 16),
+    (64, 2, 1, 65, 257, 65, 0, 64, 30), (72, 1, 5, 13, 500, 67, 1, 65, 40), (80, 2, 7, 20, 1030, 7, 1, 128, 8),
+    (128, 1, 9, 32, 640, 13, 0, 100, 64), (136, 1, 2, 31, 383, 3, 0, 129, 3), (256, 1, 4, 40, 300, 7, 0, 17, 5),
+    (512, 1, 1, 130, 200, 9, 1, 40, 20)])
+def test_any_head_dimension_on_the_matrix_cores(oracle, d, H, G, w, P, pool, mode, S, m, dtype):
+    """Scores and one round of edges for head dimensions of one to several staged pieces, rows that do
+    not fill the 32-row blocks, one to three row groups, key tails, pooling windows on both sides of what
+    the vote kernel pools itself, window rows beyond one batch of statistics."""
+    cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=P + w, window=w, head_dim=d, n_kv_heads=H, n_q_heads=H * G,
+                       pool_kernel=pool, budget=w + 5, n_sources=S, n_neighbors=m, dtype=dtype)
+    say(f"any head dimension d={d} H={H} G={G} w={w} P={P} pool={pool}/{mode} S={S} m={m} {dtype}")
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 2)
+    p = util.params_from_cfg(cfg, pool_mode=mode)
+    s = gk.graphkv_score(p, Kd, Qd).cpu().numpy()
+    util.assert_scores_close(s, oracle.score(K, Q, dtype, pool, mode))
+    s0 = synth.random_scores(cfg)
+    s1, src, nbr, ev = run_propagate(p, Kd, s0)
+    util.check_round_staged(oracle, K, dtype, w, s0, s1, src[0], nbr[0], ev[0], S, m, p.decay, 0)
+
+
+@pytest.mark.parametrize("P,m", [(256, 255), (513, 200), (2049, 256), (8192, 100), (8193, 30), (32768, 256)])
+def test_edge_rows_small_m(oracle, P, m):
+    """The m best of dense edge rows: every register count, more winners than thread maxima can
+    separate, rows of equal edges (the list overflows, the general algorithm takes over) and ties."""
+    say(f"edge rows P={P} m={m}")
+    H, S, d, w = 1, 6, 8, 2
+    rng = np.random.default_rng(P + m)
+    K = rng.standard_normal((H, P + w, d)).astype(np.float32)
+    K[0, 3:P:2] = K[0, 1]                     # half the nodes are copies of one key
+    s0 = rng.random((H, P)).astype(np.float32)
+    s0[0, [0, 1, 2, 3, 4, 5]] += 5.0          # sources: copies (rows of equal edges) and others
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, budget=w + 1, n_sources=S,
+                  n_neighbors=m, rounds=1, dtype=gk.FP32)
+    s1, src, nbr, ev = run_propagate(p, torch.from_numpy(K).cuda(), s0)
+    pf = gk.Params(**{**p.__dict__, "n_neighbors": P - 1})
+    _, src_f, nbr_f, ev_f = run_propagate(pf, torch.from_numpy(K).cuda(), s0)
+    for a in range(S):                        # the call's own full edge row gives the expected list
+        row = np.full(P, -np.inf)
+        row[nbr_f[0, 0, a]] = ev_f[0, 0, a]
+        want, _ = oracle.topk(row, m)
+        assert np.array_equal(nbr[0, 0, a], want) and np.array_equal(ev[0, 0, a], row[want].astype(np.float32))
