@@ -817,151 +817,149 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 }
 
 // The same select for short lists, one wave per source and no workgroup barrier: a lane
-// keeps the keys of up to R candidates in registers, so that a compute unit works on
+// keeps up to R candidates (edge key and node) in registers, so that a compute unit works on
 // several times as many sources at once as with a workgroup per source -- the select is
 // a chain of memory and LDS round trips, and only the number of chains in flight hides
-// them.  Everything that reaches the m-th largest key goes to a small LDS list per wave
-// (m entries and room for 64 more that are tied at the cut); only then are the key
-// indices of the listed entries fetched, the tied entries with the lowest key indices are
-// kept, and the winners are ranked by key index.  Lists longer than 64 R, with fewer than
-// m entries, or with more ties at the cut than the list has room for, raise the head's
-// overflow flag (the head is then redone exactly).
+// them.  Which slice an entry of the concatenated list belongs to comes from a mark at every
+// slice's first entry and a running maximum over the lanes.  Everything that reaches the m-th
+// largest key goes to a small LDS list per wave (m entries and room for 64 more that are tied at
+// the cut), the tied entries with the lowest key indices are kept, and the winners are ranked by
+// key index.  Lists longer than 64 R, with fewer than m entries, or with more ties at the cut than the
+// list has room for, raise the head's overflow flag (the head is then redone exactly).
+// (A walk over the slices for every register, key indices fetched a second time, scans through the
+// LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way SELW us.)
 template <int R>
 __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
                                                               const int32_t *__restrict__ cand_cnt,
                                                               int32_t *__restrict__ overflow,
                                                               const int32_t *__restrict__ src, int S, int pitch,
-                                                              int chunks, int slice_cap, int m,
+                                                              int chunks, int slice_cap, int m, SelectRows sel,
                                                               int32_t *__restrict__ nbr,
                                                               float *__restrict__ nbr_e)
 {
     static_assert(R == 16 || R == 32, "register groups of 16");
-    extern __shared__ __align__(8) uint32_t dyn[];   // per wave: [64] slice starts, [m + kTieRoom] list (64 bit)
+    // per wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit)
+    extern __shared__ __align__(16) uint32_t dyn[];
     const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
-    const int n_rows = S;        // candidate row x of the head (pitch rows) -> source slot x
+    const int waves = (int)blockDim.x >> 6;
+    const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
     if (overflow[h]) return;
     const int list_cap = m + kTieRoom;
-    uint32_t *start_s = dyn + wv * (64 + 2 * list_cap);
-    uint64_t *win = reinterpret_cast<uint64_t *>(start_s + 64);
-    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t *start_s = dyn + wv * (64 + 16 * R + 2 * ((list_cap + 1) & ~1));
+    uint8_t *mark_s = reinterpret_cast<uint8_t *>(start_s + 64);
+    uint64_t *win = reinterpret_cast<uint64_t *>(start_s + 64 + 16 * R);
 
-    for (int x = blockIdx.x * 4 + wv; x < n_rows; x += gridDim.x * 4) {
-        const long row = (long)h * pitch + x;
+    for (int x = blockIdx.x * waves + wv; x < n_rows; x += gridDim.x * waves) {
+        const int crow = sel.row ? sel.row[(long)h * S + x] : x, pos = sel.pos ? sel.pos[(long)h * S + x] : x;
+        const long row = (long)h * pitch + crow;
         const uint2 *slices = cand + row * chunks * (long)slice_cap;
-        // slice sizes -> where each slice starts in the concatenated list
         const int cnt = lane < chunks ? cand_cnt[row * chunks + lane] : 0;
-        const uint32_t self = (uint32_t)src[(long)h * S + x];
-        const long out_row = (long)h * S + x;
-        int incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
-        }
-        // (values every lane holds alike are moved to scalar registers: the code below then
-        // branches as a wave instead of masking lanes)
-        const int n = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, kWave));
+        const uint32_t self = (uint32_t)src[(long)h * S + pos];
+        const long out_row = (long)h * S + pos;
+        const int incl = (int)wave_scan_add((uint32_t)cnt);   // slice sizes -> where each slice ends in the list
+        const int n = __builtin_amdgcn_readlane(incl, 63);
         if (n > 64 * R || n < m) {   // too long for the lanes (or short of m): the head is redone exactly
             if (lane == 0) overflow[h] = 1;
             return;
         }
-        start_s[lane] = (uint32_t)(incl - cnt);
-        __builtin_amdgcn_wave_barrier();
         const int n_it = (n + 63) >> 6;
 
-        // Register it of lane L holds entry 64 it + L: first where it sits in the row's slices,
-        // then its order-preserving edge key (0 = no entry / dropped).  The slice starts are the
-        // same for every lane: a scalar walk over the slices, the last slice that starts at or
-        // before the entry wins.  The loads of 16 registers leave together.
-        uint32_t E[R];
-        // (the lane number as a value the compiler cannot see through: otherwise it keeps
-        // "64 it + lane" for every register in a register of its own across the whole loop)
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
+        // Register it of lane L holds entry 64 it + L: first where it sits in the row's slices, then edge
+        // bits (later the order-preserving key, 0 = no entry / dropped) and node.
+        uint32_t E[R], J[R];
+        if (chunks <= 8) {
+            // few slices: the last one that starts at or before the entry, slice by slice in scalars
 #pragma unroll
-        for (int it = 0; it < R; ++it) E[it] = (uint32_t)(ln + it * 64);
-        for (int c = 1; c < chunks; ++c) {
-            const int s_c = __builtin_amdgcn_readlane(incl - cnt, c);
-            const int shift = c * slice_cap - s_c;
+            for (int it = 0; it < R; ++it) J[it] = (uint32_t)(it * 64 + lane);
+            for (int c = 1; c < chunks; ++c) {
+                const int s_c = __builtin_amdgcn_readlane(incl - cnt, c), shift = c * slice_cap - s_c;
 #pragma unroll
-            for (int it = 0; it < R; ++it)
-                if ((it & ~15) < n_it) E[it] = ln >= s_c - it * 64 ? (uint32_t)(ln + (it * 64 + shift)) : E[it];
+                for (int it = 0; it < R; ++it)
+                    if ((it & ~3) < n_it) J[it] = it * 64 + lane >= s_c ? (uint32_t)(it * 64 + lane + shift) : J[it];
+            }
+        } else {
+            // many: marks, a running maximum
+            start_s[lane] = (uint32_t)(incl - cnt);
+            for (int it = 0; it < n_it; ++it) mark_s[it * 64 + lane] = 0;
+            __builtin_amdgcn_wave_barrier();
+            if (cnt > 0) mark_s[incl - cnt] = (uint8_t)lane;
+            __builtin_amdgcn_wave_barrier();
+            uint32_t carry = 0;
+#pragma unroll
+            for (int it = 0; it < R; ++it) {
+                J[it] = 0u;
+                if (it < n_it) {   // (the same for all lanes)
+                    const uint32_t c = wave_scan_op(max((uint32_t)mark_s[it * 64 + lane], carry), 0u,
+                                                    [](uint32_t a, uint32_t b) { return max(a, b); });
+                    carry = (uint32_t)__builtin_amdgcn_readlane((int)c, 63);
+                    J[it] = (uint32_t)((int)c * slice_cap + it * 64 + lane - (int)start_s[c]);
+                }
+            }
         }
+        // (entries past the end read one that is there: the loads of four registers leave together)
+        const uint32_t some = (uint32_t)__builtin_amdgcn_readfirstlane((int)J[0]);
 #pragma unroll
-        for (int it = 0; it < R; ++it) E[it] = ln < n - it * 64 ? E[it] : 0u;   // past the end: any valid entry
-        uint32_t kmin = 0xffffffffu, kmax = 0u;
-        bool dropped = false;   // this lane held the source's own column
-#pragma unroll
-        for (int g = 0; g < R; g += 16) {
+        for (int g = 0; g < R; g += 4) {
             if (g < n_it) {
-                uint2 v[16];
+                uint2 v[4];
 #pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    v[u] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(slices) + E[g + u] * 8u);
+                for (int u = 0; u < 4; ++u) v[u] = slices[(g + u) * 64 + lane < n ? J[g + u] : some];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    // the source's own column is no neighbour (Eq. 3: j != i): key 0 sorts below every edge
-                    const bool present = ln < n - (g + u) * 64, own = present && v[u].y == self;
-                    const uint32_t k = (present && !own) ? ord_key_u(v[u].x) : 0u;
-                    dropped |= own;
-                    E[g + u] = k;
-                    if (k) { kmin = min(kmin, k); kmax = max(kmax, k); }
+                for (int u = 0; u < 4; ++u) {
+                    E[g + u] = v[u].x;
+                    J[g + u] = v[u].y;
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < 16; ++u) E[g + u] = 0u;
+                for (int u = 0; u < 4; ++u) E[g + u] = 0u;
             }
         }
-        const int valid = n - (int)__popcll(__ballot(dropped));
+        uint32_t kmin = 0xffffffffu, kmax = 0u;
+        int valid = n;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, kWave));
-            kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, kWave));
-        }
-        kmin = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmin);
-        kmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmax);
+        for (int it = 0; it < R; ++it)
+            if ((it & ~3) < n_it) {
+                // the source's own column is no neighbour (Eq. 3: j != i): key 0 sorts below every edge
+                const bool present = it * 64 + lane < n, own = present && J[it] == self;
+                const uint32_t k = (present && !own) ? ord_key_u(E[it]) : 0u;
+                valid -= (int)__popcll(__ballot(own));
+                E[it] = k;
+                kmin = min(kmin, k ? k : 0xffffffffu);
+                kmax = max(kmax, k);
+            }
+        kmin = wave_min_u32(kmin);
+        kmax = wave_max_u32(kmax);
         if (valid < m) {
             if (lane == 0) overflow[h] = 1;
             return;
         }
 
         uint32_t tau;
-        if (n_it <= 4) tau = mth_largest_key<4>(E, kmin, kmax, m);
+        if (n_it <= 2) tau = mth_largest_key<2>(E, kmin, kmax, m);
+        else if (n_it <= 4) tau = mth_largest_key<4>(E, kmin, kmax, m);
         else if (n_it <= 8) tau = mth_largest_key<8>(E, kmin, kmax, m);
         else if (n_it <= 12) tau = mth_largest_key<12>(E, kmin, kmax, m);
         else if (n_it <= 16) tau = mth_largest_key<16>(E, kmin, kmax, m);
         else if (n_it <= 24) tau = mth_largest_key<(R > 24 ? 24 : R)>(E, kmin, kmax, m);
         else tau = mth_largest_key<R>(E, kmin, kmax, m);
 
-        // everything that reaches tau -> LDS list as (entry number, key), any order
+        // everything that reaches tau -> LDS list as (key index, edge bits), any order
         int listed = 0;
 #pragma unroll
         for (int it = 0; it < R; ++it)
-            if ((it & ~3) < n_it) {
+            if (it < n_it) {
                 const bool in = E[it] >= tau;
                 const uint64_t votes = __ballot(in);
-                const int at = listed + (int)__popcll(votes & below);
-                if (in && at < list_cap) win[at] = ((uint64_t)(uint32_t)(ln + it * 64) << 32) | E[it];
+                const int at = listed + (int)votes_below(votes);
+                if (in && at < list_cap) win[at] = ((uint64_t)J[it] << 32) | ord_key_inv(E[it]);
                 listed += (int)__popcll(votes);
             }
         if (listed > list_cap) {   // too many exactly equal edges at the cut
             if (lane == 0) overflow[h] = 1;
             return;
         }
-        __builtin_amdgcn_wave_barrier();
-        // the key indices of the listed entries: (key index, edge bits) from here on
-        for (int r = lane; r < listed; r += 64) {
-            const uint64_t w = win[r];
-            const int e = (int)(w >> 32);
-            int lo = 0, hi = chunks - 1;    // last slice that starts at or before entry e
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if ((int)start_s[mid] <= e) lo = mid; else hi = mid - 1;
-            }
-            const uint32_t j = slices[lo * slice_cap + (e - (int)start_s[lo])].y;
-            win[r] = ((uint64_t)j << 32) | ord_key_inv((uint32_t)w);
-        }
+        if (lane == 0 && (listed & 1)) win[listed] = ~0ull;   // (pairs are read below)
         __builtin_amdgcn_wave_barrier();
         if (listed > m) {
             // Of the entries equal to tau only those with the lowest key indices stay: one that
@@ -970,28 +968,35 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
             int n_tied = 0;
             for (int u = 0; u < listed; ++u) n_tied += (uint32_t)win[u] == tau_bits;
             const int keep = m - (listed - n_tied);
-            for (int r0 = 0; r0 < listed; r0 += 64) {
-                const int r = r0 + lane;
-                const uint64_t mine = r < listed ? win[r] : 0ull;
-                int before = 0;
-                if (r < listed && (uint32_t)mine == tau_bits)
+            // (decided for all entries first: a dropped one must still be counted by the others)
+            uint32_t drop = 0;
+            for (int r = lane, i = 0; r < listed; r += 64, ++i) {
+                const uint64_t mine = win[r];
+                if ((uint32_t)mine == tau_bits) {
+                    int before = 0;
                     for (int u = 0; u < listed; ++u) {
                         const uint64_t w = win[u];
                         before += (uint32_t)w == tau_bits && w < mine;
                     }
-                __builtin_amdgcn_wave_barrier();
-                if (before >= keep) win[r] = ~0ull;
+                    if (before >= keep) drop |= 1u << i;
+                }
             }
+            __builtin_amdgcn_wave_barrier();
+            for (int r = lane, i = 0; r < listed; r += 64, ++i)
+                if ((drop >> i) & 1u) win[r] = ~0ull;
             __builtin_amdgcn_wave_barrier();
         }
         // each winner's rank by key index is its place in the output
         for (int r = lane; r < listed; r += 64) {
             const uint64_t mine = win[r];
             if (mine != ~0ull) {
-                int pos = 0;
-                for (int u = 0; u < listed; ++u) pos += win[u] < mine;
-                nbr[out_row * m + pos] = (int32_t)(mine >> 32);
-                nbr_e[out_row * m + pos] = __uint_as_float((uint32_t)mine);
+                int at = 0;
+                for (int u = 0; u < listed; u += 2) {
+                    const ulonglong2 w = *reinterpret_cast<const ulonglong2 *>(win + u);
+                    at += (w.x < mine) + (w.y < mine);
+                }
+                nbr[out_row * m + at] = (int32_t)(mine >> 32);
+                nbr_e[out_row * m + at] = __uint_as_float((uint32_t)mine);
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -1342,19 +1347,24 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
                              float *nbr_e, hipStream_t st)
 {
     const int S = g.S, cap = g.cand_cap;
-    // Every source has a list (first round, or nothing kept) and the lists are short: a wave
-    // per source.  That kernel is long straight-line code, which only pays when there are
-    // many lists to go through; the few selections of a later round take the other one.
-    if (!rows && cap <= 64 * 32 && g.chunks <= 64) {
-        int per_head = 8192 / Hkv < 1 ? 1 : 8192 / Hkv;   // four sources per workgroup
-        const int wgs = per_head > (S + 3) / 4 ? (S + 3) / 4 : per_head;
-        const size_t lds = (size_t)4 * (64 + 2 * (m + kTieRoom)) * 4;
-        auto *kernel = cap <= 64 * 16 ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
-        hipLaunchKernelGGL(kernel, dim3(wgs, Hkv), dim3(256), lds, st, (const uint2 *)cand, cand_cnt, overflow,
-                           src, S, g.pitch, g.chunks, g.slice_cap, m, nbr, nbr_e);
+    // Short lists in at most 64 slices: a wave per list, one to a workgroup while that spreads them
+    // over the compute units (up to 2048 lists), else four.  The few selections of a later round
+    // take the other kernel when there are many heads (256 heads, us, workgroup / wave per list: 32K
+    // prompts 18 / 28, 128K 76 / 231), this one when there are few (8 heads 9.3 / 8.3).
+    const bool few = (long)S * Hkv <= 2048;
+    if (cap <= 64 * 32 && g.chunks <= 64 && (!rows || few)) {
+        const int waves = few ? 1 : 4;
+        const SelectRows sel = rows ? *rows : SelectRows{};
+        int per_head = (waves == 1 ? 2048 : 8192) / Hkv;
+        per_head = per_head < 1 ? 1 : (per_head > (S + waves - 1) / waves ? (S + waves - 1) / waves : per_head);
+        const bool small = cap <= 64 * 16;
+        const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * ((m + kTieRoom + 1) & ~1)) * 4;
+        auto *kernel = small ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
+        hipLaunchKernelGGL(kernel, dim3(per_head, Hkv), dim3(64 * waves), lds, st, (const uint2 *)cand, cand_cnt,
+                           overflow, src, S, g.pitch, g.chunks, g.slice_cap, m, sel, nbr, nbr_e);
         return hipGetLastError();
     }
-    // The workgroups of a head share its selections in turn: few workgroups when only some
+    // Longer lists: the workgroups of a head share its selections in turn: few workgroups when only some
     // sources of a round need a select (most would find nothing to do), many otherwise.
     const SelectRows sel = rows ? *rows : SelectRows{};
     int per_head = (rows ? 3072 : 16384) / Hkv;
