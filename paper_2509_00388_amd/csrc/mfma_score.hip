@@ -266,10 +266,18 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
         for (int u = tid; u < SPLIT * span; u += NT) vs[u] = 0.f;   // zero padding outside the row
 
     if (tid < R) {   // row statistics of the whole head: merge the chunks of pass A
+        // (the loads of eight chunks leave together; with few heads there are 32 chunks, and one round
+        // trip after the other made this the longest part of the kernel's start: 25.4 -> 21.9 us there)
         float mm = -INFINITY, zz = 0.f;
-        for (int ch = 0; ch < part_chunks; ++ch) {
-            const float *o = part + (((long)h * part_chunks + ch) * R_total + row_base + tid) * 2;
-            merge_stats(mm, zz, o[0], o[1]);
+        for (int c0 = 0; c0 < part_chunks; c0 += 8) {
+            float2 o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                o[u] = *reinterpret_cast<const float2 *>(
+                    part + (((long)h * part_chunks + min(c0 + u, part_chunks - 1)) * R_total + row_base + tid) * 2);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c0 + u < part_chunks) merge_stats(mm, zz, o[u].x, o[u].y);
         }
         bias_s[tid] = mm + __log2f(zz);   // zz >= 1: the row maximum itself contributes exp2(0)
     }
