@@ -372,17 +372,20 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     GKV_LAUNCH(GRAPHKV_K_REDO_ROWS,
                                launch_redo_rows(Ac, Kc, D.H, D.N, D.P, D.S, D.m, src, ovf, E, nbr, ev, st));
                 } else {
-                    GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER,
-                               launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
-                                                nullptr, 1, st));
                     int32_t *new_src = at<int32_t>(ws, W.new_src), *n_new = at<int32_t>(ws, W.n_new);
                     const SelectRows sel{at<int32_t>(ws, W.n_sel), at<int32_t>(ws, W.sel_row),
                                          at<int32_t>(ws, W.sel_pos)};
-                    GKV_LAUNCH(GRAPHKV_K_MATCH_SOURCES,
-                               launch_match_sources(prev_src, src, D.H, D.m, g, prev_nbr, prev_e, nbr, ev, ext,
-                                                    at<int32_t>(ws, W.spec_bad), ovf, t == 1, new_src, n_new,
-                                                    at<int32_t>(ws, W.sel_row), at<int32_t>(ws, W.sel_pos),
-                                                    at<int32_t>(ws, W.n_sel), st));
+                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, ovf,
+                                          at<int32_t>(ws, W.spec_bad), new_src, n_new, at<int32_t>(ws, W.sel_row),
+                                          at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel)};
+                    if (pick_match_applies(D.S)) {
+                        GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER, launch_pick_match(scores, D.P, D.H, match, src, st));
+                    } else {
+                        GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER,
+                                   launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
+                                                    nullptr, 1, st));
+                        GKV_LAUNCH(GRAPHKV_K_MATCH_SOURCES, launch_match_sources(match, src, D.H, st));
+                    }
                     // new sources without a kept list (usually none): bound and filter passes
                     // that return at once for heads that have none
                     GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,

@@ -160,17 +160,25 @@ hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, in
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                      const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
                                      int32_t *overflow, hipStream_t st);
-// From the second round on: which sources keep their list from the round before (copied from
-// prev_nbr / prev_e to nbr / nbr_e), which are speculative rows of the first round (the last X
-// entries of ext [Hkv, S + X]; not used for heads that overflowed then: spec_bad [Hkv], set by the first match of
-// a call from the first round's overflow flags), and which need another bound and filter pass
+// From the second round on (match.hpp): which sources keep their list from the round before (copied
+// from prev_nbr / prev_e to nbr / nbr_e), which are speculative rows of the first round (the last X
+// entries of ext [Hkv, S + X]; not used for heads that overflowed then: spec_bad [Hkv], set by the first
+// match of a call from the first round's overflow flags), and which need another bound and filter pass
 // (new_src [Hkv, S], n_new [Hkv]).  sel_row / sel_pos [Hkv, S], n_sel [Hkv]: the selections to
 // run as (candidate row, source slot).
-hipError_t launch_match_sources(const int32_t *prev, const int32_t *cur, int Hkv, int m, const MfmaFilterPlan &g,
-                                const int32_t *prev_nbr, const float *prev_e, int32_t *nbr, float *nbr_e,
-                                const int32_t *ext, int32_t *spec_bad, const int32_t *overflow, bool first_match,
-                                int32_t *new_src, int32_t *n_new, int32_t *sel_row, int32_t *sel_pos,
-                                int32_t *n_sel, hipStream_t st);
+struct MatchArgs {
+    int S, X, m, first;
+    const int32_t *prev_src, *prev_nbr;
+    const float *prev_e;
+    int32_t *nbr;
+    float *nbr_e;
+    const int32_t *ext, *overflow;
+    int32_t *spec_bad, *new_src, *n_new, *sel_row, *sel_pos, *n_sel;
+};
+// Source nodes (Eq. 2) of a later round and their match, one launch for S <= 256 (pick_match_applies).
+bool pick_match_applies(int S);
+hipError_t launch_pick_match(const float *x, int n, int rows, const MatchArgs &a, int32_t *src, hipStream_t st);
+hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv, hipStream_t st);
 // Exact top-m over candidate rows -> nbr / nbr_e [Hkv, S, m]; skips heads with overflow[h], and
 // raises overflow[h] itself if a row has more candidates than it can take.  rows == nullptr:
 // candidate row x -> source slot x for all S sources of src [Hkv, S]; otherwise the listed ones.

@@ -33,6 +33,7 @@
 // in use; heads without such a source return at once).
 #include "common.hpp"
 #include "kernels.hpp"
+#include "match.hpp"
 #include "mfma_tile.hpp"
 
 #include <math.h>
@@ -1003,104 +1004,14 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
     }
 }
 
-// Where each source of this round (cur [Hkv, S], ascending) gets its neighbour list from:
-//   - it was a source in the previous round (prev, ascending): its list (prev_nbr, prev_e
-//     [Hkv, S, m]) is copied to its slot of this round (nbr, nbr_e);
-//   - it is one of the head's speculative rows (entries S .. S + X of ext [Hkv, S + X],
-//     ascending, whose candidate lists the first round's filter pass built in rows
-//     spec_row0 .. of the per-row buffers) and
-//     those lists are complete (the head raised no overflow flag in the first round): the
-//     exact select runs on that row;
-//   - otherwise it goes, in order, to new_src[h, 0 .. n_new[h]) for another bound and filter
-//     pass, which uses rows 0 .. of the per-row buffers (the candidates of the first round's
-//     sources are no longer needed once their lists are selected).
-// The selections to run are listed as (candidate row, source slot) in sel_row / sel_pos
-// [Hkv, S], n_sel[h] of them.  spec_bad [Hkv] remembers across rounds whether a head's
-// speculative lists may be used: the first match of a call sets it from the overflow flags
-// of the first round (first != 0), later ones read it.  One workgroup per head.
-__global__ __launch_bounds__(256) void match_sources_kernel(
-    const int32_t *__restrict__ prev, const int32_t *__restrict__ cur, int S, int m,
-    const int32_t *__restrict__ prev_nbr, const float *__restrict__ prev_e, int32_t *__restrict__ nbr,
-    float *__restrict__ nbr_e, const int32_t *__restrict__ ext, int X, int spec_row0,
-    int32_t *__restrict__ spec_bad, const int32_t *__restrict__ overflow, int first,
-    int32_t *__restrict__ new_src, int32_t *__restrict__ n_new, int32_t *__restrict__ sel_row,
-    int32_t *__restrict__ sel_pos, int32_t *__restrict__ n_sel)
+// Matching on its own, for source lists the few-winners selection does not take (S > 256).
+__global__ __launch_bounds__(kMatchBlock) void match_sources_kernel(MatchArgs a, const int32_t *__restrict__ cur)
 {
-    extern __shared__ int32_t prev_s[];   // [S] previous sources, [S] where this round's lists come from, [X] spec
-    int32_t *code_s = prev_s + S, *spec_s = code_s + S;
-    __shared__ int32_t wave_new[4], wave_fb[4];
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const long row0 = (long)h * S;
-    for (int b = tid; b < S; b += 256) prev_s[b] = prev[row0 + b];
-    for (int b = tid; b < X; b += 256) spec_s[b] = ext[(long)h * (S + X) + S + b];   // the rows behind the S sources
-    bool bad = X == 0;
-    if (X > 0) {
-        bad = first ? overflow[h] != 0 : spec_bad[h] != 0;
-        if (first && tid == 0) spec_bad[h] = bad ? 1 : 0;
-    }
+    extern __shared__ int32_t match_lds[];
+    __shared__ int32_t wave_new[kMatchBlock / kWave], wave_fb[kMatchBlock / kWave];
+    const bool bad = match_load(a, blockIdx.x, match_lds, threadIdx.x);
     __syncthreads();
-    // first slot of a sorted list that holds i or more
-    auto lower_bound = [](const int32_t *list, int n, int32_t i) {
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (list[mid] < i) lo = mid + 1; else hi = mid;
-        }
-        return lo;
-    };
-    int base = 0, base_fb = 0;
-    for (int a0 = 0; a0 < S; a0 += 256) {
-        const int a = a0 + tid;
-        int i = 0, found = -1, spec_at = -1;
-        if (a < S) {
-            i = cur[row0 + a];
-            const int lo = lower_bound(prev_s, S, i);
-            if (lo < S && prev_s[lo] == i) found = lo;
-            if (found < 0 && !bad) {
-                const int u = lower_bound(spec_s, X, i);
-                if (u < X && spec_s[u] == i) spec_at = u;
-            }
-        }
-        const bool is_new = a < S && found < 0, is_fb = is_new && spec_at < 0;
-        const uint64_t mask = __ballot(is_new), mask_fb = __ballot(is_fb);
-        if (lane == 0) { wave_new[wv] = (int32_t)__popcll(mask); wave_fb[wv] = (int32_t)__popcll(mask_fb); }
-        __syncthreads();
-        int before = base, total = 0, before_fb = base_fb, total_fb = 0;
-        for (int u = 0; u < 4; ++u) {
-            if (u < wv) { before += wave_new[u]; before_fb += wave_fb[u]; }
-            total += wave_new[u];
-            total_fb += wave_fb[u];
-        }
-        if (a < S) code_s[a] = found;
-        if (is_new) {
-            const uint64_t lower = (1ull << lane) - 1ull;
-            const int x = before + (int)__popcll(mask & lower);
-            int crow = spec_row0 + spec_at;
-            if (is_fb) {
-                const int r = before_fb + (int)__popcll(mask_fb & lower);
-                new_src[row0 + r] = i;
-                crow = r;
-            }
-            sel_row[row0 + x] = crow;
-            sel_pos[row0 + x] = a;
-        }
-        base += total;
-        base_fb += total_fb;
-        __syncthreads();
-    }
-    if (tid == 0) {
-        n_new[h] = base_fb;
-        n_sel[h] = base;
-    }
-    // the lists that stay: the neighbourhood of a source does not depend on the scores
-    for (long u = tid; u < (long)S * m; u += 256) {
-        const int a = (int)(u / m), r = (int)(u % m);
-        const int from = code_s[a];
-        if (from >= 0) {
-            nbr[(row0 + a) * m + r] = prev_nbr[(row0 + from) * m + r];
-            nbr_e[(row0 + a) * m + r] = prev_e[(row0 + from) * m + r];
-        }
-    }
+    match_head(a, blockIdx.x, bad, cur + (long)blockIdx.x * a.S, match_lds, wave_new, wave_fb, threadIdx.x);
 }
 
 // Columns per workgroup: about 1024 workgroups in flight over all heads and source
@@ -1128,6 +1039,16 @@ int mfma_sample_cols(int P)
     if (ps < 2048) ps = 2048;
     if (ps > 8192) ps = 8192;
     return ps;
+}
+
+// Keys in the sample of a later round's pass over the new sources that have no kept list.  There are
+// usually none, so the pass gives up its chunked sample and the launch that adds the chunks up (4.6 us
+// a round) for a sample half as large that one workgroup walks; at most twice as many candidates
+// reach the looser bound, which the slices (four times the share of the full sample's) hold.
+static int late_sample_cols(int P)
+{
+    const int ps = mfma_sample_cols(P);
+    return P > 131072 ? ps : (ps / 2 > 2048 ? ps / 2 : 2048);
 }
 
 // Rank of the sampled edge that the bound is taken at.  The bound is useful for a source when at
@@ -1242,13 +1163,13 @@ int bound_chunks(int Hkv, int P, int sgroups)
 
 template <int SB, int BINS>
 hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
-                        int src_pitch, const int32_t *n_src, void *hist_part, float *tau, int pitch, int row0,
-                        int32_t *overflow, hipStream_t st)
+                        int src_pitch, const int32_t *n_src, bool late, void *hist_part, float *tau, int pitch,
+                        int row0, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
-    const int ps = mfma_sample_cols(P), stride = P / ps;
+    const int ps = late ? late_sample_cols(P) : mfma_sample_cols(P), stride = P / ps;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    const int chunks = bound_chunks(Hkv, P, sgroups);
+    const int chunks = late ? 1 : bound_chunks(Hkv, P, sgroups);
     const int chunk_cols = (((ps + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
     const int rank = mfma_bound_rank(m, stride);
     if (!allow_big_lds((const void *)cosine_bound_kernel<SB, BINS>)) return hipGetLastError();
@@ -1264,12 +1185,12 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
 
 template <int SB, int RING>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
-                         int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, int row0, const float *tau,
-                         void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
+                         int src_pitch, const int32_t *n_src, bool late, const MfmaFilterPlan &g, int row0,
+                         const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    const int stride = P / mfma_sample_cols(P);
+    const int stride = P / (late ? late_sample_cols(P) : mfma_sample_cols(P));
     // Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
     // per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
     // rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a
@@ -1291,16 +1212,10 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
 
 size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g)
 {
-    // (the first round's launch has the most rows per workgroup and the fewest groups)
-    size_t need = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        const int sb = pass == 0 ? g.sb : 2, rows = pass == 0 ? g.S + g.X : g.S;
-        const int rows_wg = kBlk * sb, sgroups = (rows + rows_wg - 1) / rows_wg;
-        const int chunks = bound_chunks(Hkv, P, sgroups);
-        const size_t bytes = chunks > 1 ? (size_t)Hkv * sgroups * chunks * rows_wg * 256 * 4 : 0;
-        if (bytes > need) need = bytes;
-    }
-    return need;
+    // (only the passes over a full source list cut the sample into chunks)
+    const int rows = g.S + g.X, rows_wg = kBlk * g.sb, sgroups = (rows + rows_wg - 1) / rows_wg;
+    const int chunks = bound_chunks(Hkv, P, sgroups);
+    return chunks > 1 ? (size_t)Hkv * sgroups * chunks * rows_wg * 256 * 4 : 0;
 }
 
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
@@ -1309,12 +1224,10 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
                                     hipStream_t st)
 {
     if (first_round && g.sb == 3)
-        return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, hist_part, tau, g.pitch,
-                                    0, overflow, st);
-    if (first_round)
-        return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, hist_part, tau, g.pitch, 0,
-                                    overflow, st);
-    return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, hist_part, tau, g.pitch, 0, overflow, st);
+        return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false,
+                                    hist_part, tau, g.pitch, 0, overflow, st);
+    return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, hist_part, tau, g.pitch, 0,
+                                overflow, st);
 }
 
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
@@ -1323,22 +1236,15 @@ hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, in
                                      int32_t *overflow, hipStream_t st)
 {
     if (first_round && g.sb == 3)
-        return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand, cand_cnt,
-                                    overflow, st);
-    if (first_round)
-        return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt, overflow, st);
-    return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt, overflow, st);
+        return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false, g, 0, tau, cand,
+                                    cand_cnt, overflow, st);
+    return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, g, 0, tau, cand, cand_cnt,
+                                overflow, st);
 }
 
-hipError_t launch_match_sources(const int32_t *prev, const int32_t *cur, int Hkv, int m, const MfmaFilterPlan &g,
-                                const int32_t *prev_nbr, const float *prev_e, int32_t *nbr, float *nbr_e,
-                                const int32_t *ext, int32_t *spec_bad, const int32_t *overflow, bool first_match,
-                                int32_t *new_src, int32_t *n_new, int32_t *sel_row, int32_t *sel_pos,
-                                int32_t *n_sel, hipStream_t st)
+hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv, hipStream_t st)
 {
-    hipLaunchKernelGGL(match_sources_kernel, dim3(Hkv), dim3(256), (size_t)(2 * g.S + g.X) * 4, st, prev, cur, g.S,
-                       m, prev_nbr, prev_e, nbr, nbr_e, ext, g.X, g.S, spec_bad, overflow, first_match ? 1 : 0, new_src,
-                       n_new, sel_row, sel_pos, n_sel);
+    hipLaunchKernelGGL(match_sources_kernel, dim3(Hkv), dim3(kMatchBlock), (size_t)(2 * a.S + a.X) * 4, st, a, cur);
     return hipGetLastError();
 }
 

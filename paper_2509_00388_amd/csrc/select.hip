@@ -14,6 +14,7 @@
 // sweeps; longer rows are re-read from L2 in every sweep.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "match.hpp"
 #include "mfma_tile.hpp"
 
 #include <type_traits>
@@ -603,6 +604,26 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
     else pick_row_long(xr, n, k, o, L, tid, lane, wv);
 }
 
+// A later round's sources and, in the same workgroup, where their lists come from (a launch of its own
+// for the match cost 6.1 us with 8 heads; a launch is 4.6 us before it does anything).
+template <int ITEMS>
+__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(const float *__restrict__ x, int n, MatchArgs a,
+                                                                int32_t *__restrict__ src_out)
+{
+    static_assert(kPickBlock == kMatchBlock, "one workgroup does both");
+    __shared__ PickLds<kPickBlock> L;
+    __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const float *xr = x + (long)h * n;
+    int32_t *src = src_out + (long)h * a.S;
+    const PickOut o{a.S, src, nullptr, nullptr};
+    const bool bad = match_load(a, h, match_lds, tid);
+    if constexpr (ITEMS > 0) pick_row<kPickBlock, ITEMS, false>(xr, n, a.S, o, L, tid, lane, wv);
+    else pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
+    __syncthreads();   // the sources are written
+    match_head(a, h, bad, src, match_lds, wave_new, wave_fb, tid);
+}
+
 // The k best edges of each row of a dense edge block, ascending indices, with their values.
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void pick_edges_kernel(const float *__restrict__ x, long ld, int n, int k,
@@ -1001,6 +1022,22 @@ static hipError_t launch_pick(const float *x, long ld, int n, int rows, int k, i
     if (n <= 1024) GKV_PICK(1);
     else if (n <= 2048) GKV_PICK(2);
     else if (n <= 4096) GKV_PICK(4);
+    else if (n <= 8192) GKV_PICK(8);
+    else if (n <= 16384) GKV_PICK(16);
+    else if (n <= 32768) GKV_PICK(32);
+    else GKV_PICK(0);
+#undef GKV_PICK
+    return hipGetLastError();
+}
+
+bool pick_match_applies(int S) { return S <= kSmallK; }
+
+hipError_t launch_pick_match(const float *x, int n, int rows, const MatchArgs &a, int32_t *src, hipStream_t st)
+{
+    if (a.S > kSmallK || a.X > kMaxExtSources) return hipErrorInvalidValue;
+#define GKV_PICK(ITEMS) \
+    hipLaunchKernelGGL(pick_match_kernel<ITEMS>, dim3(rows), dim3(kPickBlock), 0, st, x, n, a, src)
+    if (n <= 4096) GKV_PICK(4);   // (lists are kept on the filter route only: 2048 nodes or more)
     else if (n <= 8192) GKV_PICK(8);
     else if (n <= 16384) GKV_PICK(16);
     else if (n <= 32768) GKV_PICK(32);
