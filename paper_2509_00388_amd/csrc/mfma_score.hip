@@ -265,21 +265,35 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     if (fused)
         for (int u = tid; u < SPLIT * span; u += NT) vs[u] = 0.f;   // zero padding outside the row
 
-    if (tid < R) {   // row statistics of the whole head: merge the chunks of pass A
-        // (the loads of eight chunks leave together; with few heads there are 32 chunks, and one round
-        // trip after the other made this the longest part of the kernel's start: 25.4 -> 21.9 us there)
+    {   // Row statistics of the whole head: merge the chunks of pass A, PARTS threads per row, each a run
+        // of chunks whose loads leave eight at a time.  (One thread per row and one load after the
+        // other was the longest part of the kernel's start with few heads: 25.4 us with 32 chunks, 21 us now.)
+        constexpr int PARTS = NT / R;
+        __shared__ float2 stat_s[PARTS][R];
+        const int row = tid % R, pt = tid / R, per = (part_chunks + PARTS - 1) / PARTS;
+        const int cb = min(pt * per, part_chunks), ce = min(cb + per, part_chunks);
         float mm = -INFINITY, zz = 0.f;
-        for (int c0 = 0; c0 < part_chunks; c0 += 8) {
-            float2 o[8];
+        if (pt < PARTS) {
+            for (int c0 = cb; c0 < ce; c0 += 8) {
+                float2 o[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                o[u] = *reinterpret_cast<const float2 *>(
-                    part + (((long)h * part_chunks + min(c0 + u, part_chunks - 1)) * R_total + row_base + tid) * 2);
+                for (int u = 0; u < 8; ++u)
+                    o[u] = *reinterpret_cast<const float2 *>(
+                        part + (((long)h * part_chunks + min(c0 + u, ce - 1)) * R_total + row_base + row) * 2);
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (c0 + u < part_chunks) merge_stats(mm, zz, o[u].x, o[u].y);
+                for (int u = 0; u < 8; ++u)
+                    if (c0 + u < ce) merge_stats(mm, zz, o[u].x, o[u].y);
+            }
+            stat_s[pt][row] = make_float2(mm, zz);
         }
-        bias_s[tid] = mm + __log2f(zz);   // zz >= 1: the row maximum itself contributes exp2(0)
+        __syncthreads();
+        if (tid < R) {
+            mm = stat_s[0][tid].x;
+            zz = stat_s[0][tid].y;
+#pragma unroll
+            for (int u = 1; u < PARTS; ++u) merge_stats(mm, zz, stat_s[u][tid].x, stat_s[u][tid].y);
+            bias_s[tid] = mm + __log2f(zz);   // zz >= 1: the row maximum itself contributes exp2(0)
+        }
     }
     __syncthreads();
 
@@ -373,13 +387,47 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
 // wave so that loading the query operand is amortised.  The statistics pass takes half as many,
 // twice as long workgroups as the votes pass (its workgroups hold no votes in LDS, and every
 // workgroup pays for its queries and its first tiles: 423 -> 409 us on the 32-layer batch).
-constexpr int kStatsWorkgroups = 512;
-int chunk_keys_for(int Hkv, int N, int wgs = 1024)
+// Keys per workgroup of the votes pass.  A compute unit runs one of these workgroups at a time (208
+// registers a lane, eight waves), and every workgroup pays for its queries, its first tiles and the merge
+// of the statistics -- about as long as 256 keys take.  So the cut with the fewest keys per compute unit
+// wins, counting whole rounds of 256 workgroups: for few heads as many chunks as one round takes, for
+// many as few as keep the rounds full.  At most `most` keys: the votes of a chunk sit in LDS beside the
+// key tiles, two or four row groups of them; at least two tiles, as the pooling window's halo is read
+// twice.  (1024 workgroups of at least 1024 keys before, chunks of 6144 with 256 query rows; us, before /
+// now: 8 heads of 4096 keys 18.0 / 13.6, of 16384 21.0 / 16.3, of 65536 51 / 31; 128 heads of 8192 76 / 51;
+// 8 heads of 32768 keys with 256 query rows 103 / 28.)
+constexpr int kComputeUnits = 256;
+int votes_chunk_keys(int Hkv, int N, int rows)
 {
-    long ck = ((long)Hkv * N + wgs - 1) / wgs;
-    if (ck < 1024) ck = 1024;
-    ck = ((ck + 127) / 128) * 128;                            // 4 waves x 32 keys
-    return (int)ck;
+    const int least = 256, most = rows == 256 ? 6144 : 8192;
+    const int cmin = (N + most - 1) / most, cmax = (N + least - 1) / least > cmin ? (N + least - 1) / least : cmin;
+    long best = -1;
+    int keys = 0;
+    auto consider = [&](long chunks) {
+        const long c = chunks < cmin ? cmin : (chunks > cmax ? cmax : chunks);
+        const long ck = ((N + c - 1) / c + 127) / 128 * 128;
+        const long rounds = ((long)Hkv * ((N + ck - 1) / ck) + kComputeUnits - 1) / kComputeUnits;
+        const long cost = rounds * (ck + 256);
+        if (best < 0 || cost < best) { best = cost; keys = (int)ck; }
+    };
+    consider(cmin);
+    const long r0 = ((long)Hkv * cmin + kComputeUnits - 1) / kComputeUnits;
+    for (long r = r0; r < r0 + 4; ++r) consider(r * kComputeUnits / Hkv);
+    return keys;
+}
+
+// Keys per workgroup of the statistics pass: 512 workgroups of at least 1024 keys, or one round of
+// at least one tile each while 1024 keys would leave compute units idle (8 heads of 4096 keys 16.9 -> 10.2 us,
+// of 16384 17.5 -> 13.8).  Larger launches keep 512 workgroups: one round of twice as many keys is up to
+// a fifth faster for mid sizes, but a lane's sum of exponentials then runs over twice as many terms in 32
+// bits (error of the scores against 64 bits at 256 heads of 32768 keys 1.5e-6 -> 2.4e-6).
+int stats_chunk_keys(int Hkv, int N)
+{
+    const long total = (long)Hkv * N;
+    long ck = (total + 511) / 512, least = (total + kComputeUnits - 1) / kComputeUnits;
+    least = least < 128 ? 128 : (least > 1024 ? 1024 : least);
+    if (ck < least) ck = least;
+    return (int)((ck + 127) / 128 * 128);                     // 4 waves x 32 keys
 }
 
 }  // namespace
@@ -387,7 +435,7 @@ int chunk_keys_for(int Hkv, int N, int wgs = 1024)
 MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N)
 {
     MfmaScorePlan pl;
-    const int ck = chunk_keys_for(Hkv, N, kStatsWorkgroups);
+    const int ck = stats_chunk_keys(Hkv, N);
     pl.chunks = (N + ck - 1) / ck;
     pl.part_bytes = (size_t)Hkv * pl.chunks * rows * 2 * sizeof(float);
     return pl;
@@ -424,7 +472,7 @@ hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int 
 {
     const int G = Hq / Hkv, R = G * w, P = N - w;
     const MfmaScorePlan plan = mfma_score_plan(Hkv, R, N);
-    const int ck = chunk_keys_for(Hkv, N, kStatsWorkgroups);
+    const int ck = stats_chunk_keys(Hkv, N);
     const float c = scale * 1.4426950408889634f;
     const uint16_t *K = (const uint16_t *)Kc, *Q = (const uint16_t *)Qw;
     if (R == 256) {   // one workgroup takes all 256 rows: 2 key streams x 4 row groups, tiles of 64 keys
@@ -491,8 +539,8 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
     // fused pooling: a workgroup also multiplies pool_half keys on either side of its chunk; the
     // P prefix keys are spread evenly over the chunks
     const int pool_half = fused_pool_kernel > 0 ? (fused_pool_kernel - 1) / 2 : -1;
-    const int vchunks = (N + chunk_keys_for(Hkv, N) - 1) / chunk_keys_for(Hkv, N);
-    const int ck = pool_half >= 0 ? (P + vchunks - 1) / vchunks : chunk_keys_for(Hkv, N);
+    const int vck = votes_chunk_keys(Hkv, N, R), vchunks = (N + vck - 1) / vck;
+    const int ck = pool_half >= 0 ? (P + vchunks - 1) / vchunks : vck;
     const float c = scale * 1.4426950408889634f;
     const uint16_t *K = (const uint16_t *)Kc, *Q = (const uint16_t *)Qw;
     const int merged = 1;
@@ -500,10 +548,7 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
     const int vote_rows = mfma_score_vote_rows(G, w, per_qhead_votes);
     int vote_row_base = 0;
     if (R == 256 && !per_qhead_votes) {   // all rows in one workgroup (see the statistics pass): four row groups
-        // with fused pooling the votes of four row groups stay in LDS: chunks of 6144 keys
-        const int ckv = pool_half >= 0 ? 6144 : ck;
-        const dim3 gridv = pool_half >= 0 ? dim3((P + ckv - 1) / ckv, Hkv) : grid;
-        launch_votes_nb<8, 4, 2>(gridv, K, Q, N, P, w, G, ckv, c, part, plan.chunks, 0, votes, R, 0, vote_rows, 0, 1,
+        launch_votes_nb<8, 4, 2>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, 0, votes, R, 0, vote_rows, 0, 1,
                                  pool_half, st);
         return hipGetLastError();
     }
