@@ -58,9 +58,9 @@ enum { GRAPHKV_POOL_AVG = 0, GRAPHKV_POOL_MAX = 1 };
  * evicted sets the score to -infinity. */
 enum { GRAPHKV_SIGNAL_DECAY = 0, GRAPHKV_SIGNAL_ENHANCED = 1, GRAPHKV_SIGNAL_EVICTED = 2 };
 /* Kernel family: AUTO picks the bf16 MFMA kernels when the shape allows them
- * (bf16 and d = 128; for scoring also G*w a multiple of 32 and at most 256, and
- * w a multiple of 32 with max pooling) and the scalar kernels otherwise; GENERIC
- * forces the scalar kernels (same results up to fp32 rounding order). */
+ * (bf16 and d = 128; for scoring also G*w at most 256, and w a multiple of 32 with
+ * max pooling) and matrix-core kernels for any type and head dimension otherwise;
+ * GENERIC forces the scalar kernels (same results up to fp32 rounding order). */
 enum { GRAPHKV_IMPL_AUTO = 0, GRAPHKV_IMPL_GENERIC = 1 };
 /* Which tensors the edges of the whole-pass calls are cosines of (Discussion,
  * "Exploration of similarity for Graph Edge"): e_ij = cos(x_i, y_j) with x the
@@ -272,7 +272,7 @@ int32_t graphkv_profile_begin(void);
 int32_t graphkv_profile_end(double *ms, int64_t *launches);
 const char *graphkv_kernel_name(int32_t id);
 
-/* 1 if AUTO would run the MFMA kernels for these params, 0 otherwise. */
+/* 1 if AUTO would run the streaming bf16 kernels (d = 128) for scoring with these params, 0 otherwise. */
 int32_t graphkv_uses_mfma(const graphkv_params *p);
 
 #ifdef __cplusplus

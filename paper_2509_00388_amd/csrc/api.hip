@@ -62,10 +62,9 @@ struct Workspace {
     size_t total;
 };
 
-// The MFMA kernels cover bf16 keys with d = 128.  Scoring additionally needs the
-// stacked query rows G*w to fill whole 32-row MFMA blocks (at most 256 rows: 256 rows
-// in one workgroup, other counts beyond 128 in parts of 128); per-query-head votes (max pooling) need w itself to be a multiple
-// of 32.
+// The kernels of mfma_score.hip and mfma_cosine.hip cover bf16 keys with d = 128; everything else runs in
+// gemm.hip.  Scoring takes at most 256 stacked query rows G*w (filled up to whole 32-row blocks);
+// per-query-head votes (max pooling) need w itself to be a multiple of 32.
 bool mfma_cosine_ok(const graphkv_params *p)
 {
     // (fewer than 2^24 rows: the tile loads address a head's rows with 32-bit byte offsets)
@@ -77,7 +76,7 @@ bool mfma_score_ok(const graphkv_params *p)
 {
     if (!mfma_cosine_ok(p) || p->n_kv_heads < 1 || p->n_q_heads < p->n_kv_heads) return false;
     const int rows = (p->n_q_heads / p->n_kv_heads) * p->window;
-    if (rows % 32 != 0 || rows > 256) return false;
+    if (rows > 256) return false;
     // per-query-head votes: a query head's rows must not straddle a 128-row part
     if (p->pool_mode == GRAPHKV_POOL_MAX && (p->window % 32 != 0 || (rows > 128 && 128 % p->window != 0)))
         return false;
@@ -163,13 +162,15 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     const bool scoring = p->scorer == GRAPHKV_SCORER_ATTENTION && p->n_q_heads >= p->n_kv_heads &&
                          p->pool_kernel >= 1;
     W.logits = take(!D.mfma_score && scoring ? rows * D.N * 4 : 0);
-    W.row_max = take(rows * 4);
+    W.row_max = take(rows * 8);   // (or the pairs of launch_gemm_merge)
     W.row_sum = take(rows * 4);
     // votes per query head (or row group); not needed when pass B pools and groups them itself
+    const int per_q = p->pool_mode == GRAPHKV_POOL_MAX;
     const bool votes_stay_in_lds = scoring && (D.mfma_score
-        ? mfma_score_fuses_pool(D.G, D.w, p->pool_mode == GRAPHKV_POOL_MAX, p->pool_kernel)
+        ? mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel)
         : D.gemm && gemm_votes_pools(p->pool_kernel));
-    W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.Hq * D.P * 4 : 0);
+    const int vote_rows = D.mfma_score ? mfma_score_vote_rows(D.G, D.w, per_q) : D.G;
+    W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * vote_rows * D.P * 4 : 0);
     // the dense edge block [heads, S, P] of the routes that materialise it; on the filter route
     // only the scratch rows of the workgroups that redo overflowed heads
     W.E = take(D.filter ? redo_rows_scratch_bytes(D.H, D.S, D.P) : (size_t)D.H * D.S * D.P * 4);
@@ -177,7 +178,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.nbr = take((size_t)D.H * D.S * D.m * 4);
     W.nbr_e = take((size_t)D.H * D.S * D.m * 4);
     W.scores = take((size_t)D.H * D.P * 4);
-    W.part = take(D.mfma_score ? mfma_score_plan(D.H, D.G * D.w, D.N).part_bytes
+    W.part = take(D.mfma_score ? mfma_score_plan(D.H, mfma_score_rows(D.G, D.w, per_q), D.N).part_bytes
                   : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
     const MfmaFilterPlan &g = D.fp;
     const size_t frows = D.filter ? (size_t)D.H * g.pitch : 0;   // rows of the per-row buffers
@@ -268,7 +269,7 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
     if (D.mfma_score) {
         const int per_q = p->pool_mode == GRAPHKV_POOL_MAX;
         GKV_LAUNCH(GRAPHKV_K_SCORE_STATS, launch_mfma_score_stats(Kc, Qw, D.H, D.Hq, D.N, D.w, D.scale,
-                                                                  at<float>(ws, W.part), st));
+                                                                  per_q, at<float>(ws, W.part), st));
         if (mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel)) {
             // average pooling and the mean over the group happen inside pass B
             GKV_LAUNCH(GRAPHKV_K_SCORE_VOTES,
@@ -290,8 +291,15 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
         GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS,
                    launch_gemm_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale, logits, part, st));
         if (gemm_votes_pools(p->pool_kernel)) {
-            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_votes(logits, part, D.H, D.Hq, D.N, D.w, p->pool_kernel,
-                                                                  p->pool_mode, scores, st));
+            int chunks = gemm_score_plan(D.H, D.G * D.w, D.N).chunks;
+            if (gemm_merges_first(D.H, D.G * D.w, D.N)) {
+                float *stat = row_max;   // (max, sum) pairs
+                GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_merge(part, D.H, D.Hq, D.N, D.w, stat, st));
+                part = stat;
+                chunks = 1;
+            }
+            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_votes(logits, part, chunks, D.H, D.Hq, D.N, D.w,
+                                                                  p->pool_kernel, p->pool_mode, scores, st));
             return GRAPHKV_OK;
         }
         GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_merge_part(part, D.H, D.Hq, D.N, D.w, row_max, row_sum, st));

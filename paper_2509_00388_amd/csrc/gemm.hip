@@ -203,82 +203,133 @@ __global__ __launch_bounds__(256) void gemm_logits_kernel(
 }
 
 // Votes, pooling and the mean over the group in one go: scores[h, j] = 1/G sum_g pool(votes of query
-// head g).  A workgroup takes 256 keys (pool_half of them on either side only for the pooling), its
-// four groups of 256 threads share the window rows; the statistics of 64 rows at a time are merged
-// from the chunks into LDS first.  Average pooling adds the group before it pools.
-constexpr int kVoteKeys = 256;
+// head g).  A workgroup takes KEYS keys (pool_half of them on either side only for the pooling), its
+// PARTS groups of KEYS threads share the query rows; the statistics of up to kVoteRows rows at a time are
+// merged from the chunks into LDS first.  Average pooling adds the whole group before it pools, so only
+// max pooling has to stop at every query head.  (Merging the statistics of one query head at a time:
+// 24 us for 8 heads of 128 rows x 4064 keys, 30 us for 8160; this way, merge included, 17 and 27 us.)
 constexpr int kVoteHalf = 32;    // widest pooling half-window taken here
+constexpr int kVoteRows = 512;   // rows whose statistics sit in LDS
 
-__global__ __launch_bounds__(1024) void gemm_votes_kernel(
+template <int KEYS, int PARTS>
+__global__ __launch_bounds__(KEYS * PARTS) void gemm_votes_kernel(
     const float *__restrict__ logits, const float *__restrict__ part, int chunks, int N, int P, int w, int G,
     int pool_half, int pool_mode, float *__restrict__ scores)
 {
-    __shared__ float vs[4][kVoteKeys], s_max[64], s_inv[64];
-    const int h = blockIdx.y, tid = threadIdx.x, t = tid & 255, p = tid >> 8;
-    const int R = G * w, tile = kVoteKeys - 2 * pool_half;
+    constexpr int NT = KEYS * PARTS;
+    __shared__ float vs[PARTS][KEYS], s_max[kVoteRows], s_inv[kVoteRows];
+    const int h = blockIdx.y, tid = threadIdx.x, t = tid % KEYS, p = tid / KEYS;
+    const int R = G * w, tile = KEYS - 2 * pool_half;
     const int j = blockIdx.x * tile - pool_half + t;          // this thread's key
     const bool in = j >= 0 && j < P;
     const int jc = min(max(j, 0), P - 1);
-    float total = 0.f;
-    for (int g = 0; g < G; ++g) {
-        float v = 0.f;
-        for (int r0 = 0; r0 < w; r0 += 64) {
-            const int rows = min(64, w - r0);
-            __syncthreads();
-            {   // 16 lanes per row merge its chunks
-                const int r = tid >> 4, sub = tid & 15;
-                float mm = -INFINITY, zz = 0.f;
-                if (r < rows)
-                    for (int c = sub; c < chunks; c += 16) {
-                        const float2 o = *reinterpret_cast<const float2 *>(
-                            part + (((long)h * chunks + c) * R + g * w + r0 + r) * 2);
-                        merge_exp(mm, zz, o.x, o.y);
-                    }
+    const float *lh = logits + (long)h * R * N + jc;
+    float total = 0.f, v = 0.f;
+    auto all_parts = [&] {
+        float sum = vs[0][t];
 #pragma unroll
-                for (int o = 8; o > 0; o >>= 1) {
-                    const float m2 = __shfl_xor(mm, o, kWave), z2 = __shfl_xor(zz, o, kWave);
-                    merge_exp(mm, zz, m2, z2);
-                }
-                if (sub == 0 && r < rows) {
-                    s_max[r] = mm;
-                    s_inv[r] = 1.0f / zz;
-                }
-            }
-            __syncthreads();
-            const float *l = logits + ((long)h * R + g * w + r0) * N + jc;
+        for (int u = 1; u < PARTS; ++u) sum += vs[u][t];
+        return sum;
+    };
+    // rows [first, last) of the head, whose statistics start at entry first - base of the tables
+    auto vote = [&](int first, int last, int base) {
 #pragma unroll 8
-            for (int r = p; r < rows; r += 4) v += expf(l[(long)r * N] - s_max[r]) * s_inv[r];
-        }
-        vs[p][t] = v;
+        for (int r = first + p; r < last; r += PARTS) v += expf(lh[(long)r * N] - s_max[r - base]) * s_inv[r - base];
+    };
+    for (int base = 0; base < R; base += kVoteRows) {
+        const int rows = min(kVoteRows, R - base);
         __syncthreads();
-        if (p == 0) {
-            v = ((vs[0][t] + vs[1][t]) + vs[2][t]) + vs[3][t];
-            if (pool_mode == 0) total += v;
-            else vs[0][t] = in ? v : -INFINITY;
+        // the chunks of a row are merged by 8 to 64 lanes, as many as there are for all rows at once
+        int per_row = 64;
+        while (per_row > 8 && NT / per_row < rows) per_row >>= 1;
+        for (int r0 = 0; r0 < rows; r0 += NT / per_row) {
+            const int r = r0 + tid / per_row, sub = tid & (per_row - 1);
+            float mm = -INFINITY, zz = 0.f;
+            if (r < rows)
+                for (int c0 = sub; c0 < chunks; c0 += 4 * per_row) {   // (four loads leave together)
+                    float2 o[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        o[u] = *reinterpret_cast<const float2 *>(
+                            part + (((long)h * chunks + min(c0 + per_row * u, chunks - 1)) * R + base + r) * 2);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (c0 + per_row * u < chunks) merge_exp(mm, zz, o[u].x, o[u].y);
+                }
+            for (int o = per_row >> 1; o > 0; o >>= 1) {
+                const float m2 = __shfl_xor(mm, o, kWave), z2 = __shfl_xor(zz, o, kWave);
+                merge_exp(mm, zz, m2, z2);
+            }
+            if (sub == 0 && r < rows) {
+                s_max[r] = mm;
+                s_inv[r] = 1.0f / zz;
+            }
         }
-        if (pool_mode != 0) {
+        __syncthreads();
+        if (pool_mode == 0) {
+            vote(base, base + rows, base);
+            continue;
+        }
+        // max pooling: the rows of the query heads this batch touches, one head after the other
+        for (int g = base / w; g <= (base + rows - 1) / w; ++g) {
+            vote(max(base, g * w), min(base + rows, (g + 1) * w), base);
+            if ((g + 1) * w > base + rows) break;   // the head goes on in the next batch
+            vs[p][t] = v;
+            v = 0.f;
             __syncthreads();
-            if (p == 0 && t >= pool_half && t < kVoteKeys - pool_half) {
+            const float sum = all_parts();
+            __syncthreads();
+            if (p == 0) vs[0][t] = in ? sum : -INFINITY;
+            __syncthreads();
+            if (p == 0 && t >= pool_half && t < KEYS - pool_half) {
                 float best = -INFINITY;
                 for (int u = t - pool_half; u <= t + pool_half; ++u) best = fmaxf(best, vs[0][u]);
                 total += best;
             }
+            __syncthreads();
         }
     }
     if (pool_mode == 0) {
+        vs[p][t] = v;
         __syncthreads();
-        if (p == 0) vs[0][t] = in ? total : 0.f;      // zero padding outside the row
+        const float sum = all_parts();
         __syncthreads();
-        if (p == 0 && t >= pool_half && t < kVoteKeys - pool_half) {
-            total = 0.f;
+        if (p == 0) vs[0][t] = in ? sum : 0.f;      // zero padding outside the row
+        __syncthreads();
+        if (p == 0 && t >= pool_half && t < KEYS - pool_half) {
             for (int u = t - pool_half; u <= t + pool_half; ++u) total += vs[0][u];
             total = total / (float)(2 * pool_half + 1);
         }
     }
-    if (p == 0 && in && t >= pool_half && t < kVoteKeys - pool_half) scores[(long)h * P + j] = total / (float)G;
+    if (p == 0 && in && t >= pool_half && t < KEYS - pool_half) scores[(long)h * P + j] = total / (float)G;
 }
 
-// Row statistics on their own (wide pooling windows, which take the separate votes and pooling kernels).
+// Row statistics on their own: stat [rows] (max, sum).  Every workgroup of the votes kernel would otherwise
+// merge all chunks of its head again, which with 64 chunks takes longer than the votes.  16 lanes per row.
+__global__ __launch_bounds__(256) void merge_rows_kernel(const float *__restrict__ part, int chunks, int R, int rows,
+                                                         float2 *__restrict__ stat)
+{
+    const int row = blockIdx.x * 16 + (threadIdx.x >> 4), sub = threadIdx.x & 15;
+    const int h = min(row, rows - 1) / R, r = min(row, rows - 1) % R;
+    float m = -INFINITY, z = 0.f;
+    for (int c0 = sub; c0 < chunks; c0 += 64) {   // (four loads leave together)
+        float2 o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            o[u] = *reinterpret_cast<const float2 *>(part + (((long)h * chunks + min(c0 + 16 * u, chunks - 1)) * R + r) * 2);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c0 + 16 * u < chunks) merge_exp(m, z, o[u].x, o[u].y);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+        const float m2 = __shfl_xor(m, o, kWave), z2 = __shfl_xor(z, o, kWave);
+        merge_exp(m, z, m2, z2);
+    }
+    if (sub == 0 && row < rows) stat[row] = make_float2(m, z);
+}
+
+// The same for wide pooling windows, which take the separate votes and pooling kernels.
 __global__ __launch_bounds__(256) void merge_part_kernel(const float *__restrict__ part, int chunks, int R, int rows,
                                                          float *__restrict__ row_max, float *__restrict__ row_sum)
 {
@@ -367,13 +418,13 @@ __global__ __launch_bounds__(256) void gemm_cosine_kernel(
 // Rows per workgroup: up to 128, no more than the rows need.
 int row_blocks(int rows) { return rows <= 32 ? 1 : (rows <= 64 ? 2 : 4); }
 
-// Keys per workgroup: a multiple of the largest key tile, for about 1024 workgroups.
+// Keys per workgroup: whole key tiles (128 keys with one row block, 64 with more), for about 1024 workgroups.
 int gemm_chunk_keys(int Hkv, int rows, int N)
 {
     const int nb = row_blocks(rows), groups = (rows + 32 * nb - 1) / (32 * nb);
     long ck = ((long)Hkv * groups * N + 1023) / 1024;
-    ck = (ck + 127) / 128 * 128;
-    return (int)ck;
+    const long tile = nb == 1 ? Shape<1>::TK : Shape<4>::TK;
+    return (int)((ck + tile - 1) / tile * tile);
 }
 
 }  // namespace
@@ -414,13 +465,30 @@ hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_votes(const float *logits, const float *part, int Hkv, int Hq, int N, int w, int pool_kernel,
-                             int pool_mode, float *scores, hipStream_t st)
+// From 8192 (row, chunk) pairs a head on (us, merged by every votes workgroup / first: 128 rows x 128 chunks
+// 39.7 / 26.6, 128 x 64 18.0 / 17.1, 128 x 32 14.9 / 19.4, 16 x 64 14.3 / 16.5).
+bool gemm_merges_first(int Hkv, int rows, int N) { return (long)gemm_score_plan(Hkv, rows, N).chunks * rows >= 8192; }
+
+hipError_t launch_gemm_merge(const float *part, int Hkv, int Hq, int N, int w, float *stat, hipStream_t st)
 {
-    const int G = Hq / Hkv, P = N - w, half = (pool_kernel - 1) / 2, tile = kVoteKeys - 2 * half;
-    const GemmScorePlan pl = gemm_score_plan(Hkv, G * w, N);
-    hipLaunchKernelGGL(gemm_votes_kernel, dim3((P + tile - 1) / tile, Hkv), dim3(1024), 0, st, logits, part, pl.chunks,
-                       N, P, w, G, half, pool_mode, scores);
+    const int R = Hq / Hkv * w, rows = Hq * w;
+    hipLaunchKernelGGL(merge_rows_kernel, dim3((rows + 15) / 16), dim3(256), 0, st, part,
+                       gemm_score_plan(Hkv, R, N).chunks, R, rows, (float2 *)stat);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_votes(const float *logits, const float *part, int chunks, int Hkv, int Hq, int N, int w,
+                             int pool_kernel, int pool_mode, float *scores, hipStream_t st)
+{
+    const int G = Hq / Hkv, P = N - w, half = (pool_kernel - 1) / 2;
+#define GKV_VOTES(KEYS, PARTS)                                                                                     \
+    hipLaunchKernelGGL((gemm_votes_kernel<KEYS, PARTS>), dim3((P + KEYS - 2 * half - 1) / (KEYS - 2 * half), Hkv), \
+                       dim3(KEYS * PARTS), 0, st, logits, part, chunks, N, P, w, G, half, pool_mode, scores)
+    // few query rows: half-size workgroups; few keys: narrower ones, to reach all compute units
+    if (G * w <= 32) GKV_VOTES(256, 2);
+    else if ((long)Hkv * P <= 40000) GKV_VOTES(128, 8);
+    else GKV_VOTES(256, 4);
+#undef GKV_VOTES
     return hipGetLastError();
 }
 

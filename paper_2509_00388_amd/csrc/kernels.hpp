@@ -66,12 +66,15 @@ GemmScorePlan gemm_score_plan(int Hkv, int rows, int N);   // rows: stacked quer
 // logits [Hq*w, N] (fp32, scaled) and part [Hkv, chunks, G*w] (max, sum of exp) over visible keys.
 hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d, int N, int w,
                               float scale, float *logits, float *part, hipStream_t st);
-// scores [Hkv, P] from logits and part, votes, pooling and the mean over the group included
-// (gemm_votes_pools(pool_kernel)); wider pooling windows take launch_merge_part (row statistics
-// as launch_generic_logits leaves them), launch_generic_votes and launch_pool_group.
+// scores [Hkv, P] from logits and the row statistics of `chunks` chunks, votes, pooling and the mean over
+// the group included (gemm_votes_pools(pool_kernel)); wider pooling windows take launch_merge_part (row
+// statistics as launch_generic_logits leaves them), launch_generic_votes and launch_pool_group.  With many
+// chunks (gemm_merges_first) launch_gemm_merge makes one chunk of them first: stat [Hq*w] (max, sum).
 bool gemm_votes_pools(int pool_kernel);
-hipError_t launch_gemm_votes(const float *logits, const float *part, int Hkv, int Hq, int N, int w, int pool_kernel,
-                             int pool_mode, float *scores, hipStream_t st);
+bool gemm_merges_first(int Hkv, int rows, int N);
+hipError_t launch_gemm_merge(const float *part, int Hkv, int Hq, int N, int w, float *stat, hipStream_t st);
+hipError_t launch_gemm_votes(const float *logits, const float *part, int chunks, int Hkv, int Hq, int N, int w,
+                             int pool_kernel, int pool_mode, float *scores, hipStream_t st);
 hipError_t launch_merge_part(const float *part, int Hkv, int Hq, int N, int w, float *row_max, float *row_sum,
                              hipStream_t st);
 // Same contract as launch_generic_cosine.
@@ -102,13 +105,14 @@ struct MfmaScorePlan {
     int chunks;        // key chunks per head in the streaming passes
     size_t part_bytes; // bytes of per-chunk row statistics
 };
-MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N);
+int mfma_score_rows(int G, int w, int per_qhead_votes);   // stacked query rows, filled up to what the kernels take
+MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N);    // rows: mfma_score_rows()
 // Pass A: per (head, chunk, row) partial max and sum of exp2 over the chunk's visible keys.
 // Pass B: votes [Hkv * rows, P] with rows = mfma_score_vote_rows(): partial sums over
 // groups of query rows (to be added up), or one row per query head.
 int mfma_score_vote_rows(int G, int w, int per_qhead_votes);
 hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
-                                  float scale, float *part, hipStream_t st);
+                                  float scale, int per_qhead_votes, float *part, hipStream_t st);
 // fused_pool_kernel > 0 (only if mfma_score_fuses_pool()): average pooling with that kernel
 // size and the mean over the query heads are done in the same kernel; `votes` is then the
 // score array [Hkv, P] and no pooling kernel follows.

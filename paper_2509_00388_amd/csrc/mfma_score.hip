@@ -38,14 +38,17 @@ __device__ __forceinline__ void merge_stats(float &m1, float &z1, float m2, floa
     m1 = mn;
 }
 
+// Rows first .. first + 32 NB - 1 of a head's R_real query rows (the last block is filled up with the last
+// row: its statistics go nowhere and its votes are zero, see bias_s).
 template <int NB>
-__device__ __forceinline__ void load_queries(const uint16_t *Qb, int l32, int hh, bf16x8 (&q)[NB][kSteps])
+__device__ __forceinline__ void load_queries(const uint16_t *Qh, int first, int R_real, int l32, int hh,
+                                             bf16x8 (&q)[NB][kSteps])
 {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int s = 0; s < kSteps; ++s)
-            q[b][s] = load8(Qb + (long)(kBlk * b + l32) * kD + 16 * s + 8 * hh);
+            q[b][s] = load8(Qh + (long)min(first + kBlk * b + l32, R_real - 1) * kD + 16 * s + 8 * hh);
 }
 
 // The R query rows are split over SPLIT waves per key stream: a workgroup has 4
@@ -82,7 +85,7 @@ __device__ __forceinline__ void unit_of_workgroup(int nparts, int &h, int &chunk
 template <int NB, int SPLIT, int STREAMS = 4>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w,
-    int chunk_keys, float c, float *__restrict__ part, int R_total, int row_base, int nparts)
+    int chunk_keys, float c, float *__restrict__ part, int R_total, int R_real, int row_base, int nparts)
 {
     constexpr int R = NB * kBlk, NBW = NB / SPLIT, NT = 64 * STREAMS * SPLIT, TK = kBlk * STREAMS;
     extern __shared__ __align__(16) unsigned char kt[];   // two key tiles
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const int stream = wv % STREAMS, row0 = (wv / STREAMS) * NBW * kBlk;   // first query row of this wave
 
     bf16x8 q[NBW][kSteps];
-    load_queries<NBW>(Qw + ((long)h * R_total + row_base + row0) * kD, l32, hh, q);
+    load_queries<NBW>(Qw + (long)h * R_real * kD, row_base + row0, R_real, l32, hh, q);
     int last_vis[NBW];   // last key the lane's query of block b may see (causal window)
     float m[NBW], z[NBW];
 #pragma unroll
@@ -242,7 +245,7 @@ template <int NB, int SPLIT, bool PERQ, int STREAMS = 4>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w, int G,
     int chunk_keys, float c, const float *__restrict__ part, int part_chunks,
-    float *__restrict__ votes, int R_total, int row_base, int vote_rows, int vote_row_base, int nparts,
+    float *__restrict__ votes, int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int nparts,
     int pool_half)
 {
     constexpr int R = NB * kBlk, NBW = NB / SPLIT, NT = 64 * STREAMS * SPLIT, TK = kBlk * STREAMS;
@@ -292,13 +295,14 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
             zz = stat_s[0][tid].y;
 #pragma unroll
             for (int u = 1; u < PARTS; ++u) merge_stats(mm, zz, stat_s[u][tid].x, stat_s[u][tid].y);
-            bias_s[tid] = mm + __log2f(zz);   // zz >= 1: the row maximum itself contributes exp2(0)
+            // zz >= 1: the row maximum itself contributes exp2(0); rows that only fill a block vote zero
+            bias_s[tid] = row_base + tid < R_real ? mm + __log2f(zz) : INFINITY;
         }
     }
     __syncthreads();
 
     bf16x8 q[NBW][kSteps];
-    load_queries<NBW>(Qw + ((long)h * R_total + row_base + row0) * kD, l32, hh, q);
+    load_queries<NBW>(Qw + (long)h * R_real * kD, row_base + row0, R_real, l32, hh, q);
     float bias[NBW][16];
 #pragma unroll
     for (int b = 0; b < NBW; ++b)
@@ -432,6 +436,15 @@ int stats_chunk_keys(int Hkv, int N)
 
 }  // namespace
 
+// Query rows of a head as the kernels take them: whole blocks of 32, and 256 rather than two parts when
+// there are more than 128 and the votes may mix query heads (one pass over the keys at 256 rows costs less
+// than two at 128 and the rest: 32 layers of 4 heads x 224 rows x 16384 keys, the whole pass 752 -> 549 us).
+int mfma_score_rows(int G, int w, int per_qhead_votes)
+{
+    const int R = (G * w + kBlk - 1) / kBlk * kBlk;
+    return R > 128 && !per_qhead_votes ? 256 : R;
+}
+
 MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N)
 {
     MfmaScorePlan pl;
@@ -461,16 +474,16 @@ int part_split(int rows, int w, int per_qhead_votes)
 int mfma_score_vote_rows(int G, int w, int per_qhead_votes)
 {
     if (per_qhead_votes) return G;
-    const int R = G * w;
+    const int R = mfma_score_rows(G, w, per_qhead_votes);
     int rows = 0;
     for (int part = 0; 128 * part < R; ++part) rows += part_split(part_rows(R, part), w, 0);
     return rows;
 }
 
 hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
-                                  float scale, float *part, hipStream_t st)
+                                  float scale, int per_qhead_votes, float *part, hipStream_t st)
 {
-    const int G = Hq / Hkv, R = G * w, P = N - w;
+    const int G = Hq / Hkv, R_real = G * w, R = mfma_score_rows(G, w, per_qhead_votes), P = N - w;
     const MfmaScorePlan plan = mfma_score_plan(Hkv, R, N);
     const int ck = stats_chunk_keys(Hkv, N);
     const float c = scale * 1.4426950408889634f;
@@ -478,7 +491,7 @@ hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int 
     if (R == 256) {   // one workgroup takes all 256 rows: 2 key streams x 4 row groups, tiles of 64 keys
         if (!allow_big_lds((const void *)score_stats_kernel<8, 4, 2>)) return hipGetLastError();
         hipLaunchKernelGGL((score_stats_kernel<8, 4, 2>), dim3(plan.chunks, Hkv), dim3(512), 2 * 64 * kPitch, st, K, Q, N,
-                           P, w, ck, c, part, R, 0, 1);
+                           P, w, ck, c, part, R, R_real, 0, 1);
         return hipGetLastError();
     }
     // other row counts beyond 128: parts of at most 128 rows, one launch per part
@@ -488,7 +501,7 @@ hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int 
     do {                                                                                           \
         if (!allow_big_lds((const void *)score_stats_kernel<NB, SP>)) return hipGetLastError();    \
         hipLaunchKernelGGL((score_stats_kernel<NB, SP>), grid, dim3(256 * SP), 2 * kTileBytes, st, \
-                           K, Q, N, P, w, ck, c, part, R, row_base, merged);                       \
+                           K, Q, N, P, w, ck, c, part, R, R_real, row_base, merged);               \
     } while (0)
     for (int pt = 0; 128 * pt < R; pt += merged) {
         const int row_base = 128 * pt;
@@ -508,7 +521,7 @@ hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int 
 template <int NB, int SPLIT, int STREAMS = 4>
 static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int N, int P, int w, int G,
                             int ck, float c, const float *part, int chunks, int per_q, float *votes,
-                            int R_total, int row_base, int vote_rows, int vote_row_base, int nparts,
+                            int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int nparts,
                             int pool_half, hipStream_t st)
 {
     const size_t lds = 2 * (kBlk * STREAMS) * kPitch + (pool_half >= 0 ? (size_t)SPLIT * (ck + 2 * pool_half) * 4 : 0);
@@ -516,25 +529,26 @@ static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int
         if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, true, STREAMS>)) return;
         hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, true, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
                            lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           row_base, vote_rows, vote_row_base, nparts, pool_half);
+                           R_real, row_base, vote_rows, vote_row_base, nparts, pool_half);
     } else {
         if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, false, STREAMS>)) return;
         hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, false, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
                            lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           row_base, vote_rows, vote_row_base, nparts, pool_half);
+                           R_real, row_base, vote_rows, vote_row_base, nparts, pool_half);
     }
 }
 
 bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel)
 {
-    return !per_qhead_votes && (G * w <= 128 || G * w == 256) && pool_kernel <= 33;
+    const int R = mfma_score_rows(G, w, per_qhead_votes);
+    return !per_qhead_votes && (R <= 128 || R == 256) && pool_kernel <= 33;
 }
 
 hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, int fused_pool_kernel,
                                   const float *part, float *votes, hipStream_t st)
 {
-    const int G = Hq / Hkv, R = G * w, P = N - w;
+    const int G = Hq / Hkv, R_real = G * w, R = mfma_score_rows(G, w, per_qhead_votes), P = N - w;
     const MfmaScorePlan plan = mfma_score_plan(Hkv, R, N);
     // fused pooling: a workgroup also multiplies pool_half keys on either side of its chunk; the
     // P prefix keys are spread evenly over the chunks
@@ -548,13 +562,13 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
     const int vote_rows = mfma_score_vote_rows(G, w, per_qhead_votes);
     int vote_row_base = 0;
     if (R == 256 && !per_qhead_votes) {   // all rows in one workgroup (see the statistics pass): four row groups
-        launch_votes_nb<8, 4, 2>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, 0, votes, R, 0, vote_rows, 0, 1,
+        launch_votes_nb<8, 4, 2>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, 0, votes, R, R_real, 0, vote_rows, 0, 1,
                                  pool_half, st);
         return hipGetLastError();
     }
 #define GKV_VOTES(NB, SP)                                                                             \
     launch_votes_nb<NB, SP>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, per_qhead_votes, votes, R, \
-                            row_base, vote_rows, vote_row_base, merged, pool_half, st)
+                            R_real, row_base, vote_rows, vote_row_base, merged, pool_half, st)
     for (int pt = 0; 128 * pt < R; pt += merged) {
         const int row_base = 128 * pt, rows = part_rows(R, pt);
         const int split = part_split(rows, w, per_qhead_votes);

@@ -1185,3 +1185,19 @@ def test_edge_rows_small_m(oracle, P, m):
         row[nbr_f[0, 0, a]] = ev_f[0, 0, a]
         want, _ = oracle.topk(row, m)
         assert np.array_equal(nbr[0, 0, a], want) and np.array_equal(ev[0, 0, a], row[want].astype(np.float32))
+
+
+@pytest.mark.parametrize("pool_kernel", [7, 35])
+@pytest.mark.parametrize("G,w", [(1, 1), (1, 16), (3, 11), (7, 16), (5, 25), (4, 33), (5, 32), (7, 32), (1, 250), (1, 128)])
+def test_score_bf16_rows_that_do_not_fill_the_blocks(oracle, G, w, pool_kernel):
+    """Stacked query rows G*w that leave the last 32-row block partly empty, or lie between 128 and 256
+    (filled up to 256): the filling must not vote.  The wide pooling window takes the separate pooling
+    kernel, with up to four vote rows per head."""
+    cfg = small_bf16_cfg(n_tokens=1300 + w, window=w, n_kv_heads=2, n_q_heads=2 * G, budget=w + 50,
+                         pool_kernel=pool_kernel)
+    say(f"score partly filled blocks G={G} w={w} pool={pool_kernel}")
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 9)
+    p = util.params_from_cfg(cfg)
+    assert gk.graphkv_uses_mfma(p)
+    s = gk.graphkv_score(p, Kd, Qd).cpu().numpy()
+    util.assert_scores_close(s, oracle.score(K, Q, "bf16", pool_kernel, 0))
