@@ -319,10 +319,12 @@ bool propagation_is_noop(const graphkv_params *p)
 }
 
 // Ac: tensor of the sources' rows, Kc: tensor of the other nodes' rows (Eq. 1: both the keys).
+// last: if given, the last round's update may be left to the caller's next kernel over the scores.
 int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W, const void *Ac,
                       const void *Kc, float *scores, int32_t *dbg_src, int32_t *dbg_nbr, float *dbg_e, void *ws,
-                      hipStream_t st)
+                      hipStream_t st, DecayArgs *last = nullptr)
 {
+    if (last) *last = DecayArgs{};
     if (propagation_is_noop(p)) return GRAPHKV_OK;
     const size_t n_src = (size_t)D.H * D.S, n_nbr = n_src * D.m;
     float *E = at<float>(ws, W.E);
@@ -337,6 +339,10 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
     const MfmaFilterPlan &g = D.fp;
     const int32_t *prev_src = nullptr, *prev_nbr = nullptr;
     const float *prev_e = nullptr;
+    // A round's update rides along with the next kernel that has a workgroup per head, where there is one:
+    // the selection of the next round's sources, the caller's final selection.
+    const int items = decay_rides_along(D.P, D.S, D.m);
+    DecayArgs update{};
     for (int t = 0; t < D.T; ++t) {
         int32_t *src = src0, *nbr = nbr0;
         float *ev = e0;
@@ -387,7 +393,8 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                                           at<int32_t>(ws, W.spec_bad), new_src, n_new, at<int32_t>(ws, W.sel_row),
                                           at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel)};
                     if (pick_match_applies(D.S)) {
-                        GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER, launch_pick_match(scores, D.P, D.H, match, src, st));
+                        GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER, launch_pick_match(scores, D.P, D.H, match, src, update, st));
+                        update = DecayArgs{};
                     } else {
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER,
                                    launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
@@ -432,11 +439,15 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
             if (dbg_e) GKV_LAUNCH(GRAPHKV_K_COPY, launch_copy_f32(e0, dbg_e + t * n_nbr, (long)n_nbr, st));
         }
         // Eq. 5: one round of the signal
-        GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
+        const bool next_takes_it = t + 1 < D.T ? D.filter && keep && pick_match_applies(D.S) : last != nullptr;
+        update = DecayArgs{nbr, ev, next_takes_it ? items : 0, items ? D.S * D.m : 0, p->decay, p->signal};
+        if (!update.items)
+            GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
         prev_src = src;
         prev_nbr = nbr;
         prev_e = ev;
     }
+    if (last && update.items) *last = update;
     return GRAPHKV_OK;
 }
 
@@ -458,10 +469,10 @@ LayerPlan make_plan(const graphkv_params *p, int n_layers, const int32_t *budget
     return plan;
 }
 
-int32_t run_select(const Dims &D, const LayerPlan &plan, const float *scores, int32_t *idx,
+int32_t run_select(const Dims &D, const LayerPlan &plan, float *scores, int32_t *idx, const DecayArgs &update,
                    hipStream_t st)
 {
-    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, st));
+    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, update, st));
     return GRAPHKV_OK;
 }
 
@@ -481,9 +492,10 @@ int32_t run_compress(const graphkv_params *p, int n_layers, const Dims &group, c
         return rc;
     const void *edge_src = p->edges == GRAPHKV_EDGES_VV ? Vc : Kc;
     const void *edge_nbr = p->edges == GRAPHKV_EDGES_KK ? Kc : Vc;
-    if (int32_t rc = run_propagate(p, D, W, edge_src, edge_nbr, scores, nullptr, nullptr, nullptr, ws, st))
+    DecayArgs update;
+    if (int32_t rc = run_propagate(p, D, W, edge_src, edge_nbr, scores, nullptr, nullptr, nullptr, ws, st, &update))
         return rc;
-    if (int32_t rc = run_select(D, plan, scores, idx, st)) return rc;
+    if (int32_t rc = run_select(D, plan, scores, idx, update, st)) return rc;
     GKV_LAUNCH(GRAPHKV_K_GATHER, launch_gather(Kc, Vc, idx, D.H, D.N, plan, max_budget,
                                                (int)(D.d * D.esize), Kout, Vout, st));
     return GRAPHKV_OK;
@@ -604,7 +616,9 @@ int32_t graphkv_select(const graphkv_params *p, const float *scores, int32_t *id
     if (!base_ok(p) || !budget_ok(p)) return GRAPHKV_EINVAL;
     if (!aligned4(scores) || !aligned4(idx)) return GRAPHKV_EINVAL;
     const Dims D = dims_of(p);
-    return run_select(D, make_plan(p, 1, nullptr, nullptr), scores, idx, (hipStream_t)stream);
+    // (no update rides along: the scores are only read)
+    return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{},
+                      (hipStream_t)stream);
 }
 
 int32_t graphkv_compress(const graphkv_params *p, const void *Kc, const void *Vc, const void *Qw,

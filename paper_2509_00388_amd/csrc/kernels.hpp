@@ -88,6 +88,16 @@ hipError_t launch_pool_group(const float *votes, int Hkv, int Gv, int P, int poo
 // Eq. 5 for one round: scores[h, nbr] *= prod (1 -/+ alpha e), ascending source order.
 hipError_t launch_decay(float *scores, int Hkv, int P, int S, int m, const int32_t *nbr,
                         const float *nbr_e, float alpha, int signal, hipStream_t st);
+// An update that the next kernel with a workgroup per head does first (decay.hpp): items = triples per
+// thread as decay_rides_along() says, 0: none.
+struct DecayArgs {
+    const int32_t *nbr;
+    const float *nbr_e;
+    int items, count;
+    float alpha;
+    int signal;
+};
+int decay_rides_along(int P, int S, int m);
 // Kout[q,t,:] = Kc[q, idx[q,t], :] for the heads q of a batch, same for V; packed
 // outputs, per-layer budgets from the plan; row_bytes multiple of 16.
 hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int heads, int N,
@@ -95,8 +105,9 @@ hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int
                          hipStream_t st);
 // Final selection of a batch: row q keeps budget[l] - w entries and writes them,
 // followed by the window tokens P .. P + w - 1, to its packed idx row.
-hipError_t launch_topk_final(const float *scores, int P, int rows, const LayerPlan &plan, int w,
-                             int32_t *idx, hipStream_t st);
+// (An update that rides along changes the scores first.)
+hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
+                             const DecayArgs &update, hipStream_t st);
 hipError_t launch_copy_i32(const int32_t *src, int32_t *dst, long n, hipStream_t st);
 hipError_t launch_copy_f32(const float *src, float *dst, long n, hipStream_t st);
 
@@ -181,7 +192,8 @@ struct MatchArgs {
 };
 // Source nodes (Eq. 2) of a later round and their match, one launch for S <= 256 (pick_match_applies).
 bool pick_match_applies(int S);
-hipError_t launch_pick_match(const float *x, int n, int rows, const MatchArgs &a, int32_t *src, hipStream_t st);
+hipError_t launch_pick_match(float *x, int n, int rows, const MatchArgs &a, int32_t *src, const DecayArgs &update,
+                             hipStream_t st);
 hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv, hipStream_t st);
 // Exact top-m over candidate rows -> nbr / nbr_e [Hkv, S, m]; skips heads with overflow[h], and
 // raises overflow[h] itself if a row has more candidates than it can take.  rows == nullptr:

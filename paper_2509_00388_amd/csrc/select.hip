@@ -13,6 +13,7 @@
 // Rows of up to 32768 entries are read once, coalesced, and kept in LDS for all
 // sweeps; longer rows are re-read from L2 in every sweep.
 #include "common.hpp"
+#include "decay.hpp"
 #include "kernels.hpp"
 #include "match.hpp"
 #include "mfma_tile.hpp"
@@ -604,19 +605,35 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
     else pick_row_long(xr, n, k, o, L, tid, lane, wv);
 }
 
-// A later round's sources and, in the same workgroup, where their lists come from (a launch of its own
-// for the match cost 6.1 us with 8 heads; a launch is 4.6 us before it does anything).
-template <int ITEMS>
-__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(const float *__restrict__ x, int n, MatchArgs a,
-                                                                int32_t *__restrict__ src_out)
+// The update of the round before, for the kernels below that read a head's scores next: D triples per
+// thread, 0 for none.
+template <int D>
+__device__ __forceinline__ void update_first(float *xr, int h, const DecayArgs &u, unsigned char *lds, int tid)
 {
+    if constexpr (D > 0) {
+        decay_chain<uint32_t, 1024, D, true>(xr, u.count, 2048 * D, u.nbr + (long)h * u.count,
+                                             u.nbr_e + (long)h * u.count, u.alpha, u.signal, lds, tid);
+        __syncthreads();   // the row is up to date
+    }
+}
+size_t update_lds(int items) { return items ? decay_chain_lds<uint32_t>(2048 * items, 1024 * items, true) : 0; }
+
+// A later round's sources and, in the same workgroup, the update of the round before and where the
+// sources' lists come from (launches of their own cost 7.7 and 6.1 us with 8 heads; a launch is 4.6 us
+// before it does anything: 18.9 us together, update included, against 24).
+template <int ITEMS, int D>
+__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, MatchArgs a,
+                                                                int32_t *__restrict__ src_out, DecayArgs update)
+{
+    extern __shared__ __align__(16) unsigned char update_mem[];
     static_assert(kPickBlock == kMatchBlock, "one workgroup does both");
     __shared__ PickLds<kPickBlock> L;
     __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
     const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const float *xr = x + (long)h * n;
+    float *xr = x + (long)h * n;
     int32_t *src = src_out + (long)h * a.S;
     const PickOut o{a.S, src, nullptr, nullptr};
+    update_first<D>(xr, h, update, update_mem, tid);
     const bool bad = match_load(a, h, match_lds, tid);
     if constexpr (ITEMS > 0) pick_row<kPickBlock, ITEMS, false>(xr, n, a.S, o, L, tid, lane, wv);
     else pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
@@ -693,10 +710,11 @@ __device__ __forceinline__ void emit_bitmap(const uint64_t *map, int words, uint
     }
 }
 
-template <int ITEMS>
+template <int ITEMS, int D>
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
-    const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, LayerPlan plan)
+    float *x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update, LayerPlan plan)
 {
+    extern __shared__ __align__(16) unsigned char update_mem[];
     constexpr int NW = kBudgetBlock / kWave, CELLS = ITEMS * NW;
     __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
     __shared__ __align__(16) uint32_t list[kPairs];
@@ -706,7 +724,8 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
     const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
     const int k = plan.budget[g] - append_count;
     int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
-    const float *xr = x + (long)row * n;
+    float *xr = x + (long)row * n;
+    update_first<D>(xr, row, update, update_mem, tid);   // (the last round's, in a whole pass)
 
     // the loads of the row leave together (unconditional, clamped, pinned before the first use)
     float val[ITEMS];
@@ -1032,18 +1051,37 @@ static hipError_t launch_pick(const float *x, long ld, int n, int rows, int k, i
 
 bool pick_match_applies(int S) { return S <= kSmallK; }
 
-hipError_t launch_pick_match(const float *x, int n, int rows, const MatchArgs &a, int32_t *src, hipStream_t st)
+template <int D>
+static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs &a, int32_t *src,
+                                      const DecayArgs &update, hipStream_t st)
 {
-    if (a.S > kSmallK || a.X > kMaxExtSources) return hipErrorInvalidValue;
-#define GKV_PICK(ITEMS) \
-    hipLaunchKernelGGL(pick_match_kernel<ITEMS>, dim3(rows), dim3(kPickBlock), 0, st, x, n, a, src)
+#define GKV_PICK(ITEMS)                                                                                          \
+    do {                                                                                                         \
+        if (!allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError();     \
+        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), update_lds(D), st, x, n, a, \
+                           src, update);                                                                         \
+    } while (0)
     if (n <= 4096) GKV_PICK(4);   // (lists are kept on the filter route only: 2048 nodes or more)
     else if (n <= 8192) GKV_PICK(8);
     else if (n <= 16384) GKV_PICK(16);
     else if (n <= 32768) GKV_PICK(32);
-    else GKV_PICK(0);
+    else if constexpr (D == 0) GKV_PICK(0);
+    else return hipErrorInvalidValue;
 #undef GKV_PICK
     return hipGetLastError();
+}
+
+hipError_t launch_pick_match(float *x, int n, int rows, const MatchArgs &a, int32_t *src, const DecayArgs &update,
+                             hipStream_t st)
+{
+    if (a.S > kSmallK || a.X > kMaxExtSources) return hipErrorInvalidValue;
+    switch (update.items) {
+        case 0: return launch_pick_match_d<0>(x, n, rows, a, src, update, st);
+        case 1: return launch_pick_match_d<1>(x, n, rows, a, src, update, st);
+        case 2: return launch_pick_match_d<2>(x, n, rows, a, src, update, st);
+        case 4: return launch_pick_match_d<4>(x, n, rows, a, src, update, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
@@ -1119,19 +1157,41 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
 // Row length up to which the budgeted selection keeps a bitmap of the row in LDS.
 constexpr int kBitmapRow = 1 << 18;
 
-hipError_t launch_topk_final(const float *scores, int P, int rows, const LayerPlan &plan, int w,
-                             int32_t *idx, hipStream_t st)
+template <int D>
+static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
+                                  const DecayArgs &update, hipStream_t st)
 {
-    if (rows <= 0) return hipSuccess;
-#define GKV_BUDGET(ITEMS) \
-    hipLaunchKernelGGL(budget_select_kernel<ITEMS>, dim3(rows), dim3(kBudgetBlock), 0, st, scores, P, idx, P, w, plan)
+#define GKV_BUDGET(ITEMS)                                                                                       \
+    do {                                                                                                        \
+        if (!allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
+        hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), update_lds(D), st, \
+                           scores, P, idx, P, w, update, plan);                                                 \
+    } while (0)
     if (P <= 1024) GKV_BUDGET(1);
     else if (P <= 2048) GKV_BUDGET(2);
     else if (P <= 4096) GKV_BUDGET(4);
     else if (P <= 8192) GKV_BUDGET(8);
     else if (P <= 16384) GKV_BUDGET(16);
-    else if (P <= 32768) GKV_BUDGET(32);
-    else if (P <= kBitmapRow) {
+    else GKV_BUDGET(32);
+#undef GKV_BUDGET
+    return hipGetLastError();
+}
+
+hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
+                             const DecayArgs &update, hipStream_t st)
+{
+    if (rows <= 0) return hipSuccess;
+    if (P <= 32768) {
+        switch (update.items) {
+            case 0: return launch_budget_d<0>(scores, P, rows, plan, w, idx, update, st);
+            case 1: return launch_budget_d<1>(scores, P, rows, plan, w, idx, update, st);
+            case 2: return launch_budget_d<2>(scores, P, rows, plan, w, idx, update, st);
+            case 4: return launch_budget_d<4>(scores, P, rows, plan, w, idx, update, st);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (update.items) return hipErrorInvalidValue;
+    if (P <= kBitmapRow) {
         if (!allow_big_lds((const void *)budget_select_long_kernel, 140 * 1024)) return hipGetLastError();
         const size_t words = (size_t)(P + kWave - 1) / kWave;
         hipLaunchKernelGGL(budget_select_long_kernel, dim3(rows), dim3(kBudgetBlock),
@@ -1141,7 +1201,6 @@ hipError_t launch_topk_final(const float *scores, int P, int rows, const LayerPl
                            rows, 0, idx, 0L, (float *)nullptr, 0L, (float *)nullptr, P, w, (const int32_t *)nullptr, 1,
                            plan);
     }
-#undef GKV_BUDGET
     return hipGetLastError();
 }
 
