@@ -236,8 +236,8 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
 // rows (row_base .. row_base + R of R_total), one launch per part: the keys are then
 // streamed once per part.
 //
-// pool_half >= 0 (average pooling, all rows of a head in one workgroup): the votes never leave the workgroup.  Each row
-// group keeps the votes of the workgroup's keys in LDS, the workgroup also multiplies the
+// pool_half >= 0 (all rows of a head in one workgroup): the votes never leave the workgroup.  Each row
+// group (max pooling: each query head) keeps the votes of the workgroup's keys in LDS, the workgroup also multiplies the
 // pool_half keys on either side of its chunk, and at the end it writes the pooled, grouped
 // scores of its chunk itself: votes[] is then the score array [Hkv, P].  The sums are
 // formed in the order of the separate pooling kernel, so the bits are the same.
@@ -260,13 +260,14 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
 
     const int k0 = chunk * chunk_keys, k1 = min(P, k0 + chunk_keys);
     if (k0 >= P) return;
-    const bool fused = !PERQ && pool_half >= 0;
+    const bool fused = pool_half >= 0;
     const int first = fused ? max(0, k0 - pool_half) : k0;      // keys this workgroup multiplies
     const int kend = fused ? min(P, k1 + pool_half) : k1;
     const int span = chunk_keys + 2 * pool_half;
-    float *vs = reinterpret_cast<float *>(kt + 2 * TK * kPitch);   // [SPLIT][span], slot 0 = key k0 - pool_half
-    if (fused)
-        for (int u = tid; u < SPLIT * span; u += NT) vs[u] = 0.f;   // zero padding outside the row
+    // [row groups, or query heads][span], slot 0 = key k0 - pool_half
+    float *vs = reinterpret_cast<float *>(kt + 2 * TK * kPitch);
+    if (fused)   // outside the row: zeros (average), nothing (max)
+        for (int u = tid; u < (PERQ ? G : SPLIT) * span; u += NT) vs[u] = PERQ ? -INFINITY : 0.f;
 
     {   // Row statistics of the whole head: merge the chunks of pass A, PARTS threads per row, each a run
         // of chunks whose loads leave eight at a time.  (One thread per row and one load after the
@@ -354,14 +355,28 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
 #pragma unroll
                 for (int b = 0; b < NBW; ++b) p += (b / bpq == g) ? pb[b] : 0.f;
                 p = add_other_half(p);
-                if (g0 + g < G && g * bpq < NBW && hh == 0 && key < kend)
-                    votes[((long)h * G + g0 + g) * P + key] = p;
+                if (g0 + g < G && g * bpq < NBW && hh == 0 && key < kend) {
+                    if (fused) vs[(g0 + g) * span + key - (k0 - pool_half)] = p;
+                    else votes[((long)h * G + g0 + g) * P + key] = p;
+                }
             }
         }
     };
     GKV_TILE_PIPELINE_TK(TK, NT, Kh, first, kend - 1, 1, ntile, multiply_tile, (void)0);
     if (fused) {
         __syncthreads();
+        if constexpr (PERQ) {   // max pooling: per query head, then the sum over the heads
+            for (int o = tid; o < k1 - k0; o += NT) {
+                float total = 0.f;
+                for (int g = 0; g < G; ++g) {
+                    float best = -INFINITY;
+                    for (int t = 0; t <= 2 * pool_half; ++t) best = fmaxf(best, vs[g * span + o + t]);
+                    total += best;
+                }
+                votes[(long)h * P + k0 + o] = total / (float)G;
+            }
+            return;
+        }
         // votes of a key summed over the row groups (in group order, into group 0's array), then the
         // taps of every output in key order: the additions of the separate pooling kernel
         if (SPLIT > 1) {
@@ -396,14 +411,14 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
 // of the statistics -- about as long as 256 keys take.  So the cut with the fewest keys per compute unit
 // wins, counting whole rounds of 256 workgroups: for few heads as many chunks as one round takes, for
 // many as few as keep the rounds full.  At most `most` keys: the votes of a chunk sit in LDS beside the
-// key tiles, two or four row groups of them; at least two tiles, as the pooling window's halo is read
+// key tiles, one row per row group (two, or four at 256 query rows) or query head; at least two tiles, as the pooling window's halo is read
 // twice.  (1024 workgroups of at least 1024 keys before, chunks of 6144 with 256 query rows; us, before /
 // now: 8 heads of 4096 keys 18.0 / 13.6, of 16384 21.0 / 16.3, of 65536 51 / 31; 128 heads of 8192 76 / 51;
 // 8 heads of 32768 keys with 256 query rows 103 / 28.)
 constexpr int kComputeUnits = 256;
-int votes_chunk_keys(int Hkv, int N, int rows)
+int votes_chunk_keys(int Hkv, int N, int rows, int lds_rows)
 {
-    const int least = 256, most = rows == 256 ? 6144 : 8192;
+    const int least = 256, most = rows == 256 ? 6144 : (lds_rows <= 2 ? 8192 : 16384 / lds_rows / 128 * 128);
     const int cmin = (N + most - 1) / most, cmax = (N + least - 1) / least > cmin ? (N + least - 1) / least : cmin;
     long best = -1;
     int keys = 0;
@@ -524,7 +539,7 @@ static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int
                             int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int nparts,
                             int pool_half, hipStream_t st)
 {
-    const size_t lds = 2 * (kBlk * STREAMS) * kPitch + (pool_half >= 0 ? (size_t)SPLIT * (ck + 2 * pool_half) * 4 : 0);
+    const size_t lds = 2 * (kBlk * STREAMS) * kPitch + (pool_half >= 0 ? (size_t)(per_q ? G : SPLIT) * (ck + 2 * pool_half) * 4 : 0);
     if (per_q) {
         if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, true, STREAMS>)) return;
         hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, true, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
@@ -541,7 +556,7 @@ static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int
 bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel)
 {
     const int R = mfma_score_rows(G, w, per_qhead_votes);
-    return !per_qhead_votes && (R <= 128 || R == 256) && pool_kernel <= 33;
+    return (R <= 128 || (R == 256 && !per_qhead_votes)) && pool_kernel <= 33;
 }
 
 hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
@@ -553,7 +568,7 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
     // fused pooling: a workgroup also multiplies pool_half keys on either side of its chunk; the
     // P prefix keys are spread evenly over the chunks
     const int pool_half = fused_pool_kernel > 0 ? (fused_pool_kernel - 1) / 2 : -1;
-    const int vck = votes_chunk_keys(Hkv, N, R), vchunks = (N + vck - 1) / vck;
+    const int vck = votes_chunk_keys(Hkv, N, R, pool_half >= 0 && per_qhead_votes ? G : 2), vchunks = (N + vck - 1) / vck;
     const int ck = pool_half >= 0 ? (P + vchunks - 1) / vchunks : vck;
     const float c = scale * 1.4426950408889634f;
     const uint16_t *K = (const uint16_t *)Kc, *Q = (const uint16_t *)Qw;
