@@ -373,36 +373,41 @@ __global__ __launch_bounds__(BLOCK) void topk_rows_stream_kernel(
 }
 
 // A row in batches of U loads per thread of a 1024-thread workgroup, the next batch on its way
-// while one is used; use(number of the 64 entries, value, in the row) is called by whole waves.
-// Only the last batches hold entries past the end.
+// while one is used; use(number of the 64 entries, value, in the row) is called by whole waves.  The
+// batches that fill the workgroup are loaded without a condition (past the last one, the last again):
+// behind a conditional load the compiler waits for everything in flight.  The few turns behind them hold
+// the row's end.
 template <int U, typename Use>
 __device__ __forceinline__ void row_sweep(const float *__restrict__ xr, int n, int tid, int wv, Use &&use)
 {
     constexpr int BLOCK = 1024, NW = BLOCK / kWave;
     const int turns = (n + BLOCK - 1) / BLOCK, whole = n / BLOCK / U * U;
-    float a[U], b[U];
-    auto load = [&](float (&v)[U], int i0) {
+    float tail[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            v[u] = i0 < whole ? (xr + (i0 + u) * BLOCK)[tid] : xr[min((i0 + u) * BLOCK + tid, n - 1)];
-    };
-    auto work = [&](float (&v)[U], int i0) {
-        if (i0 < whole) {
+    for (int u = 0; u < U; ++u) tail[u] = xr[min((whole + u) * BLOCK + tid, n - 1)];
+    if (whole > 0) {
+        float a[U], b[U];
+        auto load = [&](float (&v)[U], int i0) {
+            const float *p = xr + (long)min(i0, whole - U) * BLOCK;
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = p[u * BLOCK + tid];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto work = [&](float (&v)[U], int i0) {
 #pragma unroll
             for (int u = 0; u < U; ++u) use((i0 + u) * NW + wv, v[u], true);
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i0 + u < turns) use((i0 + u) * NW + wv, v[u], (i0 + u) * BLOCK + tid < n);
+        };
+        load(a, 0);
+        for (int i0 = 0; i0 < whole; i0 += 2 * U) {
+            load(b, i0 + U);
+            work(a, i0);
+            load(a, i0 + 2 * U);
+            if (i0 + U < whole) work(b, i0 + U);
         }
-    };
-    load(a, 0);
-    for (int i0 = 0; i0 < turns; i0 += 2 * U) {
-        load(b, i0 + U);
-        work(a, i0);
-        load(a, i0 + 2 * U);
-        work(b, i0 + U);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (whole + u < turns) use((whole + u) * NW + wv, tail[u], (whole + u) * BLOCK + tid < n);
 }
 
 // ---- few winners (source nodes) -------------------------------------------------------
@@ -570,16 +575,16 @@ __device__ __forceinline__ void pick_row(const float *xr, int n, int k, const Pi
     pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
 }
 
-// A longer row: read twice, in batches of 16 loads per thread.
+// A longer row: read twice, in batches of 12 loads per thread.
 __device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, const PickOut &o, PickLds<kPickBlock> &L,
                                               int tid, int lane, int wv)
 {
     L.clear(tid);
     float best = -INFINITY;     // (floats order as their keys do)
-    row_sweep<16>(xr, n, tid, wv, [&](int, float v, bool in) { best = fmaxf(best, in ? v : -INFINITY); });
+    row_sweep<12>(xr, n, tid, wv, [&](int, float v, bool in) { best = fmaxf(best, in ? v : -INFINITY); });
     // (the bound need not be the key of an entry; floats compare with it as their keys do)
     const float bound = key_to_float(kth_value_bound<kPickBlock>(ord_key(best), k, L, tid, lane, wv));
-    row_sweep<16>(xr, n, tid, wv, [&](int word, float v, bool in) {
+    row_sweep<12>(xr, n, tid, wv, [&](int word, float v, bool in) {
         if (in && v >= bound) {
             const uint32_t at = atomicAdd(&L.cnt, 1u);
             if (at < (uint32_t)kPickList)
@@ -830,7 +835,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
 // second, which compares the floats with the ends of the bin, about five.  A row with more than
 // kBudgetList entries in the bin of the cut (masses of equal values), or with more ties at the cut
 // than can be ranked pair by pair, goes through the general algorithm.  (Five reads with an LDS
-// histogram of 11, 11 and 10 bits: 110 us for 8 rows of 131008 entries; this way 48 us.)
+// histogram of 11, 11 and 10 bits: 110 us for 8 rows of 131008 entries; this way 33 us.)
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, LayerPlan plan)
 {

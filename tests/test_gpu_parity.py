@@ -1201,3 +1201,40 @@ def test_score_bf16_rows_that_do_not_fill_the_blocks(oracle, G, w, pool_kernel):
     assert gk.graphkv_uses_mfma(p)
     s = gk.graphkv_score(p, Kd, Qd).cpu().numpy()
     util.assert_scores_close(s, oracle.score(K, Q, "bf16", pool_kernel, 0))
+
+
+@pytest.mark.parametrize("G,w,pool_kernel", [(1, 32, 7), (2, 64, 13), (3, 32, 33), (4, 32, 7), (4, 32, 35), (1, 96, 1)])
+def test_score_max_pooling_over_several_key_chunks(oracle, G, w, pool_kernel):
+    """Max pooling inside the votes pass: one vote row per query head in LDS, pooling windows that straddle
+    chunk ends, windows wider than it takes (separate pooling kernel)."""
+    cfg = small_bf16_cfg(n_tokens=21011 + w, window=w, n_kv_heads=2, n_q_heads=2 * G, budget=w + 50,
+                         pool_kernel=pool_kernel)
+    say(f"max pooling over chunks G={G} w={w} pool={pool_kernel}")
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 5)
+    s = gk.graphkv_score(util.params_from_cfg(cfg, pool_mode=1), Kd, Qd).cpu().numpy()
+    util.assert_scores_close(s, oracle.score(K, Q, "bf16", pool_kernel, 1))
+
+
+@pytest.mark.parametrize("P,k", [(32769, 1), (40000, 39999), (70001, 300), (131008, 4032), (200000, 60000)])
+def test_budgeted_selection_long_rows_sampled_range(oracle, P, k):
+    """The key range of a long row comes from a sample: rows whose large values all lie outside the
+    sampled stretches, inside them, at one end, in equal masses, and rows of one repeated value."""
+    say(f"selection sampled range P={P} k={k}")
+    rng = np.random.default_rng(P ^ k)
+    w, H = 2, 6
+    words = (P + 63) // 64
+    sampled = np.zeros(P, dtype=bool)
+    for i in range(64):
+        j = i * (words - 1) // 64 * 64
+        sampled[j:j + 64] = True
+    s = np.abs(rng.standard_normal((H, P))).astype(np.float32) + np.float32(0.5)
+    s[0, sampled] = 1e-3                       # the sample sees only small values
+    s[1, ~sampled] = rng.random((~sampled).sum()).astype(np.float32) * 1e-3   # the sample sees all large ones
+    s[2] = np.linspace(1, 2, P, dtype=np.float32)[::-1]
+    s[3] = rng.integers(0, 2, P)
+    s[4] = 7.0
+    s[5] *= np.where(rng.random(P) < 0.5, -1, 1)
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=8, n_tokens=P + w, window=w, budget=k + w)
+    idx = gk.graphkv_select(p, torch.from_numpy(s).cuda()).cpu().numpy()
+    ref, _ = oracle.select(s.astype(np.float64), P + w, w, k + w)
+    assert np.array_equal(idx, ref)
