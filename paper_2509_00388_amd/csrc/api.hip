@@ -123,7 +123,10 @@ bool budget_ok(const graphkv_params *p)
 
 // `like`: the dimensions of the call's full launch group, whose routes a smaller last group takes
 // too (so that the workspace sized for the full group is enough).
-Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, const Dims *like = nullptr)
+// frugal: the routes with the least scratch (no filter route below 8192 nodes, the scalar kernels where
+// gemm.hip would keep row statistics beside the logits), for a buffer that the faster ones do not fit.
+Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, const Dims *like = nullptr,
+             bool frugal = false)
 {
     Dims D;
     D.L = n_layers;
@@ -138,10 +141,11 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, c
     D.S = p->rounds > 0 ? p->n_sources : 0;
     D.m = p->rounds > 0 ? p->n_neighbors : 0;
     D.T = p->rounds;
-    D.gemm = p->impl == GRAPHKV_IMPL_AUTO;
+    D.gemm = like ? like->gemm : p->impl == GRAPHKV_IMPL_AUTO && !frugal;
     D.mfma_score = mfma_score_ok(p);
     D.mfma_cosine = mfma_cosine_ok(p);
-    D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && mfma_filter_applies(D.P, D.m, (long)D.H * D.S);
+    D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && (!frugal || D.P >= 8192) &&
+                                         mfma_filter_applies(D.P, D.m, (long)D.H * D.S);
     if (like) speculate = like->speculate;
     // The neighbourhood of a source depends on the keys alone (Eq. 1, Eq. 3), not on the
     // scores: with re-picked sources the lists of returning sources are kept.
@@ -161,8 +165,12 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     const size_t rows = (size_t)D.Hq * D.w;
     const bool scoring = p->scorer == GRAPHKV_SCORER_ATTENTION && p->n_q_heads >= p->n_kv_heads &&
                          p->pool_kernel >= 1;
+    W.scores = take((size_t)D.H * D.P * 4);
+    // The scoring stage's scratch and the propagation's take the same place: one is done with before the
+    // other begins (same stream).
+    const size_t shared = off;
     W.logits = take(!D.mfma_score && scoring ? rows * D.N * 4 : 0);
-    W.row_max = take(rows * 8);   // (or the pairs of launch_gemm_merge)
+    W.row_max = take(rows * (D.gemm ? 8 : 4));   // (or the pairs of launch_gemm_merge)
     W.row_sum = take(rows * 4);
     // votes per query head (or row group); not needed when pass B pools and groups them itself
     const int per_q = p->pool_mode == GRAPHKV_POOL_MAX;
@@ -171,15 +179,16 @@ Workspace carve(const graphkv_params *p, const Dims &D)
         : D.gemm && gemm_votes_pools(p->pool_kernel));
     const int vote_rows = D.mfma_score ? mfma_score_vote_rows(D.G, D.w, per_q) : D.G;
     W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * vote_rows * D.P * 4 : 0);
+    W.part = take(D.mfma_score ? mfma_score_plan(D.H, mfma_score_rows(D.G, D.w, per_q), D.N).part_bytes
+                  : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
+    const size_t scoring_end = off;
+    off = shared;
     // the dense edge block [heads, S, P] of the routes that materialise it; on the filter route
     // only the scratch rows of the workgroups that redo overflowed heads
     W.E = take(D.filter ? redo_rows_scratch_bytes(D.H, D.S, D.P) : (size_t)D.H * D.S * D.P * 4);
     W.src = take((size_t)D.H * D.S * 4);
     W.nbr = take((size_t)D.H * D.S * D.m * 4);
     W.nbr_e = take((size_t)D.H * D.S * D.m * 4);
-    W.scores = take((size_t)D.H * D.P * 4);
-    W.part = take(D.mfma_score ? mfma_score_plan(D.H, mfma_score_rows(D.G, D.w, per_q), D.N).part_bytes
-                  : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
     const MfmaFilterPlan &g = D.fp;
     const size_t frows = D.filter ? (size_t)D.H * g.pitch : 0;   // rows of the per-row buffers
     W.tau = take(frows * 4);
@@ -198,6 +207,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.sel_pos = take(keep ? (size_t)D.H * D.S * 4 : 0);
     W.n_sel = take(keep ? (size_t)D.H * 4 : 0);
     W.spec_bad = take(keep ? (size_t)D.H * 4 : 0);
+    if (off < scoring_end) off = scoring_end;
     W.total = off;
     return W;
 }
@@ -509,7 +519,7 @@ constexpr size_t kGroupScratchCap = (size_t)2000 << 20;
 // beats a larger one without (later rounds then stream no keys again), as long as the group
 // still has 64 heads or more to fill the chip with; below that they are dropped before a
 // group is made smaller still.
-Dims group_dims(const graphkv_params *p, int n_layers)
+Dims group_dims(const graphkv_params *p, int n_layers, bool frugal = false)
 {
     const int g0 = n_layers < kMaxLayers ? n_layers : kMaxLayers;
     for (int speculate = 1; speculate >= 0; --speculate) {
@@ -517,13 +527,13 @@ Dims group_dims(const graphkv_params *p, int n_layers)
             const bool fits_heads = (long)p->n_kv_heads * g <= 65535;
             if (speculate && g < g0 && (long)p->n_kv_heads * g < 64) break;
             if (fits_heads) {
-                const Dims D = dims_of(p, g, speculate != 0);
+                const Dims D = dims_of(p, g, speculate != 0, nullptr, frugal);
                 if (carve(p, D).total <= kGroupScratchCap) return D;
             }
             if (g == 1) break;
         }
     }
-    return dims_of(p, 1, false);
+    return dims_of(p, 1, false, nullptr, frugal);
 }
 
 // Scratch of a call: its full group's, or its smaller last group's should that need more.
@@ -543,6 +553,40 @@ bool budgets_ok(const graphkv_params *p, int n_layers, const int32_t *budgets)
         if (B <= p->window || B > p->n_tokens) return false;
     }
     return true;
+}
+
+// The whole pass for n_layers layers in launch groups like DG (valid base parameters).
+int32_t compress_layers(const graphkv_params *p, int32_t n_layers, const Dims &DG, const int32_t *budgets,
+                        const void *Kc, const void *Vc, const void *Qw, void *Kout, void *Vout, int32_t *idx,
+                        float *scores_out, void *ws, size_t ws_bytes, void *stream)
+{
+    const bool knorm = p->scorer == GRAPHKV_SCORER_KNORM;   // reads no queries: Qw may be NULL
+    if (!knorm && !score_ok(p)) return GRAPHKV_EINVAL;
+    if (!budgets_ok(p, n_layers, budgets)) return GRAPHKV_EINVAL;
+    if (!aligned16(Kc) || !aligned16(Vc) || (!knorm && !aligned16(Qw)) || !aligned16(Kout) ||
+        !aligned16(Vout) || !aligned4(idx))
+        return GRAPHKV_EINVAL;
+    if (scores_out && !aligned4(scores_out)) return GRAPHKV_EINVAL;
+    const int group = DG.L;
+    if (int32_t rc = check_ws(scratch_bytes(p, n_layers, DG), ws, ws_bytes)) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    const size_t esize = p->dtype == GRAPHKV_FP32 ? 4 : 2;
+    const size_t kv_layer = (size_t)p->n_kv_heads * p->n_tokens * p->head_dim * esize;
+    const size_t q_layer = (size_t)p->n_q_heads * p->window * p->head_dim * esize;
+    const size_t s_layer = (size_t)p->n_kv_heads * (p->n_tokens - p->window);
+    size_t out_rows = 0;   // rows of Kout / Vout / idx written so far
+    for (int l0 = 0; l0 < n_layers; l0 += group) {
+        const int nl = n_layers - l0 < group ? n_layers - l0 : group;
+        const int32_t *bl = budgets ? budgets + l0 : nullptr;
+        const int32_t rc = run_compress(
+            p, nl, DG, bl, (const char *)Kc + l0 * kv_layer, (const char *)Vc + l0 * kv_layer,
+            Qw ? (const char *)Qw + l0 * q_layer : nullptr, (char *)Kout + out_rows * p->head_dim * esize,
+            (char *)Vout + out_rows * p->head_dim * esize, idx + out_rows,
+            scores_out ? scores_out + l0 * s_layer : nullptr, ws, st);
+        if (rc) return rc;
+        for (int l = 0; l < nl; ++l) out_rows += (size_t)p->n_kv_heads * (bl ? bl[l] : p->budget);
+    }
+    return GRAPHKV_OK;
 }
 
 }  // namespace
@@ -634,14 +678,19 @@ int32_t graphkv_compress_static(const graphkv_params *p, const void *Kc, const v
 {
     const size_t need = graphkv_workspace_bytes(p);   // 0: invalid params
     if (need == 0) return GRAPHKV_EINVAL;
-    if (need > kStaticScratchBytes) return GRAPHKV_ESCRATCH;
+    Dims D = group_dims(p, 1);
+    if (need > kStaticScratchBytes) {
+        // (a short prompt with many heads may still fit with its dense edge block, logits without
+        // the statistics of their chunks)
+        D = group_dims(p, 1, true);
+        if (scratch_bytes(p, 1, D) > kStaticScratchBytes) return GRAPHKV_ESCRATCH;
+    }
     // (the pointer checks of the call below come before the address is resolved)
     if (!aligned16(Kc) || !aligned16(Vc) || !aligned16(Kout) || !aligned16(Vout) || !aligned4(idx))
         return GRAPHKV_EINVAL;
     void *ws = static_scratch();
     if (!ws) return GRAPHKV_EHIP;
-    return graphkv_compress_batched(p, 1, nullptr, Kc, Vc, Qw, Kout, Vout, idx, scores_out, ws,
-                                    kStaticScratchBytes, stream);
+    return compress_layers(p, 1, D, nullptr, Kc, Vc, Qw, Kout, Vout, idx, scores_out, ws, kStaticScratchBytes, stream);
 }
 
 size_t graphkv_workspace_bytes_batched(const graphkv_params *p, int32_t n_layers)
@@ -656,34 +705,8 @@ int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, cons
                                  size_t ws_bytes, void *stream)
 {
     if (!base_ok(p) || n_layers < 1) return GRAPHKV_EINVAL;
-    const bool knorm = p->scorer == GRAPHKV_SCORER_KNORM;   // reads no queries: Qw may be NULL
-    if (!knorm && !score_ok(p)) return GRAPHKV_EINVAL;
-    if (!budgets_ok(p, n_layers, budgets)) return GRAPHKV_EINVAL;
-    if (!aligned16(Kc) || !aligned16(Vc) || (!knorm && !aligned16(Qw)) || !aligned16(Kout) ||
-        !aligned16(Vout) || !aligned4(idx))
-        return GRAPHKV_EINVAL;
-    if (scores_out && !aligned4(scores_out)) return GRAPHKV_EINVAL;
-    const Dims DG = group_dims(p, n_layers);   // layers per group, and whether its filter passes speculate
-    const int group = DG.L;
-    if (int32_t rc = check_ws(scratch_bytes(p, n_layers, DG), ws, ws_bytes)) return rc;
-    hipStream_t st = (hipStream_t)stream;
-    const size_t esize = p->dtype == GRAPHKV_FP32 ? 4 : 2;
-    const size_t kv_layer = (size_t)p->n_kv_heads * p->n_tokens * p->head_dim * esize;
-    const size_t q_layer = (size_t)p->n_q_heads * p->window * p->head_dim * esize;
-    const size_t s_layer = (size_t)p->n_kv_heads * (p->n_tokens - p->window);
-    size_t out_rows = 0;   // rows of Kout / Vout / idx written so far
-    for (int l0 = 0; l0 < n_layers; l0 += group) {
-        const int nl = n_layers - l0 < group ? n_layers - l0 : group;
-        const int32_t *bl = budgets ? budgets + l0 : nullptr;
-        const int32_t rc = run_compress(
-            p, nl, DG, bl, (const char *)Kc + l0 * kv_layer, (const char *)Vc + l0 * kv_layer,
-            Qw ? (const char *)Qw + l0 * q_layer : nullptr, (char *)Kout + out_rows * p->head_dim * esize,
-            (char *)Vout + out_rows * p->head_dim * esize, idx + out_rows,
-            scores_out ? scores_out + l0 * s_layer : nullptr, ws, st);
-        if (rc) return rc;
-        for (int l = 0; l < nl; ++l) out_rows += (size_t)p->n_kv_heads * (bl ? bl[l] : p->budget);
-    }
-    return GRAPHKV_OK;
+    return compress_layers(p, n_layers, group_dims(p, n_layers), budgets, Kc, Vc, Qw, Kout, Vout, idx, scores_out, ws,
+                           ws_bytes, stream);
 }
 
 int32_t graphkv_profile_begin(void)

@@ -553,10 +553,13 @@ static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int
     }
 }
 
+// Widest pooling window of the votes pass: its halo is multiplied twice and sits in LDS beside the chunk.
+constexpr int kFusedPool = 129;
+
 bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel)
 {
     const int R = mfma_score_rows(G, w, per_qhead_votes);
-    return (R <= 128 || (R == 256 && !per_qhead_votes)) && pool_kernel <= 33;
+    return (R <= 128 || (R == 256 && !per_qhead_votes)) && pool_kernel <= kFusedPool;
 }
 
 hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,

@@ -1062,7 +1062,7 @@ static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs
 {
 #define GKV_PICK(ITEMS)                                                                                          \
     do {                                                                                                         \
-        if (!allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError();     \
+        if (D == 4 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
         hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), update_lds(D), st, x, n, a, \
                            src, update);                                                                         \
     } while (0)
@@ -1168,7 +1168,7 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
 {
 #define GKV_BUDGET(ITEMS)                                                                                       \
     do {                                                                                                        \
-        if (!allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
+        if (D == 4 && !allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
         hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), update_lds(D), st, \
                            scores, P, idx, P, w, update, plan);                                                 \
     } while (0)

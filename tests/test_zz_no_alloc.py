@@ -63,3 +63,23 @@ def test_static_scratch_entry_rejects_what_does_not_fit():
         cp = p.c()
         gk._check(lib.graphkv_compress_static(ctypes.byref(cp), dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(),
                                               o[0].data_ptr(), o[1].data_ptr(), o[2].data_ptr(), None, None))
+
+
+def test_static_scratch_entry_falls_back_to_the_dense_block():
+    """512 heads of a 2K prompt with 8 sources: the filter route's per-row buffers (with speculative rows)
+    would not fit the built-in buffer, the dense edge block does.  Same bytes as the workspace entry, which
+    takes the filter route."""
+    cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=2100, window=32, n_sources=8, n_neighbors=32, budget=200,
+                       n_kv_heads=8, n_q_heads=8, rounds=2)
+    host, dev = util.device_layer(cfg, 1)
+    rep = 64
+    dev = [t.repeat(rep, 1, 1).contiguous() for t in dev]
+    p = util.params_from_cfg(synth.scaled(cfg, n_kv_heads=8 * rep, n_q_heads=8 * rep), scorer=gk.SCORER_KNORM)
+    assert gk.graphkv_workspace_bytes(p) > gk.STATIC_SCRATCH_BYTES
+    want, got = outputs(p), outputs(p)
+    print("static-scratch call with 512 heads", flush=True)
+    gk.graphkv_compress(p, *dev, want[0], want[1], want[2], scores_out=want[3])
+    gk.graphkv_compress_static(p, *dev, got[0], got[1], got[2], scores_out=got[3])
+    torch.cuda.synchronize()
+    assert torch.equal(got[2], want[2]) and torch.equal(got[3], want[3])
+    assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16))
