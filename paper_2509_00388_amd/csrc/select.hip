@@ -2,16 +2,13 @@
 // ascending index order.  Used for the source nodes (Eq. 2), the neighbourhoods
 // (Eq. 3) and the final budgeted selection.
 //
-// One workgroup per row.  The k-th largest value is found by a most-significant-
-// digit-first radix select over an order-preserving 32-bit key (digits of 11,
-// 11 and 10 bits, integer histograms in LDS), which also tells how many entries
-// equal to the threshold are still needed.  A last sweep emits, in index order,
-// every entry above the threshold and the first `need` entries equal to it:
-// that is exactly "first k by (value desc, index asc)".  All counting is
-// integer, so the result does not depend on scheduling.
-//
-// Rows of up to 32768 entries are read once, coalesced, and kept in LDS for all
-// sweeps; longer rows are re-read from L2 in every sweep.
+// One workgroup per row.  The sources and the edges of a dense row (few winners) come from a short list
+// of the entries that reach a bound, the budgeted selection from one histogram sweep and a bitmap (see
+// there).  What those do not take -- more than 256 winners with values, rows beyond 2^18 entries, masses of
+// equal values, the scratch rows of the exact fallback -- goes through a most-significant-digit-first
+// radix select over an order-preserving 32-bit key, whose last sweep emits, in index order, every entry
+// above the threshold and the first `need` entries equal to it: exactly "first k by (value desc, index
+// asc)".  All counting is integer, so no result depends on scheduling.
 #include "common.hpp"
 #include "decay.hpp"
 #include "kernels.hpp"

@@ -1187,11 +1187,11 @@ def test_edge_rows_small_m(oracle, P, m):
         assert np.array_equal(nbr[0, 0, a], want) and np.array_equal(ev[0, 0, a], row[want].astype(np.float32))
 
 
-@pytest.mark.parametrize("pool_kernel", [7, 35])
+@pytest.mark.parametrize("pool_kernel", [7, 35, 131])
 @pytest.mark.parametrize("G,w", [(1, 1), (1, 16), (3, 11), (7, 16), (5, 25), (4, 33), (5, 32), (7, 32), (1, 250), (1, 128)])
 def test_score_bf16_rows_that_do_not_fill_the_blocks(oracle, G, w, pool_kernel):
     """Stacked query rows G*w that leave the last 32-row block partly empty, or lie between 128 and 256
-    (filled up to 256): the filling must not vote.  The wide pooling window takes the separate pooling
+    (filled up to 256): the filling must not vote.  The widest pooling window takes the separate pooling
     kernel, with up to four vote rows per head."""
     cfg = small_bf16_cfg(n_tokens=1300 + w, window=w, n_kv_heads=2, n_q_heads=2 * G, budget=w + 50,
                          pool_kernel=pool_kernel)
@@ -1203,7 +1203,7 @@ def test_score_bf16_rows_that_do_not_fill_the_blocks(oracle, G, w, pool_kernel):
     util.assert_scores_close(s, oracle.score(K, Q, "bf16", pool_kernel, 0))
 
 
-@pytest.mark.parametrize("G,w,pool_kernel", [(1, 32, 7), (2, 64, 13), (3, 32, 33), (4, 32, 7), (4, 32, 35), (1, 96, 1)])
+@pytest.mark.parametrize("G,w,pool_kernel", [(1, 32, 7), (2, 64, 13), (3, 32, 33), (4, 32, 7), (4, 32, 35), (4, 32, 131), (1, 96, 1)])
 def test_score_max_pooling_over_several_key_chunks(oracle, G, w, pool_kernel):
     """Max pooling inside the votes pass: one vote row per query head in LDS, pooling windows that straddle
     chunk ends, windows wider than it takes (separate pooling kernel)."""
