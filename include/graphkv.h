@@ -25,7 +25,8 @@
  *     GRAPHKV_EWORKSPACE nothing has run.  GRAPHKV_EHIP reports a failed
  *     launch (earlier launches of the same call may already be queued).
  *   - Results are deterministic: the same inputs give byte-identical outputs.
- *   - NaN inputs are not supported (selection order is then unspecified).
+ *   - NaN inputs are not supported: selection order is then unspecified (every
+ *     index written is still that of a token of the row).
  *
  * Symbols: N tokens in the layer's cache, of which the last w are the
  * observation window; P = N - w prefix tokens are the graph nodes; H_kv / H_q

@@ -28,6 +28,10 @@ __device__ __forceinline__ float key_to_float(uint32_t key)   // inverse of ord_
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
+// Key of an entry of a row, where 0 stands for no entry: the one value whose key is 0 (a NaN of all ones)
+// gets 1, so that a row always holds as many keys as entries.
+__device__ __forceinline__ uint32_t entry_key(float v) { return max(ord_key(v), 1u); }
+
 // Histogram one digit of the keys that still match the prefix.  `in` says
 // whether this lane's key takes part.  A wave whose keys all share the digit
 // (usual in the top digit) issues a single add.
@@ -536,7 +540,7 @@ __device__ __forceinline__ void pick_row(const float *xr, int n, int k, const Pi
     uint32_t key[ITEMS], best = 0;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        key[i] = i * BLOCK + tid < n ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
+        key[i] = i * BLOCK + tid < n ? entry_key(val[i]) : 0u;
         best = max(best, key[i]);
     }
     uint32_t bound = kth_value_bound<BLOCK>(best, k, L, tid, lane, wv);
@@ -572,25 +576,32 @@ __device__ __forceinline__ void pick_row(const float *xr, int n, int k, const Pi
     pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
 }
 
-// A longer row: read twice, in batches of 12 loads per thread.
+// A longer row: read twice, in batches of 12 loads per thread.  Both reads compare floats, an instruction
+// less per entry than keys; floats order as their keys do but for NaN, which every comparison leaves out.
+// So the maxima are those of the numbers, which can only lower the bound; what is not below the bound is
+// looked at by its key, and a row in which fewer than k entries reach it goes through the general algorithm,
+// by keys throughout.
 __device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, const PickOut &o, PickLds<kPickBlock> &L,
                                               int tid, int lane, int wv)
 {
     L.clear(tid);
-    float best = -INFINITY;     // (floats order as their keys do)
+    float best = -INFINITY;
     row_sweep<12>(xr, n, tid, wv, [&](int, float v, bool in) { best = fmaxf(best, in ? v : -INFINITY); });
-    // (the bound need not be the key of an entry; floats compare with it as their keys do)
-    const float bound = key_to_float(kth_value_bound<kPickBlock>(ord_key(best), k, L, tid, lane, wv));
+    // (the bound need not be the key of an entry)
+    const uint32_t bound_key = kth_value_bound<kPickBlock>(ord_key(best), k, L, tid, lane, wv);
+    const float bound = key_to_float(bound_key);
     row_sweep<12>(xr, n, tid, wv, [&](int word, float v, bool in) {
-        if (in && v >= bound) {
-            const uint32_t at = atomicAdd(&L.cnt, 1u);
-            if (at < (uint32_t)kPickList)
-                L.list[at] = ((uint64_t)ord_key(v) << 32) | (uint32_t)~(word * kWave + lane);
+        if (in && !(v < bound)) {
+            const uint32_t key = ord_key(v);
+            if (key >= bound_key) {
+                const uint32_t at = atomicAdd(&L.cnt, 1u);
+                if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~(word * kWave + lane);
+            }
         }
     });
     __syncthreads();
     const int cnt = (int)L.cnt;
-    if (cnt <= kPickList) emit_winners<kPickBlock, false>(L, cnt, k, o, tid);
+    if (cnt >= k && cnt <= kPickList) emit_winners<kPickBlock, false>(L, cnt, k, o, tid);
     else pick_general<kPickBlock, false>(xr, n, k, o, L, tid);
 }
 
@@ -693,16 +704,18 @@ __device__ __forceinline__ void rank_in_pairs(const uint32_t *list, int cnt, uin
     __syncthreads();
 }
 
-// Indices of the set bits of a bitmap in LDS -> out, ascending.  A thread owns a run of words: it
-// counts their bits, one scan over the workgroup places the run, and it writes the run's indices.
+// Indices of the k set bits of a bitmap in LDS -> out, ascending.  A thread owns a run of words: it
+// counts their bits, one scan over the workgroup places the run, and it writes the run's indices.  A bitmap
+// with another number of bits is left alone (false, the same for every thread).
 template <int NW>
-__device__ __forceinline__ void emit_bitmap(const uint64_t *map, int words, uint32_t *part, int32_t *out, int tid,
+__device__ __forceinline__ bool emit_bitmap(const uint64_t *map, int words, int k, uint32_t *part, int32_t *out, int tid,
                                             int lane, int wv)
 {
     const int per = (words + NW * kWave - 1) / (NW * kWave), w0 = min(tid * per, words), w1 = min(w0 + per, words);
     uint32_t mine = 0, total;
     for (int w = w0; w < w1; ++w) mine += (uint32_t)__popcll(map[w]);
     int32_t *o = out + block_scan_add<NW>(mine, part, lane, wv, total);
+    if (total != (uint32_t)k) return false;
     for (int w = w0; w < w1; ++w) {
         uint64_t bits = map[w];
         while (bits) {
@@ -710,6 +723,7 @@ __device__ __forceinline__ void emit_bitmap(const uint64_t *map, int words, uint
             bits &= bits - 1;
         }
     }
+    return true;
 }
 
 template <int ITEMS, int D>
@@ -744,7 +758,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const bool in = i * kBudgetBlock + tid < n;
-        key[i] = in ? ord_key(val[i]) : 0u;   // 0 is below the key of every number
+        key[i] = in ? entry_key(val[i]) : 0u;
         kmin = min(kmin, in ? key[i] : 0xffffffffu);
         kmax = max(kmax, key[i]);
     }
@@ -820,7 +834,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
         }
         __syncthreads();
     }
-    emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), s_part[1], out, tid, lane, wv);
+    (void)emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), k, s_part[1], out, tid, lane, wv);
 }
 
 // Rows beyond 32768 entries: two reads instead of five.  A coarse sample gives the key range, the
@@ -888,21 +902,30 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     }
     if (tid < 4) lkey[min(cnt + (uint32_t)tid, (uint32_t)kBudgetList - 1u)] = 0u;   // padding for reads of four
     __syncthreads();
-    // The floats at the ends of the bin (the end bins are open).  Floats compare as their keys do.
-    const uint32_t last_bin = (kmax - kmin) >> shift;
+    // The floats at the ends of the bin (the end bins are open).  Floats compare as their keys do, but for
+    // two: the key below +0.0 stands for no number and reads back as -0.0, which +0.0 does not exceed (the
+    // number below it ends the bin instead), and NaN compares with nothing.
+    const uint32_t last_bin = (kmax - kmin) >> shift, top = kmin + (bin << shift) + ((1u << shift) - 1u);
     const float flo = bin == 0 ? -INFINITY : key_to_float(kmin + (bin << shift));
-    const float fhi = bin == last_bin ? INFINITY : key_to_float(kmin + (bin << shift) + ((1u << shift) - 1u));
+    const float fhi = bin == last_bin ? INFINITY : key_to_float(top == 0x7fffffffu ? top - 1u : top);
     row_sweep<16>(xr, n, tid, wv, [&](int word, float v, bool in) {
         const bool reach = in && v >= flo, over = reach && v > fhi;
         const uint64_t above = __ballot(over);
         if (lane == 0 && word < words) map[word] = above;
         if (reach && !over) {
             const uint32_t at = atomicAdd(&s_cnt, 1u);
-            lkey[at] = ord_key(v);
-            lidx[at] = (uint32_t)(word * kWave + lane);
+            if (at < (uint32_t)kBudgetList) {
+                lkey[at] = ord_key(v);
+                lidx[at] = (uint32_t)(word * kWave + lane);
+            }
         }
     });
     __syncthreads();
+    if (s_cnt != cnt) {   // counted by key, not found by comparison: NaN in the bin
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
+                                            nullptr, 1, plan);
+        return;
+    }
     // the need-th largest of the list
     uint32_t tau, equal;
     if (cnt <= (uint32_t)kPairs) {
@@ -947,7 +970,9 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
         if (in) atomicOr(reinterpret_cast<uint32_t *>(map) + (j >> 5), 1u << (j & 31u));
     }
     __syncthreads();
-    emit_bitmap<NW>(map, words, s_part[0], out, tid, lane, wv);
+    if (!emit_bitmap<NW>(map, words, k, s_part[0], out, tid, lane, wv))   // NaN counted above the bin and not marked
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
+                                            nullptr, 1, plan);
 }
 
 // ---- neighbourhoods of heads whose candidate lists overflowed ------------------------

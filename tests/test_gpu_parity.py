@@ -1238,3 +1238,85 @@ def test_budgeted_selection_long_rows_sampled_range(oracle, P, k):
     idx = gk.graphkv_select(p, torch.from_numpy(s).cuda()).cpu().numpy()
     ref, _ = oracle.select(s.astype(np.float64), P + w, w, k + w)
     assert np.array_equal(idx, ref)
+
+
+def key_order(row, k):
+    """The k entries that come first by (bits as a total order descending, index ascending): how the
+    selections order anything, NaN included, where numbers order as numbers."""
+    u = (row + np.float32(0)).view(np.uint32)
+    key = np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.int64)
+    return np.sort(np.lexsort((np.arange(row.size), -key))[:k])
+
+
+def rows_with_nan(P, k, seed):
+    """Rows of scores with quiet NaN of either sign: everywhere, a few, more than fit the list of winners, in
+    place of the largest and of the smallest, at the cut, and the NaN of all ones."""
+    rng = np.random.default_rng(seed)
+    s = rng.standard_normal((10, P)).astype(np.float32)
+    pos, neg, ones = (np.uint32(b) for b in (0x7fc00000, 0xffc00000, 0xffffffff))
+
+    def put(h, at, bits):
+        s[h].view(np.uint32)[at] = bits
+
+    put(0, slice(None), pos)
+    put(1, slice(None), neg)
+    put(2, slice(None), ones)
+    put(3, rng.choice(P, size=7, replace=False), pos)
+    put(4, rng.choice(P, size=P // 3, replace=False), pos)
+    put(5, np.argsort(-s[5])[:max(1, k // 2)], pos)
+    put(6, np.argsort(-s[6])[k:], neg)                            # k numbers in all, NaN behind them
+    put(7, np.argsort(-s[7])[max(0, k - 3):], ones)               # fewer than k numbers
+    put(8, np.argsort(-s[8])[max(0, k - 2):k + 2], neg)           # around the cut
+    put(9, slice(0, P, 2), neg)
+    s[9, 1::4] = np.inf
+    s[9, 3::4] = -np.inf
+    return s
+
+
+@pytest.mark.parametrize("P,k", [(700, 300), (1024, 1024), (20000, 4000), (32769, 500), (40001, 40001), (131008, 4032),
+                                 (262145, 300)])
+def test_budgeted_selection_of_rows_with_nan(P, k):
+    """NaN scores (one infinite key element makes a whole head's scores NaN) have no agreed order, but what
+    is selected must be k different tokens of the row, whatever kernel the row's length takes: the order
+    of the values' bits."""
+    say(f"selection with NaN P={P} k={k}")
+    s = rows_with_nan(P, k, P + k)
+    H, w = s.shape[0], 3
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=8, n_tokens=P + w, window=w, budget=k + w)
+    idx = torch.full((H, k + w), -7, dtype=torch.int32, device="cuda")
+    idx = gk.graphkv_select(p, torch.from_numpy(s).cuda(), idx).cpu().numpy()
+    for h in range(H):
+        assert np.array_equal(idx[h, :k], key_order(s[h], k)), f"row {h}"
+        assert np.array_equal(idx[h, k:], np.arange(P, P + w))
+
+
+@pytest.mark.parametrize("P,S", [(300, 256), (5000, 32), (32769, 1), (40001, 100), (131008, 256)])
+def test_sources_of_rows_with_nan(P, S):
+    """The same for the source nodes of a round, whose rows the edge kernels load by index."""
+    say(f"sources with NaN P={P} S={S}")
+    s = rows_with_nan(P, S, P - S)
+    H, d, w = s.shape[0], 8, 2
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, budget=w + 1, n_sources=S,
+                  n_neighbors=3, rounds=1, dtype=gk.FP32)
+    K = torch.randn(H, P + w, d, generator=torch.Generator("cuda").manual_seed(P), device="cuda")
+    _, src, nbr, _ = run_propagate(p, K, s)
+    for h in range(H):
+        assert np.array_equal(src[0, h], key_order(s[h], S)), f"row {h}"
+    assert nbr.min() >= 0 and nbr.max() < P
+
+
+def test_budgeted_selection_with_the_cut_just_below_zero():
+    """A long row whose cut lies among the numbers right below zero, zeros above them, in a bin of keys that
+    ends exactly below +0.0 (the range of the row's keys is 2^31 from a multiple of 2^21)."""
+    say("selection with the cut just below zero")
+    P, w = 40001, 2
+    rng = np.random.default_rng(1)
+    s = np.full((1, P), -1.5, dtype=np.float32)
+    s[0, 0], s[0, 1] = np.uint32(0xbfffffff).view(np.float32), 2.0
+    at = rng.permutation(np.arange(64, P))
+    s[0, at[:1000]], s[0, at[1000:1500]], s[0, at[1500:1800]] = 1.0, 0.0, -1e-43
+    k = 1602
+    p = gk.Params(n_kv_heads=1, n_q_heads=1, head_dim=8, n_tokens=P + w, window=w, budget=k + w)
+    idx = torch.full((1, k + w), -7, dtype=torch.int32, device="cuda")
+    idx = gk.graphkv_select(p, torch.from_numpy(s).cuda(), idx).cpu().numpy()
+    assert np.array_equal(idx[0, :k], key_order(s[0], k))
