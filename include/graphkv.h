@@ -216,7 +216,11 @@ int32_t graphkv_compress(const graphkv_params *p, const void *Kc, const void *Vc
  *   ws         graphkv_workspace_bytes_batched(p, n_layers) bytes
  * Layers are processed in groups: at most 64 layers, fewer while the scratch
  * memory of a group would exceed 2000 MiB (long prompts).  Results are identical
- * to n_layers per-layer calls.
+ * to n_layers per-layer calls, byte for byte, with one exception: where
+ * graphkv_uses_mfma() and G*w is a multiple of 32, a group of more than 2^19 keys
+ * (layers * H_kv * N) sums its softmax rows in longer runs.  Its scores then agree
+ * to the rounding of a 32-bit sum, and what is selected agrees unless two
+ * candidates lie within that of each other.
  */
 size_t graphkv_workspace_bytes_batched(const graphkv_params *p, int32_t n_layers);
 int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, const int32_t *budgets,

@@ -44,6 +44,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 // H and Hq count the heads of the whole batch (layers x heads per layer).
 struct Dims {
     int L, H, Hq, G, d, N, w, P, B, S, m, T;
+    int Hl;              // KV heads of one layer
     bool gemm;           // contractions the kernels for bf16 and d = 128 do not cover run in gemm.hip
     bool mfma_score, mfma_cosine, filter;
     bool speculate;      // speculative rows allowed (dropped when their scratch would not fit)
@@ -130,7 +131,8 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, c
 {
     Dims D;
     D.L = n_layers;
-    D.H = p->n_kv_heads * n_layers;
+    D.Hl = p->n_kv_heads;
+    D.H = D.Hl * n_layers;
     D.Hq = (p->n_q_heads > 0 ? p->n_q_heads : p->n_kv_heads) * n_layers;
     D.G = D.Hq / D.H > 0 ? D.Hq / D.H : 1;
     D.d = p->head_dim;
@@ -179,7 +181,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
         : D.gemm && gemm_votes_pools(p->pool_kernel));
     const int vote_rows = D.mfma_score ? mfma_score_vote_rows(D.G, D.w, per_q) : D.G;
     W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * vote_rows * D.P * 4 : 0);
-    W.part = take(D.mfma_score ? mfma_score_plan(D.H, mfma_score_rows(D.G, D.w, per_q), D.N).part_bytes
+    W.part = take(D.mfma_score ? mfma_score_plan(D.H, D.Hl, D.G, D.w, D.N, per_q).part_bytes
                   : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
     const size_t scoring_end = off;
     off = shared;
@@ -278,17 +280,17 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
     float *votes = at<float>(ws, W.votes);
     if (D.mfma_score) {
         const int per_q = p->pool_mode == GRAPHKV_POOL_MAX;
-        GKV_LAUNCH(GRAPHKV_K_SCORE_STATS, launch_mfma_score_stats(Kc, Qw, D.H, D.Hq, D.N, D.w, D.scale,
+        GKV_LAUNCH(GRAPHKV_K_SCORE_STATS, launch_mfma_score_stats(Kc, Qw, D.H, D.Hl, D.Hq, D.N, D.w, D.scale,
                                                                   per_q, at<float>(ws, W.part), st));
         if (mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel)) {
             // average pooling and the mean over the group happen inside pass B
             GKV_LAUNCH(GRAPHKV_K_SCORE_VOTES,
-                       launch_mfma_score_votes(Kc, Qw, D.H, D.Hq, D.N, D.w, D.scale, per_q, p->pool_kernel,
+                       launch_mfma_score_votes(Kc, Qw, D.H, D.Hl, D.Hq, D.N, D.w, D.scale, per_q, p->pool_kernel,
                                                at<float>(ws, W.part), scores, st));
             return GRAPHKV_OK;
         }
         GKV_LAUNCH(GRAPHKV_K_SCORE_VOTES,
-                   launch_mfma_score_votes(Kc, Qw, D.H, D.Hq, D.N, D.w, D.scale, per_q, 0,
+                   launch_mfma_score_votes(Kc, Qw, D.H, D.Hl, D.Hq, D.N, D.w, D.scale, per_q, 0,
                                            at<float>(ws, W.part), votes, st));
         GKV_LAUNCH(GRAPHKV_K_POOL,
                    launch_pool_group(votes, D.H, mfma_score_vote_rows(D.G, D.w, per_q), D.P, p->pool_kernel,

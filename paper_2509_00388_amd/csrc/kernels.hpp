@@ -113,22 +113,24 @@ hipError_t launch_copy_f32(const float *src, float *dst, long n, hipStream_t st)
 
 // ---- bf16 MFMA kernels, d = 128 (mfma_score.hip, mfma_cosine.hip) ----------
 struct MfmaScorePlan {
-    int chunks;        // key chunks per head in the streaming passes
-    size_t part_bytes; // bytes of per-chunk row statistics
+    int chunk_keys, chunks;   // keys per chunk, chunks per head of the row statistics
+    int per_wg;               // chunks a workgroup of the statistics pass takes
+    size_t part_bytes;        // bytes of per-chunk row statistics
 };
 int mfma_score_rows(int G, int w, int per_qhead_votes);   // stacked query rows, filled up to what the kernels take
-MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N);    // rows: mfma_score_rows()
+// Hkv: heads of the launch; layer_heads: KV heads of one of its layers.
+MfmaScorePlan mfma_score_plan(int Hkv, int layer_heads, int G, int w, int N, int per_qhead_votes);
 // Pass A: per (head, chunk, row) partial max and sum of exp2 over the chunk's visible keys.
 // Pass B: votes [Hkv * rows, P] with rows = mfma_score_vote_rows(): partial sums over
 // groups of query rows (to be added up), or one row per query head.
 int mfma_score_vote_rows(int G, int w, int per_qhead_votes);
-hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
+hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, float *part, hipStream_t st);
 // fused_pool_kernel > 0 (only if mfma_score_fuses_pool()): average pooling with that kernel
 // size and the mean over the query heads are done in the same kernel; `votes` is then the
 // score array [Hkv, P] and no pooling kernel follows.
 bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel);
-hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
+hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, int fused_pool_kernel,
                                   const float *part, float *votes, hipStream_t st);
 // E [Hkv, S, P] from bf16 keys (same contract as launch_generic_cosine); heads with

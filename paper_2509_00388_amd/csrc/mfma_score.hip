@@ -82,18 +82,23 @@ __device__ __forceinline__ void unit_of_workgroup(int nparts, int &h, int &chunk
 }
 
 // ---------------------------------------------------------------- pass A ---
-template <int NB, int SPLIT, int STREAMS = 4>
+// MANY: a workgroup takes `per_wg` consecutive chunks (whole tiles each) and keeps their statistics apart, so
+// that a batch cuts a head's keys as a single layer does and adds the same terms in the same order.  At a
+// chunk's last tile the waves park their statistics in LDS and start over; they are stored during the next
+// tile, behind its barrier, while the one after that parks in the other half of the LDS.
+template <int NB, int SPLIT, int STREAMS, bool MANY>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w,
-    int chunk_keys, float c, float *__restrict__ part, int R_total, int R_real, int row_base, int nparts)
+    int chunk_keys, int nchunks, int per_wg, float c, float *__restrict__ part, int R_total, int R_real, int row_base,
+    int nparts)
 {
     constexpr int R = NB * kBlk, NBW = NB / SPLIT, NT = 64 * STREAMS * SPLIT, TK = kBlk * STREAMS;
     extern __shared__ __align__(16) unsigned char kt[];   // two key tiles
-    __shared__ float sm[STREAMS][R], sz[STREAMS][R];
+    __shared__ float sm[MANY ? 2 : 1][STREAMS][R], sz[MANY ? 2 : 1][STREAMS][R];
     // nparts > 1: equal parts of 128 rows share one launch
-    int h, chunk, row_part;
-    unit_of_workgroup(nparts, h, chunk, row_part);
-    const int nchunks = gridDim.x / nparts;
+    int h, unit, row_part;
+    unit_of_workgroup(nparts, h, unit, row_part);
+    const int chunk0 = MANY ? unit * per_wg : unit;   // the workgroup's first chunk
     row_base += 128 * row_part;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv % STREAMS, row0 = (wv / STREAMS) * NBW * kBlk;   // first query row of this wave
@@ -110,8 +115,44 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     }
 
     const uint16_t *Kh = Kc + (long)h * N * kD;
-    const int k0 = chunk * chunk_keys, k1 = min(N, k0 + chunk_keys);
+    const int k0 = chunk0 * chunk_keys, k1 = min(N, k0 + (MANY ? per_wg : 1) * chunk_keys);
     const int ntile = (k1 - k0 + TK - 1) / TK;
+
+    // the lane's statistics -> LDS: the two half-waves (same query, other key rows) merged, one entry per stream
+    auto park = [&](int half) {
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) {
+            const float m2 = __shfl_xor(m[b], 32, kWave), z2 = __shfl_xor(z[b], 32, kWave);
+            merge_stats(m[b], z[b], m2, z2);
+            if (hh == 0) {
+                sm[half][stream][row0 + kBlk * b + l32] = m[b];
+                sz[half][stream][row0 + kBlk * b + l32] = z[b];
+            }
+        }
+    };
+    auto store = [&](int at, int half) {   // the streams' entries merged -> the statistics of chunk0 + at
+        if (tid < R) {
+            float mm = sm[half][0][tid], zz = sz[half][0][tid];
+#pragma unroll
+            for (int u = 1; u < STREAMS; ++u) merge_stats(mm, zz, sm[half][u][tid], sz[half][u][tid]);
+            float *o = part + (((long)h * nchunks + chunk0 + at) * R_total + row_base + tid) * 2;
+            o[0] = mm;
+            o[1] = zz;
+        }
+    };
+    int at = 0, tiles_in = 0;   // chunk being summed, tiles of it that are in
+    auto before_tile = [&] {    // the chunk that ended with the tile before this one
+        if (MANY && at > 0 && tiles_in == 0) store(at - 1, (at - 1) & 1);
+    };
+    auto after_tile = [&] {
+        if (MANY && ++tiles_in == chunk_keys / TK) {
+            park(at & 1);
+#pragma unroll
+            for (int b = 0; b < NBW; ++b) { m[b] = -INFINITY; z[b] = 0.f; }
+            ++at;
+            tiles_in = 0;
+        }
+    };
 
     // Two accumulator sets: the products of tile t are issued between the softmax instructions of
     // tile t - 1, so that the matrix core works while the vector unit does the exponentials.
@@ -168,6 +209,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
         multiply(kc, 0, [](int) {});
     };
     auto body = [&](const unsigned char *buf, int t, int set) {
+        before_tile();
         bf16x8 kc[kSteps];
         tile_read(buf, stream, l32, hh, kc);
         const int kb = k0 + TK * (t - 1) + kBlk * stream;   // the block finished here
@@ -196,35 +238,26 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
             multiply(kc, set, [](int) {});
             finish(t - 1, set ^ 1);
         }
+        after_tile();
     };
     if constexpr (NBW <= 2) {
         GKV_TILE_PIPELINE_OVERLAPPED(TK, NT, Kh, k0, k1 - 1, 1, ntile, head, body, finish);
     } else {   // three row blocks per wave: a second accumulator set does not fit the registers
         auto one_tile = [&](const unsigned char *buf, int t) {
+            before_tile();
             bf16x8 kc[kSteps];
             tile_read(buf, stream, l32, hh, kc);
             multiply(kc, 0, [](int) {});
             finish(t, 0);
+            if (t + 1 < ntile) after_tile();
         };
         GKV_TILE_PIPELINE_TK(TK, NT, Kh, k0, k1 - 1, 1, ntile, one_tile, (void)0);
     }
 
-    // merge the two half-waves (same query, other key rows), then the key streams
-#pragma unroll
-    for (int b = 0; b < NBW; ++b) {
-        const float m2 = __shfl_xor(m[b], 32, kWave), z2 = __shfl_xor(z[b], 32, kWave);
-        merge_stats(m[b], z[b], m2, z2);
-        if (hh == 0) { sm[stream][row0 + kBlk * b + l32] = m[b]; sz[stream][row0 + kBlk * b + l32] = z[b]; }
-    }
+    park(at & 1);
     __syncthreads();
-    if (tid < R) {
-        float mm = sm[0][tid], zz = sz[0][tid];
-#pragma unroll
-        for (int u = 1; u < STREAMS; ++u) merge_stats(mm, zz, sm[u][tid], sz[u][tid]);
-        float *o = part + (((long)h * nchunks + chunk) * R_total + row_base + tid) * 2;
-        o[0] = mm;
-        o[1] = zz;
-    }
+    before_tile();   // (a chunk that ended with the last tile but one)
+    store(at, at & 1);
 }
 
 // ---------------------------------------------------------------- pass B ---
@@ -402,10 +435,6 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     }
 }
 
-// Keys per workgroup: about `wgs` workgroups over all heads, but at least 8 key blocks per
-// wave so that loading the query operand is amortised.  The statistics pass takes half as many,
-// twice as long workgroups as the votes pass (its workgroups hold no votes in LDS, and every
-// workgroup pays for its queries and its first tiles: 423 -> 409 us on the 32-layer batch).
 // Keys per workgroup of the votes pass.  A compute unit runs one of these workgroups at a time (208
 // registers a lane, eight waves), and every workgroup pays for its queries, its first tiles and the merge
 // of the statistics -- about as long as 256 keys take.  So the cut with the fewest keys per compute unit
@@ -435,12 +464,13 @@ int votes_chunk_keys(int Hkv, int N, int rows, int lds_rows)
     return keys;
 }
 
-// Keys per workgroup of the statistics pass: 512 workgroups of at least 1024 keys, or one round of
+// Keys per workgroup of the statistics pass: 512 workgroups of at least 1024 keys (twice as long as the votes
+// pass's: they hold no votes in LDS, and every workgroup pays for its queries and its first tiles), or one round of
 // at least one tile each while 1024 keys would leave compute units idle (8 heads of 4096 keys 16.9 -> 10.2 us,
 // of 16384 17.5 -> 13.8).  Larger launches keep 512 workgroups: one round of twice as many keys is up to
 // a fifth faster for mid sizes, but a lane's sum of exponentials then runs over twice as many terms in 32
 // bits (error of the scores against 64 bits at 256 heads of 32768 keys 1.5e-6 -> 2.4e-6).
-int stats_chunk_keys(int Hkv, int N)
+int stats_keys(int Hkv, int N)
 {
     const long total = (long)Hkv * N;
     long ck = (total + 511) / 512, least = (total + kComputeUnits - 1) / kComputeUnits;
@@ -460,12 +490,23 @@ int mfma_score_rows(int G, int w, int per_qhead_votes)
     return R > 128 && !per_qhead_votes ? 256 : R;
 }
 
-MfmaScorePlan mfma_score_plan(int Hkv, int rows, int N)
+// A sum of exponentials depends in its last bits on where the keys are cut.  A batch cuts them as one of its
+// layers alone would, a workgroup taking several chunks, so that both give the same scores -- but for launches of
+// more than 2^19 keys (heads x tokens) with whole 32-row blocks, which are cut by all their heads: a workgroup
+// then has one chunk and the votes pass two to merge (32 layers of 8 heads x 32768 keys).  Parking a chunk
+// and the votes pass's longer merge cost 1 to 4 % of a small batch (whole pass, us, cut by all heads / by a
+// layer's: 8 layers of 8 heads x 4096 keys 86.2 / 89.5, 4 x 8 x 8192 86.3 / 88.8, 32 x 4 x 16384 of 112 rows 385 / 391).
+constexpr long kLayerCutKeys = 1L << 19;
+
+MfmaScorePlan mfma_score_plan(int Hkv, int layer_heads, int G, int w, int N, int per_qhead_votes)
 {
     MfmaScorePlan pl;
-    const int ck = stats_chunk_keys(Hkv, N);
-    pl.chunks = (N + ck - 1) / ck;
-    pl.part_bytes = (size_t)Hkv * pl.chunks * rows * 2 * sizeof(float);
+    const bool as_layer = (long)Hkv * N <= kLayerCutKeys || G * w % kBlk != 0;
+    pl.chunk_keys = stats_keys(as_layer ? layer_heads : Hkv, N);
+    pl.chunks = (N + pl.chunk_keys - 1) / pl.chunk_keys;
+    pl.per_wg = stats_keys(Hkv, N) / pl.chunk_keys;
+    if (pl.per_wg < 1) pl.per_wg = 1;
+    pl.part_bytes = (size_t)Hkv * pl.chunks * mfma_score_rows(G, w, per_qhead_votes) * 2 * sizeof(float);
     return pl;
 }
 
@@ -495,42 +536,41 @@ int mfma_score_vote_rows(int G, int w, int per_qhead_votes)
     return rows;
 }
 
-hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
+template <int NB, int SPLIT, int STREAMS>
+static hipError_t launch_stats_nb(const uint16_t *K, const uint16_t *Q, int Hkv, int N, int P, int w,
+                                  const MfmaScorePlan &plan, float c, float *part, int R_total, int R_real, int row_base,
+                                  hipStream_t st)
+{
+    const dim3 grid((plan.chunks + plan.per_wg - 1) / plan.per_wg, Hkv), block(64 * STREAMS * SPLIT);
+    const size_t lds = 2 * (kBlk * STREAMS) * kPitch;
+    auto *kernel = plan.per_wg > 1 ? score_stats_kernel<NB, SPLIT, STREAMS, true> : score_stats_kernel<NB, SPLIT, STREAMS, false>;
+    if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, K, Q, N, P, w, plan.chunk_keys, plan.chunks, plan.per_wg, c, part,
+                       R_total, R_real, row_base, 1);
+    return hipGetLastError();
+}
+
+hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, float *part, hipStream_t st)
 {
     const int G = Hq / Hkv, R_real = G * w, R = mfma_score_rows(G, w, per_qhead_votes), P = N - w;
-    const MfmaScorePlan plan = mfma_score_plan(Hkv, R, N);
-    const int ck = stats_chunk_keys(Hkv, N);
+    const MfmaScorePlan plan = mfma_score_plan(Hkv, layer_heads, G, w, N, per_qhead_votes);
     const float c = scale * 1.4426950408889634f;
     const uint16_t *K = (const uint16_t *)Kc, *Q = (const uint16_t *)Qw;
-    if (R == 256) {   // one workgroup takes all 256 rows: 2 key streams x 4 row groups, tiles of 64 keys
-        if (!allow_big_lds((const void *)score_stats_kernel<8, 4, 2>)) return hipGetLastError();
-        hipLaunchKernelGGL((score_stats_kernel<8, 4, 2>), dim3(plan.chunks, Hkv), dim3(512), 2 * 64 * kPitch, st, K, Q, N,
-                           P, w, ck, c, part, R, R_real, 0, 1);
-        return hipGetLastError();
-    }
+    if (R == 256)   // one workgroup takes all 256 rows: 2 key streams x 4 row groups, tiles of 64 keys
+        return launch_stats_nb<8, 4, 2>(K, Q, Hkv, N, P, w, plan, c, part, R, R_real, 0, st);
     // other row counts beyond 128: parts of at most 128 rows, one launch per part
-    const int merged = 1;
-    dim3 grid(plan.chunks * merged, Hkv);
-#define GKV_STATS(NB, SP)                                                                          \
-    do {                                                                                           \
-        if (!allow_big_lds((const void *)score_stats_kernel<NB, SP>)) return hipGetLastError();    \
-        hipLaunchKernelGGL((score_stats_kernel<NB, SP>), grid, dim3(256 * SP), 2 * kTileBytes, st, \
-                           K, Q, N, P, w, ck, c, part, R, R_real, row_base, merged);               \
-    } while (0)
-    for (int pt = 0; 128 * pt < R; pt += merged) {
-        const int row_base = 128 * pt;
+    for (int pt = 0; 128 * pt < R; ++pt) {
+        hipError_t err = hipErrorInvalidValue;
         switch (part_rows(R, pt) / 32) {
-            case 1: GKV_STATS(1, 1); break;
-            case 2: GKV_STATS(2, 2); break;
-            case 3: GKV_STATS(3, 1); break;
-            case 4: GKV_STATS(4, 2); break;
-            default: return hipErrorInvalidValue;
+            case 1: err = launch_stats_nb<1, 1, 4>(K, Q, Hkv, N, P, w, plan, c, part, R, R_real, 128 * pt, st); break;
+            case 2: err = launch_stats_nb<2, 2, 4>(K, Q, Hkv, N, P, w, plan, c, part, R, R_real, 128 * pt, st); break;
+            case 3: err = launch_stats_nb<3, 1, 4>(K, Q, Hkv, N, P, w, plan, c, part, R, R_real, 128 * pt, st); break;
+            case 4: err = launch_stats_nb<4, 2, 4>(K, Q, Hkv, N, P, w, plan, c, part, R, R_real, 128 * pt, st); break;
         }
-        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+        if (err != hipSuccess) return err;
     }
-#undef GKV_STATS
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int NB, int SPLIT, int STREAMS = 4>
@@ -562,12 +602,12 @@ bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel)
     return (R <= 128 || (R == 256 && !per_qhead_votes)) && pool_kernel <= kFusedPool;
 }
 
-hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int Hq, int N, int w,
+hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, int fused_pool_kernel,
                                   const float *part, float *votes, hipStream_t st)
 {
     const int G = Hq / Hkv, R_real = G * w, R = mfma_score_rows(G, w, per_qhead_votes), P = N - w;
-    const MfmaScorePlan plan = mfma_score_plan(Hkv, R, N);
+    const MfmaScorePlan plan = mfma_score_plan(Hkv, layer_heads, G, w, N, per_qhead_votes);
     // fused pooling: a workgroup also multiplies pool_half keys on either side of its chunk; the
     // P prefix keys are spread evenly over the chunks
     const int pool_half = fused_pool_kernel > 0 ? (fused_pool_kernel - 1) / 2 : -1;

@@ -1064,7 +1064,7 @@ def test_batched_short_prompts_take_the_filter_route(L, n_tokens, S, m, rounds):
     """Batches of 2048 <= P < 8192 keys with 2^23 edges or more skip the dense edge block, a layer
     on its own does not: the bytes must be the same (also in the smaller last launch group of 66
     layers, which follows the full group's route).  Key norms as scores: they do not depend on how
-    a batch cuts the keys into chunks."""
+    a batch cuts the keys into chunks (beyond 2^19 keys a softmax is cut by all heads of the group)."""
     say(f"short-prompt filter route L={L} N={n_tokens} S={S} m={m} T={rounds}")
     H = 8 if L < 60 else 1
     cfg = small_bf16_cfg(n_tokens=n_tokens, n_kv_heads=H, n_q_heads=4 * H, n_sources=S, n_neighbors=m, rounds=rounds,
@@ -1320,3 +1320,38 @@ def test_budgeted_selection_with_the_cut_just_below_zero():
     idx = torch.full((1, k + w), -7, dtype=torch.int32, device="cuda")
     idx = gk.graphkv_select(p, torch.from_numpy(s).cuda(), idx).cpu().numpy()
     assert np.array_equal(idx[0, :k], key_order(s[0], k))
+
+
+def batched_and_per_layer(p, L, seed):
+    """Scores and indices of a batch of random layers, and of the same layers one call each."""
+    g = torch.Generator("cuda").manual_seed(seed)
+    td = torch.float32 if p.dtype == gk.FP32 else torch.bfloat16
+    H, Hq, N, d = p.n_kv_heads, p.n_q_heads, p.n_tokens, p.head_dim
+    K, V = (torch.randn(L, H, N, d, generator=g, device="cuda").to(td) for _ in range(2))
+    Q = torch.randn(L, Hq, p.window, d, generator=g, device="cuda").to(td)
+    sc = torch.empty((L, H, p.n_prefix), dtype=torch.float32, device="cuda")
+    idx = gk.graphkv_compress_batched(p, L, None, K, V, Q, scores_out=sc)[2].cpu().numpy().reshape(L, H, p.budget)
+    sc = sc.cpu().numpy()
+    one = torch.empty((H, p.n_prefix), dtype=torch.float32, device="cuda")
+    layers = []
+    for l in range(L):
+        i_l = gk.graphkv_compress(p, K[l], V[l], Q[l], scores_out=one)[2].cpu().numpy()
+        layers.append((one.cpu().numpy().copy(), i_l))
+    return sc, idx, layers
+
+
+@pytest.mark.parametrize("L,H,G,w,N,mode", [
+    (8, 8, 4, 32, 4096, 0), (4, 8, 4, 32, 8192, 0), (2, 8, 2, 32, 16384, 0), (8, 8, 1, 32, 4099, 0), (5, 4, 3, 32, 5000, 0),
+    (8, 8, 4, 64, 4096, 0), (4, 8, 7, 32, 8100, 0), (8, 8, 2, 32, 4096, 1), (7, 4, 4, 64, 3000, 1), (8, 2, 7, 16, 2111, 0),
+    (17, 4, 7, 16, 9001, 0), (6, 16, 1, 16, 8192, 0), (9, 16, 5, 25, 4100, 0)])
+def test_batched_scores_equal_per_layer(L, H, G, w, N, mode):
+    """A batch on the streaming kernels gives each layer's scores bit for bit: batches up to 2^19 keys, and
+    larger ones whose query rows do not fill the 32-row blocks.  One to eight chunks per workgroup of the
+    statistics pass, chunks of one tile, ends that are no whole chunk, every number of row blocks."""
+    say(f"batched scores L={L} H={H} G={G} w={w} N={N} pool mode {mode}")
+    p = gk.Params(n_kv_heads=H, n_q_heads=H * G, head_dim=128, n_tokens=N, window=w, pool_kernel=7, pool_mode=mode,
+                  budget=w + 300, n_sources=16, n_neighbors=8, rounds=2, dtype=gk.BF16)
+    assert gk.graphkv_uses_mfma(p) and (L * H * N <= 1 << 19 or G * w % 32)
+    sc, idx, layers = batched_and_per_layer(p, L, N + L)
+    for l, (s_l, i_l) in enumerate(layers):
+        assert np.array_equal(sc[l], s_l) and np.array_equal(idx[l], i_l), f"layer {l}"
