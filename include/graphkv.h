@@ -235,8 +235,10 @@ int32_t graphkv_compress_batched(const graphkv_params *p, int32_t n_layers, cons
  * `ws`: the scratch memory is a buffer of GRAPHKV_STATIC_SCRATCH_BYTES that
  * belongs to the library's code object (every GPU the library runs on holds its
  * own copy until the process ends).  The call allocates and frees nothing.
- *   - params whose graphkv_workspace_bytes() exceeds GRAPHKV_STATIC_SCRATCH_BYTES
- *     are rejected with GRAPHKV_ESCRATCH before anything is enqueued;
+ *   - params that need more scratch than GRAPHKV_STATIC_SCRATCH_BYTES are rejected
+ *     with GRAPHKV_ESCRATCH before anything is enqueued.  Whatever
+ *     graphkv_workspace_bytes() puts within it is taken, and what it puts slightly
+ *     above may be, by a slower way with less scratch and the same results;
  *   - every call on a GPU uses that GPU's one buffer: calls that overlap in time on
  *     one GPU (two streams, two host threads) race -- serialise them, or use
  *     graphkv_compress with a workspace each;

@@ -45,6 +45,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 struct Dims {
     int L, H, Hq, G, d, N, w, P, B, S, m, T;
     int Hl;              // KV heads of one layer
+    bool frugal;         // the least scratch (dims_of)
     bool gemm;           // contractions the kernels for bf16 and d = 128 do not cover run in gemm.hip
     bool mfma_score, mfma_cosine, filter;
     bool speculate;      // speculative rows allowed (dropped when their scratch would not fit)
@@ -124,8 +125,8 @@ bool budget_ok(const graphkv_params *p)
 
 // `like`: the dimensions of the call's full launch group, whose routes a smaller last group takes
 // too (so that the workspace sized for the full group is enough).
-// frugal: the routes with the least scratch (no filter route below 8192 nodes, the scalar kernels where
-// gemm.hip would keep row statistics beside the logits), for a buffer that the faster ones do not fit.
+// frugal: the least scratch (no filter route below 8192 nodes, no logits of the window's own keys), for a buffer
+// that the faster way does not fit; the results are the same.
 Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, const Dims *like = nullptr,
              bool frugal = false)
 {
@@ -143,7 +144,8 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, c
     D.S = p->rounds > 0 ? p->n_sources : 0;
     D.m = p->rounds > 0 ? p->n_neighbors : 0;
     D.T = p->rounds;
-    D.gemm = like ? like->gemm : p->impl == GRAPHKV_IMPL_AUTO && !frugal;
+    D.frugal = frugal;
+    D.gemm = p->impl == GRAPHKV_IMPL_AUTO;
     D.mfma_score = mfma_score_ok(p);
     D.mfma_cosine = mfma_cosine_ok(p);
     D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && (!frugal || D.P >= 8192) &&
@@ -171,18 +173,27 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     // The scoring stage's scratch and the propagation's take the same place: one is done with before the
     // other begins (same stream).
     const size_t shared = off;
-    W.logits = take(!D.mfma_score && scoring ? rows * D.N * 4 : 0);
-    W.row_max = take(rows * (D.gemm ? 8 : 4));   // (or the pairs of launch_gemm_merge)
-    W.row_sum = take(rows * 4);
-    // votes per query head (or row group); not needed when pass B pools and groups them itself
     const int per_q = p->pool_mode == GRAPHKV_POOL_MAX;
-    const bool votes_stay_in_lds = scoring && (D.mfma_score
-        ? mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel)
-        : D.gemm && gemm_votes_pools(p->pool_kernel));
-    const int vote_rows = D.mfma_score ? mfma_score_vote_rows(D.G, D.w, per_q) : D.G;
-    W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * vote_rows * D.P * 4 : 0);
-    W.part = take(D.mfma_score ? mfma_score_plan(D.H, D.Hl, D.G, D.w, D.N, per_q).part_bytes
-                  : D.gemm && scoring ? gemm_score_plan(D.H, D.G * D.w, D.N).part_bytes : 0);
+    if (D.mfma_score) {
+        W.logits = W.row_max = W.row_sum = off;   // (not used)
+        // votes per query head or row group; not needed when pass B pools and groups them itself
+        const bool votes_stay_in_lds = scoring && mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel);
+        W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * mfma_score_vote_rows(D.G, D.w, per_q) * D.P * 4 : 0);
+        W.part = take(mfma_score_plan(D.H, D.Hl, D.G, D.w, D.N, per_q).part_bytes);
+    } else if (D.gemm) {
+        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.frugal);
+        const size_t part = scoring ? pl.part_bytes : 0;
+        const size_t votes = scoring && !gemm_votes_pools(p->pool_kernel) ? (size_t)D.Hq * D.P * 4 : 0;
+        W.logits = take(scoring ? rows * pl.pitch * 4 : 0);
+        W.row_max = W.row_sum = take(scoring ? rows * 8 : 0);      // (max, sum) pairs
+        W.part = W.votes = take(part > votes ? part : votes);      // (merged before there are votes)
+    } else {
+        W.logits = take(scoring ? rows * D.N * 4 : 0);
+        W.row_max = take(rows * 4);
+        W.row_sum = take(rows * 4);
+        W.votes = take(scoring ? (size_t)D.Hq * D.P * 4 : 0);
+        W.part = off;                                              // (not used)
+    }
     const size_t scoring_end = off;
     off = shared;
     // the dense edge block [heads, S, P] of the routes that materialise it; on the filter route
@@ -299,27 +310,30 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
     }
     float *logits = at<float>(ws, W.logits), *row_max = at<float>(ws, W.row_max), *row_sum = at<float>(ws, W.row_sum);
     if (D.gemm) {
-        float *part = at<float>(ws, W.part);
+        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.frugal);
+        const bool pools = gemm_votes_pools(p->pool_kernel);
+        float *stat = row_max;   // (max, sum) pairs; a single chunk's statistics go there at once
+        float *part = pl.chunks > 1 ? at<float>(ws, W.part) : stat;
+        int chunks = pl.chunks;
         GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS,
-                   launch_gemm_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale, logits, part, st));
-        if (gemm_votes_pools(p->pool_kernel)) {
-            int chunks = gemm_score_plan(D.H, D.G * D.w, D.N).chunks;
-            if (gemm_merges_first(D.H, D.G * D.w, D.N)) {
-                float *stat = row_max;   // (max, sum) pairs
-                GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_merge(part, D.H, D.Hq, D.N, D.w, stat, st));
-                part = stat;
-                chunks = 1;
-            }
-            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_votes(logits, part, chunks, D.H, D.Hq, D.N, D.w,
+                   launch_gemm_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale, pl, logits, part, st));
+        if (chunks > 1 && (!pools || gemm_merges_first(pl, D.G * D.w))) {
+            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_merge(part, pl, D.H, D.Hq, D.w, stat, st));
+            part = stat;
+            chunks = 1;
+        }
+        if (pools) {
+            GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_gemm_votes(logits, pl, part, chunks, D.H, D.Hl, D.Hq, D.N, D.w,
                                                                   p->pool_kernel, p->pool_mode, scores, st));
             return GRAPHKV_OK;
         }
-        GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_merge_part(part, D.H, D.Hq, D.N, D.w, row_max, row_sum, st));
+        GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_generic_votes(logits, pl.pitch, stat, stat + 1, 2, D.Hq, D.P, D.w, votes, st));
     } else {
         GKV_LAUNCH(GRAPHKV_K_GENERIC_LOGITS, launch_generic_logits(Kc, Qw, p->dtype, D.H, D.Hq, D.d, D.N, D.w, D.scale,
                                                                    logits, row_max, row_sum, st));
+        GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES,
+                   launch_generic_votes(logits, D.N, row_max, row_sum, 1, D.Hq, D.P, D.w, votes, st));
     }
-    GKV_LAUNCH(GRAPHKV_K_GENERIC_VOTES, launch_generic_votes(logits, row_max, row_sum, D.Hq, D.N, D.w, votes, st));
     GKV_LAUNCH(GRAPHKV_K_POOL, launch_pool_group(votes, D.H, D.G, D.P, p->pool_kernel, p->pool_mode, (float)D.G,
                               scores, st));
     return GRAPHKV_OK;
@@ -682,8 +696,7 @@ int32_t graphkv_compress_static(const graphkv_params *p, const void *Kc, const v
     if (need == 0) return GRAPHKV_EINVAL;
     Dims D = group_dims(p, 1);
     if (need > kStaticScratchBytes) {
-        // (a short prompt with many heads may still fit with its dense edge block, logits without
-        // the statistics of their chunks)
+        // (a short prompt with many heads may still fit with its dense edge block, logits without the window's)
         D = group_dims(p, 1, true);
         if (scratch_bytes(p, 1, D) > kStaticScratchBytes) return GRAPHKV_ESCRATCH;
     }

@@ -95,146 +95,167 @@ template <int NBR> struct Shape {
     static constexpr int RS = NBR >= 2 ? 2 : 1, STREAMS = 4 / RS, NBW = NBR / RS, TR = 32 * NBR, TK = 32 * STREAMS;
 };
 
-// Stage I, logits of the window queries (scaled) and per (chunk of keys, row) the maximum and the sum
-// of exp over the chunk's visible keys.  Keys are the rows of the products, queries the columns: a lane
-// owns one query and keeps its statistics without cross-lane traffic.
-template <typename T, int NBR>
+// Stage I, logits of the window queries (scaled; `pitch` of the N to a row, the P prefix keys' at least) and per
+// (chunk of keys, row) the maximum and the sum of exp over the chunk's visible keys.  Keys are the rows of the products, queries the
+// columns: a lane owns one query and keeps its statistics without cross-lane traffic.  MANY: a workgroup takes
+// `per_wg` consecutive chunks, whole tiles each, and keeps their statistics apart.
+template <typename T, int NBR, bool MANY>
 __global__ __launch_bounds__(256) void gemm_logits_kernel(
     const T *__restrict__ Kc, const T *__restrict__ Qw, int d, int N, int P, int w, int R, float scale,
-    int chunk_keys, float *__restrict__ logits, float *__restrict__ part)
+    int chunk_keys, int nchunks, int per_wg, int pitch, float *__restrict__ logits, float *__restrict__ part)
 {
     using Sh = Shape<NBR>;
     __shared__ __align__(16) unsigned char kt[Sh::TK * kRowPitch], qt[Sh::TR * kRowPitch];
     __shared__ float sm[Sh::STREAMS][Sh::TR], sz[Sh::STREAMS][Sh::TR];
-    const int h = blockIdx.y, chunk = blockIdx.x, row0 = blockIdx.z * Sh::TR;
+    const int h = blockIdx.y, row0 = blockIdx.z * Sh::TR;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv % Sh::STREAMS, rs = wv / Sh::STREAMS;
     const int row_bytes = d * (int)sizeof(T);
     const char *Kh = reinterpret_cast<const char *>(Kc + (long)h * N * d);
     const char *Qh = reinterpret_cast<const char *>(Qw + (long)h * R * d);
-    const int k0 = chunk * chunk_keys, k1 = min(N, k0 + chunk_keys);
-
-    float m[Sh::NBW], z[Sh::NBW];
-    int last_vis[Sh::NBW];
-#pragma unroll
-    for (int b = 0; b < Sh::NBW; ++b) {
-        m[b] = -INFINITY;
-        z[b] = 0.f;
-        last_vis[b] = min(P + (row0 + 32 * (rs * Sh::NBW + b) + l32) % w, k1 - 1);
-    }
-    for (int t0 = k0; t0 < k1; t0 += Sh::TK) {
-        acc16 acc[Sh::NBW];
-#pragma unroll
-        for (int b = 0; b < Sh::NBW; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-        for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
-            __syncthreads();   // the tiles in LDS are free
-            stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, N - 1) * row_bytes; });
-            if (t0 == k0 || row_bytes > kRowBytes)   // (the queries stay when they fit whole)
-                stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Qh + (long)min(row0 + r, R - 1) * row_bytes; });
-            __syncthreads();
-            const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
-            const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
-            const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
-#pragma unroll
-            for (int s = 0; s < kMaxSteps; ++s) {
-                if (s >= steps) break;
-                const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
-#pragma unroll
-                for (int b = 0; b < Sh::NBW; ++b)
-                    mfma_step<T>(k, *reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), acc[b]);
-            }
-        }
-        const int key0 = t0 + 32 * stream;
+    const int first = blockIdx.x * (MANY ? per_wg : 1), last = MANY ? min(nchunks, first + per_wg) : first + 1;
+    for (int chunk = first; chunk < last; ++chunk) {
+        const int k0 = chunk * chunk_keys, k1 = min(N, k0 + chunk_keys), kstore = min(k1, pitch);
+        float m[Sh::NBW], z[Sh::NBW];
+        int last_vis[Sh::NBW];
 #pragma unroll
         for (int b = 0; b < Sh::NBW; ++b) {
-            const int row = row0 + 32 * (rs * Sh::NBW + b) + l32;
-            float tm = -INFINITY;
+            m[b] = -INFINITY;
+            z[b] = 0.f;
+            last_vis[b] = min(P + (row0 + 32 * (rs * Sh::NBW + b) + l32) % w, k1 - 1);
+        }
+        for (int t0 = k0; t0 < k1; t0 += Sh::TK) {
+            acc16 acc[Sh::NBW];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                acc[b][i] *= scale;
-                if (key0 + mfma_row(i, hh) <= last_vis[b]) tm = fmaxf(tm, acc[b][i]);
+            for (int b = 0; b < Sh::NBW; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+            for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
+                __syncthreads();   // the tiles in LDS are free
+                stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, N - 1) * row_bytes; });
+                if ((t0 == k0 && chunk == first) || row_bytes > kRowBytes)   // (the queries stay when they fit whole)
+                    stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Qh + (long)min(row0 + r, R - 1) * row_bytes; });
+                __syncthreads();
+                const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
+                const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
+                const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
+#pragma unroll
+                for (int s = 0; s < kMaxSteps; ++s) {
+                    if (s >= steps) break;
+                    const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
+#pragma unroll
+                    for (int b = 0; b < Sh::NBW; ++b)
+                        mfma_step<T>(k, *reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), acc[b]);
+                }
             }
-            const float mn = fmaxf(m[b], tm);
-            if (mn != -INFINITY) {
-                float zz = z[b] * expf(m[b] - mn);
+            const int key0 = t0 + 32 * stream;
 #pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (key0 + mfma_row(i, hh) <= last_vis[b]) zz += expf(acc[b][i] - mn);
-                m[b] = mn;
-                z[b] = zz;
-            }
-            if (row < R) {
-                float *o = logits + ((long)h * R + row) * N;
+            for (int b = 0; b < Sh::NBW; ++b) {
+                const int row = row0 + 32 * (rs * Sh::NBW + b) + l32;
+                float tm = -INFINITY;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int key = key0 + 8 * v + 4 * hh;
-                    if ((N & 3) == 0 && key + 3 < k1) {
-                        *reinterpret_cast<float4 *>(o + key) =
-                            make_float4(acc[b][4 * v], acc[b][4 * v + 1], acc[b][4 * v + 2], acc[b][4 * v + 3]);
-                    } else {
+                for (int i = 0; i < 16; ++i) {
+                    acc[b][i] *= scale;
+                    if (key0 + mfma_row(i, hh) <= last_vis[b]) tm = fmaxf(tm, acc[b][i]);
+                }
+                const float mn = fmaxf(m[b], tm);
+                if (mn != -INFINITY) {
+                    float zz = z[b] * expf(m[b] - mn);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (key + e < k1) o[key + e] = acc[b][4 * v + e];
+                    for (int i = 0; i < 16; ++i)
+                        if (key0 + mfma_row(i, hh) <= last_vis[b]) zz += expf(acc[b][i] - mn);
+                    m[b] = mn;
+                    z[b] = zz;
+                }
+                if (row < R) {
+                    float *o = logits + ((long)h * R + row) * pitch;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int key = key0 + 8 * v + 4 * hh;
+                        if ((pitch & 3) == 0 && key + 3 < kstore) {
+                            *reinterpret_cast<float4 *>(o + key) =
+                                make_float4(acc[b][4 * v], acc[b][4 * v + 1], acc[b][4 * v + 2], acc[b][4 * v + 3]);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (key + e < kstore) o[key + e] = acc[b][4 * v + e];
+                        }
                     }
                 }
             }
         }
-    }
-    // the half-waves (same query, other keys), then the key streams
+        // the half-waves (same query, other keys), then the key streams
 #pragma unroll
-    for (int b = 0; b < Sh::NBW; ++b) {
-        merge_exp(m[b], z[b], other_half(m[b]), other_half(z[b]));
-        if (hh == 0) {
-            sm[stream][32 * (rs * Sh::NBW + b) + l32] = m[b];
-            sz[stream][32 * (rs * Sh::NBW + b) + l32] = z[b];
+        for (int b = 0; b < Sh::NBW; ++b) {
+            merge_exp(m[b], z[b], other_half(m[b]), other_half(z[b]));
+            if (hh == 0) {
+                sm[stream][32 * (rs * Sh::NBW + b) + l32] = m[b];
+                sz[stream][32 * (rs * Sh::NBW + b) + l32] = z[b];
+            }
         }
-    }
-    __syncthreads();
-    if (tid < Sh::TR && row0 + tid < R) {
-        float mm = sm[0][tid], zz = sz[0][tid];
+        __syncthreads();
+        if (tid < Sh::TR && row0 + tid < R) {
+            float mm = sm[0][tid], zz = sz[0][tid];
 #pragma unroll
-        for (int u = 1; u < Sh::STREAMS; ++u) merge_exp(mm, zz, sm[u][tid], sz[u][tid]);
-        float *o = part + (((long)h * gridDim.x + chunk) * R + row0 + tid) * 2;
-        o[0] = mm;
-        o[1] = zz;
+            for (int u = 1; u < Sh::STREAMS; ++u) merge_exp(mm, zz, sm[u][tid], sz[u][tid]);
+            float *o = part + (((long)h * nchunks + chunk) * R + row0 + tid) * 2;
+            o[0] = mm;
+            o[1] = zz;
+        }
     }
 }
 
 // Votes, pooling and the mean over the group in one go: scores[h, j] = 1/G sum_g pool(votes of query
 // head g).  A workgroup takes KEYS keys (pool_half of them on either side only for the pooling), its
-// PARTS groups of KEYS threads share the query rows; the statistics of up to kVoteRows rows at a time are
+// PARTS groups of KEYS threads share the query rows, each with SUMS sums per key (the order of a key's
+// additions is that of PARTS * SUMS groups); the statistics of up to kVoteRows rows at a time are
 // merged from the chunks into LDS first.  Average pooling adds the whole group before it pools, so only
 // max pooling has to stop at every query head.  (Merging the statistics of one query head at a time:
 // 24 us for 8 heads of 128 rows x 4064 keys, 30 us for 8160; this way, merge included, 17 and 27 us.)
 constexpr int kVoteHalf = 32;    // widest pooling half-window taken here
 constexpr int kVoteRows = 512;   // rows whose statistics sit in LDS
 
-template <int KEYS, int PARTS>
+template <int KEYS, int PARTS, int SUMS>   // SUMS: 1 or 2
 __global__ __launch_bounds__(KEYS * PARTS) void gemm_votes_kernel(
-    const float *__restrict__ logits, const float *__restrict__ part, int chunks, int N, int P, int w, int G,
+    const float *__restrict__ logits, int pitch, const float *__restrict__ part, int chunks, int P, int w, int G,
     int pool_half, int pool_mode, float *__restrict__ scores)
 {
-    constexpr int NT = KEYS * PARTS;
-    __shared__ float vs[PARTS][KEYS], s_max[kVoteRows], s_inv[kVoteRows];
+    constexpr int NT = KEYS * PARTS, GROUPS = PARTS * SUMS, U = 8 / SUMS;
+    __shared__ float vs[GROUPS][KEYS], s_max[kVoteRows], s_inv[kVoteRows];
     const int h = blockIdx.y, tid = threadIdx.x, t = tid % KEYS, p = tid / KEYS;
     const int R = G * w, tile = KEYS - 2 * pool_half;
     const int j = blockIdx.x * tile - pool_half + t;          // this thread's key
     const bool in = j >= 0 && j < P;
     const int jc = min(max(j, 0), P - 1);
-    const float *lh = logits + (long)h * R * N + jc;
-    float total = 0.f, v = 0.f;
+    const float *lh = logits + (long)h * R * pitch + jc;
+    float total = 0.f, v[SUMS] = {};
+    auto put_parts = [&] {
+#pragma unroll
+        for (int q = 0; q < SUMS; ++q) {
+            vs[p + q * PARTS][t] = v[q];
+            v[q] = 0.f;
+        }
+    };
     auto all_parts = [&] {
         float sum = vs[0][t];
 #pragma unroll
-        for (int u = 1; u < PARTS; ++u) sum += vs[u][t];
+        for (int u = 1; u < GROUPS; ++u) sum += vs[u][t];
         return sum;
     };
     // rows [first, last) of the head, whose statistics start at entry first - base of the tables
     auto vote = [&](int first, int last, int base) {
-#pragma unroll 8
-        for (int r = first + p; r < last; r += PARTS) v += expf(lh[(long)r * N] - s_max[r - base]) * s_inv[r - base];
+        auto add = [&](int r, float &sum) { sum += expf(lh[(long)r * pitch] - s_max[r - base]) * s_inv[r - base]; };
+        int r = first + p;
+        if (SUMS > 1) {
+#pragma unroll U
+            for (; r + (SUMS - 1) * PARTS < last; r += GROUPS)
+#pragma unroll
+                for (int q = 0; q < SUMS; ++q) add(r + q * PARTS, v[q]);
+            if (r < last) add(r, v[0]);
+        } else {
+#pragma unroll U
+            for (; r < last; r += PARTS) add(r, v[0]);
+        }
     };
     for (int base = 0; base < R; base += kVoteRows) {
         const int rows = min(kVoteRows, R - base);
@@ -274,8 +295,7 @@ __global__ __launch_bounds__(KEYS * PARTS) void gemm_votes_kernel(
         for (int g = base / w; g <= (base + rows - 1) / w; ++g) {
             vote(max(base, g * w), min(base + rows, (g + 1) * w), base);
             if ((g + 1) * w > base + rows) break;   // the head goes on in the next batch
-            vs[p][t] = v;
-            v = 0.f;
+            put_parts();
             __syncthreads();
             const float sum = all_parts();
             __syncthreads();
@@ -290,7 +310,7 @@ __global__ __launch_bounds__(KEYS * PARTS) void gemm_votes_kernel(
         }
     }
     if (pool_mode == 0) {
-        vs[p][t] = v;
+        put_parts();
         __syncthreads();
         const float sum = all_parts();
         __syncthreads();
@@ -327,22 +347,6 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const float *__restrict
         merge_exp(m, z, m2, z2);
     }
     if (sub == 0 && row < rows) stat[row] = make_float2(m, z);
-}
-
-// The same for wide pooling windows, which take the separate votes and pooling kernels.
-__global__ __launch_bounds__(256) void merge_part_kernel(const float *__restrict__ part, int chunks, int R, int rows,
-                                                         float *__restrict__ row_max, float *__restrict__ row_sum)
-{
-    const int row = blockIdx.x * 256 + threadIdx.x;
-    if (row >= rows) return;
-    const int h = row / R, r = row % R;
-    float m = -INFINITY, z = 0.f;
-    for (int c = 0; c < chunks; ++c) {
-        const float *o = part + (((long)h * chunks + c) * R + r) * 2;
-        merge_exp(m, z, o[0], o[1]);
-    }
-    row_max[row] = m;
-    row_sum[row] = z;
 }
 
 // Eq. 1: E[h, a, j] = cosine of row src[h, a] of Ac and row j of Kc, -inf where j is the source itself
@@ -433,12 +437,30 @@ int gemm_chunk_keys(int Hkv, int rows, int N)
 
 }  // namespace
 
-GemmScorePlan gemm_score_plan(int Hkv, int rows, int N)
+// A softmax sum depends in its last bits on where the keys are cut, so a batch cuts them as one of its layers
+// alone would and gives a workgroup several chunks (whole pass, us, cut by all heads / by a layer's: 8 layers of 8
+// fp32 heads x 4096 keys 262 / 267, 32 of 4 bf16 heads x 4096 with 448 rows 812 / 836, 8 x 4 x 2048 129 / 136).
+// trim: keep the prefix keys' logits only, for a buffer that all of them do not fit (rows that are a power of two
+// apart or not: 241 us trimmed / 249 whole for 256 rows x 32768 keys, 69 / 67 for 448 x 8192).  From 32 MiB of a
+// layer's logits on there are no more chunks than hold the statistics within what the scalar kernels would need
+// for their votes (4 P / w bytes a row) and the logits of the window's own keys (4 w): trimmed, this route
+// then fits every buffer that route fits.
+GemmScorePlan gemm_score_plan(int Hkv, int layer_heads, int G, int w, int N, bool trim)
 {
     GemmScorePlan pl;
-    pl.chunk_keys = gemm_chunk_keys(Hkv, rows, N);
-    pl.chunks = (N + pl.chunk_keys - 1) / pl.chunk_keys;
-    pl.part_bytes = (size_t)Hkv * rows * pl.chunks * 2 * sizeof(float);
+    const int rows = G * w, P = N - w;
+    int ck = gemm_chunk_keys(layer_heads, rows, N);
+    if ((long)layer_heads * rows * N >= (8L << 20)) {
+        const int most = max(1, w / 2 + P / (2 * w) - 2), tile = row_blocks(rows) == 1 ? Shape<1>::TK : Shape<4>::TK;
+        const int least = (N + most - 1) / most;
+        if (ck < least) ck = (least + tile - 1) / tile * tile;
+    }
+    pl.chunk_keys = ck;
+    pl.chunks = (N + ck - 1) / ck;
+    pl.per_wg = max(1, gemm_chunk_keys(Hkv, rows, N) / ck);
+    pl.pitch = trim ? P : N;
+    // (a single chunk's statistics are the rows')
+    pl.part_bytes = pl.chunks > 1 ? (size_t)Hkv * rows * pl.chunks * 2 * sizeof(float) : 0;
     return pl;
 }
 
@@ -449,10 +471,13 @@ static void launch_logits_t(const T *K, const T *Q, int Hkv, int R, int d, int N
                             const GemmScorePlan &pl, float *logits, float *part, hipStream_t st)
 {
     const int nb = row_blocks(R);
-    const dim3 grid(pl.chunks, Hkv, (R + 32 * nb - 1) / (32 * nb));
+    const dim3 grid((pl.chunks + pl.per_wg - 1) / pl.per_wg, Hkv, (R + 32 * nb - 1) / (32 * nb));
 #define GKV_LOGITS(NB)                                                                                             \
-    hipLaunchKernelGGL((gemm_logits_kernel<T, NB>), grid, dim3(256), 0, st, K, Q, d, N, P, w, R, scale, pl.chunk_keys, \
-                       logits, part)
+    do {                                                                                                           \
+        auto *kernel = pl.per_wg > 1 ? gemm_logits_kernel<T, NB, true> : gemm_logits_kernel<T, NB, false>;         \
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, K, Q, d, N, P, w, R, scale, pl.chunk_keys, pl.chunks,   \
+                           pl.per_wg, pl.pitch, logits, part);                                                     \
+    } while (0)
     if (nb == 1) GKV_LOGITS(1);
     else if (nb == 2) GKV_LOGITS(2);
     else GKV_LOGITS(4);
@@ -460,10 +485,9 @@ static void launch_logits_t(const T *K, const T *Q, int Hkv, int R, int d, int N
 }
 
 hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d, int N, int w,
-                              float scale, float *logits, float *part, hipStream_t st)
+                              float scale, const GemmScorePlan &pl, float *logits, float *part, hipStream_t st)
 {
     const int R = Hq / Hkv * w, P = N - w;
-    const GemmScorePlan pl = gemm_score_plan(Hkv, R, N);
     if (dtype == 0) launch_logits_t((const float *)Kc, (const float *)Qw, Hkv, R, d, N, P, w, scale, pl, logits, part, st);
     else launch_logits_t((const uint16_t *)Kc, (const uint16_t *)Qw, Hkv, R, d, N, P, w, scale, pl, logits, part, st);
     return hipGetLastError();
@@ -471,38 +495,32 @@ hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv
 
 // From 8192 (row, chunk) pairs a head on (us, merged by every votes workgroup / first: 128 rows x 128 chunks
 // 39.7 / 26.6, 128 x 64 18.0 / 17.1, 128 x 32 14.9 / 19.4, 16 x 64 14.3 / 16.5).
-bool gemm_merges_first(int Hkv, int rows, int N) { return (long)gemm_score_plan(Hkv, rows, N).chunks * rows >= 8192; }
+bool gemm_merges_first(const GemmScorePlan &pl, int rows) { return pl.chunks > 1 && (long)pl.chunks * rows >= 8192; }
 
-hipError_t launch_gemm_merge(const float *part, int Hkv, int Hq, int N, int w, float *stat, hipStream_t st)
-{
-    const int R = Hq / Hkv * w, rows = Hq * w;
-    hipLaunchKernelGGL(merge_rows_kernel, dim3((rows + 15) / 16), dim3(256), 0, st, part,
-                       gemm_score_plan(Hkv, R, N).chunks, R, rows, (float2 *)stat);
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_votes(const float *logits, const float *part, int chunks, int Hkv, int Hq, int N, int w,
-                             int pool_kernel, int pool_mode, float *scores, hipStream_t st)
-{
-    const int G = Hq / Hkv, P = N - w, half = (pool_kernel - 1) / 2;
-#define GKV_VOTES(KEYS, PARTS)                                                                                     \
-    hipLaunchKernelGGL((gemm_votes_kernel<KEYS, PARTS>), dim3((P + KEYS - 2 * half - 1) / (KEYS - 2 * half), Hkv), \
-                       dim3(KEYS * PARTS), 0, st, logits, part, chunks, N, P, w, G, half, pool_mode, scores)
-    // few query rows: half-size workgroups; few keys: narrower ones, to reach all compute units
-    if (G * w <= 32) GKV_VOTES(256, 2);
-    else if ((long)Hkv * P <= 40000) GKV_VOTES(128, 8);
-    else GKV_VOTES(256, 4);
-#undef GKV_VOTES
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_part(const float *part, int Hkv, int Hq, int N, int w, float *row_max, float *row_sum,
+hipError_t launch_gemm_merge(const float *part, const GemmScorePlan &pl, int Hkv, int Hq, int w, float *stat,
                              hipStream_t st)
 {
     const int R = Hq / Hkv * w, rows = Hq * w;
-    const GemmScorePlan pl = gemm_score_plan(Hkv, R, N);
-    hipLaunchKernelGGL(merge_part_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, part, pl.chunks, R, rows, row_max,
-                       row_sum);
+    hipLaunchKernelGGL(merge_rows_kernel, dim3((rows + 15) / 16), dim3(256), 0, st, part, pl.chunks, R, rows,
+                       (float2 *)stat);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_votes(const float *logits, const GemmScorePlan &pl, const float *part, int chunks, int Hkv,
+                             int layer_heads, int Hq, int N, int w, int pool_kernel, int pool_mode, float *scores,
+                             hipStream_t st)
+{
+    const int G = Hq / Hkv, P = N - w, half = (pool_kernel - 1) / 2;
+#define GKV_VOTES(KEYS, PARTS, SUMS)                                                                               \
+    hipLaunchKernelGGL((gemm_votes_kernel<KEYS, PARTS, SUMS>), dim3((P + KEYS - 2 * half - 1) / (KEYS - 2 * half), Hkv), \
+                       dim3(KEYS * PARTS), 0, st, logits, pl.pitch, part, chunks, P, w, G, half, pool_mode, scores)
+    // few query rows: half-size workgroups; few keys: narrower ones, to reach all compute units.  The order of a
+    // key's additions goes by the layer's keys, so that a batch gives the same bits.
+    if (G * w <= 32) GKV_VOTES(256, 2, 1);
+    else if ((long)layer_heads * P > 40000) GKV_VOTES(256, 4, 1);
+    else if ((long)Hkv * P > 40000) GKV_VOTES(256, 4, 2);   // (a batch; as 128 x 8: 136 -> 144 us in the last case above)
+    else GKV_VOTES(128, 8, 1);
+#undef GKV_VOTES
     return hipGetLastError();
 }
 

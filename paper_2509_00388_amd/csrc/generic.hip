@@ -63,18 +63,19 @@ __global__ __launch_bounds__(256) void generic_logits_kernel(
     if (threadIdx.x == 0) { row_max[row] = mx; row_sum[row] = z; }
 }
 
-// votes[q, j] = sum over window rows r of exp(l_rj - max_r) / sum_r, j < P.
+// votes[q, j] = sum over window rows r of exp(l_rj - max_r) / sum_r, j < P.  A row of logits has `pitch`
+// entries, the statistics of consecutive rows are `step` apart.
 __global__ __launch_bounds__(256) void generic_votes_kernel(
-    const float *__restrict__ logits, const float *__restrict__ row_max,
-    const float *__restrict__ row_sum, int N, int w, float *__restrict__ votes)
+    const float *__restrict__ logits, int pitch, const float *__restrict__ row_max,
+    const float *__restrict__ row_sum, int step, int P, int w, float *__restrict__ votes)
 {
-    const int q = blockIdx.y, P = N - w;
+    const int q = blockIdx.y;
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= P) return;
     float acc = 0.f;
     for (int r = 0; r < w; ++r) {
         const int row = q * w + r;
-        acc += expf(logits[(long)row * N + j] - row_max[row]) / row_sum[row];
+        acc += expf(logits[(long)row * pitch + j] - row_max[(long)row * step]) / row_sum[(long)row * step];
     }
     votes[(long)q * P + j] = acc;
 }
@@ -210,12 +211,11 @@ hipError_t launch_generic_logits(const void *Kc, const void *Qw, int dtype, int 
     return hipGetLastError();
 }
 
-hipError_t launch_generic_votes(const float *logits, const float *row_max, const float *row_sum,
-                                int Hq, int N, int w, float *votes, hipStream_t st)
+hipError_t launch_generic_votes(const float *logits, int pitch, const float *row_max, const float *row_sum, int step,
+                                int Hq, int P, int w, float *votes, hipStream_t st)
 {
-    const int P = N - w;
-    hipLaunchKernelGGL(generic_votes_kernel, dim3((P + 255) / 256, Hq), dim3(256), 0, st, logits,
-                       row_max, row_sum, N, w, votes);
+    hipLaunchKernelGGL(generic_votes_kernel, dim3((P + 255) / 256, Hq), dim3(256), 0, st, logits, pitch, row_max,
+                       row_sum, step, P, w, votes);
     return hipGetLastError();
 }
 

@@ -46,9 +46,9 @@ hipError_t launch_redo_rows(const void *Ac, const void *Kc, int heads, int N, in
 hipError_t launch_generic_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d,
                                  int N, int w, float scale, float *logits, float *row_max,
                                  float *row_sum, hipStream_t st);
-// votes [Hq, P]: softmax weights summed over the window rows.
-hipError_t launch_generic_votes(const float *logits, const float *row_max, const float *row_sum,
-                                int Hq, int N, int w, float *votes, hipStream_t st);
+// votes [Hq, P]: softmax weights summed over the window rows; rows of `pitch` logits, row statistics `step` apart.
+hipError_t launch_generic_votes(const float *logits, int pitch, const float *row_max, const float *row_sum, int step,
+                                int Hq, int P, int w, float *votes, hipStream_t st);
 // E [Hkv, S, P] cosine of row src[h,a] of Ac against every prefix row of Kc; self = -inf.
 // (Eq. 1: Ac = Kc = keys; other pairings of tensors give the Discussion's other edges.)
 hipError_t launch_generic_cosine(const void *Ac, const void *Kc, int dtype, int Hkv, int d, int N, int P, int S,
@@ -59,23 +59,26 @@ hipError_t launch_knorm(const void *Kc, int dtype, int Hkv, int d, int N, int P,
 
 // ---- the same contractions on the matrix cores, any dtype / shape (gemm.hip) ----------
 struct GemmScorePlan {
-    int chunk_keys, chunks;   // keys per workgroup, workgroups per head and row group
-    size_t part_bytes;        // bytes of per-chunk row statistics
+    int chunk_keys, chunks;   // keys per chunk, chunks per head of the row statistics
+    int per_wg;               // chunks a workgroup takes
+    int pitch;                // logits kept per row
+    size_t part_bytes;        // bytes of per-chunk row statistics, 0 for a single chunk
 };
-GemmScorePlan gemm_score_plan(int Hkv, int rows, int N);   // rows: stacked query rows per KV head
-// logits [Hq*w, N] (fp32, scaled) and part [Hkv, chunks, G*w] (max, sum of exp) over visible keys.
+// Hkv: heads of the launch; layer_heads: KV heads of one of its layers.
+GemmScorePlan gemm_score_plan(int Hkv, int layer_heads, int G, int w, int N, bool trim);
+// logits [Hq*w, pitch] (fp32, scaled) and part [Hkv, chunks, G*w] (max, sum of exp) over visible keys.
 hipError_t launch_gemm_logits(const void *Kc, const void *Qw, int dtype, int Hkv, int Hq, int d, int N, int w,
-                              float scale, float *logits, float *part, hipStream_t st);
+                              float scale, const GemmScorePlan &pl, float *logits, float *part, hipStream_t st);
 // scores [Hkv, P] from logits and the row statistics of `chunks` chunks, votes, pooling and the mean over
-// the group included (gemm_votes_pools(pool_kernel)); wider pooling windows take launch_merge_part (row
-// statistics as launch_generic_logits leaves them), launch_generic_votes and launch_pool_group.  With many
-// chunks (gemm_merges_first) launch_gemm_merge makes one chunk of them first: stat [Hq*w] (max, sum).
+// the group included (gemm_votes_pools(pool_kernel)).  launch_gemm_merge makes one chunk of many, stat
+// [Hq*w] (max, sum): in front of it where there are many (gemm_merges_first), and in front of
+// launch_generic_votes and launch_pool_group, which wider pooling windows take.
 bool gemm_votes_pools(int pool_kernel);
-bool gemm_merges_first(int Hkv, int rows, int N);
-hipError_t launch_gemm_merge(const float *part, int Hkv, int Hq, int N, int w, float *stat, hipStream_t st);
-hipError_t launch_gemm_votes(const float *logits, const float *part, int chunks, int Hkv, int Hq, int N, int w,
-                             int pool_kernel, int pool_mode, float *scores, hipStream_t st);
-hipError_t launch_merge_part(const float *part, int Hkv, int Hq, int N, int w, float *row_max, float *row_sum,
+bool gemm_merges_first(const GemmScorePlan &pl, int rows);   // rows: stacked query rows per KV head
+hipError_t launch_gemm_merge(const float *part, const GemmScorePlan &pl, int Hkv, int Hq, int w, float *stat,
+                             hipStream_t st);
+hipError_t launch_gemm_votes(const float *logits, const GemmScorePlan &pl, const float *part, int chunks, int Hkv,
+                             int layer_heads, int Hq, int N, int w, int pool_kernel, int pool_mode, float *scores,
                              hipStream_t st);
 // Same contract as launch_generic_cosine.
 hipError_t launch_gemm_cosine(const void *Ac, const void *Kc, int dtype, int Hkv, int d, int N, int P, int S,

@@ -1355,3 +1355,19 @@ def test_batched_scores_equal_per_layer(L, H, G, w, N, mode):
     sc, idx, layers = batched_and_per_layer(p, L, N + L)
     for l, (s_l, i_l) in enumerate(layers):
         assert np.array_equal(sc[l], s_l) and np.array_equal(idx[l], i_l), f"layer {l}"
+
+
+@pytest.mark.parametrize("dtype,d,L,H,G,w,N,pool,mode", [
+    ("fp32", 128, 6, 8, 4, 32, 4096, 7, 0), ("fp32", 64, 9, 4, 1, 16, 1500, 5, 0), ("bf16", 64, 12, 8, 2, 20, 3001, 7, 1),
+    ("bf16", 64, 5, 16, 1, 32, 8192, 7, 0), ("bf16", 128, 6, 4, 7, 64, 5000, 7, 0), ("bf16", 128, 4, 2, 3, 20, 9000, 13, 1),
+    ("fp32", 80, 33, 2, 2, 48, 700, 67, 0), ("bf16", 256, 7, 4, 9, 70, 1100, 5, 1), ("fp32", 128, 64, 1, 1, 9, 260, 131, 1)])
+def test_batched_scores_equal_per_layer_any_type(dtype, d, L, H, G, w, N, pool, mode):
+    """The same for everything the streaming kernels do not take, at any size: one to many chunks per
+    workgroup, statistics merged beforehand or not, narrow and wide pooling windows."""
+    say(f"batched scores {dtype} d={d} L={L} H={H} G={G} w={w} N={N} pool={pool}/{mode}")
+    p = gk.Params(n_kv_heads=H, n_q_heads=H * G, head_dim=d, n_tokens=N, window=w, pool_kernel=pool, pool_mode=mode,
+                  budget=w + 60, n_sources=8, n_neighbors=5, rounds=1, dtype=gk.FP32 if dtype == "fp32" else gk.BF16)
+    assert not gk.graphkv_uses_mfma(p)
+    sc, idx, layers = batched_and_per_layer(p, L, N + d)
+    for l, (s_l, i_l) in enumerate(layers):
+        assert np.array_equal(sc[l], s_l) and np.array_equal(idx[l], i_l), f"layer {l}"

@@ -83,3 +83,26 @@ def test_static_scratch_entry_falls_back_to_the_dense_block():
     torch.cuda.synchronize()
     assert torch.equal(got[2], want[2]) and torch.equal(got[3], want[3])
     assert torch.equal(got[0].view(torch.int16), want[0].view(torch.int16))
+
+
+@pytest.mark.parametrize("H,G,w,P,pool", [(8, 1, 128, 15892, 7), (2, 4, 128, 16056, 7), (1, 4, 181, 22640, 7), (4, 2, 64, 31500, 131)])
+def test_static_scratch_entry_with_logits_that_nearly_fill_it(H, G, w, P, pool):
+    """fp32 logits of 61 to 63 MiB: what the row statistics need beside them must not push the call to kernels
+    that add up in another order.  Same bytes as the workspace entry."""
+    p = gk.Params(n_kv_heads=H, n_q_heads=H * G, head_dim=64, n_tokens=P + w, window=w, pool_kernel=pool, budget=w + 500,
+                  n_sources=8, n_neighbors=8, rounds=1, dtype=gk.FP32)
+    assert 4 * H * G * w * P > 60 << 20
+    g = torch.Generator("cuda").manual_seed(P)
+    dev = [torch.randn(h, n, 64, generator=g, device="cuda") for h, n in ((H, P + w), (H, P + w), (H * G, w))]
+    print(f"static-scratch call H={H} G={G} w={w} P={P}", flush=True)
+
+    def outs():
+        return [torch.empty(H, p.budget, 64, device="cuda"), torch.empty(H, p.budget, 64, device="cuda"),
+                torch.empty(H, p.budget, dtype=torch.int32, device="cuda"), torch.empty(H, P, device="cuda")]
+
+    want, got = outs(), outs()
+    gk.graphkv_compress(p, *dev, want[0], want[1], want[2], scores_out=want[3])
+    gk.graphkv_compress_static(p, *dev, got[0], got[1], got[2], scores_out=got[3])
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
