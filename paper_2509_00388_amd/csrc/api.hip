@@ -41,11 +41,15 @@ void *static_scratch()
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
+// Ways with less scratch, for a buffer that the ordinary one does not fit; the results are the same.
+// kLess: no logits of the window's own keys, short candidate slices; kDense: also no filter route below 8192 nodes.
+enum Scratch { kOrdinary, kLess, kDense };
+
 // H and Hq count the heads of the whole batch (layers x heads per layer).
 struct Dims {
     int L, H, Hq, G, d, N, w, P, B, S, m, T;
     int Hl;              // KV heads of one layer
-    bool frugal;         // the least scratch (dims_of)
+    Scratch scratch;     // how much scratch may be spent
     bool gemm;           // contractions the kernels for bf16 and d = 128 do not cover run in gemm.hip
     bool mfma_score, mfma_cosine, filter;
     bool speculate;      // speculative rows allowed (dropped when their scratch would not fit)
@@ -125,10 +129,8 @@ bool budget_ok(const graphkv_params *p)
 
 // `like`: the dimensions of the call's full launch group, whose routes a smaller last group takes
 // too (so that the workspace sized for the full group is enough).
-// frugal: the least scratch (no filter route below 8192 nodes, no logits of the window's own keys), for a buffer
-// that the faster way does not fit; the results are the same.
 Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, const Dims *like = nullptr,
-             bool frugal = false)
+             Scratch scratch = kOrdinary)
 {
     Dims D;
     D.L = n_layers;
@@ -144,18 +146,18 @@ Dims dims_of(const graphkv_params *p, int n_layers = 1, bool speculate = true, c
     D.S = p->rounds > 0 ? p->n_sources : 0;
     D.m = p->rounds > 0 ? p->n_neighbors : 0;
     D.T = p->rounds;
-    D.frugal = frugal;
+    D.scratch = scratch;
     D.gemm = p->impl == GRAPHKV_IMPL_AUTO;
     D.mfma_score = mfma_score_ok(p);
     D.mfma_cosine = mfma_cosine_ok(p);
-    D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && (!frugal || D.P >= 8192) &&
+    D.filter = like ? like->filter : D.mfma_cosine && D.T > 0 && (scratch != kDense || D.P >= 8192) &&
                                          mfma_filter_applies(D.P, D.m, (long)D.H * D.S);
     if (like) speculate = like->speculate;
     // The neighbourhood of a source depends on the keys alone (Eq. 1, Eq. 3), not on the
     // scores: with re-picked sources the lists of returning sources are kept.
     D.speculate = speculate;
     D.keep = D.filter && D.T > 1 && p->reselect && source_reuse_applies(D.S);
-    D.fp = D.filter ? mfma_filter_plan(D.H, D.P, D.S, D.m, D.keep, speculate) : MfmaFilterPlan{};
+    D.fp = D.filter ? mfma_filter_plan(D.H, D.P, D.S, D.m, D.keep, speculate, scratch != kOrdinary) : MfmaFilterPlan{};
     D.scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)D.d);
     D.esize = p->dtype == GRAPHKV_FP32 ? 4 : 2;
     return D;
@@ -181,7 +183,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
         W.votes = take(scoring && !votes_stay_in_lds ? (size_t)D.H * mfma_score_vote_rows(D.G, D.w, per_q) * D.P * 4 : 0);
         W.part = take(mfma_score_plan(D.H, D.Hl, D.G, D.w, D.N, per_q).part_bytes);
     } else if (D.gemm) {
-        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.frugal);
+        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.scratch != kOrdinary);
         const size_t part = scoring ? pl.part_bytes : 0;
         const size_t votes = scoring && !gemm_votes_pools(p->pool_kernel) ? (size_t)D.Hq * D.P * 4 : 0;
         W.logits = take(scoring ? rows * pl.pitch * 4 : 0);
@@ -310,7 +312,7 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
     }
     float *logits = at<float>(ws, W.logits), *row_max = at<float>(ws, W.row_max), *row_sum = at<float>(ws, W.row_sum);
     if (D.gemm) {
-        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.frugal);
+        const GemmScorePlan pl = gemm_score_plan(D.H, D.Hl, D.G, D.w, D.N, D.scratch != kOrdinary);
         const bool pools = gemm_votes_pools(p->pool_kernel);
         float *stat = row_max;   // (max, sum) pairs; a single chunk's statistics go there at once
         float *part = pl.chunks > 1 ? at<float>(ws, W.part) : stat;
@@ -535,7 +537,7 @@ constexpr size_t kGroupScratchCap = (size_t)2000 << 20;
 // beats a larger one without (later rounds then stream no keys again), as long as the group
 // still has 64 heads or more to fill the chip with; below that they are dropped before a
 // group is made smaller still.
-Dims group_dims(const graphkv_params *p, int n_layers, bool frugal = false)
+Dims group_dims(const graphkv_params *p, int n_layers, Scratch scratch = kOrdinary)
 {
     const int g0 = n_layers < kMaxLayers ? n_layers : kMaxLayers;
     for (int speculate = 1; speculate >= 0; --speculate) {
@@ -543,13 +545,13 @@ Dims group_dims(const graphkv_params *p, int n_layers, bool frugal = false)
             const bool fits_heads = (long)p->n_kv_heads * g <= 65535;
             if (speculate && g < g0 && (long)p->n_kv_heads * g < 64) break;
             if (fits_heads) {
-                const Dims D = dims_of(p, g, speculate != 0, nullptr, frugal);
+                const Dims D = dims_of(p, g, speculate != 0, nullptr, scratch);
                 if (carve(p, D).total <= kGroupScratchCap) return D;
             }
             if (g == 1) break;
         }
     }
-    return dims_of(p, 1, false, nullptr, frugal);
+    return dims_of(p, 1, false, nullptr, scratch);
 }
 
 // Scratch of a call: its full group's, or its smaller last group's should that need more.
@@ -692,14 +694,11 @@ int32_t graphkv_compress(const graphkv_params *p, const void *Kc, const void *Vc
 int32_t graphkv_compress_static(const graphkv_params *p, const void *Kc, const void *Vc, const void *Qw,
                                 void *Kout, void *Vout, int32_t *idx, float *scores_out, void *stream)
 {
-    const size_t need = graphkv_workspace_bytes(p);   // 0: invalid params
-    if (need == 0) return GRAPHKV_EINVAL;
+    if (!base_ok(p)) return GRAPHKV_EINVAL;
     Dims D = group_dims(p, 1);
-    if (need > kStaticScratchBytes) {
-        // (a short prompt with many heads may still fit with its dense edge block, logits without the window's)
-        D = group_dims(p, 1, true);
-        if (scratch_bytes(p, 1, D) > kStaticScratchBytes) return GRAPHKV_ESCRATCH;
-    }
+    for (const Scratch way : {kLess, kDense})
+        if (scratch_bytes(p, 1, D) > kStaticScratchBytes) D = group_dims(p, 1, way);
+    if (scratch_bytes(p, 1, D) > kStaticScratchBytes) return GRAPHKV_ESCRATCH;
     // (the pointer checks of the call below come before the address is resolved)
     if (!aligned16(Kc) || !aligned16(Vc) || !aligned16(Kout) || !aligned16(Vout) || !aligned4(idx))
         return GRAPHKV_EINVAL;

@@ -163,7 +163,8 @@ struct MfmaFilterPlan {
     int slice_cap;    // entries per (row, chunk) slice
     int cand_cap;     // entries the exact select can take per row
 };
-MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, bool speculate);
+// short_slices: no more memory for candidates than keys in no particular order need.
+MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, bool speculate, bool short_slices);
 size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // per-chunk histograms (0 if one chunk)
 // Bound pass: tau = a value that at least m of the row's edges reach (but for about one row in
 // 10^7, which the select notices), from the edges to every (P / sample_cols)-th key; clears

@@ -1033,7 +1033,7 @@ int chunk_cols_for(int Hkv, int sgroups, int n_cols, int min_chunks = 1)
 
 }  // namespace
 
-// Keys in the strided sample of the bound pass: every 8th key, between 2048 and 8192 keys (one
+// Most keys in the strided sample of the bound pass: every 8th key, between 2048 and 8192 keys (one
 // workgroup walks the whole sample of a head's sources).  A denser sample costs the bound pass
 // more and gives a tighter bound, i.e. fewer candidates for the filter pass to park and list
 // (measured at 131008 keys and m = 128: 8192 sampled keys 10.2 ms per 32-layer pass, 16384 keys
@@ -1056,6 +1056,17 @@ static int late_sample_cols(int P)
     return P > 131072 ? ps : (ps / 2 > 2048 ? ps / 2 : 2048);
 }
 
+// The sample: every stride-th key of the whole row, at most `most` of them.  (The stride rounded down would
+// leave up to half of the row's end out, and a source whose near keys sit there -- neighbours in position, as
+// rotary position codes make them -- gets a bound far too low: lists overflow and heads are redone row by
+// row.  One round of 40 heads x 72 sources x 4064 keys in runs of 250 alike: 562 us, 181 with the whole row sampled.)
+struct Sample { int stride, cols; };
+static Sample sample_of(int P, int most)
+{
+    const int stride = (P + most - 1) / most;
+    return {stride, (P + stride - 1) / stride};
+}
+
 // Rank of the sampled edge that the bound is taken at.  The bound is useful for a source when at
 // least m of its edges lie above it, i.e. when fewer than `rank` of its m - 1 largest edges fell
 // into the sample.  With every stride-th key sampled that count is binomial, (m - 1) trials at
@@ -1073,8 +1084,8 @@ int mfma_bound_rank(int m, int stride)
 
 int mfma_cand_cap(int P, int m)
 {
-    // four times the rank * stride keys expected above the bound (the bin that the bound is
-    // rounded down to adds up to a few hundred more at long prompts)
+    // about four times the rank * stride keys expected above the bound (the bin that the bound is
+    // rounded down to adds up to a few hundred more at long prompts; here the stride is rounded down)
     const int stride = P / mfma_sample_cols(P);
     long cap = 4L * mfma_bound_rank(m, stride) * stride;
     if (cap < 1024) cap = 1024;
@@ -1105,7 +1116,8 @@ bool source_reuse_applies(int S) { return S <= 4096; }   // the previous list an
 // source list still fits the small-k source selection; their workgroups then carry three
 // 32-row groups.  Key chunks per head and the capacity of one (row, chunk) slice: four times
 // the expected share of a chunk, at least 2 m (and 64) entries.
-MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, bool speculate)
+MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, bool speculate,
+                                bool short_slices)
 {
     MfmaFilterPlan g{};
     g.S = S;
@@ -1135,6 +1147,10 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
     long sc = 4L * share + 2L * m;
     if (sc < 64) sc = 64;
     g.cand_cap = mfma_cand_cap(P, m);
+    // Short prompts: a row's slices may take what its row of the dense edge block would (whole 128-byte lines),
+    // which holds most lists whose entries all sit in one chunk (the round above: 181 -> 94 us, in runs of 1000
+    // alike 568 -> 97; keys in random order take 92 either way).
+    if (P < 8192 && !short_slices && sc < P / (2 * g.chunks)) sc = P / (2 * g.chunks) / 16 * 16;
     if (sc > g.cand_cap) sc = g.cand_cap;
     g.slice_cap = (int)sc;
     return g;
@@ -1176,15 +1192,15 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
                         int row0, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
-    const int ps = late ? late_sample_cols(P) : mfma_sample_cols(P), stride = P / ps;
+    const Sample smp = sample_of(P, late ? late_sample_cols(P) : mfma_sample_cols(P));
     const int sgroups = (rows + ROWS - 1) / ROWS;
     const int chunks = late ? 1 : bound_chunks(Hkv, P, sgroups);
-    const int chunk_cols = (((ps + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
-    const int rank = mfma_bound_rank(m, stride);
+    const int chunk_cols = (((smp.cols + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
+    const int rank = mfma_bound_rank(m, smp.stride);
     if (!allow_big_lds((const void *)cosine_bound_kernel<SB, BINS>)) return hipGetLastError();
     hipLaunchKernelGGL((cosine_bound_kernel<SB, BINS>), dim3(sgroups, Hkv, chunks), dim3(256 * SB),
-                       2 * kTileBytes + ROWS * BINS * 4, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, ps,
-                       stride, rows, src_pitch, src, n_src, rank, chunk_cols, (uint32_t *)hist_part, tau, pitch, row0,
+                       2 * kTileBytes + ROWS * BINS * 4, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols,
+                       smp.stride, rows, src_pitch, src, n_src, rank, chunk_cols, (uint32_t *)hist_part, tau, pitch, row0,
                        overflow);
     if (chunks > 1)
         hipLaunchKernelGGL((bound_merge_kernel<SB, BINS>), dim3((rows + 3) / 4, Hkv), dim3(256), 0, st,
@@ -1199,7 +1215,7 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    const int stride = P / (late ? late_sample_cols(P) : mfma_sample_cols(P));
+    const int stride = sample_of(P, late ? late_sample_cols(P) : mfma_sample_cols(P)).stride;
     // Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
     // per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
     // rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a

@@ -1371,3 +1371,41 @@ def test_batched_scores_equal_per_layer_any_type(dtype, d, L, H, G, w, N, pool, 
     sc, idx, layers = batched_and_per_layer(p, L, N + d)
     for l, (s_l, i_l) in enumerate(layers):
         assert np.array_equal(sc[l], s_l) and np.array_equal(idx[l], i_l), f"layer {l}"
+
+
+@pytest.mark.parametrize("P,H,m,run", [(4064, 40, 32, 1000), (3000, 64, 32, 1000), (7968, 32, 32, 200), (6000, 64, 64, 500)])
+def test_short_prompts_whose_similar_keys_are_neighbours(P, H, m, run):
+    """The filter route on short prompts made of runs of similar keys, so that a source's neighbours all sit in
+    one stretch of the row: the sample has to cover the whole row and a slice to take a whole list, or every
+    head is redone row by row (0.5 to 1 ms here, against 6 us for a launch that finds nothing to redo, which
+    the same keys in random order give).  Same bytes as the dense route of fewer heads."""
+    say(f"runs of similar keys P={P} H={H} m={m} run={run}")
+    w, S, d = 32, 72, 128
+    N = P + w
+    g = torch.Generator("cuda").manual_seed(P)
+    centre = torch.randn(H, (N + run - 1) // run, d, generator=g, device="cuda")
+    K = centre.repeat_interleave(run, dim=1)[:, :N] + torch.randn(H, N, d, generator=g, device="cuda")
+    K = K.to(torch.bfloat16).contiguous()
+    s0 = torch.rand(H, P, generator=g, device="cuda")
+    order = torch.randperm(P, generator=g, device="cuda")
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=w + 1, n_sources=S, n_neighbors=m,
+                  rounds=1, dtype=gk.BF16)
+    assert 8 * S * P < 1 << 23 <= H * S * P
+
+    def redo_ms(k, s):
+        best = np.inf
+        for _ in range(3):
+            gk.graphkv_profile_begin()
+            gk.graphkv_propagate(p, k, s.clone())
+            torch.cuda.synchronize()
+            best = min(best, gk.graphkv_profile_end()["redo_rows"][0])
+        return best
+
+    shuffled = redo_ms(torch.cat([K[:, order], K[:, P:]], dim=1).contiguous(), s0[:, order].contiguous())
+    in_runs = redo_ms(K, s0)
+    assert in_runs < 3 * shuffled + 0.05, f"redo {in_runs:.3f} ms, shuffled {shuffled:.3f} ms"
+    s1, src, nbr, ev = run_propagate(p, K, s0.cpu().numpy())
+    few = gk.Params(**{**p.__dict__, "n_kv_heads": 8, "n_q_heads": 8})
+    s8, src8, nbr8, ev8 = run_propagate(few, K[:8].contiguous(), s0[:8].cpu().numpy())
+    assert np.array_equal(src[0, :8], src8[0]) and np.array_equal(nbr[0, :8], nbr8[0])
+    assert np.array_equal(ev[0, :8], ev8[0]) and np.array_equal(s1[:8], s8)
