@@ -122,6 +122,13 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(v), 63);
 }
+// LDS words that other lanes of the wave wrote before it are read after it: a wave's LDS operations complete in
+// order, so it costs nothing, but without the fence the compiler may move them.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // Number of lanes below this one whose bit is set in a wave vote.
 __device__ __forceinline__ uint32_t votes_below(uint64_t votes)
 {

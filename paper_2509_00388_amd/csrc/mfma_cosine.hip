@@ -888,9 +888,9 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
             // many: marks, a running maximum
             start_s[lane] = (uint32_t)(incl - cnt);
             for (int it = 0; it < n_it; ++it) mark_s[it * 64 + lane] = 0;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             if (cnt > 0) mark_s[incl - cnt] = (uint8_t)lane;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             uint32_t carry = 0;
 #pragma unroll
             for (int it = 0; it < R; ++it) {
@@ -966,7 +966,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
             return;
         }
         if (lane == 0 && (listed & 1)) win[listed] = ~0ull;   // (pairs are read below)
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         if (listed > m) {
             // Of the entries equal to tau only those with the lowest key indices stay: one that
             // `keep` or more tied entries precede is dropped (a dropped entry sorts behind all).
@@ -987,10 +987,10 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
                     if (before >= keep) drop |= 1u << i;
                 }
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             for (int r = lane, i = 0; r < listed; r += 64, ++i)
                 if ((drop >> i) & 1u) win[r] = ~0ull;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         }
         // each winner's rank by key index is its place in the output
         for (int r = lane; r < listed; r += 64) {
@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
                 nbr_e[out_row * m + at] = __uint_as_float((uint32_t)mine);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
 }
 
