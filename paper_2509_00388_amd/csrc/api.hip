@@ -399,8 +399,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                         lst = ext;
                     } else {
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES,
-                                   launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
-                                                    nullptr, 1, st));
+                                   launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, st));
                     }
                     GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND,
                                launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
@@ -425,8 +424,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                         update = DecayArgs{};
                     } else {
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER,
-                                   launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
-                                                    nullptr, 1, st));
+                                   launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, st));
                         GKV_LAUNCH(GRAPHKV_K_MATCH_SOURCES, launch_match_sources(match, src, D.H, st));
                     }
                     // new sources without a kept list (usually none): bound and filter passes
@@ -445,11 +443,10 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
             } else {
                 // Eq. 2: source nodes
                 GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES,
-                           launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, nullptr, 0, 0,
-                                            nullptr, 1, st));
+                           launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, st));
                 // Eq. 1: edges from every source to every node
                 if (D.mfma_cosine)
-                    GKV_LAUNCH(GRAPHKV_K_COSINE, launch_mfma_cosine(Ac, Kc, D.H, D.N, D.P, D.S, src, E, nullptr, st));
+                    GKV_LAUNCH(GRAPHKV_K_COSINE, launch_mfma_cosine(Ac, Kc, D.H, D.N, D.P, D.S, src, E, st));
                 else if (D.gemm)
                     GKV_LAUNCH(GRAPHKV_K_GENERIC_COSINE,
                                launch_gemm_cosine(Ac, Kc, p->dtype, D.H, D.d, D.N, D.P, D.S, src, E, st));
@@ -458,8 +455,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                                launch_generic_cosine(Ac, Kc, p->dtype, D.H, D.d, D.N, D.P, D.S, src, E, st));
                 // Eq. 3: neighbourhoods
                 GKV_LAUNCH(GRAPHKV_K_TOPK_NEIGHBORS,
-                           launch_topk_rows(E, D.P, D.P, D.H * D.S, D.m, nbr, D.m, ev, D.m, nullptr, 0, 0,
-                                            nullptr, 1, st));
+                           launch_topk_rows(E, D.P, D.P, D.H * D.S, D.m, nbr, D.m, ev, D.m, st));
             }
         } else {
             if (dbg_src) GKV_LAUNCH(GRAPHKV_K_COPY, launch_copy_i32(src0, dbg_src + t * n_src, (long)n_src, st));

@@ -15,21 +15,15 @@ namespace gkv {
 bool allow_big_lds(const void *kernel, int bytes = 160 * 1024 - 8192);
 
 // ---- selection (select.hip) -------------------------------------------------
-// For each of `rows` rows of x (row r starts at x + r*ld, n entries): the k
-// entries that come first by (value descending, index ascending), written in
-// ascending index order to idx_out + r*idx_ld (and their values to val_out +
-// r*val_ld when val_out != nullptr).  After the k picks, `append_count`
-// consecutive integers starting at `append_from` are appended to idx_out.
-// tau_out (optional) receives the k-th largest value of each row; idx_out may
-// then be nullptr.  gate (optional): row r is skipped when gate[r / rows_per_gate] == 0.
-hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k,
-                            int32_t *idx_out, long idx_ld, float *val_out, long val_ld,
-                            float *tau_out, int append_from, int append_count,
-                            const int32_t *gate, int rows_per_gate, hipStream_t st);
+// For each of `rows` rows of x (row r starts at x + r*ld, n entries): the k entries that come first
+// by (value descending, index ascending), written in ascending index order to idx_out + r*idx_ld
+// (and their values to val_out + r*val_ld when val_out != nullptr).
+hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int32_t *idx_out, long idx_ld,
+                            float *val_out, long val_ld, hipStream_t st);
 
 // Source nodes (Eq. 2) plus the X nodes ranked right behind them: src [rows, S] gets the S
 // best entries of each row (ascending index), ext [rows, S + X] the same S followed by the next
-// X (ascending index), by (value descending, index ascending).  4096 < n, S + X <= kMaxExtSources.
+// X (ascending index), by (value descending, index ascending).  S + X <= n, S + X <= kMaxExtSources.
 hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, int X, int32_t *src,
                                int32_t *ext, hipStream_t st);
 
@@ -136,10 +130,9 @@ bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel);
 hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, int fused_pool_kernel,
                                   const float *part, float *votes, hipStream_t st);
-// E [Hkv, S, P] from bf16 keys (same contract as launch_generic_cosine); heads with
-// gate[h] == 0 are skipped when gate != nullptr.
+// E [Hkv, S, P] from bf16 keys (same contract as launch_generic_cosine).
 hipError_t launch_mfma_cosine(const void *Ac, const void *Kc, int Hkv, int N, int P, int S, const int32_t *src,
-                              float *E, const int32_t *gate, hipStream_t st);
+                              float *E, hipStream_t st);
 // Neighbourhoods without the dense block (see mfma_cosine.hip):
 bool mfma_filter_applies(int P, int m, long rows);   // rows: heads x sources of the launch
 int mfma_sample_cols(int P);          // keys in the strided sample
@@ -152,8 +145,7 @@ constexpr int kMaxExtSources = 256;   // largest S + kSpecRows the source select
 // [Hkv, pitch, chunks, slice_cap] x 8 bytes, cand_cnt [Hkv, pitch, chunks]) hold, per head,
 // the S sources of the first round, then X speculative rows (the nodes ranked right behind the
 // sources: the likeliest new sources of later rounds, whose candidate lists the first round's
-// pass builds on the side), then fb_rows rows for new sources of later rounds that have no kept
-// list.  Without speculation (X = 0) nothing outlives a round and later rounds reuse rows 0 .. S.
+// pass builds on the side).  New sources of later rounds that have no kept list reuse rows 0 .. S - 1.
 struct MfmaFilterPlan {
     int S, X;
     int sb;           // 32-row groups per workgroup in the passes over the full source list

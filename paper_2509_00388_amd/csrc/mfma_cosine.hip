@@ -89,13 +89,10 @@ __device__ __forceinline__ void load_sources(const uint16_t *Ah, const int32_t *
     }
 }
 
-// Dense block: E[h, slot, c] = e for column c = key c * key_stride (key_stride = 1:
-// every key), -inf where the key is the source itself.  If fa.overflow is set, the first
-// workgroup of a head also clears the head's overflow flag for the filter pass that follows.
+// Dense block: E[h, slot, key] = e, -inf where the key is the source itself.
 __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride, int S,
-    const int32_t *__restrict__ src, int chunk_cols, float *__restrict__ E, FilterArgs fa,
-    const int32_t *__restrict__ gate)
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int P, int S,
+    const int32_t *__restrict__ src, int chunk_cols, float *__restrict__ E)
 {
     __shared__ float inv_s[kRows];
     __shared__ int32_t idx_s[kRows];
@@ -105,12 +102,9 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
     const int h = blockIdx.y, chunk = blockIdx.x, s_base = blockIdx.z * kRows;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv & 3, grp = wv >> 2;
-    if (gate && gate[h] == 0) return;
     const uint16_t *Kh = Kc + (long)h * N * kD;
-    const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
-    if (c0 >= n_cols) return;
-
-    if (fa.overflow && chunk == 0 && blockIdx.z == 0 && tid == 0) fa.overflow[h] = 0;
+    const int c0 = chunk * chunk_cols, c1 = min(P, c0 + chunk_cols);
+    if (c0 >= P) return;
 
     bf16x8 q[kSteps];
     load_sources(Ac + (long)h * N * kD, src + (long)h * S, S, s_base, grp, stream, l32, hh, q, inv_s, idx_s);
@@ -133,21 +127,20 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
         float sq = half_row_sumsq(kc);
         sq = add_other_half(sq);
         const float inv_k = inv_norm(sq);
-        const int col = c0 + kTileKeys * t + kBlk * stream + l32;
-        const int key = col * key_stride;
-        if (col < c1) {
+        const int key = c0 + kTileKeys * t + kBlk * stream + l32;
+        if (key < c1) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int slot = s_base + kBlk * grp + acc_row(i, hh);
                 if (slot < S) {
                     float e = (acc[i] * inv_k) * inv_src[i];
                     if (key == idx_s[kBlk * grp + acc_row(i, hh)]) e = -INFINITY;
-                    E[((long)h * S + slot) * n_cols + col] = e;
+                    E[((long)h * S + slot) * P + key] = e;
                 }
             }
         }
     };
-    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, key_stride, ntile, multiply_tile, (void)0);
+    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, multiply_tile, (void)0);
 }
 
 // Bound pass: for every source a value that at least m of its edges reach (short of about one
@@ -1157,7 +1150,7 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
 }
 
 hipError_t launch_mfma_cosine(const void *Ac, const void *Kc, int Hkv, int N, int P, int S, const int32_t *src,
-                              float *E, const int32_t *gate, hipStream_t st)
+                              float *E, hipStream_t st)
 {
     const int sgroups = (S + kRows - 1) / kRows;
     // One workgroup per compute unit while that leaves each a tile (a layer of a short prompt: 8 heads of
@@ -1166,10 +1159,9 @@ hipError_t launch_mfma_cosine(const void *Ac, const void *Kc, int Hkv, int N, in
     const long one = ((long)Hkv * sgroups * P + 255) / 256;
     if (one < 1024) ck = (int)((one + kTileKeys - 1) / kTileKeys * kTileKeys);
     const int chunks = (P + ck - 1) / ck;
-    FilterArgs fa{};
     if (!allow_big_lds((const void *)cosine_dense_kernel)) return hipGetLastError();
     hipLaunchKernelGGL(cosine_dense_kernel, dim3(chunks, Hkv, sgroups), dim3(kThreads), 2 * kTileBytes,
-                       st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, 1, S, src, ck, E, fa, gate);
+                       st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, S, src, ck, E);
     return hipGetLastError();
 }
 

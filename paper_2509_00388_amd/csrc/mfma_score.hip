@@ -58,29 +58,6 @@ __device__ __forceinline__ void load_queries(const uint16_t *Qh, int first, int 
 // 256 registers, two waves share a SIMD, and one wave's exp2 work overlaps the
 // other's MFMAs.
 
-// Which (head, chunk, part) a workgroup takes.  The parts of a key chunk stream the same keys
-// and should run at about the same time on the same XCD, so that all but the first find the
-// keys in that XCD's L2.  Workgroups go to the 8 XCDs round robin in the order of their linear
-// number, so the parts of one (head, chunk) unit sit 8 apart: 8 units x their parts take
-// 8 x nparts consecutive numbers.  (Unit counts that are no multiple of 8 keep the plain order,
-// parts next to each other.)
-__device__ __forceinline__ void unit_of_workgroup(int nparts, int &h, int &chunk, int &part)
-{
-    const int nchunks = gridDim.x / nparts;
-    h = blockIdx.y;
-    chunk = blockIdx.x / nparts;
-    part = blockIdx.x % nparts;
-    if (nparts > 1 && ((long)gridDim.y * nchunks) % 8 == 0) {
-        const long lin = (long)blockIdx.y * gridDim.x + blockIdx.x;
-        const long grp8 = lin / (8 * nparts);
-        const int r = (int)(lin % (8 * nparts));
-        const long unit = grp8 * 8 + (r & 7);
-        h = (int)(unit / nchunks);
-        chunk = (int)(unit % nchunks);
-        part = r >> 3;
-    }
-}
-
 // ---------------------------------------------------------------- pass A ---
 // MANY: a workgroup takes `per_wg` consecutive chunks (whole tiles each) and keeps their statistics apart, so
 // that a batch cuts a head's keys as a single layer does and adds the same terms in the same order.  At a
@@ -89,17 +66,12 @@ __device__ __forceinline__ void unit_of_workgroup(int nparts, int &h, int &chunk
 template <int NB, int SPLIT, int STREAMS, bool MANY>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w,
-    int chunk_keys, int nchunks, int per_wg, float c, float *__restrict__ part, int R_total, int R_real, int row_base,
-    int nparts)
+    int chunk_keys, int nchunks, int per_wg, float c, float *__restrict__ part, int R_total, int R_real, int row_base)
 {
     constexpr int R = NB * kBlk, NBW = NB / SPLIT, NT = 64 * STREAMS * SPLIT, TK = kBlk * STREAMS;
     extern __shared__ __align__(16) unsigned char kt[];   // two key tiles
     __shared__ float sm[MANY ? 2 : 1][STREAMS][R], sz[MANY ? 2 : 1][STREAMS][R];
-    // nparts > 1: equal parts of 128 rows share one launch
-    int h, unit, row_part;
-    unit_of_workgroup(nparts, h, unit, row_part);
-    const int chunk0 = MANY ? unit * per_wg : unit;   // the workgroup's first chunk
-    row_base += 128 * row_part;
+    const int h = blockIdx.y, chunk0 = blockIdx.x * (MANY ? per_wg : 1);   // the workgroup's first chunk
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv % STREAMS, row0 = (wv / STREAMS) * NBW * kBlk;   // first query row of this wave
 
@@ -278,16 +250,13 @@ template <int NB, int SPLIT, bool PERQ, int STREAMS = 4>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w, int G,
     int chunk_keys, float c, const float *__restrict__ part, int part_chunks,
-    float *__restrict__ votes, int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int nparts,
+    float *__restrict__ votes, int R_total, int R_real, int row_base, int vote_rows, int vote_row_base,
     int pool_half)
 {
     constexpr int R = NB * kBlk, NBW = NB / SPLIT, NT = 64 * STREAMS * SPLIT, TK = kBlk * STREAMS;
     extern __shared__ __align__(16) unsigned char kt[];   // two key tiles
     __shared__ float bias_s[R];
-    int h, chunk, row_part;
-    unit_of_workgroup(nparts, h, chunk, row_part);
-    row_base += 128 * row_part;
-    vote_row_base += SPLIT * row_part;
+    const int h = blockIdx.y, chunk = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv % STREAMS, grp = wv / STREAMS, row0 = grp * NBW * kBlk;
 
@@ -546,7 +515,7 @@ static hipError_t launch_stats_nb(const uint16_t *K, const uint16_t *Q, int Hkv,
     auto *kernel = plan.per_wg > 1 ? score_stats_kernel<NB, SPLIT, STREAMS, true> : score_stats_kernel<NB, SPLIT, STREAMS, false>;
     if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
     hipLaunchKernelGGL(kernel, grid, block, lds, st, K, Q, N, P, w, plan.chunk_keys, plan.chunks, plan.per_wg, c, part,
-                       R_total, R_real, row_base, 1);
+                       R_total, R_real, row_base);
     return hipGetLastError();
 }
 
@@ -576,20 +545,20 @@ hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int 
 template <int NB, int SPLIT, int STREAMS = 4>
 static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int N, int P, int w, int G,
                             int ck, float c, const float *part, int chunks, int per_q, float *votes,
-                            int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int nparts,
-                            int pool_half, hipStream_t st)
+                            int R_total, int R_real, int row_base, int vote_rows, int vote_row_base, int pool_half,
+                            hipStream_t st)
 {
     const size_t lds = 2 * (kBlk * STREAMS) * kPitch + (pool_half >= 0 ? (size_t)(per_q ? G : SPLIT) * (ck + 2 * pool_half) * 4 : 0);
     if (per_q) {
         if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, true, STREAMS>)) return;
         hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, true, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
                            lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           R_real, row_base, vote_rows, vote_row_base, nparts, pool_half);
+                           R_real, row_base, vote_rows, vote_row_base, pool_half);
     } else {
         if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, false, STREAMS>)) return;
         hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, false, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
                            lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           R_real, row_base, vote_rows, vote_row_base, nparts, pool_half);
+                           R_real, row_base, vote_rows, vote_row_base, pool_half);
     }
 }
 
@@ -615,19 +584,18 @@ hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int 
     const int ck = pool_half >= 0 ? (P + vchunks - 1) / vchunks : vck;
     const float c = scale * 1.4426950408889634f;
     const uint16_t *K = (const uint16_t *)Kc, *Q = (const uint16_t *)Qw;
-    const int merged = 1;
-    dim3 grid(vchunks * merged, Hkv);
+    const dim3 grid(vchunks, Hkv);
     const int vote_rows = mfma_score_vote_rows(G, w, per_qhead_votes);
     int vote_row_base = 0;
     if (R == 256 && !per_qhead_votes) {   // all rows in one workgroup (see the statistics pass): four row groups
-        launch_votes_nb<8, 4, 2>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, 0, votes, R, R_real, 0, vote_rows, 0, 1,
+        launch_votes_nb<8, 4, 2>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, 0, votes, R, R_real, 0, vote_rows, 0,
                                  pool_half, st);
         return hipGetLastError();
     }
 #define GKV_VOTES(NB, SP)                                                                             \
     launch_votes_nb<NB, SP>(grid, K, Q, N, P, w, G, ck, c, part, plan.chunks, per_qhead_votes, votes, R, \
-                            R_real, row_base, vote_rows, vote_row_base, merged, pool_half, st)
-    for (int pt = 0; 128 * pt < R; pt += merged) {
+                            R_real, row_base, vote_rows, vote_row_base, pool_half, st)
+    for (int pt = 0; 128 * pt < R; ++pt) {
         const int row_base = 128 * pt, rows = part_rows(R, pt);
         const int split = part_split(rows, w, per_qhead_votes);
         switch (rows / 32) {

@@ -91,8 +91,7 @@ __device__ __forceinline__ void find_bin(const uint32_t *hist, uint32_t need, in
 template <int BLOCK, int DIG>
 __device__ __forceinline__ void topk_row_lds(
     int row, const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out,
-    long idx_ld, float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out,
-    int append_from, int append_count)
+    long idx_ld, float *__restrict__ val_out, long val_ld)
 {
     constexpr int NW = BLOCK / kWave;
     constexpr int NBINS = 1 << DIG;
@@ -107,12 +106,8 @@ __device__ __forceinline__ void topk_row_lds(
     uint32_t *cg = dyn + items * BLOCK;      // [ncell]
     uint32_t *ce = cg + ncell;               // [ncell]
     const float *xr = x + (long)row * ld;
-    int32_t *out = idx_out ? idx_out + (long)row * idx_ld : nullptr;
+    int32_t *out = idx_out + (long)row * idx_ld;
     float *vout = val_out ? val_out + (long)row * val_ld : nullptr;
-
-    if (out)
-        for (int r = tid; r < append_count; r += BLOCK) out[k + r] = append_from + r;
-    if (k <= 0) return;
 
     // Keys to LDS; the row's key range [kmin, kmax] on the way.
     __shared__ uint32_t s_min[NW], s_max[NW];
@@ -160,9 +155,6 @@ __device__ __forceinline__ void topk_row_lds(
         remaining = shift;
     }
     const uint32_t tau = kmin + prefix;   // key of the k-th largest entry; take `need` entries equal to it
-    if (tau_out && tid == 0) tau_out[row] = key_to_float(tau);
-    if (!out) return;
-
 
     for (int i = 0; i < items; ++i) {
         const int j = i * BLOCK + tid;
@@ -210,39 +202,22 @@ __device__ __forceinline__ void topk_row_lds(
     }
 }
 
-// One workgroup per row (WALK = false); with a gate, a smaller grid whose workgroups walk
-// the rows and skip those whose gate is 0 (WALK = true: a launch that mostly skips then
-// costs next to nothing).
-template <int BLOCK, int DIG, bool WALK>
+// One workgroup per row.
+template <int BLOCK, int DIG>
 __global__ __launch_bounds__(BLOCK) void topk_rows_lds_kernel(
-    const float *__restrict__ x, long ld, int n, int rows, int k, int32_t *__restrict__ idx_out,
-    long idx_ld, float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out,
-    int append_from, int append_count, const int32_t *__restrict__ gate, int rows_per_gate)
+    const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out, long idx_ld,
+    float *__restrict__ val_out, long val_ld)
 {
-    if constexpr (WALK) {
-        // one round trip settles the usual case of no gate being set at all
-        int any = 0;
-        for (int g = threadIdx.x; g < (rows + rows_per_gate - 1) / rows_per_gate; g += BLOCK)
-            any |= gate[g];
-        if (!__syncthreads_or(any)) return;
-        for (int row = blockIdx.x; row < rows; row += gridDim.x) {
-            if (gate[row / rows_per_gate] == 0) continue;
-            __syncthreads();   // LDS is reused from row to row
-            topk_row_lds<BLOCK, DIG>(row, x, ld, n, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                           append_from, append_count);
-        }
-    } else {
-        topk_row_lds<BLOCK, DIG>(blockIdx.x, x, ld, n, k, idx_out, idx_ld, val_out, val_ld,
-                                       tau_out, append_from, append_count);
-    }
+    topk_row_lds<BLOCK, DIG>(blockIdx.x, x, ld, n, k, idx_out, idx_ld, val_out, val_ld);
 }
 
 // ---- rows of any length: every sweep re-reads the row ------------------------
+// PLAN: k and the output row come from the per-layer budgets, `append_count` consecutive integers from append_from
+// on follow the k entries.
 template <int BLOCK, bool PLAN>
 __device__ __forceinline__ void topk_stream_row(
     int row, const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out, long idx_ld,
-    float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out, int append_from,
-    int append_count, const int32_t *__restrict__ gate, int rows_per_gate,
+    float *__restrict__ val_out, long val_ld, int append_from, int append_count,
     typename std::conditional<PLAN, LayerPlan, int>::type plan)
 {
     constexpr int NW = BLOCK / kWave;
@@ -251,20 +226,16 @@ __device__ __forceinline__ void topk_stream_row(
     __shared__ uint32_t s_bin, s_need;
     __shared__ uint32_t w_gt[NW], w_eq[NW];
 
-    if (gate && gate[row / rows_per_gate] == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float *xr = x + (long)row * ld;
-    int32_t *out = idx_out ? idx_out + (long)row * idx_ld : nullptr;
+    int32_t *out = idx_out + (long)row * idx_ld;
     float *vout = val_out ? val_out + (long)row * val_ld : nullptr;
     if constexpr (PLAN) {   // per-layer budget: k and the output row come from the plan
         const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
         k = plan.budget[g] - append_count;
         out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
-    }
-
-    if (out)
         for (int r = tid; r < append_count; r += BLOCK) out[k + r] = append_from + r;
-    if (k <= 0) return;
+    }
 
     uint32_t prefix = 0, mask = 0, need = (uint32_t)k;
     for (int pass = 0; pass < 3; ++pass) {
@@ -294,8 +265,6 @@ __device__ __forceinline__ void topk_stream_row(
         need = s_need;
     }
     const uint32_t tau = prefix;
-    if (tau_out && tid == 0) tau_out[row] = key_to_float(tau);
-    if (!out) return;
 
     // Each wave owns a contiguous, 64-aligned segment of the row.
     int seg = (n + NW - 1) / NW;
@@ -354,23 +323,12 @@ __device__ __forceinline__ void topk_stream_row(
 
 template <int BLOCK, bool PLAN>
 __global__ __launch_bounds__(BLOCK) void topk_rows_stream_kernel(
-    const float *__restrict__ x, long ld, int n, int rows, int k, int32_t *__restrict__ idx_out, long idx_ld,
-    float *__restrict__ val_out, long val_ld, float *__restrict__ tau_out, int append_from,
-    int append_count, const int32_t *__restrict__ gate, int rows_per_gate,
+    const float *__restrict__ x, long ld, int n, int k, int32_t *__restrict__ idx_out, long idx_ld,
+    float *__restrict__ val_out, long val_ld, int append_from, int append_count,
     typename std::conditional<PLAN, LayerPlan, int>::type plan)
 {
-    // (a gated launch has few workgroups that walk the rows; usually no gate is open at all)
-    if (gate) {
-        const int n_gates = (rows + rows_per_gate - 1) / rows_per_gate;
-        int open = 0;
-        for (int g = threadIdx.x; g < n_gates; g += BLOCK) open |= gate[g] != 0;
-        if (!__syncthreads_or(open)) return;
-    }
-    for (int row = blockIdx.x; row < rows; row += gridDim.x) {
-        topk_stream_row<BLOCK, PLAN>(row, x, ld, n, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
-                                     append_count, gate, rows_per_gate, plan);
-        __syncthreads();
-    }
+    topk_stream_row<BLOCK, PLAN>(blockIdx.x, x, ld, n, k, idx_out, idx_ld, val_out, val_ld, append_from, append_count,
+                                 plan);
 }
 
 // A row in batches of U loads per thread of a 1024-thread workgroup, the next batch on its way
@@ -515,7 +473,7 @@ template <int BLOCK, bool EDGES>
 __device__ __forceinline__ void pick_general(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, int tid)
 {
     int32_t *tmp = !EDGES && o.ext ? o.ext : o.src;
-    topk_stream_row<BLOCK, false>(0, xr, n, n, k, tmp, 0, EDGES ? o.val : nullptr, 0, nullptr, 0, 0, nullptr, 1, 0);
+    topk_stream_row<BLOCK, false>(0, xr, n, n, k, tmp, 0, EDGES ? o.val : nullptr, 0, 0, 0, 0);
     if (EDGES) return;
     __syncthreads();
     const int32_t j = tid < k ? tmp[tid] : 0;
@@ -896,8 +854,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     const uint32_t bin = s_out[0], cnt = s_out[2];
     uint32_t need = s_out[1];
     if (cnt > (uint32_t)kBudgetList) {   // (the same for every thread)
-        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
-                                            nullptr, 1, plan);
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
         return;
     }
     if (tid < 4) lkey[min(cnt + (uint32_t)tid, (uint32_t)kBudgetList - 1u)] = 0u;   // padding for reads of four
@@ -922,8 +879,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     });
     __syncthreads();
     if (s_cnt != cnt) {   // counted by key, not found by comparison: NaN in the bin
-        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
-                                            nullptr, 1, plan);
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
         return;
     }
     // the need-th largest of the list
@@ -955,8 +911,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
         }
     }
     if (equal != need && cnt > (uint32_t)kPairs) {   // many ties straddle the cut
-        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
-                                            nullptr, 1, plan);
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
         return;
     }
     for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
@@ -971,8 +926,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     }
     __syncthreads();
     if (!emit_bitmap<NW>(map, words, k, s_part[0], out, tid, lane, wv))   // NaN counted above the bin and not marked
-        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, nullptr, append_from, append_count,
-                                            nullptr, 1, plan);
+        topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
 }
 
 // ---- neighbourhoods of heads whose candidate lists overflowed ------------------------
@@ -1031,32 +985,21 @@ __global__ __launch_bounds__(kRedoBlock) void redo_rows_kernel(
         int32_t *out = nbr + item * m;
         float *vout = nbr_e + item * m;
         if (P <= 32768)
-            topk_row_lds<kRedoBlock, 11>(0, erow, P, P, m, out, 0, vout, 0, nullptr, 0, 0);
+            topk_row_lds<kRedoBlock, 11>(0, erow, P, P, m, out, 0, vout, 0);
         else
-            topk_stream_row<kRedoBlock, false>(0, erow, P, P, m, out, 0, vout, 0, nullptr, 0, 0, nullptr, 1, 0);
+            topk_stream_row<kRedoBlock, false>(0, erow, P, P, m, out, 0, vout, 0, 0, 0, 0);
     }
 }
 
 template <int BLOCK, int DIG>
-static hipError_t launch_lds(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
-                             long idx_ld, float *val_out, long val_ld, float *tau_out,
-                             int append_from, int append_count, const int32_t *gate,
-                             int rows_per_gate, hipStream_t st)
+static hipError_t launch_lds(const float *x, long ld, int n, int rows, int k, int32_t *idx_out, long idx_ld,
+                             float *val_out, long val_ld, hipStream_t st)
 {
     const int items = (n + BLOCK - 1) / BLOCK;
     const size_t lds = ((size_t)items * BLOCK + 2 * (size_t)items * (BLOCK / kWave)) * 4;
-    if (lds > 65536 &&    // more than 64 KiB of dynamic LDS needs a one-time opt-in
-        (!allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, DIG, false>, 140 * 1024) ||
-         !allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, DIG, true>, 140 * 1024)))
-        return hipGetLastError();
-    if (gate)
-        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, DIG, true>), dim3(rows > 1024 ? 1024 : rows),
-                           dim3(BLOCK), lds, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld,
-                           tau_out, append_from, append_count, gate, rows_per_gate);
-    else
-        hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, DIG, false>), dim3(rows), dim3(BLOCK), lds,
-                           st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
-                           append_count, gate, rows_per_gate);
+    if (lds > 65536 && !allow_big_lds((const void *)topk_rows_lds_kernel<BLOCK, DIG>, 140 * 1024)) return hipGetLastError();
+    hipLaunchKernelGGL((topk_rows_lds_kernel<BLOCK, DIG>), dim3(rows), dim3(BLOCK), lds, st, x, ld, n, k, idx_out, idx_ld,
+                       val_out, val_ld);
     return hipGetLastError();
 }
 
@@ -1111,15 +1054,12 @@ hipError_t launch_pick_match(float *x, int n, int rows, const MatchArgs &a, int3
     }
 }
 
-hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int32_t *idx_out,
-                            long idx_ld, float *val_out, long val_ld, float *tau_out,
-                            int append_from, int append_count, const int32_t *gate,
-                            int rows_per_gate, hipStream_t st)
+hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int32_t *idx_out, long idx_ld,
+                            float *val_out, long val_ld, hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;
-    if (k <= kSmallK && idx_out && !val_out && !tau_out && append_count == 0 && !gate)
-        return launch_pick(x, ld, n, rows, k, k, idx_out, idx_ld, nullptr, 0, st);
-    if (k <= kSmallK && n <= 32768 && idx_out && val_out && !tau_out && append_count == 0 && !gate) {
+    if (k <= kSmallK && !val_out) return launch_pick(x, ld, n, rows, k, k, idx_out, idx_ld, nullptr, 0, st);
+    if (k <= kSmallK && n <= 32768) {
 #define GKV_EDGES(BLOCK, ITEMS)                                                                                  \
     hipLaunchKernelGGL((pick_edges_kernel<BLOCK, ITEMS>), dim3(rows), dim3(BLOCK), 0, st, x, ld, n, k, idx_out, idx_ld, \
                        val_out, val_ld)
@@ -1133,15 +1073,10 @@ hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int
 #undef GKV_EDGES
         return hipGetLastError();
     }
-    if (n <= 4096)
-        return launch_lds<256, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                  append_from, append_count, gate, rows_per_gate, st);
-    if (n <= 32768)
-        return launch_lds<1024, 11>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out,
-                                    append_from, append_count, gate, rows_per_gate, st);
-    hipLaunchKernelGGL((topk_rows_stream_kernel<1024, false>), dim3(gate && rows > 1024 ? 1024 : rows), dim3(1024),
-                       0, st, x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, tau_out, append_from,
-                       append_count, gate, rows_per_gate, 0);
+    if (n <= 4096) return launch_lds<256, 8>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, st);
+    if (n <= 32768) return launch_lds<1024, 11>(x, ld, n, rows, k, idx_out, idx_ld, val_out, val_ld, st);
+    hipLaunchKernelGGL((topk_rows_stream_kernel<1024, false>), dim3(rows), dim3(1024), 0, st, x, ld, n, k, idx_out, idx_ld,
+                       val_out, val_ld, 0, 0, 0);
     return hipGetLastError();
 }
 
@@ -1225,8 +1160,7 @@ hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &pl
                            words * 8 + (size_t)kBudgetList * 8, st, scores, P, idx, P, w, plan);
     } else {
         hipLaunchKernelGGL((topk_rows_stream_kernel<1024, true>), dim3(rows), dim3(1024), 0, st, scores, (long)P, P,
-                           rows, 0, idx, 0L, (float *)nullptr, 0L, (float *)nullptr, P, w, (const int32_t *)nullptr, 1,
-                           plan);
+                           0, idx, 0L, (float *)nullptr, 0L, P, w, plan);
     }
     return hipGetLastError();
 }
