@@ -1039,24 +1039,14 @@ int mfma_sample_cols(int P)
     return ps;
 }
 
-// Keys in the sample of a later round's pass over the new sources that have no kept list.  There are
-// usually none, so the pass gives up its chunked sample and the launch that adds the chunks up (4.6 us
-// a round) for a sample half as large that one workgroup walks; at most twice as many candidates
-// reach the looser bound, which the slices (four times the share of the full sample's) hold.
-static int late_sample_cols(int P)
-{
-    const int ps = mfma_sample_cols(P);
-    return P > 131072 ? ps : (ps / 2 > 2048 ? ps / 2 : 2048);
-}
-
-// The sample: every stride-th key of the whole row, at most `most` of them.  (The stride rounded down would
+// The sample: every stride-th key of the whole row.  (The stride rounded down would
 // leave up to half of the row's end out, and a source whose near keys sit there -- neighbours in position, as
 // rotary position codes make them -- gets a bound far too low: lists overflow and heads are redone row by
 // row.  One round of 40 heads x 72 sources x 4064 keys in runs of 250 alike: 562 us, 181 with the whole row sampled.)
 struct Sample { int stride, cols; };
-static Sample sample_of(int P, int most)
+static Sample sample_of(int P)
 {
-    const int stride = (P + most - 1) / most;
+    const int most = mfma_sample_cols(P), stride = (P + most - 1) / most;
     return {stride, (P + stride - 1) / stride};
 }
 
@@ -1184,8 +1174,12 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
                         int row0, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
-    const Sample smp = sample_of(P, late ? late_sample_cols(P) : mfma_sample_cols(P));
+    const Sample smp = sample_of(P);
     const int sgroups = (rows + ROWS - 1) / ROWS;
+    // In later rounds there are usually no sources without a list, so one workgroup walks the whole sample and the
+    // launch that adds chunks up is saved (4.6 us a round).  (With a sample half as large more of the lists of
+    // such sources overflow: three enhanced rounds of 8 heads, mean of eight inputs, us, half / whole sample:
+    // 32736 keys 367 / 338, 65504 469 / 415, 131040 719 / 546, and no difference where there are none.)
     const int chunks = late ? 1 : bound_chunks(Hkv, P, sgroups);
     const int chunk_cols = (((smp.cols + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
     const int rank = mfma_bound_rank(m, smp.stride);
@@ -1202,12 +1196,12 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
 
 template <int SB, int RING>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
-                         int src_pitch, const int32_t *n_src, bool late, const MfmaFilterPlan &g, int row0,
+                         int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, int row0,
                          const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    const int stride = sample_of(P, late ? late_sample_cols(P) : mfma_sample_cols(P)).stride;
+    const int stride = sample_of(P).stride;
     // Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
     // per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
     // rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a
@@ -1253,9 +1247,9 @@ hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, in
                                      int32_t *overflow, hipStream_t st)
 {
     if (first_round && g.sb == 3)
-        return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false, g, 0, tau, cand,
+        return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand,
                                     cand_cnt, overflow, st);
-    return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, g, 0, tau, cand, cand_cnt,
+    return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt,
                                 overflow, st);
 }
 

@@ -1409,3 +1409,29 @@ def test_short_prompts_whose_similar_keys_are_neighbours(P, H, m, run):
     s8, src8, nbr8, ev8 = run_propagate(few, K[:8].contiguous(), s0[:8].cpu().numpy())
     assert np.array_equal(src[0, :8], src8[0]) and np.array_equal(nbr[0, :8], nbr8[0])
     assert np.array_equal(ev[0, :8], ev8[0]) and np.array_equal(s1[:8], s8)
+
+
+@pytest.mark.parametrize("P,seed", [(65504, 5), (65504, 7), (131040, 2)])
+def test_new_sources_of_later_rounds_are_not_redone(P, seed):
+    """An enhanced signal makes neighbours sources, which no list was kept for: their bound must be as good as
+    the first round's, or their lists overflow and the whole head is redone (0.5 to 1 ms a head; three
+    launches that find nothing take 0.02 ms together)."""
+    say(f"new sources of later rounds P={P} seed={seed}")
+    H, w, d = 8, 32, 128
+    g = torch.Generator("cuda").manual_seed(seed)
+    centre = torch.randn(H, 256, d, generator=g, device="cuda")
+    kind = torch.randint(0, 256, (H, P + w), generator=g, device="cuda")
+    K = torch.stack([centre[h][kind[h]] + 0.5 * torch.randn(P + w, d, generator=g, device="cuda") for h in range(H)])
+    K = K.to(torch.bfloat16)
+    s0 = torch.rand(H, P, generator=g, device="cuda")
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, budget=w + 1, n_sources=64,
+                  n_neighbors=32, rounds=3, dtype=gk.BF16, signal=1)
+    best = np.inf
+    for _ in range(3):
+        gk.graphkv_profile_begin()
+        gk.graphkv_propagate(p, K, s0.clone())
+        torch.cuda.synchronize()
+        times = gk.graphkv_profile_end()
+        best = min(best, times["redo_rows"][0])
+        assert times["cosine_bound_new"][1] == 2
+    assert best < 0.1, f"redo {best:.3f} ms"
