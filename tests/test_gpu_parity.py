@@ -1151,7 +1151,7 @@ def test_update_products_in_source_order(S, m, P, signal):
 def test_any_head_dimension_on_the_matrix_cores(oracle, d, H, G, w, P, pool, mode, S, m, dtype):
     """Scores and one round of edges for head dimensions of one to several staged pieces, rows that do
     not fill the 32-row blocks, one to three row groups, key tails, pooling windows on both sides of what
-    the vote kernel pools itself, window rows beyond one batch of statistics."""
+    the vote kernel pools itself."""
     cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=P + w, window=w, head_dim=d, n_kv_heads=H, n_q_heads=H * G,
                        pool_kernel=pool, budget=w + 5, n_sources=S, n_neighbors=m, dtype=dtype)
     say(f"any head dimension d={d} H={H} G={G} w={w} P={P} pool={pool}/{mode} S={S} m={m} {dtype}")
@@ -1435,3 +1435,22 @@ def test_new_sources_of_later_rounds_are_not_redone(P, seed):
         best = min(best, times["redo_rows"][0])
         assert times["cosine_bound_new"][1] == 2
     assert best < 0.1, f"redo {best:.3f} ms"
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("d,H,G,w,P,pool,mode", [
+    (64, 1, 9, 70, 300, 7, 0), (64, 1, 9, 70, 300, 7, 1), (72, 2, 5, 130, 150, 3, 1), (64, 1, 4, 32, 4128, 7, 0),
+    (64, 1, 4, 32, 4128, 9, 1), (64, 2, 2, 64, 4200, 131, 0), (64, 32, 4, 32, 2500, 7, 0), (64, 64, 2, 32, 1100, 5, 1),
+    (64, 64, 1, 16, 2200, 7, 0)])
+def test_any_type_scores_over_batches_and_chunks(oracle, d, H, G, w, P, pool, mode, dtype):
+    """Scores off the streaming kernels with more query rows than the 512 whose statistics sit in LDS at a
+    time (query heads that straddle two batches among them), with enough chunks that a launch of its own merges
+    the statistics (128 rows x 65 chunks), and with enough heads that a workgroup walks several tiles, for one,
+    two and four row blocks."""
+    cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=P + w, window=w, head_dim=d, n_kv_heads=H, n_q_heads=H * G,
+                       pool_kernel=pool, budget=w + 5, dtype=dtype)
+    say(f"scores over batches and chunks d={d} H={H} G={G} w={w} P={P} pool={pool}/{mode} {dtype}")
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 3)
+    p = util.params_from_cfg(cfg, pool_mode=mode)
+    assert not gk.graphkv_uses_mfma(p)
+    util.assert_scores_close(gk.graphkv_score(p, Kd, Qd).cpu().numpy(), oracle.score(K, Q, dtype, pool, mode))
