@@ -457,7 +457,9 @@ GemmScorePlan gemm_score_plan(int Hkv, int layer_heads, int G, int w, int N, boo
     }
     pl.chunk_keys = ck;
     pl.chunks = (N + ck - 1) / ck;
-    pl.per_wg = max(1, gemm_chunk_keys(Hkv, rows, N) / ck);
+    // as many workgroups a head as the heads of the launch ask for, evenly filled
+    const int all = gemm_chunk_keys(Hkv, rows, N), wgs = (N + all - 1) / all;
+    pl.per_wg = max(1, (pl.chunks + wgs - 1) / wgs);
     pl.pitch = trim ? P : N;
     // (a single chunk's statistics are the rows')
     pl.part_bytes = pl.chunks > 1 ? (size_t)Hkv * rows * pl.chunks * 2 * sizeof(float) : 0;

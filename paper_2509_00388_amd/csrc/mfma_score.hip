@@ -473,8 +473,9 @@ MfmaScorePlan mfma_score_plan(int Hkv, int layer_heads, int G, int w, int N, int
     const bool as_layer = (long)Hkv * N <= kLayerCutKeys || G * w % kBlk != 0;
     pl.chunk_keys = stats_keys(as_layer ? layer_heads : Hkv, N);
     pl.chunks = (N + pl.chunk_keys - 1) / pl.chunk_keys;
-    pl.per_wg = stats_keys(Hkv, N) / pl.chunk_keys;
-    if (pl.per_wg < 1) pl.per_wg = 1;
+    // as many workgroups a head as the heads of the launch ask for, evenly filled
+    const int all = stats_keys(Hkv, N), wgs = (N + all - 1) / all;
+    pl.per_wg = pl.chunks > wgs ? (pl.chunks + wgs - 1) / wgs : 1;
     pl.part_bytes = (size_t)Hkv * pl.chunks * mfma_score_rows(G, w, per_qhead_votes) * 2 * sizeof(float);
     return pl;
 }
