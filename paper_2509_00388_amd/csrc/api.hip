@@ -370,6 +370,10 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
     // A round's update rides along with the next kernel that has a workgroup per head, where there is one:
     // the selection of the next round's sources, the caller's final selection.
     const int items = decay_rides_along(D.P, D.S, D.m);
+    // The edges of a single source are one read of the keys, which the scalar kernel does faster but for wide bf16
+    // rows (us, matrix cores / scalar: 128 heads of 9598 fp32 keys of 128 221 / 146, of bf16 64 76 / 47, of bf16 256
+    // 165 / 198); with two sources it is no faster.
+    const bool one_source = D.S == 1 && (p->dtype == GRAPHKV_FP32 || D.d <= 64);
     DecayArgs update{};
     for (int t = 0; t < D.T; ++t) {
         int32_t *src = src0, *nbr = nbr0;
@@ -447,7 +451,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                 // Eq. 1: edges from every source to every node
                 if (D.mfma_cosine)
                     GKV_LAUNCH(GRAPHKV_K_COSINE, launch_mfma_cosine(Ac, Kc, D.H, D.N, D.P, D.S, src, E, st));
-                else if (D.gemm)
+                else if (D.gemm && !one_source)
                     GKV_LAUNCH(GRAPHKV_K_GENERIC_COSINE,
                                launch_gemm_cosine(Ac, Kc, p->dtype, D.H, D.d, D.N, D.P, D.S, src, E, st));
                 else

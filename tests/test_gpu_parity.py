@@ -1454,3 +1454,16 @@ def test_any_type_scores_over_batches_and_chunks(oracle, d, H, G, w, P, pool, mo
     p = util.params_from_cfg(cfg, pool_mode=mode)
     assert not gk.graphkv_uses_mfma(p)
     util.assert_scores_close(gk.graphkv_score(p, Kd, Qd).cpu().numpy(), oracle.score(K, Q, dtype, pool, mode))
+
+
+@pytest.mark.parametrize("dtype,d", [("fp32", 128), ("bf16", 64), ("bf16", 72), ("fp32", 24)])
+def test_one_source(oracle, dtype, d):
+    """A single source takes the scalar edge kernel or the matrix cores by type and width: same contract."""
+    cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=1200, window=7, head_dim=d, n_kv_heads=3, n_q_heads=3, budget=100,
+                       n_sources=1, n_neighbors=40, dtype=dtype)
+    say(f"one source d={d} {dtype}")
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 4)
+    p = util.params_from_cfg(cfg, rounds=1)
+    s0 = synth.random_scores(cfg)
+    s1, src, nbr, ev = run_propagate(p, Kd, s0)
+    util.check_round_staged(oracle, K, dtype, 7, s0, s1, src[0], nbr[0], ev[0], 1, 40, p.decay, 0)
