@@ -261,7 +261,9 @@ const char *graphkv_strerror(int32_t code);
  * begin and end from one host thread).  graphkv_profile_end() waits for the
  * recorded events and adds up, per kernel id, the elapsed milliseconds into
  * ms[GRAPHKV_N_KERNELS] and the number of launches into launches[...] (HOST
- * arrays, either may be NULL).
+ * arrays, either may be NULL).  The GENERIC ids count the scalar kernels and, with
+ * GRAPHKV_IMPL_AUTO, the matrix-core kernels that take their place; an update of the
+ * scores that the next selection does first is counted with that selection.
  */
 enum {
     GRAPHKV_K_SCORE_STATS = 0, GRAPHKV_K_SCORE_VOTES, GRAPHKV_K_POOL, GRAPHKV_K_TOPK_SOURCES,

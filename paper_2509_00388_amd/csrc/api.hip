@@ -296,7 +296,7 @@ int32_t run_score(const graphkv_params *p, const Dims &D, const Workspace &W, co
         GKV_LAUNCH(GRAPHKV_K_SCORE_STATS, launch_mfma_score_stats(Kc, Qw, D.H, D.Hl, D.Hq, D.N, D.w, D.scale,
                                                                   per_q, at<float>(ws, W.part), st));
         if (mfma_score_fuses_pool(D.G, D.w, per_q, p->pool_kernel)) {
-            // average pooling and the mean over the group happen inside pass B
+            // pooling and the mean over the group happen inside pass B
             GKV_LAUNCH(GRAPHKV_K_SCORE_VOTES,
                        launch_mfma_score_votes(Kc, Qw, D.H, D.Hl, D.Hq, D.N, D.w, D.scale, per_q, p->pool_kernel,
                                                at<float>(ws, W.part), scores, st));

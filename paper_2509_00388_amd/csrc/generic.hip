@@ -1,7 +1,7 @@
-// Scalar (non-MFMA) kernels for the two contractions of the pass, for any
-// storage type and head dimension.  They serve fp32 inputs and shapes the MFMA
-// kernels do not cover, and cross-check the MFMA kernels in the tests.  fp32
-// fused multiply-adds, fp32 accumulation.
+// Scalar (non-MFMA) kernels for the two contractions of the pass, for any storage type and head
+// dimension: what impl = GENERIC runs, which cross-checks the matrix-core kernels in the tests.  AUTO
+// takes the votes kernel behind gemm.hip's logits for wide pooling windows, the edges of a single source
+// and the key norms from here.  fp32 fused multiply-adds, fp32 accumulation.
 #include "common.hpp"
 #include "kernels.hpp"
 

@@ -123,8 +123,8 @@ MfmaScorePlan mfma_score_plan(int Hkv, int layer_heads, int G, int w, int N, int
 int mfma_score_vote_rows(int G, int w, int per_qhead_votes);
 hipError_t launch_mfma_score_stats(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,
                                   float scale, int per_qhead_votes, float *part, hipStream_t st);
-// fused_pool_kernel > 0 (only if mfma_score_fuses_pool()): average pooling with that kernel
-// size and the mean over the query heads are done in the same kernel; `votes` is then the
+// fused_pool_kernel > 0 (only if mfma_score_fuses_pool()): pooling with that kernel size and the
+// mean over the query heads are done in the same kernel; `votes` is then the
 // score array [Hkv, P] and no pooling kernel follows.
 bool mfma_score_fuses_pool(int G, int w, int per_qhead_votes, int pool_kernel);
 hipError_t launch_mfma_score_votes(const void *Kc, const void *Qw, int Hkv, int layer_heads, int Hq, int N, int w,

@@ -826,7 +826,7 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 // key index.  Lists longer than 64 R, with fewer than m entries, or with more ties at the cut than the
 // list has room for, raise the head's overflow flag (the head is then redone exactly).
 // (A walk over the slices for every register, key indices fetched a second time, scans through the
-// LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way SELW us.)
+// LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way 8.4 us.)
 template <int R>
 __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
                                                               const int32_t *__restrict__ cand_cnt,

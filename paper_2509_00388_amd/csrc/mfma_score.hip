@@ -409,8 +409,8 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
 // of the statistics -- about as long as 256 keys take.  So the cut with the fewest keys per compute unit
 // wins, counting whole rounds of 256 workgroups: for few heads as many chunks as one round takes, for
 // many as few as keep the rounds full.  At most `most` keys: the votes of a chunk sit in LDS beside the
-// key tiles, one row per row group (two, or four at 256 query rows) or query head; at least two tiles, as the pooling window's halo is read
-// twice.  (1024 workgroups of at least 1024 keys before, chunks of 6144 with 256 query rows; us, before /
+// key tiles, one row per row group (two, or four at 256 query rows) or query head; at least two tiles, as the
+// pooling window's halo is read twice.  (1024 workgroups of at least 1024 keys before, chunks of 6144 with 256 query rows; us, before /
 // now: 8 heads of 4096 keys 18.0 / 13.6, of 16384 21.0 / 16.3, of 65536 51 / 31; 128 heads of 8192 76 / 51;
 // 8 heads of 32768 keys with 256 query rows 103 / 28.)
 constexpr int kComputeUnits = 256;
