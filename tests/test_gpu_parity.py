@@ -1467,3 +1467,26 @@ def test_one_source(oracle, dtype, d):
     s0 = synth.random_scores(cfg)
     s1, src, nbr, ev = run_propagate(p, Kd, s0)
     util.check_round_staged(oracle, K, dtype, 7, s0, s1, src[0], nbr[0], ev[0], 1, 40, p.decay, 0)
+
+
+@pytest.mark.parametrize("dtype,N,bad", [("bf16", 1500, np.inf), ("bf16", 9100, -np.inf), ("bf16", 9100, np.nan), ("bf16", 40000, np.inf),
+                                         ("fp32", 1500, np.inf), ("fp32", 3000, np.nan)])
+def test_one_head_with_an_element_that_is_no_number(dtype, N, bad):
+    """One element of one key makes a head's scores NaN.  What that head keeps has no agreed order, but it must
+    be a valid selection (ascending tokens of the prefix, then the window, rows gathered from there), and the
+    other heads keep what they keep without it, bit for bit."""
+    say(f"no number in a head {dtype} N={N} {bad}")
+    cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=N, n_kv_heads=3, n_q_heads=6, n_sources=40, n_neighbors=12, rounds=3,
+                       budget=N // 6, dtype=dtype)
+    (K, V, Q), (Kd, Vd, Qd) = util.device_layer(cfg, 1)
+    p = util.params_from_cfg(cfg)
+    want = run_compress(p, (Kd, Vd, Qd))[0][2]
+    Kb = Kd.clone()
+    Kb[1, N // 3, 5] = bad
+    Ko, Vo, idx = run_compress(p, (Kb, Vd, Qd))[0]
+    for h in (0, 2):
+        assert np.array_equal(idx[h], want[h])
+    assert np.array_equal(Vo[1], gk.to_host_bits(Vd)[1][idx[1]])
+    k = p.budget - p.window
+    assert np.all(np.diff(idx[1]) > 0) and idx[1, 0] >= 0 and idx[1, k - 1] < p.n_prefix
+    assert np.array_equal(idx[1, k:], np.arange(p.n_prefix, N))
