@@ -113,6 +113,8 @@ def load_library() -> ctypes.CDLL:
     lib.graphkv_propagate_edges.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.graphkv_select.restype = i32
     lib.graphkv_select.argtypes = [pp, vp, vp, vp, sz, vp]
+    lib.graphkv_select_workspace_bytes.restype = sz
+    lib.graphkv_select_workspace_bytes.argtypes = [pp]
     lib.graphkv_compress.restype = i32
     lib.graphkv_compress.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.graphkv_compress_static.restype = i32
@@ -256,9 +258,12 @@ def graphkv_select(p: Params, scores, idx=None, ws=None):
     if idx is None:
         idx = torch.empty((p.n_kv_heads, p.budget), dtype=torch.int32, device=scores.device)
     cp = p.c()
+    sp = _arg(scores, "scores", torch.float32, p.n_kv_heads * p.n_prefix)
+    if ws is None and p.n_prefix > 32768:   # (shorter rows use none)
+        need = load_library().graphkv_select_workspace_bytes(ctypes.byref(cp))
+        ws = torch.empty(need, dtype=torch.uint8, device=scores.device) if need else None
     _check(load_library().graphkv_select(
-        ctypes.byref(cp), _arg(scores, "scores", torch.float32, p.n_kv_heads * p.n_prefix),
-        _arg(idx, "idx", torch.int32, p.n_kv_heads * max(p.budget, 0)),
+        ctypes.byref(cp), sp, _arg(idx, "idx", torch.int32, p.n_kv_heads * max(p.budget, 0)),
         _arg(ws, "ws", torch.uint8, 0, optional=True), ws.numel() if ws is not None else 0, _stream()))
     return idx
 

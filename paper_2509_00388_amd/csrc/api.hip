@@ -65,6 +65,7 @@ struct Workspace {
     size_t bound_hist, tau, cand, cand_cnt, overflow;
     // lists kept from one round to the next, speculative rows
     size_t src_b, nbr_b, nbr_e_b, ext, new_src, n_new, sel_row, sel_pos, n_sel, spec_bad;
+    size_t final_sel, final_bytes;   // the final selection's (0 bytes: it takes none)
     size_t total;
 };
 
@@ -223,6 +224,10 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.n_sel = take(keep ? (size_t)D.H * 4 : 0);
     W.spec_bad = take(keep ? (size_t)D.H * 4 : 0);
     if (off < scoring_end) off = scoring_end;
+    // The final selection of rows that need it comes last, with no update left to do: the same place again.
+    W.final_sel = shared;
+    W.final_bytes = D.scratch == kOrdinary ? topk_final_scratch_bytes(D.H, D.P) : 0;
+    if (off < shared + W.final_bytes) off = align_up(shared + W.final_bytes);
     W.total = off;
     return W;
 }
@@ -498,9 +503,9 @@ LayerPlan make_plan(const graphkv_params *p, int n_layers, const int32_t *budget
 }
 
 int32_t run_select(const Dims &D, const LayerPlan &plan, float *scores, int32_t *idx, const DecayArgs &update,
-                   hipStream_t st)
+                   void *scratch, hipStream_t st)
 {
-    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, update, st));
+    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, update, scratch, st));
     return GRAPHKV_OK;
 }
 
@@ -523,7 +528,8 @@ int32_t run_compress(const graphkv_params *p, int n_layers, const Dims &group, c
     DecayArgs update;
     if (int32_t rc = run_propagate(p, D, W, edge_src, edge_nbr, scores, nullptr, nullptr, nullptr, ws, st, &update))
         return rc;
-    if (int32_t rc = run_select(D, plan, scores, idx, update, st)) return rc;
+    void *sel = W.final_bytes ? at<void>(ws, W.final_sel) : nullptr;
+    if (int32_t rc = run_select(D, plan, scores, idx, update, sel, st)) return rc;
     GKV_LAUNCH(GRAPHKV_K_GATHER, launch_gather(Kc, Vc, idx, D.H, D.N, plan, max_budget,
                                                (int)(D.d * D.esize), Kout, Vout, st));
     return GRAPHKV_OK;
@@ -674,13 +680,20 @@ int32_t graphkv_propagate(const graphkv_params *p, const void *Kc, float *scores
 int32_t graphkv_select(const graphkv_params *p, const float *scores, int32_t *idx, void *ws,
                        size_t ws_bytes, void *stream)
 {
-    (void)ws; (void)ws_bytes;
     if (!base_ok(p) || !budget_ok(p)) return GRAPHKV_EINVAL;
     if (!aligned4(scores) || !aligned4(idx)) return GRAPHKV_EINVAL;
     const Dims D = dims_of(p);
+    const size_t need = topk_final_scratch_bytes(D.H, D.P);
+    void *sel = need && check_ws(need, ws, ws_bytes) == GRAPHKV_OK ? ws : nullptr;
     // (no update rides along: the scores are only read)
-    return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{},
+    return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{}, sel,
                       (hipStream_t)stream);
+}
+
+size_t graphkv_select_workspace_bytes(const graphkv_params *p)
+{
+    if (!base_ok(p)) return 0;
+    return topk_final_scratch_bytes(p->n_kv_heads, p->n_tokens - p->window);
 }
 
 int32_t graphkv_compress(const graphkv_params *p, const void *Kc, const void *Vc, const void *Qw,

@@ -102,9 +102,11 @@ hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int
                          hipStream_t st);
 // Final selection of a batch: row q keeps budget[l] - w entries and writes them,
 // followed by the window tokens P .. P + w - 1, to its packed idx row.
-// (An update that rides along changes the scores first.)
+// (An update that rides along changes the scores first.)  scratch: topk_final_scratch_bytes() bytes, with which
+// few long rows are shared out to many workgroups (0: none is used), or nullptr.
+size_t topk_final_scratch_bytes(int rows, int P);
 hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
-                             const DecayArgs &update, hipStream_t st);
+                             const DecayArgs &update, void *scratch, hipStream_t st);
 hipError_t launch_copy_i32(const int32_t *src, int32_t *dst, long n, hipStream_t st);
 hipError_t launch_copy_f32(const float *src, float *dst, long n, hipStream_t st);
 

@@ -662,6 +662,55 @@ __device__ __forceinline__ void rank_in_pairs(const uint32_t *list, int cnt, uin
     __syncthreads();
 }
 
+// The need-th largest of the cnt <= kBudgetList listed keys (padded with zeros to a multiple of four where
+// cnt <= kPairs): tau = that key, need = how many entries equal to it are among the need largest, equal =
+// how many there are.  false if many ties straddle the cut.  Every thread calls it and gets the same; `hist`,
+// `part` and `out` are free.
+__device__ __forceinline__ bool cut_of_list(const uint32_t *lkey, uint32_t cnt, uint32_t &need, uint32_t &tau,
+                                            uint32_t &equal, uint32_t *hist, uint32_t *part, uint32_t *out, int tid,
+                                            int lane, int wv)
+{
+    if (cnt <= (uint32_t)kPairs) {
+        rank_in_pairs(lkey, (int)cnt, need, out, tid);
+        tau = out[0];
+        need = out[1];
+        equal = out[2];
+        return true;
+    }
+    tau = 0u;                            // radix select over the listed keys, 11 bits a sweep
+    equal = cnt;
+    for (int left = 32; left > 0;) {
+        const int low = left > 11 ? left - 11 : 0;
+        hist[tid] = 0;
+        hist[tid + kBudgetBlock] = 0;
+        __syncthreads();
+        for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
+            const uint32_t key = lkey[r];
+            if (left == 32 || (key >> left) == (tau >> left)) atomicAdd(&hist[(key >> low) & 2047u], 1u);
+        }
+        __syncthreads();
+        find_bin_block<kBudgetBlock>(hist, need, part, out, tid, lane, wv);
+        tau |= out[0] << low;
+        need = out[1];
+        equal = out[2];
+        left = low;
+        __syncthreads();
+    }
+    return equal == need;
+}
+
+// Whether entry r of the list is among the winners that cut_of_list() cut off: of the entries equal to the
+// cut the `need` with the lowest indices are.
+__device__ __forceinline__ bool list_wins(const uint32_t *lkey, const uint32_t *lidx, uint32_t cnt, int r, uint32_t tau,
+                                          uint32_t need, uint32_t equal)
+{
+    const uint32_t key = lkey[r], j = lidx[r];
+    if (key != tau || equal == need) return key >= tau;
+    uint32_t rank = 0;
+    for (int u = 0; u < (int)cnt; ++u) rank += lkey[u] == tau && lidx[u] < j;
+    return rank < need;
+}
+
 // Indices of the k set bits of a bitmap in LDS -> out, ascending.  A thread owns a run of words: it
 // counts their bits, one scan over the workgroup places the run, and it writes the run's indices.  A bitmap
 // with another number of bits is left alone (false, the same for every thread).
@@ -884,49 +933,190 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_long_kernel(
     }
     // the need-th largest of the list
     uint32_t tau, equal;
-    if (cnt <= (uint32_t)kPairs) {
-        rank_in_pairs(lkey, (int)cnt, need, s_out, tid);
-        tau = s_out[0];
-        need = s_out[1];
-        equal = s_out[2];
-    } else {                             // radix select over the listed keys, 11 bits a sweep
-        tau = 0u;
-        equal = cnt;
-        for (int left = 32; left > 0;) {
-            const int low = left > 11 ? left - 11 : 0;
-            hist[tid] = 0;
-            hist[tid + kBudgetBlock] = 0;
-            __syncthreads();
-            for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
-                const uint32_t key = lkey[r];
-                if (left == 32 || (key >> left) == (tau >> left)) atomicAdd(&hist[(key >> low) & 2047u], 1u);
-            }
-            __syncthreads();
-            find_bin_block<kBudgetBlock>(hist, need, s_part[1], s_out, tid, lane, wv);
-            tau |= s_out[0] << low;
-            need = s_out[1];
-            equal = s_out[2];
-            left = low;
-            __syncthreads();
-        }
-    }
-    if (equal != need && cnt > (uint32_t)kPairs) {   // many ties straddle the cut
+    if (!cut_of_list(lkey, cnt, need, tau, equal, hist, s_part[1], s_out, tid, lane, wv)) {
         topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
         return;
     }
     for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
-        const uint32_t key = lkey[r], j = lidx[r];
-        bool in = key > tau || (key == tau && equal == need);
-        if (key == tau && equal != need) {           // the lowest indices of those equal to the cut
-            uint32_t rank = 0;
-            for (int u = 0; u < (int)cnt; ++u) rank += lkey[u] == tau && lidx[u] < j;
-            in = rank < need;
-        }
-        if (in) atomicOr(reinterpret_cast<uint32_t *>(map) + (j >> 5), 1u << (j & 31u));
+        const uint32_t j = lidx[r];
+        if (list_wins(lkey, lidx, cnt, r, tau, need, equal))
+            atomicOr(reinterpret_cast<uint32_t *>(map) + (j >> 5), 1u << (j & 31u));
     }
     __syncthreads();
     if (!emit_bitmap<NW>(map, words, k, s_part[0], out, tid, lane, wv))   // NaN counted above the bin and not marked
         topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
+}
+
+// Few long rows: a row's entries are shared out to workgroups of kSegment entries, in two launches.  One
+// compute unit alone spends its time on the row's vector instructions and LDS atomics (131072 entries are 512
+// wave-wide entries per SIMD, each a dozen instructions over two reads).  The first launch counts a segment's
+// keys into 2048 bins over the range of a coarse sample of the row (the same in every workgroup of a row; keys
+// outside go to the end bins) and sorts its entries by bin.  In the second, every workgroup adds up the row's
+// counts, finds the bin of the cut, fetches that bin's entries from all segments (they lie side by side in
+// each), cuts them as above, and writes the winners of its own segment: their places start behind the winners
+// of the segments before it, which the counts and the list give.  A row whose cut falls among too many equal
+// or nearly equal values goes through the general algorithm, by its first workgroup.  What is left is two launches
+// and their chains of loads.  (8 rows of 131008 entries: 32.8 us with one workgroup a row, 12.3 us this way.)
+constexpr int kSegment = 8 * kBudgetBlock;
+constexpr int kMaxSegments = 32;
+
+struct SplitScratch {
+    uint4 *range;      // [rows] kmin, kmax, shift of the bins
+    uint16_t *above;   // [rows, segments, 2048] entries of the segment in higher bins
+    uint16_t *order;   // [rows, segments, kSegment] places in the segment, highest bin first
+};
+
+__global__ __launch_bounds__(kBudgetBlock) void split_count_kernel(const float *__restrict__ x, int n, SplitScratch sc)
+{
+    constexpr int NW = kBudgetBlock / kWave, SAMPLE = 4, ITEMS = kSegment / kBudgetBlock;
+    __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
+    __shared__ __align__(16) uint16_t order[kSegment];
+    __shared__ uint32_t s_part[NW], s_min[NW], s_max[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x, seg = blockIdx.y;
+    const int words = (n + kWave - 1) / kWave, base = seg * kSegment;
+    const float *xr = x + (long)row * n;
+    float v[SAMPLE], val[ITEMS];
+#pragma unroll
+    for (int i = 0; i < SAMPLE; ++i)   // stretches of 64 entries, evenly spread
+        v[i] = xr[(int)((long)(i * NW + wv) * (words - 1) / (SAMPLE * NW)) * kWave + lane];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(base + i * kBudgetBlock + tid, n - 1)];
+    hist[tid] = 0;
+    hist[tid + kBudgetBlock] = 0;
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+    for (int i = 0; i < SAMPLE; ++i) {
+        const uint32_t key = ord_key(v[i]);
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+    }
+    kmin = wave_min_u32(kmin);
+    kmax = wave_max_u32(kmax);
+    if (lane == 0) { s_min[wv] = kmin; s_max[wv] = kmax; }
+    __syncthreads();
+    kmin = wave_min_u32(s_min[lane & (NW - 1)]);
+    kmax = wave_max_u32(s_max[lane & (NW - 1)]);
+    const int bits = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, shift = bits > 11 ? bits - 11 : 0;
+    if (seg == 0 && tid == 0) sc.range[row] = make_uint4(kmin, kmax, (uint32_t)shift, 0u);
+    uint32_t bin[ITEMS], at[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        bin[i] = (min(max(ord_key(val[i]), kmin), kmax) - kmin) >> shift;
+        at[i] = base + i * kBudgetBlock + tid < n ? atomicAdd(&hist[bin[i]], 1u) : 0u;
+    }
+    __syncthreads();
+    // thread t owns two bins, the highest pair first
+    const int hi = 2 * (kBudgetBlock - 1 - tid);
+    const uint2 c = *reinterpret_cast<const uint2 *>(hist + hi);
+    uint32_t total;
+    const uint32_t higher = block_scan_add<NW>(c.x + c.y, s_part, lane, wv, total);
+    *reinterpret_cast<uint2 *>(hist + hi) = make_uint2(higher + c.y, higher);
+    const long part = (long)row * gridDim.y + seg;
+    reinterpret_cast<uint32_t *>(sc.above + part * 2 * kBudgetBlock)[hi >> 1] = (higher + c.y) | higher << 16;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (base + i * kBudgetBlock + tid < n) order[hist[bin[i]] + at[i]] = (uint16_t)(i * kBudgetBlock + tid);
+    __syncthreads();
+    // (behind the row's end: whatever the LDS holds, never read)
+    reinterpret_cast<uint4 *>(sc.order + part * kSegment)[tid] = reinterpret_cast<const uint4 *>(order)[tid];
+}
+
+__global__ __launch_bounds__(kBudgetBlock) void split_select_kernel(
+    const float *__restrict__ x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, SplitScratch sc,
+    LayerPlan plan)
+{
+    constexpr int NW = kBudgetBlock / kWave, ITEMS = kSegment / kBudgetBlock, BINS = 2 * kBudgetBlock;
+    extern __shared__ __align__(16) uint32_t dyn[];
+    __shared__ __align__(16) uint32_t hist[BINS];
+    __shared__ uint64_t map[kSegment / kWave];
+    __shared__ uint32_t s_part[2][NW], s_out[3], s_off[kMaxSegments], s_end[kMaxSegments], s_base[kMaxSegments], s_before;
+    uint32_t *lkey = dyn, *lidx = dyn + kBudgetList;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x, seg = blockIdx.y, segs = gridDim.y;
+    const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer, base = seg * kSegment;
+    const int k = plan.budget[g] - append_count;
+    int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
+    const float *xr = x + (long)row * n;
+    const uint16_t *above = sc.above + (long)row * segs * BINS;
+    const uint4 range = sc.range[row];
+    float val[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(base + i * kBudgetBlock + tid, n - 1)];
+    // the row's entries above each bin: thread t owns bins 2 t and 2 t + 1
+    uint32_t lo = 0, hi = 0;
+    for (int s0 = 0; s0 < segs; s0 += 8) {   // (the loads of eight segments leave together)
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const uint32_t *>(above + (long)min(s0 + u, segs - 1) * BINS)[tid];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s0 + u < segs) { lo += v[u] & 0xffffu; hi += v[u] >> 16; }
+    }
+    hist[2 * tid] = lo;
+    hist[2 * tid + 1] = hi;
+    __syncthreads();
+    const uint32_t below = tid ? hist[2 * tid - 1] : (uint32_t)n, need_k = (uint32_t)k;
+    if (lo < need_k && need_k <= below) { s_out[0] = 2 * tid; s_out[1] = need_k - lo; s_out[2] = below - lo; }
+    if (hi < need_k && need_k <= lo) { s_out[0] = 2 * tid + 1; s_out[1] = need_k - hi; s_out[2] = lo - hi; }
+    __syncthreads();
+    const uint32_t bin = s_out[0], cnt = s_out[2];
+    uint32_t need = s_out[1];
+    auto general = [&] {
+        if (seg == 0)
+            topk_stream_row<kBudgetBlock, true>(row, x, n, n, 0, idx_out, 0, nullptr, 0, append_from, append_count, plan);
+    };
+    if (cnt > (uint32_t)kBudgetList) {   // (the same for every thread and workgroup of the row)
+        general();
+        return;
+    }
+    if (wv == 0) {   // where the bin's entries lie in every segment and in the list, and the winners above it before this one
+        const int s = min(lane, segs - 1);
+        const uint32_t o = above[(long)s * BINS + bin];
+        const uint32_t e = bin ? above[(long)s * BINS + bin - 1] : (uint32_t)min(kSegment, n - s * kSegment);
+        const uint32_t here = lane < segs ? e - o : 0u, incl = wave_scan_add(here);
+        const uint32_t before = wave_sum_u32(lane < seg ? o : 0u);
+        if (lane < segs) { s_off[lane] = o; s_end[lane] = e; s_base[lane] = incl - here; }
+        if (lane == 0) s_before = before;
+    }
+    if (tid < 4) lkey[min(cnt + (uint32_t)tid, (uint32_t)kBudgetList - 1u)] = 0u;   // padding for reads of four
+    __syncthreads();
+    for (int s = wv; s < segs; s += NW) {
+        const uint16_t *o = sc.order + ((long)row * segs + s) * kSegment;
+        for (uint32_t l = s_off[s] + lane; l < s_end[s]; l += kWave) {
+            const int j = s * kSegment + o[l];
+            const uint32_t to = s_base[s] + l - s_off[s];
+            lkey[to] = ord_key(xr[j]);
+            lidx[to] = (uint32_t)j;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool in = base + i * kBudgetBlock + tid < n;
+        const uint32_t b = (min(max(ord_key(val[i]), range.x), range.y) - range.x) >> range.z;
+        const uint64_t over = __ballot(in && b > bin);
+        if (lane == 0) map[i * NW + wv] = over;
+    }
+    __syncthreads();
+    uint32_t tau, equal;
+    if (!cut_of_list(lkey, cnt, need, tau, equal, hist, s_part[1], s_out, tid, lane, wv)) {
+        general();
+        return;
+    }
+    for (int r = tid; r < (int)cnt; r += kBudgetBlock) {
+        const int j = (int)lidx[r];
+        if (j < base + kSegment && list_wins(lkey, lidx, cnt, r, tau, need, equal)) {
+            if (j < base) atomicAdd(&s_before, 1u);
+            else atomicOr(reinterpret_cast<uint32_t *>(map) + ((j - base) >> 5), 1u << (j & 31));
+        }
+    }
+    __syncthreads();
+    // a thread writes the winners among eight neighbours
+    uint32_t eight = reinterpret_cast<const uint8_t *>(map)[tid], total;
+    int32_t *o = out + s_before + block_scan_add<NW>((uint32_t)__popc(eight), s_part[0], lane, wv, total);
+    for (int j = base + 8 * tid; eight; eight >>= 1, ++j)
+        if (eight & 1u) *o++ = j;
+    if (seg == 0)
+        for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
 }
 
 // ---- neighbourhoods of heads whose candidate lists overflowed ------------------------
@@ -1118,6 +1308,7 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
 
 // Row length up to which the budgeted selection keeps a bitmap of the row in LDS.
 constexpr int kBitmapRow = 1 << 18;
+static_assert(kBitmapRow <= kMaxSegments * kSegment, "segments of a row");
 
 template <int D>
 static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
@@ -1139,8 +1330,24 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
     return hipGetLastError();
 }
 
+// Segments of a row that is shared out (0: it is not): rows longer than the kernels that hold one in registers
+// take, up to the longest with a bitmap in LDS, as long as there are no more workgroups than compute units, or
+// twice as many from eight segments on (us, one workgroup a row / split: 8 rows of 40000 entries 16.6 / 11.9,
+// 64 17.1 / 18.3; 8 of 131008 32.8 / 12.3, 32 33.7 / 22.4, 64 34.5 / 41.2; 16 of 262144 56.6 / 25.0).
+static int split_segments(int rows, int P)
+{
+    const int segs = (P + kSegment - 1) / kSegment;
+    return P > 32768 && P <= kBitmapRow && (long)rows * segs <= (segs >= 8 ? 512 : 256) ? segs : 0;
+}
+
+size_t topk_final_scratch_bytes(int rows, int P)
+{
+    return (size_t)rows * split_segments(rows, P) * (2 * kBudgetBlock + kSegment) * sizeof(uint16_t) +
+           (split_segments(rows, P) ? (size_t)rows * sizeof(uint4) : 0);
+}
+
 hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
-                             const DecayArgs &update, hipStream_t st)
+                             const DecayArgs &update, void *scratch, hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;
     if (P <= 32768) {
@@ -1153,6 +1360,19 @@ hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &pl
         }
     }
     if (update.items) return hipErrorInvalidValue;
+    const int segs = scratch ? split_segments(rows, P) : 0;
+    if (segs) {
+        SplitScratch sc;
+        sc.range = reinterpret_cast<uint4 *>(scratch);
+        sc.above = reinterpret_cast<uint16_t *>(sc.range + rows);
+        sc.order = sc.above + (size_t)rows * segs * 2 * kBudgetBlock;
+        if (!allow_big_lds((const void *)split_select_kernel, 140 * 1024)) return hipGetLastError();
+        // (a row's workgroups `rows` apart in both launches: with 8 rows each stays on one XCD)
+        hipLaunchKernelGGL(split_count_kernel, dim3(rows, segs), dim3(kBudgetBlock), 0, st, scores, P, sc);
+        hipLaunchKernelGGL(split_select_kernel, dim3(rows, segs), dim3(kBudgetBlock), (size_t)kBudgetList * 8, st, scores, P,
+                           idx, P, w, sc, plan);
+        return hipGetLastError();
+    }
     if (P <= kBitmapRow) {
         if (!allow_big_lds((const void *)budget_select_long_kernel, 140 * 1024)) return hipGetLastError();
         const size_t words = (size_t)(P + kWave - 1) / kWave;

@@ -1,0 +1,71 @@
+"""Routes that a call takes by its sizes give the results of the general ones (GPU)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_00388_amd import binding as gk
+from tests.test_gpu_parity import key_order, rows_with_nan
+
+pytestmark = pytest.mark.gpu
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+def select_scratch(p):
+    cp = p.c()
+    return int(gk.load_library().graphkv_select_workspace_bytes(ctypes.byref(cp)))
+
+
+# (a segment is 8192 entries: rows that fill their last one, that leave one entry for it, the longest row)
+@pytest.mark.parametrize("P,k", [(32769, 1), (40960, 40959), (40961, 2000), (131008, 32768), (1 << 18, 4000)])
+def test_long_rows_shared_out(P, k):
+    """The budgeted selection of few long rows by many workgroups, against one workgroup a row (which is what
+    a call without workspace takes) and against the order of the keys."""
+    say(f"selection shared out P={P} k={k}")
+    rng = np.random.default_rng(P + k)
+    w = 3
+    s = rows_with_nan(P, k, P ^ k)
+    s = np.concatenate([s, rng.standard_normal((5, P)).astype(np.float32)])
+    s[10, ::3] = 0.0
+    s[10, 1::3] = -0.0
+    s[11] = rng.integers(0, 40, P)                                  # ties in every segment
+    s[12, rng.choice(P, size=min(P, k + 5), replace=False)] = 9.0   # the cut among equal values
+    s[13] = 1.0 + np.arange(P, dtype=np.float32) * np.float32(1e-7)  # neighbouring values, all in few bins
+    s = s[:max(1, 256 // -(-P // 8192))]
+    H = s.shape[0]
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=8, n_tokens=P + w, window=w, budget=k + w)
+    assert select_scratch(p) > 0
+    x = torch.from_numpy(s).cuda()
+    none = torch.empty(256, dtype=torch.uint8, device="cuda")
+    one = gk.graphkv_select(p, x, torch.full((H, k + w), -7, dtype=torch.int32, device="cuda"), none).cpu().numpy()
+    for _ in range(2):
+        ws = torch.randint(0, 256, (select_scratch(p),), dtype=torch.uint8, device="cuda")
+        idx = gk.graphkv_select(p, x, torch.full((H, k + w), -7, dtype=torch.int32, device="cuda"), ws).cpu().numpy()
+        assert np.array_equal(idx, one)
+    for h in range(H):
+        assert np.array_equal(idx[h, :k], key_order(s[h], k)), f"row {h}"
+        assert np.array_equal(idx[h, k:], np.arange(P, P + w))
+
+
+def test_long_rows_shared_out_in_a_whole_pass():
+    """A layer of a long prompt: its final selection is shared out, that of the same layer in a batch whose heads
+    fill the chip is not."""
+    say("whole pass with a long row, alone and in a batch")
+    L, H, N, d, w, B = 65, 4, 33000, 8, 4, 700
+    g = torch.Generator("cuda").manual_seed(5)
+    K = torch.randn(L, H, N, d, generator=g, device="cuda")
+    V = torch.randn(L, H, N, d, generator=g, device="cuda")
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=B, dtype=gk.FP32,
+                  scorer=gk.SCORER_KNORM)
+    Ks, Vs, idx = gk.graphkv_compress_batched(p, L, None, K, V, None)
+    for l in (0, L - 1):
+        K1, V1, i1 = gk.graphkv_compress(p, K[l], V[l], None)
+        at = slice(l * H * B, (l + 1) * H * B)
+        assert torch.equal(i1.flatten(), idx[at])
+        assert torch.equal(K1.view(-1, d), Ks[at]) and torch.equal(V1.view(-1, d), Vs[at])
+        ref = K[l, :, :N - w].double().norm(dim=2).neg().topk(B - w, dim=1).indices.sort(dim=1).values
+        assert (i1[:, :B - w] == ref).float().mean() > 0.99
