@@ -48,6 +48,43 @@ template <> struct CellOf<uint64_t> {
     }
 };
 
+// Product of the factors of the chain that ends with triple t (edge e), in ascending triples; edge_of(u) = edge of
+// triple u, whatever lies beyond the last one for any other u.
+template <typename EdgeOf>
+__device__ __forceinline__ float chain_factor(int t, float e, const uint16_t *next, bool neg, float alpha, int signal,
+                                              EdgeOf &&edge_of)
+{
+    float f = 1.0f;
+    if (next[t] == kChainEnd) {
+        f *= signal_factor(e, alpha, signal, neg);
+        return f;
+    }
+    // the chain's triples in ascending order, the next kLinks of them by each walk
+    for (uint32_t from = 0, last = 0; last != kChainEnd;) {
+        uint32_t low[kLinks];
+#pragma unroll
+        for (int i = 0; i < kLinks; ++i) low[i] = kChainEnd;
+        for (uint32_t u = (uint32_t)t; u != kChainEnd; u = next[u]) {
+            uint32_t x = u >= from ? u : kChainEnd;
+#pragma unroll
+            for (int i = 0; i < kLinks; ++i) {
+                const uint32_t keep = min(low[i], x);
+                x = max(low[i], x);
+                low[i] = keep;
+            }
+        }
+        float el[kLinks];
+#pragma unroll
+        for (int i = 0; i < kLinks; ++i) el[i] = edge_of(low[i]);
+#pragma unroll
+        for (int i = 0; i < kLinks; ++i)
+            if (low[i] != kChainEnd) f *= signal_factor(el[i], alpha, signal, neg);
+        last = low[kLinks - 1];
+        from = last + 1;
+    }
+    return f;
+}
+
 // Bytes of dynamic LDS: cells, edges (unless they stay in global memory), links.
 template <typename Cell> size_t decay_chain_lds(int cells, int slots, bool edges)
 {
@@ -129,41 +166,97 @@ __device__ __forceinline__ void decay_chain(float *s, int count, int cells, cons
             const int q = q0 + b, t = q * BLOCK + tid;
             if (!head[b]) continue;
             if (signal == 2) { s[node[q]] = -INFINITY; continue; }
-            const bool neg = sj[b] < 0.f;
-            float f = 1.0f;
-            if (next[t] == kChainEnd) {
-                f *= signal_factor(e[b], alpha, signal, neg);
-            } else {
-                // the chain's triples in ascending order, the next kLinks of them by each walk
-                for (uint32_t from = 0, last = 0; last != kChainEnd;) {
-                    uint32_t low[kLinks];
-#pragma unroll
-                    for (int i = 0; i < kLinks; ++i) low[i] = kChainEnd;
-                    for (uint32_t u = (uint32_t)t; u != kChainEnd; u = next[u]) {
-                        uint32_t x = u >= from ? u : kChainEnd;
-#pragma unroll
-                        for (int i = 0; i < kLinks; ++i) {
-                            const uint32_t keep = min(low[i], x);
-                            x = max(low[i], x);
-                            low[i] = keep;
-                        }
-                    }
-                    float el[kLinks];
-#pragma unroll
-                    for (int i = 0; i < kLinks; ++i) {
-                        const uint32_t u = min(low[i], (uint32_t)count - 1u);
-                        el[i] = EDGES ? edge[u] : ne[u];
-                    }
-#pragma unroll
-                    for (int i = 0; i < kLinks; ++i)
-                        if (low[i] != kChainEnd) f *= signal_factor(el[i], alpha, signal, neg);
-                    last = low[kLinks - 1];
-                    from = last + 1;
-                }
-            }
+            const float f = chain_factor(t, e[b], next, sj[b] < 0.f, alpha, signal, [&](uint32_t u) {
+                const uint32_t in = min(u, (uint32_t)count - 1u);
+                return EDGES ? edge[in] : ne[in];
+            });
             s[node[q]] = sj[b] * f;
         }
     }
+}
+
+// The same update in front of a kernel that holds the head's row in registers, entry i of thread tid being node
+// i * 1024 + tid: D triples per thread, P <= 1024 ITEMS <= 32768.  A table in LDS with a word per node takes the
+// place of the hash table (only the words of the triples' nodes are ever set), so a link is one exchange; the new
+// scores go to memory and, through the table, into the registers that hold the old ones.  Returns with a barrier,
+// behind which `mem` is free.  (Hash chains, then a read of the row: the row was ready 7.6 us into a workgroup with
+// 32736 nodes and 2048 triples, 5.6 with 16384; this way 4.8 and 4.5, of which the row's own 128 KiB take 2.)
+constexpr int kUpdateBlock = 1024;
+template <int ITEMS, int D> constexpr size_t update_row_lds()   // table, marks, edges (4 per thread stay in memory), links
+{
+    return D ? (size_t)kUpdateBlock * (4 * ITEMS + 4 + (D < 4 ? 4 * D : 0) + 2 * D) : 0;
+}
+
+// The thread's triples; asked for in front of the row, which takes longer.
+template <int D> struct Triples {
+    uint32_t node[D > 0 ? D : 1];   // node and edge of triple q * kUpdateBlock + tid
+    float e[D > 0 ? D : 1];
+    __device__ __forceinline__ void load(const DecayArgs &u, int h, int tid)   // (unconditional, clamped)
+    {
+#pragma unroll
+        for (int q = 0; q < D; ++q) node[q] = (uint32_t)u.nbr[(long)h * u.count + min(q * kUpdateBlock + tid, u.count - 1)];
+#pragma unroll
+        for (int q = 0; q < D; ++q) e[q] = u.nbr_e[(long)h * u.count + min(q * kUpdateBlock + tid, u.count - 1)];
+    }
+};
+
+template <int ITEMS, int D>
+__device__ __forceinline__ void update_row(float (&val)[ITEMS], const Triples<D> &tri, float *xr, int h, const DecayArgs &u,
+                                           unsigned char *mem, int tid)
+{
+    constexpr int BLOCK = kUpdateBlock;
+    constexpr bool EDGES = D < 4;
+    static_assert(ITEMS <= 32, "one mark per entry of a thread");
+    uint32_t *cell = reinterpret_cast<uint32_t *>(mem);                 // [BLOCK * ITEMS] by node
+    uint32_t *mark = cell + BLOCK * ITEMS;                              // [BLOCK] bit i: entry i of the thread is new
+    float *edge = reinterpret_cast<float *>(mark + BLOCK);              // [BLOCK * D] if EDGES
+    uint16_t *next = reinterpret_cast<uint16_t *>(edge + (EDGES ? BLOCK * D : 0));
+    const float *ne = u.nbr_e + (long)h * u.count;
+    const uint32_t (&node)[D] = tri.node;
+    const float (&e)[D] = tri.e;
+    uint32_t link[D];
+    float sj[D];
+    bool head[D];
+    mark[tid] = 0;
+#pragma unroll
+    for (int q = 0; q < D; ++q) cell[node[q]] = kChainEnd;   // (clamped triples set their last one's again)
+#pragma unroll
+    for (int q = 0; q < D; ++q) sj[q] = xr[node[q]];
+    if (EDGES) {
+#pragma unroll
+        for (int q = 0; q < D; ++q) edge[q * BLOCK + tid] = e[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < D; ++q)
+        link[q] = q * BLOCK + tid < u.count ? atomicExch(&cell[node[q]], (uint32_t)(q * BLOCK + tid)) : kChainEnd;
+#pragma unroll
+    for (int q = 0; q < D; ++q) next[q * BLOCK + tid] = (uint16_t)link[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < D; ++q) head[q] = q * BLOCK + tid < u.count && cell[node[q]] == (uint32_t)(q * BLOCK + tid);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+        if (!head[q]) continue;
+        float now = -INFINITY;
+        if (u.signal != 2)
+            now = sj[q] * chain_factor(q * BLOCK + tid, e[q], next, sj[q] < 0.f, u.alpha, u.signal, [&](uint32_t t) {
+                      const uint32_t in = min(t, (uint32_t)u.count - 1u);
+                      return EDGES ? edge[in] : ne[in];
+                  });
+        xr[node[q]] = now;
+        cell[node[q]] = __float_as_uint(now);
+        atomicOr(&mark[node[q] & (BLOCK - 1)], 1u << (node[q] / BLOCK));
+    }
+    __syncthreads();
+    const uint32_t fresh = mark[tid];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const float now = __uint_as_float(cell[i * BLOCK + tid]);
+        val[i] = (fresh >> i) & 1u ? now : val[i];
+    }
+    __syncthreads();
 }
 
 }  // namespace gkv

@@ -1,6 +1,7 @@
 // From the second round on: where each source gets its neighbour list from.
 #pragma once
 #include "common.hpp"
+#include "decay.hpp"
 #include "kernels.hpp"
 
 namespace gkv {
@@ -38,9 +39,53 @@ __device__ __forceinline__ bool match_load(const MatchArgs &a, int h, int32_t *l
     return bad;
 }
 
-// (A barrier lies between match_load() and this.)
+// The lists that stay are copied: the neighbourhood of a source does not depend on the scores.  Lists that the
+// thread holds already (the triples of the update that rode along: entry q * kMatchBlock + tid of the previous
+// round's lists) are not read again.
+template <int D>
+__device__ __forceinline__ void match_copy(const MatchArgs &a, int h, const int32_t *code_s, const int32_t *to_s,
+                                           const Triples<D> &tri, int tid)
+{
+    const long row0 = (long)h * a.S;
+    const int entries = a.S * a.m;   // (lists are kept for S <= 4096 and m <= 1024)
+    if constexpr (D > 0) {
+#pragma unroll
+        for (int q = 0; q < D; ++q) {
+            const int u = q * kMatchBlock + tid, s = min(u, entries - 1) / a.m, to = to_s[s];
+            if (u < entries && to >= 0) {
+                a.nbr[(row0 + to) * a.m + (u - s * a.m)] = (int32_t)tri.node[q];
+                a.nbr_e[(row0 + to) * a.m + (u - s * a.m)] = tri.e[q];
+            }
+        }
+        return;
+    }
+    for (int u0 = tid; u0 < entries; u0 += 4 * kMatchBlock) {
+        int32_t n[4];
+        float e[4];
+        bool kept[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {   // (loads of four entries leave together)
+            const int u = min(u0 + v * kMatchBlock, entries - 1), s = u / a.m;
+            const int from = code_s[s];
+            const long at = (row0 + max(from, 0)) * a.m + (u - s * a.m);
+            kept[v] = u0 + v * kMatchBlock < entries && from >= 0;
+            n[v] = a.prev_nbr[at];
+            e[v] = a.prev_e[at];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (kept[v]) {
+                a.nbr[row0 * a.m + u0 + v * kMatchBlock] = n[v];
+                a.nbr_e[row0 * a.m + u0 + v * kMatchBlock] = e[v];
+            }
+    }
+}
+
+// (A barrier lies between match_load() and this; to_s [S] is set to -1 in front of it if D > 0.)
+template <int D>
 __device__ __forceinline__ void match_head(const MatchArgs &a, int h, bool bad, const int32_t *cur, int32_t *lds,
-                                           int32_t *wave_new, int32_t *wave_fb, int tid)
+                                           int32_t *to_s, int32_t *wave_new, int32_t *wave_fb, const Triples<D> &tri,
+                                           int tid)
 {
     constexpr int NW = kMatchBlock / kWave;
     const int S = a.S, X = a.X, lane = tid & 63, wv = tid >> 6;
@@ -79,6 +124,7 @@ __device__ __forceinline__ void match_head(const MatchArgs &a, int h, bool bad, 
             total_fb += wave_fb[u];
         }
         if (s < S) code_s[s] = found;
+        if (D > 0 && found >= 0) to_s[found] = s;
         if (is_new) {
             const int x = before + (int)votes_below(mask);
             int crow = S + spec_at;
@@ -98,28 +144,7 @@ __device__ __forceinline__ void match_head(const MatchArgs &a, int h, bool bad, 
         a.n_new[h] = base_fb;
         a.n_sel[h] = base;
     }
-    // the lists that stay: the neighbourhood of a source does not depend on the scores
-    const int entries = S * a.m;   // (lists are kept for S <= 4096 and m <= 1024)
-    for (int u0 = tid; u0 < entries; u0 += 4 * kMatchBlock) {
-        int32_t n[4];
-        float e[4];
-        bool kept[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {   // (loads of four entries leave together)
-            const int u = min(u0 + v * kMatchBlock, entries - 1), s = u / a.m;
-            const int from = code_s[s];
-            const long at = (row0 + max(from, 0)) * a.m + (u - s * a.m);
-            kept[v] = u0 + v * kMatchBlock < entries && from >= 0;
-            n[v] = a.prev_nbr[at];
-            e[v] = a.prev_e[at];
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (kept[v]) {
-                a.nbr[row0 * a.m + u0 + v * kMatchBlock] = n[v];
-                a.nbr_e[row0 * a.m + u0 + v * kMatchBlock] = e[v];
-            }
-    }
+    match_copy<D>(a, h, code_s, to_s, tri, tid);
 }
 
 }  // namespace gkv

@@ -1009,7 +1009,8 @@ __global__ __launch_bounds__(kMatchBlock) void match_sources_kernel(MatchArgs a,
     __shared__ int32_t wave_new[kMatchBlock / kWave], wave_fb[kMatchBlock / kWave];
     const bool bad = match_load(a, blockIdx.x, match_lds, threadIdx.x);
     __syncthreads();
-    match_head(a, blockIdx.x, bad, cur + (long)blockIdx.x * a.S, match_lds, wave_new, wave_fb, threadIdx.x);
+    match_head<0>(a, blockIdx.x, bad, cur + (long)blockIdx.x * a.S, match_lds, nullptr, wave_new, wave_fb, Triples<0>{},
+                  threadIdx.x);
 }
 
 // Columns per workgroup: about 1024 workgroups in flight over all heads and source

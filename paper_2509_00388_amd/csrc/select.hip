@@ -380,8 +380,8 @@ __device__ __forceinline__ void row_sweep(const float *__restrict__ xr, int n, i
 // and LDS round trips.  Rows of up to 32768 entries are read once into registers, longer ones
 // twice.  (A group bound through LDS maxima, a radix sweep and one wave that finished the row
 // alone, bit by bit: 21.4 us with k = 96 and 16.4 us with k = 64 for 8 rows of 32736 entries;
-// this way 9.8 and 8.2 us; 256 rows of
-// 131008 entries with k = 192 and k = 128: 72 and 58 us before, 56 and 49 us now.)
+// this way 9.8 and 8.2 us, 7.7 and 6.2 since floats are compared and several threads share
+// an entry's rank; 256 rows of 131008 entries with k = 192 and k = 128: 72 and 58 us before, 56 and 49 us now.)
 //
 // The same code takes the m best edges of a source from its row of the dense edge block (Eq. 3): 256
 // threads per row of up to 8192 edges, no split, the edges' values beside their indices.  (Three LDS
@@ -435,37 +435,71 @@ __device__ __forceinline__ uint32_t kth_value_bound(uint32_t best, int k, PickLd
     return kmin + (L.out[0] << shift);
 }
 
-// The list of cnt >= k entries (zeros behind them) -> the row's outputs.
-template <int BLOCK, bool EDGES>
-__device__ __forceinline__ void emit_winners(PickLds<BLOCK> &L, int cnt, int k, const PickOut &o, int tid)
+// Sum over groups of 2^LOG neighbouring lanes (LOG <= 3), in every lane of the group.
+template <int LOG> __device__ __forceinline__ int lane_group_sum(int v)
 {
-    for (int t = tid; t < cnt; t += BLOCK) {
-        const uint64_t mine = L.list[t];
+#define GKV_DPP(ctrl) __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, false)
+    if constexpr (LOG > 0) v += GKV_DPP(0xb1);    // quad_perm: the neighbour
+    if constexpr (LOG > 1) v += GKV_DPP(0x4e);    // quad_perm: the other pair
+    if constexpr (LOG > 2) v += GKV_DPP(0x141);   // row_half_mirror: the other four
+#undef GKV_DPP
+    return v;
+}
+
+// Ranks of the cnt listed entries -> win (and val): 2^LOG neighbouring threads share an entry.
+template <int BLOCK, int LOG, bool EDGES>
+__device__ __forceinline__ void rank_winners(PickLds<BLOCK> &L, int cnt, int k, int tid)
+{
+    constexpr int G = 1 << LOG;
+    for (int t0 = 0; t0 < cnt; t0 += BLOCK / G) {   // (once if the entries fit)
+        const int t = t0 + tid / G;
+        const uint64_t mine = L.list[min(t, kPickList - 1)];
         int rank = 0;
-        for (int u = 0; u < cnt; u += 2) {
+        for (int u = 2 * (tid % G); u < cnt; u += 2 * G) {
             const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(L.list + u);
             rank += (v.x > mine) + (v.y > mine);
         }
-        if (rank < k) {
+        rank = lane_group_sum<LOG>(rank);
+        if (tid % G == 0 && t < cnt && rank < k) {
             L.win[rank] = ~(uint32_t)mine;
             if (EDGES) L.val[rank] = (uint32_t)(mine >> 32);
         }
     }
     __syncthreads();
-    if (tid < k) {
-        const uint32_t mine = L.win[tid];
-        if (EDGES) {
-            int at = 0;
-            for (int u = 0; u < k; ++u) at += L.win[u] < mine;
-            o.src[at] = (int32_t)mine;
-            o.val[at] = key_to_float(L.val[tid]);
-        } else {
-            int at = tid < o.S ? 0 : o.S;
-            for (int u = 0; u < k; ++u) at += L.win[u] < mine && (u < o.S) == (tid < o.S);
-            if (at < o.S) o.src[at] = (int32_t)mine;
-            if (o.ext) o.ext[at] = (int32_t)mine;
+}
+
+// The k winners -> the row's outputs, by index within their group (the S best, the others).
+template <int BLOCK, int LOG, bool EDGES>
+__device__ __forceinline__ void place_winners(PickLds<BLOCK> &L, int k, const PickOut &o, int tid)
+{
+    constexpr int G = 1 << LOG;
+    for (int t0 = 0; t0 < k; t0 += BLOCK / G) {
+        const int t = min(t0 + tid / G, k - 1), from = EDGES || t < o.S ? 0 : o.S, to = EDGES || t >= o.S ? k : o.S;
+        const uint32_t mine = L.win[t];
+        int at = 0;
+        for (int u = from + tid % G; u < to; u += G) at += L.win[u] < mine;
+        at = from + lane_group_sum<LOG>(at);
+        if (tid % G == 0 && t0 + tid / G < k) {
+            if (EDGES) {
+                o.src[at] = (int32_t)mine;
+                o.val[at] = key_to_float(L.val[t]);
+            } else {
+                if (at < o.S) o.src[at] = (int32_t)mine;
+                if (o.ext) o.ext[at] = (int32_t)mine;
+            }
         }
     }
+}
+
+// The list of cnt >= k entries (zeros behind them) -> the row's outputs.
+template <int BLOCK, bool EDGES>
+__device__ __forceinline__ void emit_winners(PickLds<BLOCK> &L, int cnt, int k, const PickOut &o, int tid)
+{
+    if (cnt <= BLOCK / 8) rank_winners<BLOCK, 3, EDGES>(L, cnt, k, tid);
+    else if (cnt <= BLOCK / 2) rank_winners<BLOCK, 1, EDGES>(L, cnt, k, tid);
+    else rank_winners<BLOCK, 0, EDGES>(L, cnt, k, tid);
+    if (k <= BLOCK / 8) place_winners<BLOCK, 3, EDGES>(L, k, o, tid);
+    else place_winners<BLOCK, 2, EDGES>(L, k, o, tid);
 }
 
 // Masses of equal values: the general algorithm picks the k entries, the list holds just them.
@@ -482,56 +516,83 @@ __device__ __forceinline__ void pick_general(const float *xr, int n, int k, cons
     emit_winners<BLOCK, false>(L, k, k, o, tid);
 }
 
-// A row of at most ITEMS * BLOCK entries.
-template <int BLOCK, int ITEMS, bool EDGES>
-__device__ __forceinline__ void pick_row(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, int tid,
-                                         int lane, int wv)
+// A row of at most ITEMS * BLOCK entries (and, with ITEMS > 2, more than half as many), entry i of thread tid being
+// number i * BLOCK + tid: all its loads leave together, unconditional and clamped.
+template <int BLOCK, int ITEMS>
+__device__ __forceinline__ void load_row(const float *xr, int n, int tid, float (&val)[ITEMS])
 {
-    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
-    // the loads of the row leave together: unconditional, clamped, pinned before the first use
-    float val[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * BLOCK + tid, n - 1)];
+}
+
+// More than kPickList entries reach the bound: one histogram over all of them raises it, then the list or, with
+// masses of equal values, the general algorithm.  The row is read again.
+template <int BLOCK, bool EDGES>
+__device__ __forceinline__ void pick_again(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, uint32_t bound)
+{
+    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t mx = 0u;
+    for (int j = tid; j < n; j += BLOCK) mx = max(mx, ord_key(xr[j]));
+    mx = wave_max_u32(mx);
+    __syncthreads();
     L.clear(tid);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));
-    uint32_t key[ITEMS], best = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        key[i] = i * BLOCK + tid < n ? entry_key(val[i]) : 0u;
-        best = max(best, key[i]);
+    if (lane == 0) L.hi[wv] = mx;
+    __syncthreads();
+    mx = wave_max_u32(L.hi[lane & (NW - 1)]);
+    const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > BITS ? bits - BITS : 0;
+    for (int j = tid; j < n; j += BLOCK) {
+        const uint32_t key = ord_key(xr[j]);
+        if (key >= bound) atomicAdd(&L.hist[(key - bound) >> shift], 1u);
     }
-    uint32_t bound = kth_value_bound<BLOCK>(best, k, L, tid, lane, wv);
-    for (int turn = 0;; ++turn) {
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            if (key[i] >= bound) {
-                const uint32_t at = atomicAdd(&L.cnt, 1u);
-                if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key[i] << 32) | (uint32_t)~(i * BLOCK + tid);
-            }
-        __syncthreads();
-        const int cnt = (int)L.cnt;
-        if (cnt <= kPickList) {   // (the same for every thread, like all branches here)
-            emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
-            return;
+    __syncthreads();
+    find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+    bound += L.out[0] << shift;
+    for (int j = tid; j < n; j += BLOCK) {
+        const uint32_t key = ord_key(xr[j]);
+        if (key >= bound) {
+            const uint32_t at = atomicAdd(&L.cnt, 1u);
+            if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~j;
         }
-        if (turn) break;
-        // too many entries reach the bound: one histogram over all of them raises it
-        __syncthreads();
-        uint32_t mx = wave_max_u32(best);
-        if (lane == 0) L.hi[wv] = mx;
-        L.clear(tid);
-        __syncthreads();
-        mx = wave_max_u32(L.hi[lane & (NW - 1)]);
-        const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > BITS ? bits - BITS : 0;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            if (key[i] >= bound) atomicAdd(&L.hist[(key[i] - bound) >> shift], 1u);
-        __syncthreads();
-        find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
-        bound += L.out[0] << shift;
     }
-    pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
+    __syncthreads();
+    const int cnt = (int)L.cnt;
+    if (cnt <= kPickList) emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
+    else pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
+}
+
+// Its k best, from the registers; L is cleared.  Floats are compared, an instruction per entry where keys take half
+// a dozen (an instruction for every entry of a row of 32768 takes a compute unit 0.2 us).  They order as their keys
+// do but for NaN, which every comparison leaves out: so the maxima are those of the numbers, which can only lower
+// the bound; what is not below the bound is looked at by its key, and a row in which fewer than k entries reach it
+// goes through the general algorithm, by keys throughout.
+template <int BLOCK, int ITEMS, bool EDGES>
+__device__ __forceinline__ void pick_row(float (&val)[ITEMS], const float *xr, int n, int k, const PickOut &o,
+                                         PickLds<BLOCK> &L, int tid, int lane, int wv)
+{
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));   // (the batch of loads stays one)
+#pragma unroll
+    for (int i = ITEMS > 2 ? ITEMS / 2 : 0; i < ITEMS; ++i) val[i] = i * BLOCK + tid < n ? val[i] : -INFINITY;
+    float best = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) best = val[i] > best ? val[i] : best;   // (never NaN)
+    const uint32_t bound_key = kth_value_bound<BLOCK>(tid < n ? ord_key(best) : 0u, k, L, tid, lane, wv);
+    const float bound = key_to_float(bound_key);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (!(val[i] < bound)) {
+            const uint32_t key = ord_key(val[i]);
+            if (key >= bound_key && i * BLOCK + tid < n) {
+                const uint32_t at = atomicAdd(&L.cnt, 1u);
+                if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~(i * BLOCK + tid);
+            }
+        }
+    __syncthreads();
+    const int cnt = (int)L.cnt;   // (the same for every thread, like all branches here)
+    if (cnt < k) pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
+    else if (cnt <= kPickList) emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
+    else pick_again<BLOCK, EDGES>(xr, n, k, o, L, bound_key);
 }
 
 // A longer row: read twice, in batches of 12 loads per thread.  Both reads compare floats, an instruction
@@ -572,44 +633,61 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float *xr = x + (long)row * ld;
     const PickOut o{S, src_out + (long)row * src_ld, ext_out ? ext_out + (long)row * ext_ld : nullptr, nullptr};
-    if constexpr (ITEMS > 0) pick_row<kPickBlock, ITEMS, false>(xr, n, k, o, L, tid, lane, wv);
-    else pick_row_long(xr, n, k, o, L, tid, lane, wv);
-}
-
-// The update of the round before, for the kernels below that read a head's scores next: D triples per
-// thread, 0 for none.
-template <int D>
-__device__ __forceinline__ void update_first(float *xr, int h, const DecayArgs &u, unsigned char *lds, int tid)
-{
-    if constexpr (D > 0) {
-        decay_chain<uint32_t, 1024, D, true>(xr, u.count, 2048 * D, u.nbr + (long)h * u.count,
-                                             u.nbr_e + (long)h * u.count, u.alpha, u.signal, lds, tid);
-        __syncthreads();   // the row is up to date
+    if constexpr (ITEMS > 0) {
+        float val[ITEMS];
+        load_row<kPickBlock>(xr, n, tid, val);
+        L.clear(tid);
+        pick_row<kPickBlock, ITEMS, false>(val, xr, n, k, o, L, tid, lane, wv);
+    } else {
+        pick_row_long(xr, n, k, o, L, tid, lane, wv);
     }
 }
-size_t update_lds(int items) { return items ? decay_chain_lds<uint32_t>(2048 * items, 1024 * items, true) : 0; }
 
 // A later round's sources and, in the same workgroup, the update of the round before and where the
 // sources' lists come from (launches of their own cost 7.7 and 6.1 us with 8 heads; a launch is 4.6 us
-// before it does anything: 18.9 us together, update included, against 24).
+// before it does anything).  The lists that the update reads are those that the match hands on.  (8 heads with 2048
+// triples: 19.4 us for 32736 nodes and 17.0 for 15969 with the row read behind the update and the lists read again;
+// 16.6 and 12.7 this way.)
 template <int ITEMS, int D>
 __global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, MatchArgs a,
                                                                 int32_t *__restrict__ src_out, DecayArgs update)
 {
-    extern __shared__ __align__(16) unsigned char update_mem[];
-    static_assert(kPickBlock == kMatchBlock, "one workgroup does both");
-    __shared__ PickLds<kPickBlock> L;
-    __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
+    static_assert(kPickBlock == kMatchBlock && kPickBlock == kUpdateBlock, "one workgroup does all");
+    extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
+    PickLds<kPickBlock> &L = *reinterpret_cast<PickLds<kPickBlock> *>(mem);
+    __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], to_s[kSmallK];
+    __shared__ int32_t wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
     const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     float *xr = x + (long)h * n;
     int32_t *src = src_out + (long)h * a.S;
     const PickOut o{a.S, src, nullptr, nullptr};
-    update_first<D>(xr, h, update, update_mem, tid);
-    const bool bad = match_load(a, h, match_lds, tid);
-    if constexpr (ITEMS > 0) pick_row<kPickBlock, ITEMS, false>(xr, n, a.S, o, L, tid, lane, wv);
-    else pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
+    Triples<D> tri;
+    bool bad;
+    if constexpr (ITEMS > 0) {
+        // (what the match needs first, then the update, then the row: loads come back in the order they leave)
+        const int32_t prev = a.prev_src[(long)h * a.S + min(tid, a.S - 1)];
+        const int32_t spec = a.X > 0 ? a.ext[(long)h * (a.S + a.X) + a.S + min(tid, a.X - 1)] : 0;
+        bad = a.X == 0 || (a.first ? a.overflow[h] : a.spec_bad[h]) != 0;
+        tri.load(update, h, tid);
+        float val[ITEMS];
+        load_row<kPickBlock>(xr, n, tid, val);
+        if (a.X > 0 && a.first && tid == 0) a.spec_bad[h] = bad ? 1 : 0;
+        if (tid < a.S) match_lds[tid] = prev;
+        if (tid < a.X) match_lds[2 * a.S + tid] = spec;
+        if (tid < kSmallK) to_s[tid] = -1;
+        if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, h, update, mem, tid);
+        L.clear(tid);
+        pick_row<kPickBlock, ITEMS, false>(val, xr, n, a.S, o, L, tid, lane, wv);
+    } else {
+        bad = match_load(a, h, match_lds, tid);
+        pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
+    }
     __syncthreads();   // the sources are written
-    match_head(a, h, bad, src, match_lds, wave_new, wave_fb, tid);
+    match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
+}
+template <int ITEMS, int D> constexpr size_t pick_match_lds()
+{
+    return update_row_lds<ITEMS, D>() > sizeof(PickLds<kPickBlock>) ? update_row_lds<ITEMS, D>() : sizeof(PickLds<kPickBlock>);
 }
 
 // The k best edges of each row of a dense edge block, ascending indices, with their values.
@@ -622,7 +700,10 @@ __global__ __launch_bounds__(BLOCK) void pick_edges_kernel(const float *__restri
     const long row = blockIdx.x;
     const int tid = threadIdx.x;
     const PickOut o{k, idx_out + row * idx_ld, nullptr, val_out + row * val_ld};
-    pick_row<BLOCK, ITEMS, true>(x + row * ld, n, k, o, L, tid, tid & 63, tid >> 6);
+    float val[ITEMS];
+    load_row<BLOCK>(x + row * ld, n, tid, val);
+    L.clear(tid);
+    pick_row<BLOCK, ITEMS, true>(val, x + row * ld, n, k, o, L, tid, tid & 63, tid >> 6);
 }
 
 // ---- budgeted selection ---------------------------------------------------------------
@@ -733,34 +814,46 @@ __device__ __forceinline__ bool emit_bitmap(const uint64_t *map, int words, int 
     return true;
 }
 
+struct BudgetLds {
+    __align__(16) uint32_t hist[2 * kBudgetBlock];
+    __align__(16) uint32_t list[kPairs];
+    uint32_t part[2][kBudgetBlock / kWave], lo[kBudgetBlock / kWave], hi[kBudgetBlock / kWave], out[3], cnt;
+    uint64_t map[1];   // ITEMS * 16 words
+};
+template <int ITEMS, int D> constexpr size_t budget_lds()
+{
+    const size_t own = sizeof(BudgetLds) + (size_t)ITEMS * (kBudgetBlock / kWave) * 8;
+    return update_row_lds<ITEMS, D>() > own ? update_row_lds<ITEMS, D>() : own;
+}
+
 template <int ITEMS, int D>
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
     float *x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update, LayerPlan plan)
 {
-    extern __shared__ __align__(16) unsigned char update_mem[];
     constexpr int NW = kBudgetBlock / kWave, CELLS = ITEMS * NW;
-    __shared__ __align__(16) uint32_t hist[2 * kBudgetBlock];
-    __shared__ __align__(16) uint32_t list[kPairs];
-    __shared__ uint64_t map[CELLS];
-    __shared__ uint32_t s_part[2][NW], s_min[NW], s_max[NW], s_out[3], s_cnt;
+    static_assert(kBudgetBlock == kUpdateBlock, "one workgroup does both");
+    extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
+    BudgetLds &L = *reinterpret_cast<BudgetLds *>(mem);
+    uint32_t *hist = L.hist, *list = L.list, *s_out = L.out;
+    uint64_t *map = L.map;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
     const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
     const int k = plan.budget[g] - append_count;
     int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
     float *xr = x + (long)row * n;
-    update_first<D>(xr, row, update, update_mem, tid);   // (the last round's, in a whole pass)
 
-    // the loads of the row leave together (unconditional, clamped, pinned before the first use)
+    Triples<D> tri;
+    tri.load(update, row, tid);
     float val[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * kBudgetBlock + tid, n - 1)];
+    load_row<kBudgetBlock>(xr, n, tid, val);
+    for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+    if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
     hist[tid] = 0;
     hist[tid + kBudgetBlock] = 0;
     list[tid] = 0;
-    if (tid == 0) s_cnt = 0;
-    for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+    if (tid == 0) L.cnt = 0;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));
+    for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));   // (the batch of loads stays one)
     uint32_t key[ITEMS], kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
@@ -771,10 +864,10 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
     }
     kmin = wave_min_u32(kmin);
     kmax = wave_max_u32(kmax);
-    if (lane == 0) { s_min[wv] = kmin; s_max[wv] = kmax; }
+    if (lane == 0) { L.lo[wv] = kmin; L.hi[wv] = kmax; }
     __syncthreads();
-    kmin = wave_min_u32(s_min[lane & (NW - 1)]);
-    kmax = wave_max_u32(s_max[lane & (NW - 1)]);
+    kmin = wave_min_u32(L.lo[lane & (NW - 1)]);
+    kmax = wave_max_u32(L.hi[lane & (NW - 1)]);
 
     // radix select on key - kmin from the top bit in which the row's keys differ; it ends when the
     // bin of the cut is one key wide or holds few enough entries to rank them pair by pair
@@ -793,7 +886,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
         for (int i = 0; i < ITEMS; ++i)
             if (key[i] >= tau && key[i] - tau <= width) atomicAdd(&hist[(key[i] - tau) >> shift], 1u);
         __syncthreads();
-        find_bin_block<kBudgetBlock>(hist, need, s_part[0], s_out, tid, lane, wv);
+        find_bin_block<kBudgetBlock>(hist, need, L.part[0], s_out, tid, lane, wv);
         tau += s_out[0] << shift;
         need = s_out[1];
         equal = s_out[2];
@@ -801,7 +894,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
             const uint32_t bin = (1u << shift) - 1u;
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i)
-                if (key[i] - tau <= bin) list[atomicAdd(&s_cnt, 1u)] = key[i];   // (lower keys wrap around, bin < 2^21)
+                if (key[i] - tau <= bin) list[atomicAdd(&L.cnt, 1u)] = key[i];   // (lower keys wrap around, bin < 2^21)
             __syncthreads();   // (also: s_out is read by every thread)
             rank_in_pairs(list, (int)equal, need, s_out, tid);
             tau = s_out[0];
@@ -830,7 +923,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
         }
         __syncthreads();
         uint32_t total;
-        const uint32_t before = block_scan_add<NW>(tid < CELLS ? hist[tid] : 0u, s_part[0], lane, wv, total);
+        const uint32_t before = block_scan_add<NW>(tid < CELLS ? hist[tid] : 0u, L.part[0], lane, wv, total);
         if (tid < CELLS) hist[tid] = before;
         __syncthreads();
 #pragma unroll
@@ -841,7 +934,7 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
         }
         __syncthreads();
     }
-    (void)emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), k, s_part[1], out, tid, lane, wv);
+    (void)emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), k, L.part[1], out, tid, lane, wv);
 }
 
 // Rows beyond 32768 entries: two reads instead of five.  A coarse sample gives the key range, the
@@ -1217,9 +1310,9 @@ static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs
 {
 #define GKV_PICK(ITEMS)                                                                                          \
     do {                                                                                                         \
-        if (D == 4 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
-        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), update_lds(D), st, x, n, a, \
-                           src, update);                                                                         \
+        constexpr size_t lds = pick_match_lds<ITEMS, D>();                                                       \
+        if (lds > 40 * 1024 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, (int)lds)) return hipGetLastError(); \
+        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), lds, st, x, n, a, src, update); \
     } while (0)
     if (n <= 4096) GKV_PICK(4);   // (lists are kept on the filter route only: 2048 nodes or more)
     else if (n <= 8192) GKV_PICK(8);
@@ -1316,8 +1409,9 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
 {
 #define GKV_BUDGET(ITEMS)                                                                                       \
     do {                                                                                                        \
-        if (D == 4 && !allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, 96 * 1024)) return hipGetLastError(); \
-        hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), update_lds(D), st, \
+        constexpr size_t lds = budget_lds<ITEMS, D>();                                                          \
+        if (lds > 40 * 1024 && !allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, (int)lds)) return hipGetLastError(); \
+        hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), lds, st,           \
                            scores, P, idx, P, w, update, plan);                                                 \
     } while (0)
     if (P <= 1024) GKV_BUDGET(1);
