@@ -62,7 +62,7 @@ struct Dims {
 // Workspace: a bump allocation of every scratch array any entry point may need.
 struct Workspace {
     size_t logits, row_max, row_sum, votes, E, src, nbr, nbr_e, scores, part;
-    size_t bound_hist, tau, cand, cand_cnt, overflow;
+    size_t bound_hist, tau, cand, cand_cnt, overflow, done;
     // lists kept from one round to the next, speculative rows
     size_t src_b, nbr_b, nbr_e_b, ext, new_src, n_new, sel_row, sel_pos, n_sel, spec_bad;
     size_t final_sel, final_bytes;   // the final selection's (0 bytes: it takes none)
@@ -211,7 +211,8 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
     W.cand = take(frows * g.chunks * g.slice_cap * 8);
     W.cand_cnt = take(frows * g.chunks * 4);
-    W.overflow = take((size_t)D.H * 4);
+    W.overflow = take((size_t)D.H * 2 * 4);   // flags of two consecutive rounds
+    W.done = take((size_t)D.H * 2 * 4);
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);
     W.nbr_b = take(keep ? (size_t)D.H * D.S * D.m * 4 : 0);
@@ -381,6 +382,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
     const bool one_source = D.S == 1 && (p->dtype == GRAPHKV_FP32 || D.d <= 64);
     DecayArgs update{};
     for (int t = 0; t < D.T; ++t) {
+        RedoArgs redo_left{};
         int32_t *src = src0, *nbr = nbr0;
         float *ev = e0;
         if (t == 0 || p->reselect) {
@@ -396,7 +398,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                 // Eq. 1 + Eq. 3 in one streaming pass over the keys: a bound per source from a
                 // strided sample that at least m of its edges reach, then only edges above it are kept.
                 float *tau = at<float>(ws, W.tau);
-                int32_t *cnt = at<int32_t>(ws, W.cand_cnt), *ovf = at<int32_t>(ws, W.overflow);
+                int32_t *cnt = at<int32_t>(ws, W.cand_cnt), *ovf = at<int32_t>(ws, W.overflow) + (t & 1) * D.H;
+                int32_t *done = at<int32_t>(ws, W.done);
+                const RedoArgs redo{Ac, Kc, D.N, D.P, D.S, D.m, D.H, src, ovf, done, E, nbr, ev};
                 void *cand = at<char>(ws, W.cand);
                 int32_t *ext = at<int32_t>(ws, W.ext);
                 if (!(keep && prev_src)) {
@@ -412,22 +416,19 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND,
                                launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
-                                                        at<char>(ws, W.bound_hist), tau, ovf, st));
+                                                        at<char>(ws, W.bound_hist), tau, ovf, done, st));
                     GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER,
                                launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr, tau, cand,
                                                          cnt, ovf, st));
                     GKV_LAUNCH(GRAPHKV_K_NBR_SELECT,
                                launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, nullptr, nbr, ev, st));
-                    // heads whose lists overflowed are redone row by row, exactly
-                    GKV_LAUNCH(GRAPHKV_K_REDO_ROWS,
-                               launch_redo_rows(Ac, Kc, D.H, D.N, D.P, D.S, D.m, src, ovf, E, nbr, ev, st));
                 } else {
                     int32_t *new_src = at<int32_t>(ws, W.new_src), *n_new = at<int32_t>(ws, W.n_new);
                     const SelectRows sel{at<int32_t>(ws, W.n_sel), at<int32_t>(ws, W.sel_row),
                                          at<int32_t>(ws, W.sel_pos)};
-                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, ovf,
+                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, at<int32_t>(ws, W.overflow),
                                           at<int32_t>(ws, W.spec_bad), new_src, n_new, at<int32_t>(ws, W.sel_row),
-                                          at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel)};
+                                          at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel), ovf};
                     if (pick_match_applies(D.S)) {
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER, launch_pick_match(scores, D.P, D.H, match, src, update, st));
                         update = DecayArgs{};
@@ -438,17 +439,27 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     // new sources without a kept list (usually none): bound and filter passes
                     // that return at once for heads that have none
-                    GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
-                               launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
-                                                        at<char>(ws, W.bound_hist), tau, ovf, st));
-                    GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER_NEW,
-                               launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new, tau,
-                                                         cand, cnt, ovf, st));
-                    GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
-                               launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));
-                    GKV_LAUNCH(GRAPHKV_K_REDO_ROWS,
-                               launch_redo_rows(Ac, Kc, D.H, D.N, D.P, D.S, D.m, src, ovf, E, nbr, ev, st));
+                    // (An enhanced signal does make new sources, whose bound one workgroup a head takes in less time
+                    // than all of them that share the memory's rate: 3 rounds of 8 heads x 32736 keys 542 us in
+                    // three launches a round, 615 in one.)
+                    if (p->signal != GRAPHKV_SIGNAL_ENHANCED && pick_match_applies(D.S) && late_lists_apply(D.H, g)) {
+                        GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
+                                   launch_late_lists(Ac, Kc, D.H, D.N, D.P, D.m, g, new_src, n_new, sel, cand, cnt, ovf,
+                                                     done + D.H, src, nbr, ev, st));
+                    } else {
+                        GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
+                                   launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
+                                                            at<char>(ws, W.bound_hist), tau, ovf, nullptr, st));
+                        GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER_NEW,
+                                   launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new, tau,
+                                                             cand, cnt, ovf, st));
+                        GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
+                                   launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));
+                    }
                 }
+                // heads whose lists overflowed are redone row by row, exactly: by the kernel that takes the update
+                // along, where there is one
+                redo_left = redo;
             } else {
                 // Eq. 2: source nodes
                 GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES,
@@ -473,9 +484,16 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
         }
         // Eq. 5: one round of the signal
         const bool next_takes_it = t + 1 < D.T ? D.filter && keep && pick_match_applies(D.S) : last != nullptr;
-        update = DecayArgs{nbr, ev, next_takes_it ? items : 0, items ? D.S * D.m : 0, p->decay, p->signal};
-        if (!update.items)
-            GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
+        update = DecayArgs{nbr, ev, items, D.S * D.m, p->decay, p->signal, redo_left};
+        if (!next_takes_it || !items) {
+            if (items && redo_left.overflow) {
+                GKV_LAUNCH(GRAPHKV_K_REDO_ROWS, launch_redo_decay(scores, D.H, D.P, update, st));
+            } else {
+                if (redo_left.overflow) GKV_LAUNCH(GRAPHKV_K_REDO_ROWS, launch_redo_rows(redo_left, st));
+                GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
+            }
+            update = DecayArgs{};
+        }
         prev_src = src;
         prev_nbr = nbr;
         prev_e = ev;

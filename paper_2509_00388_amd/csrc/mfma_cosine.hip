@@ -194,37 +194,20 @@ __device__ __forceinline__ uint4 histogram_words(const uint32_t *row, int lane)
     return lane < BINS / 4 ? *reinterpret_cast<const uint4 *>(row + 4 * lane) : make_uint4(0, 0, 0, 0);
 }
 
-// SB 32-row groups of sources per workgroup (4 SB waves); BINS bins over [-1, 1]: 256 for two
+// A workgroup's source rows (s_base .. of the Sh in use) against columns c0 .. c1 - 1 of the sample, counted into
+// hist [ROWS][BINS].  SB 32-row groups of sources per workgroup (4 SB waves); BINS bins over [-1, 1]: 256 for two
 // groups, 224 for three (the histograms of 96 rows and the two key tiles must fit the LDS), so
-// the bound is at most 2 / BINS below the m-th largest sampled edge.
+// the bound is at most 2 / BINS below the m-th largest sampled edge.  Ends with a barrier.
 template <int SB, int BINS>
-__global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride,
-    int S, int src_pitch, const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int m,
-    int chunk_cols, uint32_t *__restrict__ hist_part, float *__restrict__ tau, int pitch, int row0,
-    int32_t *__restrict__ overflow)
+__device__ __forceinline__ void count_sample(const uint16_t *Ah, const uint16_t *Kh, const int32_t *src_h, int Sh, int s_base,
+                                             int c0, int c1, int key_stride, unsigned char *kt, uint32_t *hist, float *inv_s,
+                                             int32_t *idx_s, int tid)
 {
     constexpr int ROWS = SB * kBlk, NT = 256 * SB;
-    __shared__ float inv_s[ROWS];
-    __shared__ int32_t idx_s[ROWS];
-    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the histograms
-    unsigned char *kt = smem;
-    uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);   // [ROWS][BINS]
-
-    // with few heads the sample is cut into chunks (blockIdx.z) whose histograms are added up
-    // by bound_merge_kernel: otherwise a handful of workgroups would walk the sample alone
-    const int h = blockIdx.y, s_base = blockIdx.x * ROWS, chunk = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+    const int lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv & 3, grp = wv >> 2;
-    const uint16_t *Kh = Kc + (long)h * N * kD;
-    const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
-    if (blockIdx.x == 0 && chunk == 0 && tid == 0) overflow[h] = 0;
-    // rows of this head's source list in use
-    const int Sh = n_src ? n_src[h] : S;
-    if (s_base >= Sh) return;
-
     bf16x8 q[kSteps];
-    load_sources(Ac + (long)h * N * kD, src + (long)h * src_pitch, Sh, s_base, grp, stream, l32, hh, q, inv_s, idx_s);
+    load_sources(Ah, src_h, Sh, s_base, grp, stream, l32, hh, q, inv_s, idx_s);
     for (int u = tid; u < ROWS * BINS; u += NT) hist[u] = 0;
     __syncthreads();
     float inv_src[16];   // 1/|k_i| times half the number of bins: edge -> bin in one multiply-add
@@ -270,6 +253,35 @@ __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
         }
     }
     __syncthreads();
+}
+
+template <int SB, int BINS>
+__global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride,
+    int S, int src_pitch, const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int m,
+    int chunk_cols, uint32_t *__restrict__ hist_part, float *__restrict__ tau, int pitch, int row0,
+    int32_t *__restrict__ overflow, int32_t *__restrict__ done)
+{
+    constexpr int ROWS = SB * kBlk, NT = 256 * SB;
+    __shared__ float inv_s[ROWS];
+    __shared__ int32_t idx_s[ROWS];
+    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the histograms
+    uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);   // [ROWS][BINS]
+
+    // with few heads the sample is cut into chunks (blockIdx.z) whose histograms are added up
+    // by bound_merge_kernel: otherwise a handful of workgroups would walk the sample alone
+    const int h = blockIdx.y, s_base = blockIdx.x * ROWS, chunk = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
+    if (blockIdx.x == 0 && chunk == 0 && tid == 0) {
+        overflow[h] = 0;
+        if (done) done[h] = done[gridDim.y + h] = 0;
+    }
+    // rows of this head's source list in use
+    const int Sh = n_src ? n_src[h] : S;
+    if (s_base >= Sh) return;
+    count_sample<SB, BINS>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, src + (long)h * src_pitch, Sh, s_base, c0, c1,
+                           key_stride, smem, hist, inv_s, idx_s, tid);
 
     if (gridDim.z > 1) {   // this chunk's counts go to global memory
         uint4 *out = reinterpret_cast<uint4 *>(
@@ -339,48 +351,38 @@ __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__rest
 constexpr int kStagePitch = 80;    // bytes per parked row: 16 dots, |k|^2, key (72, padded)
 constexpr int kLaterCap = 128;     // entries of each of the two LDS lists of hits beyond a row's fourth
 
-template <int SB, int RING>
-__global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
-    const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa)
+template <int SB> struct FilterLds {
+    static constexpr int ROWS = SB * kBlk;
+    float inv_s[ROWS], det_s[ROWS];
+    int32_t idx_s[ROWS];
+    int32_t row_pos[ROWS];     // entries written to each source's slice
+    int32_t idle_pos[kWave];   // takes the additions of 0 of hits that are not there
+    // (edge bits, key, source row) of the hits beyond a row's fourth: one list for even and one
+    // for odd drain periods, each emptied right after the barrier that ends its period
+    __align__(16) uint4 later[2][kLaterCap];
+    int32_t n_later[2], later_lost;   // entries ever listed (never reset)
+};
+
+// One chunk of head h's keys against source rows s_base .. of the Sh in use; smem: two key tiles, then the rings.
+// tau_of(r): bound of row s_base + r.
+template <int SB, int RING, typename TauOf>
+__device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t *Kc, int N, int n_cols, const int32_t *src,
+                                             int chunk_cols, const FilterArgs &fa, int h, int chunk, int n_chunks, int Sh,
+                                             int s_base, FilterLds<SB> &F, unsigned char *smem, int tid, TauOf &&tau_of)
 {
     constexpr int ROWS = SB * kBlk, NT = 256 * SB;
     static_assert(RING == 32 || RING == 64, "a ring takes a tile's 32 rows and is indexed with a mask");
-    __shared__ float inv_s[ROWS], det_s[ROWS];
-    __shared__ int32_t idx_s[ROWS];
-    __shared__ int32_t row_pos[ROWS];   // entries written to each source's slice
-    __shared__ int32_t idle_pos[kWave];  // takes the additions of 0 of hits that are not there
-    // (edge bits, key, source row) of the hits beyond a row's fourth: one list for even and one
-    // for odd drain periods, each emptied right after the barrier that ends its period
-    __shared__ uint4 later[2][kLaterCap];
-    __shared__ int32_t n_later[2], later_lost;   // entries ever listed (never reset)
-    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the rings
+    float *inv_s = F.inv_s, *det_s = F.det_s;
+    int32_t *idx_s = F.idx_s, *row_pos = F.row_pos, *idle_pos = F.idle_pos, *n_later = F.n_later;
+    int32_t &later_lost = F.later_lost;
+    auto &later = F.later;
     unsigned char *kt = smem;
     unsigned char *stage_mem = smem + 2 * kTileBytes;
 
-    // The workgroups that stream the same keys (the source groups of a key chunk) should run at
-    // about the same time on the same XCD, so that all but the first find the keys in that XCD's
-    // L2.  Workgroups go to the 8 XCDs round robin in the order of their linear number, so the
-    // groups of one (head, chunk) unit sit 8 apart: 8 units x all their groups take 8 x sgroups
-    // consecutive numbers.  (Unit counts that are no multiple of 8 keep the plain order.)
-    const int n_chunks = gridDim.x / fa.sgroups;
-    int h = blockIdx.y, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * ROWS;
-    if (fa.sgroups > 1 && ((long)gridDim.y * n_chunks) % 8 == 0) {
-        const long lin = (long)blockIdx.y * gridDim.x + blockIdx.x;
-        const long grp8 = lin / (8 * fa.sgroups);
-        const int r = (int)(lin % (8 * fa.sgroups));
-        const long unit = grp8 * 8 + (r & 7);
-        h = (int)(unit / n_chunks);
-        chunk = (int)(unit % n_chunks);
-        s_base = (r >> 3) * ROWS;
-    }
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+    const int lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv & 3, grp = wv >> 2;
     const uint16_t *Kh = Kc + (long)h * N * kD;
     const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
-    if (c0 >= n_cols) return;
-    const int Sh = fa.n_src ? fa.n_src[h] : S;
-    if (s_base >= Sh) return;
     const long buf_row0 = (long)h * fa.pitch + fa.row0 + s_base;   // this workgroup's first row of the per-row buffers
 
     bf16x8 q[kSteps];
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
         // lowered by twice the slack, divided by 1/|k_i|.  Rows past the last source and
         // impossible bounds never hit; a zero source (all edges 0) hits everywhere.
         const int slot = s_base + tid;
-        const float t = fa.tau[buf_row0 + min(tid, Sh - 1 - s_base)];
+        const float t = tau_of(min(tid, Sh - 1 - s_base));
         const float slack = 4e-6f + 1e-5f * fabsf(t);
         const float inv = inv_s[tid];
         const float lo2 = t - 2.f * slack;
@@ -577,6 +579,38 @@ __global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
         fa.cand_cnt[(buf_row0 + tid) * n_chunks + chunk] = c < fa.slice_cap ? c : fa.slice_cap;
         if (c > fa.slice_cap || later_lost) fa.overflow[h] = 1;
     }
+}
+
+template <int SB, int RING>
+__global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
+    const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa)
+{
+    constexpr int ROWS = SB * kBlk;
+    __shared__ FilterLds<SB> F;
+    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the rings
+    // The workgroups that stream the same keys (the source groups of a key chunk) should run at
+    // about the same time on the same XCD, so that all but the first find the keys in that XCD's
+    // L2.  Workgroups go to the 8 XCDs round robin in the order of their linear number, so the
+    // groups of one (head, chunk) unit sit 8 apart: 8 units x all their groups take 8 x sgroups
+    // consecutive numbers.  (Unit counts that are no multiple of 8 keep the plain order.)
+    const int n_chunks = gridDim.x / fa.sgroups;
+    int h = blockIdx.y, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * ROWS;
+    if (fa.sgroups > 1 && ((long)gridDim.y * n_chunks) % 8 == 0) {
+        const long lin = (long)blockIdx.y * gridDim.x + blockIdx.x;
+        const long grp8 = lin / (8 * fa.sgroups);
+        const int r = (int)(lin % (8 * fa.sgroups));
+        const long unit = grp8 * 8 + (r & 7);
+        h = (int)(unit / n_chunks);
+        chunk = (int)(unit % n_chunks);
+        s_base = (r >> 3) * ROWS;
+    }
+    if (chunk * chunk_cols >= n_cols) return;
+    const int Sh = fa.n_src ? fa.n_src[h] : S;
+    if (s_base >= Sh) return;
+    const float *tau = fa.tau + (long)h * fa.pitch + fa.row0 + s_base;
+    filter_chunk<SB, RING>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, threadIdx.x,
+                           [&](int r) { return tau[r]; });
 }
 
 constexpr int kTieRoom = 64;   // entries tied at the cut that a select lists beyond the m winners
@@ -827,29 +861,25 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 // list has room for, raise the head's overflow flag (the head is then redone exactly).
 // (A walk over the slices for every register, key indices fetched a second time, scans through the
 // LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way 8.4 us.)
+// LDS words of a wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit).
+template <int R> __host__ __device__ constexpr int select_wave_words(int m) { return 64 + 16 * R + 2 * ((m + kTieRoom + 1) & ~1); }
+
+// Selections x0, x0 + step, .. of the n_rows of head h by one wave; ends, and raises the head's flag, at a list that
+// does not do.
 template <int R>
-__global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
-                                                              const int32_t *__restrict__ cand_cnt,
-                                                              int32_t *__restrict__ overflow,
-                                                              const int32_t *__restrict__ src, int S, int pitch,
-                                                              int chunks, int slice_cap, int m, SelectRows sel,
-                                                              int32_t *__restrict__ nbr,
-                                                              float *__restrict__ nbr_e)
+__device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, const int32_t *__restrict__ cand_cnt,
+                                               int32_t *__restrict__ overflow, const int32_t *__restrict__ src, int S,
+                                               int pitch, int chunks, int slice_cap, int m, const SelectRows &sel,
+                                               int32_t *__restrict__ nbr, float *__restrict__ nbr_e, int h, int x0, int step,
+                                               int n_rows, uint32_t *words, int lane)
 {
     static_assert(R == 16 || R == 32, "register groups of 16");
-    // per wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit)
-    extern __shared__ __align__(16) uint32_t dyn[];
-    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
-    const int waves = (int)blockDim.x >> 6;
-    const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
-    if (overflow[h]) return;
     const int list_cap = m + kTieRoom;
-    uint32_t *start_s = dyn + wv * (64 + 16 * R + 2 * ((list_cap + 1) & ~1));
+    uint32_t *start_s = words;
     uint8_t *mark_s = reinterpret_cast<uint8_t *>(start_s + 64);
     uint64_t *win = reinterpret_cast<uint64_t *>(start_s + 64 + 16 * R);
 
-    for (int x = blockIdx.x * waves + wv; x < n_rows; x += gridDim.x * waves) {
+    for (int x = x0; x < n_rows; x += step) {
         const int crow = sel.row ? sel.row[(long)h * S + x] : x, pos = sel.pos ? sel.pos[(long)h * S + x] : x;
         const long row = (long)h * pitch + crow;
         const uint2 *slices = cand + row * chunks * (long)slice_cap;
@@ -869,11 +899,11 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
         uint32_t E[R], J[R];
         if (chunks <= 8) {
             // few slices: the last one that starts at or before the entry, slice by slice in scalars
-#pragma unroll
+    #pragma unroll
             for (int it = 0; it < R; ++it) J[it] = (uint32_t)(it * 64 + lane);
             for (int c = 1; c < chunks; ++c) {
                 const int s_c = __builtin_amdgcn_readlane(incl - cnt, c), shift = c * slice_cap - s_c;
-#pragma unroll
+    #pragma unroll
                 for (int it = 0; it < R; ++it)
                     if ((it & ~3) < n_it) J[it] = it * 64 + lane >= s_c ? (uint32_t)(it * 64 + lane + shift) : J[it];
             }
@@ -885,7 +915,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
             if (cnt > 0) mark_s[incl - cnt] = (uint8_t)lane;
             wave_sync();
             uint32_t carry = 0;
-#pragma unroll
+    #pragma unroll
             for (int it = 0; it < R; ++it) {
                 J[it] = 0u;
                 if (it < n_it) {   // (the same for all lanes)
@@ -898,25 +928,25 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
         }
         // (entries past the end read one that is there: the loads of four registers leave together)
         const uint32_t some = (uint32_t)__builtin_amdgcn_readfirstlane((int)J[0]);
-#pragma unroll
+    #pragma unroll
         for (int g = 0; g < R; g += 4) {
             if (g < n_it) {
                 uint2 v[4];
-#pragma unroll
+    #pragma unroll
                 for (int u = 0; u < 4; ++u) v[u] = slices[(g + u) * 64 + lane < n ? J[g + u] : some];
-#pragma unroll
+    #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     E[g + u] = v[u].x;
                     J[g + u] = v[u].y;
                 }
             } else {
-#pragma unroll
+    #pragma unroll
                 for (int u = 0; u < 4; ++u) E[g + u] = 0u;
             }
         }
         uint32_t kmin = 0xffffffffu, kmax = 0u;
         int valid = n;
-#pragma unroll
+    #pragma unroll
         for (int it = 0; it < R; ++it)
             if ((it & ~3) < n_it) {
                 // the source's own column is no neighbour (Eq. 3: j != i): key 0 sorts below every edge
@@ -945,7 +975,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
 
         // everything that reaches tau -> LDS list as (key index, edge bits), any order
         int listed = 0;
-#pragma unroll
+    #pragma unroll
         for (int it = 0; it < R; ++it)
             if (it < n_it) {
                 const bool in = E[it] >= tau;
@@ -1000,6 +1030,79 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
         }
         wave_sync();
     }
+}
+
+template <int R>
+__global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
+                                                              const int32_t *__restrict__ cand_cnt,
+                                                              int32_t *__restrict__ overflow,
+                                                              const int32_t *__restrict__ src, int S, int pitch,
+                                                              int chunks, int slice_cap, int m, SelectRows sel,
+                                                              int32_t *__restrict__ nbr,
+                                                              float *__restrict__ nbr_e)
+{
+    extern __shared__ __align__(16) uint32_t dyn[];
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
+    const int waves = (int)blockDim.x >> 6;
+    const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
+    if (overflow[h]) return;
+    select_by_wave<R>(cand, cand_cnt, overflow, src, S, pitch, chunks, slice_cap, m, sel, nbr, nbr_e, h,
+                      blockIdx.x * waves + wv, gridDim.x * waves, n_rows, dyn + wv * select_wave_words<R>(m), lane);
+}
+
+// A later round's bound, filter and select passes in one launch, for few heads.  New sources without a kept list are
+// rare (none at all on ordinary inputs), so what counts is the launches they cost every round: a head without one
+// has its promoted rows' lists selected from, a wave a row, the first waves of all workgroups first, and that is
+// all.  A head with new sources takes the passes here: every workgroup of the head takes the bound from the whole
+// sample itself (there are compute units enough, which would wait for one workgroup otherwise), filters its
+// chunk, and the one that is done last, which `done` counts, selects for the head.  (8 heads, a round without new
+// sources: 15 us in three launches, 7.5 in one.)
+template <int R>
+__global__ __launch_bounds__(kThreads) void late_lists_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
+    const int32_t *__restrict__ new_src, int chunk_cols, FilterArgs fa, int sample_cols, int key_stride, int rank,
+    int32_t *done, const int32_t *__restrict__ cur, int m, SelectRows sel, int32_t *__restrict__ nbr,
+    float *__restrict__ nbr_e)
+{
+    constexpr int BINS = 256, NW = kThreads / kWave;
+    __shared__ FilterLds<kSB> F;
+    __shared__ float tau_s[kRows];
+    __shared__ int32_t last;
+    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the rings (or the histograms); the selects'
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_chunks = gridDim.x / fa.sgroups, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * kRows;
+    const int Sh = fa.n_src[h], n_sel = sel.n_rows[h];
+    int first = wv * gridDim.x + blockIdx.x, step = NW * gridDim.x;   // selections of this wave
+    if (Sh > 0) {
+        if (s_base >= Sh) return;   // (s_base = 0 has rows)
+        uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);
+        count_sample<kSB, BINS>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, new_src + (long)h * fa.src_pitch, Sh, s_base, 0,
+                                sample_cols, key_stride, smem, hist, F.inv_s, F.idx_s, tid);
+        for (int r = wv; r < kRows; r += NW) {
+            const uint4 w4 = histogram_words<BINS>(&hist[r * BINS], lane);
+            bound_from_histogram<BINS>(w4, rank, lane, &tau_s[r]);
+        }
+        __syncthreads();
+        filter_chunk<kSB, 64>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, tid,
+                              [&](int r) { return tau_s[r]; });
+        __syncthreads();
+        if (tid == 0) {
+            __threadfence();   // the workgroup's candidates are visible before it is counted
+            const int all = n_chunks * ((Sh + kRows - 1) / kRows);
+            last = atomicAdd(&done[h], 1) == all - 1;
+            if (last) done[h] = 0;
+        }
+        __syncthreads();
+        if (!last) return;
+        __threadfence();       // and the others' before they are read
+        if (*(volatile int32_t *)&fa.overflow[h]) return;
+        first = wv;
+        step = NW;
+    }
+    select_by_wave<R>(fa.cand, fa.cand_cnt, fa.overflow, cur, S, fa.pitch, n_chunks, fa.slice_cap, m, sel, nbr, nbr_e, h,
+                      first, step, n_sel, reinterpret_cast<uint32_t *>(smem) + wv * select_wave_words<R>(m), lane);
 }
 
 // Matching on its own, for source lists the few-winners selection does not take (S > 256).
@@ -1172,7 +1275,7 @@ int bound_chunks(int Hkv, int P, int sgroups)
 template <int SB, int BINS>
 hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                         int src_pitch, const int32_t *n_src, bool late, void *hist_part, float *tau, int pitch,
-                        int row0, int32_t *overflow, hipStream_t st)
+                        int row0, int32_t *overflow, int32_t *done, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const Sample smp = sample_of(P);
@@ -1188,11 +1291,24 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     hipLaunchKernelGGL((cosine_bound_kernel<SB, BINS>), dim3(sgroups, Hkv, chunks), dim3(256 * SB),
                        2 * kTileBytes + ROWS * BINS * 4, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols,
                        smp.stride, rows, src_pitch, src, n_src, rank, chunk_cols, (uint32_t *)hist_part, tau, pitch, row0,
-                       overflow);
+                       overflow, done);
     if (chunks > 1)
         hipLaunchKernelGGL((bound_merge_kernel<SB, BINS>), dim3((rows + 3) / 4, Hkv), dim3(256), 0, st,
                            (const uint32_t *)hist_part, chunks, sgroups, rows, n_src, rank, tau, pitch, row0);
     return hipGetLastError();
+}
+
+// Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
+// per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
+// rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a
+// half-wave's 32 lanes get a row and the ring is not yet full.
+int filter_drain_every(int P, int m, int ring)
+{
+    const int stride = sample_of(P).stride;
+    const double rate = (double)mfma_bound_rank(m, stride) * stride / (double)P;
+    const double per_tile = 32.0 * (1.0 - pow(1.0 - (rate < 1.0 ? rate : 1.0), 16.0));
+    const int every = (int)((ring > kBlk ? 30.0 : 24.0) / (per_tile > 0.45 ? per_tile : 0.45));
+    return every < 1 ? 1 : every;
 }
 
 template <int SB, int RING>
@@ -1202,16 +1318,7 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    const int stride = sample_of(P).stride;
-    // Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
-    // per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
-    // rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a
-    // half-wave's 32 lanes get a row and the ring is not yet full.
-    const double rate = (double)mfma_bound_rank(m, stride) * stride / (double)P;
-    const double per_tile = 32.0 * (1.0 - pow(1.0 - (rate < 1.0 ? rate : 1.0), 16.0));
-    int drain_every = (int)((RING > kBlk ? 30.0 : 24.0) / (per_tile > 0.45 ? per_tile : 0.45));
-    if (drain_every < 1) drain_every = 1;
-    FilterArgs fa{n_src, tau, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, drain_every, sgroups, src_pitch,
+    FilterArgs fa{n_src, tau, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, filter_drain_every(P, m, RING), sgroups, src_pitch,
                   g.pitch, row0};
     if (!allow_big_lds((const void *)cosine_filter_kernel<SB, RING>)) return hipGetLastError();
     hipLaunchKernelGGL((cosine_filter_kernel<SB, RING>), dim3(g.chunks * sgroups, Hkv), dim3(256 * SB),
@@ -1233,13 +1340,13 @@ size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g)
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                     const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                     const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
-                                    hipStream_t st)
+                                    int32_t *done, hipStream_t st)
 {
     if (first_round && g.sb == 3)
         return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false,
-                                    hist_part, tau, g.pitch, 0, overflow, st);
+                                    hist_part, tau, g.pitch, 0, overflow, done, st);
     return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, hist_part, tau, g.pitch, 0,
-                                overflow, st);
+                                overflow, done, st);
 }
 
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
@@ -1260,6 +1367,37 @@ hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv,
     return hipGetLastError();
 }
 
+// Lists short enough for a wave each.
+static bool wave_select_applies(const MfmaFilterPlan &g) { return g.cand_cap <= 64 * 32 && g.chunks <= 64; }
+
+// Up to two rounds of its workgroups (us a round without new sources, three launches / one: 8 heads of 16K keys 15.0
+// / 7.5, 256 heads of 20K, where the selects take longer than the launches, 32 / 33, of 32K 26 / 33).
+bool late_lists_apply(int Hkv, const MfmaFilterPlan &g)
+{
+    return wave_select_applies(g) && (long)Hkv * g.chunks * ((g.S + kRows - 1) / kRows) <= 512;
+}
+
+hipError_t launch_late_lists(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
+                             const int32_t *new_src, const int32_t *n_new, const SelectRows &rows, void *cand,
+                             int32_t *cand_cnt, int32_t *overflow, int32_t *done, const int32_t *src, int32_t *nbr,
+                             float *nbr_e, hipStream_t st)
+{
+    const int sgroups = (g.S + kRows - 1) / kRows;
+    const Sample smp = sample_of(P);
+    FilterArgs fa{n_new, nullptr, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, filter_drain_every(P, m, 64), sgroups, g.S,
+                  g.pitch, 0};
+    const bool small = g.cand_cap <= 64 * 16;
+    auto *kernel = small ? late_lists_kernel<16> : late_lists_kernel<32>;
+    const size_t filter = 2 * kTileBytes + 2 * (4 * kSB) * 64 * kStagePitch;   // (the histograms of 64 rows fit the rings)
+    const size_t select = (size_t)(kThreads / kWave) * (small ? select_wave_words<16>(m) : select_wave_words<32>(m)) * 4;
+    static_assert(kRows * 256 * 4 <= 2 * (4 * kSB) * 64 * kStagePitch, "the histograms take the rings' place");
+    if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
+    hipLaunchKernelGGL(kernel, dim3(g.chunks * sgroups, Hkv), dim3(kThreads), filter > select ? filter : select, st,
+                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, g.S, new_src, g.chunk_cols, fa, smp.cols, smp.stride,
+                       mfma_bound_rank(m, smp.stride), done, src, m, rows, nbr, nbr_e);
+    return hipGetLastError();
+}
+
 hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st)
@@ -1270,13 +1408,13 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
     // take the other kernel when there are many heads (256 heads, us, workgroup / wave per list: 32K
     // prompts 18 / 28, 128K 76 / 231), this one when there are few (8 heads 9.3 / 8.3).
     const bool few = (long)S * Hkv <= 2048;
-    if (cap <= 64 * 32 && g.chunks <= 64 && (!rows || few)) {
+    if (wave_select_applies(g) && (!rows || few)) {
         const int waves = few ? 1 : 4;
         const SelectRows sel = rows ? *rows : SelectRows{};
         int per_head = (waves == 1 ? 2048 : 8192) / Hkv;
         per_head = per_head < 1 ? 1 : (per_head > (S + waves - 1) / waves ? (S + waves - 1) / waves : per_head);
         const bool small = cap <= 64 * 16;
-        const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * ((m + kTieRoom + 1) & ~1)) * 4;
+        const size_t lds = (size_t)waves * (small ? select_wave_words<16>(m) : select_wave_words<32>(m)) * 4;
         auto *kernel = small ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
         hipLaunchKernelGGL(kernel, dim3(per_head, Hkv), dim3(64 * waves), lds, st, (const uint2 *)cand, cand_cnt,
                            overflow, src, S, g.pitch, g.chunks, g.slice_cap, m, sel, nbr, nbr_e);

@@ -109,13 +109,13 @@ __device__ __forceinline__ float inv_norm(float sq)
     return sq == 0.f ? 0.f : __builtin_amdgcn_rsqf(sq);
 }
 
-// Sum of squares of the 64 elements a lane holds of its row (8 k-steps x 8),
+// Sum of squares of the 64 elements a lane holds of its row (8 k-steps x 8, or the next of them on top of a),
 // two bf16 products per instruction, fp32 accumulation.
-__device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[kSteps])
+template <int STEPS>
+__device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float a = 0.f)
 {
-    float a = 0.f;
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s)
+    for (int s = 0; s < STEPS; ++s)
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
             const bf16x2 v = {r[s][e], r[s][e + 1]};

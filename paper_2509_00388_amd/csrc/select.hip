@@ -313,7 +313,7 @@ __device__ __forceinline__ void topk_stream_row(
             if (g || (e && e_before < need)) {
                 const uint32_t pos = g_before + min(e_before, need);
                 out[pos] = j;
-                if (vout) vout[pos] = t[u];
+                if (vout) vout[pos] = t[u] + 0.0f;   // (no -0.0, as everywhere else)
             }
             base_g += __popcll(mg);
             base_e += __popcll(me);
@@ -502,18 +502,50 @@ __device__ __forceinline__ void emit_winners(PickLds<BLOCK> &L, int cnt, int k, 
     else place_winners<BLOCK, 2, EDGES>(L, k, o, tid);
 }
 
-// Masses of equal values: the general algorithm picks the k entries, the list holds just them.
+// More entries reach the bound than the list holds, or fewer than k: a histogram over all of them raises the bound,
+// or, for masses of equal values, the general algorithm picks the k entries.  Returns the entries of the list, or 0
+// if the outputs are written.  The row is read again.
 template <int BLOCK, bool EDGES>
-__device__ __forceinline__ void pick_general(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, int tid)
+__device__ __forceinline__ int pick_hard(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, uint32_t bound,
+                                         int cnt)
 {
+    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (cnt > kPickList) {
+        uint32_t mx = 0u;
+        for (int j = tid; j < n; j += BLOCK) mx = max(mx, ord_key(xr[j]));
+        mx = wave_max_u32(mx);
+        __syncthreads();
+        L.clear(tid);
+        if (lane == 0) L.hi[wv] = mx;
+        __syncthreads();
+        mx = wave_max_u32(L.hi[lane & (NW - 1)]);
+        const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > BITS ? bits - BITS : 0;
+        for (int j = tid; j < n; j += BLOCK) {
+            const uint32_t key = ord_key(xr[j]);
+            if (key >= bound) atomicAdd(&L.hist[(key - bound) >> shift], 1u);
+        }
+        __syncthreads();
+        find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
+        bound += L.out[0] << shift;
+        for (int j = tid; j < n; j += BLOCK) {
+            const uint32_t key = ord_key(xr[j]);
+            if (key >= bound) {
+                const uint32_t at = atomicAdd(&L.cnt, 1u);
+                if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~j;
+            }
+        }
+        __syncthreads();
+        if (L.cnt <= (uint32_t)kPickList) return (int)L.cnt;
+    }
     int32_t *tmp = !EDGES && o.ext ? o.ext : o.src;
     topk_stream_row<BLOCK, false>(0, xr, n, n, k, tmp, 0, EDGES ? o.val : nullptr, 0, 0, 0, 0);
-    if (EDGES) return;
+    if (EDGES) return 0;
     __syncthreads();
     const int32_t j = tid < k ? tmp[tid] : 0;
     L.list[tid] = tid < k ? ((uint64_t)ord_key(xr[j]) << 32) | (uint32_t)~j : 0ull;   // (k <= 256 <= BLOCK)
     __syncthreads();
-    emit_winners<BLOCK, false>(L, k, k, o, tid);
+    return k;
 }
 
 // A row of at most ITEMS * BLOCK entries (and, with ITEMS > 2, more than half as many), entry i of thread tid being
@@ -525,55 +557,20 @@ __device__ __forceinline__ void load_row(const float *xr, int n, int tid, float 
     for (int i = 0; i < ITEMS; ++i) val[i] = xr[min(i * BLOCK + tid, n - 1)];
 }
 
-// More than kPickList entries reach the bound: one histogram over all of them raises it, then the list or, with
-// masses of equal values, the general algorithm.  The row is read again.
-template <int BLOCK, bool EDGES>
-__device__ __forceinline__ void pick_again(const float *xr, int n, int k, const PickOut &o, PickLds<BLOCK> &L, uint32_t bound)
-{
-    constexpr int NW = PickLds<BLOCK>::NW, BITS = PickLds<BLOCK>::kBits;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t mx = 0u;
-    for (int j = tid; j < n; j += BLOCK) mx = max(mx, ord_key(xr[j]));
-    mx = wave_max_u32(mx);
-    __syncthreads();
-    L.clear(tid);
-    if (lane == 0) L.hi[wv] = mx;
-    __syncthreads();
-    mx = wave_max_u32(L.hi[lane & (NW - 1)]);
-    const int bits = mx > bound ? 32 - __clz(mx - bound) : 0, shift = bits > BITS ? bits - BITS : 0;
-    for (int j = tid; j < n; j += BLOCK) {
-        const uint32_t key = ord_key(xr[j]);
-        if (key >= bound) atomicAdd(&L.hist[(key - bound) >> shift], 1u);
-    }
-    __syncthreads();
-    find_bin_block<BLOCK>(L.hist, (uint32_t)k, L.part[0], L.out, tid, lane, wv);
-    bound += L.out[0] << shift;
-    for (int j = tid; j < n; j += BLOCK) {
-        const uint32_t key = ord_key(xr[j]);
-        if (key >= bound) {
-            const uint32_t at = atomicAdd(&L.cnt, 1u);
-            if (at < (uint32_t)kPickList) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~j;
-        }
-    }
-    __syncthreads();
-    const int cnt = (int)L.cnt;
-    if (cnt <= kPickList) emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
-    else pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
-}
-
 // Its k best, from the registers; L is cleared.  Floats are compared, an instruction per entry where keys take half
 // a dozen (an instruction for every entry of a row of 32768 takes a compute unit 0.2 us).  They order as their keys
 // do but for NaN, which every comparison leaves out: so the maxima are those of the numbers, which can only lower
 // the bound; what is not below the bound is looked at by its key, and a row in which fewer than k entries reach it
 // goes through the general algorithm, by keys throughout.
-template <int BLOCK, int ITEMS, bool EDGES>
+template <int BLOCK, int ITEMS, bool EDGES, bool ANY = false>   // ANY: a row of any length up to ITEMS * BLOCK
 __device__ __forceinline__ void pick_row(float (&val)[ITEMS], const float *xr, int n, int k, const PickOut &o,
                                          PickLds<BLOCK> &L, int tid, int lane, int wv)
 {
+    static_assert(ITEMS <= 32, "one bit per entry of a thread");
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) asm volatile("" : "+v"(val[i]));   // (the batch of loads stays one)
 #pragma unroll
-    for (int i = ITEMS > 2 ? ITEMS / 2 : 0; i < ITEMS; ++i) val[i] = i * BLOCK + tid < n ? val[i] : -INFINITY;
+    for (int i = ITEMS > 2 && !ANY ? ITEMS / 2 : 0; i < ITEMS; ++i) val[i] = i * BLOCK + tid < n ? val[i] : -INFINITY;
     float best = -INFINITY;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) best = val[i] > best ? val[i] : best;   // (never NaN)
@@ -589,10 +586,12 @@ __device__ __forceinline__ void pick_row(float (&val)[ITEMS], const float *xr, i
             }
         }
     __syncthreads();
-    const int cnt = (int)L.cnt;   // (the same for every thread, like all branches here)
-    if (cnt < k) pick_general<BLOCK, EDGES>(xr, n, k, o, L, tid);
-    else if (cnt <= kPickList) emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
-    else pick_again<BLOCK, EDGES>(xr, n, k, o, L, bound_key);
+    int cnt = (int)L.cnt;   // (the same for every thread, like all branches here)
+    if (cnt < k || cnt > kPickList) {
+        cnt = pick_hard<BLOCK, EDGES>(xr, n, k, o, L, bound_key, cnt);
+        if (cnt == 0) return;
+    }
+    emit_winners<BLOCK, EDGES>(L, cnt, k, o, tid);
 }
 
 // A longer row: read twice, in batches of 12 loads per thread.  Both reads compare floats, an instruction
@@ -619,9 +618,161 @@ __device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, con
         }
     });
     __syncthreads();
-    const int cnt = (int)L.cnt;
-    if (cnt >= k && cnt <= kPickList) emit_winners<kPickBlock, false>(L, cnt, k, o, tid);
-    else pick_general<kPickBlock, false>(xr, n, k, o, L, tid);
+    int cnt = (int)L.cnt;
+    if (cnt < k || cnt > kPickList) cnt = pick_hard<kPickBlock, false>(xr, n, k, o, L, bound_key, cnt);
+    emit_winners<kPickBlock, false>(L, cnt, k, o, tid);
+}
+
+// ---- neighbourhoods of heads whose candidate lists overflowed ------------------------
+// The filter route (mfma_cosine.hip) gives up on a head when a candidate list cannot hold what
+// reaches the bound (masses of equal edges, an adversarial key order) and raises the head's
+// flag.  Such heads are rare, so they are not worth an [heads, S, P] edge block in memory: a
+// fixed number of workgroups walk the (head, source) rows of the flagged heads, and each row's
+// edges (Eq. 1) go to the workgroup's own scratch row of P floats, out of which the exact top-m
+// (Eq. 3) is taken by the row kernels above.  The edges are formed exactly as in the streaming
+// kernels -- the same matrix-core instruction sequence with the source in every operand row, the
+// same norms -- so that a head gets the same bits whichever route it takes.
+//
+// A launch of its own that finds no flag set costs 2 to 5 us, and there is one in every round.  So where the
+// next kernel has a workgroup per head anyway (an update that rides along) that kernel does the rows first:
+// without a flag its workgroups go straight on; with one, all of them (as many more than heads as the rows want)
+// take rows, unflagged heads go on at once, and a flagged head is gone on with by the workgroup that finishes its
+// last row.  Nobody waits for another.
+constexpr int kRedoBlock = 1024;
+constexpr size_t kRedoLds = (size_t)(kRedoBlock / kWave) * kBlk * kPitch;   // a block of keys per wave
+
+// Workgroups that walk the rows of flagged heads: one per compute unit, fewer for long rows
+// (their scratch rows stay within 64 MiB), at least 16.
+__host__ __device__ inline int redo_rows_workgroups(int heads, int S, int P)
+{
+    const long items = (long)heads * S;
+    long wgs = ((long)64 << 20) / ((long)P * 4);
+    wgs = wgs < 16 ? 16 : (wgs > 256 ? 256 : wgs);
+    return (int)(items < wgs ? items : wgs);
+}
+
+// The thread's number, read anew: what is computed from it stays where it is used.  (The loops of the kernels below go
+// round once but for heads that are redone; without this the compiler moves the addresses of a row's 32 loads and
+// much else in front of them, and 128 registers a lane then spill: 12.7 -> 33 us for a source selection.)
+__device__ __forceinline__ int here(int tid)
+{
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
+// Row `item` (head * S + source slot): its edges to the workgroup's scratch row, its m best to the lists.  mem: kRedoLds
+// bytes.  Begins and ends with a barrier.  A wave takes 32 keys at a time, fetched whole rows at a time and turned
+// into operand layout in its own part of the LDS (operand layout straight from memory touches every line four
+// times, and the waves' lines do not fit the first-level cache).  (64 heads x 64 rows of 10000 keys, the whole
+// call, with the fetch in operand layout and a radix selection from the LDS: 1438 us; this way 1070 with the few-
+// winners selection in a launch of its own, 1177 in front of the next kernel with the general one, which needs no
+// more registers.)
+template <bool PICK>   // PICK: the selection of short rows, for the kernel that does nothing else
+__device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned char *mem)
+{
+    const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5, h = (int)(item / a.S);
+    float *erow = a.rows + (long)blockIdx.x * a.P;
+    const int32_t i = a.src[item];
+    const uint16_t *ah = (const uint16_t *)a.Ac + (long)h * a.N * kD, *kh = (const uint16_t *)a.Kc + (long)h * a.N * kD;
+    unsigned char *tile = mem + wv * (kBlk * kPitch);
+    __syncthreads();                          // the previous row's LDS and scratch row are free
+    // the source's row in every row of the operand (a lane holds elements 16 s + 8 hh ..)
+    bf16x8 q[kSteps];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) q[s] = load8(ah + (long)i * kD + 16 * s + 8 * hh);
+    float sq_i = half_row_sumsq(q);
+    sq_i = add_other_half(sq_i);
+    const float inv_i = inv_norm(sq_i);
+    // key l32 of a block is the operand's column
+    for (int j0 = wv * kBlk; j0 < a.P; j0 += (kRedoBlock / kWave) * kBlk) {
+        u32x4 piece[kSteps];
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const int g = lane + kWave * u;   // 16 bytes: row g / 16 of the block
+            const uint32_t at = (uint32_t)min(j0 + (g >> 4), a.P - 1) * (uint32_t)(2 * kD) + 16u * (g & 15);   // (below 4 GiB)
+            piece[u] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(kh) + at);
+        }
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const int g = lane + kWave * u;
+            *reinterpret_cast<u32x4 *>(tile + (g >> 4) * kPitch + 16 * (g & 15)) = piece[u];
+        }
+        wave_sync();
+        f32x16 acc;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc[u] = 0.f;
+        float sq = 0.f;
+        const unsigned char *mine = tile + l32 * kPitch + 16 * hh;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {   // (in two halves: registers)
+            bf16x8 kc[kSteps / 2];
+#pragma unroll
+            for (int s = 0; s < kSteps / 2; ++s) kc[s] = *reinterpret_cast<const bf16x8 *>(mine + 32 * (half * (kSteps / 2) + s));
+#pragma unroll
+            for (int s = 0; s < kSteps / 2; ++s)   // rows = the source (32 times), columns = keys
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[half * (kSteps / 2) + s], kc[s], acc, 0, 0, 0);
+            sq = half_row_sumsq(kc, sq);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        sq = add_other_half(sq);
+        const float e = (acc[0] * inv_norm(sq)) * inv_i;
+        const int j = j0 + l32;
+        if (hh == 0 && j < a.P) erow[j] = j == i ? -INFINITY : e;   // (Eq. 3: j != i)
+        wave_sync();                          // the tile is read before the next block's rows go in
+    }
+    __syncthreads();                          // the row is complete and visible to the workgroup
+    if (PICK && a.P <= 32 * kRedoBlock && a.m <= kSmallK) {
+        PickLds<kRedoBlock> &L = *reinterpret_cast<PickLds<kRedoBlock> *>(mem);
+        const PickOut o{a.m, a.nbr + item * a.m, nullptr, a.nbr_e + item * a.m};
+        float val[32];
+        load_row<kRedoBlock>(erow, a.P, tid, val);
+        L.clear(tid);
+        pick_row<kRedoBlock, 32, true, true>(val, erow, a.P, a.m, o, L, tid, lane, wv);
+    } else {
+        topk_stream_row<kRedoBlock, false>(0, erow, a.P, a.P, a.m, a.nbr + item * a.m, 0, a.nbr_e + item * a.m, 0, 0, 0, 0);
+    }
+    __syncthreads();
+}
+
+// Whether any head is flagged (the same for every thread; contains a barrier).
+__device__ __forceinline__ bool redo_flagged(const int32_t *overflow, int heads, int tid)
+{
+    int open = 0;
+    for (int g = tid; g < heads; g += kRedoBlock) open |= overflow[g] != 0;
+    return __syncthreads_or(open) != 0;
+}
+
+// Rows from `item` on, a workgroup's share of them, up to one that completes its head: that head, or -1 when there
+// are no more.  `last` is a word of LDS.
+__device__ __forceinline__ int redo_next(const RedoArgs &a, long &item, int32_t *last, unsigned char *mem)
+{
+    const int wgs = redo_rows_workgroups(a.heads, a.S, a.P);
+    while ((int)blockIdx.x < wgs && item < (long)a.heads * a.S) {
+        const long row = item;
+        const int h = (int)(row / a.S);
+        item += wgs;
+        if (a.overflow[h] == 0) continue;   // (not written in this launch: the same for every thread)
+        redo_row<false>(a, row, mem);
+        if (threadIdx.x == 0) {
+            __threadfence();        // the row is visible before it is counted
+            *last = atomicAdd(&a.done[h], 1) == a.S - 1;
+            if (*last) a.done[h] = 0;
+        }
+        __syncthreads();
+        if (*last) {
+            __threadfence();        // and the other workgroups' rows before they are read
+            return h;
+        }
+    }
+    return -1;
+}
+
+__global__ __launch_bounds__(kRedoBlock) void redo_rows_kernel(RedoArgs a)
+{
+    extern __shared__ __align__(16) unsigned char mem[];
+    if (!redo_flagged(a.overflow, a.heads, threadIdx.x)) return;
+    for (long item = blockIdx.x; item < (long)a.heads * a.S; item += gridDim.x)
+        if (a.overflow[item / a.S]) redo_row<true>(a, item, mem);   // (the same for every thread)
 }
 
 template <int ITEMS>   // 0: rows beyond 32768 entries
@@ -649,45 +800,98 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
 // triples: 19.4 us for 32736 nodes and 17.0 for 15969 with the row read behind the update and the lists read again;
 // 16.6 and 12.7 this way.)
 template <int ITEMS, int D>
-__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, MatchArgs a,
+__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, int heads, MatchArgs a,
                                                                 int32_t *__restrict__ src_out, DecayArgs update)
 {
-    static_assert(kPickBlock == kMatchBlock && kPickBlock == kUpdateBlock, "one workgroup does all");
+    static_assert(kPickBlock == kMatchBlock && kPickBlock == kUpdateBlock && kPickBlock == kRedoBlock, "one workgroup does all");
     extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
     PickLds<kPickBlock> &L = *reinterpret_cast<PickLds<kPickBlock> *>(mem);
     __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], to_s[kSmallK];
     __shared__ int32_t wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    float *xr = x + (long)h * n;
-    int32_t *src = src_out + (long)h * a.S;
-    const PickOut o{a.S, src, nullptr, nullptr};
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     Triples<D> tri;
-    bool bad;
-    if constexpr (ITEMS > 0) {
-        // (what the match needs first, then the update, then the row: loads come back in the order they leave)
-        const int32_t prev = a.prev_src[(long)h * a.S + min(tid, a.S - 1)];
-        const int32_t spec = a.X > 0 ? a.ext[(long)h * (a.S + a.X) + a.S + min(tid, a.X - 1)] : 0;
-        bad = a.X == 0 || (a.first ? a.overflow[h] : a.spec_bad[h]) != 0;
-        tri.load(update, h, tid);
-        float val[ITEMS];
-        load_row<kPickBlock>(xr, n, tid, val);
-        if (a.X > 0 && a.first && tid == 0) a.spec_bad[h] = bad ? 1 : 0;
-        if (tid < a.S) match_lds[tid] = prev;
-        if (tid < a.X) match_lds[2 * a.S + tid] = spec;
-        if (tid < kSmallK) to_s[tid] = -1;
-        if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, h, update, mem, tid);
-        L.clear(tid);
-        pick_row<kPickBlock, ITEMS, false>(val, xr, n, a.S, o, L, tid, lane, wv);
-    } else {
-        bad = match_load(a, h, match_lds, tid);
+    if constexpr (ITEMS == 0) {
+        const int h = blockIdx.x;
+        float *xr = x + (long)h * n;
+        int32_t *src = src_out + (long)h * a.S;
+        const PickOut o{a.S, src, nullptr, nullptr};
+        if (tid == 0) a.clear[h] = 0;
+        const bool bad = match_load(a, h, match_lds, tid);
         pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
+        __syncthreads();   // the sources are written
+        match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
+    } else {
+        int h = min((int)blockIdx.x, heads - 1);
+        // (what the match needs first, then the update, then the row: loads come back in the order they leave)
+        int32_t prev, spec;
+        bool bad;
+        float val[ITEMS];
+        auto ask = [&] {
+            const int tid = here(threadIdx.x);
+            prev = a.prev_src[(long)h * a.S + min(tid, a.S - 1)];
+            spec = a.X > 0 ? a.ext[(long)h * (a.S + a.X) + a.S + min(tid, a.X - 1)] : 0;
+            bad = a.X == 0 || (a.first ? a.overflow[h] : a.spec_bad[h]) != 0;
+            tri.load(update, h, tid);
+            load_row<kPickBlock>(x + (long)h * n, n, tid, val);
+        };
+        ask();
+        bool redo = false, mine = (int)blockIdx.x < heads;
+        long item = blockIdx.x;
+        if (D > 0 && update.redo.overflow) {
+            redo = redo_flagged(update.redo.overflow, heads, tid);
+            mine = mine && !(redo && update.redo.overflow[h]);
+        }
+        while (true) {
+            if (mine) {
+                const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
+                float *xr = x + (long)h * n;
+                int32_t *src = src_out + (long)h * a.S;
+                const PickOut o{a.S, src, nullptr, nullptr};
+                if (tid == 0) a.clear[h] = 0;
+                if (a.X > 0 && a.first && tid == 0) a.spec_bad[h] = bad ? 1 : 0;
+                if (tid < a.S) match_lds[tid] = prev;
+                if (tid < a.X) match_lds[2 * a.S + tid] = spec;
+                if (tid < kSmallK) to_s[tid] = -1;
+                if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, h, update, mem, tid);
+                L.clear(tid);
+                pick_row<kPickBlock, ITEMS, false>(val, xr, n, a.S, o, L, tid, lane, wv);
+                __syncthreads();   // the sources are written
+                match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
+            }
+            if (!redo) return;
+            __syncthreads();
+            h = redo_next(update.redo, item, wave_new, mem);
+            if (h < 0) return;
+            ask();
+            mine = true;
+        }
     }
-    __syncthreads();   // the sources are written
-    match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
 }
 template <int ITEMS, int D> constexpr size_t pick_match_lds()
 {
     return update_row_lds<ITEMS, D>() > sizeof(PickLds<kPickBlock>) ? update_row_lds<ITEMS, D>() : sizeof(PickLds<kPickBlock>);
+}
+
+// The update alone, rows redone first.
+template <int D>
+__global__ __launch_bounds__(kRedoBlock) void redo_decay_kernel(float *x, int P, int heads, DecayArgs u)
+{
+    extern __shared__ __align__(16) unsigned char mem[];
+    __shared__ int32_t last;
+    const int tid = threadIdx.x;
+    const bool redo = redo_flagged(u.redo.overflow, heads, tid);
+    int h = blockIdx.x;
+    bool mine = h < heads && !(redo && u.redo.overflow[h]);
+    for (long item = blockIdx.x;;) {
+        if (mine)
+            decay_chain<uint32_t, kRedoBlock, D, true>(x + (long)h * P, u.count, 2048 * D, u.nbr + (long)h * u.count,
+                                                       u.nbr_e + (long)h * u.count, u.alpha, u.signal, mem, tid);
+        if (!redo) return;
+        __syncthreads();
+        h = redo_next(u.redo, item, &last, mem);
+        if (h < 0) return;
+        mine = true;
+    }
 }
 
 // The k best edges of each row of a dense edge block, ascending indices, with their values.
@@ -826,28 +1030,17 @@ template <int ITEMS, int D> constexpr size_t budget_lds()
     return update_row_lds<ITEMS, D>() > own ? update_row_lds<ITEMS, D>() : own;
 }
 
-template <int ITEMS, int D>
-__global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
-    float *x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update, LayerPlan plan)
+// The k best of a row held in registers, ascending indices -> out.
+template <int ITEMS>
+__device__ __forceinline__ void budget_row(const float (&row)[ITEMS], int n, int k, int32_t *out, BudgetLds &L, int tid,
+                                           int lane, int wv)
 {
     constexpr int NW = kBudgetBlock / kWave, CELLS = ITEMS * NW;
-    static_assert(kBudgetBlock == kUpdateBlock, "one workgroup does both");
-    extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
-    BudgetLds &L = *reinterpret_cast<BudgetLds *>(mem);
     uint32_t *hist = L.hist, *list = L.list, *s_out = L.out;
     uint64_t *map = L.map;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = blockIdx.x;
-    const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
-    const int k = plan.budget[g] - append_count;
-    int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
-    float *xr = x + (long)row * n;
-
-    Triples<D> tri;
-    tri.load(update, row, tid);
     float val[ITEMS];
-    load_row<kBudgetBlock>(xr, n, tid, val);
-    for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
-    if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) val[i] = row[i];
     hist[tid] = 0;
     hist[tid + kBudgetBlock] = 0;
     list[tid] = 0;
@@ -935,6 +1128,55 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
         __syncthreads();
     }
     (void)emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), k, L.part[1], out, tid, lane, wv);
+}
+
+// REDO: rows of the last round may have to be redone first (the registers that takes cost the others 1 us).
+template <int ITEMS, int D, bool REDO>
+__global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
+    float *x, int n, int heads, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update,
+    LayerPlan plan)
+{
+    static_assert(kBudgetBlock == kUpdateBlock && kBudgetBlock == kRedoBlock, "one workgroup does all");
+    extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
+    BudgetLds &L = *reinterpret_cast<BudgetLds *>(mem);
+    __shared__ int32_t last;
+    (void)last;
+    const int tid = threadIdx.x;
+    int row = min((int)blockIdx.x, heads - 1);
+    Triples<D> tri;
+    float val[ITEMS];
+    auto ask = [&] {
+        const int tid = here(threadIdx.x);
+        tri.load(update, row, tid);
+        load_row<kBudgetBlock>(x + (long)row * n, n, tid, val);
+    };
+    ask();
+    bool redo = false, mine = (int)blockIdx.x < heads;
+    long item = blockIdx.x;
+    if constexpr (REDO) {
+        redo = redo_flagged(update.redo.overflow, heads, tid);
+        mine = mine && !(redo && update.redo.overflow[row]);
+    }
+    while (true) {
+        if (mine) {
+            const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
+            const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
+            const int k = plan.budget[g] - append_count;
+            int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
+            float *xr = x + (long)row * n;
+            for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+            if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
+            budget_row<ITEMS>(val, n, k, out, L, tid, lane, wv);
+        }
+        if (!REDO || !redo) return;
+        if constexpr (REDO) {
+            __syncthreads();
+            row = redo_next(update.redo, item, &last, mem);
+            if (row < 0) return;
+            ask();
+            mine = true;
+        }
+    }
 }
 
 // Rows beyond 32768 entries: two reads instead of five.  A coarse sample gives the key range, the
@@ -1212,68 +1454,6 @@ __global__ __launch_bounds__(kBudgetBlock) void split_select_kernel(
         for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
 }
 
-// ---- neighbourhoods of heads whose candidate lists overflowed ------------------------
-// The filter route (mfma_cosine.hip) gives up on a head when a candidate list cannot hold what
-// reaches the bound (masses of equal edges, an adversarial key order) and raises the head's
-// flag.  Such heads are rare, so they are not worth an [heads, S, P] edge block in memory: a
-// fixed number of workgroups walk the (head, source) rows of the flagged heads, and each row's
-// edges (Eq. 1) go to the workgroup's own scratch row of P floats, out of which the exact top-m
-// (Eq. 3) is taken by the row kernels above.  The edges are formed exactly as in the streaming
-// kernels -- the same matrix-core instruction sequence with the source in every operand row, the
-// same norms -- so that a head gets the same bits whichever route it takes.  A launch that
-// finds no flag set returns after one round trip.
-constexpr int kRedoBlock = 1024;
-
-__global__ __launch_bounds__(kRedoBlock) void redo_rows_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int P, int S, int m, int heads,
-    const int32_t *__restrict__ src, const int32_t *__restrict__ overflow, float *__restrict__ rows,
-    int32_t *__restrict__ nbr, float *__restrict__ nbr_e)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-    int open = 0;
-    for (int g = tid; g < heads; g += kRedoBlock) open |= overflow[g] != 0;
-    if (!__syncthreads_or(open)) return;
-    float *erow = rows + (long)blockIdx.x * P;
-    for (long item = blockIdx.x; item < (long)heads * S; item += gridDim.x) {
-        const int h = (int)(item / S);
-        if (overflow[h] == 0) continue;           // (the same for every thread)
-        const int32_t i = src[item];
-        const uint16_t *ah = Ac + (long)h * N * kD, *kh = Kc + (long)h * N * kD;
-        __syncthreads();                          // the previous row's LDS and scratch row are free
-        // the source's row in every row of the operand (a lane holds elements 16 s + 8 hh ..)
-        bf16x8 q[kSteps];
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s) q[s] = load8(ah + (long)i * kD + 16 * s + 8 * hh);
-        float sq_i = half_row_sumsq(q);
-        sq_i = add_other_half(sq_i);
-        const float inv_i = inv_norm(sq_i);
-        // blocks of 32 keys, one per wave at a time: key l32 of the block is the operand's column
-        for (int j0 = wv * kBlk; j0 < P; j0 += (kRedoBlock / kWave) * kBlk) {
-            const int j = min(j0 + l32, P - 1);
-            bf16x8 kc[kSteps];
-#pragma unroll
-            for (int s = 0; s < kSteps; ++s) kc[s] = load8(kh + (long)j * kD + 16 * s + 8 * hh);
-            f32x16 acc;
-#pragma unroll
-            for (int u = 0; u < 16; ++u) acc[u] = 0.f;
-#pragma unroll
-            for (int s = 0; s < kSteps; ++s)   // rows = the source (32 times), columns = keys
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[s], kc[s], acc, 0, 0, 0);
-            float sq = half_row_sumsq(kc);
-            sq = add_other_half(sq);
-            const float e = (acc[0] * inv_norm(sq)) * inv_i;
-            if (hh == 0 && j0 + l32 < P) erow[j] = j == i ? -INFINITY : e;   // (Eq. 3: j != i)
-        }
-        __syncthreads();                          // the row is complete and visible to the workgroup
-        int32_t *out = nbr + item * m;
-        float *vout = nbr_e + item * m;
-        if (P <= 32768)
-            topk_row_lds<kRedoBlock, 11>(0, erow, P, P, m, out, 0, vout, 0);
-        else
-            topk_stream_row<kRedoBlock, false>(0, erow, P, P, m, out, 0, vout, 0, 0, 0, 0);
-    }
-}
-
 template <int BLOCK, int DIG>
 static hipError_t launch_lds(const float *x, long ld, int n, int rows, int k, int32_t *idx_out, long idx_ld,
                              float *val_out, long val_ld, hipStream_t st)
@@ -1304,15 +1484,21 @@ static hipError_t launch_pick(const float *x, long ld, int n, int rows, int k, i
 
 bool pick_match_applies(int S) { return S <= kSmallK; }
 
+static int redo_grid(int heads, const DecayArgs &update);
+static size_t redo_lds(size_t own, const DecayArgs &update);
+constexpr int kBigLds = 147456;   // dynamic LDS of the kernels that take an update along, at most
+static_assert(update_row_lds<32, 2>() <= kBigLds && update_row_lds<32, 4>() <= kBigLds && kRedoLds <= kBigLds, "");
+
 template <int D>
 static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs &a, int32_t *src,
                                       const DecayArgs &update, hipStream_t st)
 {
 #define GKV_PICK(ITEMS)                                                                                          \
     do {                                                                                                         \
-        constexpr size_t lds = pick_match_lds<ITEMS, D>();                                                       \
-        if (lds > 40 * 1024 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, (int)lds)) return hipGetLastError(); \
-        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), lds, st, x, n, a, src, update); \
+        const size_t lds = redo_lds(pick_match_lds<ITEMS, D>(), update);                                         \
+        if (D > 0 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, kBigLds)) return hipGetLastError(); \
+        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(redo_grid(rows, update)), dim3(kPickBlock), lds, st, x, n, \
+                           rows, a, src, update);                                                                \
     } while (0)
     if (n <= 4096) GKV_PICK(4);   // (lists are kept on the filter route only: 2048 nodes or more)
     else if (n <= 8192) GKV_PICK(8);
@@ -1363,31 +1549,44 @@ hipError_t launch_topk_rows(const float *x, long ld, int n, int rows, int k, int
     return hipGetLastError();
 }
 
-// Workgroups that walk the rows of flagged heads: one per compute unit, fewer for long rows
-// (their scratch rows stay within 64 MiB), at least 16.
-int redo_rows_workgroups(int heads, int S, int P)
-{
-    const long items = (long)heads * S;
-    long wgs = ((long)64 << 20) / ((long)P * 4);
-    wgs = wgs < 16 ? 16 : (wgs > 256 ? 256 : wgs);
-    return (int)(items < wgs ? items : wgs);
-}
-
 size_t redo_rows_scratch_bytes(int heads, int S, int P)
 {
     return (size_t)redo_rows_workgroups(heads, S, P) * P * sizeof(float);
 }
 
-hipError_t launch_redo_rows(const void *Ac, const void *Kc, int heads, int N, int P, int S, int m,
-                            const int32_t *src, const int32_t *overflow, float *rows, int32_t *nbr,
-                            float *nbr_e, hipStream_t st)
+hipError_t launch_redo_rows(const RedoArgs &a, hipStream_t st)
 {
-    const int items = P <= 32768 ? (P + kRedoBlock - 1) / kRedoBlock : 0;   // keys of a row in LDS
-    const size_t lds = ((size_t)items * kRedoBlock + 2 * (size_t)items * (kRedoBlock / kWave)) * 4;
-    if (lds > 65536 && !allow_big_lds((const void *)redo_rows_kernel, 140 * 1024)) return hipGetLastError();
-    hipLaunchKernelGGL(redo_rows_kernel, dim3(redo_rows_workgroups(heads, S, P)), dim3(kRedoBlock), lds, st,
-                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, S, m, heads, src, overflow, rows, nbr,
-                       nbr_e);
+    if (!allow_big_lds((const void *)redo_rows_kernel, (int)kRedoLds)) return hipGetLastError();
+    hipLaunchKernelGGL(redo_rows_kernel, dim3(redo_rows_workgroups(a.heads, a.S, a.P)), dim3(kRedoBlock), kRedoLds, st, a);
+    return hipGetLastError();
+}
+
+// Workgroups of a kernel with a workgroup per head that redoes rows first.
+static int redo_grid(int heads, const DecayArgs &update)
+{
+    if (!update.redo.overflow) return heads;
+    const int wgs = redo_rows_workgroups(heads, update.redo.S, update.redo.P);
+    return wgs > heads ? wgs : heads;
+}
+// ... and its dynamic LDS.
+static size_t redo_lds(size_t own, const DecayArgs &update) { return update.redo.overflow && own < kRedoLds ? kRedoLds : own; }
+
+// The last round's update as a launch of its own, rows redone first.
+hipError_t launch_redo_decay(float *scores, int rows, int P, const DecayArgs &u, hipStream_t st)
+{
+#define GKV_DECAY(D)                                                                                                  \
+    do {                                                                                                              \
+        const size_t lds = redo_lds(decay_chain_lds<uint32_t>(2048 * D, 1024 * D, true), u);                          \
+        if (!allow_big_lds((const void *)redo_decay_kernel<D>, (int)lds)) return hipGetLastError();                    \
+        hipLaunchKernelGGL(redo_decay_kernel<D>, dim3(redo_grid(rows, u)), dim3(kRedoBlock), lds, st, scores, P, rows, u); \
+    } while (0)
+    switch (u.items) {
+        case 1: GKV_DECAY(1); break;
+        case 2: GKV_DECAY(2); break;
+        case 4: GKV_DECAY(4); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef GKV_DECAY
     return hipGetLastError();
 }
 
@@ -1409,12 +1608,14 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
 {
 #define GKV_BUDGET(ITEMS)                                                                                       \
     do {                                                                                                        \
-        constexpr size_t lds = budget_lds<ITEMS, D>();                                                          \
-        if (lds > 40 * 1024 && !allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, (int)lds)) return hipGetLastError(); \
-        hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), lds, st,           \
-                           scores, P, idx, P, w, update, plan);                                                 \
+        const size_t lds = redo_lds(budget_lds<ITEMS, D>(), update);                                            \
+        constexpr bool may = ITEMS > 1 && D > 0;                                                                \
+        auto *kernel = may && update.redo.overflow ? budget_select_kernel<ITEMS, D, may> : budget_select_kernel<ITEMS, D, false>; \
+        if (D > 0 && !allow_big_lds((const void *)kernel, kBigLds)) return hipGetLastError();                   \
+        hipLaunchKernelGGL(kernel, dim3(redo_grid(rows, update)), dim3(kBudgetBlock), lds, st, scores, P, rows, \
+                           idx, P, w, update, plan);                                                            \
     } while (0)
-    if (P <= 1024) GKV_BUDGET(1);
+    if (P <= 1024) GKV_BUDGET(1);   // (the filter route, whose rows may be redone, starts at 2048)
     else if (P <= 2048) GKV_BUDGET(2);
     else if (P <= 4096) GKV_BUDGET(4);
     else if (P <= 8192) GKV_BUDGET(8);

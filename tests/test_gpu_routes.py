@@ -69,3 +69,37 @@ def test_long_rows_shared_out_in_a_whole_pass():
         assert torch.equal(K1.view(-1, d), Ks[at]) and torch.equal(V1.view(-1, d), Vs[at])
         ref = K[l, :, :N - w].double().norm(dim=2).neg().topk(B - w, dim=1).indices.sort(dim=1).values
         assert (i1[:, :B - w] == ref).float().mean() > 0.99
+
+
+@pytest.mark.parametrize("N,S,m,signal", [(8300, 64, 32, 0), (8224, 40, 90, 0), (9000, 64, 16, 1), (16416, 20, 200, 2)])
+def test_redone_heads_in_few_and_in_many(N, S, m, signal):
+    """Three rounds over layers in which a head's candidate lists overflow (runs of similar keys) and one's do not: few
+    heads take a round's late lists in one launch, many in three, and with both the heads that are redone are gone
+    on with by the workgroup that finishes their last row (m = 90 and 200: more triples than a kernel takes along,
+    or lists that the general selection makes)."""
+    say(f"redone heads, few and many N={N} S={S} m={m} signal={signal}")
+    L, H, d, w, B = 40, 3, 128, 32, 300
+    g = torch.Generator("cuda").manual_seed(N)
+    K = torch.randn(L, H, N, d, generator=g, device="cuda")
+    run = 900
+    centre = torch.randn(L, -(-N // run), d, generator=g, device="cuda")
+    K[:, 1] = centre.repeat_interleave(run, dim=1)[:, :N] + 0.7 * K[:, 1]
+    kind = torch.randint(0, 64, (L, N), generator=g, device="cuda")
+    K[:, 2] = 0.4 * K[:, 2] + torch.randn(L, 64, d, generator=g, device="cuda").gather(1, kind[..., None].expand(-1, -1, d))
+    K = K.to(torch.bfloat16)
+    V = torch.randn(L, H, N, d, generator=g, device="cuda").to(torch.bfloat16)
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=B, n_sources=S, n_neighbors=m,
+                  rounds=3, signal=signal, scorer=gk.SCORER_KNORM)
+    sc = torch.empty(L, H, N - w, device="cuda")
+    Ks, Vs, idx = gk.graphkv_compress_batched(p, L, None, K, V, None, scores_out=sc)
+    generic = gk.Params(**{**p.__dict__, "impl": gk.IMPL_GENERIC})
+    for l in (0, 7, L - 1):
+        s1, s2 = (torch.empty(H, N - w, device="cuda") for _ in range(2))
+        K1, V1, i1 = gk.graphkv_compress(p, K[l], V[l], None, scores_out=s1)
+        at = slice(l * H * B, (l + 1) * H * B)
+        assert torch.equal(i1.flatten(), idx[at]) and torch.equal(s1, sc[l])
+        assert torch.equal(K1.view(-1, d).view(torch.int16), Ks[at].view(torch.int16))
+        # the scalar kernels, whose edges round otherwise: the same nodes but for near-ties
+        _, _, i2 = gk.graphkv_compress(generic, K[l], V[l], None, scores_out=s2)
+        assert (i1 == i2).float().mean() > 0.95
+        assert torch.isclose(s1, s2, rtol=1e-3, atol=0.0).float().mean() > 0.95   # (evicted nodes: equal infinities)
