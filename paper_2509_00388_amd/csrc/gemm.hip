@@ -5,7 +5,7 @@
 //
 // A workgroup of four waves multiplies a tile of keys with up to 128 rows (window queries, or source
 // keys).  Rows and keys pass through LDS in pieces of 256 bytes a row, read from memory with coalesced
-// 16-byte loads and padded to 272 bytes against bank conflicts.  A lane reads 16 bytes of its row per
+// 16-byte loads and padded by 16 bytes against bank conflicts.  A lane reads 16 bytes of its row per
 // step: for bf16 the eight elements of one instruction, for fp32 four elements that feed four
 // instructions (instruction e takes element e of both half-waves: k = 8 s + e and 8 s + 4 + e, the same
 // pairs for rows and keys).  What bounds the kernels at these sizes is the matrix rate for fp32 and
@@ -21,10 +21,9 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float acc16 __attribute__((ext_vector_type(16)));
 
-constexpr int kRowBytes = 256;              // bytes of a row staged at a time
-constexpr int kRowPitch = kRowBytes + 16;   // in LDS
-constexpr int kPieces = kRowBytes / 16;
-constexpr int kMaxSteps = kRowBytes / 32;
+// PB: bytes of a row staged at a time, 256 or, for rows of up to 128 bytes, 128 (half the loads and LDS writes would
+// be of zeros otherwise).
+constexpr int pitch_of(int PB) { return PB + 16; }   // in LDS
 
 __device__ __forceinline__ int mfma_row(int i, int hh) { return 8 * (i >> 2) + 4 * hh + (i & 3); }
 
@@ -52,29 +51,33 @@ template <typename T> __device__ __forceinline__ float sum_squares(const uint4 &
     return s;
 }
 
-// ROWS rows of row_bytes bytes each (row(r) = address of row r) -> LDS, bytes c0 .. c0 + 255 of each,
-// zeros past the end of a row.  Four loads in flight per thread.
-template <int ROWS, typename Row>
-__device__ __forceinline__ void stage_rows(unsigned char *lds, int c0, int row_bytes, int tid, Row &&row)
-{
-    static_assert(ROWS * kPieces % (256 * 2) == 0, "pieces per thread");
-    constexpr int PER = ROWS * kPieces / 256, B = PER < 4 ? PER : 4;
+// ROWS rows on their way to the LDS: bytes c0 .. c0 + PB - 1 of each (row(r) = address of row r), zeros past the end
+// of a row.  The loads of a piece are asked for while the piece before it is multiplied.  (Before, each piece was
+// fetched four loads at a time behind the barrier that frees the LDS, 256 bytes whatever the row: logits and edges of
+// 16 heads x 8160 bf16 keys of 64 with 32 rows 14.1 and 14.9 us, 11.3 and 12.4 this way; edges of 8 heads x 4064
+// fp32 keys of 128 with 32 sources 12.2, now 10.7.)
+template <int ROWS, int PB> struct Staged {
+    static constexpr int PIECES = PB / 16, PER = ROWS * PIECES / 256;
+    static_assert(ROWS * PIECES % 256 == 0, "pieces per thread");
+    uint4 v[PER];
+    template <typename Row> __device__ __forceinline__ void ask(int c0, int row_bytes, int tid, Row &&row)
+    {
 #pragma unroll
-    for (int u0 = 0; u0 < PER; u0 += B) {
-        uint4 v[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-            const int g = tid + (u0 + u) * 256, r = g / kPieces, at = c0 + 16 * (g % kPieces);
-            v[u] = *reinterpret_cast<const uint4 *>(row(r) + (at < row_bytes ? at : 0));
-            if (at >= row_bytes) v[u] = make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-            const int g = tid + (u0 + u) * 256;
-            *reinterpret_cast<uint4 *>(lds + (g / kPieces) * kRowPitch + 16 * (g % kPieces)) = v[u];
+        for (int u = 0; u < PER; ++u) {
+            const int g = tid + u * 256;
+            v[u] = *reinterpret_cast<const uint4 *>(row(g / PIECES) + min(c0 + 16 * (g % PIECES), row_bytes - 16));
         }
     }
-}
+    __device__ __forceinline__ void put(unsigned char *lds, int c0, int row_bytes, int tid) const
+    {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int g = tid + u * 256;
+            const bool in = c0 + 16 * (g % PIECES) < row_bytes;
+            *reinterpret_cast<uint4 *>(lds + (g / PIECES) * pitch_of(PB) + 16 * (g % PIECES)) = in ? v[u] : make_uint4(0, 0, 0, 0);
+        }
+    }
+};
 
 __device__ __forceinline__ float other_half(float x)   // x of the lane 32 places away
 {
@@ -99,13 +102,14 @@ template <int NBR> struct Shape {
 // (chunk of keys, row) the maximum and the sum of exp over the chunk's visible keys.  Keys are the rows of the products, queries the
 // columns: a lane owns one query and keeps its statistics without cross-lane traffic.  MANY: a workgroup takes
 // `per_wg` consecutive chunks, whole tiles each, and keeps their statistics apart.
-template <typename T, int NBR, bool MANY>
+template <typename T, int NBR, int PB, bool MANY>
 __global__ __launch_bounds__(256) void gemm_logits_kernel(
     const T *__restrict__ Kc, const T *__restrict__ Qw, int d, int N, int P, int w, int R, float scale,
     int chunk_keys, int nchunks, int per_wg, int pitch, float *__restrict__ logits, float *__restrict__ part)
 {
     using Sh = Shape<NBR>;
-    __shared__ __align__(16) unsigned char kt[Sh::TK * kRowPitch], qt[Sh::TR * kRowPitch];
+    constexpr int PITCH = pitch_of(PB), STEPS = PB / 32;
+    __shared__ __align__(16) unsigned char kt[Sh::TK * PITCH], qt[Sh::TR * PITCH];
     __shared__ float sm[Sh::STREAMS][Sh::TR], sz[Sh::STREAMS][Sh::TR];
     const int h = blockIdx.y, row0 = blockIdx.z * Sh::TR;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
@@ -114,6 +118,17 @@ __global__ __launch_bounds__(256) void gemm_logits_kernel(
     const char *Kh = reinterpret_cast<const char *>(Kc + (long)h * N * d);
     const char *Qh = reinterpret_cast<const char *>(Qw + (long)h * R * d);
     const int first = blockIdx.x * (MANY ? per_wg : 1), last = MANY ? min(nchunks, first + per_wg) : first + 1;
+    const bool whole = row_bytes <= PB;   // (the queries stay when they fit whole)
+    Staged<Sh::TK, PB> kin;
+    Staged<Sh::TR, PB> qin;
+    auto ask_keys = [&](int t0, int c0) {
+        kin.ask(c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, N - 1) * row_bytes; });
+    };
+    auto ask_queries = [&](int c0) {
+        qin.ask(c0, row_bytes, tid, [&](int r) { return Qh + (long)min(row0 + r, R - 1) * row_bytes; });
+    };
+    ask_keys(first * chunk_keys, 0);
+    ask_queries(0);
     for (int chunk = first; chunk < last; ++chunk) {
         const int k0 = chunk * chunk_keys, k1 = min(N, k0 + chunk_keys), kstore = min(k1, pitch);
         float m[Sh::NBW], z[Sh::NBW];
@@ -130,22 +145,25 @@ __global__ __launch_bounds__(256) void gemm_logits_kernel(
             for (int b = 0; b < Sh::NBW; ++b)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-            for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
+            for (int c0 = 0; c0 < row_bytes; c0 += PB) {
                 __syncthreads();   // the tiles in LDS are free
-                stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, N - 1) * row_bytes; });
-                if ((t0 == k0 && chunk == first) || row_bytes > kRowBytes)   // (the queries stay when they fit whole)
-                    stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Qh + (long)min(row0 + r, R - 1) * row_bytes; });
+                kin.put(kt, c0, row_bytes, tid);
+                if (!whole || (t0 == k0 && chunk == first)) qin.put(qt, c0, row_bytes, tid);
                 __syncthreads();
-                const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
-                const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
-                const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
+                // the next piece: of this tile, or of the next one (past the last, rows that are there)
+                const int cn = c0 + PB < row_bytes ? c0 + PB : 0;
+                ask_keys(cn ? t0 : t0 + Sh::TK, cn);
+                if (!whole) ask_queries(cn);
+                const int steps = (min(row_bytes - c0, PB) + 31) / 32;
+                const unsigned char *kp = kt + (32 * stream + l32) * PITCH + 16 * hh;
+                const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * PITCH + 16 * hh;
 #pragma unroll
-                for (int s = 0; s < kMaxSteps; ++s) {
+                for (int s = 0; s < STEPS; ++s) {
                     if (s >= steps) break;
                     const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
 #pragma unroll
                     for (int b = 0; b < Sh::NBW; ++b)
-                        mfma_step<T>(k, *reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), acc[b]);
+                        mfma_step<T>(k, *reinterpret_cast<const uint4 *>(qp + 32 * b * PITCH + 32 * s), acc[b]);
                 }
             }
             const int key0 = t0 + 32 * stream;
@@ -352,13 +370,14 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const float *__restrict
 // Eq. 1: E[h, a, j] = cosine of row src[h, a] of Ac and row j of Kc, -inf where j is the source itself
 // (Eq. 3).  Sources are the rows of the products and keys the columns: a lane owns one key, whose norm
 // it sums from the very registers that feed the products, and stores run along the keys.
-template <typename T, int NBR>
+template <typename T, int NBR, int PB>
 __global__ __launch_bounds__(256) void gemm_cosine_kernel(
     const T *__restrict__ Ac, const T *__restrict__ Kc, int d, int N, int P, int S, const int32_t *__restrict__ src,
     int chunk_keys, float *__restrict__ E)
 {
     using Sh = Shape<NBR>;
-    __shared__ __align__(16) unsigned char kt[Sh::TK * kRowPitch], qt[Sh::TR * kRowPitch];
+    constexpr int PITCH = pitch_of(PB), STEPS = PB / 32;
+    __shared__ __align__(16) unsigned char kt[Sh::TK * PITCH], qt[Sh::TR * PITCH];
     __shared__ float inv_s[Sh::TR];
     __shared__ int32_t idx_s[Sh::TR];
     const int h = blockIdx.y, row0 = blockIdx.z * Sh::TR;
@@ -368,7 +387,20 @@ __global__ __launch_bounds__(256) void gemm_cosine_kernel(
     const char *Kh = reinterpret_cast<const char *>(Kc + (long)h * N * d);
     const char *Ah = reinterpret_cast<const char *>(Ac + (long)h * N * d);
     const int k0 = blockIdx.x * chunk_keys, k1 = min(P, k0 + chunk_keys);
-    for (int r = tid; r < Sh::TR; r += 256) idx_s[r] = src[(long)h * S + min(row0 + r, S - 1)];
+    const bool whole = row_bytes <= PB;
+    Staged<Sh::TK, PB> kin;
+    Staged<Sh::TR, PB> qin;
+    auto ask_keys = [&](int t0, int c0) {
+        kin.ask(c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, P - 1) * row_bytes; });
+    };
+    auto ask_sources = [&](int c0) {
+        qin.ask(c0, row_bytes, tid, [&](int r) { return Ah + (long)idx_s[r] * row_bytes; });
+    };
+    const int32_t mine = src[(long)h * S + min(row0 + tid, S - 1)];   // (in front of the keys: the sources' rows wait for it)
+    ask_keys(k0, 0);
+    if (tid < Sh::TR) idx_s[tid] = mine;
+    __syncthreads();
+    ask_sources(0);
     for (int t0 = k0; t0 < k1; t0 += Sh::TK) {
         acc16 acc[Sh::NBW];
 #pragma unroll
@@ -376,26 +408,28 @@ __global__ __launch_bounds__(256) void gemm_cosine_kernel(
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
         float sq = 0.f, sq_src = 0.f;
-        for (int c0 = 0; c0 < row_bytes; c0 += kRowBytes) {
-            __syncthreads();   // the tiles in LDS are free, the source indices there
-            stage_rows<Sh::TK>(kt, c0, row_bytes, tid, [&](int r) { return Kh + (long)min(t0 + r, P - 1) * row_bytes; });
-            if (t0 == k0 || row_bytes > kRowBytes)
-                stage_rows<Sh::TR>(qt, c0, row_bytes, tid, [&](int r) { return Ah + (long)idx_s[r] * row_bytes; });
+        for (int c0 = 0; c0 < row_bytes; c0 += PB) {
+            __syncthreads();   // the tiles in LDS are free
+            kin.put(kt, c0, row_bytes, tid);
+            if (!whole || t0 == k0) qin.put(qt, c0, row_bytes, tid);
             __syncthreads();
-            const int steps = (min(row_bytes - c0, kRowBytes) + 31) / 32;
+            const int cn = c0 + PB < row_bytes ? c0 + PB : 0;   // the next piece
+            ask_keys(cn ? t0 : t0 + Sh::TK, cn);
+            if (!whole) ask_sources(cn);
+            const int steps = (min(row_bytes - c0, PB) + 31) / 32;
             if (t0 == k0 && tid < Sh::TR)   // a thread per source (zeros behind the row's end)
                 for (int u = 0; u < 2 * steps; ++u)
-                    sq_src = sum_squares<T>(*reinterpret_cast<const uint4 *>(qt + tid * kRowPitch + 16 * u), sq_src);
-            const unsigned char *kp = kt + (32 * stream + l32) * kRowPitch + 16 * hh;
-            const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * kRowPitch + 16 * hh;
+                    sq_src = sum_squares<T>(*reinterpret_cast<const uint4 *>(qt + tid * PITCH + 16 * u), sq_src);
+            const unsigned char *kp = kt + (32 * stream + l32) * PITCH + 16 * hh;
+            const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * PITCH + 16 * hh;
 #pragma unroll
-            for (int s = 0; s < kMaxSteps; ++s) {
+            for (int s = 0; s < STEPS; ++s) {
                 if (s >= steps) break;
                 const uint4 k = *reinterpret_cast<const uint4 *>(kp + 32 * s);
                 sq = sum_squares<T>(k, sq);
 #pragma unroll
                 for (int b = 0; b < Sh::NBW; ++b)
-                    mfma_step<T>(*reinterpret_cast<const uint4 *>(qp + 32 * b * kRowPitch + 32 * s), k, acc[b]);
+                    mfma_step<T>(*reinterpret_cast<const uint4 *>(qp + 32 * b * PITCH + 32 * s), k, acc[b]);
             }
         }
         if (t0 == k0) {
@@ -474,9 +508,11 @@ static void launch_logits_t(const T *K, const T *Q, int Hkv, int R, int d, int N
 {
     const int nb = row_blocks(R);
     const dim3 grid((pl.chunks + pl.per_wg - 1) / pl.per_wg, Hkv, (R + 32 * nb - 1) / (32 * nb));
+    const bool narrow = d * (int)sizeof(T) <= 128;
 #define GKV_LOGITS(NB)                                                                                             \
     do {                                                                                                           \
-        auto *kernel = pl.per_wg > 1 ? gemm_logits_kernel<T, NB, true> : gemm_logits_kernel<T, NB, false>;         \
+        auto *kernel = narrow ? (pl.per_wg > 1 ? gemm_logits_kernel<T, NB, 128, true> : gemm_logits_kernel<T, NB, 128, false>)  \
+                              : (pl.per_wg > 1 ? gemm_logits_kernel<T, NB, 256, true> : gemm_logits_kernel<T, NB, 256, false>); \
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, K, Q, d, N, P, w, R, scale, pl.chunk_keys, pl.chunks,   \
                            pl.per_wg, pl.pitch, logits, part);                                                     \
     } while (0)
@@ -532,8 +568,12 @@ static void launch_cosine_t(const T *A, const T *K, int Hkv, int d, int N, int P
 {
     const int nb = row_blocks(S), ck = gemm_chunk_keys(Hkv, S, P);
     const dim3 grid((P + ck - 1) / ck, Hkv, (S + 32 * nb - 1) / (32 * nb));
-#define GKV_COSINE(NB) \
-    hipLaunchKernelGGL((gemm_cosine_kernel<T, NB>), grid, dim3(256), 0, st, A, K, d, N, P, S, src, ck, E)
+    const bool narrow = d * (int)sizeof(T) <= 128;
+#define GKV_COSINE(NB)                                                                                             \
+    do {                                                                                                           \
+        auto *kernel = narrow ? gemm_cosine_kernel<T, NB, 128> : gemm_cosine_kernel<T, NB, 256>;                   \
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, A, K, d, N, P, S, src, ck, E);                          \
+    } while (0)
     if (nb == 1) GKV_COSINE(1);
     else if (nb == 2) GKV_COSINE(2);
     else GKV_COSINE(4);

@@ -103,3 +103,35 @@ def test_redone_heads_in_few_and_in_many(N, S, m, signal):
         _, _, i2 = gk.graphkv_compress(generic, K[l], V[l], None, scores_out=s2)
         assert (i1 == i2).float().mean() > 0.95
         assert torch.isclose(s1, s2, rtol=1e-3, atol=0.0).float().mean() > 0.95   # (evicted nodes: equal infinities)
+
+
+# (rows of 16 bytes, of exactly 128, of a little more, of exactly 256, of several pieces and a rest)
+@pytest.mark.parametrize("fp32,d", [(0, 8), (0, 64), (0, 72), (1, 32), (1, 40), (1, 64), (1, 168), (0, 200)])
+@pytest.mark.parametrize("G,w,S", [(1, 16, 5), (2, 24, 40), (4, 33, 70)])
+def test_tiled_products_by_row_length(fp32, d, G, w, S):
+    """Scores and edges of the tiled matrix products against 64 bits for every length of a row that is staged
+    differently, with one, two and four row blocks and tiles that end in the middle."""
+    say(f"tiled products fp32={fp32} d={d} rows={G * w} S={S}")
+    H, N = 2, 777
+    g = torch.Generator("cuda").manual_seed(100 * d + S)
+    td = torch.float32 if fp32 else torch.bfloat16
+    K = torch.randn(H, N, d, generator=g, device="cuda").to(td)
+    Q = torch.randn(H * G, w, d, generator=g, device="cuda").to(td)
+    P = N - w
+    p = gk.Params(n_kv_heads=H, n_q_heads=H * G, head_dim=d, n_tokens=N, window=w, pool_kernel=5, budget=w + 1, n_sources=S,
+                  n_neighbors=P - 1, rounds=1, dtype=gk.FP32 if fp32 else gk.BF16)
+    sc = gk.graphkv_score(p, K, Q)
+    l = (Q.double().view(H, G * w, d) @ K.double().transpose(1, 2).contiguous()) / d ** 0.5
+    hidden = torch.arange(N, device="cuda")[None] > (P + torch.arange(w, device="cuda").repeat(G))[:, None]
+    votes = l.masked_fill(hidden, -torch.inf).softmax(2)[:, :, :P].sum(1)
+    ref = torch.nn.functional.avg_pool1d(votes[:, None], 5, 1, 2)[:, 0] / G
+    # 32-bit logits of size up to |l| are off by 2e-7 |l| d^0.5 at most, their exponentials by as much
+    assert ((sc - ref).abs() <= 2e-5 * ref).all()
+    src = torch.empty(1, H, S, dtype=torch.int32, device="cuda")
+    nbr = torch.empty(1, H, S, P - 1, dtype=torch.int32, device="cuda")
+    e = torch.empty(1, H, S, P - 1, device="cuda")
+    gk.graphkv_propagate(p, K, sc.clone(), src, nbr, e)
+    Kn = torch.nn.functional.normalize(K[:, :P].double(), dim=2)
+    for h in range(H):   # m = P - 1: every edge but a source's own
+        full = Kn[h][src[0, h].long()] @ Kn[h].T
+        assert ((full.gather(1, nbr[0, h].long()) - e[0, h]).abs() <= 2e-5).all()
