@@ -521,9 +521,9 @@ LayerPlan make_plan(const graphkv_params *p, int n_layers, const int32_t *budget
 }
 
 int32_t run_select(const Dims &D, const LayerPlan &plan, float *scores, int32_t *idx, const DecayArgs &update,
-                   void *scratch, hipStream_t st)
+                   const GatherArgs &gather, void *scratch, hipStream_t st)
 {
-    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, update, scratch, st));
+    GKV_LAUNCH(GRAPHKV_K_TOPK_FINAL, launch_topk_final(scores, D.P, D.H, plan, D.w, idx, update, gather, scratch, st));
     return GRAPHKV_OK;
 }
 
@@ -547,9 +547,13 @@ int32_t run_compress(const graphkv_params *p, int n_layers, const Dims &group, c
     if (int32_t rc = run_propagate(p, D, W, edge_src, edge_nbr, scores, nullptr, nullptr, nullptr, ws, st, &update))
         return rc;
     void *sel = W.final_bytes ? at<void>(ws, W.final_sel) : nullptr;
-    if (int32_t rc = run_select(D, plan, scores, idx, update, sel, st)) return rc;
-    GKV_LAUNCH(GRAPHKV_K_GATHER, launch_gather(Kc, Vc, idx, D.H, D.N, plan, max_budget,
-                                               (int)(D.d * D.esize), Kout, Vout, st));
+    const int row_bytes = (int)(D.d * D.esize);
+    GatherArgs gather{Kc, Vc, Kout, Vout, D.N, row_bytes};
+    const bool with_it = topk_final_gathers(D.P, max_budget, row_bytes);
+    if (!with_it) gather.Kout = nullptr;
+    if (int32_t rc = run_select(D, plan, scores, idx, update, gather, sel, st)) return rc;
+    if (!with_it)
+        GKV_LAUNCH(GRAPHKV_K_GATHER, launch_gather(Kc, Vc, idx, D.H, D.N, plan, max_budget, row_bytes, Kout, Vout, st));
     return GRAPHKV_OK;
 }
 
@@ -704,7 +708,8 @@ int32_t graphkv_select(const graphkv_params *p, const float *scores, int32_t *id
     const size_t need = topk_final_scratch_bytes(D.H, D.P);
     void *sel = need && check_ws(need, ws, ws_bytes) == GRAPHKV_OK ? ws : nullptr;
     // (no update rides along: the scores are only read)
-    return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{}, sel,
+    return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{}, GatherArgs{},
+                      sel,
                       (hipStream_t)stream);
 }
 

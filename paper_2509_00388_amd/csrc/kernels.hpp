@@ -116,9 +116,16 @@ hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int
 // followed by the window tokens P .. P + w - 1, to its packed idx row.
 // (An update that rides along changes the scores first.)  scratch: topk_final_scratch_bytes() bytes, with which
 // few long rows are shared out to many workgroups (0: none is used), or nullptr.
+// gather: Kout null, or the retained rows are copied too (topk_final_gathers()).
+struct GatherArgs {
+    const void *Kc, *Vc;
+    void *Kout, *Vout;
+    int N, row_bytes;
+};
+bool topk_final_gathers(int P, int max_budget, int row_bytes);
 size_t topk_final_scratch_bytes(int rows, int P);
 hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
-                             const DecayArgs &update, void *scratch, hipStream_t st);
+                             const DecayArgs &update, const GatherArgs &gather, void *scratch, hipStream_t st);
 hipError_t launch_copy_i32(const int32_t *src, int32_t *dst, long n, hipStream_t st);
 hipError_t launch_copy_f32(const float *src, float *dst, long n, hipStream_t st);
 

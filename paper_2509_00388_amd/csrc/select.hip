@@ -1134,7 +1134,7 @@ __device__ __forceinline__ void budget_row(const float (&row)[ITEMS], int n, int
 template <int ITEMS, int D, bool REDO>
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
     float *x, int n, int heads, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update,
-    LayerPlan plan)
+    GatherArgs rows, LayerPlan plan)
 {
     static_assert(kBudgetBlock == kUpdateBlock && kBudgetBlock == kRedoBlock, "one workgroup does all");
     extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
@@ -1167,6 +1167,19 @@ __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
             for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
             if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
             budget_row<ITEMS>(val, n, k, out, L, tid, lane, wv);
+            if (rows.Kout) {
+                // The retained rows of K and V, 16 bytes a thread: with little to copy that is done before a launch
+                // of its own would have begun.
+                __syncthreads();   // the indices are written
+                const int pieces = rows.row_bytes / 16, B = k + append_count;
+                const long from0 = (long)row * rows.N, to0 = (plan.row_off[g] + (long)hl * plan.budget[g]) * pieces;
+                for (int u = tid; u < B * pieces; u += kBudgetBlock) {
+                    const long from = (from0 + out[u / pieces]) * pieces + u % pieces;
+                    const uint4 a = ((const uint4 *)rows.Kc)[from], b = ((const uint4 *)rows.Vc)[from];
+                    ((uint4 *)rows.Kout)[to0 + u] = a;
+                    ((uint4 *)rows.Vout)[to0 + u] = b;
+                }
+            }
         }
         if (!REDO || !redo) return;
         if constexpr (REDO) {
@@ -1604,7 +1617,7 @@ static_assert(kBitmapRow <= kMaxSegments * kSegment, "segments of a row");
 
 template <int D>
 static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
-                                  const DecayArgs &update, hipStream_t st)
+                                  const DecayArgs &update, const GatherArgs &gather, hipStream_t st)
 {
 #define GKV_BUDGET(ITEMS)                                                                                       \
     do {                                                                                                        \
@@ -1613,7 +1626,7 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
         auto *kernel = may && update.redo.overflow ? budget_select_kernel<ITEMS, D, may> : budget_select_kernel<ITEMS, D, false>; \
         if (D > 0 && !allow_big_lds((const void *)kernel, kBigLds)) return hipGetLastError();                   \
         hipLaunchKernelGGL(kernel, dim3(redo_grid(rows, update)), dim3(kBudgetBlock), lds, st, scores, P, rows, \
-                           idx, P, w, update, plan);                                                            \
+                           idx, P, w, update, gather, plan);                                                    \
     } while (0)
     if (P <= 1024) GKV_BUDGET(1);   // (the filter route, whose rows may be redone, starts at 2048)
     else if (P <= 2048) GKV_BUDGET(2);
@@ -1641,20 +1654,25 @@ size_t topk_final_scratch_bytes(int rows, int P)
            (split_segments(rows, P) ? (size_t)rows * sizeof(uint4) : 0);
 }
 
+// Few enough bytes of a head's retained rows for its workgroup (whole passes, us, a launch of its own / in the
+// selection: 4 heads x 64 rows of 256 bytes 34.2 / 31.9, 8 heads x 256 19.9 / 16.2 with key norms; 8 heads x 512 rows
+// 44.9 / 47.9).
+bool topk_final_gathers(int P, int max_budget, int row_bytes) { return P <= 32768 && (long)max_budget * row_bytes <= (64 << 10); }
+
 hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
-                             const DecayArgs &update, void *scratch, hipStream_t st)
+                             const DecayArgs &update, const GatherArgs &gather, void *scratch, hipStream_t st)
 {
     if (rows <= 0) return hipSuccess;
     if (P <= 32768) {
         switch (update.items) {
-            case 0: return launch_budget_d<0>(scores, P, rows, plan, w, idx, update, st);
-            case 1: return launch_budget_d<1>(scores, P, rows, plan, w, idx, update, st);
-            case 2: return launch_budget_d<2>(scores, P, rows, plan, w, idx, update, st);
-            case 4: return launch_budget_d<4>(scores, P, rows, plan, w, idx, update, st);
+            case 0: return launch_budget_d<0>(scores, P, rows, plan, w, idx, update, gather, st);
+            case 1: return launch_budget_d<1>(scores, P, rows, plan, w, idx, update, gather, st);
+            case 2: return launch_budget_d<2>(scores, P, rows, plan, w, idx, update, gather, st);
+            case 4: return launch_budget_d<4>(scores, P, rows, plan, w, idx, update, gather, st);
             default: return hipErrorInvalidValue;
         }
     }
-    if (update.items) return hipErrorInvalidValue;
+    if (update.items || gather.Kout) return hipErrorInvalidValue;
     const int segs = scratch ? split_segments(rows, P) : 0;
     if (segs) {
         SplitScratch sc;

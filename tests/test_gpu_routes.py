@@ -135,3 +135,27 @@ def test_tiled_products_by_row_length(fp32, d, G, w, S):
     for h in range(H):   # m = P - 1: every edge but a source's own
         full = Kn[h][src[0, h].long()] @ Kn[h].T
         assert ((full.gather(1, nbr[0, h].long()) - e[0, h]).abs() <= 2e-5).all()
+
+
+@pytest.mark.parametrize("P,B,fp32,d", [(900, 256, 0, 128), (900, 257, 0, 128), (3000, 128, 1, 128), (3000, 129, 1, 128),
+                                        (40, 7, 0, 8), (32768, 4096, 0, 8), (32768, 4097, 0, 8), (32769, 100, 0, 8)])
+def test_few_retained_rows_are_gathered_by_the_selection(P, B, fp32, d):
+    """Heads with up to 64 KiB of retained rows are copied by the workgroup that selected them: both sides of that
+    limit, of the row length up to which the kernel serves, and budgets that differ from layer to layer."""
+    say(f"gather by the selection P={P} B={B} fp32={fp32} d={d}")
+    L, H, w = 3, 2, 3
+    N = P + w
+    budgets = [B, max(w + 1, B - 3), max(w + 1, B // 2)]
+    g = torch.Generator("cuda").manual_seed(P + B)
+    td = torch.float32 if fp32 else torch.bfloat16
+    K, V = (torch.randn(L, H, N, d, generator=g, device="cuda").to(td) for _ in range(2))
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=B, n_sources=3, n_neighbors=2,
+                  rounds=1, dtype=gk.FP32 if fp32 else gk.BF16, scorer=gk.SCORER_KNORM)
+    Ks, Vs, idx = gk.graphkv_compress_batched(p, L, budgets, K, V, None)
+    row = 0
+    for l, b in enumerate(budgets):
+        for h in range(H):
+            i = idx[row:row + b].long()
+            assert (i[1:] > i[:-1]).all() and torch.equal(i[-w:], torch.arange(P, N, device="cuda"))
+            assert torch.equal(Ks[row:row + b], K[l, h][i]) and torch.equal(Vs[row:row + b], V[l, h][i])
+            row += b
