@@ -211,8 +211,8 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
     W.cand = take(frows * g.chunks * g.slice_cap * 8);
     W.cand_cnt = take(frows * g.chunks * 4);
-    W.overflow = take((size_t)D.H * 2 * 4);   // flags of two consecutive rounds
-    W.done = take((size_t)D.H * 2 * 4);
+    W.overflow = take((size_t)D.H * 4 * 4);   // flags of two consecutive rounds, two counters
+    W.done = W.overflow + (size_t)D.H * 2 * 4;
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);
     W.nbr_b = take(keep ? (size_t)D.H * D.S * D.m * 4 : 0);

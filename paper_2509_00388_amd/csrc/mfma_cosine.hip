@@ -1032,8 +1032,9 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
     }
 }
 
+// (three waves per SIMD at least: with 173 registers a lane, and so two, 256 heads of 128K keys took 280 us, 203 with 152)
 template <int R>
-__global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
+__global__ __launch_bounds__(256, 3) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
                                                               const int32_t *__restrict__ cand_cnt,
                                                               int32_t *__restrict__ overflow,
                                                               const int32_t *__restrict__ src, int S, int pitch,
