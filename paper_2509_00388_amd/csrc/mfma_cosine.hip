@@ -1088,16 +1088,7 @@ __global__ __launch_bounds__(kThreads) void late_lists_kernel(
         __syncthreads();
         filter_chunk<kSB, 64>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, tid,
                               [&](int r) { return tau_s[r]; });
-        __syncthreads();
-        if (tid == 0) {
-            __threadfence();   // the workgroup's candidates are visible before it is counted
-            const int all = n_chunks * ((Sh + kRows - 1) / kRows);
-            last = atomicAdd(&done[h], 1) == all - 1;
-            if (last) done[h] = 0;
-        }
-        __syncthreads();
-        if (!last) return;
-        __threadfence();       // and the others' before they are read
+        if (!finishes_last(&done[h], n_chunks * ((Sh + kRows - 1) / kRows), &last)) return;
         if (*(volatile int32_t *)&fa.overflow[h]) return;
         first = wv;
         step = NW;

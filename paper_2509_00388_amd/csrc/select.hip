@@ -753,16 +753,7 @@ __device__ __forceinline__ int redo_next(const RedoArgs &a, long &item, int32_t 
         item += wgs;
         if (a.overflow[h] == 0) continue;   // (not written in this launch: the same for every thread)
         redo_row<false>(a, row, mem);
-        if (threadIdx.x == 0) {
-            __threadfence();        // the row is visible before it is counted
-            *last = atomicAdd(&a.done[h], 1) == a.S - 1;
-            if (*last) a.done[h] = 0;
-        }
-        __syncthreads();
-        if (*last) {
-            __threadfence();        // and the other workgroups' rows before they are read
-            return h;
-        }
+        if (finishes_last(&a.done[h], a.S, last)) return h;
     }
     return -1;
 }
