@@ -265,8 +265,8 @@ const char *graphkv_strerror(int32_t code);
  * GRAPHKV_IMPL_AUTO, the matrix-core kernels that take their place; an update of the
  * scores that the next selection does first is counted with that selection, and so are
  * the redoing of rows in front of it and the gather of few rows behind it (an update on
- * its own with rows to redo counts as redo_rows); a later round's bound, filter and
- * select in one launch count as cosine_bound_new.
+ * its own with rows to redo counts as redo_rows); a later round's bound and filter in
+ * one launch count as cosine_bound_new.
  */
 enum {
     GRAPHKV_K_SCORE_STATS = 0, GRAPHKV_K_SCORE_VOTES, GRAPHKV_K_POOL, GRAPHKV_K_TOPK_SOURCES,

@@ -211,7 +211,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
     W.cand = take(frows * g.chunks * g.slice_cap * 8);
     W.cand_cnt = take(frows * g.chunks * 4);
-    W.overflow = take((size_t)D.H * 4 * 4);   // flags of two consecutive rounds, two counters
+    W.overflow = take((size_t)D.H * 4 * 3);   // flags of two consecutive rounds, a counter
     W.done = W.overflow + (size_t)D.H * 2 * 4;
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);
@@ -439,13 +439,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     // new sources without a kept list (usually none): bound and filter passes
                     // that return at once for heads that have none
-                    // (An enhanced signal does make new sources, whose bound one workgroup a head takes in less time
-                    // than all of them that share the memory's rate: 3 rounds of 8 heads x 32736 keys 542 us in
-                    // three launches a round, 615 in one.)
-                    if (p->signal != GRAPHKV_SIGNAL_ENHANCED && pick_match_applies(D.S) && late_lists_apply(D.H, g)) {
+                    if (pick_match_applies(D.S) && late_filter_applies(D.H, g)) {
                         GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
-                                   launch_late_lists(Ac, Kc, D.H, D.N, D.P, D.m, g, new_src, n_new, sel, cand, cnt, ovf,
-                                                     done + D.H, src, nbr, ev, st));
+                                   launch_late_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, new_src, n_new, cand, cnt, ovf, st));
                     } else {
                         GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
                                    launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
@@ -453,9 +449,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                         GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER_NEW,
                                    launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new, tau,
                                                              cand, cnt, ovf, st));
-                        GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
-                                   launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));
                     }
+                    GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
+                               launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));
                 }
                 // heads whose lists overflowed are redone row by row, exactly: by the kernel that takes the update
                 // along, where there is one

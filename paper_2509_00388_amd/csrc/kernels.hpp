@@ -181,7 +181,7 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
 size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // per-chunk histograms (0 if one chunk)
 // Bound pass: tau = a value that at least m of the row's edges reach (but for about one row in
 // 10^7, which the select notices), from the edges to every (P / sample_cols)-th key; clears
-// overflow [Hkv] and, unless null, done [2 Hkv] (the counters of RedoArgs and of launch_late_lists).  first_round: src is the extended list
+// overflow [Hkv] and, unless null, done [Hkv] (the counters of RedoArgs).  first_round: src is the extended list
 // [Hkv, S + X] (all rows in use, rows 0 .. of the buffers); otherwise src is the list of new
 // sources [Hkv, S], n_src [Hkv] of them in use, rows 0 .. of the buffers.
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
@@ -226,12 +226,10 @@ struct SelectRows {
 hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st);
-// A later round's bound, filter and select passes in one launch, for few heads: those without a new source, nearly
-// all of them, only select.  done [Hkv]: a counter, zero before and after.
-bool late_lists_apply(int Hkv, const MfmaFilterPlan &g);
-hipError_t launch_late_lists(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
-                             const int32_t *new_src, const int32_t *n_new, const SelectRows &rows, void *cand,
-                             int32_t *cand_cnt, int32_t *overflow, int32_t *done, const int32_t *src, int32_t *nbr,
-                             float *nbr_e, hipStream_t st);
+// A later round's bound and filter passes in one launch, for few heads (overflow is not cleared).
+bool late_filter_applies(int Hkv, const MfmaFilterPlan &g);
+hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
+                              const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
+                              int32_t *overflow, hipStream_t st);
 
 }  // namespace gkv

@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
     const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
     if (blockIdx.x == 0 && chunk == 0 && tid == 0) {
         overflow[h] = 0;
-        if (done) done[h] = done[gridDim.y + h] = 0;
+        if (done) done[h] = 0;
     }
     // rows of this head's source list in use
     const int Sh = n_src ? n_src[h] : S;
@@ -861,25 +861,29 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 // list has room for, raise the head's overflow flag (the head is then redone exactly).
 // (A walk over the slices for every register, key indices fetched a second time, scans through the
 // LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way 8.4 us.)
-// LDS words of a wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit).
-template <int R> __host__ __device__ constexpr int select_wave_words(int m) { return 64 + 16 * R + 2 * ((m + kTieRoom + 1) & ~1); }
-
-// Selections x0, x0 + step, .. of the n_rows of head h by one wave; ends, and raises the head's flag, at a list that
-// does not do.
 template <int R>
-__device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, const int32_t *__restrict__ cand_cnt,
-                                               int32_t *__restrict__ overflow, const int32_t *__restrict__ src, int S,
-                                               int pitch, int chunks, int slice_cap, int m, const SelectRows &sel,
-                                               int32_t *__restrict__ nbr, float *__restrict__ nbr_e, int h, int x0, int step,
-                                               int n_rows, uint32_t *words, int lane)
+__global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
+                                                              const int32_t *__restrict__ cand_cnt,
+                                                              int32_t *__restrict__ overflow,
+                                                              const int32_t *__restrict__ src, int S, int pitch,
+                                                              int chunks, int slice_cap, int m, SelectRows sel,
+                                                              int32_t *__restrict__ nbr,
+                                                              float *__restrict__ nbr_e)
 {
     static_assert(R == 16 || R == 32, "register groups of 16");
+    // per wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit)
+    extern __shared__ __align__(16) uint32_t dyn[];
+    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
+    const int waves = (int)blockDim.x >> 6;
+    const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
+    if (overflow[h]) return;
     const int list_cap = m + kTieRoom;
-    uint32_t *start_s = words;
+    uint32_t *start_s = dyn + wv * (64 + 16 * R + 2 * ((list_cap + 1) & ~1));
     uint8_t *mark_s = reinterpret_cast<uint8_t *>(start_s + 64);
     uint64_t *win = reinterpret_cast<uint64_t *>(start_s + 64 + 16 * R);
 
-    for (int x = x0; x < n_rows; x += step) {
+    for (int x = blockIdx.x * waves + wv; x < n_rows; x += gridDim.x * waves) {
         const int crow = sel.row ? sel.row[(long)h * S + x] : x, pos = sel.pos ? sel.pos[(long)h * S + x] : x;
         const long row = (long)h * pitch + crow;
         const uint2 *slices = cand + row * chunks * (long)slice_cap;
@@ -899,11 +903,11 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
         uint32_t E[R], J[R];
         if (chunks <= 8) {
             // few slices: the last one that starts at or before the entry, slice by slice in scalars
-    #pragma unroll
+#pragma unroll
             for (int it = 0; it < R; ++it) J[it] = (uint32_t)(it * 64 + lane);
             for (int c = 1; c < chunks; ++c) {
                 const int s_c = __builtin_amdgcn_readlane(incl - cnt, c), shift = c * slice_cap - s_c;
-    #pragma unroll
+#pragma unroll
                 for (int it = 0; it < R; ++it)
                     if ((it & ~3) < n_it) J[it] = it * 64 + lane >= s_c ? (uint32_t)(it * 64 + lane + shift) : J[it];
             }
@@ -915,7 +919,7 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
             if (cnt > 0) mark_s[incl - cnt] = (uint8_t)lane;
             wave_sync();
             uint32_t carry = 0;
-    #pragma unroll
+#pragma unroll
             for (int it = 0; it < R; ++it) {
                 J[it] = 0u;
                 if (it < n_it) {   // (the same for all lanes)
@@ -928,25 +932,25 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
         }
         // (entries past the end read one that is there: the loads of four registers leave together)
         const uint32_t some = (uint32_t)__builtin_amdgcn_readfirstlane((int)J[0]);
-    #pragma unroll
+#pragma unroll
         for (int g = 0; g < R; g += 4) {
             if (g < n_it) {
                 uint2 v[4];
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < 4; ++u) v[u] = slices[(g + u) * 64 + lane < n ? J[g + u] : some];
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     E[g + u] = v[u].x;
                     J[g + u] = v[u].y;
                 }
             } else {
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < 4; ++u) E[g + u] = 0u;
             }
         }
         uint32_t kmin = 0xffffffffu, kmax = 0u;
         int valid = n;
-    #pragma unroll
+#pragma unroll
         for (int it = 0; it < R; ++it)
             if ((it & ~3) < n_it) {
                 // the source's own column is no neighbour (Eq. 3: j != i): key 0 sorts below every edge
@@ -975,7 +979,7 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
 
         // everything that reaches tau -> LDS list as (key index, edge bits), any order
         int listed = 0;
-    #pragma unroll
+#pragma unroll
         for (int it = 0; it < R; ++it)
             if (it < n_it) {
                 const bool in = E[it] >= tau;
@@ -1032,69 +1036,32 @@ __device__ __forceinline__ void select_by_wave(const uint2 *__restrict__ cand, c
     }
 }
 
-// (three waves per SIMD at least: with 173 registers a lane, and so two, 256 heads of 128K keys took 280 us, 203 with 152)
-template <int R>
-__global__ __launch_bounds__(256, 3) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
-                                                              const int32_t *__restrict__ cand_cnt,
-                                                              int32_t *__restrict__ overflow,
-                                                              const int32_t *__restrict__ src, int S, int pitch,
-                                                              int chunks, int slice_cap, int m, SelectRows sel,
-                                                              int32_t *__restrict__ nbr,
-                                                              float *__restrict__ nbr_e)
-{
-    extern __shared__ __align__(16) uint32_t dyn[];
-    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
-    const int waves = (int)blockDim.x >> 6;
-    const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
-    if (overflow[h]) return;
-    select_by_wave<R>(cand, cand_cnt, overflow, src, S, pitch, chunks, slice_cap, m, sel, nbr, nbr_e, h,
-                      blockIdx.x * waves + wv, gridDim.x * waves, n_rows, dyn + wv * select_wave_words<R>(m), lane);
-}
-
-// A later round's bound, filter and select passes in one launch, for few heads.  New sources without a kept list are
-// rare (none at all on ordinary inputs), so what counts is the launches they cost every round: a head without one
-// has its promoted rows' lists selected from, a wave a row, the first waves of all workgroups first, and that is
-// all.  A head with new sources takes the passes here: every workgroup of the head takes the bound from the whole
-// sample itself (there are compute units enough, which would wait for one workgroup otherwise), filters its
-// chunk, and the one that is done last, which `done` counts, selects for the head.  (8 heads, a round without new
-// sources: 15 us in three launches, 7.5 in one.)
-template <int R>
-__global__ __launch_bounds__(kThreads) void late_lists_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
-    const int32_t *__restrict__ new_src, int chunk_cols, FilterArgs fa, int sample_cols, int key_stride, int rank,
-    int32_t *done, const int32_t *__restrict__ cur, int m, SelectRows sel, int32_t *__restrict__ nbr,
-    float *__restrict__ nbr_e)
+// A later round's bound and filter passes in one launch, for few heads: nearly always no head has a new source, and
+// then what counts is the launches.  Every workgroup of a head with new sources takes the bound from the whole sample
+// itself and filters its chunk, which lasts as long as one workgroup's walk over the sample in front of the others'
+// filter as long as each has a compute unit to itself.
+__global__ __launch_bounds__(kThreads) void late_filter_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols,
+    const int32_t *__restrict__ new_src, int chunk_cols, FilterArgs fa, int sample_cols, int key_stride, int rank)
 {
     constexpr int BINS = 256, NW = kThreads / kWave;
     __shared__ FilterLds<kSB> F;
     __shared__ float tau_s[kRows];
-    __shared__ int32_t last;
-    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the rings (or the histograms); the selects'
-    const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_chunks = gridDim.x / fa.sgroups, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * kRows;
-    const int Sh = fa.n_src[h], n_sel = sel.n_rows[h];
-    int first = wv * gridDim.x + blockIdx.x, step = NW * gridDim.x;   // selections of this wave
-    if (Sh > 0) {
-        if (s_base >= Sh) return;   // (s_base = 0 has rows)
-        uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);
-        count_sample<kSB, BINS>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, new_src + (long)h * fa.src_pitch, Sh, s_base, 0,
-                                sample_cols, key_stride, smem, hist, F.inv_s, F.idx_s, tid);
-        for (int r = wv; r < kRows; r += NW) {
-            const uint4 w4 = histogram_words<BINS>(&hist[r * BINS], lane);
-            bound_from_histogram<BINS>(w4, rank, lane, &tau_s[r]);
-        }
-        __syncthreads();
-        filter_chunk<kSB, 64>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, tid,
-                              [&](int r) { return tau_s[r]; });
-        if (!finishes_last(&done[h], n_chunks * ((Sh + kRows - 1) / kRows), &last)) return;
-        if (*(volatile int32_t *)&fa.overflow[h]) return;
-        first = wv;
-        step = NW;
+    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the histograms, then the rings
+    const int h = blockIdx.y, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * kRows;
+    const int Sh = fa.n_src[h];
+    if (s_base >= Sh) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);
+    count_sample<kSB, BINS>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, new_src + (long)h * fa.src_pitch, Sh, s_base, 0,
+                            sample_cols, key_stride, smem, hist, F.inv_s, F.idx_s, tid);
+    for (int r = wv; r < kRows; r += NW) {
+        const uint4 w4 = histogram_words<BINS>(&hist[r * BINS], lane);
+        bound_from_histogram<BINS>(w4, rank, lane, &tau_s[r]);
     }
-    select_by_wave<R>(fa.cand, fa.cand_cnt, fa.overflow, cur, S, fa.pitch, n_chunks, fa.slice_cap, m, sel, nbr, nbr_e, h,
-                      first, step, n_sel, reinterpret_cast<uint32_t *>(smem) + wv * select_wave_words<R>(m), lane);
+    __syncthreads();
+    filter_chunk<kSB, 64>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, gridDim.x / fa.sgroups, Sh, s_base, F, smem,
+                          tid, [&](int r) { return tau_s[r]; });
 }
 
 // Matching on its own, for source lists the few-winners selection does not take (S > 256).
@@ -1359,34 +1326,29 @@ hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv,
     return hipGetLastError();
 }
 
-// Lists short enough for a wave each.
-static bool wave_select_applies(const MfmaFilterPlan &g) { return g.cand_cap <= 64 * 32 && g.chunks <= 64; }
-
-// Up to two rounds of its workgroups (us a round without new sources, three launches / one: 8 heads of 16K keys 15.0
-// / 7.5, 256 heads of 20K, where the selects take longer than the launches, 32 / 33, of 32K 26 / 33).
-bool late_lists_apply(int Hkv, const MfmaFilterPlan &g)
+// A compute unit for each workgroup: with more, the walks over the sample share the units with each other.  (Three
+// rounds of 8 heads, us, two launches a round / one.  No new sources: 16K keys 107.7 / 103.9, 64K keys, 512 workgroups,
+// 236.7 / 233.0.  Many, from key norms: 16K keys, 64 sources, 128 workgroups 221.7 / 217.5; 128 sources, 256 277 / 274;
+// 192 sources, 384 372 / 418; 64K keys, 64 sources, 512 656 / 813.  The lists selected in the same launch, by the
+// workgroup that finishes last: 101.3 without new sources, but 326 and 773 with 64 and 192 and many of them new.)
+bool late_filter_applies(int Hkv, const MfmaFilterPlan &g)
 {
-    return wave_select_applies(g) && (long)Hkv * g.chunks * ((g.S + kRows - 1) / kRows) <= 512;
+    return (long)Hkv * g.chunks * ((g.S + kRows - 1) / kRows) <= 256;
 }
 
-hipError_t launch_late_lists(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
-                             const int32_t *new_src, const int32_t *n_new, const SelectRows &rows, void *cand,
-                             int32_t *cand_cnt, int32_t *overflow, int32_t *done, const int32_t *src, int32_t *nbr,
-                             float *nbr_e, hipStream_t st)
+hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
+                              const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
+                              int32_t *overflow, hipStream_t st)
 {
     const int sgroups = (g.S + kRows - 1) / kRows;
     const Sample smp = sample_of(P);
     FilterArgs fa{n_new, nullptr, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, filter_drain_every(P, m, 64), sgroups, g.S,
                   g.pitch, 0};
-    const bool small = g.cand_cap <= 64 * 16;
-    auto *kernel = small ? late_lists_kernel<16> : late_lists_kernel<32>;
-    const size_t filter = 2 * kTileBytes + 2 * (4 * kSB) * 64 * kStagePitch;   // (the histograms of 64 rows fit the rings)
-    const size_t select = (size_t)(kThreads / kWave) * (small ? select_wave_words<16>(m) : select_wave_words<32>(m)) * 4;
     static_assert(kRows * 256 * 4 <= 2 * (4 * kSB) * 64 * kStagePitch, "the histograms take the rings' place");
-    if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
-    hipLaunchKernelGGL(kernel, dim3(g.chunks * sgroups, Hkv), dim3(kThreads), filter > select ? filter : select, st,
-                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, g.S, new_src, g.chunk_cols, fa, smp.cols, smp.stride,
-                       mfma_bound_rank(m, smp.stride), done, src, m, rows, nbr, nbr_e);
+    if (!allow_big_lds((const void *)late_filter_kernel)) return hipGetLastError();
+    hipLaunchKernelGGL(late_filter_kernel, dim3(g.chunks * sgroups, Hkv), dim3(kThreads),
+                       2 * kTileBytes + 2 * (4 * kSB) * 64 * kStagePitch, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P,
+                       new_src, g.chunk_cols, fa, smp.cols, smp.stride, mfma_bound_rank(m, smp.stride));
     return hipGetLastError();
 }
 
@@ -1400,13 +1362,13 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
     // take the other kernel when there are many heads (256 heads, us, workgroup / wave per list: 32K
     // prompts 18 / 28, 128K 76 / 231), this one when there are few (8 heads 9.3 / 8.3).
     const bool few = (long)S * Hkv <= 2048;
-    if (wave_select_applies(g) && (!rows || few)) {
+    if (cap <= 64 * 32 && g.chunks <= 64 && (!rows || few)) {
         const int waves = few ? 1 : 4;
         const SelectRows sel = rows ? *rows : SelectRows{};
         int per_head = (waves == 1 ? 2048 : 8192) / Hkv;
         per_head = per_head < 1 ? 1 : (per_head > (S + waves - 1) / waves ? (S + waves - 1) / waves : per_head);
         const bool small = cap <= 64 * 16;
-        const size_t lds = (size_t)waves * (small ? select_wave_words<16>(m) : select_wave_words<32>(m)) * 4;
+        const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * ((m + kTieRoom + 1) & ~1)) * 4;
         auto *kernel = small ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
         hipLaunchKernelGGL(kernel, dim3(per_head, Hkv), dim3(64 * waves), lds, st, (const uint2 *)cand, cand_cnt,
                            overflow, src, S, g.pitch, g.chunks, g.slice_cap, m, sel, nbr, nbr_e);

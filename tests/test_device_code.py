@@ -60,7 +60,7 @@ def test_stores_are_complete_before_a_workgroup_is_counted(kernels):
             before = next((code[i] for i in range(barrier, -1, -1)
                            if re.match(r"(global|flat|buffer)_store", code[i]) or re.match(r"s_waitcnt vmcnt\(0\)", code[i])), "")
             counted.setdefault(name, []).append(before)
-    for kernel in ("pick_match_kernel", "budget_select_kernel", "redo_decay_kernel", "late_lists_kernel"):
+    for kernel in ("pick_match_kernel", "budget_select_kernel", "redo_decay_kernel"):
         assert any(kernel in name for name in counted), f"{kernel} counts no workgroups"
     bad = {name: ops for name, ops in counted.items() if not all(op.startswith("s_waitcnt") for op in ops)}
     assert not bad, bad

@@ -159,3 +159,36 @@ def test_few_retained_rows_are_gathered_by_the_selection(P, B, fp32, d):
             assert (i[1:] > i[:-1]).all() and torch.equal(i[-w:], torch.arange(P, N, device="cuda"))
             assert torch.equal(Ks[row:row + b], K[l, h][i]) and torch.equal(Vs[row:row + b], V[l, h][i])
             row += b
+
+
+@pytest.mark.parametrize("H,N,S,scorer", [(8, 16384, 64, 1), (8, 16384, 192, 1), (8, 32768, 128, 1), (8, 16384, 192, 0)])
+def test_new_lists_of_later_rounds_cost_no_more_than_the_first(H, N, S, scorer):
+    """Few heads whose sources are exchanged from round to round (key norms lie close together; more sources than
+    are promoted): a later round's bound, filter and select passes take no longer than those of the first round,
+    which are over all sources (and half as much again for what a clock shows; selected from by one workgroup a
+    head they took three times as long), whether they are one launch or several."""
+    say(f"new lists of later rounds H={H} N={N} S={S} scorer={scorer}")
+    d, w, T = 128, 32, 3
+    g = torch.Generator("cuda").manual_seed(S)
+    centre = torch.randn(H, 256, d, generator=g, device="cuda")
+    kind = torch.randint(0, 256, (H, N, 1), generator=g, device="cuda").expand(-1, -1, d)
+    K = centre.gather(1, kind) + 0.3 * torch.randn(H, N, d, generator=g, device="cuda")
+    K[:, :, :4] *= 8.0
+    K = K.to(torch.bfloat16)
+    Q = (0.5 * K[:, :w] + torch.randn(H, w, d, generator=g, device="cuda")).to(torch.bfloat16)
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=w + 500, n_sources=S, n_neighbors=32,
+                  rounds=T, scorer=scorer, dtype=gk.BF16)
+    first = later = np.inf
+    for _ in range(4):
+        gk.graphkv_profile_begin()
+        gk.graphkv_compress(p, K, K, Q)
+        torch.cuda.synchronize()
+        took = gk.graphkv_profile_end()
+
+        def ms(*kernels):
+            return sum(took[k][0] for k in kernels if k in took)   # (bound and filter may be one launch)
+
+        first = min(first, ms("cosine_bound", "cosine_filter", "nbr_select"))
+        later = min(later, ms("cosine_bound_new", "cosine_filter_new", "nbr_select_later") / (T - 1))
+    say(f"  first round {first:.3f} ms, a later one {later:.3f} ms")
+    assert later < 1.5 * first + 0.01
