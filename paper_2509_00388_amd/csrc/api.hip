@@ -62,7 +62,7 @@ struct Dims {
 // Workspace: a bump allocation of every scratch array any entry point may need.
 struct Workspace {
     size_t logits, row_max, row_sum, votes, E, src, nbr, nbr_e, scores, part;
-    size_t bound_hist, tau, cand, cand_cnt, overflow, done;
+    size_t bound_hist, tau, cand, cand_cnt, overflow, overflow_odd;
     // lists kept from one round to the next, speculative rows
     size_t src_b, nbr_b, nbr_e_b, ext, new_src, n_new, sel_row, sel_pos, n_sel, spec_bad;
     size_t final_sel, final_bytes;   // the final selection's (0 bytes: it takes none)
@@ -211,8 +211,10 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
     W.cand = take(frows * g.chunks * g.slice_cap * 8);
     W.cand_cnt = take(frows * g.chunks * 4);
-    W.overflow = take((size_t)D.H * 4 * 3);   // flags of two consecutive rounds, a counter
-    W.done = W.overflow + (size_t)D.H * 2 * 4;
+    // 16-bit flags of even and of odd rounds, each from a whole word on (within the 256 bytes that H words would take)
+    const size_t flags = ((size_t)D.H + 1) / 2 * 4;
+    W.overflow = take(2 * flags);
+    W.overflow_odd = W.overflow + flags;
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);
     W.nbr_b = take(keep ? (size_t)D.H * D.S * D.m * 4 : 0);
@@ -398,9 +400,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                 // Eq. 1 + Eq. 3 in one streaming pass over the keys: a bound per source from a
                 // strided sample that at least m of its edges reach, then only edges above it are kept.
                 float *tau = at<float>(ws, W.tau);
-                int32_t *cnt = at<int32_t>(ws, W.cand_cnt), *ovf = at<int32_t>(ws, W.overflow) + (t & 1) * D.H;
-                int32_t *done = at<int32_t>(ws, W.done);
-                const RedoArgs redo{Ac, Kc, D.N, D.P, D.S, D.m, D.H, src, ovf, done, E, nbr, ev};
+                int32_t *cnt = at<int32_t>(ws, W.cand_cnt);
+                uint16_t *ovf = at<uint16_t>(ws, t & 1 ? W.overflow_odd : W.overflow);
+                const RedoArgs redo{Ac, Kc, D.N, D.P, D.S, D.m, D.H, src, ovf, E, nbr, ev};
                 void *cand = at<char>(ws, W.cand);
                 int32_t *ext = at<int32_t>(ws, W.ext);
                 if (!(keep && prev_src)) {
@@ -416,7 +418,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND,
                                launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
-                                                        at<char>(ws, W.bound_hist), tau, ovf, done, st));
+                                                        at<char>(ws, W.bound_hist), tau, ovf, st));
                     GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER,
                                launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr, tau, cand,
                                                          cnt, ovf, st));
@@ -426,7 +428,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     int32_t *new_src = at<int32_t>(ws, W.new_src), *n_new = at<int32_t>(ws, W.n_new);
                     const SelectRows sel{at<int32_t>(ws, W.n_sel), at<int32_t>(ws, W.sel_row),
                                          at<int32_t>(ws, W.sel_pos)};
-                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, at<int32_t>(ws, W.overflow),
+                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, at<uint16_t>(ws, W.overflow),
                                           at<int32_t>(ws, W.spec_bad), new_src, n_new, at<int32_t>(ws, W.sel_row),
                                           at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel), ovf};
                     if (pick_match_applies(D.S)) {
@@ -445,7 +447,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     } else {
                         GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
                                    launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
-                                                            at<char>(ws, W.bound_hist), tau, ovf, nullptr, st));
+                                                            at<char>(ws, W.bound_hist), tau, ovf, st));
                         GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER_NEW,
                                    launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new, tau,
                                                              cand, cnt, ovf, st));

@@ -83,24 +83,6 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
     return r;
 }
 
-// Counts the calling workgroup among the `full` that share a job: true, the same for every thread, in the one that is
-// counted last, to all of whose threads what any of them stored before is then visible.  count is zero before and after;
-// `last` is a word of LDS.  Every wave waits for its own stores first: a barrier alone does not (it orders them within
-// the workgroup, which shares a cache), and a fence of the thread that counts waits for its own wave's.
-__device__ __forceinline__ bool finishes_last(int32_t *count, int full, int32_t *last)
-{
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        *last = __hip_atomic_fetch_add(count, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == full - 1;
-        if (*last) *count = 0;
-    }
-    __syncthreads();
-    if (!*last) return false;
-    __threadfence();
-    return true;
-}
-
 // ---- wave-wide scans and reductions on the vector ALU --------------------------------
 // gfx9 data-parallel primitives move a value along the lanes inside a vector instruction
 // (a shift within a row of 16 lanes, then the last lane of a row to the next row, then lane 31 to

@@ -31,12 +31,12 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
 // number of workgroups walk the (head, source) rows of those heads, each computing one row of
 // edges into its own scratch row (rows: redo_rows_scratch_bytes()) and taking the exact top-m.
 // Or the kernel behind does it, before it takes what it needs (DecayArgs): flagged heads then wait for their last
-// row, which `done` [heads] counts (zero before and after).
+// row, up to which their flags count (S <= 4096 there).  A flag is 16 bits, so that two rounds' fit 4 bytes a head.
 struct RedoArgs {
     const void *Ac, *Kc;
     int N, P, S, m, heads;
-    const int32_t *src, *overflow;   // overflow: nullptr for no rows to redo
-    int32_t *done;
+    const int32_t *src;
+    uint16_t *overflow;   // nullptr for no rows to redo
     float *rows;
     int32_t *nbr;
     float *nbr_e;
@@ -181,19 +181,19 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
 size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // per-chunk histograms (0 if one chunk)
 // Bound pass: tau = a value that at least m of the row's edges reach (but for about one row in
 // 10^7, which the select notices), from the edges to every (P / sample_cols)-th key; clears
-// overflow [Hkv] and, unless null, done [Hkv] (the counters of RedoArgs).  first_round: src is the extended list
+// overflow [Hkv].  first_round: src is the extended list
 // [Hkv, S + X] (all rows in use, rows 0 .. of the buffers); otherwise src is the list of new
 // sources [Hkv, S], n_src [Hkv] of them in use, rows 0 .. of the buffers.
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                     const MfmaFilterPlan &g, bool first_round, const int32_t *src,
-                                    const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
-                                    int32_t *done, hipStream_t st);
+                                    const int32_t *n_src, void *hist_part, float *tau, uint16_t *overflow,
+                                    hipStream_t st);
 // Filter pass: streams all keys; edges that reach a row's tau go to its slices, their number
 // per slice to cand_cnt.  Same source lists and rows as the bound pass.
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                      const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
-                                     int32_t *overflow, hipStream_t st);
+                                     uint16_t *overflow, hipStream_t st);
 // From the second round on (match.hpp): which sources keep their list from the round before (copied
 // from prev_nbr / prev_e to nbr / nbr_e), which are speculative rows of the first round (the last X
 // entries of ext [Hkv, S + X]; not used for heads that overflowed then: spec_bad [Hkv], set by the first
@@ -206,9 +206,10 @@ struct MatchArgs {
     const float *prev_e;
     int32_t *nbr;
     float *nbr_e;
-    const int32_t *ext, *overflow;
+    const int32_t *ext;
+    const uint16_t *overflow;
     int32_t *spec_bad, *new_src, *n_new, *sel_row, *sel_pos, *n_sel;
-    int32_t *clear;   // [Hkv] overflow flags of this round, cleared
+    uint16_t *clear;   // [Hkv] overflow flags of this round, cleared
 };
 // Source nodes (Eq. 2) of a later round and their match, one launch for S <= 256 (pick_match_applies).
 bool pick_match_applies(int S);
@@ -223,13 +224,13 @@ struct SelectRows {
     const int32_t *row;      // [Hkv, S] candidate row of the x-th selection
     const int32_t *pos;      // [Hkv, S] its source slot in this round's list
 };
-hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
+hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, uint16_t *overflow, const int32_t *src,
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st);
 // A later round's bound and filter passes in one launch, for few heads (overflow is not cleared).
 bool late_filter_applies(int Hkv, const MfmaFilterPlan &g);
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
-                              int32_t *overflow, hipStream_t st);
+                              uint16_t *overflow, hipStream_t st);
 
 }  // namespace gkv

@@ -735,11 +735,31 @@ __device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned 
 }
 
 // Whether any head is flagged (the same for every thread; contains a barrier).
-__device__ __forceinline__ bool redo_flagged(const int32_t *overflow, int heads, int tid)
+__device__ __forceinline__ bool redo_flagged(const uint16_t *overflow, int heads, int tid)
 {
     int open = 0;
     for (int g = tid; g < heads; g += kRedoBlock) open |= overflow[g] != 0;
     return __syncthreads_or(open) != 0;
+}
+
+// Counts a row of a flagged head in the head's flag, 1 when it is raised: true, the same for every thread, in the
+// workgroup whose row is the last, to all of whose threads every row is then visible.  `last` is a word of LDS.  Every
+// wave waits for its own stores first: a barrier alone does not (it orders them within the workgroup, which shares a
+// cache), and a fence of the thread that counts waits for its own wave's.
+__device__ __forceinline__ bool redo_counted(uint16_t *flag, int S, int32_t *last)
+{
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) {   // (two flags to a word; no count carries over: S <= 4096)
+        const int odd = (int)(reinterpret_cast<uintptr_t>(flag) >> 1) & 1, shift = 16 * odd;
+        const uint32_t was = __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(flag - odd), 1u << shift, __ATOMIC_ACQ_REL,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        *last = (int)((was >> shift) & 0xffffu) == S;
+    }
+    __syncthreads();
+    if (!*last) return false;
+    __threadfence();
+    return true;
 }
 
 // Rows from `item` on, a workgroup's share of them, up to one that completes its head: that head, or -1 when there
@@ -751,9 +771,9 @@ __device__ __forceinline__ int redo_next(const RedoArgs &a, long &item, int32_t 
         const long row = item;
         const int h = (int)(row / a.S);
         item += wgs;
-        if (a.overflow[h] == 0) continue;   // (not written in this launch: the same for every thread)
+        if (a.overflow[h] == 0) continue;   // (a flag neither comes nor goes in this launch: the same for every thread)
         redo_row<false>(a, row, mem);
-        if (finishes_last(&a.done[h], a.S, last)) return h;
+        if (redo_counted(a.overflow + h, a.S, last)) return h;
     }
     return -1;
 }

@@ -54,7 +54,7 @@ def test_stores_are_complete_before_a_workgroup_is_counted(kernels):
     counted = {}
     for name, code in kernels.items():
         for at, op in enumerate(code):
-            if not (re.match(r"global_atomic_(add|inc)\b", op) and "sc0" in op.split()):   # (sc0: the old value is used)
+            if not (re.match(r"(global|flat)_atomic_(add|inc)\b", op) and "sc0" in op.split()):   # (sc0: the old value is used)
                 continue
             barrier = next(i for i in range(at, -1, -1) if code[i].startswith("s_barrier"))
             before = next((code[i] for i in range(barrier, -1, -1)

@@ -142,6 +142,20 @@ def test_static_scratch_entry_checks_on_the_host(lib):
     assert re.search(r"#define GRAPHKV_STATIC_SCRATCH_BYTES \(\(size_t\)64 << 20\)", header)
 
 
+@pytest.mark.parametrize("H,d,T,S,m,N", [
+    (17, 64, 1, 39, 6, 24666), (17, 128, 3, 39, 4, 24525), (24, 64, 1, 29, 27, 23255), (24, 128, 1, 4, 10, 102588),
+    (48, 64, 1, 39, 28, 8690), (48, 128, 3, 21, 2, 13215), (64, 64, 1, 17, 21, 14530), (64, 128, 3, 40, 18, 8447)])
+def test_static_scratch_entry_takes_what_fills_it(lib, H, d, T, S, m, N):
+    """Layers whose scratch comes within 512 bytes of the built-in buffer's size, with 17 heads and more (whose flags take
+    256 bytes at 4 a head and would not at 16).  (Null pointers: for a call whose scratch fits they are an invalid
+    argument; one whose scratch does not never looks at them.)"""
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=8, budget=9, n_sources=S, n_neighbors=m, rounds=T,
+                  dtype=gk.BF16, scorer=gk.SCORER_KNORM)
+    assert gk.STATIC_SCRATCH_BYTES - 512 <= gk.graphkv_workspace_bytes(p) <= gk.STATIC_SCRATCH_BYTES
+    cp = p.c()
+    assert lib.graphkv_compress_static(ctypes.byref(cp), None, None, None, None, None, None, None, None) == -1
+
+
 def test_binding_fails_loudly_without_library(monkeypatch):
     monkeypatch.setattr(gk, "_lib", None)
     monkeypatch.setattr(gk, "LIB_PATH", "/nonexistent/libgraphkv.so")
