@@ -263,10 +263,9 @@ const char *graphkv_strerror(int32_t code);
  * ms[GRAPHKV_N_KERNELS] and the number of launches into launches[...] (HOST
  * arrays, either may be NULL).  The GENERIC ids count the scalar kernels and, with
  * GRAPHKV_IMPL_AUTO, the matrix-core kernels that take their place; an update of the
- * scores that the next selection does first is counted with that selection, and so are
- * the redoing of rows in front of it and the gather of few rows behind it (an update on
- * its own with rows to redo counts as redo_rows); a later round's bound and filter in
- * one launch count as cosine_bound_new.
+ * scores that the next selection does first is counted with that selection, and so is
+ * the gather of few rows behind it; a later round's bound and filter in one launch count
+ * as cosine_bound_new.
  */
 enum {
     GRAPHKV_K_SCORE_STATS = 0, GRAPHKV_K_SCORE_VOTES, GRAPHKV_K_POOL, GRAPHKV_K_TOPK_SOURCES,

@@ -62,7 +62,7 @@ struct Dims {
 // Workspace: a bump allocation of every scratch array any entry point may need.
 struct Workspace {
     size_t logits, row_max, row_sum, votes, E, src, nbr, nbr_e, scores, part;
-    size_t bound_hist, tau, cand, cand_cnt, overflow, overflow_odd;
+    size_t bound_hist, tau, cand, cand_cnt, overflow;
     // lists kept from one round to the next, speculative rows
     size_t src_b, nbr_b, nbr_e_b, ext, new_src, n_new, sel_row, sel_pos, n_sel, spec_bad;
     size_t final_sel, final_bytes;   // the final selection's (0 bytes: it takes none)
@@ -211,10 +211,7 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
     W.cand = take(frows * g.chunks * g.slice_cap * 8);
     W.cand_cnt = take(frows * g.chunks * 4);
-    // 16-bit flags of even and of odd rounds, each from a whole word on (within the 256 bytes that H words would take)
-    const size_t flags = ((size_t)D.H + 1) / 2 * 4;
-    W.overflow = take(2 * flags);
-    W.overflow_odd = W.overflow + flags;
+    W.overflow = take((size_t)D.H * 4);
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);
     W.nbr_b = take(keep ? (size_t)D.H * D.S * D.m * 4 : 0);
@@ -384,7 +381,6 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
     const bool one_source = D.S == 1 && (p->dtype == GRAPHKV_FP32 || D.d <= 64);
     DecayArgs update{};
     for (int t = 0; t < D.T; ++t) {
-        RedoArgs redo_left{};
         int32_t *src = src0, *nbr = nbr0;
         float *ev = e0;
         if (t == 0 || p->reselect) {
@@ -400,9 +396,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                 // Eq. 1 + Eq. 3 in one streaming pass over the keys: a bound per source from a
                 // strided sample that at least m of its edges reach, then only edges above it are kept.
                 float *tau = at<float>(ws, W.tau);
-                int32_t *cnt = at<int32_t>(ws, W.cand_cnt);
-                uint16_t *ovf = at<uint16_t>(ws, t & 1 ? W.overflow_odd : W.overflow);
-                const RedoArgs redo{Ac, Kc, D.N, D.P, D.S, D.m, D.H, src, ovf, E, nbr, ev};
+                int32_t *cnt = at<int32_t>(ws, W.cand_cnt), *ovf = at<int32_t>(ws, W.overflow);
                 void *cand = at<char>(ws, W.cand);
                 int32_t *ext = at<int32_t>(ws, W.ext);
                 if (!(keep && prev_src)) {
@@ -428,9 +422,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     int32_t *new_src = at<int32_t>(ws, W.new_src), *n_new = at<int32_t>(ws, W.n_new);
                     const SelectRows sel{at<int32_t>(ws, W.n_sel), at<int32_t>(ws, W.sel_row),
                                          at<int32_t>(ws, W.sel_pos)};
-                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, at<uint16_t>(ws, W.overflow),
+                    const MatchArgs match{D.S, g.X, D.m, t == 1, prev_src, prev_nbr, prev_e, nbr, ev, ext, ovf,
                                           at<int32_t>(ws, W.spec_bad), new_src, n_new, at<int32_t>(ws, W.sel_row),
-                                          at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel), ovf};
+                                          at<int32_t>(ws, W.sel_pos), at<int32_t>(ws, W.n_sel)};
                     if (pick_match_applies(D.S)) {
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES_LATER, launch_pick_match(scores, D.P, D.H, match, src, update, st));
                         update = DecayArgs{};
@@ -455,9 +449,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
                                launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));
                 }
-                // heads whose lists overflowed are redone row by row, exactly: by the kernel that takes the update
-                // along, where there is one
-                redo_left = redo;
+                // heads whose lists overflowed are redone row by row, exactly
+                GKV_LAUNCH(GRAPHKV_K_REDO_ROWS,
+                           launch_redo_rows(Ac, Kc, D.H, D.N, D.P, D.S, D.m, src, ovf, E, nbr, ev, st));
             } else {
                 // Eq. 2: source nodes
                 GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES,
@@ -482,16 +476,9 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
         }
         // Eq. 5: one round of the signal
         const bool next_takes_it = t + 1 < D.T ? D.filter && keep && pick_match_applies(D.S) : last != nullptr;
-        update = DecayArgs{nbr, ev, items, D.S * D.m, p->decay, p->signal, redo_left};
-        if (!next_takes_it || !items) {
-            if (items && redo_left.overflow) {
-                GKV_LAUNCH(GRAPHKV_K_REDO_ROWS, launch_redo_decay(scores, D.H, D.P, update, st));
-            } else {
-                if (redo_left.overflow) GKV_LAUNCH(GRAPHKV_K_REDO_ROWS, launch_redo_rows(redo_left, st));
-                GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
-            }
-            update = DecayArgs{};
-        }
+        update = DecayArgs{nbr, ev, next_takes_it ? items : 0, items ? D.S * D.m : 0, p->decay, p->signal};
+        if (!update.items)
+            GKV_LAUNCH(GRAPHKV_K_DECAY, launch_decay(scores, D.H, D.P, D.S, D.m, nbr, ev, p->decay, p->signal, st));
         prev_src = src;
         prev_nbr = nbr;
         prev_e = ev;

@@ -182,9 +182,12 @@ __device__ __forceinline__ void decay_chain(float *s, int count, int cells, cons
 // behind which `mem` is free.  (Hash chains, then a read of the row: the row was ready 7.6 us into a workgroup with
 // 32736 nodes and 2048 triples, 5.6 with 16384; this way 4.8 and 4.5, of which the row's own 128 KiB take 2.)
 constexpr int kUpdateBlock = 1024;
-template <int ITEMS, int D> constexpr size_t update_row_lds()   // table, marks, edges (4 per thread stay in memory), links
+// Table, marks, links and, where that fits, edges: not with four triples a thread and 32 entries, whose edges stay in
+// memory.
+template <int ITEMS, int D> constexpr bool update_row_edges() { return ITEMS < 32 || D < 4; }
+template <int ITEMS, int D> constexpr size_t update_row_lds()
 {
-    return D ? (size_t)kUpdateBlock * (4 * ITEMS + 4 + (D < 4 ? 4 * D : 0) + 2 * D) : 0;
+    return D ? (size_t)kUpdateBlock * (4 * ITEMS + 4 + (update_row_edges<ITEMS, D>() ? 4 * D : 0) + 2 * D) : 0;
 }
 
 // The thread's triples; asked for in front of the row, which takes longer.
@@ -205,7 +208,7 @@ __device__ __forceinline__ void update_row(float (&val)[ITEMS], const Triples<D>
                                            unsigned char *mem, int tid)
 {
     constexpr int BLOCK = kUpdateBlock;
-    constexpr bool EDGES = D < 4;
+    constexpr bool EDGES = update_row_edges<ITEMS, D>();
     static_assert(ITEMS <= 32, "one mark per entry of a thread");
     uint32_t *cell = reinterpret_cast<uint32_t *>(mem);                 // [BLOCK * ITEMS] by node
     uint32_t *mark = cell + BLOCK * ITEMS;                              // [BLOCK] bit i: entry i of the thread is new

@@ -30,19 +30,9 @@ hipError_t launch_pick_sources(const float *x, long ld, int n, int rows, int S, 
 // Neighbourhoods of the heads whose overflow flag is set (filter route, bf16, d = 128): a fixed
 // number of workgroups walk the (head, source) rows of those heads, each computing one row of
 // edges into its own scratch row (rows: redo_rows_scratch_bytes()) and taking the exact top-m.
-// Or the kernel behind does it, before it takes what it needs (DecayArgs): flagged heads then wait for their last
-// row, up to which their flags count (S <= 4096 there).  A flag is 16 bits, so that two rounds' fit 4 bytes a head.
-struct RedoArgs {
-    const void *Ac, *Kc;
-    int N, P, S, m, heads;
-    const int32_t *src;
-    uint16_t *overflow;   // nullptr for no rows to redo
-    float *rows;
-    int32_t *nbr;
-    float *nbr_e;
-};
 size_t redo_rows_scratch_bytes(int heads, int S, int P);
-hipError_t launch_redo_rows(const RedoArgs &a, hipStream_t st);
+hipError_t launch_redo_rows(const void *Ac, const void *Kc, int heads, int N, int P, int S, int m, const int32_t *src,
+                            const int32_t *overflow, float *rows, int32_t *nbr, float *nbr_e, hipStream_t st);
 
 // ---- scalar kernels for any dtype / shape (generic.hip) ----------------------
 // logits [Hq*w, N] (fp32, scaled), then per-row max and sum of exp.
@@ -102,11 +92,8 @@ struct DecayArgs {
     int items, count;
     float alpha;
     int signal;
-    RedoArgs redo;   // (done before the update; only with one that rides along)
 };
 int decay_rides_along(int P, int S, int m);
-// ... or, where there is none but rows to redo (u.items > 0, u.redo.overflow set), with those alone.
-hipError_t launch_redo_decay(float *scores, int rows, int P, const DecayArgs &u, hipStream_t st);
 // Kout[q,t,:] = Kc[q, idx[q,t], :] for the heads q of a batch, same for V; packed
 // outputs, per-layer budgets from the plan; row_bytes multiple of 16.
 hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int heads, int N,
@@ -186,14 +173,14 @@ size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // p
 // sources [Hkv, S], n_src [Hkv] of them in use, rows 0 .. of the buffers.
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                     const MfmaFilterPlan &g, bool first_round, const int32_t *src,
-                                    const int32_t *n_src, void *hist_part, float *tau, uint16_t *overflow,
+                                    const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
                                     hipStream_t st);
 // Filter pass: streams all keys; edges that reach a row's tau go to its slices, their number
 // per slice to cand_cnt.  Same source lists and rows as the bound pass.
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                      const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
-                                     uint16_t *overflow, hipStream_t st);
+                                     int32_t *overflow, hipStream_t st);
 // From the second round on (match.hpp): which sources keep their list from the round before (copied
 // from prev_nbr / prev_e to nbr / nbr_e), which are speculative rows of the first round (the last X
 // entries of ext [Hkv, S + X]; not used for heads that overflowed then: spec_bad [Hkv], set by the first
@@ -207,9 +194,8 @@ struct MatchArgs {
     int32_t *nbr;
     float *nbr_e;
     const int32_t *ext;
-    const uint16_t *overflow;
+    int32_t *overflow;   // [Hkv] flags of the round before, cleared for this one by launch_pick_match()
     int32_t *spec_bad, *new_src, *n_new, *sel_row, *sel_pos, *n_sel;
-    uint16_t *clear;   // [Hkv] overflow flags of this round, cleared
 };
 // Source nodes (Eq. 2) of a later round and their match, one launch for S <= 256 (pick_match_applies).
 bool pick_match_applies(int S);
@@ -224,13 +210,13 @@ struct SelectRows {
     const int32_t *row;      // [Hkv, S] candidate row of the x-th selection
     const int32_t *pos;      // [Hkv, S] its source slot in this round's list
 };
-hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, uint16_t *overflow, const int32_t *src,
+hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st);
 // A later round's bound and filter passes in one launch, for few heads (overflow is not cleared).
 bool late_filter_applies(int Hkv, const MfmaFilterPlan &g);
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
-                              uint16_t *overflow, hipStream_t st);
+                              int32_t *overflow, hipStream_t st);
 
 }  // namespace gkv

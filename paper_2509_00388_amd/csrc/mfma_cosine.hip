@@ -53,7 +53,7 @@ struct FilterArgs {
     const float *tau;      // [Hkv, pitch] the bound pass's value per row: edges below it are dropped
     uint2 *cand;           // [Hkv, pitch, chunks, slice_cap] (edge bits, key index): one slice per key chunk
     int32_t *cand_cnt;     // [Hkv, pitch, chunks] entries in each slice
-    uint16_t *overflow;    // [Hkv]
+    int32_t *overflow;     // [Hkv]
     int slice_cap;
     int drain_every;       // tiles between two scheduled drains of the rings
     int sgroups;           // workgroups (groups of source rows) per key chunk
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride,
     int S, int src_pitch, const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int m,
     int chunk_cols, uint32_t *__restrict__ hist_part, float *__restrict__ tau, int pitch, int row0,
-    uint16_t *__restrict__ overflow)
+    int32_t *__restrict__ overflow)
 {
     constexpr int ROWS = SB * kBlk, NT = 256 * SB;
     __shared__ float inv_s[ROWS];
@@ -640,7 +640,7 @@ __device__ __forceinline__ uint32_t ord_key_inv(uint32_t k)
 // (src [Hkv, S]); without those lists row x goes to slot x.
 __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict__ cand,
                                                          const int32_t *__restrict__ cand_cnt,
-                                                         uint16_t *__restrict__ overflow,
+                                                         int32_t *__restrict__ overflow,
                                                          const int32_t *__restrict__ src, int S, int pitch,
                                                          int chunks, int slice_cap, int cap, int m,
                                                          SelectRows sel, int32_t *__restrict__ nbr,
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 template <int R>
 __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
                                                               const int32_t *__restrict__ cand_cnt,
-                                                              uint16_t *__restrict__ overflow,
+                                                              int32_t *__restrict__ overflow,
                                                               const int32_t *__restrict__ src, int S, int pitch,
                                                               int chunks, int slice_cap, int m, SelectRows sel,
                                                               int32_t *__restrict__ nbr,
@@ -1231,7 +1231,7 @@ int bound_chunks(int Hkv, int P, int sgroups)
 template <int SB, int BINS>
 hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                         int src_pitch, const int32_t *n_src, bool late, void *hist_part, float *tau, int pitch,
-                        int row0, uint16_t *overflow, hipStream_t st)
+                        int row0, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const Sample smp = sample_of(P);
@@ -1270,7 +1270,7 @@ int filter_drain_every(int P, int m, int ring)
 template <int SB, int RING>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                          int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, int row0,
-                         const float *tau, void *cand, int32_t *cand_cnt, uint16_t *overflow, hipStream_t st)
+                         const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
@@ -1295,7 +1295,7 @@ size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g)
 
 hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                     const MfmaFilterPlan &g, bool first_round, const int32_t *src,
-                                    const int32_t *n_src, void *hist_part, float *tau, uint16_t *overflow,
+                                    const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
                                     hipStream_t st)
 {
     if (first_round && g.sb == 3)
@@ -1308,7 +1308,7 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                      const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
-                                     uint16_t *overflow, hipStream_t st)
+                                     int32_t *overflow, hipStream_t st)
 {
     if (first_round && g.sb == 3)
         return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand,
@@ -1335,7 +1335,7 @@ bool late_filter_applies(int Hkv, const MfmaFilterPlan &g)
 
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
-                              uint16_t *overflow, hipStream_t st)
+                              int32_t *overflow, hipStream_t st)
 {
     const int sgroups = (g.S + kRows - 1) / kRows;
     const Sample smp = sample_of(P);
@@ -1349,7 +1349,7 @@ hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, in
     return hipGetLastError();
 }
 
-hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, uint16_t *overflow, const int32_t *src,
+hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st)
 {

@@ -23,6 +23,16 @@ namespace {
 
 constexpr int kBins = 2048;   // bins of the streaming variant (11-bit digits)
 
+// The thread's number, read anew: what is computed from it stays where it is used.  (Where a kernel begins with the
+// loads of a whole row, or loops over rows, the compiler otherwise moves the addresses of much that comes later in front
+// of them.  Redone rows: 146 registers a lane spill, 294 -> 334 us for 8 heads of 32736 keys; a selection that takes
+// the update along: 16352 entries 25.4 -> 27.9 us with 68 registers instead of 57.)
+__device__ __forceinline__ int here(int tid)
+{
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 __device__ __forceinline__ float key_to_float(uint32_t key)   // inverse of ord_key
 {
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
@@ -632,12 +642,6 @@ __device__ __forceinline__ void pick_row_long(const float *xr, int n, int k, con
 // (Eq. 3) is taken by the row kernels above.  The edges are formed exactly as in the streaming
 // kernels -- the same matrix-core instruction sequence with the source in every operand row, the
 // same norms -- so that a head gets the same bits whichever route it takes.
-//
-// A launch of its own that finds no flag set costs 2 to 5 us, and there is one in every round.  So where the
-// next kernel has a workgroup per head anyway (an update that rides along) that kernel does the rows first:
-// without a flag its workgroups go straight on; with one, all of them (as many more than heads as the rows want)
-// take rows, unflagged heads go on at once, and a flagged head is gone on with by the workgroup that finishes its
-// last row.  Nobody waits for another.
 constexpr int kRedoBlock = 1024;
 constexpr size_t kRedoLds = (size_t)(kRedoBlock / kWave) * kBlk * kPitch;   // a block of keys per wave
 
@@ -651,29 +655,28 @@ __host__ __device__ inline int redo_rows_workgroups(int heads, int S, int P)
     return (int)(items < wgs ? items : wgs);
 }
 
-// The thread's number, read anew: what is computed from it stays where it is used.  (The loops of the kernels below go
-// round once but for heads that are redone; without this the compiler moves the addresses of a row's 32 loads and
-// much else in front of them, and 128 registers a lane then spill: 12.7 -> 33 us for a source selection.)
-__device__ __forceinline__ int here(int tid)
-{
-    asm volatile("" : "+v"(tid));
-    return tid;
-}
+struct RedoArgs {
+    const uint16_t *Ac, *Kc;
+    int N, P, S, m, heads;
+    const int32_t *src, *overflow;
+    float *rows;
+    int32_t *nbr;
+    float *nbr_e;
+};
 
 // Row `item` (head * S + source slot): its edges to the workgroup's scratch row, its m best to the lists.  mem: kRedoLds
-// bytes.  Begins and ends with a barrier.  A wave takes 32 keys at a time, fetched whole rows at a time and turned
-// into operand layout in its own part of the LDS (operand layout straight from memory touches every line four
-// times, and the waves' lines do not fit the first-level cache).  (64 heads x 64 rows of 10000 keys, the whole
-// call, with the fetch in operand layout and a radix selection from the LDS: 1438 us; this way 1070 with the few-
-// winners selection in a launch of its own, 1177 in front of the next kernel with the general one, which needs no
-// more registers.)
-template <bool PICK>   // PICK: the selection of short rows, for the kernel that does nothing else
+// bytes.  Begins with a barrier.  A wave takes 32 keys at a time, fetched whole rows at a time and turned into operand
+// layout in its own part of the LDS (operand layout straight from memory touches every line four times, and the waves'
+// lines do not fit the first-level cache).  (Key norms, clustered keys, two rounds, whole calls, us, the fetch in operand
+// layout and a radix selection from the LDS / this way / this way with the general selection, in front of the kernel
+// that takes the update along and without a launch of its own: 8 heads of 32736 keys 460 / 294 / 338, 64 heads of 16352
+// 526 / 438 / 490, 256 heads of 32736 9000 / 4895 / 8300; 8 heads of 16 K keys with nothing to redo 120.0 / 105.0 / 104.3.)
 __device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned char *mem)
 {
     const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5, h = (int)(item / a.S);
     float *erow = a.rows + (long)blockIdx.x * a.P;
     const int32_t i = a.src[item];
-    const uint16_t *ah = (const uint16_t *)a.Ac + (long)h * a.N * kD, *kh = (const uint16_t *)a.Kc + (long)h * a.N * kD;
+    const uint16_t *ah = a.Ac + (long)h * a.N * kD, *kh = a.Kc + (long)h * a.N * kD;
     unsigned char *tile = mem + wv * (kBlk * kPitch);
     __syncthreads();                          // the previous row's LDS and scratch row are free
     // the source's row in every row of the operand (a lane holds elements 16 s + 8 hh ..)
@@ -721,7 +724,7 @@ __device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned 
         wave_sync();                          // the tile is read before the next block's rows go in
     }
     __syncthreads();                          // the row is complete and visible to the workgroup
-    if (PICK && a.P <= 32 * kRedoBlock && a.m <= kSmallK) {
+    if (a.P <= 32 * kRedoBlock && a.m <= kSmallK) {
         PickLds<kRedoBlock> &L = *reinterpret_cast<PickLds<kRedoBlock> *>(mem);
         const PickOut o{a.m, a.nbr + item * a.m, nullptr, a.nbr_e + item * a.m};
         float val[32];
@@ -731,59 +734,16 @@ __device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned 
     } else {
         topk_stream_row<kRedoBlock, false>(0, erow, a.P, a.P, a.m, a.nbr + item * a.m, 0, a.nbr_e + item * a.m, 0, 0, 0, 0);
     }
-    __syncthreads();
-}
-
-// Whether any head is flagged (the same for every thread; contains a barrier).
-__device__ __forceinline__ bool redo_flagged(const uint16_t *overflow, int heads, int tid)
-{
-    int open = 0;
-    for (int g = tid; g < heads; g += kRedoBlock) open |= overflow[g] != 0;
-    return __syncthreads_or(open) != 0;
-}
-
-// Counts a row of a flagged head in the head's flag, 1 when it is raised: true, the same for every thread, in the
-// workgroup whose row is the last, to all of whose threads every row is then visible.  `last` is a word of LDS.  Every
-// wave waits for its own stores first: a barrier alone does not (it orders them within the workgroup, which shares a
-// cache), and a fence of the thread that counts waits for its own wave's.
-__device__ __forceinline__ bool redo_counted(uint16_t *flag, int S, int32_t *last)
-{
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {   // (two flags to a word; no count carries over: S <= 4096)
-        const int odd = (int)(reinterpret_cast<uintptr_t>(flag) >> 1) & 1, shift = 16 * odd;
-        const uint32_t was = __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(flag - odd), 1u << shift, __ATOMIC_ACQ_REL,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        *last = (int)((was >> shift) & 0xffffu) == S;
-    }
-    __syncthreads();
-    if (!*last) return false;
-    __threadfence();
-    return true;
-}
-
-// Rows from `item` on, a workgroup's share of them, up to one that completes its head: that head, or -1 when there
-// are no more.  `last` is a word of LDS.
-__device__ __forceinline__ int redo_next(const RedoArgs &a, long &item, int32_t *last, unsigned char *mem)
-{
-    const int wgs = redo_rows_workgroups(a.heads, a.S, a.P);
-    while ((int)blockIdx.x < wgs && item < (long)a.heads * a.S) {
-        const long row = item;
-        const int h = (int)(row / a.S);
-        item += wgs;
-        if (a.overflow[h] == 0) continue;   // (a flag neither comes nor goes in this launch: the same for every thread)
-        redo_row<false>(a, row, mem);
-        if (redo_counted(a.overflow + h, a.S, last)) return h;
-    }
-    return -1;
 }
 
 __global__ __launch_bounds__(kRedoBlock) void redo_rows_kernel(RedoArgs a)
 {
     extern __shared__ __align__(16) unsigned char mem[];
-    if (!redo_flagged(a.overflow, a.heads, threadIdx.x)) return;
+    int open = 0;   // any flagged head at all?  (a few loads instead of a walk over all rows)
+    for (int g = threadIdx.x; g < a.heads; g += kRedoBlock) open |= a.overflow[g] != 0;
+    if (!__syncthreads_or(open)) return;
     for (long item = blockIdx.x; item < (long)a.heads * a.S; item += gridDim.x)
-        if (a.overflow[item / a.S]) redo_row<true>(a, item, mem);   // (the same for every thread)
+        if (a.overflow[item / a.S]) redo_row(a, item, mem);   // (the same for every thread)
 }
 
 template <int ITEMS>   // 0: rows beyond 32768 entries
@@ -811,98 +771,47 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
 // triples: 19.4 us for 32736 nodes and 17.0 for 15969 with the row read behind the update and the lists read again;
 // 16.6 and 12.7 this way.)
 template <int ITEMS, int D>
-__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, int heads, MatchArgs a,
-                                                                int32_t *__restrict__ src_out, DecayArgs update)
+__global__ __launch_bounds__(kPickBlock) void pick_match_kernel(float *x, int n, MatchArgs a, int32_t *__restrict__ src_out,
+                                                                DecayArgs update)
 {
-    static_assert(kPickBlock == kMatchBlock && kPickBlock == kUpdateBlock && kPickBlock == kRedoBlock, "one workgroup does all");
+    static_assert(kPickBlock == kMatchBlock && kPickBlock == kUpdateBlock, "one workgroup does all");
     extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
     PickLds<kPickBlock> &L = *reinterpret_cast<PickLds<kPickBlock> *>(mem);
     __shared__ int32_t match_lds[2 * kSmallK + kMaxExtSources], to_s[kSmallK];
     __shared__ int32_t wave_new[kPickBlock / kWave], wave_fb[kPickBlock / kWave];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    float *xr = x + (long)h * n;
+    int32_t *src = src_out + (long)h * a.S;
+    const PickOut o{a.S, src, nullptr, nullptr};
     Triples<D> tri;
+    bool bad;
     if constexpr (ITEMS == 0) {
-        const int h = blockIdx.x;
-        float *xr = x + (long)h * n;
-        int32_t *src = src_out + (long)h * a.S;
-        const PickOut o{a.S, src, nullptr, nullptr};
-        if (tid == 0) a.clear[h] = 0;
-        const bool bad = match_load(a, h, match_lds, tid);
+        bad = match_load(a, h, match_lds, tid);
         pick_row_long(xr, n, a.S, o, L, tid, lane, wv);
-        __syncthreads();   // the sources are written
-        match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
     } else {
-        int h = min((int)blockIdx.x, heads - 1);
         // (what the match needs first, then the update, then the row: loads come back in the order they leave)
-        int32_t prev, spec;
-        bool bad;
+        const int32_t prev = a.prev_src[(long)h * a.S + min(tid, a.S - 1)];
+        const int32_t spec = a.X > 0 ? a.ext[(long)h * (a.S + a.X) + a.S + min(tid, a.X - 1)] : 0;
+        bad = a.X == 0 || (a.first ? a.overflow[h] : a.spec_bad[h]) != 0;
+        tri.load(update, h, tid);
         float val[ITEMS];
-        auto ask = [&] {
-            const int tid = here(threadIdx.x);
-            prev = a.prev_src[(long)h * a.S + min(tid, a.S - 1)];
-            spec = a.X > 0 ? a.ext[(long)h * (a.S + a.X) + a.S + min(tid, a.X - 1)] : 0;
-            bad = a.X == 0 || (a.first ? a.overflow[h] : a.spec_bad[h]) != 0;
-            tri.load(update, h, tid);
-            load_row<kPickBlock>(x + (long)h * n, n, tid, val);
-        };
-        ask();
-        bool redo = false, mine = (int)blockIdx.x < heads;
-        long item = blockIdx.x;
-        if (D > 0 && update.redo.overflow) {
-            redo = redo_flagged(update.redo.overflow, heads, tid);
-            mine = mine && !(redo && update.redo.overflow[h]);
-        }
-        while (true) {
-            if (mine) {
-                const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
-                float *xr = x + (long)h * n;
-                int32_t *src = src_out + (long)h * a.S;
-                const PickOut o{a.S, src, nullptr, nullptr};
-                if (tid == 0) a.clear[h] = 0;
-                if (a.X > 0 && a.first && tid == 0) a.spec_bad[h] = bad ? 1 : 0;
-                if (tid < a.S) match_lds[tid] = prev;
-                if (tid < a.X) match_lds[2 * a.S + tid] = spec;
-                if (tid < kSmallK) to_s[tid] = -1;
-                if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, h, update, mem, tid);
-                L.clear(tid);
-                pick_row<kPickBlock, ITEMS, false>(val, xr, n, a.S, o, L, tid, lane, wv);
-                __syncthreads();   // the sources are written
-                match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
-            }
-            if (!redo) return;
-            __syncthreads();
-            h = redo_next(update.redo, item, wave_new, mem);
-            if (h < 0) return;
-            ask();
-            mine = true;
-        }
+        load_row<kPickBlock>(xr, n, here(threadIdx.x), val);
+        const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
+        if (a.X > 0 && a.first && tid == 0) a.spec_bad[h] = bad ? 1 : 0;
+        if (tid < a.S) match_lds[tid] = prev;
+        if (tid < a.X) match_lds[2 * a.S + tid] = spec;
+        if (tid < kSmallK) to_s[tid] = -1;
+        if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, h, update, mem, tid);
+        L.clear(tid);
+        pick_row<kPickBlock, ITEMS, false>(val, xr, n, a.S, o, L, tid, lane, wv);
     }
+    __syncthreads();   // the sources are written, the flag is read
+    if (tid == 0) a.overflow[h] = 0;
+    match_head<D>(a, h, bad, src, match_lds, to_s, wave_new, wave_fb, tri, tid);
 }
 template <int ITEMS, int D> constexpr size_t pick_match_lds()
 {
     return update_row_lds<ITEMS, D>() > sizeof(PickLds<kPickBlock>) ? update_row_lds<ITEMS, D>() : sizeof(PickLds<kPickBlock>);
-}
-
-// The update alone, rows redone first.
-template <int D>
-__global__ __launch_bounds__(kRedoBlock) void redo_decay_kernel(float *x, int P, int heads, DecayArgs u)
-{
-    extern __shared__ __align__(16) unsigned char mem[];
-    __shared__ int32_t last;
-    const int tid = threadIdx.x;
-    const bool redo = redo_flagged(u.redo.overflow, heads, tid);
-    int h = blockIdx.x;
-    bool mine = h < heads && !(redo && u.redo.overflow[h]);
-    for (long item = blockIdx.x;;) {
-        if (mine)
-            decay_chain<uint32_t, kRedoBlock, D, true>(x + (long)h * P, u.count, 2048 * D, u.nbr + (long)h * u.count,
-                                                       u.nbr_e + (long)h * u.count, u.alpha, u.signal, mem, tid);
-        if (!redo) return;
-        __syncthreads();
-        h = redo_next(u.redo, item, &last, mem);
-        if (h < 0) return;
-        mine = true;
-    }
 }
 
 // The k best edges of each row of a dense edge block, ascending indices, with their values.
@@ -1141,65 +1050,38 @@ __device__ __forceinline__ void budget_row(const float (&row)[ITEMS], int n, int
     (void)emit_bitmap<NW>(map, min(CELLS, (n + kWave - 1) / kWave), k, L.part[1], out, tid, lane, wv);
 }
 
-// REDO: rows of the last round may have to be redone first (the registers that takes cost the others 1 us).
-template <int ITEMS, int D, bool REDO>
+template <int ITEMS, int D>
 __global__ __launch_bounds__(kBudgetBlock) void budget_select_kernel(
-    float *x, int n, int heads, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update,
-    GatherArgs rows, LayerPlan plan)
+    float *x, int n, int32_t *__restrict__ idx_out, int append_from, int append_count, DecayArgs update, GatherArgs rows,
+    LayerPlan plan)
 {
-    static_assert(kBudgetBlock == kUpdateBlock && kBudgetBlock == kRedoBlock, "one workgroup does all");
+    static_assert(kBudgetBlock == kUpdateBlock, "one workgroup does both");
     extern __shared__ __align__(16) unsigned char mem[];   // the update's, then the selection's
     BudgetLds &L = *reinterpret_cast<BudgetLds *>(mem);
-    __shared__ int32_t last;
-    (void)last;
-    const int tid = threadIdx.x;
-    int row = min((int)blockIdx.x, heads - 1);
+    const int row = blockIdx.x;
+    const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
+    const int k = plan.budget[g] - append_count;
+    int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
+    float *xr = x + (long)row * n;
     Triples<D> tri;
+    tri.load(update, row, threadIdx.x);
     float val[ITEMS];
-    auto ask = [&] {
-        const int tid = here(threadIdx.x);
-        tri.load(update, row, tid);
-        load_row<kBudgetBlock>(x + (long)row * n, n, tid, val);
-    };
-    ask();
-    bool redo = false, mine = (int)blockIdx.x < heads;
-    long item = blockIdx.x;
-    if constexpr (REDO) {
-        redo = redo_flagged(update.redo.overflow, heads, tid);
-        mine = mine && !(redo && update.redo.overflow[row]);
-    }
-    while (true) {
-        if (mine) {
-            const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
-            const int g = row / plan.heads_per_layer, hl = row % plan.heads_per_layer;
-            const int k = plan.budget[g] - append_count;
-            int32_t *out = idx_out + (plan.row_off[g] + (long)hl * plan.budget[g]);
-            float *xr = x + (long)row * n;
-            for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
-            if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
-            budget_row<ITEMS>(val, n, k, out, L, tid, lane, wv);
-            if (rows.Kout) {
-                // The retained rows of K and V, 16 bytes a thread: with little to copy that is done before a launch
-                // of its own would have begun.
-                __syncthreads();   // the indices are written
-                const int pieces = rows.row_bytes / 16, B = k + append_count;
-                const long from0 = (long)row * rows.N, to0 = (plan.row_off[g] + (long)hl * plan.budget[g]) * pieces;
-                for (int u = tid; u < B * pieces; u += kBudgetBlock) {
-                    const long from = (from0 + out[u / pieces]) * pieces + u % pieces;
-                    const uint4 a = ((const uint4 *)rows.Kc)[from], b = ((const uint4 *)rows.Vc)[from];
-                    ((uint4 *)rows.Kout)[to0 + u] = a;
-                    ((uint4 *)rows.Vout)[to0 + u] = b;
-                }
-            }
-        }
-        if (!REDO || !redo) return;
-        if constexpr (REDO) {
-            __syncthreads();
-            row = redo_next(update.redo, item, &last, mem);
-            if (row < 0) return;
-            ask();
-            mine = true;
-        }
+    load_row<kBudgetBlock>(xr, n, here(threadIdx.x), val);
+    const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6;
+    for (int r = tid; r < append_count; r += kBudgetBlock) out[k + r] = append_from + r;
+    if constexpr (D > 0) update_row<ITEMS, D>(val, tri, xr, row, update, mem, tid);   // (the last round's, in a whole pass)
+    budget_row<ITEMS>(val, n, k, out, L, tid, lane, wv);
+    if (!rows.Kout) return;
+    // The retained rows of K and V, 16 bytes a thread: with little to copy that is done before a launch of its own
+    // would have begun.
+    __syncthreads();   // the indices are written
+    const int pieces = rows.row_bytes / 16, B = k + append_count;
+    const long from0 = (long)row * rows.N, to0 = (plan.row_off[g] + (long)hl * plan.budget[g]) * pieces;
+    for (int u = tid; u < B * pieces; u += kBudgetBlock) {
+        const long from = (from0 + out[u / pieces]) * pieces + u % pieces;
+        const uint4 a = ((const uint4 *)rows.Kc)[from], b = ((const uint4 *)rows.Vc)[from];
+        ((uint4 *)rows.Kout)[to0 + u] = a;
+        ((uint4 *)rows.Vout)[to0 + u] = b;
     }
 }
 
@@ -1508,10 +1390,8 @@ static hipError_t launch_pick(const float *x, long ld, int n, int rows, int k, i
 
 bool pick_match_applies(int S) { return S <= kSmallK; }
 
-static int redo_grid(int heads, const DecayArgs &update);
-static size_t redo_lds(size_t own, const DecayArgs &update);
 constexpr int kBigLds = 147456;   // dynamic LDS of the kernels that take an update along, at most
-static_assert(update_row_lds<32, 2>() <= kBigLds && update_row_lds<32, 4>() <= kBigLds && kRedoLds <= kBigLds, "");
+static_assert(update_row_lds<32, 2>() <= kBigLds && update_row_lds<32, 4>() <= kBigLds, "");
 
 template <int D>
 static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs &a, int32_t *src,
@@ -1519,10 +1399,9 @@ static hipError_t launch_pick_match_d(float *x, int n, int rows, const MatchArgs
 {
 #define GKV_PICK(ITEMS)                                                                                          \
     do {                                                                                                         \
-        const size_t lds = redo_lds(pick_match_lds<ITEMS, D>(), update);                                         \
         if (D > 0 && !allow_big_lds((const void *)pick_match_kernel<ITEMS, D>, kBigLds)) return hipGetLastError(); \
-        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(redo_grid(rows, update)), dim3(kPickBlock), lds, st, x, n, \
-                           rows, a, src, update);                                                                \
+        hipLaunchKernelGGL((pick_match_kernel<ITEMS, D>), dim3(rows), dim3(kPickBlock), (pick_match_lds<ITEMS, D>()), st, x, n, \
+                           a, src, update);                                                                      \
     } while (0)
     if (n <= 4096) GKV_PICK(4);   // (lists are kept on the filter route only: 2048 nodes or more)
     else if (n <= 8192) GKV_PICK(8);
@@ -1578,39 +1457,12 @@ size_t redo_rows_scratch_bytes(int heads, int S, int P)
     return (size_t)redo_rows_workgroups(heads, S, P) * P * sizeof(float);
 }
 
-hipError_t launch_redo_rows(const RedoArgs &a, hipStream_t st)
+hipError_t launch_redo_rows(const void *Ac, const void *Kc, int heads, int N, int P, int S, int m, const int32_t *src,
+                            const int32_t *overflow, float *rows, int32_t *nbr, float *nbr_e, hipStream_t st)
 {
+    const RedoArgs a{(const uint16_t *)Ac, (const uint16_t *)Kc, N, P, S, m, heads, src, overflow, rows, nbr, nbr_e};
     if (!allow_big_lds((const void *)redo_rows_kernel, (int)kRedoLds)) return hipGetLastError();
-    hipLaunchKernelGGL(redo_rows_kernel, dim3(redo_rows_workgroups(a.heads, a.S, a.P)), dim3(kRedoBlock), kRedoLds, st, a);
-    return hipGetLastError();
-}
-
-// Workgroups of a kernel with a workgroup per head that redoes rows first.
-static int redo_grid(int heads, const DecayArgs &update)
-{
-    if (!update.redo.overflow) return heads;
-    const int wgs = redo_rows_workgroups(heads, update.redo.S, update.redo.P);
-    return wgs > heads ? wgs : heads;
-}
-// ... and its dynamic LDS.
-static size_t redo_lds(size_t own, const DecayArgs &update) { return update.redo.overflow && own < kRedoLds ? kRedoLds : own; }
-
-// The last round's update as a launch of its own, rows redone first.
-hipError_t launch_redo_decay(float *scores, int rows, int P, const DecayArgs &u, hipStream_t st)
-{
-#define GKV_DECAY(D)                                                                                                  \
-    do {                                                                                                              \
-        const size_t lds = redo_lds(decay_chain_lds<uint32_t>(2048 * D, 1024 * D, true), u);                          \
-        if (!allow_big_lds((const void *)redo_decay_kernel<D>, (int)lds)) return hipGetLastError();                    \
-        hipLaunchKernelGGL(redo_decay_kernel<D>, dim3(redo_grid(rows, u)), dim3(kRedoBlock), lds, st, scores, P, rows, u); \
-    } while (0)
-    switch (u.items) {
-        case 1: GKV_DECAY(1); break;
-        case 2: GKV_DECAY(2); break;
-        case 4: GKV_DECAY(4); break;
-        default: return hipErrorInvalidValue;
-    }
-#undef GKV_DECAY
+    hipLaunchKernelGGL(redo_rows_kernel, dim3(redo_rows_workgroups(heads, S, P)), dim3(kRedoBlock), kRedoLds, st, a);
     return hipGetLastError();
 }
 
@@ -1632,14 +1484,11 @@ static hipError_t launch_budget_d(float *scores, int P, int rows, const LayerPla
 {
 #define GKV_BUDGET(ITEMS)                                                                                       \
     do {                                                                                                        \
-        const size_t lds = redo_lds(budget_lds<ITEMS, D>(), update);                                            \
-        constexpr bool may = ITEMS > 1 && D > 0;                                                                \
-        auto *kernel = may && update.redo.overflow ? budget_select_kernel<ITEMS, D, may> : budget_select_kernel<ITEMS, D, false>; \
-        if (D > 0 && !allow_big_lds((const void *)kernel, kBigLds)) return hipGetLastError();                   \
-        hipLaunchKernelGGL(kernel, dim3(redo_grid(rows, update)), dim3(kBudgetBlock), lds, st, scores, P, rows, \
-                           idx, P, w, update, gather, plan);                                                    \
+        if (D > 0 && !allow_big_lds((const void *)budget_select_kernel<ITEMS, D>, kBigLds)) return hipGetLastError(); \
+        hipLaunchKernelGGL((budget_select_kernel<ITEMS, D>), dim3(rows), dim3(kBudgetBlock), (budget_lds<ITEMS, D>()), st, \
+                           scores, P, idx, P, w, update, gather, plan);                                         \
     } while (0)
-    if (P <= 1024) GKV_BUDGET(1);   // (the filter route, whose rows may be redone, starts at 2048)
+    if (P <= 1024) GKV_BUDGET(1);
     else if (P <= 2048) GKV_BUDGET(2);
     else if (P <= 4096) GKV_BUDGET(4);
     else if (P <= 8192) GKV_BUDGET(8);
