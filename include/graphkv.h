@@ -19,7 +19,8 @@
  *     the default stream).  Inputs are read-only unless stated otherwise.
  *   - `ws` is scratch memory of at least graphkv_workspace_bytes(params) bytes,
  *     256-byte aligned; its contents are undefined before and after a call.
- *     Two calls that overlap in time need two workspaces.
+ *     Two calls that overlap in time need two workspaces.  (graphkv_select does
+ *     without, see there; graphkv_score_knorm uses none.)
  *   - Return value: GRAPHKV_OK (0) or a negative code.  Arguments are checked
  *     on the host before anything is enqueued: on GRAPHKV_EINVAL or
  *     GRAPHKV_EWORKSPACE nothing has run.  GRAPHKV_EHIP reports a failed
@@ -179,7 +180,14 @@ int32_t graphkv_propagate_edges(const graphkv_params *p, const void *Ac, const v
  * the window tokens P..N-1.
  *   scores [H_kv, P]  in   fp32
  *   idx    [H_kv, B]  out  int32
+ * `ws` is optional and changes nothing but the time.  Few rows of more than 32768
+ * entries are shared out to many workgroups where it is there, 256-byte aligned and
+ * of at least graphkv_select_workspace_bytes() bytes (0: none is used; never more
+ * than graphkv_workspace_bytes()); NULL, or a smaller or misaligned one, is no error:
+ * a workgroup takes each row.  Used or not, calls that overlap in time must not share
+ * one.
  */
+size_t graphkv_select_workspace_bytes(const graphkv_params *p);
 int32_t graphkv_select(const graphkv_params *p, const float *scores, int32_t *idx,
                        void *ws, size_t ws_bytes, void *stream);
 

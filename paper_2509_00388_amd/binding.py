@@ -28,7 +28,7 @@ EXPORTS = ("graphkv_workspace_bytes", "graphkv_score", "graphkv_score_knorm", "g
            "graphkv_select", "graphkv_compress", "graphkv_strerror", "graphkv_uses_mfma",
            "graphkv_profile_begin", "graphkv_profile_end", "graphkv_kernel_name",
            "graphkv_workspace_bytes_batched", "graphkv_compress_batched", "graphkv_propagate_edges",
-           "graphkv_compress_static")
+           "graphkv_compress_static", "graphkv_select_workspace_bytes")
 STATIC_SCRATCH_BYTES = 64 << 20
 N_KERNELS = 23
 
@@ -254,7 +254,8 @@ def graphkv_propagate_edges(p: Params, Ac, Bc, scores, dbg_src=None, dbg_nbr=Non
 
 
 def graphkv_select(p: Params, scores, idx=None, ws=None):
-    """idx [H_kv, B] int32.  Stage IV, selection."""
+    """idx [H_kv, B] int32.  Stage IV, selection.  Rows of more than 32768 entries: without `ws` scratch memory is
+    allocated (graphkv_select_workspace_bytes(); a smaller one, an empty one too, is taken and costs time only)."""
     if idx is None:
         idx = torch.empty((p.n_kv_heads, p.budget), dtype=torch.int32, device=scores.device)
     cp = p.c()

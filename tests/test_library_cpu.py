@@ -3,6 +3,8 @@ header declares, and rejects bad arguments on the host before touching a GPU."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -33,6 +35,30 @@ def test_exports_match_header(lib):
     assert declared == set(gk.EXPORTS)
     for name in declared:
         assert hasattr(lib, name), name
+
+
+def test_header_declares_every_exported_symbol(lib):
+    nm = shutil.which("nm")
+    if nm is None:
+        pytest.skip("no nm")
+    out = subprocess.run([nm, "-D", "--defined-only", gk.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    exported = set(re.findall(r"\bT (graphkv_[a-z_]+)$", out, re.M))
+    assert exported == set(gk.EXPORTS)
+
+
+def test_select_workspace_is_part_of_the_general_one(lib):
+    """What graphkv_select can use never exceeds what any call of these params may ask for; rows that one workgroup
+    holds, rows without a bitmap and many rows use none."""
+    used = 0
+    for H in (1, 8, 40, 64, 200):
+        for P in (1000, 32768, 32769, 40961, 131072, 1 << 18, (1 << 18) + 1):
+            p = good_params(n_kv_heads=H, n_q_heads=H, n_tokens=P + 32)
+            need = lib.graphkv_select_workspace_bytes(ctypes.byref(p.c()))
+            assert need <= gk.graphkv_workspace_bytes(p)
+            assert need == 0 or 32768 < P <= 1 << 18
+            used += need > 0
+    assert used >= 10
+    assert lib.graphkv_select_workspace_bytes(ctypes.byref(good_params(head_dim=12).c())) == 0
 
 
 def test_params_struct_layout_matches_header():
