@@ -71,38 +71,59 @@ def test_long_rows_shared_out_in_a_whole_pass():
         assert (i1[:, :B - w] == ref).float().mean() > 0.99
 
 
-@pytest.mark.parametrize("N,S,m,signal", [(8300, 64, 32, 0), (8224, 40, 90, 0), (9000, 64, 16, 1), (16416, 20, 200, 2)])
-def test_redone_heads_in_few_and_in_many(N, S, m, signal):
-    """Three rounds over layers in which a head's candidate lists overflow (runs of similar keys) and one's do not: few
-    heads take a round's late lists in one launch, many in three, and with both the heads that are redone are gone
-    on with by the workgroup that finishes their last row (m = 90 and 200: more triples than a kernel takes along,
-    or lists that the general selection makes)."""
-    say(f"redone heads, few and many N={N} S={S} m={m} signal={signal}")
+# (an update of up to 4096 triples rides along with the next selection, a larger one does not; more than 256 sources are
+# matched in a launch of their own; 300 neighbours are more than the quick selection of a redone row takes)
+@pytest.mark.parametrize("N,S,m,signal", [(8300, 64, 32, 0), (8224, 40, 90, 0), (9000, 64, 16, 1), (16416, 20, 200, 2),
+                                          (8300, 64, 80, 0), (8300, 300, 8, 2), (33100, 8, 300, 0), (33100, 16, 24, 0)])
+@pytest.mark.parametrize("T", [1, 3])
+def test_redone_heads_in_few_and_in_many(N, S, m, signal, T):
+    """Layers in which one head's candidate lists overflow for certain: half of its keys are one vector, of the lowest
+    norm, so that they are the sources and every list has thousands of equal edges.  Which nodes it keeps is known:
+    the sources' neighbours are the m lowest of those nodes (m + 1 with the sources that are among them), and what
+    is left of them, lowest first, is best.  The same with the head's layer alone, and for the other heads."""
+    say(f"redone heads, few and many N={N} S={S} m={m} signal={signal} T={T}")
     L, H, d, w, B = 40, 3, 128, 32, 300
-    g = torch.Generator("cuda").manual_seed(N)
+    P = N - w
+    g = torch.Generator("cuda").manual_seed(N + S)
     K = torch.randn(L, H, N, d, generator=g, device="cuda")
-    run = 900
-    centre = torch.randn(L, -(-N // run), d, generator=g, device="cuda")
-    K[:, 1] = centre.repeat_interleave(run, dim=1)[:, :N] + 0.7 * K[:, 1]
+    same = torch.rand(L, P, generator=g, device="cuda") < 0.5
+    same[:, 0] = True
+    K[:, 1, :P] = torch.where(same[..., None], 0.25 * K[:, 1, :1], K[:, 1, :P])
     kind = torch.randint(0, 64, (L, N), generator=g, device="cuda")
     K[:, 2] = 0.4 * K[:, 2] + torch.randn(L, 64, d, generator=g, device="cuda").gather(1, kind[..., None].expand(-1, -1, d))
     K = K.to(torch.bfloat16)
     V = torch.randn(L, H, N, d, generator=g, device="cuda").to(torch.bfloat16)
     p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=N, window=w, budget=B, n_sources=S, n_neighbors=m,
-                  rounds=3, signal=signal, scorer=gk.SCORER_KNORM)
-    sc = torch.empty(L, H, N - w, device="cuda")
-    Ks, Vs, idx = gk.graphkv_compress_batched(p, L, None, K, V, None, scores_out=sc)
+                  rounds=T, signal=signal, scorer=gk.SCORER_KNORM)
+
+    def batch(K):
+        sc = torch.empty(L, H, P, device="cuda")
+        gk.graphkv_profile_begin()
+        out = gk.graphkv_compress_batched(p, L, None, K, V, None, scores_out=sc)
+        torch.cuda.synchronize()
+        return out, sc, gk.graphkv_profile_end()["redo_rows"]
+
+    plain = K[:, :1].expand(-1, H, -1, -1).contiguous()
+    batch(plain)
+    nothing = batch(plain)[2]
+    (Ks, Vs, idx), sc, redone = batch(K)
+    assert redone[1] == nothing[1] == T and redone[0] > 4 * nothing[0], (redone, nothing)
     generic = gk.Params(**{**p.__dict__, "impl": gk.IMPL_GENERIC})
     for l in (0, 7, L - 1):
-        s1, s2 = (torch.empty(H, N - w, device="cuda") for _ in range(2))
+        s1, s2 = (torch.empty(H, P, device="cuda") for _ in range(2))
         K1, V1, i1 = gk.graphkv_compress(p, K[l], V[l], None, scores_out=s1)
         at = slice(l * H * B, (l + 1) * H * B)
         assert torch.equal(i1.flatten(), idx[at]) and torch.equal(s1, sc[l])
         assert torch.equal(K1.view(-1, d).view(torch.int16), Ks[at].view(torch.int16))
+        if signal != 1:   # (an enhanced signal keeps the neighbours instead)
+            left = same[l].nonzero().flatten()[m + 1:]
+            assert torch.equal(i1[1, :B - w].long(), left[:B - w])
+            assert torch.equal(V1[1, :B - w].view(torch.int16), V[l, 1][left[:B - w]].view(torch.int16))
         # the scalar kernels, whose edges round otherwise: the same nodes but for near-ties
         _, _, i2 = gk.graphkv_compress(generic, K[l], V[l], None, scores_out=s2)
-        assert (i1 == i2).float().mean() > 0.95
-        assert torch.isclose(s1, s2, rtol=1e-3, atol=0.0).float().mean() > 0.95   # (evicted nodes: equal infinities)
+        for h in range(H):
+            assert len(set(i1[h].tolist()) ^ set(i2[h].tolist())) <= 4, f"layer {l} head {h}"
+        assert torch.isclose(s1, s2, rtol=1e-3, atol=0.0).float().mean() > 0.99   # (evicted nodes: equal infinities)
 
 
 # (rows of 16 bytes, of exactly 128, of a little more, of exactly 256, of several pieces and a rest)
