@@ -230,9 +230,14 @@ __device__ __forceinline__ void update_row(float (&val)[ITEMS], const Triples<D>
         for (int q = 0; q < D; ++q) edge[q * BLOCK + tid] = e[q];
     }
     __syncthreads();
+    // (The chains end, and are multiplied out, at the thread that links last.  All threads' first triples go first, then
+    // the second ones and so on: the ends of long chains are then one to a thread and not several, one behind another.
+    // 152 nodes with 20 factors each, update and selection: 45 us without the barriers, 31 with them.)
 #pragma unroll
-    for (int q = 0; q < D; ++q)
+    for (int q = 0; q < D; ++q) {
+        if (q > 0) __syncthreads();
         link[q] = q * BLOCK + tid < u.count ? atomicExch(&cell[node[q]], (uint32_t)(q * BLOCK + tid)) : kChainEnd;
+    }
 #pragma unroll
     for (int q = 0; q < D; ++q) next[q * BLOCK + tid] = (uint16_t)link[q];
     __syncthreads();

@@ -213,3 +213,31 @@ def test_new_lists_of_later_rounds_cost_no_more_than_the_first(H, N, S, scorer):
         later = min(later, ms("cosine_bound_new", "cosine_filter_new", "nbr_select_later") / (T - 1))
     say(f"  first round {first:.3f} ms, a later one {later:.3f} ms")
     assert later < 1.5 * first + 0.01
+
+
+@pytest.mark.parametrize("P,S,m", [(152, 152, 20), (300, 100, 40), (900, 128, 30)])
+def test_update_in_front_of_the_selection_takes_long_chains(P, S, m):
+    """Few nodes that many sources reach, up to 4096 triples: the update that the final selection does first takes
+    no longer than the update and the selection of their own (and a fifth more for what a clock shows; with the ends
+    of the chains several to a thread it took half as much again)."""
+    say(f"long chains P={P} S={S} m={m}")
+    H, w, d = 4, 32, 128
+    g = torch.Generator("cuda").manual_seed(P)
+    K = torch.randn(H, P + w, d, generator=g, device="cuda").to(torch.bfloat16)
+    p = gk.Params(n_kv_heads=H, n_q_heads=H, head_dim=d, n_tokens=P + w, window=w, budget=w + P // 2, n_sources=S, n_neighbors=m,
+                  rounds=1, scorer=gk.SCORER_KNORM)
+    s = gk.graphkv_score_knorm(p, K)
+    both = update = select = np.inf
+    for _ in range(6):
+        gk.graphkv_profile_begin()
+        kept = gk.graphkv_compress(p, K, K, None)[2]
+        torch.cuda.synchronize()
+        both = min(both, gk.graphkv_profile_end()["topk_final"][0])
+        gk.graphkv_profile_begin()
+        alone = gk.graphkv_select(p, gk.graphkv_propagate(p, K, s.clone()))
+        torch.cuda.synchronize()
+        took = gk.graphkv_profile_end()
+        update, select = min(update, took["decay"][0]), min(select, took["topk_final"][0])
+    say(f"  together {1e3 * both:.1f} us, update {1e3 * update:.1f}, selection {1e3 * select:.1f}")
+    assert torch.equal(kept, alone)
+    assert both < 1.2 * (update + select)
