@@ -694,8 +694,7 @@ int32_t graphkv_select(const graphkv_params *p, const float *scores, int32_t *id
     void *sel = need && check_ws(need, ws, ws_bytes) == GRAPHKV_OK ? ws : nullptr;
     // (no update rides along: the scores are only read)
     return run_select(D, make_plan(p, 1, nullptr, nullptr), const_cast<float *>(scores), idx, DecayArgs{}, GatherArgs{},
-                      sel,
-                      (hipStream_t)stream);
+                      sel, (hipStream_t)stream);
 }
 
 size_t graphkv_select_workspace_bytes(const graphkv_params *p)

@@ -391,7 +391,7 @@ __device__ __forceinline__ void row_sweep(const float *__restrict__ xr, int n, i
 // twice.  (A group bound through LDS maxima, a radix sweep and one wave that finished the row
 // alone, bit by bit: 21.4 us with k = 96 and 16.4 us with k = 64 for 8 rows of 32736 entries;
 // this way 9.8 and 8.2 us, 7.7 and 6.2 since floats are compared and several threads share
-// an entry's rank; 256 rows of 131008 entries with k = 192 and k = 128: 72 and 58 us before, 56 and 49 us now.)
+// an entry's rank; 256 rows of 131008 entries with k = 192: 72 us before, 49 us now.)
 //
 // The same code takes the m best edges of a source from its row of the dense edge block (Eq. 3): 256
 // threads per row of up to 8192 edges, no split, the edges' values beside their indices.  (Three LDS
@@ -667,10 +667,11 @@ struct RedoArgs {
 // Row `item` (head * S + source slot): its edges to the workgroup's scratch row, its m best to the lists.  mem: kRedoLds
 // bytes.  Begins with a barrier.  A wave takes 32 keys at a time, fetched whole rows at a time and turned into operand
 // layout in its own part of the LDS (operand layout straight from memory touches every line four times, and the waves'
-// lines do not fit the first-level cache).  (Key norms, clustered keys, two rounds, whole calls, us, the fetch in operand
-// layout and a radix selection from the LDS / this way / this way with the general selection, in front of the kernel
-// that takes the update along and without a launch of its own: 8 heads of 32736 keys 460 / 294 / 338, 64 heads of 16352
-// 526 / 438 / 490, 256 heads of 32736 9000 / 4895 / 8300; 8 heads of 16 K keys with nothing to redo 120.0 / 105.0 / 104.3.)
+// lines do not fit the first-level cache).  Whole calls, us, operand layout from memory and a radix selection / this way:
+// 64 heads x 64 rows of 10000 keys 1438 / 770; key norms, clustered keys, two rounds: 8 heads of 32736 keys 460 / 294,
+// 64 of 16352 526 / 438, 256 of 32736 9000 / 4895.  (The same in front of the kernel that takes the update along, with the
+// general selection, which needs no more registers, and without a launch of its own: 338, 490 and 8300, and 104.3 instead
+// of 105.4 for 8 heads of 16K keys with nothing to redo.)
 __device__ __forceinline__ void redo_row(const RedoArgs &a, long item, unsigned char *mem)
 {
     const int tid = here(threadIdx.x), lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5, h = (int)(item / a.S);
@@ -766,8 +767,7 @@ __global__ __launch_bounds__(kPickBlock) void pick_sources_kernel(
 }
 
 // A later round's sources and, in the same workgroup, the update of the round before and where the
-// sources' lists come from (launches of their own cost 7.7 and 6.1 us with 8 heads; a launch is 4.6 us
-// before it does anything).  The lists that the update reads are those that the match hands on.  (8 heads with 2048
+// sources' lists come from (launches of their own cost 7.7 and 6.1 us with 8 heads).  The lists that the update reads are those that the match hands on.  (8 heads with 2048
 // triples: 19.4 us for 32736 nodes and 17.0 for 15969 with the row read behind the update and the lists read again;
 // 16.6 and 12.7 this way.)
 template <int ITEMS, int D>
@@ -1515,8 +1515,8 @@ size_t topk_final_scratch_bytes(int rows, int P)
 }
 
 // Few enough bytes of a head's retained rows for its workgroup (whole passes, us, a launch of its own / in the
-// selection: 4 heads x 64 rows of 256 bytes 34.2 / 31.9, 8 heads x 256 19.9 / 16.2 with key norms; 8 heads x 512 rows
-// 44.9 / 47.9).
+// selection: 4 heads x 64 rows of 256 bytes 34.2 / 31.9, 8 heads x 256 19.9 / 16.2 with key norms and 54.7 / 55.3 with
+// two rounds, 256 heads x 256 305.5 / 302.6, 1024 x 256 1019 / 1014; 8 heads x 512 rows 44.9 / 47.9).
 bool topk_final_gathers(int P, int max_budget, int row_bytes) { return P <= 32768 && (long)max_budget * row_bytes <= (64 << 10); }
 
 hipError_t launch_topk_final(float *scores, int P, int rows, const LayerPlan &plan, int w, int32_t *idx,
