@@ -209,8 +209,8 @@ Workspace carve(const graphkv_params *p, const Dims &D)
     const size_t frows = D.filter ? (size_t)D.H * g.pitch : 0;   // rows of the per-row buffers
     W.tau = take(frows * 4);
     W.bound_hist = take(D.filter ? mfma_bound_scratch_bytes(D.H, D.P, g) : 0);
-    W.cand = take(frows * g.chunks * g.slice_cap * 8);
-    W.cand_cnt = take(frows * g.chunks * 4);
+    W.cand = take(frows * g.row_slots * 8);
+    W.cand_cnt = take(frows * g.chunk_slots * 4);
     W.overflow = take((size_t)D.H * 4);
     const bool keep = D.keep;
     W.src_b = take(keep ? (size_t)D.H * D.S * 4 : 0);

@@ -14,6 +14,14 @@ namespace gkv {
 // several host threads at once.  Returns false if the opt-in failed.
 bool allow_big_lds(const void *kernel, int bytes = 160 * 1024 - 8192);
 
+// Whether a call's keys are too many for a pass over them to leave behind what the next pass could find in the 256 MiB
+// of the memory-side cache: then they are loaded (and large outputs stored) without a claim to a place in the caches,
+// which leaves the L2 to lists that are written a few bytes at a time.  (Whole pass, us, with a claim / without: heads
+// of 32K keys, 8 of them (64 MiB) 144 / 150, 24 260 / 274, 32 278 / 279, 48 417 / 398, 64 468 / 431, 128 840 / 755; key
+// norms of 8000 keys, 64 heads (125 MiB) 121 / 125, 128 193 / 190, 256 372 / 325; one score call of 128 MiB 103 / 117, of
+// 256 MiB 103 / 117, of 384 MiB 177 / 179.)
+inline bool reads_past_caches(size_t key_bytes) { return key_bytes > (size_t)256 << 20; }
+
 // ---- selection (select.hip) -------------------------------------------------
 // For each of `rows` rows of x (row r starts at x + r*ld, n entries): the k entries that come first
 // by (value descending, index ascending), written in ascending index order to idx_out + r*idx_ld
@@ -161,6 +169,8 @@ struct MfmaFilterPlan {
     int chunk_cols;   // keys per workgroup of the filter pass
     int chunks;       // workgroups (= candidate slices) per head and source group
     int slice_cap;    // entries per (row, chunk) slice
+    int chunk_slots;  // slice sizes a row has room for (cand_cnt)
+    long row_slots;   // entries a row has room for (cand), at least chunks * slice_cap
     int cand_cap;     // entries the exact select can take per row
 };
 // short_slices: no more memory for candidates than keys in no particular order need.

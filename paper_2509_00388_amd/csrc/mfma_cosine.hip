@@ -2,10 +2,11 @@
 // prefix key (bf16 inputs, d = 128, fp32 accumulation), and each source's m
 // largest edges without ever storing the S x P edge block.
 //
-// Up to 96 source rows (three 32-row MFMA blocks, one per row group of waves) are
-// held in registers; keys stream from HBM through LDS tiles into MFMA operand
-// registers, as in the scoring kernels.  The squared norm of each streamed key is
-// accumulated from the very registers that feed the MFMA, so the keys are read once.
+// Up to 96 source rows (three 32-row MFMA blocks) are held in registers; keys stream
+// from HBM through the LDS into MFMA operand registers, in tiles that a workgroup
+// shares as in the scoring kernels, or (the filter pass) in blocks of a wave's own.  The
+// squared norm of each streamed key is accumulated from the very registers that feed
+// the MFMA, so the keys are read once.
 //
 // Neighbourhoods in one streaming pass:
 //   1. a first pass over an evenly strided sample of the keys (every 8th) counts
@@ -15,7 +16,7 @@
 //      a subset's m-th largest can only be smaller, but lets 8 m keys through
 //      where r lets 8 r);
 //   2. the streaming pass keeps only the edges that reach the bound (a couple of
-//      hundred per source), staged in LDS and appended to per-source lists;
+//      hundred per source), parked in LDS and appended to per-source lists;
 //   3. an exact (value desc, index asc) top-m over each short list -- exact whenever
 //      the list holds m entries or more, since it then holds every edge that is at
 //      least the bound and the m largest are among those.
@@ -55,7 +56,6 @@ struct FilterArgs {
     int32_t *cand_cnt;     // [Hkv, pitch, chunks] entries in each slice
     int32_t *overflow;     // [Hkv]
     int slice_cap;
-    int drain_every;       // tiles between two scheduled drains of the rings
     int sgroups;           // workgroups (groups of source rows) per key chunk
     int src_pitch;         // entries per head of the source list
     int pitch, row0;
@@ -322,71 +322,113 @@ __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__rest
     bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + row0 + slot]);
 }
 
-// Filter pass over all keys.  A lane holds, per key block, the 16 dots of its key
-// with 16 of the wave's sources.  It tests them all at once against the sources'
-// bounds (dot >= bound_i * |k_j|, bounds a hair lowered so that rounding can never
-// lose an edge) with 16 fused multiply-adds and a max tree; the few lanes that
-// have a hit park their 16 dots, the key's squared norm and the key index in an
-// LDS ring.  Every half-wave has a ring of its own and positions are a prefix
-// count over the hit lanes, so parking needs no atomic and waits for nothing.
-// Every few tiles (a schedule the host derives from the expected hit rate, so
-// that most of a half-wave's 32 lanes get a row) all waves drain their rings at
-// the same time -- a drain is a chain of LDS round trips, and a wave that drains
-// alone would keep the others waiting at the tile barrier.  A half-wave
-// drains its own ring, so the 16 sources of a parked row are the draining lane's
-// own 16 sources and their bounds sit in registers: the same test picks the row's
-// hits, their dots become exact edges (the dense kernel's formula, bit for bit),
-// and they are appended to the workgroup's own slice of each source's global
-// candidate list (one slice per key chunk, so no workgroup ever waits for
-// another: positions come from LDS counters).  A ring holds RING rows (64 with two
-// row groups per workgroup, 32 with three: the rings share the LDS with the key
-// tiles); before a tile's rows are parked a wave drains on its own if a ring could
-// not take them.  The source's own column may be among the candidates:
-// the exact select drops it.  If a slice (or one of the short LDS lists that take
-// a row's hits beyond its fourth) overflows, the head's overflow flag is raised and
-// the head is redone exactly, row by row.
-constexpr int kStagePitch = 80;    // bytes per parked row: 16 dots, |k|^2, key (72, padded)
-constexpr int kLaterCap = 128;     // entries of each of the two LDS lists of hits beyond a row's fourth
+// Filter pass over all keys, barrier-free: a wave holds all source rows of its workgroup (SB groups of 32) in
+// registers and takes key blocks of 32 on its own, copying each through a piece of LDS that nobody else touches.
+// The loads of its next block are in flight while it works on one; the eight waves of a workgroup share nothing
+// but the candidate counters, so that one wave's matrix instructions run beside another's vector work and LDS
+// round trips, and the key norms are formed once per key and not once per row group.  (Tiles of 128 keys shared
+// by twelve waves behind a barrier each, a wave per stream and row group: the waves loaded, multiplied, tested
+// and parked in step, 1.6 us per tile of 96 rows whatever bound the call.  256 heads x 96 rows x 32736 keys 467 -> 370 us
+// with the keys kept out of the caches, 362 without a hit; x 192 rows x 131008 keys 3290 -> 2430, where the matrix
+// core is busy 37 % of the time at 1.7 GHz, or 53 % at the 1.46 GHz that the chip sustains without a hit, 2000.  A
+// second set of accumulators, or the drain behind the next block's loads, made no difference.)
+//
+// A lane holds, per key block and group, the 16 dots of its key with 16 sources.  Whether one of them may reach
+// its bound is tested by the matrix core too: one more instruction adds -det_i |k_j| to the dots (det_i: what
+// dot / |k_j| must reach), both factors as a sum of two bf16 numbers (error below 2^-17 of the product), with the
+// bounds lowered by more than that; then the largest of the 16 results, compared as integers, has no sign bit
+// where there may be a hit.  That is 8 vector instructions instead of 31 per block and group.  The few lanes with
+// a possible hit park their 16 dots, the key's squared norm, the key index and the group in an LDS ring.  Every
+// half-wave has a ring of its own and positions are a prefix count over the hit lanes, so parking needs no atomic.
+// Once a ring holds 32 rows the wave drains both, one row per lane: the test is repeated in 32-bit floats with
+// the bounds from LDS, the hits' dots become exact edges (the dense kernel's formula, bit for bit), and they are
+// appended to the workgroup's own slice of each source's global candidate list (one slice per key chunk, positions
+// from LDS counters, so no workgroup ever waits for another).  The source's own column may be among the
+// candidates: the exact select drops it.  If a slice overflows, the head's overflow flag is raised and the head is
+// redone exactly, row by row.
+constexpr int kStagePitch = 80;    // bytes per parked row: 16 dots, |k|^2, key, first row of the group (76, padded)
+constexpr int kRing = 64;          // rows of a ring: up to 31 waiting and a group's 32
+constexpr int kFilterWaves = 8;    // two per SIMD: 256 registers each
+constexpr int kBlkBytes = kBlk * kPitch;
+constexpr int kFilterLdsBytes = kFilterWaves * (kBlkBytes + 2 * kRing * kStagePitch);
 
 template <int SB> struct FilterLds {
     static constexpr int ROWS = SB * kBlk;
-    float inv_s[ROWS], det_s[ROWS];
+    float inv_s[ROWS];
+    __align__(16) float det_s[ROWS];
+    __align__(16) uint4 test_s[2][ROWS];   // the source's operand of the test: what each half-wave holds
     int32_t idx_s[ROWS];
     int32_t row_pos[ROWS];     // entries written to each source's slice
     int32_t idle_pos[kWave];   // takes the additions of 0 of hits that are not there
-    // (edge bits, key, source row) of the hits beyond a row's fourth: one list for even and one
-    // for odd drain periods, each emptied right after the barrier that ends its period
-    __align__(16) uint4 later[2][kLaterCap];
-    int32_t n_later[2], later_lost;   // entries ever listed (never reset)
 };
 
-// One chunk of head h's keys against source rows s_base .. of the Sh in use; smem: two key tiles, then the rings.
-// tau_of(r): bound of row s_base + r.
-template <int SB, int RING, typename TauOf>
+// x as a sum of two bf16 numbers, (rounded x, rounded rest) as a pair in one register.
+__device__ __forceinline__ uint32_t two_bf16(float x)
+{
+    const __bf16 hi = (__bf16)x;
+    const bf16x2 r = {hi, (__bf16)(x - (float)hi)};
+    return __builtin_bit_cast(uint32_t, r);
+}
+
+// One chunk of head h's keys against source rows s_base .. of the Sh in use; smem: kFilterLdsBytes.
+// tau_of(r): bound of row s_base + r.  ONCE: no other workgroup reads these keys, so they need not stay in the L2;
+// the candidate lists' lines then do until they are full (256 heads of 32768 keys 468 -> 384 us, 390 without the
+// lists' stores; where a second
+// workgroup finds the keys there, 128 sources and 131072 keys, 2.45 -> 2.84 ms).
+template <int SB, bool ONCE, typename TauOf>
 __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t *Kc, int N, int n_cols, const int32_t *src,
                                              int chunk_cols, const FilterArgs &fa, int h, int chunk, int n_chunks, int Sh,
                                              int s_base, FilterLds<SB> &F, unsigned char *smem, int tid, TauOf &&tau_of)
 {
-    constexpr int ROWS = SB * kBlk, NT = 256 * SB;
-    static_assert(RING == 32 || RING == 64, "a ring takes a tile's 32 rows and is indexed with a mask");
-    float *inv_s = F.inv_s, *det_s = F.det_s;
-    int32_t *idx_s = F.idx_s, *row_pos = F.row_pos, *idle_pos = F.idle_pos, *n_later = F.n_later;
-    int32_t &later_lost = F.later_lost;
-    auto &later = F.later;
-    unsigned char *kt = smem;
-    unsigned char *stage_mem = smem + 2 * kTileBytes;
-
-    const int lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
-    const int stream = wv & 3, grp = wv >> 2;
+    constexpr int ROWS = SB * kBlk, NW = kFilterWaves;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hh = lane >> 5;
     const uint16_t *Kh = Kc + (long)h * N * kD;
     const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
     const long buf_row0 = (long)h * fa.pitch + fa.row0 + s_base;   // this workgroup's first row of the per-row buffers
+    const int nblk = (c1 - c0 + kBlk - 1) / kBlk;
+    const int groups = min(SB, (Sh - s_base + kBlk - 1) / kBlk);   // row groups with sources
 
-    bf16x8 q[kSteps];
-    load_sources(Ac + (long)h * N * kD, src + (long)h * fa.src_pitch, Sh, s_base, grp, stream, l32, hh, q, inv_s, idx_s);
-    if (tid < ROWS) row_pos[tid] = 0;
-    if (tid < 2) n_later[tid] = 0;
-    if (tid == 0) later_lost = 0;
+    // Block b, whole: the last one of a head starts early where the head's rows end (N >= 32), so that every load
+    // is in bounds, and the keys in front of its own are left out below.
+    auto block_first = [&](int b) { return min(c0 + kBlk * b, N - kBlk); };
+    u32x4 stage[8];   // 1 KiB of consecutive keys per load
+    auto load_block = [&](int b) {
+        const u32x4 *p = reinterpret_cast<const u32x4 *>(Kh + (long)block_first(b) * kD);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) stage[u] = ONCE ? __builtin_nontemporal_load(p + 64 * u + lane) : p[64 * u + lane];
+    };
+    load_block(min(wv, nblk - 1));
+
+    // The source rows pass through the LDS once for all waves (slots beyond Sh repeat the last source): read straight
+    // into operand layout by every wave they take 192 loads of 32 rows each, about 1.5 us of the start.
+    bf16x8 q[SB][kSteps];
+    {
+        const uint16_t *Ah = Ac + (long)h * N * kD;
+        const int32_t *src_h = src + (long)h * fa.src_pitch;
+        constexpr int PER = ROWS * 16 / (64 * NW);   // 16-byte pieces per thread
+        u32x4 piece[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + 64 * NW * u;
+            const int32_t i = src_h[min(s_base + (at >> 4), Sh - 1)];
+            piece[u] = *reinterpret_cast<const u32x4 *>(Ah + (long)i * kD + 8 * (at & 15));
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + 64 * NW * u;
+            *reinterpret_cast<u32x4 *>(smem + (at >> 4) * kPitch + (at & 15) * 16) = piece[u];
+        }
+        if (tid < ROWS) F.row_pos[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < SB; ++g) {
+            tile_read(smem, g, l32, hh, q[g]);
+            if (wv == g) {
+                const float inv = inv_norm(add_other_half(half_row_sumsq(q[g])));
+                if (hh == 0) F.inv_s[kBlk * g + l32] = inv;
+            }
+        }
+    }
     __syncthreads();
     if (tid < ROWS) {
         // det: what dot / |k_j| must reach for the edge to be listed, i.e. the source's bound,
@@ -395,17 +437,26 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
         const int slot = s_base + tid;
         const float t = tau_of(min(tid, Sh - 1 - s_base));
         const float slack = 4e-6f + 1e-5f * fabsf(t);
-        const float inv = inv_s[tid];
+        const float inv = F.inv_s[tid];
         const float lo2 = t - 2.f * slack;
-        det_s[tid] = slot >= Sh ? INFINITY : (inv > 0.f ? lo2 / inv : (lo2 <= 0.f ? -INFINITY : INFINITY));
+        const float det = slot >= Sh ? INFINITY : (inv > 0.f ? lo2 / inv : (lo2 <= 0.f ? -INFINITY : INFINITY));
+        F.det_s[tid] = det;
+        // The matrix core's test lets through whatever the one with det does: det lowered by more than the error of
+        // the two-piece product, a constant for products that underflow, everything where det is beyond all dots
+        // from below; the upper limit keeps the pieces' products finite.
+        const float most = 1.15292150e18f;   // 2^60
+        const float low = det > most ? most : det - 2e-5f * fabsf(det);
+        const bool all = !(low >= -most);
+        const uint32_t pieces = all ? 0u : two_bf16(low);
+        const uint32_t hi = pieces & 0xffffu, lo = pieces >> 16;
+        const uint32_t extra = all ? 0x7f80u : 0x0da2u;   // +inf / 1e-30
+        F.test_s[0][tid] = make_uint4(hi | (hi << 16), lo | (lo << 16), extra, 0u);
+        F.test_s[1][tid] = make_uint4(0u, 0u, 0u, 0u);   // (not the same again: infinity times 0 is none)
     }
     __syncthreads();
-    // this lane's 16 sources: row acc_row(i, hh) of row group grp
-    float det[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) det[i] = det_s[kBlk * grp + acc_row(i, hh)];
 
-    unsigned char *ring = stage_mem + (2 * wv + hh) * (RING * kStagePitch);
+    unsigned char *mine = smem + wv * (kBlkBytes + 2 * kRing * kStagePitch);   // this wave's block, then its two rings
+    unsigned char *ring = mine + kBlkBytes + hh * (kRing * kStagePitch);
     const uint64_t half_before = (hh ? 0xffffffff00000000ull : 0x00000000ffffffffull) & ((1ull << lane) - 1ull);
     uint2 *slice0 = fa.cand + (buf_row0 * n_chunks + chunk) * fa.slice_cap;
     const long slice_row_stride = (long)n_chunks * fa.slice_cap;
@@ -413,32 +464,33 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     int tail0 = 0, tail1 = 0, head0 = 0, head1 = 0;
 
     // Each half-wave turns up to 32 waiting rows of its ring into list entries, one per lane.
-    // No loop in here holds a global store: after such a loop the compiler can no longer
-    // count the memory operations in flight and would make the next LDS store of a key tile
-    // wait for every outstanding prefetch.  A row's first four hits are stored by straight-
-    // line code; further ones (keys that are close to many sources at once) go to the LDS
-    // list of the current tile's parity.
-    auto drain = [&](int par) {
+    auto drain = [&] {
         const int n0 = min(tail0 - head0, kBlk), n1 = min(tail1 - head1, kBlk);
+        wave_sync();
         if (l32 < (hh ? n1 : n0)) {
-            const unsigned char *row_mem = ring + (((hh ? head1 : head0) + l32) & (RING - 1)) * kStagePitch;
+            const unsigned char *row_mem = ring + (((hh ? head1 : head0) + l32) & (kRing - 1)) * kStagePitch;
             const float4 *vals = reinterpret_cast<const float4 *>(row_mem);
-            const float2 extra = *reinterpret_cast<const float2 *>(row_mem + 64);   // |k|^2, key
+            const float4 extra = vals[4];   // |k|^2, key, group
             const float inv_k = inv_norm(extra.x);   // the dense kernel's formula
             const float norm_k = __builtin_amdgcn_sqrtf(extra.x);
             const uint32_t key = __float_as_uint(extra.y);
-            // the test that parked the row, source by source: bit i of `hits` = (dot_i - det_i |k|
-            // is not negative), gathered from the sign bits, source 15 first
+            const int row0 = (__float_as_int(extra.z) & ~(kBlk - 1)) + 4 * hh;   // row of dot 0 (a multiple of 4)
+            // bit i of `hits` = (dot_i - det_i |k| is not negative), gathered from the sign bits, source 15 first;
+            // none unless one of them is a number that is not negative (not NaN: a key with an infinity)
             uint32_t neg = 0;
+            float best = -INFINITY;
 #pragma unroll
             for (int v = 3; v >= 0; --v) {
-                const float4 dv = vals[v];
-                const float d4[4] = {dv.x, dv.y, dv.z, dv.w};
+                const float4 dv = vals[v], tv = *reinterpret_cast<const float4 *>(&F.det_s[row0 + 8 * v]);
+                const float d4[4] = {dv.x, dv.y, dv.z, dv.w}, t4[4] = {tv.x, tv.y, tv.z, tv.w};
 #pragma unroll
-                for (int u = 3; u >= 0; --u)
-                    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(fmaf(-det[4 * v + u], norm_k, d4[u])), 31);
+                for (int u = 3; u >= 0; --u) {
+                    const float d = fmaf(-t4[u], norm_k, d4[u]);
+                    best = fmaxf(best, d);
+                    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(d), 31);
+                }
             }
-            uint32_t hits = ~neg & 0xffffu;
+            uint32_t hits = best >= 0.f ? ~neg & 0xffffu : 0u;
             // The row's first four hits without a branch, so that their LDS reads and list
             // positions are asked for together and waited for once: a hit that is not there
             // reads dot 0 and adds 0 to a counter nobody reads (one per lane).
@@ -452,10 +504,10 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
                 const int i = valid ? __ffs(hits) - 1 : 0;
                 hits &= hits - 1;
                 validk |= valid ? 1u << k : 0u;
-                rowk[k] = kBlk * grp + acc_row(i, hh);
+                rowk[k] = row0 + acc_row(i, 0);
                 dotk[k] = reinterpret_cast<const float *>(row_mem)[i];
-                invk[k] = inv_s[rowk[k]];
-                atk[k] = atomicAdd(valid ? &row_pos[rowk[k]] : &idle_pos[lane], valid ? 1 : 0);
+                invk[k] = F.inv_s[rowk[k]];
+                atk[k] = atomicAdd(valid ? &F.row_pos[rowk[k]] : &F.idle_pos[lane], valid ? 1 : 0);
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(dotk[k]), "+v"(invk[k]), "+v"(atk[k]));
@@ -464,128 +516,92 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
                 if (((validk >> k) & 1u) && atk[k] < fa.slice_cap)
                     slice0[rowk[k] * slice_row_stride + atk[k]] =
                         make_uint2(__float_as_uint((dotk[k] * inv_k) * invk[k]), key);
-            while (hits) {
+            while (hits) {   // keys close to many sources at once
                 const int i = __ffs(hits) - 1;
                 hits &= hits - 1;
-                const int row = kBlk * grp + acc_row(i, hh);
-                const float e = (reinterpret_cast<const float *>(row_mem)[i] * inv_k) * inv_s[row];
-                const int at = atomicAdd(&n_later[par], 1);
-                later[par][at & (kLaterCap - 1)] = make_uint4(__float_as_uint(e), key, (uint32_t)row, 0u);
+                const int row = row0 + acc_row(i, 0);
+                const float e = (reinterpret_cast<const float *>(row_mem)[i] * inv_k) * F.inv_s[row];
+                const int at = atomicAdd(&F.row_pos[row], 1);
+                if (at < fa.slice_cap) slice0[row * slice_row_stride + at] = make_uint2(__float_as_uint(e), key);
             }
         }
+        wave_sync();
         head0 += n0;
         head1 += n1;
     };
 
-    const int ntile = (c1 - c0 + kTileKeys - 1) / kTileKeys;
-    // The host's schedule is for lanes whose 16 rows are all sources; with fewer (a short
-    // list fills the rows in order, four to a lane at a time) the rings fill that much slower.
-    const int lane_rows = min(16, 4 * ((min(Sh - s_base, kBlk) + 7) / 8));
-    const int de = fa.drain_every * 16 / lane_rows;
-    // Tiles come in periods of `de`, the last tile of a period being the one with the scheduled
-    // drain.  Hits beyond a row's fourth go to the LDS list of the period's parity, which is stored
-    // once the period has ended, while the next period fills the other list.
-    int period = 0, period_end = de - 1;   // (the same in every thread)
-    // a row group without sources only helps to move the key tiles
-    const bool idle = s_base + kBlk * grp >= Sh;
-    // Entries listed during the period that just ended are final behind its last barrier, and the
-    // next period lists into the other list: one thread per entry stores them.  A list holds
-    // kLaterCap entries; more than that in one period and the head is redone exactly.  The list of
-    // a period is stored during the first tile of the next one, inside the tile's work and in
-    // front of its prefetch loads: a store behind the tile barrier would sit between the loads of
-    // two tiles, and the compiler then makes every other tile wait for all loads in flight
-    // instead of leaving the newer tile's outstanding.  (Threads 0 .. 127 do it: they belong to
-    // the first row group, which always has sources.)
-    int later_seen[2] = {0, 0};
-    auto store_later = [&](int par) {
-        const int n = n_later[par];
-        const int x = later_seen[par] + tid;
-        if (n - later_seen[par] > kLaterCap && tid == 0) later_lost = 1;
-        later_seen[par] = n;
-        if (x < n) {
-            const uint4 r = later[par][x & (kLaterCap - 1)];
-            const int at = atomicAdd(&row_pos[r.z], 1);
-            if (at < fa.slice_cap) slice0[(long)r.z * slice_row_stride + at] = make_uint2(r.x, r.y);
-        }
-    };
-    auto multiply_tile = [&](const unsigned char *buf, int t) {
-        if (idle) return;
-        if (period > 0 && t == period_end - de + 1) store_later((period - 1) & 1);
+    for (int b = wv; b < nblk; b += NW) {
+        // the block that has arrived -> this wave's LDS; the loads of the next one leave at once (the last block
+        // again past the end), behind a drain's stores: waiting for them then waits for nothing newer
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            *reinterpret_cast<u32x4 *>(mine + (4 * u + (lane >> 4)) * kPitch + (lane & 15) * 16) = stage[u];
+        if (tail0 - head0 >= kBlk || tail1 - head1 >= kBlk) drain();
+        load_block(min(b + NW, nblk - 1));
+        wave_sync();
         bf16x8 kc[kSteps];
-        tile_read(buf, stream, l32, hh, kc);
-        f32x16 acc;
+        tile_read(mine, 0, l32, hh, kc);
+        const float sq = add_other_half(half_row_sumsq(kc));
+        // the key's operand of the test: -|k| in two pieces against each piece of det, 1 against the constant
+        const uint32_t pieces = two_bf16(-__builtin_amdgcn_sqrtf(sq));
+        u32x4 ke = {hh ? 0u : pieces, hh ? 0u : pieces, hh ? 0u : 0x3f80u, 0u};
+        const int key = block_first(b) + l32;
+        // (norms beyond 2^59 or NaN: left to the drain's test)
+        const bool in_block = key >= c0 + kBlk * b && key < c1, sure = !(sq < 1e35f);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        for (int g = 0; g < SB; ++g) {
+            if (g > 0 && g >= groups) break;
+            u32x4 qe = *reinterpret_cast<const u32x4 *>(&F.test_s[hh][kBlk * g + l32]);
+            f32x16 acc;
 #pragma unroll
-        for (int s = 0; s < kSteps; ++s)   // rows = sources, columns = keys
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[s], kc[s], acc, 0, 0, 0);
-
-        float sq = half_row_sumsq(kc);
-        sq = add_other_half(sq);
-        const float norm_k = __builtin_amdgcn_sqrtf(sq);
-        float d[16];   // dot - bound * |k_j|: >= 0 means the edge may reach the bound
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) d[i] = fmaf(-det[i], norm_k, acc[i]);
-        float best = d[0];
+            for (int s = 0; s < kSteps; ++s)   // rows = sources, columns = keys
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[g][s], kc[s], acc, 0, 0, 0);
+            // dot - det |k_j| (the upper half-wave's part of the operands is 0)
+            const f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qe),
+                                                                     __builtin_bit_cast(bf16x8, ke), acc, 0, 0, 0);
+            int best = __float_as_int(d[0]);
 #pragma unroll
-        for (int i = 1; i < 16; ++i) best = fmaxf(best, d[i]);
-        const int key = c0 + kTileKeys * t + kBlk * stream + l32;
-        const bool hit = best >= 0.f && key < c1;
-        const uint64_t hit_lanes = __ballot(hit);
-        const int add0 = (int)__popcll(hit_lanes & 0x00000000ffffffffull), add1 = (int)__popcll(hit_lanes >> 32);
-        // a ring that could not take this tile's rows is drained first: one pass takes up to
-        // 32 rows out, after which the (at most 32) new rows fit
-        if (tail0 - head0 + add0 > RING || tail1 - head1 + add1 > RING) drain(period & 1);
-        if (hit) {
-            const int at = (hh ? tail1 : tail0) + (int)__popcll(hit_lanes & half_before);
-            unsigned char *row_mem = ring + (at & (RING - 1)) * kStagePitch;
+            for (int i = 1; i < 16; ++i) best = max(best, __float_as_int(d[i]));
+            const bool hit = (best >= 0 || sure) && in_block;
+            const uint64_t hit_lanes = __ballot(hit);
+            const int add0 = (int)__popcll(hit_lanes & 0x00000000ffffffffull), add1 = (int)__popcll(hit_lanes >> 32);
+            // a ring that could not take these rows is drained first: one pass takes up to
+            // 32 rows out, after which the (at most 32) new rows fit
+            if (tail0 - head0 + add0 > kRing || tail1 - head1 + add1 > kRing) drain();
+            if (hit) {
+                const int at = (hh ? tail1 : tail0) + (int)__popcll(hit_lanes & half_before);
+                unsigned char *row_mem = ring + (at & (kRing - 1)) * kStagePitch;
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                *reinterpret_cast<float4 *>(row_mem + 16 * v) =
-                    make_float4(acc[4 * v], acc[4 * v + 1], acc[4 * v + 2], acc[4 * v + 3]);
-            *reinterpret_cast<float2 *>(row_mem + 64) = make_float2(sq, __int_as_float(key));
+                for (int v = 0; v < 4; ++v)
+                    *reinterpret_cast<float4 *>(row_mem + 16 * v) =
+                        make_float4(acc[4 * v], acc[4 * v + 1], acc[4 * v + 2], acc[4 * v + 3]);
+                *reinterpret_cast<float4 *>(row_mem + 64) =
+                    make_float4(sq, __int_as_float(key), __int_as_float(kBlk * g), 0.f);
+            }
+            tail0 += add0;
+            tail1 += add1;
         }
-        tail0 += add0;
-        tail1 += add1;
-        // A scheduled drain empties the rings (a pass takes 32 rows per half-wave).  It sits
-        // here, in front of the tile's prefetch loads: the drain's stores are then older than
-        // those loads, and the wait in front of the next LDS store of a key tile -- a count of
-        // memory operations still in flight -- lets the loads stay in flight.
-        if (t == period_end) {
-            drain(period & 1);
-            if (RING > kBlk) drain(period & 1);
-        }
-    };
-    auto end_of_tile = [&](int tile_done) {
-        if (tile_done - 1 == period_end) {
-            ++period;
-            period_end += de;
-        }
-    };
-    GKV_TILE_PIPELINE(NT, Kh, c0, c1 - 1, 1, ntile, multiply_tile, end_of_tile(tile_done));
-    drain(period & 1);
-    drain(period & 1);
-    __syncthreads();
-    if (!idle) {
-        store_later(0);
-        store_later(1);
     }
+    drain();
+    drain();
     __syncthreads();      // every candidate is counted
     if (tid < ROWS && s_base + tid < Sh) {
-        const int c = row_pos[tid];
+        const int c = F.row_pos[tid];
         fa.cand_cnt[(buf_row0 + tid) * n_chunks + chunk] = c < fa.slice_cap ? c : fa.slice_cap;
-        if (c > fa.slice_cap || later_lost) fa.overflow[h] = 1;
+        if (c > fa.slice_cap) fa.overflow[h] = 1;
     }
 }
 
-template <int SB, int RING>
-__global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
+template <int SB, bool ONCE>
+__global__ __launch_bounds__(64 * kFilterWaves) void cosine_filter_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
     const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa)
 {
     constexpr int ROWS = SB * kBlk;
     __shared__ FilterLds<SB> F;
-    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the rings
+    extern __shared__ __align__(16) unsigned char smem[];   // key blocks and rings, wave by wave
     // The workgroups that stream the same keys (the source groups of a key chunk) should run at
     // about the same time on the same XCD, so that all but the first find the keys in that XCD's
     // L2.  Workgroups go to the 8 XCDs round robin in the order of their linear number, so the
@@ -606,8 +622,8 @@ __global__ __launch_bounds__(256 * SB) void cosine_filter_kernel(
     const int Sh = fa.n_src ? fa.n_src[h] : S;
     if (s_base >= Sh) return;
     const float *tau = fa.tau + (long)h * fa.pitch + fa.row0 + s_base;
-    filter_chunk<SB, RING>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, threadIdx.x,
-                           [&](int r) { return tau[r]; });
+    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, threadIdx.x,
+                     [&](int r) { return tau[r]; });
 }
 
 constexpr int kTieRoom = 64;   // entries tied at the cut that a select lists beyond the m winners
@@ -1057,8 +1073,8 @@ __global__ __launch_bounds__(kThreads) void late_filter_kernel(
         bound_from_histogram<BINS>(w4, rank, lane, &tau_s[r]);
     }
     __syncthreads();
-    filter_chunk<kSB, 64>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, gridDim.x / fa.sgroups, Sh, s_base, F, smem,
-                          tid, [&](int r) { return tau_s[r]; });
+    filter_chunk<kSB, false>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, gridDim.x / fa.sgroups, Sh, s_base, F, smem,
+                      tid, [&](int r) { return tau_s[r]; });
 }
 
 // Matching on its own, for source lists the few-winners selection does not take (S > 256).
@@ -1072,16 +1088,36 @@ __global__ __launch_bounds__(kMatchBlock) void match_sources_kernel(MatchArgs a,
                   threadIdx.x);
 }
 
-// Columns per workgroup: about 1024 workgroups in flight over all heads and source
-// groups, at least 8 key blocks per wave, and at least `min_chunks` chunks per head.
-int chunk_cols_for(int Hkv, int sgroups, int n_cols, int min_chunks = 1)
+// Columns per workgroup of the dense block: about 1024 workgroups in flight over all heads and source
+// groups, at least 8 key blocks per wave.  (The filter pass's scratch is sized by it too.)
+int chunk_cols_for(int Hkv, int sgroups, int n_cols)
 {
     long ck = ((long)Hkv * sgroups * n_cols + 1023) / 1024;
     if (ck < 1024) ck = 1024;
-    const long cap = (n_cols + min_chunks - 1) / min_chunks;
-    if (ck > cap) ck = cap;
+    if (ck > n_cols) ck = n_cols;
     ck = ((ck + 127) / 128) * 128;
     return (int)(ck < 128 ? 128 : ck);
+}
+
+// Columns per workgroup of the filter pass, whole blocks for each of its waves, at most `most` chunks a head.  A compute
+// unit runs one workgroup at a time, and each pays for its sources and its last drains about as long as 768 keys take:
+// the cut with the fewest keys per compute unit, counting whole rounds of 256 workgroups.  (1024 workgroups of at least
+// 1024 keys before; whole pass, us, before / now: 8 heads of 16K keys 106.4 / 97.5, 24 of 32K 256 / 234, 40 of 32K 382 /
+// 327; at least four rounds instead: 105.7, 245, 350, and 256 heads of 20K 1013 / 999, of 32K 1399 / 1403.)
+int filter_cols_for(int Hkv, int sgroups, int P, int most)
+{
+    const long units = (long)Hkv * sgroups, r0 = (units + 255) / 256;
+    long best = -1;
+    int cols = 0;
+    for (long r = r0; r < r0 + 8; ++r) {
+        long chunks = r * 256 / units;
+        if (chunks > most) chunks = most;
+        const long ck = ((P + chunks - 1) / chunks + 255) / 256 * 256;
+        const long rounds = (units * ((P + ck - 1) / ck) + 255) / 256;
+        const long cost = rounds * (ck + 768);
+        if (best < 0 || cost < best) { best = cost; cols = (int)ck; }
+    }
+    return cols;
 }
 
 }  // namespace
@@ -1154,6 +1190,8 @@ bool mfma_filter_applies(int P, int m, long rows)
 
 bool source_reuse_applies(int S) { return S <= 4096; }   // the previous list and the match's bookkeeping sit in LDS
 
+constexpr long kManyChunksBytes = 32L << 20;
+
 // Geometry of the filter route for a call.  X speculative rows (see the head of this file)
 // ride along in the first round when the lists are kept from round to round and the extended
 // source list still fits the small-k source selection; their workgroups then carry three
@@ -1177,25 +1215,44 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
     g.pitch = S + g.X;
     const int rows_wg = kBlk * g.sb;
     const int sgroups = (S + g.X + rows_wg - 1) / rows_wg;
-    g.chunk_cols = chunk_cols_for(Hkv, sgroups, P);
-    g.chunks = (P + g.chunk_cols - 1) / g.chunk_cols;
-    if (g.chunks > 256) {   // the exact select keeps the slice sizes of a source in LDS
-        g.chunk_cols = (((P + 255) / 256 + 127) / 128) * 128;
-        g.chunks = (P + g.chunk_cols - 1) / g.chunk_cols;
-    }
+    g.cand_cap = mfma_cand_cap(P, m);
     // a slice holds four times its expected share of a row's ~rank * stride candidates (rank: the
     // bound pass's rank in the sample), and 2 m on top
     const int stride = P / mfma_sample_cols(P);
-    const long share = ((long)mfma_bound_rank(m, stride) * stride + g.chunks - 1) / g.chunks;
-    long sc = 4L * share + 2L * m;
-    if (sc < 64) sc = 64;
-    g.cand_cap = mfma_cand_cap(P, m);
-    // Short prompts: a row's slices may take what its row of the dense edge block would (whole 128-byte lines),
-    // which holds most lists whose entries all sit in one chunk (the round above: 181 -> 94 us, in runs of 1000
-    // alike 568 -> 97; keys in random order take 92 either way).
-    if (P < 8192 && !short_slices && sc < P / (2 * g.chunks)) sc = P / (2 * g.chunks) / 16 * 16;
-    if (sc > g.cand_cap) sc = g.cand_cap;
-    g.slice_cap = (int)sc;
+    const long listed = (long)mfma_bound_rank(m, stride) * stride;
+    auto slice_for = [&](int chunks) {
+        long sc = 4L * ((listed + chunks - 1) / chunks) + 2L * m;
+        if (sc < 64) sc = 64;
+        // Short prompts: a row's slices may take what its row of the dense edge block would (whole 128-byte lines),
+        // which holds most lists whose entries all sit in one chunk (the round above: 181 -> 94 us, in runs of 1000
+        // alike 568 -> 97; keys in random order take 92 either way).
+        if (P < 8192 && !short_slices && sc < P / (2 * chunks)) sc = P / (2 * chunks) / 16 * 16;
+        return sc > g.cand_cap ? (long)g.cand_cap : sc;
+    };
+    // The memory for a row's slices is what this cut's take (at most 256 of them: the exact select keeps the slice sizes
+    // of a source in LDS).  The pass makes more chunks than that only where their slices take little; with
+    // fewer chunks a slice is the longer.
+    int cols = chunk_cols_for(Hkv, sgroups, P), chunks = (P + cols - 1) / cols;
+    if (chunks > 256) {
+        cols = (((P + 255) / 256 + 127) / 128) * 128;
+        chunks = (P + cols - 1) / cols;
+    }
+    g.chunk_cols = cols;
+    g.chunks = g.chunk_slots = chunks;
+    g.slice_cap = (int)slice_for(chunks);
+    g.row_slots = (long)chunks * g.slice_cap;
+    if (short_slices) return g;
+    int most = 256;
+    while (most > chunks && (long)Hkv * g.pitch * most * slice_for(most) * 8 > kManyChunksBytes) most = most / 2 > chunks ? most / 2 : chunks;
+    g.chunk_cols = filter_cols_for(Hkv, sgroups, P, most);
+    g.chunks = (P + g.chunk_cols - 1) / g.chunk_cols;
+    if (g.chunks > chunks) {
+        g.chunk_slots = g.chunks;
+        g.slice_cap = (int)slice_for(g.chunks);
+        g.row_slots = (long)g.chunks * g.slice_cap;
+    } else {
+        g.slice_cap = (int)(g.row_slots / g.chunks);
+    }
     return g;
 }
 
@@ -1254,32 +1311,19 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     return hipGetLastError();
 }
 
-// Rows a half-wave parks per tile: 32 lanes x P(a lane's 16 edges hold a hit), with a
-// per-edge hit rate of about rank * stride / P (each source keeps about that many candidates,
-// rank = the bound pass's rank in the sample).  Drains are scheduled for when most of a
-// half-wave's 32 lanes get a row and the ring is not yet full.
-int filter_drain_every(int P, int m, int ring)
-{
-    const int stride = sample_of(P).stride;
-    const double rate = (double)mfma_bound_rank(m, stride) * stride / (double)P;
-    const double per_tile = 32.0 * (1.0 - pow(1.0 - (rate < 1.0 ? rate : 1.0), 16.0));
-    const int every = (int)((ring > kBlk ? 30.0 : 24.0) / (per_tile > 0.45 ? per_tile : 0.45));
-    return every < 1 ? 1 : every;
-}
-
-template <int SB, int RING>
+template <int SB>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                          int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, int row0,
                          const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    FilterArgs fa{n_src, tau, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, filter_drain_every(P, m, RING), sgroups, src_pitch,
-                  g.pitch, row0};
-    if (!allow_big_lds((const void *)cosine_filter_kernel<SB, RING>)) return hipGetLastError();
-    hipLaunchKernelGGL((cosine_filter_kernel<SB, RING>), dim3(g.chunks * sgroups, Hkv), dim3(256 * SB),
-                       2 * kTileBytes + 2 * (4 * SB) * RING * kStagePitch, st, (const uint16_t *)Ac,
-                       (const uint16_t *)Kc, N, P, rows, src, g.chunk_cols, fa);
+    FilterArgs fa{n_src, tau, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, sgroups, src_pitch, g.pitch, row0};
+    const bool once = sgroups == 1 && reads_past_caches((size_t)Hkv * N * kD * 2);
+    auto *kernel = once ? cosine_filter_kernel<SB, true> : cosine_filter_kernel<SB, false>;
+    if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
+    hipLaunchKernelGGL(kernel, dim3(g.chunks * sgroups, Hkv), dim3(64 * kFilterWaves), kFilterLdsBytes, st,
+                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, rows, src, g.chunk_cols, fa);
     return hipGetLastError();
 }
 
@@ -1311,9 +1355,9 @@ hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, in
                                      int32_t *overflow, hipStream_t st)
 {
     if (first_round && g.sb == 3)
-        return launch_filter<3, 32>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand,
+        return launch_filter<3>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand,
                                     cand_cnt, overflow, st);
-    return launch_filter<2, 64>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt,
+    return launch_filter<2>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt,
                                 overflow, st);
 }
 
@@ -1339,12 +1383,11 @@ hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, in
 {
     const int sgroups = (g.S + kRows - 1) / kRows;
     const Sample smp = sample_of(P);
-    FilterArgs fa{n_new, nullptr, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, filter_drain_every(P, m, 64), sgroups, g.S,
-                  g.pitch, 0};
-    static_assert(kRows * 256 * 4 <= 2 * (4 * kSB) * 64 * kStagePitch, "the histograms take the rings' place");
+    FilterArgs fa{n_new, nullptr, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, sgroups, g.S, g.pitch, 0};
+    static_assert(2 * kTileBytes + kRows * 256 * 4 <= kFilterLdsBytes, "the histograms take the rings' place");
     if (!allow_big_lds((const void *)late_filter_kernel)) return hipGetLastError();
     hipLaunchKernelGGL(late_filter_kernel, dim3(g.chunks * sgroups, Hkv), dim3(kThreads),
-                       2 * kTileBytes + 2 * (4 * kSB) * 64 * kStagePitch, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P,
+                       kFilterLdsBytes, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P,
                        new_src, g.chunk_cols, fa, smp.cols, smp.stride, mfma_bound_rank(m, smp.stride));
     return hipGetLastError();
 }

@@ -241,3 +241,44 @@ def test_update_in_front_of_the_selection_takes_long_chains(P, S, m):
     say(f"  together {1e3 * both:.1f} us, update {1e3 * update:.1f}, selection {1e3 * select:.1f}")
     assert torch.equal(kept, alone)
     assert both < 1.2 * (update + select)
+
+
+# (row groups of 32 per workgroup: one and two in a single round, three with the next-ranked nodes along, two workgroups of
+# three; the last key block short, or starting early at the end of the head; keys beyond 256 MiB, which stay out of the caches)
+@pytest.mark.parametrize("P,w,S,m,T,H", [(2080, 1, 32, 4, 1, 128), (2175, 5, 33, 9, 1, 128), (4097, 1, 64, 32, 2, 36),
+                                         (8191, 32, 129, 20, 2, 8), (2049, 63, 65, 16, 2, 64), (2050, 2, 8, 5, 1, 512)])
+def test_filter_pass_row_groups_and_key_blocks(P, w, S, m, T, H):
+    """The filter pass against the dense edge block, bit for bit: many heads take the one, the same heads alone the
+    other.  Among the sources a zero key; among the nodes zero keys, keys of norms that leave the range of the matrix
+    cores' test of the bounds, keys close to all sources of a kind, blocks in which every key is a candidate."""
+    say(f"filter pass P={P} w={w} S={S} m={m} T={T} H={H}")
+    d, few, N = 128, 4, P + w
+    assert H * S * P >= 1 << 23 > few * S * P
+    g = torch.Generator("cuda").manual_seed(P + S)
+    kind = torch.randint(0, 16, (few, N, 1), generator=g, device="cuda")
+    cent = torch.randn(few, 16, d, generator=g, device="cuda")
+    K = cent.gather(1, kind.expand(-1, -1, d)) + 0.7 * torch.randn(few, N, d, generator=g, device="cuda")
+    K[:, 64:96] = cent[:, 3:4] + 0.05 * torch.randn(few, 32, d, generator=g, device="cuda")
+    s = torch.rand(few, P, generator=g, device="cuda") + 0.1
+    K[1, P - 1] = 0.0
+    K[1, 7] = 0.0
+    s[1, 7] = 5.0                                                   # a source all of whose edges are 0
+    for j, norm in ((100, 1e-18), (101, 1e18), (102, 3e17), (P - 2, 1e-12), (P - 3, 1e12)):
+        K[2, j] *= norm / 10.0
+        s[2, j] = 3.0 if j == 102 else s[2, j]
+    K = K.to(torch.bfloat16)
+    rep = -(-H // few)
+    kw = dict(head_dim=d, n_tokens=N, window=w, n_sources=S, n_neighbors=m, rounds=T)
+
+    def run(heads, K, s):
+        p = gk.Params(n_kv_heads=heads, n_q_heads=heads, **kw)
+        dbg = [torch.full((T, heads, S, n) if n else (T, heads, S), -1, dtype=t, device="cuda")
+               for n, t in ((0, torch.int32), (m, torch.int32), (m, torch.float32))]
+        out = gk.graphkv_propagate(p, K, s.clone(), *dbg)
+        return (out, *dbg)
+
+    dense = run(few, K, s)
+    many = run(rep * few, K.repeat(rep, 1, 1), s.repeat(rep, 1))
+    assert torch.equal(many[0].view(rep, few, P), dense[0].expand(rep, -1, -1))
+    for a, b in zip(many[1:], dense[1:]):
+        assert torch.equal(a.view(T, rep, *b.shape[1:]), b[:, None].expand(-1, rep, *[-1] * (b.dim() - 1)))
