@@ -7,6 +7,8 @@ namespace gkv {
 
 constexpr int kWave = 64;
 
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes, a plain vector register group
+
 // Per-layer quantities of a batched call, passed to kernels by value.  A batch is
 // a run of layers whose tensors are contiguous ([L, H, ...]), so every (layer,
 // head) pair is simply head q = l * H + h of a layer with L*H heads; only the

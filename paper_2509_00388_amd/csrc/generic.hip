@@ -142,7 +142,7 @@ __device__ __forceinline__ float lane_group_sum(float v)
 // up with row r of them stores it, one coalesced store per wave.  (A thread per row, as before,
 // touches 64 rows per load instruction: 523 us for 524 MB of bf16 keys with d = 128, 1.0 TB/s;
 // this way 124 us, 4.2 TB/s.)
-template <typename T, int LPR>
+template <typename T, int LPR, bool ONCE>
 __global__ __launch_bounds__(256) void knorm_kernel(const T *__restrict__ Kc, int d, int N, int P,
                                                     float *__restrict__ scores)
 {
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void knorm_kernel(const T *__restrict__ Kc, in
     const int j0 = blockIdx.x * 256 + wv * kWave;
     if (j0 >= P) return;
     const int g = lane / LPR, c = lane % LPR, vpr = d / V;
-    const uint4 *kh = reinterpret_cast<const uint4 *>(Kc + (long)h * N * d);
+    const u32x4 *kh = reinterpret_cast<const u32x4 *>(Kc + (long)h * N * d);
     float mine = 0.f;
 #pragma unroll
     for (int b0 = 0; b0 < LPR; b0 += B) {
@@ -163,7 +163,11 @@ __global__ __launch_bounds__(256) void knorm_kernel(const T *__restrict__ Kc, in
             uint4 v[B];
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                v[u] = kh[(long)min(j0 + (b0 + u) * RPS + g, P - 1) * vpr + (in ? c0 + c : 0)];
+            {
+                const u32x4 *p = kh + (long)min(j0 + (b0 + u) * RPS + g, P - 1) * vpr + (in ? c0 + c : 0);
+                const u32x4 x = ONCE ? __builtin_nontemporal_load(p) : *p;
+                v[u] = make_uint4(x.x, x.y, x.z, x.w);
+            }
 #pragma unroll
             for (int u = 0; u < B; ++u) {
                 float t[V];
@@ -187,7 +191,10 @@ static void launch_knorm_t(const T *Kc, int Hkv, int d, int N, int P, float *sco
 {
     const int vpr = d / Elem<T>::kPerVec;
     const dim3 grid((P + 255) / 256, Hkv);
-#define GKV_KNORM(LPR) hipLaunchKernelGGL((knorm_kernel<T, LPR>), grid, dim3(256), 0, st, Kc, d, N, P, scores)
+    const bool once = reads_past_caches((size_t)Hkv * N * d * sizeof(T));
+#define GKV_KNORM(LPR)                                                                                             \
+    hipLaunchKernelGGL((once ? knorm_kernel<T, LPR, true> : knorm_kernel<T, LPR, false>), grid, dim3(256), 0, st, Kc, d, \
+                       N, P, scores)
     if (vpr <= 8) GKV_KNORM(8);
     else if (vpr <= 16) GKV_KNORM(16);
     else if (vpr <= 32) GKV_KNORM(32);

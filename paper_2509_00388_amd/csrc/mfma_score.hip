@@ -63,7 +63,7 @@ __device__ __forceinline__ void load_queries(const uint16_t *Qh, int first, int 
 // that a batch cuts a head's keys as a single layer does and adds the same terms in the same order.  At a
 // chunk's last tile the waves park their statistics in LDS and start over; they are stored during the next
 // tile, behind its barrier, while the one after that parks in the other half of the LDS.
-template <int NB, int SPLIT, int STREAMS, bool MANY>
+template <int NB, int SPLIT, int STREAMS, bool MANY, bool ONCE>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w,
     int chunk_keys, int nchunks, int per_wg, float c, float *__restrict__ part, int R_total, int R_real, int row_base)
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
         after_tile();
     };
     if constexpr (NBW <= 2) {
-        GKV_TILE_PIPELINE_OVERLAPPED(TK, NT, Kh, k0, k1 - 1, 1, ntile, head, body, finish);
+        GKV_TILE_PIPELINE_OVERLAPPED(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, head, body, finish);
     } else {   // three row blocks per wave: a second accumulator set does not fit the registers
         auto one_tile = [&](const unsigned char *buf, int t) {
             before_tile();
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
             finish(t, 0);
             if (t + 1 < ntile) after_tile();
         };
-        GKV_TILE_PIPELINE_TK(TK, NT, Kh, k0, k1 - 1, 1, ntile, one_tile, (void)0);
+        GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, one_tile, (void)0);
     }
 
     park(at & 1);
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
 // pool_half keys on either side of its chunk, and at the end it writes the pooled, grouped
 // scores of its chunk itself: votes[] is then the score array [Hkv, P].  The sums are
 // formed in the order of the separate pooling kernel, so the bits are the same.
-template <int NB, int SPLIT, bool PERQ, int STREAMS = 4>
+template <int NB, int SPLIT, bool PERQ, int STREAMS, bool ONCE>
 __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Qw, int N, int P, int w, int G,
     int chunk_keys, float c, const float *__restrict__ part, int part_chunks,
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE_TK(TK, NT, Kh, first, kend - 1, 1, ntile, multiply_tile, (void)0);
+    GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, first, kend - 1, 1, ntile, multiply_tile, (void)0);
     if (fused) {
         __syncthreads();
         if constexpr (PERQ) {   // max pooling: per query head, then the sum over the heads
@@ -513,7 +513,9 @@ static hipError_t launch_stats_nb(const uint16_t *K, const uint16_t *Q, int Hkv,
 {
     const dim3 grid((plan.chunks + plan.per_wg - 1) / plan.per_wg, Hkv), block(64 * STREAMS * SPLIT);
     const size_t lds = 2 * (kBlk * STREAMS) * kPitch;
-    auto *kernel = plan.per_wg > 1 ? score_stats_kernel<NB, SPLIT, STREAMS, true> : score_stats_kernel<NB, SPLIT, STREAMS, false>;
+    const bool once = reads_past_caches((size_t)Hkv * N * kD * 2);
+    auto *kernel = plan.per_wg > 1 ? (once ? score_stats_kernel<NB, SPLIT, STREAMS, true, true> : score_stats_kernel<NB, SPLIT, STREAMS, true, false>)
+                                   : (once ? score_stats_kernel<NB, SPLIT, STREAMS, false, true> : score_stats_kernel<NB, SPLIT, STREAMS, false, false>);
     if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
     hipLaunchKernelGGL(kernel, grid, block, lds, st, K, Q, N, P, w, plan.chunk_keys, plan.chunks, plan.per_wg, c, part,
                        R_total, R_real, row_base);
@@ -550,17 +552,12 @@ static void launch_votes_nb(dim3 grid, const uint16_t *K, const uint16_t *Q, int
                             hipStream_t st)
 {
     const size_t lds = 2 * (kBlk * STREAMS) * kPitch + (pool_half >= 0 ? (size_t)(per_q ? G : SPLIT) * (ck + 2 * pool_half) * 4 : 0);
-    if (per_q) {
-        if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, true, STREAMS>)) return;
-        hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, true, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
-                           lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           R_real, row_base, vote_rows, vote_row_base, pool_half);
-    } else {
-        if (!allow_big_lds((const void *)score_votes_kernel<NB, SPLIT, false, STREAMS>)) return;
-        hipLaunchKernelGGL((score_votes_kernel<NB, SPLIT, false, STREAMS>), grid, dim3(64 * STREAMS * SPLIT),
-                           lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
-                           R_real, row_base, vote_rows, vote_row_base, pool_half);
-    }
+    const bool once = reads_past_caches((size_t)grid.y * N * kD * 2);
+    auto *kernel = per_q ? (once ? score_votes_kernel<NB, SPLIT, true, STREAMS, true> : score_votes_kernel<NB, SPLIT, true, STREAMS, false>)
+                         : (once ? score_votes_kernel<NB, SPLIT, false, STREAMS, true> : score_votes_kernel<NB, SPLIT, false, STREAMS, false>);
+    if (!allow_big_lds((const void *)kernel)) return;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * STREAMS * SPLIT), lds, st, K, Q, N, P, w, G, ck, c, part, chunks, votes, R_total,
+                       R_real, row_base, vote_rows, vote_row_base, pool_half);
 }
 
 // Widest pooling window of the votes pass: its halo is multiplied twice and sits in LDS beside the chunk.

@@ -19,7 +19,6 @@ namespace gkv {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes, a plain vector register group
 
 constexpr int kD = 128;          // head dimension
 constexpr int kSteps = 8;        // k-steps of 16 per 128
@@ -52,7 +51,8 @@ template <int NT, int TK = kTileKeys> __device__ __forceinline__ int tile_piece(
 
 // Global -> registers.  Tile row t is key (first + t) * stride, clamped to
 // last_key (rows past the range are loaded from a valid address and masked later).
-template <int NT, int TK = kTileKeys, int PER>
+// ONCE: nobody reads these rows again while a cache could hold them (reads_past_caches()).
+template <int NT, int TK = kTileKeys, bool ONCE = false, int PER>
 __device__ __forceinline__ void tile_load(const uint16_t *Kh, int first, int last_key, int stride,
                                           int tid, u32x4 (&r)[PER])
 {
@@ -64,7 +64,8 @@ __device__ __forceinline__ void tile_load(const uint16_t *Kh, int first, int las
     for (int u = 0; u < PER; ++u) {
         const int g = tile_piece<NT, TK>(tid, u), row = g >> 4, c = g & 15;
         const uint32_t off = (uint32_t)(min(first + row, last_key) * stride) * (uint32_t)(kD * 2) + (uint32_t)c * 16u;
-        r[u] = *reinterpret_cast<const u32x4 *>(base + off);
+        const u32x4 *p = reinterpret_cast<const u32x4 *>(base + off);
+        r[u] = ONCE ? __builtin_nontemporal_load(p) : *p;
     }
 }
 
@@ -139,25 +140,25 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // wait in front of each LDS store leaves the newer tile's loads outstanding.
 // With conditional loads it has to assume they were skipped and waits for
 // everything.
-#define GKV_TILE_PIPELINE_TK(TK_, NT_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)         \
+#define GKV_TILE_PIPELINE_TK(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)  \
     do {                                                                                               \
         constexpr int tile_bytes_ = (TK_) * kPitch;                                                    \
         u32x4 stage_a[tile_pieces<NT_, TK_>()], stage_b[tile_pieces<NT_, TK_>()];                      \
-        tile_load<NT_, TK_>(Kh_, first_, clamp_, stride_, tid, stage_a);                               \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_, clamp_, stride_, tid, stage_a);                        \
         tile_store<NT_, TK_>(kt, tid, stage_a);                                                        \
-        tile_load<NT_, TK_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                       \
-        tile_load<NT_, TK_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);                   \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);            \
         __syncthreads();                                                                               \
         for (int t_ = 0; t_ < ntile_; t_ += 2) {                                                       \
             body(kt, t_);                                                                              \
             tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                      \
-            tile_load<NT_, TK_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_a);        \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_a); \
             __syncthreads();                                                                           \
             { const int tile_done = t_ + 1; (void)tile_done; AFTER_TILE; }                             \
             if (t_ + 1 >= ntile_) break;                                                               \
             body(kt + tile_bytes_, t_ + 1);                                                            \
             tile_store<NT_, TK_>(kt, tid, stage_b);                                                    \
-            tile_load<NT_, TK_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_b);        \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_b); \
             __syncthreads();                                                                           \
             { const int tile_done = t_ + 2; (void)tile_done; AFTER_TILE; }                             \
         }                                                                                              \
@@ -170,35 +171,35 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // 0 into set 0; `body(buf, t, set)` multiplies tile t into `set` and finishes tile t - 1 from the
 // other set; `tail(t, set)` finishes the last tile.  `set` is a literal at every call, so the
 // accumulator sets stay in registers.
-#define GKV_TILE_PIPELINE_OVERLAPPED(TK_, NT_, Kh_, first_, clamp_, stride_, ntile_, head, body, tail)  \
+#define GKV_TILE_PIPELINE_OVERLAPPED(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, head, body, tail) \
     do {                                                                                               \
         constexpr int tile_bytes_ = (TK_) * kPitch;                                                    \
         u32x4 stage_a[tile_pieces<NT_, TK_>()], stage_b[tile_pieces<NT_, TK_>()];                      \
-        tile_load<NT_, TK_>(Kh_, first_, clamp_, stride_, tid, stage_a);                               \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_, clamp_, stride_, tid, stage_a);                        \
         tile_store<NT_, TK_>(kt, tid, stage_a);                                                        \
-        tile_load<NT_, TK_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                       \
-        tile_load<NT_, TK_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);                   \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);            \
         __syncthreads();                                                                               \
         head(kt);                                                                                      \
         tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                          \
-        tile_load<NT_, TK_>(Kh_, first_ + 3 * (TK_), clamp_, stride_, tid, stage_a);                   \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 3 * (TK_), clamp_, stride_, tid, stage_a);            \
         __syncthreads();                                                                               \
         int t_ = 1;                                                                                    \
         for (; t_ < ntile_; t_ += 2) {                                                                 \
             body(kt + tile_bytes_, t_, 1);                                                             \
             tile_store<NT_, TK_>(kt, tid, stage_b);                                                    \
-            tile_load<NT_, TK_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_b);        \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_b); \
             __syncthreads();                                                                           \
             if (t_ + 1 >= ntile_) break;                                                               \
             body(kt, t_ + 1, 0);                                                                       \
             tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                      \
-            tile_load<NT_, TK_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_a);        \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_a); \
             __syncthreads();                                                                           \
         }                                                                                              \
         if ((ntile_ - 1) & 1) tail(ntile_ - 1, 1); else tail(ntile_ - 1, 0);                           \
     } while (0)
 
 #define GKV_TILE_PIPELINE(NT_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE) \
-    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)
+    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, false, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)
 
 }  // namespace gkv

@@ -313,11 +313,12 @@ __global__ __launch_bounds__(1024) void decay_sequential_kernel(
 // Kout[q, t, :] = Kc[q, idx[q, t], :] for head q = l * H + h of a batch, same for V;
 // 16 bytes per thread, rows of 16 * vec_per_row bytes.  Outputs and idx are packed
 // layer after layer (layer l holds H * B_l rows).
-__global__ __launch_bounds__(256) void gather_kernel(const uint4 *__restrict__ Kc,
-                                                     const uint4 *__restrict__ Vc,
+template <bool ONCE>
+__global__ __launch_bounds__(256) void gather_kernel(const u32x4 *__restrict__ Kc,
+                                                     const u32x4 *__restrict__ Vc,
                                                      const int32_t *__restrict__ idx, int N,
-                                                     int vec_per_row, uint4 *__restrict__ Kout,
-                                                     uint4 *__restrict__ Vout, LayerPlan plan)
+                                                     int vec_per_row, u32x4 *__restrict__ Kout,
+                                                     u32x4 *__restrict__ Vout, LayerPlan plan)
 {
     const int q = blockIdx.y;
     const int l = q / plan.heads_per_layer, hl = q % plan.heads_per_layer;
@@ -329,9 +330,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4 *__restrict__ K
     const int32_t j = idx[out_row];
     const long src = ((long)q * N + j) * vec_per_row + c;
     const long dst = out_row * vec_per_row + c;
-    const uint4 *in = blockIdx.z == 0 ? Kc : Vc;
-    uint4 *out = blockIdx.z == 0 ? Kout : Vout;
-    out[dst] = in[src];
+    const u32x4 *in = blockIdx.z == 0 ? Kc : Vc;
+    u32x4 *out = blockIdx.z == 0 ? Kout : Vout;
+    if (ONCE) __builtin_nontemporal_store(in[src], out + dst);
+    else out[dst] = in[src];
 }
 
 template <typename T>
@@ -436,9 +438,9 @@ hipError_t launch_gather(const void *Kc, const void *Vc, const int32_t *idx, int
 {
     const int vpr = row_bytes / 16;
     const long per_head = (long)max_budget * vpr;
-    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((per_head + 255) / 256), heads, 2), dim3(256), 0,
-                       st, (const uint4 *)Kc, (const uint4 *)Vc, idx, N, vpr, (uint4 *)Kout,
-                       (uint4 *)Vout, plan);
+    const bool once = reads_past_caches((size_t)heads * N * row_bytes);
+    hipLaunchKernelGGL(once ? gather_kernel<true> : gather_kernel<false>, dim3((unsigned)((per_head + 255) / 256), heads, 2),
+                       dim3(256), 0, st, (const u32x4 *)Kc, (const u32x4 *)Vc, idx, N, vpr, (u32x4 *)Kout, (u32x4 *)Vout, plan);
     return hipGetLastError();
 }
 
