@@ -414,8 +414,8 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                                launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
                                                         at<char>(ws, W.bound_hist), tau, ovf, st));
                     GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER,
-                               launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr, tau, cand,
-                                                         cnt, ovf, st));
+                               launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
+                                                         at<char>(ws, W.bound_hist), tau, cand, cnt, ovf, st));
                     GKV_LAUNCH(GRAPHKV_K_NBR_SELECT,
                                launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, nullptr, nbr, ev, st));
                 } else {
@@ -435,7 +435,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     // new sources without a kept list (usually none): bound and filter passes
                     // that return at once for heads that have none
-                    if (pick_match_applies(D.S) && late_filter_applies(D.H, g)) {
+                    if (pick_match_applies(D.S) && late_filter_applies(D.H, D.P, D.m, g)) {
                         GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
                                    launch_late_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, new_src, n_new, cand, cnt, ovf, st));
                     } else {
@@ -443,8 +443,8 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                                    launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
                                                             at<char>(ws, W.bound_hist), tau, ovf, st));
                         GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER_NEW,
-                                   launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new, tau,
-                                                             cand, cnt, ovf, st));
+                                   launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, false, new_src, n_new,
+                                                             nullptr, tau, cand, cnt, ovf, st));
                     }
                     GKV_LAUNCH(GRAPHKV_K_NBR_SELECT_LATER,
                                launch_nbr_select(cand, cnt, ovf, src, D.H, D.m, g, &sel, nbr, ev, st));

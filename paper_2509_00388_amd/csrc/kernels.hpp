@@ -158,7 +158,7 @@ bool source_reuse_applies(int S);     // lists can be kept from round to round
 constexpr int kSpecRows = 32;         // speculative rows per head: one or two MFMA row blocks of 32
 constexpr int kMaxExtSources = 256;   // largest S + kSpecRows the source selection splits
 // Geometry of the filter route for one call.  The per-row buffers (tau [Hkv, pitch], cand
-// [Hkv, pitch, chunks, slice_cap] x 8 bytes, cand_cnt [Hkv, pitch, chunks]) hold, per head,
+// [Hkv, pitch, row_slots] x 8 bytes, cand_cnt [Hkv, pitch, chunk_slots]) hold, per head,
 // the S sources of the first round, then X speculative rows (the nodes ranked right behind the
 // sources: the likeliest new sources of later rounds, whose candidate lists the first round's
 // pass builds on the side).  New sources of later rounds that have no kept list reuse rows 0 .. S - 1.
@@ -169,6 +169,7 @@ struct MfmaFilterPlan {
     int chunk_cols;   // keys per workgroup of the filter pass
     int chunks;       // workgroups (= candidate slices) per head and source group
     int slice_cap;    // entries per (row, chunk) slice
+    int late_cols, late_chunks, late_slice_cap;   // the same for the passes over new sources of later rounds
     int chunk_slots;  // slice sizes a row has room for (cand_cnt)
     long row_slots;   // entries a row has room for (cand), at least chunks * slice_cap
     int cand_cap;     // entries the exact select can take per row
@@ -189,8 +190,8 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
 // per slice to cand_cnt.  Same source lists and rows as the bound pass.
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
-                                     const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
-                                     int32_t *overflow, hipStream_t st);
+                                     const int32_t *n_src, const void *hist_part, const float *tau, void *cand,
+                                     int32_t *cand_cnt, int32_t *overflow, hipStream_t st);
 // From the second round on (match.hpp): which sources keep their list from the round before (copied
 // from prev_nbr / prev_e to nbr / nbr_e), which are speculative rows of the first round (the last X
 // entries of ext [Hkv, S + X]; not used for heads that overflowed then: spec_bad [Hkv], set by the first
@@ -224,7 +225,7 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st);
 // A later round's bound and filter passes in one launch, for few heads (overflow is not cleared).
-bool late_filter_applies(int Hkv, const MfmaFilterPlan &g);
+bool late_filter_applies(int Hkv, int P, int m, const MfmaFilterPlan &g);
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
                               int32_t *overflow, hipStream_t st);

@@ -52,10 +52,14 @@ constexpr int kThreads = 256 * kSB;
 struct FilterArgs {
     const int32_t *n_src;  // [Hkv] rows of the head's source list in use; null: all S
     const float *tau;      // [Hkv, pitch] the bound pass's value per row: edges below it are dropped
-    uint2 *cand;           // [Hkv, pitch, chunks, slice_cap] (edge bits, key index): one slice per key chunk
-    int32_t *cand_cnt;     // [Hkv, pitch, chunks] entries in each slice
+    // or, with few heads, what the bound pass's chunks left (null: tau has the bounds), and its sample
+    const float *part;
+    int rank, key_stride;
+    uint2 *cand;           // [Hkv, pitch, row_slots] (edge bits, key index): a slice of slice_cap per key chunk
+    int32_t *cand_cnt;     // [Hkv, pitch, chunk_slots] entries in each slice
     int32_t *overflow;     // [Hkv]
-    int slice_cap;
+    long row_slots;
+    int chunk_slots, slice_cap;
     int sgroups;           // workgroups (groups of source rows) per key chunk
     int src_pitch;         // entries per head of the source list
     int pitch, row0;
@@ -322,6 +326,260 @@ __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__rest
     bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + row0 + slot]);
 }
 
+// The passes below that share nothing between waves: a wave holds all source rows of its workgroup (SB groups of 32) and
+// takes blocks of 32 keys of its own through a piece of LDS.
+constexpr int kOwnWaves = 8;       // two per SIMD: 256 registers each
+constexpr int kBlkBytes = kBlk * kPitch;
+
+// This thread's part of the workgroup's source rows (slots beyond Sh repeat the last source).
+template <int SB> struct SourcePieces {
+    static constexpr int PER = SB * kBlk * 16 / (kWave * kOwnWaves);   // 16-byte pieces per thread
+    u32x4 piece[PER];
+    __device__ __forceinline__ void load(const uint16_t *Ah, const int32_t *src_h, int Sh, int s_base, int tid)
+    {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + kWave * kOwnWaves * u;
+            const int32_t i = src_h[min(s_base + (at >> 4), Sh - 1)];
+            piece[u] = *reinterpret_cast<const u32x4 *>(Ah + (long)i * kD + 8 * (at & 15));
+        }
+    }
+    // Through the LDS (SB * kBlkBytes) into every wave's operand registers; 1/|k_i| of the rows to inv_s.  Read straight
+    // into operand layout by every wave, 96 rows take 192 loads of 32 rows each, about 1.5 us of the start.  Ends with a barrier.
+    __device__ __forceinline__ void spread(unsigned char *smem, float *inv_s, int tid, bf16x8 (&q)[SB][kSteps])
+    {
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hh = lane >> 5;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + kWave * kOwnWaves * u;
+            *reinterpret_cast<u32x4 *>(smem + (at >> 4) * kPitch + (at & 15) * 16) = piece[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < SB; ++g) {
+            tile_read(smem, g, l32, hh, q[g]);
+            if (wv == g) {
+                const float inv = inv_norm(add_other_half(half_row_sumsq(q[g])));
+                if (hh == 0) inv_s[kBlk * g + l32] = inv;
+            }
+        }
+        __syncthreads();
+    }
+};
+
+// Bound pass without counting: the sample is dealt out to groups of keys, 256 of them a workgroup (a group is what one
+// lane position of one wave meets), every group keeps its largest edge in a register, and the bound is the rank-th
+// largest of the groups' maxima -- at least `rank` sampled edges reach it, as they do the rank-th largest edge itself, and
+// hardly any more do while the rank is small against the number of groups (5 % more at rank 26).  Two
+// vector instructions an edge and no LDS.  (Counted into a histogram, 32 lanes hit the thirty or so bins in which the
+// edges of one source lie, and the bound is only as fine as a bin.)
+constexpr int kGroups = 256;
+constexpr int kMaximaRank = 64;   // beyond it the maxima of 256 groups are too loose (15 % more edges reach the bound)
+template <int SB> constexpr int maxima_lds_bytes() { return SB * kBlk * kGroups * 4; }   // (more than the key blocks take)
+
+// A workgroup's source rows against n_cols >= 32 sampled keys (column c = row c * key_stride of Kh): vals [ROWS][kGroups]
+// gets the groups' largest edges, -inf where a group has none.  Any 256 consecutive columns are of different
+// groups, so that keys that are alike and neighbours don't hide behind one another.  Ends with a barrier.
+template <int SB>
+__device__ __forceinline__ void sample_maxima(const uint16_t *Ah, const uint16_t *Kh, const int32_t *src_h, int Sh, int s_base,
+                                              int n_cols, int key_stride, unsigned char *smem, float *inv_s, int tid)
+{
+    constexpr int NW = kOwnWaves;
+    static_assert(maxima_lds_bytes<SB>() >= SB * kBlkBytes, "the rows' way through the LDS");
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hh = lane >> 5;
+    const int nblk = (n_cols + kBlk - 1) / kBlk;
+    // (the last block of the sample starts early, as in the filter pass)
+    auto block_first = [&](int b) { return min(kBlk * b, n_cols - kBlk); };
+    const uint32_t row_bytes = (uint32_t)key_stride * (kD * 2), off = (uint32_t)(lane >> 4) * row_bytes + (lane & 15) * 16u;
+    u32x4 stage[8];
+    auto load_block = [&](int b) {
+        const char *p = reinterpret_cast<const char *>(Kh) + (size_t)block_first(b) * row_bytes;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) stage[u] = *reinterpret_cast<const u32x4 *>(p + (off + 4u * u * row_bytes));
+    };
+    SourcePieces<SB> sp;
+    sp.load(Ah, src_h, Sh, s_base, tid);
+    load_block(min(wv, nblk - 1));
+    bf16x8 q[SB][kSteps];
+    sp.spread(smem, inv_s, tid, q);
+
+    float best[SB][16];
+#pragma unroll
+    for (int g = 0; g < SB; ++g)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) best[g][i] = -INFINITY;
+    unsigned char *mine = smem + wv * kBlkBytes;
+    for (int b = wv; b < nblk; b += NW) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            *reinterpret_cast<u32x4 *>(mine + (4 * u + (lane >> 4)) * kPitch + (lane & 15) * 16) = stage[u];
+        load_block(min(b + NW, nblk - 1));
+        wave_sync();
+        bf16x8 kc[kSteps];
+        tile_read(mine, 0, l32, hh, kc);
+        const int col = block_first(b) + l32;
+        const float sq = add_other_half(half_row_sumsq(kc));
+        const float inv_k = col >= kBlk * b ? inv_norm(sq) : NAN;   // (a maximum passes NaN by)
+#pragma unroll
+        for (int g = 0; g < SB; ++g) {
+            f32x16 acc;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s)   // rows = sources, columns = keys
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[g][s], kc[s], acc, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) best[g][i] = fmaxf(best[g][i], acc[i] * inv_k);
+        }
+        wave_sync();
+    }
+    __syncthreads();   // the key blocks' place is free
+    float *vals = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int g = 0; g < SB; ++g)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int row = kBlk * g + acc_row(i, hh);
+            vals[row * kGroups + kBlk * wv + l32] = best[g][i] * inv_s[row];   // the dense kernel's edge
+        }
+    __syncthreads();
+}
+
+// Waves wv, wv + kOwnWaves, ..: the bounds of their rows < n_rows, tau_of(row, bound), from vals [n_rows][kGroups] in LDS: the
+// rank-th largest value, rounded down to a multiple of 1/1024 between -1 and 1 (-inf: fewer reach -1).  Halved eleven
+// times, a vote per register and step, four rows side by side so that one's votes are counted while another's compare.
+// A row whose own column, which is no neighbour (Eq. 3: j != i), is among the sampled keys needs a value more.
+template <typename Out>
+__device__ __forceinline__ void bounds_from_maxima(const float *vals, int n_rows, const int32_t *src_rows, int key_stride, int rank,
+                                                   int wv, int lane, Out &&out)
+{
+    constexpr int V = kGroups / kWave, RB = 4;
+    for (int r0 = wv; r0 < n_rows; r0 += RB * kOwnWaves) {
+        float v[RB][V];
+        int need[RB], lo[RB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) {
+            const int row = min(r0 + k * kOwnWaves, n_rows - 1);
+#pragma unroll
+            for (int u = 0; u < V; ++u) v[k][u] = vals[row * kGroups + lane + kWave * u];
+            need[k] = rank + (src_rows[row] % key_stride == 0 ? 1 : 0);
+        }
+        auto reach = [&](int k, int t) {
+            const float x = (float)t * (1.f / 1024.f);
+            int c = 0;
+#pragma unroll
+            for (int u = 0; u < V; ++u) c += (int)__popcll(__ballot(v[k][u] >= x));
+            return c >= need[k];
+        };
+        bool any[RB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) { lo[k] = -1024; any[k] = reach(k, -1024); }
+#pragma unroll
+        for (int step = 1024; step > 0; step >>= 1)
+#pragma unroll
+            for (int k = 0; k < RB; ++k) lo[k] = reach(k, lo[k] + step) ? lo[k] + step : lo[k];
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            if (lane == 0 && r0 + k * kOwnWaves < n_rows) out(r0 + k * kOwnWaves, any[k] ? (float)lo[k] * (1.f / 1024.f) : -INFINITY);
+    }
+}
+
+// The same from kParts values a row in memory, where a chunk each of a short head's sample left some: all rows of a wave
+// at once through histograms of 128 bins (hist: [kOwnWaves][PER][128] words of LDS), a pair of bins a lane, then four
+// halvings of the bin.  (Twelve halvings a row took 10 us of the filter pass, more than the launch that
+// added up the chunks' histograms before; bounds left at the lower edge of a bin let lists of keys that are alike
+// and neighbours overflow their slices.)
+constexpr int kParts = 128;
+template <int ROWS, typename Out>
+__device__ __forceinline__ void bounds_from_parts(const float *part, int n_rows, const int32_t *src_rows, int key_stride, int rank,
+                                                  uint32_t *hist, int wv, int lane, Out &&out)
+{
+    constexpr int PER = ROWS / kOwnWaves;
+    uint2 *mine = reinterpret_cast<uint2 *>(hist + wv * PER * 128);
+    float2 v[PER];
+    int own[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int row = min(wv + k * kOwnWaves, n_rows - 1);
+        v[k] = *reinterpret_cast<const float2 *>(part + (long)row * kParts + 2 * lane);
+        own[k] = src_rows[row];
+        mine[k * kWave + lane] = make_uint2(0u, 0u);
+    }
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const float x[2] = {v[k].x, v[k].y};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int b = (int)fminf((x[u] + 1.f) * 64.f, 127.f);   // (the filter pass lowers bounds by more than this rounds)
+            if (x[u] >= -1.f) atomicAdd(reinterpret_cast<uint32_t *>(&mine[k * kWave]) + 127 - b, 1u);   // highest first
+        }
+    }
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const uint2 c = mine[k * kWave + lane];
+        const uint32_t need = (uint32_t)(rank + (own[k] % key_stride == 0 ? 1 : 0));
+        const uint32_t upto = wave_scan_add(c.x + c.y);   // in this lane's bins and all higher ones
+        const uint64_t reached = __ballot(upto >= need);
+        const int row = wv + k * kOwnWaves;
+        float lo = -INFINITY;
+        if (reached) {   // (the same in all lanes from here on)
+            const int first = __ffsll((unsigned long long)reached) - 1;
+            const uint32_t high = (uint32_t)__builtin_amdgcn_readlane((int)(upto - c.y), first);
+            const int bin = 127 - 2 * first - (high >= need ? 0 : 1);
+            lo = (float)bin * (1.f / 64.f) - 1.f;
+#pragma unroll
+            for (int half = 1; half <= 4; ++half) {
+                const float t = lo + 1.f / (float)(64 << half);
+                if ((uint32_t)(__popcll(__ballot(v[k].x >= t)) + __popcll(__ballot(v[k].y >= t))) >= need) lo = t;
+            }
+        }
+        if (lane == 0 && row < n_rows) out(row, lo);
+    }
+}
+
+// Parts of the sample (blockIdx.z of them, every so many-th column) when there are few heads: each leaves per_chunk values
+// a row in part [head, source group][ROWS][kParts], its 256 taken together by their largest, and the filter pass
+// takes the bounds from all of them.  (Consecutive columns go to different parts for the same reason as to different groups.)
+template <int SB>
+__global__ __launch_bounds__(kWave * kOwnWaves) void cosine_maxima_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride, int S, int src_pitch,
+    const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int rank, int per_chunk,
+    float *__restrict__ part, float *__restrict__ tau, int pitch, int row0, int32_t *__restrict__ overflow)
+{
+    constexpr int ROWS = SB * kBlk, NT = kWave * kOwnWaves;
+    __shared__ float inv_s[ROWS];
+    extern __shared__ __align__(16) unsigned char smem[];   // key blocks, then the groups' maxima
+    const float *vals = reinterpret_cast<const float *>(smem);
+    const int h = blockIdx.y, s_base = blockIdx.x * ROWS, chunk = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blockIdx.x == 0 && chunk == 0 && tid == 0) overflow[h] = 0;
+    // rows of this head's source list in use
+    const int Sh = n_src ? n_src[h] : S;
+    if (s_base >= Sh) return;
+    const int parts = gridDim.z;
+    const int32_t *src_h = src + (long)h * src_pitch;
+    sample_maxima<SB>(Ac + (long)h * N * kD, Kc + ((long)h * N + chunk * key_stride) * kD, src_h, Sh, s_base,
+                      (n_cols - chunk + parts - 1) / parts, key_stride * parts, smem, inv_s, tid);
+    if (parts > 1) {
+        float *out = part + ((long)h * gridDim.x + blockIdx.x) * ROWS * kParts + chunk * per_chunk;
+        for (int u = tid; u < ROWS * per_chunk; u += NT) {
+            const int row = u / per_chunk, o = u % per_chunk;
+            float best = -INFINITY;
+            for (int k = o; k < kGroups; k += per_chunk) best = fmaxf(best, vals[row * kGroups + k]);
+            out[row * kParts + o] = best;
+        }
+        if (chunk == parts - 1) {   // (and nothing in what is left)
+            const int left = kParts - per_chunk * parts;
+            for (int u = tid; u < ROWS * left; u += NT) out[(u / left) * kParts + per_chunk + u % left] = -INFINITY;
+        }
+        return;
+    }
+    float *tau_h = tau + (long)h * pitch + row0 + s_base;
+    bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, key_stride, rank, wv, lane, [&](int row, float t) { tau_h[row] = t; });
+}
+
 // Filter pass over all keys, barrier-free: a wave holds all source rows of its workgroup (SB groups of 32) in
 // registers and takes key blocks of 32 on its own, copying each through a piece of LDS that nobody else touches.
 // The loads of its next block are in flight while it works on one; the eight waves of a workgroup share nothing
@@ -348,16 +606,13 @@ __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__rest
 // redone exactly, row by row.
 constexpr int kStagePitch = 80;    // bytes per parked row: 16 dots, |k|^2, key, first row of the group (76, padded)
 constexpr int kRing = 64;          // rows of a ring: up to 31 waiting and a group's 32
-constexpr int kFilterWaves = 8;    // two per SIMD: 256 registers each
-constexpr int kBlkBytes = kBlk * kPitch;
-constexpr int kFilterLdsBytes = kFilterWaves * (kBlkBytes + 2 * kRing * kStagePitch);
+constexpr int kFilterLdsBytes = kOwnWaves * (kBlkBytes + 2 * kRing * kStagePitch);
 
 template <int SB> struct FilterLds {
     static constexpr int ROWS = SB * kBlk;
     float inv_s[ROWS];
     __align__(16) float det_s[ROWS];
     __align__(16) uint4 test_s[2][ROWS];   // the source's operand of the test: what each half-wave holds
-    int32_t idx_s[ROWS];
     int32_t row_pos[ROWS];     // entries written to each source's slice
     int32_t idle_pos[kWave];   // takes the additions of 0 of hits that are not there
 };
@@ -371,16 +626,17 @@ __device__ __forceinline__ uint32_t two_bf16(float x)
 }
 
 // One chunk of head h's keys against source rows s_base .. of the Sh in use; smem: kFilterLdsBytes.
-// tau_of(r): bound of row s_base + r.  ONCE: no other workgroup reads these keys, so they need not stay in the L2;
+// take_bounds(): called first, by all threads; tau_of(r): bound of row s_base + r.  ONCE: no other workgroup reads these keys, so they need not stay in the L2;
 // the candidate lists' lines then do until they are full (256 heads of 32768 keys 468 -> 384 us, 390 without the
 // lists' stores; where a second
 // workgroup finds the keys there, 128 sources and 131072 keys, 2.45 -> 2.84 ms).
-template <int SB, bool ONCE, typename TauOf>
+template <int SB, bool ONCE, typename Take, typename TauOf>
 __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t *Kc, int N, int n_cols, const int32_t *src,
-                                             int chunk_cols, const FilterArgs &fa, int h, int chunk, int n_chunks, int Sh,
-                                             int s_base, FilterLds<SB> &F, unsigned char *smem, int tid, TauOf &&tau_of)
+                                             int chunk_cols, const FilterArgs &fa, int h, int chunk, int Sh,
+                                             int s_base, FilterLds<SB> &F, unsigned char *smem, int tid, Take &&take_bounds,
+                                             TauOf &&tau_of)
 {
-    constexpr int ROWS = SB * kBlk, NW = kFilterWaves;
+    constexpr int ROWS = SB * kBlk, NW = kOwnWaves;
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hh = lane >> 5;
     const uint16_t *Kh = Kc + (long)h * N * kD;
     const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
@@ -399,37 +655,12 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     };
     load_block(min(wv, nblk - 1));
 
-    // The source rows pass through the LDS once for all waves (slots beyond Sh repeat the last source): read straight
-    // into operand layout by every wave they take 192 loads of 32 rows each, about 1.5 us of the start.
+    SourcePieces<SB> sp;
+    sp.load(Ac + (long)h * N * kD, src + (long)h * fa.src_pitch, Sh, s_base, tid);
+    take_bounds();
+    if (tid < ROWS) F.row_pos[tid] = 0;
     bf16x8 q[SB][kSteps];
-    {
-        const uint16_t *Ah = Ac + (long)h * N * kD;
-        const int32_t *src_h = src + (long)h * fa.src_pitch;
-        constexpr int PER = ROWS * 16 / (64 * NW);   // 16-byte pieces per thread
-        u32x4 piece[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int at = tid + 64 * NW * u;
-            const int32_t i = src_h[min(s_base + (at >> 4), Sh - 1)];
-            piece[u] = *reinterpret_cast<const u32x4 *>(Ah + (long)i * kD + 8 * (at & 15));
-        }
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int at = tid + 64 * NW * u;
-            *reinterpret_cast<u32x4 *>(smem + (at >> 4) * kPitch + (at & 15) * 16) = piece[u];
-        }
-        if (tid < ROWS) F.row_pos[tid] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < SB; ++g) {
-            tile_read(smem, g, l32, hh, q[g]);
-            if (wv == g) {
-                const float inv = inv_norm(add_other_half(half_row_sumsq(q[g])));
-                if (hh == 0) F.inv_s[kBlk * g + l32] = inv;
-            }
-        }
-    }
-    __syncthreads();
+    sp.spread(smem, F.inv_s, tid, q);
     if (tid < ROWS) {
         // det: what dot / |k_j| must reach for the edge to be listed, i.e. the source's bound,
         // lowered by twice the slack, divided by 1/|k_i|.  Rows past the last source and
@@ -458,8 +689,7 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     unsigned char *mine = smem + wv * (kBlkBytes + 2 * kRing * kStagePitch);   // this wave's block, then its two rings
     unsigned char *ring = mine + kBlkBytes + hh * (kRing * kStagePitch);
     const uint64_t half_before = (hh ? 0xffffffff00000000ull : 0x00000000ffffffffull) & ((1ull << lane) - 1ull);
-    uint2 *slice0 = fa.cand + (buf_row0 * n_chunks + chunk) * fa.slice_cap;
-    const long slice_row_stride = (long)n_chunks * fa.slice_cap;
+    uint2 *slice0 = fa.cand + buf_row0 * fa.row_slots + (long)chunk * fa.slice_cap;
     // rows ever parked / ever drained by the lower and the upper half-wave (same in every lane)
     int tail0 = 0, tail1 = 0, head0 = 0, head1 = 0;
 
@@ -514,7 +744,7 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (((validk >> k) & 1u) && atk[k] < fa.slice_cap)
-                    slice0[rowk[k] * slice_row_stride + atk[k]] =
+                    slice0[rowk[k] * fa.row_slots + atk[k]] =
                         make_uint2(__float_as_uint((dotk[k] * inv_k) * invk[k]), key);
             while (hits) {   // keys close to many sources at once
                 const int i = __ffs(hits) - 1;
@@ -522,7 +752,7 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
                 const int row = row0 + acc_row(i, 0);
                 const float e = (reinterpret_cast<const float *>(row_mem)[i] * inv_k) * F.inv_s[row];
                 const int at = atomicAdd(&F.row_pos[row], 1);
-                if (at < fa.slice_cap) slice0[row * slice_row_stride + at] = make_uint2(__float_as_uint(e), key);
+                if (at < fa.slice_cap) slice0[row * fa.row_slots + at] = make_uint2(__float_as_uint(e), key);
             }
         }
         wave_sync();
@@ -589,13 +819,13 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     __syncthreads();      // every candidate is counted
     if (tid < ROWS && s_base + tid < Sh) {
         const int c = F.row_pos[tid];
-        fa.cand_cnt[(buf_row0 + tid) * n_chunks + chunk] = c < fa.slice_cap ? c : fa.slice_cap;
+        fa.cand_cnt[(buf_row0 + tid) * fa.chunk_slots + chunk] = c < fa.slice_cap ? c : fa.slice_cap;
         if (c > fa.slice_cap) fa.overflow[h] = 1;
     }
 }
 
 template <int SB, bool ONCE>
-__global__ __launch_bounds__(64 * kFilterWaves) void cosine_filter_kernel(
+__global__ __launch_bounds__(kWave * kOwnWaves) void cosine_filter_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
     const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa)
 {
@@ -621,10 +851,31 @@ __global__ __launch_bounds__(64 * kFilterWaves) void cosine_filter_kernel(
     if (chunk * chunk_cols >= n_cols) return;
     const int Sh = fa.n_src ? fa.n_src[h] : S;
     if (s_base >= Sh) return;
-    const float *tau = fa.tau + (long)h * fa.pitch + fa.row0 + s_base;
-    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, n_chunks, Sh, s_base, F, smem, threadIdx.x,
-                     [&](int r) { return tau[r]; });
+    __shared__ float tau_s[ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto take_bounds = [&] {
+        if (fa.part) {
+            static_assert(ROWS * 128 * 4 <= kFilterLdsBytes, "the histograms take the blocks' and rings' place");
+            bounds_from_parts<ROWS>(fa.part + ((long)h * fa.sgroups + s_base / ROWS) * ROWS * kParts, min(ROWS, Sh - s_base),
+                                    src + (long)h * fa.src_pitch + s_base, fa.key_stride, fa.rank,
+                                    reinterpret_cast<uint32_t *>(smem), wv, lane, [&](int row, float t) { tau_s[row] = t; });
+            __syncthreads();
+        } else if (tid < ROWS && s_base + tid < Sh) {
+            tau_s[tid] = fa.tau[(long)h * fa.pitch + fa.row0 + s_base + tid];
+        }
+    };
+    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, tid, take_bounds,
+                           [&](int r) { return tau_s[r]; });
 }
+
+// How a candidate row's entries lie: in one slice per key chunk of the pass that listed them.  From the second round on the
+// rows below `late_rows` hold lists of that round's own pass.
+struct Slices {
+    long row_slots;
+    int chunk_slots, chunks, slice_cap, late_rows, late_chunks, late_cap;
+    __device__ __forceinline__ int chunks_of(int row) const { return row < late_rows ? late_chunks : chunks; }
+    __device__ __forceinline__ int cap_of(int row) const { return row < late_rows ? late_cap : slice_cap; }
+};
 
 constexpr int kTieRoom = 64;   // entries tied at the cut that a select lists beyond the m winners
 
@@ -658,8 +909,7 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
                                                          const int32_t *__restrict__ cand_cnt,
                                                          int32_t *__restrict__ overflow,
                                                          const int32_t *__restrict__ src, int S, int pitch,
-                                                         int chunks, int slice_cap, int cap, int m,
-                                                         SelectRows sel, int32_t *__restrict__ nbr,
+                                                         Slices sl, int cap, int m, SelectRows sel, int32_t *__restrict__ nbr,
                                                          float *__restrict__ nbr_e)
 {
     extern __shared__ __align__(8) uint32_t dyn[];
@@ -684,16 +934,17 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
         const long at = (long)h * S + x;
         crow_r = sel.row ? sel.row[at] : x;
         pos_r = sel.pos ? sel.pos[at] : x;
-        cnt_r = tid < chunks ? cand_cnt[((long)h * pitch + crow_r) * chunks + tid] : 0;
+        cnt_r = tid < sl.chunks_of(crow_r) ? cand_cnt[((long)h * pitch + crow_r) * sl.chunk_slots + tid] : 0;
         self_r = src[(long)h * S + pos_r];
     };
     int32_t cnt_r = 0, self_r = 0, pos_r = 0, crow_r = 0;
     int search_steps = 0;   // bisection steps over the slices
-    while ((1 << search_steps) < chunks) ++search_steps;
+    while ((1 << search_steps) < sl.chunk_slots) ++search_steps;
     if ((int)blockIdx.x < n_rows) ask(blockIdx.x, cnt_r, self_r, pos_r, crow_r);
 
     for (int x = blockIdx.x; x < n_rows; x += gridDim.x) {
         const long row = (long)h * pitch + crow_r;
+        const int chunks = sl.chunks_of(crow_r), slice_cap = sl.cap_of(crow_r);
         int incl = cnt_r;   // running total of the slice sizes
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -714,7 +965,7 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
         }
         const uint32_t self = s_self;
         const long out_row = (long)h * S + s_pos;
-        const uint2 *slices = cand + row * chunks * (long)slice_cap;
+        const uint2 *slices = cand + row * sl.row_slots;
         // where entry r of the concatenated slices sits: the first slice that ends behind it
         auto locate = [&](int r) {
             int lo = 0, hi = chunks - 1;
@@ -879,7 +1130,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
                                                               const int32_t *__restrict__ cand_cnt,
                                                               int32_t *__restrict__ overflow,
                                                               const int32_t *__restrict__ src, int S, int pitch,
-                                                              int chunks, int slice_cap, int m, SelectRows sel,
+                                                              Slices sl, int m, SelectRows sel,
                                                               int32_t *__restrict__ nbr,
                                                               float *__restrict__ nbr_e)
 {
@@ -899,8 +1150,9 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
     for (int x = blockIdx.x * waves + wv; x < n_rows; x += gridDim.x * waves) {
         const int crow = sel.row ? sel.row[(long)h * S + x] : x, pos = sel.pos ? sel.pos[(long)h * S + x] : x;
         const long row = (long)h * pitch + crow;
-        const uint2 *slices = cand + row * chunks * (long)slice_cap;
-        const int cnt = lane < chunks ? cand_cnt[row * chunks + lane] : 0;
+        const int chunks = sl.chunks_of(crow), slice_cap = sl.cap_of(crow);
+        const uint2 *slices = cand + row * sl.row_slots;
+        const int cnt = lane < chunks ? cand_cnt[row * sl.chunk_slots + lane] : 0;
         const uint32_t self = (uint32_t)src[(long)h * S + pos];
         const long out_row = (long)h * S + pos;
         const int incl = (int)wave_scan_add((uint32_t)cnt);   // slice sizes -> where each slice ends in the list
@@ -1049,32 +1301,35 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
     }
 }
 
-// A later round's bound and filter passes in one launch, for few heads: nearly always no head has a new source, and
-// then what counts is the launches.  Every workgroup of a head with new sources takes the bound from the whole sample
-// itself and filters its chunk, which lasts as long as one workgroup's walk over the sample in front of the others'
-// filter as long as each has a compute unit to itself.
-__global__ __launch_bounds__(kThreads) void late_filter_kernel(
-    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols,
-    const int32_t *__restrict__ new_src, int chunk_cols, FilterArgs fa, int sample_cols, int key_stride, int rank)
+// Bound and filter passes in one launch; every workgroup takes the bounds of its rows from the whole sample itself.  In the
+// first round where a head is one workgroup (S rows, the head's flag is cleared here): a launch, the way of the sources
+// into the registers and the tail of a round of workgroups less.  In a later round (new sources only, n_src of
+// them) for few heads: nearly always no head has one, and then what counts is the launches; with some, the walk over
+// the sample is in front of every chunk's filter as long as each workgroup has a compute unit to itself.
+template <int SB, bool ONCE>
+__global__ __launch_bounds__(kWave * kOwnWaves) void bound_filter_kernel(
+    const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
+    const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa, int sample_cols)
 {
-    constexpr int BINS = 256, NW = kThreads / kWave;
-    __shared__ FilterLds<kSB> F;
-    __shared__ float tau_s[kRows];
-    extern __shared__ __align__(16) unsigned char smem[];   // two key tiles, then the histograms, then the rings
-    const int h = blockIdx.y, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * kRows;
-    const int Sh = fa.n_src[h];
+    constexpr int ROWS = SB * kBlk;
+    static_assert(maxima_lds_bytes<SB>() <= kFilterLdsBytes, "the groups' maxima take the blocks' and rings' place");
+    __shared__ FilterLds<SB> F;
+    __shared__ float tau_s[ROWS];
+    extern __shared__ __align__(16) unsigned char smem[];   // key blocks, the groups' maxima, the filter pass's
+    const int h = blockIdx.y, chunk = blockIdx.x / fa.sgroups, s_base = (blockIdx.x % fa.sgroups) * ROWS;
+    const int Sh = fa.n_src ? fa.n_src[h] : S;
     if (s_base >= Sh) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);
-    count_sample<kSB, BINS>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, new_src + (long)h * fa.src_pitch, Sh, s_base, 0,
-                            sample_cols, key_stride, smem, hist, F.inv_s, F.idx_s, tid);
-    for (int r = wv; r < kRows; r += NW) {
-        const uint4 w4 = histogram_words<BINS>(&hist[r * BINS], lane);
-        bound_from_histogram<BINS>(w4, rank, lane, &tau_s[r]);
-    }
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t *src_h = src + (long)h * fa.src_pitch;
+    if (!fa.n_src && tid == 0) fa.overflow[h] = 0;
+    sample_maxima<SB>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, src_h, Sh, s_base, sample_cols, fa.key_stride, smem,
+                      F.inv_s, tid);
+    const float *vals = reinterpret_cast<const float *>(smem);
+    bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, fa.key_stride, fa.rank, wv, lane,
+                       [&](int row, float t) { tau_s[row] = t; });
     __syncthreads();
-    filter_chunk<kSB, false>(Ac, Kc, N, n_cols, new_src, chunk_cols, fa, h, chunk, gridDim.x / fa.sgroups, Sh, s_base, F, smem,
-                      tid, [&](int r) { return tau_s[r]; });
+    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, tid, [] {},
+                           [&](int r) { return tau_s[r]; });
 }
 
 // Matching on its own, for source lists the few-winners selection does not take (S > 256).
@@ -1230,16 +1485,17 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
         return sc > g.cand_cap ? (long)g.cand_cap : sc;
     };
     // The memory for a row's slices is what this cut's take (at most 256 of them: the exact select keeps the slice sizes
-    // of a source in LDS).  The pass makes more chunks than that only where their slices take little; with
-    // fewer chunks a slice is the longer.
+    // of a source in LDS), and a later round's passes make no fewer chunks: a few heads with new sources among many
+    // without must not be a workgroup each.  The first round's pass makes more chunks than that only where their
+    // slices take little; with fewer chunks a slice is the longer.
     int cols = chunk_cols_for(Hkv, sgroups, P), chunks = (P + cols - 1) / cols;
     if (chunks > 256) {
         cols = (((P + 255) / 256 + 127) / 128) * 128;
         chunks = (P + cols - 1) / cols;
     }
-    g.chunk_cols = cols;
-    g.chunks = g.chunk_slots = chunks;
-    g.slice_cap = (int)slice_for(chunks);
+    g.late_cols = g.chunk_cols = cols;
+    g.late_chunks = g.chunks = g.chunk_slots = chunks;
+    g.late_slice_cap = g.slice_cap = (int)slice_for(chunks);
     g.row_slots = (long)chunks * g.slice_cap;
     if (short_slices) return g;
     int most = 256;
@@ -1247,8 +1503,9 @@ MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, b
     g.chunk_cols = filter_cols_for(Hkv, sgroups, P, most);
     g.chunks = (P + g.chunk_cols - 1) / g.chunk_cols;
     if (g.chunks > chunks) {
-        g.chunk_slots = g.chunks;
-        g.slice_cap = (int)slice_for(g.chunks);
+        g.late_cols = g.chunk_cols;
+        g.late_chunks = g.chunk_slots = g.chunks;
+        g.late_slice_cap = g.slice_cap = (int)slice_for(g.chunks);
         g.row_slots = (long)g.chunks * g.slice_cap;
     } else {
         g.slice_cap = (int)(g.row_slots / g.chunks);
@@ -1285,6 +1542,36 @@ int bound_chunks(int Hkv, int P, int sgroups)
     return chunks < 1 ? 1 : chunks;
 }
 
+// Chunks of the sample whose maxima the filter pass puts together itself (1: the bound pass writes the bounds).  In later
+// rounds there are usually no sources without a list, and one workgroup walks the whole sample.  (With a sample half as
+// large more of the lists of such sources overflow: three enhanced rounds of 8 heads, mean of eight inputs, us, half /
+// whole sample: 32736 keys 367 / 338, 65504 469 / 415, 131040 719 / 546, and no difference where there are none.)
+int maxima_chunks(int Hkv, int P, int sgroups, int rank, bool late)
+{
+    return late || rank > kMaximaRank ? 1 : min(bound_chunks(Hkv, P, sgroups), kParts / 2);
+}
+int values_per_chunk(int chunks)
+{
+    int n = kParts;
+    while (n * chunks > kParts) n /= 2;
+    return n;
+}
+
+template <int SB>
+hipError_t launch_maxima(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int rank, const int32_t *src,
+                         int src_pitch, const int32_t *n_src, bool late, void *part, float *tau, int pitch, int row0,
+                         int32_t *overflow, hipStream_t st)
+{
+    constexpr int ROWS = SB * kBlk;
+    const Sample smp = sample_of(P);
+    const int sgroups = (rows + ROWS - 1) / ROWS, chunks = maxima_chunks(Hkv, P, sgroups, rank, late);
+    if (!allow_big_lds((const void *)cosine_maxima_kernel<SB>)) return hipGetLastError();
+    hipLaunchKernelGGL(cosine_maxima_kernel<SB>, dim3(sgroups, Hkv, chunks), dim3(kWave * kOwnWaves), maxima_lds_bytes<SB>(), st,
+                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols, smp.stride, rows, src_pitch, src, n_src, rank,
+                       values_per_chunk(chunks), (float *)part, tau, pitch, row0, overflow);
+    return hipGetLastError();
+}
+
 template <int SB, int BINS>
 hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                         int src_pitch, const int32_t *n_src, bool late, void *hist_part, float *tau, int pitch,
@@ -1293,13 +1580,11 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     constexpr int ROWS = SB * kBlk;
     const Sample smp = sample_of(P);
     const int sgroups = (rows + ROWS - 1) / ROWS;
-    // In later rounds there are usually no sources without a list, so one workgroup walks the whole sample and the
-    // launch that adds chunks up is saved (4.6 us a round).  (With a sample half as large more of the lists of
-    // such sources overflow: three enhanced rounds of 8 heads, mean of eight inputs, us, half / whole sample:
-    // 32736 keys 367 / 338, 65504 469 / 415, 131040 719 / 546, and no difference where there are none.)
     const int chunks = late ? 1 : bound_chunks(Hkv, P, sgroups);
     const int chunk_cols = (((smp.cols + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
     const int rank = mfma_bound_rank(m, smp.stride);
+    if (rank <= kMaximaRank)
+        return launch_maxima<SB>(Ac, Kc, Hkv, N, P, rows, rank, src, src_pitch, n_src, late, hist_part, tau, pitch, row0, overflow, st);
     if (!allow_big_lds((const void *)cosine_bound_kernel<SB, BINS>)) return hipGetLastError();
     hipLaunchKernelGGL((cosine_bound_kernel<SB, BINS>), dim3(sgroups, Hkv, chunks), dim3(256 * SB),
                        2 * kTileBytes + ROWS * BINS * 4, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols,
@@ -1311,19 +1596,36 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     return hipGetLastError();
 }
 
+// Whether the first round's filter pass takes the bounds itself (a later round's: late_filter_applies()).
+bool filter_takes_bounds(int P, int m, const MfmaFilterPlan &g)
+{
+    return g.chunks == 1 && g.S + g.X <= kBlk * g.sb && mfma_bound_rank(m, sample_of(P).stride) <= kMaximaRank;
+}
+
 template <int SB>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
-                         int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, int row0,
-                         const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
+                         int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, bool late, bool with_bounds,
+                         const void *part, const float *tau, void *cand, int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
-    constexpr int ROWS = SB * kBlk;
-    const int sgroups = (rows + ROWS - 1) / ROWS;
-    FilterArgs fa{n_src, tau, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, sgroups, src_pitch, g.pitch, row0};
+    const int sgroups = (rows + SB * kBlk - 1) / (SB * kBlk);
+    const Sample smp = sample_of(P);
+    const int rank = mfma_bound_rank(m, smp.stride), parts = maxima_chunks(Hkv, P, sgroups, rank, late);
+    FilterArgs fa{n_src, tau, parts > 1 ? (const float *)part : nullptr, rank, smp.stride, (uint2 *)cand, cand_cnt, overflow,
+                  g.row_slots, g.chunk_slots, late ? g.late_slice_cap : g.slice_cap, sgroups, src_pitch, g.pitch, 0};
     const bool once = sgroups == 1 && reads_past_caches((size_t)Hkv * N * kD * 2);
+    const dim3 grid((late ? g.late_chunks : g.chunks) * sgroups, Hkv), block(kWave * kOwnWaves);
+    const int cols = late ? g.late_cols : g.chunk_cols;
+    if (with_bounds) {
+        auto *kernel = once ? bound_filter_kernel<SB, true> : bound_filter_kernel<SB, false>;
+        if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
+        hipLaunchKernelGGL(kernel, grid, block, kFilterLdsBytes, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, rows, src,
+                           cols, fa, smp.cols);
+        return hipGetLastError();
+    }
     auto *kernel = once ? cosine_filter_kernel<SB, true> : cosine_filter_kernel<SB, false>;
     if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
-    hipLaunchKernelGGL(kernel, dim3(g.chunks * sgroups, Hkv), dim3(64 * kFilterWaves), kFilterLdsBytes, st,
-                       (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, rows, src, g.chunk_cols, fa);
+    hipLaunchKernelGGL(kernel, grid, block, kFilterLdsBytes, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, rows, src, cols,
+                       fa);
     return hipGetLastError();
 }
 
@@ -1342,6 +1644,7 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
                                     const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
                                     hipStream_t st)
 {
+    if (first_round && filter_takes_bounds(P, m, g)) return hipSuccess;
     if (first_round && g.sb == 3)
         return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false,
                                     hist_part, tau, g.pitch, 0, overflow, st);
@@ -1351,14 +1654,15 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
 
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
-                                     const int32_t *n_src, const float *tau, void *cand, int32_t *cand_cnt,
-                                     int32_t *overflow, hipStream_t st)
+                                     const int32_t *n_src, const void *hist_part, const float *tau, void *cand,
+                                     int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
+    const bool with_bounds = first_round && filter_takes_bounds(P, m, g);
     if (first_round && g.sb == 3)
-        return launch_filter<3>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, 0, tau, cand,
-                                    cand_cnt, overflow, st);
-    return launch_filter<2>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, 0, tau, cand, cand_cnt,
-                                overflow, st);
+        return launch_filter<3>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, false, with_bounds, hist_part, tau,
+                                cand, cand_cnt, overflow, st);
+    return launch_filter<2>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, g, !first_round, with_bounds, hist_part, tau, cand,
+                            cand_cnt, overflow, st);
 }
 
 hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv, hipStream_t st)
@@ -1372,24 +1676,17 @@ hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv,
 // 236.7 / 233.0.  Many, from key norms: 16K keys, 64 sources, 128 workgroups 221.7 / 217.5; 128 sources, 256 277 / 274;
 // 192 sources, 384 372 / 418; 64K keys, 64 sources, 512 656 / 813.  The lists selected in the same launch, by the
 // workgroup that finishes last: 101.3 without new sources, but 326 and 773 with 64 and 192 and many of them new.)
-bool late_filter_applies(int Hkv, const MfmaFilterPlan &g)
+bool late_filter_applies(int Hkv, int P, int m, const MfmaFilterPlan &g)
 {
-    return (long)Hkv * g.chunks * ((g.S + kRows - 1) / kRows) <= 256;
+    return mfma_bound_rank(m, sample_of(P).stride) <= kMaximaRank && (long)Hkv * g.late_chunks * ((g.S + kRows - 1) / kRows) <= 256;
 }
 
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
                               int32_t *overflow, hipStream_t st)
 {
-    const int sgroups = (g.S + kRows - 1) / kRows;
-    const Sample smp = sample_of(P);
-    FilterArgs fa{n_new, nullptr, (uint2 *)cand, cand_cnt, overflow, g.slice_cap, sgroups, g.S, g.pitch, 0};
-    static_assert(2 * kTileBytes + kRows * 256 * 4 <= kFilterLdsBytes, "the histograms take the rings' place");
-    if (!allow_big_lds((const void *)late_filter_kernel)) return hipGetLastError();
-    hipLaunchKernelGGL(late_filter_kernel, dim3(g.chunks * sgroups, Hkv), dim3(kThreads),
-                       kFilterLdsBytes, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P,
-                       new_src, g.chunk_cols, fa, smp.cols, smp.stride, mfma_bound_rank(m, smp.stride));
-    return hipGetLastError();
+    return launch_filter<kSB>(Ac, Kc, Hkv, N, P, g.S, m, new_src, g.S, n_new, g, true, true, nullptr, nullptr, cand, cand_cnt, overflow,
+                              st);
 }
 
 hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t *overflow, const int32_t *src,
@@ -1397,12 +1694,13 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
                              float *nbr_e, hipStream_t st)
 {
     const int S = g.S, cap = g.cand_cap;
+    const Slices sl{g.row_slots, g.chunk_slots, g.chunks, g.slice_cap, rows ? S : 0, g.late_chunks, g.late_slice_cap};
     // Short lists in at most 64 slices: a wave per list, one to a workgroup while that spreads them
     // over the compute units (up to 2048 lists), else four.  The few selections of a later round
     // take the other kernel when there are many heads (256 heads, us, workgroup / wave per list: 32K
     // prompts 18 / 28, 128K 76 / 231), this one when there are few (8 heads 9.3 / 8.3).
     const bool few = (long)S * Hkv <= 2048;
-    if (cap <= 64 * 32 && g.chunks <= 64 && (!rows || few)) {
+    if (cap <= 64 * 32 && g.chunk_slots <= 64 && (!rows || few)) {
         const int waves = few ? 1 : 4;
         const SelectRows sel = rows ? *rows : SelectRows{};
         int per_head = (waves == 1 ? 2048 : 8192) / Hkv;
@@ -1411,7 +1709,7 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
         const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * ((m + kTieRoom + 1) & ~1)) * 4;
         auto *kernel = small ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
         hipLaunchKernelGGL(kernel, dim3(per_head, Hkv), dim3(64 * waves), lds, st, (const uint2 *)cand, cand_cnt,
-                           overflow, src, S, g.pitch, g.chunks, g.slice_cap, m, sel, nbr, nbr_e);
+                           overflow, src, S, g.pitch, sl, m, sel, nbr, nbr_e);
         return hipGetLastError();
     }
     // Longer lists: the workgroups of a head share its selections in turn: few workgroups when only some
@@ -1422,7 +1720,7 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
     const size_t lds = (size_t)(cap + (cap & 1)) * 4 + (size_t)(m + kTieRoom) * 8;
     if (!allow_big_lds((const void *)nbr_select_kernel)) return hipGetLastError();
     hipLaunchKernelGGL(nbr_select_kernel, dim3(per_head, Hkv), dim3(256), lds, st, (const uint2 *)cand,
-                       cand_cnt, overflow, src, S, g.pitch, g.chunks, g.slice_cap, cap, m, sel, nbr, nbr_e);
+                       cand_cnt, overflow, src, S, g.pitch, sl, cap, m, sel, nbr, nbr_e);
     return hipGetLastError();
 }
 

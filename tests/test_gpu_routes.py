@@ -246,7 +246,12 @@ def test_update_in_front_of_the_selection_takes_long_chains(P, S, m):
 # (row groups of 32 per workgroup: one and two in a single round, three with the next-ranked nodes along, two workgroups of
 # three; the last key block short, or starting early at the end of the head; keys beyond 256 MiB, which stay out of the caches)
 @pytest.mark.parametrize("P,w,S,m,T,H", [(2080, 1, 32, 4, 1, 128), (2175, 5, 33, 9, 1, 128), (4097, 1, 64, 32, 2, 36),
-                                         (8191, 32, 129, 20, 2, 8), (2049, 63, 65, 16, 2, 64), (2050, 2, 8, 5, 1, 512)])
+                                         (8191, 32, 129, 20, 2, 8), (2049, 63, 65, 16, 2, 64), (2050, 2, 8, 5, 1, 512),
+                                         # bounds put together from 10, 8, 6 and 3 parts of the sample, in the filter pass
+                                         # (a head a workgroup), of the last rank taken from maxima and of the first counted
+                                         (8190, 1, 96, 32, 1, 12), (8191, 1, 65, 7, 1, 16), (4099, 3, 100, 64, 3, 24),
+                                         (2100, 4, 128, 32, 1, 40), (2200, 4, 40, 32, 2, 260), (8190, 1, 40, 133, 1, 28),
+                                         (8190, 1, 40, 134, 1, 28), (8190, 1, 40, 134, 2, 280)])
 def test_filter_pass_row_groups_and_key_blocks(P, w, S, m, T, H):
     """The filter pass against the dense edge block, bit for bit: many heads take the one, the same heads alone the
     other.  Among the sources a zero key; among the nodes zero keys, keys of norms that leave the range of the matrix
