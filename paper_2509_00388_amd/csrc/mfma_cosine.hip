@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, multiply_tile, (void)0);
+    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, (void)0, multiply_tile, (void)0);
 }
 
 // Bound pass: for every source a value that at least m of its edges reach (short of about one
@@ -243,7 +243,7 @@ __device__ __forceinline__ void count_sample(const uint16_t *Ah, const uint16_t 
             }
         }
     };
-    if (ntile > 0) GKV_TILE_PIPELINE(NT, Kh, c0, c1 - 1, key_stride, ntile, multiply_tile, (void)0);
+    if (ntile > 0) GKV_TILE_PIPELINE(NT, Kh, c0, c1 - 1, key_stride, ntile, (void)0, multiply_tile, (void)0);
     __syncthreads();
     // The source's own column is no neighbour (Eq. 3: j != i).  If it is one of the sampled
     // keys of this workgroup it was counted into the top bin (its edge is 1 up to rounding;

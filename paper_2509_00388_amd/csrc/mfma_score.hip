@@ -38,19 +38,6 @@ __device__ __forceinline__ void merge_stats(float &m1, float &z1, float m2, floa
     m1 = mn;
 }
 
-// Rows first .. first + 32 NB - 1 of a head's R_real query rows (the last block is filled up with the last
-// row: its statistics go nowhere and its votes are zero, see bias_s).
-template <int NB>
-__device__ __forceinline__ void load_queries(const uint16_t *Qh, int first, int R_real, int l32, int hh,
-                                             bf16x8 (&q)[NB][kSteps])
-{
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s)
-            q[b][s] = load8(Qh + (long)min(first + kBlk * b + l32, R_real - 1) * kD + 16 * s + 8 * hh);
-}
-
 // The R query rows are split over SPLIT waves per key stream: a workgroup has 4
 // key streams (wave & 3) and SPLIT row groups (wave >> 2), i.e. 4*SPLIT waves.  The
 // waves of one stream load the same key block (the second load hits L1) and each
@@ -75,8 +62,12 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l32 = lane & 31, hh = lane >> 5;
     const int stream = wv % STREAMS, row0 = (wv / STREAMS) * NBW * kBlk;   // first query row of this wave
 
+    // (rows of the last block beyond R_real repeat the last row: their statistics go nowhere and their votes are zero)
     bf16x8 q[NBW][kSteps];
-    load_queries<NBW>(Qw + (long)h * R_real * kD, row_base + row0, R_real, l32, hh, q);
+    const uint16_t *Qh = Qw + (long)h * R_real * kD;
+    auto queries = [&] {
+        spread_rows<NT, R, 2 * TK>(kt, tid, row0, [&](int x) { return Qh + (long)min(row_base + x, R_real - 1) * kD; }, q, [] {});
+    };
     int last_vis[NBW];   // last key the lane's query of block b may see (causal window)
     float m[NBW], z[NBW];
 #pragma unroll
@@ -213,7 +204,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
         after_tile();
     };
     if constexpr (NBW <= 2) {
-        GKV_TILE_PIPELINE_OVERLAPPED(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, head, body, finish);
+        GKV_TILE_PIPELINE_OVERLAPPED(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, queries(), head, body, finish);
     } else {   // three row blocks per wave: a second accumulator set does not fit the registers
         auto one_tile = [&](const unsigned char *buf, int t) {
             before_tile();
@@ -223,7 +214,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
             finish(t, 0);
             if (t + 1 < ntile) after_tile();
         };
-        GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, one_tile, (void)0);
+        GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, queries(), one_tile, (void)0);
     }
 
     park(at & 1);
@@ -271,46 +262,50 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
     if (fused)   // outside the row: zeros (average), nothing (max)
         for (int u = tid; u < (PERQ ? G : SPLIT) * span; u += NT) vs[u] = PERQ ? -INFINITY : 0.f;
 
-    {   // Row statistics of the whole head: merge the chunks of pass A, PARTS threads per row, each a run
-        // of chunks whose loads leave eight at a time.  (One thread per row and one load after the
-        // other was the longest part of the kernel's start with few heads: 25.4 us with 32 chunks, 21 us now.)
-        constexpr int PARTS = NT / R;
-        __shared__ float2 stat_s[PARTS][R];
-        const int row = tid % R, pt = tid / R, per = (part_chunks + PARTS - 1) / PARTS;
-        const int cb = min(pt * per, part_chunks), ce = min(cb + per, part_chunks);
-        float mm = -INFINITY, zz = 0.f;
-        if (pt < PARTS) {
-            for (int c0 = cb; c0 < ce; c0 += 8) {
-                float2 o[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    o[u] = *reinterpret_cast<const float2 *>(
-                        part + (((long)h * part_chunks + min(c0 + u, ce - 1)) * R_total + row_base + row) * 2);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c0 + u < ce) merge_stats(mm, zz, o[u].x, o[u].y);
-            }
-            stat_s[pt][row] = make_float2(mm, zz);
-        }
-        __syncthreads();
-        if (tid < R) {
-            mm = stat_s[0][tid].x;
-            zz = stat_s[0][tid].y;
-#pragma unroll
-            for (int u = 1; u < PARTS; ++u) merge_stats(mm, zz, stat_s[u][tid].x, stat_s[u][tid].y);
-            // zz >= 1: the row maximum itself contributes exp2(0); rows that only fill a block vote zero
-            bias_s[tid] = row_base + tid < R_real ? mm + __log2f(zz) : INFINITY;
-        }
-    }
-    __syncthreads();
-
     bf16x8 q[NBW][kSteps];
-    load_queries<NBW>(Qw + (long)h * R_real * kD, row_base + row0, R_real, l32, hh, q);
+    const uint16_t *Qh = Qw + (long)h * R_real * kD;
     float bias[NBW][16];
+    auto statistics = [&] {
+        {   // Row statistics of the whole head: merge the chunks of pass A, PARTS threads per row, each a run
+            // of chunks whose loads leave eight at a time.  (One thread per row and one load after the
+            // other was the longest part of the kernel's start with few heads: 25.4 us with 32 chunks, 21 us now.)
+            constexpr int PARTS = NT / R;
+            __shared__ float2 stat_s[PARTS][R];
+            const int row = tid % R, pt = tid / R, per = (part_chunks + PARTS - 1) / PARTS;
+            const int cb = min(pt * per, part_chunks), ce = min(cb + per, part_chunks);
+            float mm = -INFINITY, zz = 0.f;
+            if (pt < PARTS) {
+                for (int c0 = cb; c0 < ce; c0 += 8) {
+                    float2 o[8];
 #pragma unroll
-    for (int b = 0; b < NBW; ++b)
+                    for (int u = 0; u < 8; ++u)
+                        o[u] = *reinterpret_cast<const float2 *>(
+                            part + (((long)h * part_chunks + min(c0 + u, ce - 1)) * R_total + row_base + row) * 2);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) bias[b][i] = bias_s[row0 + kBlk * b + acc_row(i, hh)];
+                    for (int u = 0; u < 8; ++u)
+                        if (c0 + u < ce) merge_stats(mm, zz, o[u].x, o[u].y);
+                }
+                stat_s[pt][row] = make_float2(mm, zz);
+            }
+            __syncthreads();
+            if (tid < R) {
+                mm = stat_s[0][tid].x;
+                zz = stat_s[0][tid].y;
+#pragma unroll
+                for (int u = 1; u < PARTS; ++u) merge_stats(mm, zz, stat_s[u][tid].x, stat_s[u][tid].y);
+                // zz >= 1: the row maximum itself contributes exp2(0); rows that only fill a block vote zero
+                bias_s[tid] = row_base + tid < R_real ? mm + __log2f(zz) : INFINITY;
+            }
+        }
+    };
+    auto queries = [&] {   // (its barriers make bias_s known to all)
+        spread_rows<NT, R, 2 * TK>(kt, tid, row0, [&](int x) { return Qh + (long)min(row_base + x, R_real - 1) * kD; }, q,
+                                   statistics);
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bias[b][i] = bias_s[row0 + kBlk * b + acc_row(i, hh)];
+    };
 
     const uint16_t *Kh = Kc + (long)h * N * kD;
     const int ntile = (kend - first + TK - 1) / TK;
@@ -364,7 +359,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, first, kend - 1, 1, ntile, multiply_tile, (void)0);
+    GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, first, kend - 1, 1, ntile, queries(), multiply_tile, (void)0);
     if (fused) {
         __syncthreads();
         if constexpr (PERQ) {   // max pooling: per query head, then the sum over the heads

@@ -89,6 +89,40 @@ __device__ __forceinline__ void tile_read(const unsigned char *buf, int stream, 
     for (int s = 0; s < kSteps; ++s) kc[s] = *reinterpret_cast<const bf16x8 *>(p + 32 * s);
 }
 
+// R rows that a workgroup's waves hold in operand registers (row x of them: row_of(x), 256 bytes in memory), read with
+// coalesced loads and spread through the LDS, CAP rows at a time: wave rows row0 .. row0 + 32 NB - 1 into q.
+// Loaded straight into operand layout each instruction touches 32 rows, and every wave that holds a row reads it again: 128
+// query rows in eight waves take 128 such loads, about 2 us of a kernel's start.  Ends with a barrier.
+template <int NT, int R, int CAP, int NB, typename RowOf, typename Meanwhile>
+__device__ __forceinline__ void spread_rows(unsigned char *smem, int tid, int row0, RowOf &&row_of, bf16x8 (&q)[NB][kSteps],
+                                            Meanwhile &&meanwhile)
+{
+    const int lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int first = 0; first < R; first += CAP) {
+        constexpr int rows = R < CAP ? R : CAP, PER = rows * 16 / NT;
+        static_assert(R % rows == 0 && rows * 16 % NT == 0 && rows % (kBlk * NB) == 0, "whole pieces, whole waves");
+        u32x4 piece[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + NT * u;
+            piece[u] = *reinterpret_cast<const u32x4 *>(row_of(first + (at >> 4)) + 8 * (at & 15));
+        }
+        if (first == 0) meanwhile();   // (while they are on their way)
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int at = tid + NT * u;
+            *reinterpret_cast<u32x4 *>(smem + (at >> 4) * kPitch + (at & 15) * 16) = piece[u];
+        }
+        __syncthreads();
+        if (row0 >= first && row0 < first + rows) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) tile_read(smem + (row0 - first) * kPitch, b, l32, hh, q[b]);
+        }
+        __syncthreads();
+    }
+}
+
 // x of this lane plus x of the lane 32 places away (the other half of the wave), without a
 // trip through the LDS crossbar: gfx950's v_permlane32_swap exchanges the upper half of one
 // register with the lower half of another, so two copies of x become (low half twice) and
@@ -127,7 +161,8 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 
 // The tile loop shared by the streaming kernels.  Tile t is multiplied out of LDS
 // while tiles t+1 and t+2 are on their way from HBM in two sets of staging
-// registers: two tiles (64 KiB) in flight per workgroup (a third set brought no
+// registers (`ahead` runs while the first two are on their way, the LDS not yet in use):
+// two tiles (64 KiB) in flight per workgroup (a third set brought no
 // gain when measured).  One barrier per tile separates the writers of an LDS
 // buffer from its readers.  `body(buf, t)` multiplies tile t; AFTER_TILE runs
 // right after each tile's barrier with `tile_done` = number of tiles finished (it
@@ -140,25 +175,26 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // wait in front of each LDS store leaves the newer tile's loads outstanding.
 // With conditional loads it has to assume they were skipped and waits for
 // everything.
-#define GKV_TILE_PIPELINE_TK(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)  \
+#define GKV_TILE_PIPELINE_TK(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE)\
     do {                                                                                               \
         constexpr int tile_bytes_ = (TK_) * kPitch;                                                    \
         u32x4 stage_a[tile_pieces<NT_, TK_>()], stage_b[tile_pieces<NT_, TK_>()];                      \
         tile_load<NT_, TK_, ONCE_>(Kh_, first_, clamp_, stride_, tid, stage_a);                        \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_b);                \
+        ahead;                                                                                         \
         tile_store<NT_, TK_>(kt, tid, stage_a);                                                        \
-        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                \
-        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);            \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_a);            \
         __syncthreads();                                                                               \
         for (int t_ = 0; t_ < ntile_; t_ += 2) {                                                       \
             body(kt, t_);                                                                              \
-            tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                      \
-            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_a); \
+            tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_b);                                      \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_b); \
             __syncthreads();                                                                           \
             { const int tile_done = t_ + 1; (void)tile_done; AFTER_TILE; }                             \
             if (t_ + 1 >= ntile_) break;                                                               \
             body(kt + tile_bytes_, t_ + 1);                                                            \
-            tile_store<NT_, TK_>(kt, tid, stage_b);                                                    \
-            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_b); \
+            tile_store<NT_, TK_>(kt, tid, stage_a);                                                    \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_a); \
             __syncthreads();                                                                           \
             { const int tile_done = t_ + 2; (void)tile_done; AFTER_TILE; }                             \
         }                                                                                              \
@@ -171,35 +207,36 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // 0 into set 0; `body(buf, t, set)` multiplies tile t into `set` and finishes tile t - 1 from the
 // other set; `tail(t, set)` finishes the last tile.  `set` is a literal at every call, so the
 // accumulator sets stay in registers.
-#define GKV_TILE_PIPELINE_OVERLAPPED(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, head, body, tail) \
+#define GKV_TILE_PIPELINE_OVERLAPPED(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, ahead, head, body, tail) \
     do {                                                                                               \
         constexpr int tile_bytes_ = (TK_) * kPitch;                                                    \
         u32x4 stage_a[tile_pieces<NT_, TK_>()], stage_b[tile_pieces<NT_, TK_>()];                      \
         tile_load<NT_, TK_, ONCE_>(Kh_, first_, clamp_, stride_, tid, stage_a);                        \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_b);                \
+        ahead;                                                                                         \
         tile_store<NT_, TK_>(kt, tid, stage_a);                                                        \
-        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_), clamp_, stride_, tid, stage_a);                \
-        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_b);            \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 2 * (TK_), clamp_, stride_, tid, stage_a);            \
         __syncthreads();                                                                               \
         head(kt);                                                                                      \
-        tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                          \
-        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 3 * (TK_), clamp_, stride_, tid, stage_a);            \
+        tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_b);                                          \
+        tile_load<NT_, TK_, ONCE_>(Kh_, first_ + 3 * (TK_), clamp_, stride_, tid, stage_b);            \
         __syncthreads();                                                                               \
         int t_ = 1;                                                                                    \
         for (; t_ < ntile_; t_ += 2) {                                                                 \
             body(kt + tile_bytes_, t_, 1);                                                             \
-            tile_store<NT_, TK_>(kt, tid, stage_b);                                                    \
-            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_b); \
+            tile_store<NT_, TK_>(kt, tid, stage_a);                                                    \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_a); \
             __syncthreads();                                                                           \
             if (t_ + 1 >= ntile_) break;                                                               \
             body(kt, t_ + 1, 0);                                                                       \
-            tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_a);                                      \
-            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_a); \
+            tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_b);                                      \
+            tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_b); \
             __syncthreads();                                                                           \
         }                                                                                              \
         if ((ntile_ - 1) & 1) tail(ntile_ - 1, 1); else tail(ntile_ - 1, 0);                           \
     } while (0)
 
-#define GKV_TILE_PIPELINE(NT_, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE) \
-    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, false, Kh_, first_, clamp_, stride_, ntile_, body, AFTER_TILE)
+#define GKV_TILE_PIPELINE(NT_, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE) \
+    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, false, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE)
 
 }  // namespace gkv
