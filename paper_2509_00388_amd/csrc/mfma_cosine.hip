@@ -110,12 +110,22 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
     const int c0 = chunk * chunk_cols, c1 = min(P, c0 + chunk_cols);
     if (c0 >= P) return;
 
-    bf16x8 q[kSteps];
-    load_sources(Ac + (long)h * N * kD, src + (long)h * S, S, s_base, grp, stream, l32, hh, q, inv_s, idx_s);
-    __syncthreads();
+    // (slots beyond S repeat the last source)
+    bf16x8 q[1][kSteps];
     float inv_src[16];
+    auto sources = [&] {
+        const uint16_t *Ah = Ac + (long)h * N * kD;
+        const int32_t *src_h = src + (long)h * S;
+        spread_rows<kThreads, kRows, kRows>(kt, tid, kBlk * grp, [&](int x) { return Ah + (long)src_h[min(s_base + x, S - 1)] * kD; }, q,
+                                            [&] { if (tid < kRows) idx_s[tid] = src_h[min(s_base + tid, S - 1)]; });
+        if (stream == 0) {
+            const float inv = inv_norm(add_other_half(half_row_sumsq(q[0])));
+            if (hh == 0) inv_s[kBlk * grp + l32] = inv;
+        }
+        __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) inv_src[i] = inv_s[kBlk * grp + acc_row(i, hh)];
+        for (int i = 0; i < 16; ++i) inv_src[i] = inv_s[kBlk * grp + acc_row(i, hh)];
+    };
 
     const int ntile = (c1 - c0 + kTileKeys - 1) / kTileKeys;
     auto multiply_tile = [&](const unsigned char *buf, int t) {
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
         for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
         for (int s = 0; s < kSteps; ++s)   // rows = sources, columns = keys
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[s], kc[s], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[0][s], kc[s], acc, 0, 0, 0);
 
         float sq = half_row_sumsq(kc);
         sq = add_other_half(sq);
@@ -144,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, (void)0, multiply_tile, (void)0);
+    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, sources(), multiply_tile, (void)0);
 }
 
 // Bound pass: for every source a value that at least m of its edges reach (short of about one
