@@ -176,10 +176,11 @@ __device__ __forceinline__ void find_bin_block(const uint32_t *hist, uint32_t ne
     __syncthreads();
 }
 
-// The m-th largest of the keys in the first NIT registers of every lane (unused registers
+// The m-th largest of the keys in the first NIT registers of every lane, or a value that no other keys reach (unused registers
 // hold 0, below every key), all between kmin and kmax: built bit by bit from the top; the
 // count of the keys that reach a trial value is one wave vote per register.  Straight-line
-// code for a given NIT: branches between the votes would cost more than the votes.
+// code for a given NIT: branches between the votes would cost more than the votes.  A trial that exactly m keys
+// reach ends it: the same keys reach it as reach the m-th largest.
 template <int NIT, int R>
 __device__ __forceinline__ uint32_t mth_largest_key(const uint32_t (&E)[R], uint32_t kmin, uint32_t kmax, int m)
 {
@@ -191,7 +192,10 @@ __device__ __forceinline__ uint32_t mth_largest_key(const uint32_t (&E)[R], uint
             int reach = 0;
 #pragma unroll
             for (int it = 0; it < NIT; ++it) reach += (int)__popcll(__ballot(E[it] >= trial));
-            if (trial > tau && reach >= m) tau = trial;   // (a trial that wrapped around is beyond every key)
+            if (trial > tau && reach >= m) {   // (a trial that wrapped around is beyond every key)
+                tau = trial;
+                if (reach == m) break;
+            }
         }
     }
     return tau;

@@ -950,9 +950,10 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
     int32_t cnt_r = 0, self_r = 0, pos_r = 0, crow_r = 0;
     int search_steps = 0;   // bisection steps over the slices
     while ((1 << search_steps) < sl.chunk_slots) ++search_steps;
-    if ((int)blockIdx.x < n_rows) ask(blockIdx.x, cnt_r, self_r, pos_r, crow_r);
+    const int wg = (int)((blockIdx.x + h) % gridDim.x);   // (few rows a head: on all XCDs)
+    if (wg < n_rows) ask(wg, cnt_r, self_r, pos_r, crow_r);
 
-    for (int x = blockIdx.x; x < n_rows; x += gridDim.x) {
+    for (int x = wg; x < n_rows; x += gridDim.x) {
         const long row = (long)h * pitch + crow_r;
         const int chunks = sl.chunks_of(crow_r), slice_cap = sl.cap_of(crow_r);
         int incl = cnt_r;   // running total of the slice sizes
@@ -1135,6 +1136,11 @@ __global__ __launch_bounds__(256) void nbr_select_kernel(const uint2 *__restrict
 // list has room for, raise the head's overflow flag (the head is then redone exactly).
 // (A walk over the slices for every register, key indices fetched a second time, scans through the
 // LDS crossbar: 15.8 us for 512 lists in 32 slices each; this way 8.4 us.)
+// (Key index and edge of a winner in one 64-bit word, ranked by comparing those: 222 us for 32768 lists of 420 entries,
+// m = 128; indices in 32 bits, four a read: 180; the vote on the m-th largest ended when exactly m reach: 153.)
+// Words for the key indices, and for the edges, of a wave's list: read four at a time, up to three past the end.
+__host__ __device__ inline int wave_list_room(int m) { return (m + kTieRoom + 6) & ~3; }
+
 template <int R>
 __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__restrict__ cand,
                                                               const int32_t *__restrict__ cand_cnt,
@@ -1145,19 +1151,21 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
                                                               float *__restrict__ nbr_e)
 {
     static_assert(R == 16 || R == 32, "register groups of 16");
-    // per wave: [64] slice starts, [64 R] marks (bytes), [m + kTieRoom, even] list (64 bit)
+    // per wave: [64] slice starts, [64 R] marks (bytes), [list_room] key indices and edge bits of the list
     extern __shared__ __align__(16) uint32_t dyn[];
     const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // (scalar: so are the row and its addresses)
     const int waves = (int)blockDim.x >> 6;
     const int n_rows = sel.n_rows ? sel.n_rows[h] : S;
     if (overflow[h]) return;
-    const int list_cap = m + kTieRoom;
-    uint32_t *start_s = dyn + wv * (64 + 16 * R + 2 * ((list_cap + 1) & ~1));
+    const int list_cap = m + kTieRoom, list_room = wave_list_room(m);
+    uint32_t *start_s = dyn + wv * (64 + 16 * R + 2 * list_room);
     uint8_t *mark_s = reinterpret_cast<uint8_t *>(start_s + 64);
-    uint64_t *win = reinterpret_cast<uint64_t *>(start_s + 64 + 16 * R);
+    uint32_t *win_j = start_s + 64 + 16 * R, *win_e = win_j + list_room;
 
-    for (int x = blockIdx.x * waves + wv; x < n_rows; x += gridDim.x * waves) {
+    // (with few rows a head their workgroups are the first of the head's; turned by the head they land on all XCDs)
+    const int wg = (int)((blockIdx.x + h) % gridDim.x);
+    for (int x = wg * waves + wv; x < n_rows; x += gridDim.x * waves) {
         const int crow = sel.row ? sel.row[(long)h * S + x] : x, pos = sel.pos ? sel.pos[(long)h * S + x] : x;
         const long row = (long)h * pitch + crow;
         const int chunks = sl.chunks_of(crow), slice_cap = sl.cap_of(crow);
@@ -1252,7 +1260,7 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
         else if (n_it <= 24) tau = mth_largest_key<(R > 24 ? 24 : R)>(E, kmin, kmax, m);
         else tau = mth_largest_key<R>(E, kmin, kmax, m);
 
-        // everything that reaches tau -> LDS list as (key index, edge bits), any order
+        // everything that reaches tau -> LDS list, key index and edge bits, any order
         int listed = 0;
 #pragma unroll
         for (int it = 0; it < R; ++it)
@@ -1260,51 +1268,51 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
                 const bool in = E[it] >= tau;
                 const uint64_t votes = __ballot(in);
                 const int at = listed + (int)votes_below(votes);
-                if (in && at < list_cap) win[at] = ((uint64_t)J[it] << 32) | ord_key_inv(E[it]);
+                if (in && at < list_cap) {
+                    win_j[at] = J[it];
+                    win_e[at] = ord_key_inv(E[it]);
+                }
                 listed += (int)__popcll(votes);
             }
         if (listed > list_cap) {   // too many exactly equal edges at the cut
             if (lane == 0) overflow[h] = 1;
             return;
         }
-        if (lane == 0 && (listed & 1)) win[listed] = ~0ull;   // (pairs are read below)
+        if (lane < 3) win_j[listed + lane] = ~0u;   // (fours are read below)
         wave_sync();
         if (listed > m) {
             // Of the entries equal to tau only those with the lowest key indices stay: one that
             // `keep` or more tied entries precede is dropped (a dropped entry sorts behind all).
             const uint32_t tau_bits = ord_key_inv(tau);
             int n_tied = 0;
-            for (int u = 0; u < listed; ++u) n_tied += (uint32_t)win[u] == tau_bits;
+            for (int u = 0; u < listed; ++u) n_tied += win_e[u] == tau_bits;
             const int keep = m - (listed - n_tied);
             // (decided for all entries first: a dropped one must still be counted by the others)
             uint32_t drop = 0;
             for (int r = lane, i = 0; r < listed; r += 64, ++i) {
-                const uint64_t mine = win[r];
-                if ((uint32_t)mine == tau_bits) {
+                if (win_e[r] == tau_bits) {
+                    const uint32_t mine = win_j[r];
                     int before = 0;
-                    for (int u = 0; u < listed; ++u) {
-                        const uint64_t w = win[u];
-                        before += (uint32_t)w == tau_bits && w < mine;
-                    }
+                    for (int u = 0; u < listed; ++u) before += win_e[u] == tau_bits && win_j[u] < mine;
                     if (before >= keep) drop |= 1u << i;
                 }
             }
             wave_sync();
             for (int r = lane, i = 0; r < listed; r += 64, ++i)
-                if ((drop >> i) & 1u) win[r] = ~0ull;
+                if ((drop >> i) & 1u) win_j[r] = ~0u;
             wave_sync();
         }
         // each winner's rank by key index is its place in the output
         for (int r = lane; r < listed; r += 64) {
-            const uint64_t mine = win[r];
-            if (mine != ~0ull) {
+            const uint32_t mine = win_j[r];
+            if (mine != ~0u) {
                 int at = 0;
-                for (int u = 0; u < listed; u += 2) {
-                    const ulonglong2 w = *reinterpret_cast<const ulonglong2 *>(win + u);
-                    at += (w.x < mine) + (w.y < mine);
+                for (int u = 0; u < listed; u += 4) {
+                    const uint4 w = *reinterpret_cast<const uint4 *>(win_j + u);
+                    at += (w.x < mine) + (w.y < mine) + (w.z < mine) + (w.w < mine);
                 }
-                nbr[out_row * m + at] = (int32_t)(mine >> 32);
-                nbr_e[out_row * m + at] = __uint_as_float((uint32_t)mine);
+                nbr[out_row * m + at] = (int32_t)mine;
+                nbr_e[out_row * m + at] = __uint_as_float(win_e[r]);
             }
         }
         wave_sync();
@@ -1705,18 +1713,18 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
 {
     const int S = g.S, cap = g.cand_cap;
     const Slices sl{g.row_slots, g.chunk_slots, g.chunks, g.slice_cap, rows ? S : 0, g.late_chunks, g.late_slice_cap};
-    // Short lists in at most 64 slices: a wave per list, one to a workgroup while that spreads them
-    // over the compute units (up to 2048 lists), else four.  The few selections of a later round
-    // take the other kernel when there are many heads (256 heads, us, workgroup / wave per list: 32K
-    // prompts 18 / 28, 128K 76 / 231), this one when there are few (8 heads 9.3 / 8.3).
+    // Short lists in at most 64 slices: a wave per list, one to a workgroup while that spreads them over the compute units
+    // (up to 2048 lists), else four.  (Few selections of a later round with many heads took the other kernel before
+    // the heads' first workgroups were turned to different XCDs; 256 heads, us, workgroup / wave per list then / wave now:
+    // 32K prompts 16 / 20 / 10, 20K 22 / 21 / 11, 128K 83 / 151 / 47.)
     const bool few = (long)S * Hkv <= 2048;
-    if (cap <= 64 * 32 && g.chunk_slots <= 64 && (!rows || few)) {
+    if (cap <= 64 * 32 && g.chunk_slots <= 64) {
         const int waves = few ? 1 : 4;
         const SelectRows sel = rows ? *rows : SelectRows{};
         int per_head = (waves == 1 ? 2048 : 8192) / Hkv;
         per_head = per_head < 1 ? 1 : (per_head > (S + waves - 1) / waves ? (S + waves - 1) / waves : per_head);
         const bool small = cap <= 64 * 16;
-        const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * ((m + kTieRoom + 1) & ~1)) * 4;
+        const size_t lds = (size_t)waves * (64 + 16 * (small ? 16 : 32) + 2 * wave_list_room(m)) * 4;
         auto *kernel = small ? nbr_select_wave_kernel<16> : nbr_select_wave_kernel<32>;
         hipLaunchKernelGGL(kernel, dim3(per_head, Hkv), dim3(64 * waves), lds, st, (const uint2 *)cand, cand_cnt,
                            overflow, src, S, g.pitch, sl, m, sel, nbr, nbr_e);
