@@ -410,9 +410,10 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                         GKV_LAUNCH(GRAPHKV_K_TOPK_SOURCES,
                                    launch_topk_rows(scores, D.P, D.P, D.H, D.S, src, D.S, nullptr, 0, st));
                     }
-                    GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND,
-                               launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
-                                                        at<char>(ws, W.bound_hist), tau, ovf, st));
+                    if (!mfma_filter_takes_bounds(D.P, D.m, g))
+                        GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND,
+                                   launch_mfma_cosine_bound(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
+                                                            at<char>(ws, W.bound_hist), tau, ovf, st));
                     GKV_LAUNCH(GRAPHKV_K_COSINE_FILTER,
                                launch_mfma_cosine_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, true, lst, nullptr,
                                                          at<char>(ws, W.bound_hist), tau, cand, cnt, ovf, st));

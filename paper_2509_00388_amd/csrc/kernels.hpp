@@ -176,7 +176,9 @@ struct MfmaFilterPlan {
 };
 // short_slices: no more memory for candidates than keys in no particular order need.
 MfmaFilterPlan mfma_filter_plan(int Hkv, int P, int S, int m, bool keep_lists, bool speculate, bool short_slices);
-size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // per-chunk histograms (0 if one chunk)
+size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g);   // what chunks of the sample leave (0 if one chunk)
+// Whether the first round's filter pass takes the bounds itself: the bound pass is then left out.
+bool mfma_filter_takes_bounds(int P, int m, const MfmaFilterPlan &g);
 // Bound pass: tau = a value that at least m of the row's edges reach (but for about one row in
 // 10^7, which the select notices), from the edges to every (P / sample_cols)-th key; clears
 // overflow [Hkv].  first_round: src is the extended list
@@ -187,7 +189,7 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
                                     const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
                                     hipStream_t st);
 // Filter pass: streams all keys; edges that reach a row's tau go to its slices, their number
-// per slice to cand_cnt.  Same source lists and rows as the bound pass.
+// per slice to cand_cnt.  Same source lists, rows and hist_part (first round) as the bound pass.
 hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m,
                                      const MfmaFilterPlan &g, bool first_round, const int32_t *src,
                                      const int32_t *n_src, const void *hist_part, const float *tau, void *cand,

@@ -1614,12 +1614,6 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     return hipGetLastError();
 }
 
-// Whether the first round's filter pass takes the bounds itself (a later round's: late_filter_applies()).
-bool filter_takes_bounds(int P, int m, const MfmaFilterPlan &g)
-{
-    return g.chunks == 1 && g.S + g.X <= kBlk * g.sb && mfma_bound_rank(m, sample_of(P).stride) <= kMaximaRank;
-}
-
 template <int SB>
 hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                          int src_pitch, const int32_t *n_src, const MfmaFilterPlan &g, bool late, bool with_bounds,
@@ -1649,9 +1643,15 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
 
 }  // namespace
 
+bool mfma_filter_takes_bounds(int P, int m, const MfmaFilterPlan &g)
+{
+    return g.chunks == 1 && g.S + g.X <= kBlk * g.sb && mfma_bound_rank(m, sample_of(P).stride) <= kMaximaRank;
+}
+
 size_t mfma_bound_scratch_bytes(int Hkv, int P, const MfmaFilterPlan &g)
 {
-    // (only the passes over a full source list cut the sample into chunks)
+    // (Only the passes over a full source list cut the sample into chunks.  Sized for chunks whose edges are counted; the
+    // maxima of others take less.)
     const int rows = g.S + g.X, rows_wg = kBlk * g.sb, sgroups = (rows + rows_wg - 1) / rows_wg;
     const int chunks = bound_chunks(Hkv, P, sgroups);
     return chunks > 1 ? (size_t)Hkv * sgroups * chunks * rows_wg * 256 * 4 : 0;
@@ -1662,7 +1662,6 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
                                     const int32_t *n_src, void *hist_part, float *tau, int32_t *overflow,
                                     hipStream_t st)
 {
-    if (first_round && filter_takes_bounds(P, m, g)) return hipSuccess;
     if (first_round && g.sb == 3)
         return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false,
                                     hist_part, tau, g.pitch, 0, overflow, st);
@@ -1675,7 +1674,7 @@ hipError_t launch_mfma_cosine_filter(const void *Ac, const void *Kc, int Hkv, in
                                      const int32_t *n_src, const void *hist_part, const float *tau, void *cand,
                                      int32_t *cand_cnt, int32_t *overflow, hipStream_t st)
 {
-    const bool with_bounds = first_round && filter_takes_bounds(P, m, g);
+    const bool with_bounds = first_round && mfma_filter_takes_bounds(P, m, g);
     if (first_round && g.sb == 3)
         return launch_filter<3>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, g, false, with_bounds, hist_part, tau,
                                 cand, cand_cnt, overflow, st);
