@@ -9,9 +9,9 @@
 // the MFMA, so the keys are read once.
 //
 // Neighbourhoods in one streaming pass:
-//   1. a first pass over an evenly strided sample of the keys (every 8th) counts
-//      each source's edges into a histogram and takes a bound from it: the sampled
-//      edge of rank r, where r < m is chosen so that all but about one source in 10^7
+//   1. a first pass over an evenly strided sample of the keys (every 8th) takes a
+//      bound for each source, a value that r of its sampled edges reach and hardly any
+//      more, where r < m is chosen so that all but about one source in 10^7
 //      have at least m edges above it (mfma_bound_rank; r = m would make that certain,
 //      a subset's m-th largest can only be smaller, but lets 8 m keys through
 //      where r lets 8 r);
@@ -154,10 +154,11 @@ __global__ __launch_bounds__(kThreads) void cosine_dense_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, sources(), multiply_tile, (void)0);
+    GKV_TILE_PIPELINE(kThreads, Kh, c0, c1 - 1, 1, ntile, sources(), multiply_tile);
 }
 
-// Bound pass: for every source a value that at least m of its edges reach (short of about one
+// Bound pass for ranks beyond kMaximaRank (few prompts ask for so many neighbours; others: cosine_maxima_kernel): for every
+// source a value that at least m of its edges reach (short of about one
 // source in 10^7, which the select catches), from the edges to a strided sample of the keys
 // (column c = key c * key_stride).  `m` below is the rank in the sample that the host chose
 // (mfma_bound_rank).  One workgroup takes the whole
@@ -253,7 +254,7 @@ __device__ __forceinline__ void count_sample(const uint16_t *Ah, const uint16_t 
             }
         }
     };
-    if (ntile > 0) GKV_TILE_PIPELINE(NT, Kh, c0, c1 - 1, key_stride, ntile, (void)0, multiply_tile, (void)0);
+    if (ntile > 0) GKV_TILE_PIPELINE(NT, Kh, c0, c1 - 1, key_stride, ntile, (void)0, multiply_tile);
     __syncthreads();
     // The source's own column is no neighbour (Eq. 3: j != i).  If it is one of the sampled
     // keys of this workgroup it was counted into the top bin (its edge is 1 up to rounding;

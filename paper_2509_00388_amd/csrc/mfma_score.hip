@@ -214,7 +214,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_stats_kernel(
             finish(t, 0);
             if (t + 1 < ntile) after_tile();
         };
-        GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, queries(), one_tile, (void)0);
+        GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, k0, k1 - 1, 1, ntile, queries(), one_tile);
     }
 
     park(at & 1);
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(64 * STREAMS * SPLIT) void score_votes_kernel(
             }
         }
     };
-    GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, first, kend - 1, 1, ntile, queries(), multiply_tile, (void)0);
+    GKV_TILE_PIPELINE_TK(TK, NT, ONCE, Kh, first, kend - 1, 1, ntile, queries(), multiply_tile);
     if (fused) {
         __syncthreads();
         if constexpr (PERQ) {   // max pooling: per query head, then the sum over the heads

@@ -164,9 +164,7 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // registers (`ahead` runs while the first two are on their way, the LDS not yet in use):
 // two tiles (64 KiB) in flight per workgroup (a third set brought no
 // gain when measured).  One barrier per tile separates the writers of an LDS
-// buffer from its readers.  `body(buf, t)` multiplies tile t; AFTER_TILE runs
-// right after each tile's barrier with `tile_done` = number of tiles finished (it
-// may contain barriers: every thread reaches it).  The loop is unrolled twice so
+// buffer from its readers.  `body(buf, t)` multiplies tile t.  The loop is unrolled twice so
 // that the LDS buffer and the register set of a tile are compile-time choices.
 //
 // The prefetch loads are issued unconditionally, also past the last tile (rows are
@@ -175,7 +173,7 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
 // wait in front of each LDS store leaves the newer tile's loads outstanding.
 // With conditional loads it has to assume they were skipped and waits for
 // everything.
-#define GKV_TILE_PIPELINE_TK(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE)\
+#define GKV_TILE_PIPELINE_TK(TK_, NT_, ONCE_, Kh_, first_, clamp_, stride_, ntile_, ahead, body)            \
     do {                                                                                               \
         constexpr int tile_bytes_ = (TK_) * kPitch;                                                    \
         u32x4 stage_a[tile_pieces<NT_, TK_>()], stage_b[tile_pieces<NT_, TK_>()];                      \
@@ -190,13 +188,11 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
             tile_store<NT_, TK_>(kt + tile_bytes_, tid, stage_b);                                      \
             tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 3), clamp_, stride_, tid, stage_b); \
             __syncthreads();                                                                           \
-            { const int tile_done = t_ + 1; (void)tile_done; AFTER_TILE; }                             \
             if (t_ + 1 >= ntile_) break;                                                               \
             body(kt + tile_bytes_, t_ + 1);                                                            \
             tile_store<NT_, TK_>(kt, tid, stage_a);                                                    \
             tile_load<NT_, TK_, ONCE_>(Kh_, first_ + (TK_) * (t_ + 4), clamp_, stride_, tid, stage_a); \
             __syncthreads();                                                                           \
-            { const int tile_done = t_ + 2; (void)tile_done; AFTER_TILE; }                             \
         }                                                                                              \
     } while (0)
 
@@ -236,7 +232,7 @@ __device__ __forceinline__ float half_row_sumsq(const bf16x8 (&r)[STEPS], float 
         if ((ntile_ - 1) & 1) tail(ntile_ - 1, 1); else tail(ntile_ - 1, 0);                           \
     } while (0)
 
-#define GKV_TILE_PIPELINE(NT_, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE) \
-    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, false, Kh_, first_, clamp_, stride_, ntile_, ahead, body, AFTER_TILE)
+#define GKV_TILE_PIPELINE(NT_, Kh_, first_, clamp_, stride_, ntile_, ahead, body) \
+    GKV_TILE_PIPELINE_TK(kTileKeys, NT_, false, Kh_, first_, clamp_, stride_, ntile_, ahead, body)
 
 }  // namespace gkv

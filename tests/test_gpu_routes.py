@@ -287,3 +287,29 @@ def test_filter_pass_row_groups_and_key_blocks(P, w, S, m, T, H):
     assert torch.equal(many[0].view(rep, few, P), dense[0].expand(rep, -1, -1))
     for a, b in zip(many[1:], dense[1:]):
         assert torch.equal(a.view(T, rep, *b.shape[1:]), b[:, None].expand(-1, rep, *[-1] * (b.dim() - 1)))
+
+
+@pytest.mark.parametrize("w,pool_mode,scorer", [(20, 0, 0), (32, 1, 0), (64, 0, 0), (8, 0, 1)])
+def test_calls_with_more_keys_than_the_caches_hold(w, pool_mode, scorer):
+    """Batches beyond 256 MiB of keys read and write past the caches; their layers alone (8 MiB each) don't.  Scores that are cut
+    as a layer's are the same bits; others (whole blocks of 32 query rows) agree to the rounding of 32-bit sums."""
+    say(f"past the caches w={w} pool_mode={pool_mode} scorer={scorer}")
+    L, H, G, N, d, B = 34, 4, 4 if w == 64 else 1, 8192 + w, 128, w + 100
+    g = torch.Generator("cuda").manual_seed(w)
+    K, V = (torch.randn(L, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    Q = (torch.randn(L, H * G, w, d, generator=g, device="cuda") + K[:, :, :w].repeat_interleave(G, dim=1)).to(torch.bfloat16)
+    p = gk.Params(n_kv_heads=H, n_q_heads=H * G, head_dim=d, n_tokens=N, window=w, budget=B, pool_kernel=7, pool_mode=pool_mode,
+                  rounds=0, scorer=scorer, dtype=gk.BF16)
+    assert L * H * N * d * 2 > 256 << 20
+    sc = torch.empty(L, H, N - w, device="cuda")
+    Ks, Vs, idx = gk.graphkv_compress_batched(p, L, None, K, V, Q, scores_out=sc)
+    idx = idx.view(L, H, B)
+    at = idx.long()[..., None].expand(-1, -1, -1, d)
+    assert torch.equal(Ks.view(L, H, B, d), K.gather(2, at)) and torch.equal(Vs.view(L, H, B, d), V.gather(2, at))
+    for l in (0, 16, L - 1):
+        s1 = torch.empty(H, N - w, device="cuda")
+        _, _, i1 = gk.graphkv_compress(p, K[l], V[l], Q[l], scores_out=s1)
+        if scorer or (G * w) % 32:
+            assert torch.equal(s1, sc[l]) and torch.equal(i1, idx[l])
+        else:   # (sums of 8192 terms in another order, 2^-24 each)
+            assert (s1 - sc[l]).abs().max() <= 1e-5 * s1.abs().max()
