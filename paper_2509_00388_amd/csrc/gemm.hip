@@ -374,7 +374,9 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(const float *__restrict
 // it sums from the very registers that feed the products, and stores run along the keys.
 // (Two waves per SIMD at least, which prefetched pieces of 256 bytes and four row blocks would otherwise exceed by ten
 // registers: 8 heads x 8160 bf16 keys of 256 with 128 sources, key norms, whole call 93.6 us, 79.7 this way, 78.5 with
-// nothing prefetched; 96 sources 83.4, 69.3 and 72.3; 32 heads with 128 205, 164 and 176.)
+// nothing prefetched; 96 sources 83.4, 69.3 and 72.3; 32 heads with 128 205, 164 and 176.  The sources' norms, a thread each
+// while the others wait, one LDS read behind the other: edges of 8 heads x 4064 fp32 keys with 32 sources 11.5 us, four at a
+// time 9.9.)
 template <typename T, int NBR, int PB>
 __global__ __launch_bounds__(256, 2) void gemm_cosine_kernel(
     const T *__restrict__ Ac, const T *__restrict__ Kc, int d, int N, int P, int S, const int32_t *__restrict__ src,
@@ -422,9 +424,16 @@ __global__ __launch_bounds__(256, 2) void gemm_cosine_kernel(
             ask_keys(cn ? t0 : t0 + Sh::TK, cn);
             if (!whole) ask_sources(cn);
             const int steps = (min(row_bytes - c0, PB) + 31) / 32;
-            if (t0 == k0 && tid < Sh::TR)   // a thread per source (zeros behind the row's end)
-                for (int u = 0; u < 2 * steps; ++u)
-                    sq_src = sum_squares<T>(*reinterpret_cast<const uint4 *>(qt + tid * PITCH + 16 * u), sq_src);
+            if (t0 == k0 && tid < Sh::TR) {   // a thread per source (zeros behind the row's end), four reads at a time
+#pragma unroll
+                for (int u0 = 0; u0 < 2 * STEPS; u0 += 4) {
+                    uint4 x[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const uint4 *>(qt + tid * PITCH + 16 * (u0 + u));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sq_src = sum_squares<T>(x[u], sq_src);
+                }
+            }
             const unsigned char *kp = kt + (32 * stream + l32) * PITCH + 16 * hh;
             const unsigned char *qp = qt + (32 * rs * Sh::NBW + l32) * PITCH + 16 * hh;
 #pragma unroll
