@@ -1347,7 +1347,11 @@ __global__ __launch_bounds__(kWave * kOwnWaves) void bound_filter_kernel(
     bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, fa.key_stride, fa.rank, wv, lane,
                        [&](int row, float t) { tau_s[row] = t; });
     __syncthreads();
-    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, tid, [] {},
+    // (The thread's number, read anew: what the first half forms of it need not live through it; with three groups four
+    // registers would spill.)
+    int again = threadIdx.x;
+    asm volatile("" : "+v"(again));
+    filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, again, [] {},
                            [&](int r) { return tau_s[r]; });
 }
 
