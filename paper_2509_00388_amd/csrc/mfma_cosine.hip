@@ -36,6 +36,7 @@
 #include "kernels.hpp"
 #include "match.hpp"
 #include "mfma_tile.hpp"
+#include "reach.hpp"
 
 #include <math.h>
 
@@ -673,15 +674,7 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     bf16x8 q[SB][kSteps];
     sp.spread(smem, F.inv_s, tid, q);
     if (tid < ROWS) {
-        // det: what dot / |k_j| must reach for the edge to be listed, i.e. the source's bound,
-        // lowered by twice the slack, divided by 1/|k_i|.  Rows past the last source and
-        // impossible bounds never hit; a zero source (all edges 0) hits everywhere.
-        const int slot = s_base + tid;
-        const float t = tau_of(min(tid, Sh - 1 - s_base));
-        const float slack = 4e-6f + 1e-5f * fabsf(t);
-        const float inv = F.inv_s[tid];
-        const float lo2 = t - 2.f * slack;
-        const float det = slot >= Sh ? INFINITY : (inv > 0.f ? lo2 / inv : (lo2 <= 0.f ? -INFINITY : INFINITY));
+        const float det = dot_bound(tau_of(min(tid, Sh - 1 - s_base)), F.inv_s[tid], s_base + tid < Sh);
         F.det_s[tid] = det;
         // The matrix core's test lets through whatever the one with det does: det lowered by more than the error of
         // the two-piece product, a constant for products that underflow, everything where det is beyond all dots
@@ -713,25 +706,18 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
             const float4 *vals = reinterpret_cast<const float4 *>(row_mem);
             const float4 extra = vals[4];   // |k|^2, key, group
             const float inv_k = inv_norm(extra.x);   // the dense kernel's formula
-            const float norm_k = __builtin_amdgcn_sqrtf(extra.x);
+            const float norm_k = norm_for_test(__builtin_amdgcn_sqrtf(extra.x));
             const uint32_t key = __float_as_uint(extra.y);
             const int row0 = (__float_as_int(extra.z) & ~(kBlk - 1)) + 4 * hh;   // row of dot 0 (a multiple of 4)
-            // bit i of `hits` = (dot_i - det_i |k| is not negative), gathered from the sign bits, source 15 first;
-            // none unless one of them is a number that is not negative (not NaN: a key with an infinity)
-            uint32_t neg = 0;
-            float best = -INFINITY;
+            // bit i of `hits`: dot_i reaches what its source asks for
+            uint32_t misses = 0;
 #pragma unroll
             for (int v = 3; v >= 0; --v) {
                 const float4 dv = vals[v], tv = *reinterpret_cast<const float4 *>(&F.det_s[row0 + 8 * v]);
                 const float d4[4] = {dv.x, dv.y, dv.z, dv.w}, t4[4] = {tv.x, tv.y, tv.z, tv.w};
-#pragma unroll
-                for (int u = 3; u >= 0; --u) {
-                    const float d = fmaf(-t4[u], norm_k, d4[u]);
-                    best = fmaxf(best, d);
-                    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(d), 31);
-                }
+                misses = push_misses(misses, d4, t4, norm_k);
             }
-            uint32_t hits = best >= 0.f ? ~neg & 0xffffu : 0u;
+            uint32_t hits = ~misses & 0xffffu;
             // The row's first four hits without a branch, so that their LDS reads and list
             // positions are asked for together and waited for once: a hit that is not there
             // reads dot 0 and adds 0 to a counter nobody reads (one per lane).

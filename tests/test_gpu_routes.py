@@ -289,6 +289,41 @@ def test_filter_pass_row_groups_and_key_blocks(P, w, S, m, T, H):
         assert torch.equal(a.view(T, rep, *b.shape[1:]), b[:, None].expand(-1, rep, *[-1] * (b.dim() - 1)))
 
 
+# (row groups of 32 that sources fill in part: 1, 31 and 8 rows of the last one are no source's)
+@pytest.mark.parametrize("P,S,m,H", [(4200, 63, 8, 64), (4200, 33, 20, 64), (8191, 88, 4, 16)])
+def test_filter_pass_with_mostly_zero_keys(P, S, m, H):
+    """Edges to zero keys and of zero sources are 0, whichever route forms them, and ties go to the lowest index: heads
+    with little more than m keys that are not 0, with half of them 0, and beside a head with an infinite key (whose
+    lists have no agreed order, but stay its own)."""
+    say(f"mostly zero keys P={P} S={S} m={m} H={H}")
+    d, few, N = 128, 4, P + 2
+    assert H * S * P >= 1 << 23 > few * S * P
+    g = torch.Generator("cuda").manual_seed(P + S)
+    K = torch.randn(few, N, d, generator=g, device="cuda")
+    s = torch.rand(few, P, generator=g, device="cuda") + 0.1
+    K[0, : P - m - 20] = 0.0                     # the others lie behind the zero keys, which win the ties
+    s[0, P - m - 20:] += 1.0
+    K[1, torch.rand(N, generator=g, device="cuda") < 0.5] = 0.0
+    K[3, 1000] = torch.inf
+    K = K.to(torch.bfloat16)
+    rep = H // few
+    kw = dict(head_dim=d, n_tokens=N, window=2, n_sources=S, n_neighbors=m, rounds=1)
+
+    def run(heads, K, s):
+        p = gk.Params(n_kv_heads=heads, n_q_heads=heads, **kw)
+        dbg = [torch.full((heads, S, n) if n else (heads, S), -1, dtype=t, device="cuda")
+               for n, t in ((0, torch.int32), (m, torch.int32), (m, torch.float32))]
+        out = gk.graphkv_propagate(p, K, s.clone(), *dbg)
+        return (out, *dbg)
+
+    dense = run(few, K, s)
+    many = run(H, K.repeat(rep, 1, 1), s.repeat(rep, 1))
+    for a, b in zip(many, dense):
+        a = a.view(rep, *b.shape)[:, :3]
+        assert torch.equal(a, b[None, :3].expand_as(a))
+    assert 0 <= int(many[2].min()) and int(many[2].max()) < P
+
+
 @pytest.mark.parametrize("w,pool_mode,scorer", [(20, 0, 0), (32, 1, 0), (64, 0, 0), (8, 0, 1)])
 def test_calls_with_more_keys_than_the_caches_hold(w, pool_mode, scorer):
     """Batches beyond 256 MiB of keys read and write past the caches; their layers alone (8 MiB each) don't.  Scores that are cut
