@@ -386,7 +386,10 @@ template <int SB> struct SourcePieces {
 // vector instructions an edge and no LDS.  (Counted into a histogram, 32 lanes hit the thirty or so bins in which the
 // edges of one source lie, and the bound is only as fine as a bin.)
 constexpr int kGroups = 256;
-constexpr int kMaximaRank = 64;   // beyond it the maxima of 256 groups are too loose (15 % more edges reach the bound)
+// Ranks beyond it are counted: the 64th largest of 256 maxima has 15 % more edges above it, the 62nd largest of the 128
+// that parts of a sample leave 36 %.  (Counted or not, whole call of one round, us: rank 62, 128 values, 8 heads x 65504 keys
+// x 64 sources 160 / 137, 64 heads 432 / 351; rank 39 of 128, 8 heads x 131008 209 / 180.)
+constexpr int kMaximaRank = 64;
 template <int SB> constexpr int maxima_lds_bytes() { return SB * kBlk * kGroups * 4; }   // (more than the key blocks take)
 
 // A workgroup's source rows against n_cols >= 32 sampled keys (column c = row c * key_stride of Kh): vals [ROWS][kGroups]
@@ -1559,12 +1562,11 @@ int maxima_chunks(int Hkv, int P, int sgroups, int rank, bool late)
 {
     return late || rank > kMaximaRank ? 1 : min(bound_chunks(Hkv, P, sgroups), kParts / 2);
 }
-int values_per_chunk(int chunks)
-{
-    int n = kParts;
-    while (n * chunks > kParts) n /= 2;
-    return n;
-}
+// As many values a chunk as there is room for: 104 to 128 in all with the at most 32 chunks there are.  (Powers of two leave
+// 68 of 17 chunks, and the 62nd largest of those, for 240 neighbours among 65504 keys, lets 1278 keys through on
+// average and fills the longest list once in 60 rows, whose head is then redone: 15 heads with 64 sources 412 us.  119
+// values let 692 through, 1022 at most in 1500 rows, and 128 672.)
+int values_per_chunk(int chunks) { return kParts / chunks; }
 
 template <int SB>
 hipError_t launch_maxima(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int rank, const int32_t *src,

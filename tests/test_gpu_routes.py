@@ -324,6 +324,38 @@ def test_filter_pass_with_mostly_zero_keys(P, S, m, H):
     assert 0 <= int(many[2].min()) and int(many[2].max()) < P
 
 
+# (9, 17, 18 and 25 parts, whose maxima can't be 128 altogether; ranks 62 and 64 of them; one source group and two)
+@pytest.mark.parametrize("P,S,m,H", [(65000, 64, 240, 28), (65000, 64, 240, 15), (131008, 64, 490, 14), (65000, 100, 240, 5)])
+def test_bounds_from_uneven_parts_of_the_sample(P, S, m, H):
+    """Bounds taken from as many maxima as so many parts of the sample leave are as tight as a list needs, even of the
+    largest ranks: no head is redone.  Lists and scores are those of many heads, whose bounds come from the whole sample."""
+    say(f"uneven parts P={P} S={S} m={m} H={H}")
+    d, rep = 128, -(-130 // H)
+    g = torch.Generator("cuda").manual_seed(P + H)
+    K = torch.randn(H, P + 8, d, generator=g, device="cuda").to(torch.bfloat16)
+    s = torch.rand(H, P, generator=g, device="cuda") + 0.1
+    kw = dict(head_dim=d, n_tokens=P + 8, window=8, n_sources=S, n_neighbors=m, rounds=1)
+
+    def run(heads, K, s):
+        p = gk.Params(n_kv_heads=heads, n_q_heads=heads, **kw)
+        nbr = torch.full((heads, S, m), -1, dtype=torch.int32, device="cuda")
+        ws = gk.alloc_workspace(p, "cuda")
+        redo = np.inf
+        for _ in range(3):
+            gk.graphkv_profile_begin()
+            out = gk.graphkv_propagate(p, K, s.clone(), None, nbr, None, ws)
+            torch.cuda.synchronize()
+            redo = min(redo, 1e3 * gk.graphkv_profile_end()["redo_rows"][0])
+        return out, nbr, redo
+
+    out, nbr, redo = run(H, K, s)
+    say(f"  redo launch {redo:.1f} us")
+    assert redo < 50     # (6 where no head is flagged; a head takes 180 and more)
+    want, lists, _ = run(rep * H, K.repeat(rep, 1, 1), s.repeat(rep, 1))
+    assert torch.equal(lists.view(rep, H, S, m), nbr.expand(rep, -1, -1, -1))
+    assert torch.equal(want.view(rep, H, P), out.expand(rep, -1, -1))
+
+
 @pytest.mark.parametrize("w,pool_mode,scorer", [(20, 0, 0), (32, 1, 0), (64, 0, 0), (8, 0, 1)])
 def test_calls_with_more_keys_than_the_caches_hold(w, pool_mode, scorer):
     """Batches beyond 256 MiB of keys read and write past the caches; their layers alone (8 MiB each) don't.  Scores that are cut
