@@ -436,7 +436,7 @@ int32_t run_propagate(const graphkv_params *p, const Dims &D, const Workspace &W
                     }
                     // new sources without a kept list (usually none): bound and filter passes
                     // that return at once for heads that have none
-                    if (pick_match_applies(D.S) && late_filter_applies(D.H, D.P, D.m, g)) {
+                    if (pick_match_applies(D.S) && late_filter_applies(D.H, g)) {
                         GKV_LAUNCH(GRAPHKV_K_COSINE_BOUND_NEW,
                                    launch_late_filter(Ac, Kc, D.H, D.N, D.P, D.m, g, new_src, n_new, cand, cnt, ovf, st));
                     } else {

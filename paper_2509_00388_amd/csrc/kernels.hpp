@@ -227,7 +227,7 @@ hipError_t launch_nbr_select(const void *cand, const int32_t *cand_cnt, int32_t 
                              int Hkv, int m, const MfmaFilterPlan &g, const SelectRows *rows, int32_t *nbr,
                              float *nbr_e, hipStream_t st);
 // A later round's bound and filter passes in one launch, for few heads (overflow is not cleared).
-bool late_filter_applies(int Hkv, int P, int m, const MfmaFilterPlan &g);
+bool late_filter_applies(int Hkv, const MfmaFilterPlan &g);
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,
                               const int32_t *new_src, const int32_t *n_new, void *cand, int32_t *cand_cnt,
                               int32_t *overflow, hipStream_t st);

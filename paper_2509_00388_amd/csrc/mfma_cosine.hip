@@ -1313,8 +1313,9 @@ __global__ __launch_bounds__(256) void nbr_select_wave_kernel(const uint2 *__res
 // first round where a head is one workgroup (S rows, the head's flag is cleared here): a launch, the way of the sources
 // into the registers and the tail of a round of workgroups less.  In a later round (new sources only, n_src of
 // them) for few heads: nearly always no head has one, and then what counts is the launches; with some, the walk over
-// the sample is in front of every chunk's filter as long as each workgroup has a compute unit to itself.
-template <int SB, bool ONCE>
+// the sample is in front of every chunk's filter as long as each workgroup has a compute unit to itself.  COUNT: ranks
+// beyond kMaximaRank (later rounds only).
+template <int SB, bool ONCE, bool COUNT>
 __global__ __launch_bounds__(kWave * kOwnWaves) void bound_filter_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int S,
     const int32_t *__restrict__ src, int chunk_cols, FilterArgs fa, int sample_cols)
@@ -1330,11 +1331,21 @@ __global__ __launch_bounds__(kWave * kOwnWaves) void bound_filter_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t *src_h = src + (long)h * fa.src_pitch;
     if (!fa.n_src && tid == 0) fa.overflow[h] = 0;
-    sample_maxima<SB>(Ac + (long)h * N * kD, Kc + (long)h * N * kD, src_h, Sh, s_base, sample_cols, fa.key_stride, smem,
-                      F.inv_s, tid);
-    const float *vals = reinterpret_cast<const float *>(smem);
-    bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, fa.key_stride, fa.rank, wv, lane,
-                       [&](int row, float t) { tau_s[row] = t; });
+    const uint16_t *Ah = Ac + (long)h * N * kD, *Kh = Kc + (long)h * N * kD;
+    if constexpr (COUNT) {
+        constexpr int BINS = 256;
+        static_assert(256 * SB == kWave * kOwnWaves && 2 * kTileBytes + ROWS * BINS * 4 <= kFilterLdsBytes, "two tiles, the histograms");
+        __shared__ int32_t idx_s[ROWS];
+        uint32_t *hist = reinterpret_cast<uint32_t *>(smem + 2 * kTileBytes);
+        count_sample<SB, BINS>(Ah, Kh, src_h, Sh, s_base, 0, sample_cols, fa.key_stride, smem, hist, F.inv_s, idx_s, tid);
+        for (int r = wv; r < ROWS; r += kOwnWaves)
+            bound_from_histogram<BINS>(histogram_words<BINS>(&hist[r * BINS], lane), fa.rank, lane, &tau_s[r]);
+    } else {
+        sample_maxima<SB>(Ah, Kh, src_h, Sh, s_base, sample_cols, fa.key_stride, smem, F.inv_s, tid);
+        const float *vals = reinterpret_cast<const float *>(smem);
+        bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, fa.key_stride, fa.rank, wv, lane,
+                           [&](int row, float t) { tau_s[row] = t; });
+    }
     __syncthreads();
     // (The thread's number, read anew: what the first half forms of it need not live through it; with three groups four
     // registers would spill.)
@@ -1621,7 +1632,9 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
     const dim3 grid((late ? g.late_chunks : g.chunks) * sgroups, Hkv), block(kWave * kOwnWaves);
     const int cols = late ? g.late_cols : g.chunk_cols;
     if (with_bounds) {
-        auto *kernel = once ? bound_filter_kernel<SB, true> : bound_filter_kernel<SB, false>;
+        auto *kernel = once ? bound_filter_kernel<SB, true, false> : bound_filter_kernel<SB, false, false>;
+        if constexpr (SB == kSB)   // (a later round; in the first one ranks that are counted have a bound pass)
+            if (rank > kMaximaRank) kernel = once ? bound_filter_kernel<SB, true, true> : bound_filter_kernel<SB, false, true>;
         if (!allow_big_lds((const void *)kernel)) return hipGetLastError();
         hipLaunchKernelGGL(kernel, grid, block, kFilterLdsBytes, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, P, rows, src,
                            cols, fa, smp.cols);
@@ -1686,9 +1699,9 @@ hipError_t launch_match_sources(const MatchArgs &a, const int32_t *cur, int Hkv,
 // 236.7 / 233.0.  Many, from key norms: 16K keys, 64 sources, 128 workgroups 221.7 / 217.5; 128 sources, 256 277 / 274;
 // 192 sources, 384 372 / 418; 64K keys, 64 sources, 512 656 / 813.  The lists selected in the same launch, by the
 // workgroup that finishes last: 101.3 without new sources, but 326 and 773 with 64 and 192 and many of them new.)
-bool late_filter_applies(int Hkv, int P, int m, const MfmaFilterPlan &g)
+bool late_filter_applies(int Hkv, const MfmaFilterPlan &g)
 {
-    return mfma_bound_rank(m, sample_of(P).stride) <= kMaximaRank && (long)Hkv * g.late_chunks * ((g.S + kRows - 1) / kRows) <= 256;
+    return (long)Hkv * g.late_chunks * ((g.S + kRows - 1) / kRows) <= 256;
 }
 
 hipError_t launch_late_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, int m, const MfmaFilterPlan &g,

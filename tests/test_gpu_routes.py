@@ -356,6 +356,40 @@ def test_bounds_from_uneven_parts_of_the_sample(P, S, m, H):
     assert torch.equal(want.view(rep, H, P), out.expand(rep, -1, -1))
 
 
+# (ranks 64 and 65 of the sample: the last taken from maxima and the first counted; the largest of a long prompt; two source groups)
+@pytest.mark.parametrize("P,S,m,H,signal", [(16001, 40, 249, 8, 1), (16001, 40, 256, 8, 1), (16001, 70, 256, 4, 1), (131008, 33, 600, 2, 1)])
+def test_later_rounds_of_few_heads_take_bound_and_filter_in_one_launch(P, S, m, H, signal):
+    """Whatever the rank; with new sources in every round (an enhanced signal), each round against a one-round call of many
+    heads on the scores of the round before."""
+    say(f"later rounds P={P} S={S} m={m} H={H}")
+    d, T, rep = 128, 3, -(-130 // H)
+    g = torch.Generator("cuda").manual_seed(P + m)
+    cent = torch.randn(H, 64, d, generator=g, device="cuda")
+    kind = torch.randint(0, 64, (H, P + 8, 1), generator=g, device="cuda").expand(-1, -1, d)
+    K = (cent.gather(1, kind) + 0.5 * torch.randn(H, P + 8, d, generator=g, device="cuda")).to(torch.bfloat16)
+    s = torch.rand(H, P, generator=g, device="cuda") + 0.1
+
+    def run(heads, K, s, rounds):
+        p = gk.Params(n_kv_heads=heads, n_q_heads=heads, head_dim=d, n_tokens=P + 8, window=8, n_sources=S, n_neighbors=m,
+                      rounds=rounds, signal=signal)
+        dbg = [torch.full((rounds, heads, S, n) if n else (rounds, heads, S), -1, dtype=t, device="cuda")
+               for n, t in ((0, torch.int32), (m, torch.int32), (m, torch.float32))]
+        gk.graphkv_profile_begin()
+        out = gk.graphkv_propagate(p, K, s.clone(), *dbg)
+        torch.cuda.synchronize()
+        return gk.graphkv_profile_end(), out, *dbg
+
+    took, _, *few = run(H, K, s, T)
+    assert took["cosine_bound_new"][1] == T - 1 and "cosine_filter_new" not in took
+    many = K.repeat(rep, 1, 1)
+    for t in range(T):
+        _, out, *one = run(rep * H, many, s.repeat(rep, 1), 1)
+        for a, b in zip(one, few):
+            a = a.view(rep, *b[t].shape)
+            assert torch.equal(a, b[t][None].expand_as(a)), t
+        s = out[:H]
+
+
 @pytest.mark.parametrize("w,pool_mode,scorer", [(20, 0, 0), (32, 1, 0), (64, 0, 0), (8, 0, 1)])
 def test_calls_with_more_keys_than_the_caches_hold(w, pool_mode, scorer):
     """Batches beyond 256 MiB of keys read and write past the caches; their layers alone (8 MiB each) don't.  Scores that are cut
