@@ -48,8 +48,7 @@ constexpr int kSB = 2;            // source blocks of 32 per workgroup = row gro
 constexpr int kRows = kSB * kBlk; // source rows per workgroup
 constexpr int kThreads = 256 * kSB;
 
-// The per-row buffers (tau, cand, cand_cnt) hold `pitch` rows per head; the rows of one launch's
-// source list start at row `row0` of them.
+// The per-row buffers (tau, cand, cand_cnt) hold `pitch` rows per head, of which a launch's source list takes the first.
 struct FilterArgs {
     const int32_t *n_src;  // [Hkv] rows of the head's source list in use; null: all S
     const float *tau;      // [Hkv, pitch] the bound pass's value per row: edges below it are dropped
@@ -63,7 +62,7 @@ struct FilterArgs {
     int chunk_slots, slice_cap;
     int sgroups;           // workgroups (groups of source rows) per key chunk
     int src_pitch;         // entries per head of the source list
-    int pitch, row0;
+    int pitch;
 };
 
 // Both kernels below: a workgroup has 4 key streams (wave & 3) and 2 source row
@@ -275,7 +274,7 @@ template <int SB, int BINS>
 __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride,
     int S, int src_pitch, const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int m,
-    int chunk_cols, uint32_t *__restrict__ hist_part, float *__restrict__ tau, int pitch, int row0,
+    int chunk_cols, uint32_t *__restrict__ hist_part, float *__restrict__ tau, int pitch,
     int32_t *__restrict__ overflow)
 {
     constexpr int ROWS = SB * kBlk, NT = 256 * SB;
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
     for (int r = 0; r < 8; ++r) {
         const int row = wv * 8 + r;
         const uint4 w4 = histogram_words<BINS>(&hist[row * BINS], lane);
-        if (s_base + row < Sh) bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + row0 + s_base + row]);
+        if (s_base + row < Sh) bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + s_base + row]);
     }
 }
 
@@ -317,7 +316,7 @@ template <int SB, int BINS>
 __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__restrict__ hist_part,
                                                           int chunks, int sgroups, int S,
                                                           const int32_t *__restrict__ n_src, int m,
-                                                          float *__restrict__ tau, int pitch, int row0)
+                                                          float *__restrict__ tau, int pitch)
 {
     constexpr int ROWS = SB * kBlk;
     const int lane = threadIdx.x & 63;
@@ -335,7 +334,7 @@ __global__ __launch_bounds__(256) void bound_merge_kernel(const uint32_t *__rest
         for (int u = 0; u < 8; ++u)
             if (c0 + u < chunks) { w4.x += v[u].x; w4.y += v[u].y; w4.z += v[u].z; w4.w += v[u].w; }
     }
-    bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + row0 + slot]);
+    bound_from_histogram<BINS>(w4, m, lane, &tau[(long)h * pitch + slot]);
 }
 
 // The passes below that share nothing between waves: a wave holds all source rows of its workgroup (SB groups of 32) and
@@ -561,7 +560,7 @@ template <int SB>
 __global__ __launch_bounds__(kWave * kOwnWaves) void cosine_maxima_kernel(
     const uint16_t *__restrict__ Ac, const uint16_t *__restrict__ Kc, int N, int n_cols, int key_stride, int S, int src_pitch,
     const int32_t *__restrict__ src, const int32_t *__restrict__ n_src, int rank, int per_chunk,
-    float *__restrict__ part, float *__restrict__ tau, int pitch, int row0, int32_t *__restrict__ overflow)
+    float *__restrict__ part, float *__restrict__ tau, int pitch, int32_t *__restrict__ overflow)
 {
     constexpr int ROWS = SB * kBlk, NT = kWave * kOwnWaves;
     __shared__ float inv_s[ROWS];
@@ -591,7 +590,7 @@ __global__ __launch_bounds__(kWave * kOwnWaves) void cosine_maxima_kernel(
         }
         return;
     }
-    float *tau_h = tau + (long)h * pitch + row0 + s_base;
+    float *tau_h = tau + (long)h * pitch + s_base;
     bounds_from_maxima(vals, min(ROWS, Sh - s_base), src_h + s_base, key_stride, rank, wv, lane, [&](int row, float t) { tau_h[row] = t; });
 }
 
@@ -655,7 +654,7 @@ __device__ __forceinline__ void filter_chunk(const uint16_t *Ac, const uint16_t 
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hh = lane >> 5;
     const uint16_t *Kh = Kc + (long)h * N * kD;
     const int c0 = chunk * chunk_cols, c1 = min(n_cols, c0 + chunk_cols);
-    const long buf_row0 = (long)h * fa.pitch + fa.row0 + s_base;   // this workgroup's first row of the per-row buffers
+    const long buf_row0 = (long)h * fa.pitch + s_base;   // this workgroup's first row of the per-row buffers
     const int nblk = (c1 - c0 + kBlk - 1) / kBlk;
     const int groups = min(SB, (Sh - s_base + kBlk - 1) / kBlk);   // row groups with sources
 
@@ -861,7 +860,7 @@ __global__ __launch_bounds__(kWave * kOwnWaves) void cosine_filter_kernel(
                                     reinterpret_cast<uint32_t *>(smem), wv, lane, [&](int row, float t) { tau_s[row] = t; });
             __syncthreads();
         } else if (tid < ROWS && s_base + tid < Sh) {
-            tau_s[tid] = fa.tau[(long)h * fa.pitch + fa.row0 + s_base + tid];
+            tau_s[tid] = fa.tau[(long)h * fa.pitch + s_base + tid];
         }
     };
     filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, tid, take_bounds,
@@ -1581,8 +1580,8 @@ int values_per_chunk(int chunks) { return kParts / chunks; }
 
 template <int SB>
 hipError_t launch_maxima(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int rank, const int32_t *src,
-                         int src_pitch, const int32_t *n_src, bool late, void *part, float *tau, int pitch, int row0,
-                         int32_t *overflow, hipStream_t st)
+                         int src_pitch, const int32_t *n_src, bool late, void *part, float *tau, int pitch, int32_t *overflow,
+                         hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const Sample smp = sample_of(P);
@@ -1590,14 +1589,14 @@ hipError_t launch_maxima(const void *Ac, const void *Kc, int Hkv, int N, int P, 
     if (!allow_big_lds((const void *)cosine_maxima_kernel<SB>)) return hipGetLastError();
     hipLaunchKernelGGL(cosine_maxima_kernel<SB>, dim3(sgroups, Hkv, chunks), dim3(kWave * kOwnWaves), maxima_lds_bytes<SB>(), st,
                        (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols, smp.stride, rows, src_pitch, src, n_src, rank,
-                       values_per_chunk(chunks), (float *)part, tau, pitch, row0, overflow);
+                       values_per_chunk(chunks), (float *)part, tau, pitch, overflow);
     return hipGetLastError();
 }
 
 template <int SB, int BINS>
 hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, int rows, int m, const int32_t *src,
                         int src_pitch, const int32_t *n_src, bool late, void *hist_part, float *tau, int pitch,
-                        int row0, int32_t *overflow, hipStream_t st)
+                        int32_t *overflow, hipStream_t st)
 {
     constexpr int ROWS = SB * kBlk;
     const Sample smp = sample_of(P);
@@ -1606,15 +1605,15 @@ hipError_t launch_bound(const void *Ac, const void *Kc, int Hkv, int N, int P, i
     const int chunk_cols = (((smp.cols + chunks - 1) / chunks + kTileKeys - 1) / kTileKeys) * kTileKeys;
     const int rank = mfma_bound_rank(m, smp.stride);
     if (rank <= kMaximaRank)
-        return launch_maxima<SB>(Ac, Kc, Hkv, N, P, rows, rank, src, src_pitch, n_src, late, hist_part, tau, pitch, row0, overflow, st);
+        return launch_maxima<SB>(Ac, Kc, Hkv, N, P, rows, rank, src, src_pitch, n_src, late, hist_part, tau, pitch, overflow, st);
     if (!allow_big_lds((const void *)cosine_bound_kernel<SB, BINS>)) return hipGetLastError();
     hipLaunchKernelGGL((cosine_bound_kernel<SB, BINS>), dim3(sgroups, Hkv, chunks), dim3(256 * SB),
                        2 * kTileBytes + ROWS * BINS * 4, st, (const uint16_t *)Ac, (const uint16_t *)Kc, N, smp.cols,
-                       smp.stride, rows, src_pitch, src, n_src, rank, chunk_cols, (uint32_t *)hist_part, tau, pitch, row0,
+                       smp.stride, rows, src_pitch, src, n_src, rank, chunk_cols, (uint32_t *)hist_part, tau, pitch,
                        overflow);
     if (chunks > 1)
         hipLaunchKernelGGL((bound_merge_kernel<SB, BINS>), dim3((rows + 3) / 4, Hkv), dim3(256), 0, st,
-                           (const uint32_t *)hist_part, chunks, sgroups, rows, n_src, rank, tau, pitch, row0);
+                           (const uint32_t *)hist_part, chunks, sgroups, rows, n_src, rank, tau, pitch);
     return hipGetLastError();
 }
 
@@ -1627,7 +1626,7 @@ hipError_t launch_filter(const void *Ac, const void *Kc, int Hkv, int N, int P, 
     const Sample smp = sample_of(P);
     const int rank = mfma_bound_rank(m, smp.stride), parts = maxima_chunks(Hkv, P, sgroups, rank, late);
     FilterArgs fa{n_src, tau, parts > 1 ? (const float *)part : nullptr, rank, smp.stride, (uint2 *)cand, cand_cnt, overflow,
-                  g.row_slots, g.chunk_slots, late ? g.late_slice_cap : g.slice_cap, sgroups, src_pitch, g.pitch, 0};
+                  g.row_slots, g.chunk_slots, late ? g.late_slice_cap : g.slice_cap, sgroups, src_pitch, g.pitch};
     const bool once = sgroups == 1 && reads_past_caches((size_t)Hkv * N * kD * 2);
     const dim3 grid((late ? g.late_chunks : g.chunks) * sgroups, Hkv), block(kWave * kOwnWaves);
     const int cols = late ? g.late_cols : g.chunk_cols;
@@ -1670,8 +1669,8 @@ hipError_t launch_mfma_cosine_bound(const void *Ac, const void *Kc, int Hkv, int
 {
     if (first_round && g.sb == 3)
         return launch_bound<3, 224>(Ac, Kc, Hkv, N, P, g.S + g.X, m, src, g.S + g.X, n_src, false,
-                                    hist_part, tau, g.pitch, 0, overflow, st);
-    return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, hist_part, tau, g.pitch, 0,
+                                    hist_part, tau, g.pitch, overflow, st);
+    return launch_bound<2, 256>(Ac, Kc, Hkv, N, P, g.S, m, src, g.S, n_src, !first_round, hist_part, tau, g.pitch,
                                 overflow, st);
 }
 
