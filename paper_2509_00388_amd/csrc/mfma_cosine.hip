@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256 * SB) void cosine_bound_kernel(
         for (int u = tid; u < ROWS * BINS / 4; u += NT) out[u] = in[u];
         return;
     }
-    // Wave w scans the histograms of rows 8w .. 8w+7 from the top; lane L holds bins 8L .. 8L+7.
+    // Wave w scans the histograms of rows 8w .. 8w+7 from the top; lane L holds bins 4L .. 4L+3.
     for (int r = 0; r < 8; ++r) {
         const int row = wv * 8 + r;
         const uint4 w4 = histogram_words<BINS>(&hist[row * BINS], lane);
@@ -386,7 +386,7 @@ template <int SB> struct SourcePieces {
 // edges of one source lie, and the bound is only as fine as a bin.)
 constexpr int kGroups = 256;
 // Ranks beyond it are counted: the 64th largest of 256 maxima has 15 % more edges above it, the 62nd largest of the 128
-// that parts of a sample leave 36 %.  (Counted or not, whole call of one round, us: rank 62, 128 values, 8 heads x 65504 keys
+// that parts of a sample leave 37 %.  (Counted or not, whole call of one round, us: rank 62, 128 values, 8 heads x 65504 keys
 // x 64 sources 160 / 137, 64 heads 432 / 351; rank 39 of 128, 8 heads x 131008 209 / 180.)
 constexpr int kMaximaRank = 64;
 template <int SB> constexpr int maxima_lds_bytes() { return SB * kBlk * kGroups * 4; }   // (more than the key blocks take)
@@ -498,7 +498,7 @@ __device__ __forceinline__ void bounds_from_maxima(const float *vals, int n_rows
     }
 }
 
-// The same from kParts values a row in memory, where a chunk each of a short head's sample left some: all rows of a wave
+// The same from kParts places a row in memory, 104 to 128 of them values that the parts of a sample left: all rows of a wave
 // at once through histograms of 128 bins (hist: [kOwnWaves][PER][128] words of LDS), a pair of bins a lane, then four
 // halvings of the bin.  (Twelve halvings a row took 10 us of the filter pass, more than the launch that
 // added up the chunks' histograms before; bounds left at the lower edge of a bin let lists of keys that are alike
@@ -1346,8 +1346,8 @@ __global__ __launch_bounds__(kWave * kOwnWaves) void bound_filter_kernel(
                            [&](int row, float t) { tau_s[row] = t; });
     }
     __syncthreads();
-    // (The thread's number, read anew: what the first half forms of it need not live through it; with three groups four
-    // registers would spill.)
+    // (The thread's number, read anew: what the first half forms of it need not live through it; with three groups a few
+    // would spill.)
     int again = threadIdx.x;
     asm volatile("" : "+v"(again));
     filter_chunk<SB, ONCE>(Ac, Kc, N, n_cols, src, chunk_cols, fa, h, chunk, Sh, s_base, F, smem, again, [] {},
@@ -1429,7 +1429,9 @@ static Sample sample_of(int P)
 // 1 / stride: the rank is its mean plus six standard deviations (and one), at most m, so that
 // about one source in 10^7 comes out short -- which the select notices (fewer than m candidates)
 // and answers by redoing the head exactly, like an overflow.  About rank * stride keys lie above
-// the bound instead of m * stride: fewer rows to park, list and select from.
+// the rank-th sampled edge instead of m * stride: fewer rows to park, list and select from.  (Above the rank-th
+// largest of V groups' maxima lie -V ln(1 - rank / V) * stride: 5 % more at rank 26 of 256, 15 % at 64, 37 % at 62 of the 128
+// that parts of the sample leave, 55 % at the most, 64 of 104.)
 int mfma_bound_rank(int m, int stride)
 {
     if (stride <= 1) return m;
@@ -1440,8 +1442,8 @@ int mfma_bound_rank(int m, int stride)
 
 int mfma_cand_cap(int P, int m)
 {
-    // about four times the rank * stride keys expected above the bound (the bin that the bound is
-    // rounded down to adds up to a few hundred more at long prompts; here the stride is rounded down)
+    // about four times the rank * stride keys above the rank-th sampled edge (maxima of groups let up to 55 % more
+    // through, bins of a histogram a few hundred at long prompts; here the stride is rounded down)
     const int stride = P / mfma_sample_cols(P);
     long cap = 4L * mfma_bound_rank(m, stride) * stride;
     if (cap < 1024) cap = 1024;
@@ -1457,8 +1459,8 @@ int mfma_cand_cap(int P, int m)
 bool mfma_filter_applies(int P, int m, long rows)
 {
     // The sample must hold far more than m keys for its m-th largest edge to be a
-    // useful bound, the key index must fit the 24 bits of a staged candidate, and
-    // the select kernel's LDS must hold a full list.
+    // useful bound, a head's rows must lie within the 32-bit byte offsets of the tile
+    // loads, and the select kernel's LDS must hold a full list.
     if (P < 2048 || P >= (1 << 24)) return false;
     if (P < 8192 && rows * P < (8L << 20)) return false;
     if (m > mfma_sample_cols(P) / 8) return false;

@@ -889,7 +889,7 @@ def test_full_size_batched_c3(oracle):
 
 
 def test_million_token_prompt(oracle):
-    """A prompt of 2^20 + 77 tokens on one head (32-bit offsets, 24-bit key numbers in the candidate
+    """A prompt of 2^20 + 77 tokens on one head (32-bit offsets, key numbers beyond 20 bits in the candidate
     lists, the streaming top-k, key chunks of 8192 sampled keys): the whole pass against the oracle.
     (A 4 M-token run of the same script agrees as well; it takes half a minute, mostly the oracle.)"""
     cfg = synth.scaled(synth.CONFIGS["c2"], n_tokens=(1 << 20) + 77, window=32, n_kv_heads=1, n_q_heads=1,
